@@ -19,9 +19,9 @@
 // shift).  Which eight contraction indices a lane feeds to a given matrix instruction is
 // the same for A and for B, which is all the sum needs.
 //
-// Two kernels share this plan: k_gemm (any K that is a multiple of 32; the workgroup stages
-// chunks through registers into shared LDS buffers, one barrier per chunk) and k_gemm_dma
-// (K a multiple of 128; every wave fills its own LDS with asynchronous global -> LDS copies
+// Two kernels share this plan: k_gemm (the workgroup stages chunks through registers into
+// shared LDS buffers, one barrier per chunk; only for K > 2^24, beyond the others' 32-bit
+// offsets) and k_gemm_dma (K a multiple of 128; every wave fills its own LDS with asynchronous global -> LDS copies
 // and never meets a barrier).
 #include <hip/hip_runtime.h>
 
@@ -475,6 +475,299 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm_dma(
 }
 
 // ----------------------------------------------------------------------------------------
+// k_gemm_tile: C in tiles of any of several shapes (TileShape), for the many products whose
+// 256 x 256 tiles would leave most compute units idle, and for every K that is not a multiple of
+// 128.  A workgroup has SM x SN waves over its tile of C, each holding WM x WN instruction tiles
+// (32 x 32), in KS copies that share the contraction axis: copy kg takes HPW pieces of 64 steps of
+// every chunk, and the copies' partial tiles are added through LDS at the end, always in the same
+// order.  Splitting the contraction axis inside the workgroup is what fills the chip when C is
+// small, without a second pass or a place for partial sums.
+//
+// What bounds it.  A wave of 2 x 2 instruction tiles issues 8 vector instructions (the
+// expansion, 4 cycles each) per matrix instruction (32 cycles): both pipes are equally busy and
+// must run at once, which takes several waves per SIMD (the bare loop, no memory accesses: 206
+// cycles per 4 matrix instructions with one wave per SIMD, 188 with two, 142 with four; the
+// matrix pipe alone 128).  So the small tiles keep to 128 registers and 40 KiB of LDS per four
+// waves.  Waves of 4 x 2 expand less per matrix instruction (6 vector instructions) and hold 256
+// registers; they pay only where their larger tiles fill the chip.
+//
+// Chunks arrive by asynchronous global -> LDS copies, all waves of the workgroup together: codes
+// 16 bytes and scale pairs 2 bytes per lane (a pair lands as one 32-bit word), which asks nothing
+// of the alignment of scale lines, so K may be any multiple of 32.  Past the end of K a copy
+// re-reads the row's last unit and the reader takes its scales as zero (those products are +-0).
+// Unit u of LDS row r sits at position u ^ swz(r), so that the 16 (codes) or 64 (pairs) lanes
+// of one LDS access pass hit all banks.  One barrier per chunk: it comes after the wait for the
+// own copies of the chunk, so behind it the chunk is complete and the stage of the chunk before is
+// free for the next copies.  K <= 2^24 (32-bit lane offsets).
+template <int WM_, int WN_, int SM_, int SN_, int KS_, int HPW_, int NST_>
+struct TileShape {
+  static constexpr int WM = WM_, WN = WN_, SM = SM_, SN = SN_, KS = KS_, HPW = HPW_, NST = NST_;
+  static constexpr int kWaves = SM * SN * KS, kThreads = 64 * kWaves;
+  static constexpr int BM = 32 * WM * SM, BN = 32 * WN * SN, ROWS = BM + BN;
+  static constexpr int CK = 64 * KS * HPW;                // contraction steps per chunk
+  static constexpr int U = CK / 32;                       // 16-byte units of codes (= scale pairs) per row
+  static constexpr int kCopies = ROWS * U / 64;           // copy instructions per chunk, codes (and scales)
+  static constexpr int NC = (kCopies + kWaves - 1) / kWaves;
+  static constexpr uint32_t kScaleBase = ROWS * U * 16, STAGE = ROWS * U * 20;
+  static constexpr int T = WM + WN, kTiles = WM * WN;
+  // partial sums of the KS groups: each owns kOwn instruction tiles, exchanged in PH phases
+  static constexpr int kOwn = KS == 1 ? kTiles : kTiles >= KS ? kTiles / KS : 1;
+  static constexpr int kPartialTile = (KS - 1) * SM * SN * 4096;
+  static constexpr int kPerPhaseMax = KS == 1 ? kTiles : 160 * 1024 / kPartialTile;
+  static constexpr int PER = kPerPhaseMax < kTiles ? kPerPhaseMax : kTiles;
+  static constexpr int LDS_STAGES = NST * STAGE, LDS_PART = KS == 1 ? 0 : PER * kPartialTile;
+  static constexpr int LDS = LDS_STAGES > LDS_PART ? LDS_STAGES : LDS_PART;
+  static_assert(ROWS * U % 64 == 0 && BM % (64 / U) == 0 && U <= 16, "a copy instruction stays within one operand");
+  static_assert(LDS <= 160 * 1024, "the stages must fit the LDS");
+  static_assert(kTiles % KS == 0 || KS % kTiles == 0, "whole tiles per owner");
+  static_assert((NST - 1) * 2 * NC < 63, "vmcnt counts to 63");
+};
+// as NV_DMA16, two bytes per lane, each into a 32-bit word of LDS
+#define NV_DMA2(lds_sgpr, voff, gbase)                                                        \
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_ushort %1, %2"                           \
+               :: "s"(lds_sgpr), "v"(voff), "s"(gbase) : "memory", "m0")
+
+template <typename S, bool KFULL, bool OUTF32>
+__global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 : 4) void k_gemm_tile(
+    const uint8_t *__restrict__ codes_a, const uint8_t *__restrict__ scales_a,
+    const float *__restrict__ alpha_a, const uint8_t *__restrict__ codes_b,
+    const uint8_t *__restrict__ scales_b, const float *__restrict__ alpha_b,
+    void *__restrict__ out, int64_t M, int64_t N, uint32_t K, uint32_t tiles_m, uint32_t tiles_n,
+    uint32_t sha, uint32_t shb) {
+  constexpr int WM = S::WM, WN = S::WN, KS = S::KS, HPW = S::HPW, NST = S::NST, U = S::U, T = S::T;
+  typedef uint32_t v4 __attribute__((ext_vector_type(4)));
+  extern __shared__ __align__(16) uint8_t lds_raw[];
+  const uint32_t t = threadIdx.x, lane = t & 63u;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const uint32_t r = lane & 31u, g = lane >> 5;
+  const uint32_t kg = wave / (S::SM * S::SN), spatial = wave % (S::SM * S::SN);
+  const uint32_t wm = spatial / S::SN, wn = spatial % S::SN;
+
+  // Workgroups go to the eight dies in turn; consecutive tiles (row by row of C) stay on one die
+  // so that its L2 holds the operand rows they share.
+  const uint32_t tiles = tiles_m * tiles_n, xcd = blockIdx.x & 7u, seq = blockIdx.x >> 3;
+  const uint32_t per = tiles >> 3, extra = tiles & 7u;
+  const uint32_t tile = xcd * per + (xcd < extra ? xcd : extra) + seq;
+  const uint32_t tile_m = tile / tiles_n, tile_n = tile - tile_m * tiles_n;
+  const int64_t m0 = (int64_t)tile_m * S::BM, n0 = (int64_t)tile_n * S::BN;
+  const uint32_t row_codes = K / 2, row_scales = K / 16;
+  const uint32_t rows_a = (uint32_t)(M - m0 < S::BM ? M - m0 : S::BM);     // rows the tile really has
+  const uint32_t rows_b = (uint32_t)(N - n0 < S::BN ? N - n0 : S::BN);
+  const float scale = alpha_a[0] * alpha_b[0];
+
+  auto uniform = [](const uint8_t *p) {
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);
+  };
+  const uint8_t *gca = uniform(codes_a + m0 * row_codes), *gcb = uniform(codes_b + n0 * row_codes);
+  const uint8_t *gsa = uniform(scales_a + (m0 >> sha) * row_scales);
+  const uint8_t *gsb = uniform(scales_b + (n0 >> shb) * row_scales);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds_raw;
+
+  // 16 / U rows of codes, and 64 / U rows of pairs, fill the 256 bytes of all banks once
+  auto swz_c = [](uint32_t row) { return (row / (16 / U)) & (U - 1u); };
+  auto swz_s = [](uint32_t row) { return ((row / (64 / U)) << 1) & (U - 1u); };
+  // copy instruction i moves the 64 / U LDS rows from i * 64 / U on; wave w issues i = w, w +
+  // kWaves, ... (the last one again where they do not divide evenly: same bytes, same place).
+  // A row past the end of its operand re-reads the last one (its products are never stored).
+  uint32_t off_c[S::NC], off_s[S::NC];                    // the lane's byte offsets at chunk 0
+#pragma unroll
+  for (int n = 0; n < S::NC; ++n) {
+    uint32_t i = wave + n * S::kWaves;
+    if (S::kCopies % S::kWaves != 0 && i >= (uint32_t)S::kCopies) i = S::kCopies - 1;
+    const uint32_t row = i * (64 / U) + lane / U, pos = lane % U;
+    const bool is_a = i * (64 / U) < (uint32_t)S::BM;
+    const uint32_t line = row - (is_a ? 0u : (uint32_t)S::BM), last = (is_a ? rows_a : rows_b) - 1;
+    const uint32_t l = line < last ? line : last;
+    off_c[n] = l * row_codes + (pos ^ swz_c(row)) * 16;
+    off_s[n] = (l >> (is_a ? sha : shb)) * row_scales + (pos ^ swz_s(row)) * 2;
+  }
+  auto copy_chunk = [&](uint32_t c, uint32_t stage) {
+    const uint32_t lds = lds0 + stage * S::STAGE;
+    const uint32_t k0 = c * S::CK;
+#pragma unroll
+    for (int n = 0; n < S::NC; ++n) {
+      uint32_t i = wave + n * S::kWaves;
+      if (S::kCopies % S::kWaves != 0 && i >= (uint32_t)S::kCopies) i = S::kCopies - 1;
+      const bool is_a = i * (64 / U) < (uint32_t)S::BM;
+      const uint8_t *bc = (is_a ? gca : gcb) + k0 / 2, *bs = (is_a ? gsa : gsb) + k0 / 16;
+      uint32_t oc = off_c[n], os = off_s[n];
+      if constexpr (!KFULL) {
+        // units past the end of K: the row's last one instead
+        const uint32_t row = i * (64 / U) + lane / U, pos = lane % U;
+        const uint32_t uc = pos ^ swz_c(row), us = pos ^ swz_s(row);
+        if (k0 + uc * 32 >= K) oc -= (k0 + uc * 32 - (K - 32)) / 2;
+        if (k0 + us * 32 >= K) os -= (k0 + us * 32 - (K - 32)) / 16;
+      }
+      NV_DMA16(lds + i * 1024, oc, bc);
+      NV_DMA2(lds + S::kScaleBase + i * 256, os, bs);
+    }
+  };
+
+  // a lane's share of one piece: 32 codes and their two scales per operand tile (WM of A, WN of B)
+  struct Raw {
+    v4 c[T];
+    uint32_t s[T];
+  };
+  const uint32_t row_a = wm * (32 * WM) + r, row_b = S::BM + wn * (32 * WN) + r;
+  auto read_piece = [&](uint32_t c, uint32_t stage, uint32_t h, Raw &x) {
+    const uint32_t u = 2 * (kg * HPW + h) + g;
+    const uint8_t *st = lds_raw + stage * S::STAGE;
+#pragma unroll
+    for (int i = 0; i < T; ++i) {
+      const uint32_t row = i < WM ? row_a + 32 * i : row_b + 32 * (i - WM);
+      x.c[i] = *reinterpret_cast<const v4 *>(st + row * (U * 16) + (u ^ swz_c(r)) * 16);
+      x.s[i] = *reinterpret_cast<const uint32_t *>(st + S::kScaleBase + row * (U * 4) + (u ^ swz_s(r)) * 4);
+    }
+    if constexpr (!KFULL) {
+      const uint32_t keep = c * S::CK + u * 32 < K ? 0xffffffffu : 0u;
+#pragma unroll
+      for (int i = 0; i < T; ++i) x.s[i] &= keep;
+    }
+  };
+  auto expand_one = [&](Raw &x, int s, int i) {
+    if (s == 0) x.s[i] = __builtin_amdgcn_perm(0u, x.s[i], 0x0c010c00u) << 7;
+    const h2 pair = __builtin_bit_cast(h2, x.s[i]);
+    return expand8(x.c[i][s], s < 2 ? pair.x : pair.y);
+  };
+
+  f32x16 acc[WM][WN];
+#pragma unroll
+  for (int i = 0; i < WM; ++i)
+#pragma unroll
+    for (int j = 0; j < WN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+
+  const uint32_t nchunks = (K + S::CK - 1) / S::CK;
+  auto clamp_chunk = [&](uint32_t c) { return c < nchunks ? c : nchunks - 1; };
+  if constexpr (S::kTiles <= 4) {
+    // four waves per SIMD hide each other's LDS reads and expansions: plain order, few registers
+#pragma unroll
+    for (int p = 0; p < NST - 1; ++p) copy_chunk(clamp_chunk(p), p);
+    uint32_t stage = 0, freed = NST - 1;
+    for (uint32_t c = 0; c < nchunks; ++c) {
+      // chunk c is complete, and nobody reads the stage of chunk c - 1 any more
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((NST - 2) * 2 * S::NC) : "memory");
+      copy_chunk(clamp_chunk(c + NST - 1), freed);
+#pragma unroll
+      for (int h = 0; h < HPW; ++h) {
+        Raw x;
+        read_piece(c, stage, h, x);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          h8 f[T];
+#pragma unroll
+          for (int i = 0; i < T; ++i) f[i] = expand_one(x, s, i);
+#pragma unroll
+          for (int i = 0; i < WM; ++i)
+#pragma unroll
+            for (int j = 0; j < WN; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f[i], f[WM + j], acc[i][j], 0, 0, 0);
+        }
+      }
+      freed = stage;
+      stage = stage + 1 == (uint32_t)NST ? 0u : stage + 1;
+    }
+  } else {
+#pragma unroll
+    for (int p = 0; p < NST; ++p) copy_chunk(clamp_chunk(p), p);
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((NST - 1) * 2 * S::NC) : "memory");
+    // two waves per SIMD: a software pipeline over steps of 16 contraction indices, the next step's
+    // operands expanded in the shadow of this step's matrix instructions
+    Raw x, xn;
+    h8 f[2][T];
+    read_piece(0, 0, 0, x);
+#pragma unroll
+    for (int i = 0; i < T; ++i) f[0][i] = expand_one(x, 0, i);
+
+    uint32_t stage = 0;
+    for (uint32_t c = 0; c < nchunks; ++c) {
+      const uint32_t nxt = stage + 1 == (uint32_t)NST ? 0u : stage + 1;
+#pragma unroll
+      for (int h = 0; h < HPW; ++h) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const bool sync = s == 2 && h == HPW - 1;
+          if (s == 1 && h < HPW - 1) read_piece(c, stage, h + 1, xn);
+          if (sync) {
+            // every wave's reads of this stage are done and chunk c + 1 is complete
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((NST - 2) * 2 * S::NC) : "memory");
+            read_piece(clamp_chunk(c + 1), nxt, 0, xn);
+            copy_chunk(clamp_chunk(c + NST), stage);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          Raw &src = s == 3 ? xn : x;
+#pragma unroll
+          for (int i = 0; i < T; ++i) f[(s + 1) & 1][i] = expand_one(src, (s + 1) & 3, i);
+          if (s == 3) x = xn;
+#pragma unroll
+          for (int i = 0; i < WM; ++i)
+#pragma unroll
+            for (int j = 0; j < WN; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f[s & 1][i], f[s & 1][WM + j], acc[i][j], 0, 0, 0);
+          constexpr int kV = (8 * T + S::kTiles - 1) / S::kTiles + 1;
+#pragma unroll
+          for (int q = 0; q < S::kTiles; ++q) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, kV, 0);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      stage = nxt;
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");       // nothing may still be writing LDS
+
+  if constexpr (KS > 1) {
+    typedef float Part[KS - 1][S::SM * S::SN][16][64];
+    Part *part = reinterpret_cast<Part *>(lds_raw);
+#pragma unroll
+    for (int e0 = 0; e0 < S::kTiles; e0 += S::PER) {
+      if (e0 > 0) __syncthreads();
+#pragma unroll
+      for (int e = e0; e < e0 + S::PER && e < S::kTiles; ++e) {
+        const uint32_t owner = e / S::kOwn;
+        if (owner != kg) {
+          const uint32_t slot = kg - (kg > owner ? 1u : 0u);
+#pragma unroll
+          for (int v = 0; v < 16; ++v) part[e - e0][slot][spatial][v][lane] = acc[e / WN][e % WN][v];
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int e = e0; e < e0 + S::PER && e < S::kTiles; ++e)
+        if ((uint32_t)(e / S::kOwn) == kg) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v)
+#pragma unroll
+            for (int w = 0; w < KS - 1; ++w) acc[e / WN][e % WN][v] += part[e - e0][w][spatial][v][lane];
+        }
+    }
+  }
+
+#pragma unroll
+  for (int e = 0; e < S::kTiles; ++e) {
+    if (KS > 1 && (uint32_t)(e / S::kOwn) != kg) continue;
+    const uint32_t col = wn * (32 * WN) + 32 * (e % WN) + r;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const uint32_t row = wm * (32 * WM) + 32 * (e / WN) + 8 * (v / 4) + 4 * g + (v % 4);
+      if (row < rows_a && col < rows_b) {
+        const float c = acc[e / WN][e % WN][v] * scale;
+        if (OUTF32)
+          static_cast<float *>(out)[(m0 + row) * N + n0 + col] = c;
+        else
+          static_cast<uint16_t *>(out)[(m0 + row) * N + n0 + col] = (uint16_t)pack_bf16x2(c, 0.0f);
+      }
+    }
+  }
+}
+
+// ----------------------------------------------------------------------------------------
 // Few rows of A (a small batch of activations against a weight matrix; the entry point says
 // how few).  The product
 // is then bound by reading B once from HBM -- which is where four-bit operands pay on this
@@ -493,16 +786,16 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm_dma(
 // A there is room for two such pieces per wave and the copy of the chunk after next runs
 // while a chunk is multiplied; otherwise the next chunk's copy overlaps this chunk's
 // arithmetic and the other waves' work.
-// MT = number of 32-row tiles of A (1, 2 or 4).  K must be a multiple of 256 and <= 2^24.
+// MT = number of 32-row tiles of A (1 or 2).  K must be a multiple of 256 and <= 2^24.
 constexpr int SK = 256;          // contraction indices per chunk
-// Waves per workgroup and staging pieces per wave, for 1, 2 and 4 tiles of A.  Four waves were
+// Waves per workgroup and staging pieces per wave, for 1 and 2 tiles of A.  Four waves were
 // fastest on every weight shape timed (8192 x 8192, 28672 x 8192, 8192 x 28672, 4096 x 4096;
 // 2 to 10 waves and 1 to 4 pieces were tried): with one tile of A the workgroup then needs
 // 72 KiB of LDS and two of them share a compute unit, so one's start and end overlap the
 // other's stream.
-constexpr int kSkinnyShape[3][2] = {{4, 2}, {4, 1}, {4, 1}};
-constexpr int skinny_waves(int mt) { return kSkinnyShape[mt == 1 ? 0 : mt == 2 ? 1 : 2][0]; }
-constexpr int skinny_stages(int mt) { return kSkinnyShape[mt == 1 ? 0 : mt == 2 ? 1 : 2][1]; }
+constexpr int kSkinnyShape[2][2] = {{4, 2}, {4, 1}};
+constexpr int skinny_waves(int mt) { return kSkinnyShape[mt - 1][0]; }
+constexpr int skinny_stages(int mt) { return kSkinnyShape[mt - 1][1]; }
 constexpr uint32_t skinny_rows(int mt) { return 32u + 32u * mt; }        // B rows, then A rows
 constexpr uint32_t skinny_scale_rows(int mt) { return (skinny_rows(mt) + 63u) / 64u * 64u; }
 constexpr uint32_t skinny_stage_bytes(int mt) {
@@ -514,16 +807,15 @@ constexpr size_t skinny_lds_bytes(int mt) {
   return stages > partials ? stages : partials;
 }
 
-static_assert(skinny_lds_bytes(1) <= 160 * 1024 && skinny_lds_bytes(2) <= 160 * 1024 &&
-              skinny_lds_bytes(4) <= 160 * 1024, "the stages must fit the LDS");
+static_assert(skinny_lds_bytes(1) <= 160 * 1024 && skinny_lds_bytes(2) <= 160 * 1024,
+              "the stages must fit the LDS");
 
 template <int MT, bool OUTF32>
 __global__ __launch_bounds__(64 * skinny_waves(MT)) void k_gemm_skinny(
     const uint8_t *__restrict__ codes_a, const uint8_t *__restrict__ scales_a,
     const float *__restrict__ alpha_a, const uint8_t *__restrict__ codes_b,
     const uint8_t *__restrict__ scales_b, const float *__restrict__ alpha_b,
-    void *__restrict__ out, int64_t M, int64_t N, int64_t K, uint32_t sha, uint32_t shb,
-    uint32_t slabs) {
+    void *__restrict__ out, int64_t M, int64_t N, int64_t K, uint32_t sha, uint32_t shb) {
   constexpr int W = skinny_waves(MT), NST = skinny_stages(MT);
   constexpr uint32_t ROWS = skinny_rows(MT), STAGE = skinny_stage_bytes(MT);
   constexpr int NC = ROWS / 8, NS = skinny_scale_rows(MT) / 64;   // copy instructions per chunk
@@ -531,18 +823,8 @@ __global__ __launch_bounds__(64 * skinny_waves(MT)) void k_gemm_skinny(
   const uint32_t t = threadIdx.x, lane = t & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const uint32_t r = lane & 31u, g = lane >> 5;
-  // More than 32 MT rows of A are handled in slabs of 32 MT rows, each by a workgroup of its own.
-  // Workgroups go to the chip's eight dies in turn and each die has its own L2, so the slabs
-  // of one 32-column strip are consecutive workgroups of one die: B is fetched into one L2.
-  const uint32_t xcd = blockIdx.x & 7u, seq = blockIdx.x >> 3;
-  const uint32_t slab = seq % slabs, strip = (seq / slabs) * 8 + xcd;
-  const int64_t n0 = (int64_t)strip * 32;
-  if (n0 >= N) return;                                   // padding of the grid to whole turns
+  const int64_t n0 = (int64_t)blockIdx.x * 32;
   const int64_t row_codes = K / 2, row_scales = K / 16;
-  const int64_t m0 = (int64_t)slab * (32 * MT);
-  codes_a += m0 * row_codes;
-  scales_a += (m0 >> sha) * row_scales;
-  M -= m0;                                               // rows left from this slab's first on
   const uint8_t *wl = lds_raw + wave * (NST * STAGE);
   const uint32_t lds_wave = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds_raw +
                             wave * (NST * STAGE);
@@ -685,9 +967,9 @@ __global__ __launch_bounds__(64 * skinny_waves(MT)) void k_gemm_skinny(
         if (row < M && col < N) {
           const float cval = sum * scale;
           if (OUTF32)
-            static_cast<float *>(out)[(m0 + row) * N + col] = cval;
+            static_cast<float *>(out)[row * N + col] = cval;
           else
-            static_cast<uint16_t *>(out)[(m0 + row) * N + col] = (uint16_t)pack_bf16x2(cval, 0.0f);
+            static_cast<uint16_t *>(out)[row * N + col] = (uint16_t)pack_bf16x2(cval, 0.0f);
         }
       }
   }
@@ -865,7 +1147,8 @@ static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 // The kernels compile side by side when this file is built in parts: NVFP4_46_GEMM_PART =
 // 1..4 hold one instantiation of the staged kernel each (by far the slowest to compile),
-// 5 the copy-based kernel, 6 the small-batch kernel, 0 the entry point; without the macro
+// 5 the copy-based kernel, 6 the small-batch kernels and the kernel for smaller tiles, 0 the entry
+// point; without the macro
 // the file is one self-contained translation unit.
 #ifndef NVFP4_46_GEMM_PART
 #define NVFP4_46_GEMM_PART (-1)
@@ -884,12 +1167,14 @@ struct GemmArgs {
   hipStream_t stream;
 };
 
-// Every run_* raises the kernel's dynamic LDS limit (all three need more than the 64 KiB a
+// Every run_* raises the kernel's dynamic LDS limit (most need more than the 64 KiB a
 // kernel gets without asking), launches, and returns a status of the C ABI.
 template <bool KFULL, bool OUTF32>
 int run_gemm_staged(const GemmArgs &a);
 int run_gemm_dma(const GemmArgs &a);
 int run_gemm_skinny(const GemmArgs &a);
+template <typename S>
+int run_gemm_tile(const GemmArgs &a);
 
 template <typename Kernel, typename... Args>
 static int launch_with_lds(Kernel kernel, dim3 grid, dim3 block, size_t lds_bytes, hipStream_t s,
@@ -940,12 +1225,9 @@ int run_gemm_dma(const GemmArgs &a) {
 // Few rows of A: one workgroup per 32 columns of C, bound by streaming B.
 int run_gemm_skinny(const GemmArgs &a) {
   auto go = [&](auto kernel, int mt) {
-    const int64_t slabs = (a.M + 32 * mt - 1) / (32 * mt), strips = (a.N + 31) / 32;
-    const int64_t grid = (strips + 7) / 8 * 8 * slabs;      // whole turns over the eight dies
-    return launch_with_lds(kernel, dim3((uint32_t)grid), dim3(64 * skinny_waves(mt)),
+    return launch_with_lds(kernel, dim3((uint32_t)((a.N + 31) / 32)), dim3(64 * skinny_waves(mt)),
                            skinny_lds_bytes(mt), a.stream, a.codes_a, a.scales_a, a.alpha_a,
-                           a.codes_b, a.scales_b, a.alpha_b, a.out, a.M, a.N, a.K, a.sha, a.shb,
-                           (uint32_t)slabs);
+                           a.codes_b, a.scales_b, a.alpha_b, a.out, a.M, a.N, a.K, a.sha, a.shb);
   };
   if (a.M <= 16) {
     auto go16 = [&](auto kernel) {
@@ -956,9 +1238,48 @@ int run_gemm_skinny(const GemmArgs &a) {
     return a.f32 ? go16(k_gemm_skinny16<true>) : go16(k_gemm_skinny16<false>);
   }
   if (a.M <= 32) return a.f32 ? go(k_gemm_skinny<1, true>, 1) : go(k_gemm_skinny<1, false>, 1);
-  if (a.M <= 64) return a.f32 ? go(k_gemm_skinny<2, true>, 2) : go(k_gemm_skinny<2, false>, 2);
-  return a.f32 ? go(k_gemm_skinny<4, true>, 4) : go(k_gemm_skinny<4, false>, 4);
+  return a.f32 ? go(k_gemm_skinny<2, true>, 2) : go(k_gemm_skinny<2, false>, 2);
 }
+#endif
+
+// The shapes of k_gemm_tile that are in use.  (Timed against these: 64 x 64 with three stages, 128
+// x 64 and 128 x 128 in two copies, 32 x 64, 32 x 32 in four copies, 256 x 256.)
+using Tile32 = TileShape<1, 1, 1, 1, 8, 1, 2>;         // 32 x 32, 8 waves, each an eighth of K
+using Tile64x32 = TileShape<2, 1, 1, 1, 4, 1, 2>;      // 64 x 32, 4 waves
+using Tile64 = TileShape<2, 2, 1, 1, 4, 1, 2>;         // 64 x 64, 4 waves; four workgroups per CU
+using Tile128 = TileShape<2, 2, 2, 2, 4, 1, 2>;        // 128 x 128, 16 waves
+using Tile256x128 = TileShape<4, 2, 2, 2, 2, 1, 4>;    // 256 x 128, 8 waves
+
+template <typename S>
+static int64_t tiles_of(const GemmArgs &a) {
+  return ((a.M + S::BM - 1) / S::BM) * ((a.N + S::BN - 1) / S::BN);
+}
+
+#if NVFP4_46_GEMM_HAS(6)
+template <typename S>
+int run_gemm_tile(const GemmArgs &a) {
+  auto go = [&](auto kernel) {
+    return launch_with_lds(kernel, dim3((uint32_t)tiles_of<S>(a)), dim3(S::kThreads), S::LDS,
+                           a.stream, a.codes_a, a.scales_a, a.alpha_a, a.codes_b, a.scales_b,
+                           a.alpha_b, a.out, a.M, a.N, (uint32_t)a.K,
+                           (uint32_t)((a.M + S::BM - 1) / S::BM),
+                           (uint32_t)((a.N + S::BN - 1) / S::BN), a.sha, a.shb);
+  };
+  if (a.K % S::CK == 0) return a.f32 ? go(k_gemm_tile<S, true, true>) : go(k_gemm_tile<S, true, false>);
+  return a.f32 ? go(k_gemm_tile<S, false, true>) : go(k_gemm_tile<S, false, false>);
+}
+#endif
+#if NVFP4_46_GEMM_PART == 0
+#define NVFP4_46_TILE(S) extern template int run_gemm_tile<S>(const GemmArgs &);
+#elif NVFP4_46_GEMM_PART == 6
+#define NVFP4_46_TILE(S) template int run_gemm_tile<S>(const GemmArgs &);
+#endif
+#ifdef NVFP4_46_TILE
+NVFP4_46_TILE(Tile32)
+NVFP4_46_TILE(Tile64x32)
+NVFP4_46_TILE(Tile64)
+NVFP4_46_TILE(Tile128)
+NVFP4_46_TILE(Tile256x128)
 #endif
 
 }  // namespace nvfp4_46
@@ -994,17 +1315,38 @@ extern "C" int nvfp4_46_gemm(const void *codes_a, const void *scales_a, const fl
                    (flags & NVFP4_GEMM_B_TILE_SCALES) ? 4u : 0u, out_dtype == NVFP4_OUT_F32,
                    static_cast<hipStream_t>(stream)};
   const bool offsets_fit = K <= ((int64_t)1 << 24);     // 32-bit lane offsets of the copies
-  // The kernel that streams B takes up to 128 rows of A at its best and, in slabs of 128 rows,
-  // up to 512 as long as the 128 x 128 tiles of the other kernels would not even fill the
-  // chip's 256 compute units once (timed on 8192 x 8192, 28672 x 8192, 8192 x 28672 and
-  // 4096 x 4096 weights: with fewer tiles than that, those kernels wait on HBM chunk by chunk).
-  const bool few_rows = M <= 128 || (M <= 512 && tiles_m * tiles_n <= 256);
-  if (few_rows && (K % SK) == 0 && offsets_fit) return run_gemm_skinny(a);
-  // K a multiple of 128: the variant with asynchronous global -> LDS copies
-  if ((K % GK) == 0 && offsets_fit) return run_gemm_dma(a);
-  if ((K % GK) == 0)
-    return a.f32 ? run_gemm_staged<true, true>(a) : run_gemm_staged<true, false>(a);
-  return a.f32 ? run_gemm_staged<false, true>(a) : run_gemm_staged<false, false>(a);
+  if (!offsets_fit)
+    return (K % GK) == 0
+               ? (a.f32 ? run_gemm_staged<true, true>(a) : run_gemm_staged<true, false>(a))
+               : (a.f32 ? run_gemm_staged<false, true>(a) : run_gemm_staged<false, false>(a));
+
+  // Which kernel: times in us, BF16 out, back to back on one card, M x N x K.
+  //
+  // Few rows of A against a large weight: the kernels that stream B, one workgroup per 32 columns.
+  // Up to 32 rows always (16 x 8192 x 8192: 9.5, in 32 x 32 tiles 12.1; 32 x 8192 x 28672: 27.8 /
+  // 34.4); from 33 to 64 rows only between the widths whose 32 x 32 tiles are at most one
+  // per compute unit (64 x 4096 x 4096: 10.2, tiles 7.6) and those that fill the chip in 64 x 64
+  // tiles (64 x 28672 x 8192: 49.7, tiles 37.7; between them 64 x 8192 x 8192: 16.8 / 17.9).
+  constexpr int64_t kCus = 256;
+  const int64_t t32 = tiles_of<Tile32>(a), t64 = tiles_of<Tile64>(a);
+  if ((K % SK) == 0 && (M <= 32 || (M <= 64 && t32 > kCus && t64 <= kCus))) return run_gemm_skinny(a);
+
+  // The largest tiles (the fewest expansions and copies per product) whose last turn over the chip
+  // leaves little of it idle.  256 x 256 tiles of the copy-based kernel from 62 % (2816 x 4096 x
+  // 4096, 176 tiles: 96, in 64 x 64 tiles 111; but 4352 x 4096 x 2048, 272 tiles: 106 / 90);
+  // 256 x 128 tiles from 80 % (2048 x 4096 x 4096: 80 in 256 x 256, 65; 2048 x 3072 x 4096, 75 %:
+  // 59, in 64 x 64 tiles 55); 128 x 128 from 87 % (1000 x 4096 x 4096: 76 in 256 x 256, 35, in
+  // 64 x 64 38; 2048 x 3072 x 4096, 75 %: 63).
+  auto fill = [&](int64_t tiles) { return (double)tiles / (double)((tiles + kCus - 1) / kCus * kCus); };
+  if ((K % GK) == 0 && fill(tiles_m * tiles_n) >= 0.62) return run_gemm_dma(a);
+  if (fill(tiles_of<Tile256x128>(a)) >= 0.8) return run_gemm_tile<Tile256x128>(a);
+  if (fill(tiles_of<Tile128>(a)) >= 0.87) return run_gemm_tile<Tile128>(a);
+  // Small products: the smallest tiles that are at most one per compute unit (64 x 1024 x 4096:
+  // 7.6 in 32 x 32, 9.9 in 64 x 32, 13.0 in 64 x 64; 128 x 4096 x 4096: 11.4 / 10.6 / 13.1; 200 x
+  // 4096 x 4096: 18.8 / 15.1 / 13.9); 32 rows or columns would leave larger tiles half empty.
+  if (M <= 32 || t32 <= kCus) return run_gemm_tile<Tile32>(a);
+  if (N <= 32 || tiles_of<Tile64x32>(a) <= kCus) return run_gemm_tile<Tile64x32>(a);
+  return run_gemm_tile<Tile64>(a);
 }
 
 #endif

@@ -134,6 +134,55 @@ def test_small_batch_gemm_is_exact_when_every_partial_sum_is_representable(M):
     assert np.array_equal(got.cpu().numpy().astype(np.float64), c_ref)
 
 
+# Every tile shape of the kernel for smaller tiles (the dispatch picks it by the sizes), at the
+# edges of tiles and of the chunks of the contraction axis (512, 256 and 128 indices), with K
+# whole and ragged; the operands in `tiled` carry one scale line per 16 rows.
+TILE_SHAPES = [
+    # 32 x 32
+    (1, 1, 32, ""), (31, 33, 64, ""), (32, 64, 512, "ab"), (33, 32, 544, "b"), (250, 997, 1056, ""),
+    (7, 9001, 4128, ""),
+    # 64 x 32
+    (304, 848, 96, "ab"), (301, 833, 256, ""), (320, 831, 288, "a"), (2111, 31, 992, ""),
+    # 64 x 64
+    (701, 799, 32, ""), (705, 769, 512, ""), (704, 784, 800, "ab"),
+    # 128 x 128
+    (1901, 1920, 288, "b"), (1793, 1921, 256, ""),
+    # 256 x 128
+    (2049, 2945, 96, ""), (2304, 2944, 128, "b"), (2064, 2931, 416, "a")]
+
+
+@pytest.mark.parametrize("M,N,K,tiled", TILE_SHAPES)
+def test_tile_shapes_are_exact_when_every_partial_sum_is_representable(M, N, K, tiled):
+    """Scales 0.5 .. 4 as above: every product is a multiple of 1/8 of magnitude at most 288, so
+    all sums over K <= 4128 are exact in fp32 (2^21 / 2^-3 = 2^24) in any order and the result is
+    the oracle's bit for bit."""
+    _log(f"gemm tile case M={M} N={N} K={K} tiled={tiled!r}")
+    rng = np.random.default_rng(M * 7919 + N * 31 + K)
+    ca = rng.integers(0, 256, (M, K // 2), dtype=np.uint8)
+    cb = rng.integers(0, 256, (N, K // 2), dtype=np.uint8)
+    la, lb = (M // 16 if "a" in tiled else M), (N // 16 if "b" in tiled else N)
+    sa = rng.choice(np.array([0x30, 0x38, 0x40], np.uint8), (la, K // 16))
+    sb = rng.choice(np.array([0x38, 0x40, 0x48], np.uint8), (lb, K // 16))
+    flags = (B.GEMM_A_TILE_SCALES if "a" in tiled else 0) | (B.GEMM_B_TILE_SCALES if "b" in tiled else 0)
+    got = B.nvfp4_46_gemm(_dev(ca), _dev(sa), _alpha(1.0), _dev(cb), _dev(sb), _alpha(1.0),
+                          out_dtype=B.OUT_F32, flags=flags)
+    # (the products of decoded values; float64 sums of multiples of 1/8 below 2^21 are exact too)
+    grid = np.array([0, .5, 1, 1.5, 2, 3, 4, 6, 0, -.5, -1, -1.5, -2, -3, -4, -6])
+    value = {0x30: 0.5, 0x38: 1.0, 0x40: 2.0, 0x48: 4.0}
+
+    def decoded(codes, scales, lines):
+        v = np.stack((grid[codes & 15], grid[codes >> 4]), axis=-1).reshape(codes.shape[0], -1)
+        s = np.repeat(np.vectorize(value.get)(scales), 16, axis=1)
+        return v * (np.repeat(s, 16, axis=0) if lines != codes.shape[0] else s)
+
+    want = decoded(ca, sa, la) @ decoded(cb, sb, lb).T
+    assert np.abs(want).max() < 2.0 ** 21
+    assert np.array_equal(got.cpu().numpy().astype(np.float64), want)
+    got16 = B.nvfp4_46_gemm(_dev(ca), _dev(sa), _alpha(1.0), _dev(cb), _dev(sb), _alpha(1.0),
+                            out_dtype=B.OUT_BF16, flags=flags)
+    assert torch.equal(got16.cpu(), torch.from_numpy(want.astype(np.float32)).to(torch.bfloat16))
+
+
 def test_small_batch_gemm_with_tile_scaled_operands():
     """Sixteen rows of A and a B operand, both quantized in 16x16 tiles (one scale line per
     16 rows), through the 16-row kernel; and the same B against 32 rows of A."""
