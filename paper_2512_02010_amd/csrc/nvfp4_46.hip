@@ -50,6 +50,18 @@ constexpr int kFlatShortRoundsPerCu = 16;  // ... and rounds left to one-round w
 constexpr int kFlatAmaxWgPerCu = 2;     // k_flat as the amax pass of the Hadamard transform
 constexpr int kAmaxRhtColWgPerCu = 8;   // k_amax_rht_col
 
+// The pass for the tensor scale reads x just before the quantizing pass, both usually first to
+// last.  A tensor larger than what the 256 MB memory-side cache holds of it has then always just
+// lost the part that is read next; read last to first, the quantizing pass finds most of a
+// cacheful.  Scale + quantize, forwards / backwards: fp32 8192 x 8192 into both packings of 16x16
+// tiles 130 / 111 us, rowwise 97 / 93, both orientations 122 / 114; BF16 16384 x 8192 columnwise
+// 121 / 112, rowwise 110 / 104.  Below the line everything is found either way (BF16 8192 x 8192:
+// 16x16 tiles 70 / 71, both orientations 81 / 82), so small tensors keep their order.
+constexpr int64_t kLastLevelBytes = (int64_t)192 << 20;
+constexpr uint32_t runs_backwards(int64_t elements, bool xf32) {
+  return elements * (xf32 ? 4 : 2) > kLastLevelBytes;
+}
+
 // Streaming accesses.  Dequantized BF16 tensors are write-once streams and leave with
 // nontemporal stores (dequantize 45 -> 28 us per 8192 x 8192, and their write-back no
 // longer competes with the next kernel).  Codes, scales and choice bytes use ordinary
@@ -316,7 +328,7 @@ __global__ __launch_bounds__(kThreads) void k_flat(
     const uint4 *__restrict__ x, const float *__restrict__ alpha_p, uint2 *__restrict__ codes,
     uint8_t *__restrict__ scales, uint8_t *__restrict__ choice, uint4 *__restrict__ out_bf16,
     uint32_t *amax_bits, int64_t nblocks, uint32_t nb_per_row, uint64_t sr_seed,
-    uint64_t rht_seed, uint32_t n_long, uint32_t rounds_long, AmaxFinish fin) {
+    uint64_t rht_seed, uint32_t n_long, uint32_t rounds_long, uint32_t backwards, AmaxFinish fin) {
   __shared__ ScaleTable tab;
   // fake-quant only: a wave's 2 KiB of output is turned round in LDS so that each of its
   // two store instructions writes 1 KiB of whole cache lines (streaming stores of half
@@ -448,14 +460,17 @@ __global__ __launch_bounds__(kThreads) void k_flat(
     step = gridDim.x - n_long;
     end = rounds;
   }
+  // turn t of the deal above works on round t, or on the t-th from the end (kLastLevelBytes)
+  auto place = [&](uint32_t t) { return OUT != kOutAmax && backwards ? rounds - 1u - t : t; };
   auto fetch = [&](uint32_t next, Raw &raw) {
-    const uint32_t rr = next < end ? next : 0u;
+    const uint32_t rr = place(next < end ? next : 0u);
     const uint32_t last = lanes_in_round(rr) - 1;
     const uint32_t lane = tid < last ? tid : last;
     const uint4 *xb = x + Raw::kPieces * ((int64_t)rr * kThreads);
     load_block<XF32>(xb + Raw::kPieces * lane, raw);
   };
-  auto run = [&](uint32_t r, const Raw &raw) {
+  auto run = [&](uint32_t turn, const Raw &raw) {
+    const uint32_t r = place(turn);
     const uint32_t live = lanes_in_round(r);
     if (OUT == kOutFake || tid < live) work(r, live, raw);
   };
@@ -527,13 +542,15 @@ struct TileCoord {
 // top to bottom, merged only the columnwise lines: 66.6 -> 58.6 us for both orientations of
 // 8192 x 8192.)
 struct TileMap {
-  uint32_t sx, sy;   // super-tile width and height in tiles
+  uint32_t sx, sy;      // super-tile width and height in tiles
+  uint32_t backwards;   // take the tiles last to first (see kLastLevelBytes)
 };
 
 NV_DEV TileCoord tile_of_workgroup(int64_t rows, int64_t cols, TileMap m) {
   const uint32_t nt_r = (uint32_t)((rows + TR - 1) / TR), nt_c = (uint32_t)((cols + TC - 1) / TC);
   const uint32_t per = m.sx * m.sy, nsx = (nt_c + m.sx - 1) / m.sx;
-  const uint32_t xcd = blockIdx.x & 7u, slot = blockIdx.x >> 3;
+  const uint32_t id = m.backwards ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
+  const uint32_t xcd = id & 7u, slot = id >> 3;
   const uint32_t round = slot / per, within = slot - round * per;
   const uint32_t S = round * 8u + xcd;                      // super-tile, row-major
   const uint32_t sy = S / nsx, sx = S - sy * nsx;
@@ -848,7 +865,7 @@ __global__ __launch_bounds__(kThreads) void k_block2d(
     const void *__restrict__ x_any, const float *__restrict__ alpha_p, uint8_t *__restrict__ codes,
     uint8_t *__restrict__ scales, uint8_t *__restrict__ choice, uint8_t *__restrict__ codes_col,
     uint8_t *__restrict__ scales_col, uint8_t *__restrict__ choice_col,
-    uint16_t *__restrict__ out_bf16, int64_t rows, int64_t cols, uint64_t sr_seed) {
+    uint16_t *__restrict__ out_bf16, int64_t rows, int64_t cols, uint64_t sr_seed, uint32_t backwards) {
   __shared__ ScaleTable tab;
   const ScaleConsts sc = build_scale_table(tab, *alpha_p);
   const uint32_t tid = threadIdx.x, r_in_tile = tid & 15u, grp = tid >> 4;
@@ -982,7 +999,8 @@ __global__ __launch_bounds__(kThreads) void k_block2d(
                           pack_bf16x2(D1[4], D1[5]), pack_bf16x2(D1[6], D1[7]));
     }
   };
-  for (uint32_t id = blockIdx.x; id < n_ids; id += gridDim.x) {
+  for (uint32_t turn = blockIdx.x; turn < n_ids; turn += gridDim.x) {
+    const uint32_t id = backwards ? n_ids - 1u - turn : turn;
     // by units: the same for the whole workgroup
     const uint32_t slot = id >> 3, unit = (((slot >> 2) << 3) + (id & 7u)) * 4u + (slot & 3u);
     const uint32_t mr = unit / ncq, cq = unit - mr * ncq;
@@ -1171,7 +1189,8 @@ static int launch_flat(const FlatArgs &a) {
   }
   return launch(k_flat<XF32, ROUNDING, SELECT, RHT, OUT>, dim3((uint32_t)grid), dim3(kThreads),
                 a.stream, a.x, a.alpha, a.codes, a.scales, a.choice, a.out, a.amax, a.nblocks,
-                a.nb_per_row, a.sr_seed, a.rht_seed, (uint32_t)n_long, (uint32_t)rounds_long, a.fin);
+                a.nb_per_row, a.sr_seed, a.rht_seed, (uint32_t)n_long, (uint32_t)rounds_long,
+                runs_backwards(a.nblocks * 16, XF32), a.fin);
 }
 
 template <bool XF32, int ROUNDING, int SELECT>
@@ -1207,9 +1226,9 @@ struct TileArgs {
 
 // Super-tiles of 8 x 16 tiles, smaller along an axis that has fewer tiles (a small tensor
 // would otherwise launch mostly workgroups without a tile).
-static TileMap tile_map(int64_t rows, int64_t cols) {
+static TileMap tile_map(int64_t rows, int64_t cols, uint32_t backwards = 0) {
   const int64_t nt_r = (rows + TR - 1) / TR, nt_c = (cols + TC - 1) / TC;
-  return TileMap{(uint32_t)(nt_c < 8 ? nt_c : 8), (uint32_t)(nt_r < 16 ? nt_r : 16)};
+  return TileMap{(uint32_t)(nt_c < 8 ? nt_c : 8), (uint32_t)(nt_r < 16 ? nt_r : 16), backwards};
 }
 
 // Whole turns over the eight XCDs, each turn one super-tile per XCD.
@@ -1225,7 +1244,8 @@ static int launch_tile(const TileArgs &a) {
   return launch(k_tile<XF32, ROUNDING, SELECT, RHT, WANT_ROW, OUT>, dim3(tile_grid(a.rows, a.cols)),
                 dim3(kThreads), a.stream, a.x, a.alpha, a.codes_row, a.scales_row, a.choice_row,
                 a.codes_col, a.scales_col, a.choice_col, a.out, a.rows, a.cols, a.sr_seed,
-                a.rht_seed, tile_map(a.rows, a.cols));
+                a.rht_seed,
+                tile_map(a.rows, a.cols, runs_backwards(a.rows * a.cols, XF32)));
 }
 
 // variant: 0 = columnwise codes, 1 = columnwise codes + rht, 2 = both orientations,
@@ -1273,7 +1293,7 @@ static int launch_block2d(const Block2dArgs &a, int out) {
   auto go = [&](auto kernel) {
     return launch(kernel, dim3(grid), dim3(kThreads), a.stream, a.x, a.alpha, a.codes, a.scales,
                   a.choice, a.codes_col, a.scales_col, a.choice_col, a.out, a.rows, a.cols,
-                  a.sr_seed);
+                  a.sr_seed, runs_backwards(a.rows * a.cols, XF32));
   };
   if (out == kOutCodes && a.codes_col) return go(k_block2d<XF32, ROUNDING, SELECT, kOutCodes, true>);
   if (out == kOutCodes) return go(k_block2d<XF32, ROUNDING, SELECT, kOutCodes, false>);

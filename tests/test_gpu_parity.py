@@ -694,6 +694,30 @@ def test_workload_c5_full_rht_sr():
     check_case(wl.make("c5"), rounding=B.SR, rht=1, tag="c5-full")
 
 
+@pytest.mark.parametrize("kw", [dict(layout=B.ROWWISE), dict(layout=B.ROWWISE, rht=1, rht_seed=9),
+                                dict(layout=B.COLWISE), dict(layout=B.BOTH),
+                                dict(layout=B.ROWWISE, block2d=1), dict(layout=B.BOTH, block2d=1)],
+                         ids=lambda kw: "-".join(f"{k}{v}" for k, v in kw.items()))
+def test_tensors_that_are_read_last_to_first(kw):
+    """More than 192 MiB of x: the quantizing kernels take their work from the end.  Slabs of the same
+    tensor (whole 16-row blocks, read first to last) must give the same bytes.  Rowwise the last
+    of the rounds of 256 blocks holds a single block; tiles are ragged both ways."""
+    rows, cols, slab = (3073, 16400, 769) if kw["layout"] == B.ROWWISE and not kw.get("block2d") else (3088, 16400, 784)
+    x = torch.randn(rows, cols, device="cuda", generator=torch.Generator("cuda").manual_seed(46))
+    assert x.numel() * 4 > 192 << 20 and slab * cols * 4 < 192 << 20
+    alpha = B.nvfp4_46_tensor_scale(x)
+    big = B.nvfp4_46_quantize(x, alpha, **kw)
+    parts = [B.nvfp4_46_quantize(x[r:r + slab], alpha, **kw) for r in range(0, rows, slab)]
+    for name, v in big.items():
+        if v is not None:
+            want = torch.cat([p[name] for p in parts], dim=0 if name.endswith("row") else 1)
+            assert torch.equal(v, want), name
+    if kw["layout"] != B.BOTH and not kw.get("rht"):
+        fq = B.nvfp4_46_fake_quant(x, alpha, **kw)
+        want = torch.cat([B.nvfp4_46_fake_quant(x[r:r + slab], alpha, **kw) for r in range(0, rows, slab)])
+        assert torch.equal(fq.view(torch.int16), want.view(torch.int16))
+
+
 @pytest.mark.parametrize("dtype,rows,cols", [(torch.bfloat16, 8192, 8192), (torch.float32, 4096, 6152),
                                              (torch.bfloat16, 16, 8), (torch.float32, 48, 8)])
 def test_tensor_scale_of_hadamard_transformed_columns_at_size(dtype, rows, cols):
