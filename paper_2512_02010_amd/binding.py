@@ -129,15 +129,17 @@ def _ptr(t):
     if t is None:
         return None
     if isinstance(t, int):
-        return C.c_void_p(t)
+        return t
     assert t.is_cuda and t.is_contiguous(), "tensors must be contiguous device tensors"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream(stream):
+    # The current stream's handle itself: building torch.cuda.current_stream()'s object costs 2.7 us
+    # of the 10 to 13 us a call of this module took, its handle 0.2 us (a launch: 3.3 us).
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _check(rc: int, where: str):
