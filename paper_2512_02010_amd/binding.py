@@ -76,6 +76,8 @@ def lib() -> C.CDLL:
         L.nvfp4_46_tensor_scale_static.argtypes = [vp, pp, vp, vp]
         L.nvfp4_46_quantize.restype = C.c_int
         L.nvfp4_46_quantize.argtypes = [vp, pp, vp, vp, vp, vp, vp, vp, vp, vp]
+        L.nvfp4_46_scale_quantize.restype = C.c_int
+        L.nvfp4_46_scale_quantize.argtypes = [vp, pp, vp, vp, C.c_size_t, vp, vp, vp, vp, vp, vp, vp]
         L.nvfp4_46_dequantize.restype = C.c_int
         L.nvfp4_46_dequantize.argtypes = [vp, vp, vp, i64, i64, u32, vp, vp]
         L.nvfp4_46_fake_quant.restype = C.c_int
@@ -270,6 +272,26 @@ def nvfp4_46_quantize(x: torch.Tensor, alpha: torch.Tensor, layout: int = ROWWIS
     _check(quantize_raw(x, p, alpha, o["codes_row"], o["scales_row"], o["codes_col"],
                         o["scales_col"], o["choice_row"], o["choice_col"], stream),
            "nvfp4_46_quantize")
+    return o
+
+
+def nvfp4_46_scale_quantize(x: torch.Tensor, workspace: torch.Tensor | None = None,
+                            layout: int = ROWWISE, rounding: int = RTN, select: int = SEL_46_MSE,
+                            rht: int = 0, sr_seed: int = 0, rht_seed: int = 0,
+                            fp8_max: float = 256.0, want_choice: bool = True, stream=None,
+                            block2d: int = 0) -> dict:
+    """nvfp4_46_tensor_scale(_ws) and nvfp4_46_quantize in one call; the scale comes as "alpha"."""
+    rows, cols = _shape_of(x)
+    alpha = _new((1,), torch.float32, x.device)
+    o = alloc_outputs(rows, cols, layout, x.device, want_choice, block2d)
+    p = make_params(rows, cols, layout, rounding, select, rht, sr_seed, rht_seed, fp8_max,
+                    block2d, x_dtype_of(x))
+    _check(lib().nvfp4_46_scale_quantize(
+        _ptr(x), C.byref(p), _ptr(alpha), _ptr(workspace),
+        workspace.numel() if workspace is not None else 0, _ptr(o["codes_row"]),
+        _ptr(o["scales_row"]), _ptr(o["codes_col"]), _ptr(o["scales_col"]), _ptr(o["choice_row"]),
+        _ptr(o["choice_col"]), _stream(stream)), "nvfp4_46_scale_quantize")
+    o["alpha"] = alpha
     return o
 
 

@@ -22,6 +22,7 @@
 #include "block.hpp"
 #include "launch.hpp"
 #include "nvfp4_46.h"
+#include "nvfp4_46_fused.h"
 
 // The quantizing kernels exist once per (input type, rounding mode, selection rule, ...):
 // several hundred instantiations.  To compile them side by side this file can be built in
@@ -37,7 +38,7 @@
 namespace nvfp4_46 {
 
 constexpr int kThreads = 256;
-enum : int { kOutCodes = 0, kOutFake = 1, kOutAmax = 2 };
+enum : int { kOutCodes = 0, kOutFake = 1, kOutAmax = 2, kOutScaleAndCodes = 3 };
 
 // Launch shapes (workgroups per compute unit; every kernel strides over its input).  Each
 // value is the fastest of a timed sweep on 8192 x 8192 tensors.
@@ -224,14 +225,12 @@ __global__ void k_finish_alpha(float *alpha, float fp8_max) { *alpha = alpha_of(
 
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
-// max|x| without the transform: compare magnitudes as integers (15 bits of a BF16 value, 31
-// of an fp32 value).  Several independent 128-bit loads per lane are in flight at a time.
+// Largest magnitude, compared as integers (15 bits of a BF16 value, 31 of an fp32 value).
 template <bool XF32>
-__global__ __launch_bounds__(kThreads) void k_amax_plain(const uint4 *__restrict__ x, int64_t n16,
-                                                         uint32_t *amax_bits, AmaxFinish fin) {
+struct PlainAmax {
   u16x2 acc = {0, 0};
   uint32_t acc32 = 0;
-  auto fold = [&](const uint4 &w) {
+  NV_DEV void fold(const uint4 &w) {
     const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -243,7 +242,17 @@ __global__ __launch_bounds__(kThreads) void k_amax_plain(const uint4 *__restrict
         acc = __builtin_elementwise_max(acc, *reinterpret_cast<u16x2 *>(&m));
       }
     }
-  };
+  }
+  NV_DEV float value() const {
+    return u2f(XF32 ? acc32 : (uint32_t)(acc.x > acc.y ? acc.x : acc.y) << 16);
+  }
+};
+
+// max|x| without the transform.  Several independent 128-bit loads per lane are in flight at a time.
+template <bool XF32>
+__global__ __launch_bounds__(kThreads) void k_amax_plain(const uint4 *__restrict__ x, int64_t n16,
+                                                         uint32_t *amax_bits, AmaxFinish fin) {
+  PlainAmax<XF32> m;
   constexpr int U = kAmaxUnroll;
   const int64_t stride = (int64_t)gridDim.x * kThreads;
   int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
@@ -252,12 +261,57 @@ __global__ __launch_bounds__(kThreads) void k_amax_plain(const uint4 *__restrict
 #pragma unroll
     for (int j = 0; j < U; ++j) w[j] = load_stream(x + i + j * stride);
 #pragma unroll
-    for (int j = 0; j < U; ++j) fold(w[j]);
+    for (int j = 0; j < U; ++j) m.fold(w[j]);
   }
-  for (; i < n16; i += stride) fold(load_stream(x + i));
-  const uint32_t top = XF32 ? acc32 : (uint32_t)(acc.x > acc.y ? acc.x : acc.y) << 16;
-  publish_amax(u2f(top), amax_bits, fin);
+  for (; i < n16; i += stride) m.fold(load_stream(x + i));
+  publish_amax(m.value(), amax_bits, fin);
 }
+
+// A small tensor, one workgroup for all of it: nothing has to be agreed on between workgroups, so
+// no scratch words, no atomics and no launches before and after.  Sixteen waves with eight
+// loads each in flight take what one compute unit can (256 KiB in 3.3 us); kOneWgBytes says
+// where that ends.
+constexpr int kSmallThreads = 1024;
+template <bool XF32>
+NV_DEV float small_tensor_alpha(const uint4 *__restrict__ x, uint32_t n16, float fp8_max) {
+  __shared__ float wave_part[kSmallThreads / 64];
+  PlainAmax<XF32> acc;
+  constexpr int U = 8;
+  uint32_t i = threadIdx.x;
+  for (; i + (U - 1) * kSmallThreads < n16; i += U * kSmallThreads) {
+    uint4 w[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) w[j] = load_stream(x + i + j * kSmallThreads);
+#pragma unroll
+    for (int j = 0; j < U; ++j) acc.fold(w[j]);
+  }
+  if (i < n16) {
+    // the rest, still with all its loads in flight; past the end the lane's first piece again
+    uint4 w[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const uint32_t k = i + j * kSmallThreads;
+      w[j] = load_stream(x + (k < n16 ? k : i));
+    }
+#pragma unroll
+    for (int j = 0; j < U; ++j) acc.fold(w[j]);
+  }
+  float m = wave_max(acc.value());
+  if ((threadIdx.x & 63) == 0) wave_part[threadIdx.x >> 6] = m;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kSmallThreads / 64; ++w) m = fmaxf(m, wave_part[w]);
+  return alpha_of(m, fp8_max);
+}
+
+#if NVFP4_46_MAIN
+template <bool XF32>
+__global__ __launch_bounds__(kSmallThreads) void k_scale_small(const uint4 *__restrict__ x, uint32_t n16,
+                                                               float *alpha, float fp8_max) {
+  const float a = small_tensor_alpha<XF32>(x, n16, fp8_max);
+  if (threadIdx.x == 0) *alpha = a;
+}
+#endif
 
 // max|y| over the Hadamard-transformed column blocks (16 consecutive rows of one column),
 // without LDS: a lane loads one 16-byte piece from each of the 16 rows of a row block -- 8
@@ -487,6 +541,33 @@ __global__ __launch_bounds__(kThreads) void k_flat(
     r += step;
   }
   if (OUT == kOutAmax) publish_amax(amax, amax_bits, fin);
+}
+
+// Tensor scale and rowwise codes of a small tensor in one launch: every workgroup reads the whole
+// tensor for its maximum (it comes out of the L2 after the first), then quantizes its own 1024
+// blocks, one per lane.  16 x 8192 BF16: 6.4 us, where the two kernels took 4.8 + 4.0 and the gap
+// between them; kScaleQuantizeBytes says where that ends.
+template <bool XF32, int SELECT>
+__global__ __launch_bounds__(kSmallThreads) void k_scale_quantize_small(
+    const uint4 *__restrict__ x, float *__restrict__ alpha_out, uint2 *__restrict__ codes,
+    uint8_t *__restrict__ scales, uint8_t *__restrict__ choice, uint32_t nblocks, float fp8_max) {
+  __shared__ ScaleTable tab;
+  using Raw = RawBlock<XF32>;
+  const uint32_t k = blockIdx.x * kSmallThreads + threadIdx.x;
+  Raw raw;
+  load_block<XF32>(x + Raw::kPieces * (k < nblocks ? k : nblocks - 1), raw);
+  const float alpha = small_tensor_alpha<XF32>(x, nblocks * Raw::kPieces, fp8_max);
+  if (k == 0) *alpha_out = alpha;
+  const ScaleConsts sc = build_scale_table(tab, alpha);
+  if (k >= nblocks) return;
+  float v[16];
+  const uint32_t u[16] = {};
+  unpack16(raw, v);
+  auto again = [&](float (&w)[16], uint32_t (&)[16]) { unpack16(raw, w); };
+  const BlockResult res = quantize_block<kRTN, SELECT>(v, u, sc, tab, again);
+  store_as<kNtCodes>(codes + k, make_uint2(res.lo, res.hi));
+  store_as<kNtCodes>(scales + k, (uint8_t)res.scale);
+  if (choice) store_as<kNtCodes>(choice + k, (uint8_t)res.four);
 }
 
 #if NVFP4_46_MAIN
@@ -1154,7 +1235,7 @@ struct FlatArgs {
   uint32_t nb_per_row;
   uint64_t sr_seed, rht_seed;
   hipStream_t stream;
-  AmaxFinish fin{nullptr, nullptr, 0.0f};   // the amax pass only
+  AmaxFinish fin{nullptr, nullptr, 0.0f};   // the amax pass, and (its alpha) kOutScaleAndCodes
 };
 
 template <bool XF32, int ROUNDING, int SELECT, bool RHT, int OUT>
@@ -1195,6 +1276,13 @@ static int launch_flat(const FlatArgs &a) {
 
 template <bool XF32, int ROUNDING, int SELECT>
 static int launch_flat_variant(const FlatArgs &a, bool rht, int out) {
+  if constexpr (ROUNDING == kRTN) {
+    if (out == kOutScaleAndCodes)
+      return launch(k_scale_quantize_small<XF32, SELECT>,
+                    dim3((uint32_t)((a.nblocks + kSmallThreads - 1) / kSmallThreads)), dim3(kSmallThreads),
+                    a.stream, a.x, a.fin.alpha, a.codes, a.scales, a.choice, (uint32_t)a.nblocks,
+                    a.fin.fp8_max);
+  }
   if (out == kOutCodes) {
     if (rht) return launch_flat<XF32, ROUNDING, SELECT, true, kOutCodes>(a);
     return launch_flat<XF32, ROUNDING, SELECT, false, kOutCodes>(a);
@@ -1382,6 +1470,34 @@ static int check_params(const void *x, const nvfp4_46_params *p, bool one_layout
   return NVFP4_OK;
 }
 
+static int check_outputs(const nvfp4_46_params *p, const void *codes_row, const void *scales_row,
+                         const void *codes_col, const void *scales_col, const void *choice_row,
+                         const void *choice_col) {
+  const bool want_row = p->layout & NVFP4_ROWWISE, want_col = p->layout & NVFP4_COLWISE;
+  if (want_row && (!codes_row || !scales_row)) return NVFP4_ERR_NULL;
+  if (want_col && (!codes_col || !scales_col)) return NVFP4_ERR_NULL;
+  if (!want_row && (codes_row || scales_row || choice_row)) return NVFP4_ERR_PARAM;
+  if (!want_col && (codes_col || scales_col || choice_col)) return NVFP4_ERR_PARAM;
+  if (!aligned16(codes_row) || !aligned16(scales_row) || !aligned16(codes_col) ||
+      !aligned16(scales_col) || !aligned16(choice_row) || !aligned16(choice_col))
+    return NVFP4_ERR_ALIGN;
+  return NVFP4_OK;
+}
+
+static int check_workspace(const void *workspace, size_t bytes) {
+  if (bytes < NVFP4_46_TENSOR_SCALE_WS_BYTES) return NVFP4_ERR_PARAM;
+  return aligned16(workspace) ? NVFP4_OK : NVFP4_ERR_ALIGN;
+}
+
+// Where the small-tensor kernels end, by kernel durations (BF16 rows of 8192; a gap of 1 to 2 us
+// passes between dependent kernels, and a launch costs the host 3.3 us):
+//   k_scale_small          128 KiB 2.7 us, 256 KiB 3.3, 512 KiB 5.1, 1 MiB 8.7, 2 MiB 15.6
+//   instead, three launches    1.4 + 3.6 + 1.4 us and two gaps: up to 1 MiB
+//   instead, k_amax_plain with scratch words    4.8 to 5.0 us throughout: up to 256 KiB
+//   k_scale_quantize_small 256 KiB 6.4 us, 512 KiB 8.0, 1 MiB 11.6
+//   instead, scale and k_flat  3.3 to 5.0 + 3.9 us and a gap: up to 512 KiB
+constexpr int64_t kOneWgBytes = 1 << 20, kOneWgBytesWs = 256 << 10, kScaleQuantizeBytes = 512 << 10;
+
 // Eq. (1) for all three entry points.  scratch == nullptr: the reduction runs on the caller's
 // alpha word between a zeroing launch and a finishing launch.  Otherwise scratch points at
 // kScratchWords zeroed words and one launch does it all (see AmaxFinish).
@@ -1392,13 +1508,19 @@ static int tensor_scale(const void *x, const nvfp4_46_params *p, float *alpha, u
   if (rc != NVFP4_OK) return rc;
   uint32_t *amax = reinterpret_cast<uint32_t *>(alpha);      // the plain form's running maximum
   const AmaxFinish fin{scratch, alpha, p->fp8_max};
+  const int64_t n = p->rows * p->cols;
+  const bool xf32 = p->x_dtype == NVFP4_X_F32;
+  const uint4 *x4 = static_cast<const uint4 *>(x);
+  const int64_t bytes = n * (xf32 ? 4 : 2);
+  if (!p->rht && bytes <= (scratch ? kOneWgBytesWs : kOneWgBytes)) {
+    const uint32_t n16 = (uint32_t)(bytes / 16);       // n is a multiple of 8 by the shape checks
+    return xf32 ? launch(k_scale_small<true>, dim3(1), dim3(kSmallThreads), s, x4, n16, alpha, p->fp8_max)
+                : launch(k_scale_small<false>, dim3(1), dim3(kSmallThreads), s, x4, n16, alpha, p->fp8_max);
+  }
   if (!scratch) {
     rc = launch(k_store_u32, dim3(1), dim3(1), s, amax, 0u);
     if (rc != NVFP4_OK) return rc;
   }
-  const int64_t n = p->rows * p->cols;
-  const bool xf32 = p->x_dtype == NVFP4_X_F32;
-  const uint4 *x4 = static_cast<const uint4 *>(x);
   if (!p->rht) {
     // 128-bit pieces (n is a multiple of 8 by the shape checks)
     const int64_t n16 = xf32 ? n / 4 : n / 8;
@@ -1440,8 +1562,8 @@ int nvfp4_46_tensor_scale(const void *x, const nvfp4_46_params *p, float *alpha,
 int nvfp4_46_tensor_scale_ws(const void *x, const nvfp4_46_params *p, float *alpha,
                              void *workspace, size_t workspace_bytes, void *stream) {
   if (!workspace) return NVFP4_ERR_NULL;
-  if (workspace_bytes < NVFP4_46_TENSOR_SCALE_WS_BYTES) return NVFP4_ERR_PARAM;
-  if (!aligned16(workspace)) return NVFP4_ERR_ALIGN;
+  const int rc = check_workspace(workspace, workspace_bytes);
+  if (rc != NVFP4_OK) return rc;
   return tensor_scale(x, p, alpha, static_cast<uint32_t *>(workspace), static_cast<hipStream_t>(stream));
 }
 
@@ -1482,13 +1604,8 @@ int nvfp4_46_quantize(const void *x, const nvfp4_46_params *p, const float *alph
   if (rc != NVFP4_OK) return rc;
   const bool xf32 = p->x_dtype == NVFP4_X_F32;
   const bool want_row = p->layout & NVFP4_ROWWISE, want_col = p->layout & NVFP4_COLWISE;
-  if (want_row && (!codes_row || !scales_row)) return NVFP4_ERR_NULL;
-  if (want_col && (!codes_col || !scales_col)) return NVFP4_ERR_NULL;
-  if (!want_row && (codes_row || scales_row || choice_row)) return NVFP4_ERR_PARAM;
-  if (!want_col && (codes_col || scales_col || choice_col)) return NVFP4_ERR_PARAM;
-  if (!aligned16(codes_row) || !aligned16(scales_row) || !aligned16(codes_col) ||
-      !aligned16(scales_col) || !aligned16(choice_row) || !aligned16(choice_col))
-    return NVFP4_ERR_ALIGN;
+  rc = check_outputs(p, codes_row, scales_row, codes_col, scales_col, choice_row, choice_col);
+  if (rc != NVFP4_OK) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (p->block2d) {
     Block2dArgs a{xf32, x, alpha, static_cast<uint8_t *>(codes_row),
@@ -1509,6 +1626,32 @@ int nvfp4_46_quantize(const void *x, const nvfp4_46_params *p, const float *alph
              static_cast<uint8_t *>(choice_col), nullptr, p->rows, p->cols, p->sr_seed,
              p->rht_seed, s};
   return dispatch_tile(a, p->rounding, p->select, want_row ? 2 : (p->rht ? 1 : 0));
+}
+
+int nvfp4_46_scale_quantize(const void *x, const nvfp4_46_params *p, float *alpha,
+                            void *workspace, size_t workspace_bytes, void *codes_row,
+                            void *scales_row, void *codes_col, void *scales_col,
+                            void *choice_row, void *choice_col, void *stream) {
+  if (!alpha) return NVFP4_ERR_NULL;
+  int rc = check_params(x, p, false);
+  if (rc == NVFP4_OK)
+    rc = check_outputs(p, codes_row, scales_row, codes_col, scales_col, choice_row, choice_col);
+  if (rc == NVFP4_OK && workspace) rc = check_workspace(workspace, workspace_bytes);
+  if (rc != NVFP4_OK) return rc;
+  const bool xf32 = p->x_dtype == NVFP4_X_F32;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  if (p->layout == NVFP4_ROWWISE && p->rounding == NVFP4_RTN && !p->rht && !p->block2d &&
+      p->rows * p->cols * (xf32 ? 4 : 2) <= kScaleQuantizeBytes) {
+    FlatArgs a{xf32, static_cast<const uint4 *>(x), nullptr, static_cast<uint2 *>(codes_row),
+               static_cast<uint8_t *>(scales_row), static_cast<uint8_t *>(choice_row), nullptr,
+               nullptr, p->rows * p->cols / 16, (uint32_t)(p->cols / 16), 0, 0, s,
+               AmaxFinish{nullptr, alpha, p->fp8_max}};
+    return dispatch_flat(a, p->rounding, p->select, false, kOutScaleAndCodes);
+  }
+  rc = tensor_scale(x, p, alpha, static_cast<uint32_t *>(workspace), s);
+  if (rc != NVFP4_OK) return rc;
+  return nvfp4_46_quantize(x, p, alpha, codes_row, scales_row, codes_col, scales_col, choice_row,
+                           choice_col, stream);
 }
 
 int nvfp4_46_dequantize(const void *codes, const void *scales, const float *alpha, int64_t rows,

@@ -1,7 +1,7 @@
 """The NVFP4 linear layer of Fig. 3 as a sequence of library calls.
 
-Nothing is computed here: every function strings together ``nvfp4_46_tensor_scale``,
-``nvfp4_46_quantize`` and ``nvfp4_46_gemm`` the way the figure wires them.
+Nothing is computed here: every function strings together ``nvfp4_46_scale_quantize`` (tensor
+scale and codes from one call) and ``nvfp4_46_gemm`` the way the figure wires them.
 
     FPROP   y  = x W^T          x [T][K] BF16 rowwise, RTN          W [N][K] FP32 rowwise
     DGRAD   dx = dy W           dy [T][N] BF16 rowwise, SR          W columnwise (= W^T rowwise)
@@ -24,33 +24,24 @@ import torch
 from . import binding as B
 
 
-def _tensor_scale(t, stream, workspace, **kw):
-    if workspace is None:
-        return B.nvfp4_46_tensor_scale(t, stream=stream, **kw)
-    return B.nvfp4_46_tensor_scale_ws(t, workspace, stream=stream, **kw)
-
-
 def quantize_weight(w: torch.Tensor, select: int = B.SEL_46_MSE, block2d: bool = True,
                     stream=None, workspace: torch.Tensor | None = None) -> dict:
     """W [N][K] (FP32 master copy or BF16) -> both packings and the tensor scale."""
-    alpha = _tensor_scale(w, stream, workspace)
-    q = B.nvfp4_46_quantize(w, alpha, layout=B.BOTH, select=select, want_choice=False,
-                            block2d=int(block2d), stream=stream)
-    q.update(alpha=alpha, block2d=bool(block2d), shape=tuple(w.shape))
+    q = B.nvfp4_46_scale_quantize(w, workspace, layout=B.BOTH, select=select, want_choice=False,
+                                  block2d=int(block2d), stream=stream)
+    q.update(block2d=bool(block2d), shape=tuple(w.shape))
     return q
 
 
 def _rowwise(t, stream, workspace, **kw):
-    alpha = _tensor_scale(t, stream, workspace)
-    q = B.nvfp4_46_quantize(t, alpha, want_choice=False, stream=stream, **kw)
-    return q["codes_row"], q["scales_row"], alpha
+    q = B.nvfp4_46_scale_quantize(t, workspace, want_choice=False, stream=stream, **kw)
+    return q["codes_row"], q["scales_row"], q["alpha"]
 
 
 def _columnwise(t, stream, workspace, rht_seed, **kw):
-    alpha = _tensor_scale(t, stream, workspace, layout=B.COLWISE, rht=1, rht_seed=rht_seed)
-    q = B.nvfp4_46_quantize(t, alpha, layout=B.COLWISE, rht=1, rht_seed=rht_seed,
-                            want_choice=False, stream=stream, **kw)
-    return q["codes_col"], q["scales_col"], alpha
+    q = B.nvfp4_46_scale_quantize(t, workspace, layout=B.COLWISE, rht=1, rht_seed=rht_seed,
+                                  want_choice=False, stream=stream, **kw)
+    return q["codes_col"], q["scales_col"], q["alpha"]
 
 
 def fprop(x: torch.Tensor, qw: dict, select: int = B.SEL_46_MSE, stream=None,

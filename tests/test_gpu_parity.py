@@ -694,6 +694,58 @@ def test_workload_c5_full_rht_sr():
     check_case(wl.make("c5"), rounding=B.SR, rht=1, tag="c5-full")
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,cols", [(1, 16), (1, 8192), (3, 5456), (16, 8192), (17, 8192), (31, 8192 + 16),
+                                       (33, 8192), (64, 8192), (65, 8192), (129, 4096)])
+def test_small_tensors_scale_and_codes(rows, cols, dtype):
+    """Both sides of the sizes at which one workgroup takes the tensor scale (256 KiB with scratch
+    words, 1 MiB without) and at which scale and codes come from one launch (512 KiB), with
+    rest counts of the 1024-lane kernels: the oracle's scale and codes, from every call."""
+    g = torch.Generator().manual_seed(rows * 16384 + cols)
+    x = (torch.randn(rows, cols, generator=g) * torch.exp(torch.randn(rows, 1, generator=g))).to(dtype)
+    x.view(-1)[-1] = -37.0        # the maximum sits in the last element
+    xd, ws = x.cuda(), B.new_workspace()
+    print(f"small case {rows}x{cols} {dtype}", flush=True)
+    a_ref = ref.tensor_scale(wl.host_array(x))
+    for a in (B.nvfp4_46_tensor_scale(xd), B.nvfp4_46_tensor_scale_ws(xd, ws)):
+        assert _alpha_bits(a.item()) == _alpha_bits(a_ref)
+    for select in (B.SEL_46_MSE, B.SEL_46_MAE, B.SEL_FORCE6):
+        codes, scales, choice = ref.quantize(wl.host_array(x), a_ref, select=select)
+        for w in (ws, None):
+            q = B.nvfp4_46_scale_quantize(xd, w, select=select)
+            assert _alpha_bits(q["alpha"].item()) == _alpha_bits(a_ref)
+            assert np.array_equal(q["codes_row"].cpu().numpy(), codes)
+            assert np.array_equal(q["scales_row"].cpu().numpy(), scales)
+            assert np.array_equal(q["choice_row"].cpu().numpy(), choice)
+    assert int(ws.max()) == 0
+    zero = B.nvfp4_46_scale_quantize(torch.zeros_like(xd), ws)
+    assert zero["alpha"].item() == 1.0 and int(zero["codes_row"].max()) == 0
+
+
+@pytest.mark.parametrize("kw", [dict(layout=B.COLWISE, rht=1, rht_seed=7), dict(layout=B.BOTH),
+                                dict(layout=B.BOTH, block2d=1), dict(rounding=B.SR, sr_seed=5),
+                                dict(rht=1, rht_seed=7), dict(fp8_max=448.0)],
+                         ids=lambda kw: "-".join(f"{k}{v}" for k, v in kw.items()))
+def test_scale_quantize_equals_the_two_calls(kw):
+    """Every other combination of options, small and large: the same bytes as the two calls."""
+    for rows in (64, 4096):
+        x = wl.make("c5", rows, 1056).cuda()
+        sk = {k: kw[k] for k in ("layout", "rht", "rht_seed", "fp8_max") if k in kw and "rht" in kw or k == "fp8_max" and k in kw}
+        alpha = B.nvfp4_46_tensor_scale(x, **sk)
+        want = B.nvfp4_46_quantize(x, alpha, **kw)
+        got = B.nvfp4_46_scale_quantize(x, B.new_workspace(), **kw)
+        assert torch.equal(got.pop("alpha"), alpha)
+        for name, v in want.items():
+            assert (v is None) == (got[name] is None) and (v is None or torch.equal(v, got[name])), name
+    bad = torch.empty(8, 24, dtype=torch.bfloat16, device="cuda")          # 24 columns: no whole blocks
+    with pytest.raises(B.Nvfp4Error) as e:
+        B.nvfp4_46_scale_quantize(bad, B.new_workspace())
+    assert e.value.status == 2
+    with pytest.raises(B.Nvfp4Error) as e:
+        B.nvfp4_46_scale_quantize(x, torch.zeros(64, dtype=torch.uint8, device="cuda"), **kw)
+    assert e.value.status == 4
+
+
 @pytest.mark.parametrize("kw", [dict(layout=B.ROWWISE), dict(layout=B.ROWWISE, rht=1, rht_seed=9),
                                 dict(layout=B.COLWISE), dict(layout=B.BOTH),
                                 dict(layout=B.ROWWISE, block2d=1), dict(layout=B.BOTH, block2d=1)],
