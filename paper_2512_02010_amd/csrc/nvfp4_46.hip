@@ -658,10 +658,32 @@ __global__ __launch_bounds__(kThreads) void k_tile(
   __shared__ uint8_t stage_scale[OUT == kOutCodes ? kColItems : 1];   // [TC][TR/16]
   __shared__ uint8_t stage_choice[OUT == kOutCodes ? kColItems : 1];  // [TC][TR/16]
 
+  // The random words of the tile, one Philox call per four neighbouring elements of a row, as the
+  // generator hands them out.  A lane of phase 2 owns two of the four columns, so without this
+  // place every call was made twice and its other half dropped, and the words of both columns sat in
+  // registers (224 of them, two waves per SIMD).  Columnwise Hadamard + SR on 8192 x 8192:
+  // 138 -> 110 us with its tensor scale, both orientations with SR 200 -> 166.
+  constexpr bool kWords = ROUNDING != kRTN;
+  __shared__ uint4 words[kWords ? TR * TC / 4 : 1];                   // [TR][TC / 4]
+
   const TileCoord tcd = tile_of_workgroup(rows, cols, map);
   if (!tcd.valid) return;  // uniform over the workgroup
   const int64_t r0 = tcd.r0, c0 = tcd.c0;
   const int t = threadIdx.x;
+
+  if (kWords) {
+    // (cols is a multiple of 8, so four columns are in or out together and share a call)
+#pragma unroll 2
+    for (int j = 0; j < TR * TC / 4 / kThreads; ++j) {
+      const int idx = t + j * kThreads;
+      const int64_t gr = r0 + idx / (TC / 4), gc = c0 + idx % (TC / 4) * 4;
+      if (gr < rows && gc < cols) {
+        uint32_t w[4];
+        sr_words4(sr_seed, ((uint64_t)gr * (uint64_t)cols + (uint64_t)gc) >> 2, w);
+        words[idx] = make_uint4(w[0], w[1], w[2], w[3]);
+      }
+    }
+  }   // (the barrier at the end of the scale table comes before the first use)
 
   // Only columnwise codes wanted: nothing needs the tile in LDS -- a lane reads its two columns
   // straight from memory, a row at a time (a wave's load covers 256 contiguous bytes of a row).
@@ -715,9 +737,15 @@ __global__ __launch_bounds__(kThreads) void k_tile(
 #pragma unroll
           for (int q = 0; q < Raw::kPieces; ++q) mine.w[q] = own[q];
           unpack16(mine, w);
-          if (ROUNDING != kRTN) {
+          if (kWords) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) sr_words4(sr_seed, (uint64_t)k * 4u + q, &uu[4 * q]);
+            for (int q = 0; q < 4; ++q) {
+              const uint4 w4 = words[row * (TC / 4) + rbk * 4 + q];
+              uu[4 * q] = w4.x;
+              uu[4 * q + 1] = w4.y;
+              uu[4 * q + 2] = w4.z;
+              uu[4 * q + 3] = w4.w;
+            }
           }
         };
         take(v, u);
@@ -740,9 +768,9 @@ __global__ __launch_bounds__(kThreads) void k_tile(
     const int64_t gc = c0 + 2 * cp;               // even column of the pair
     if (gr >= rows || gc >= cols) continue;       // (cols is even, so the pair is in or out together)
     float va[16], vb[16];
-    uint32_t ua[16], ub[16];
-    // the lane's two column blocks (transformed, with their random words) out of the tile or memory
-    auto take = [&](float (&wa)[16], float (&wb)[16], uint32_t (&uua)[16], uint32_t (&uub)[16]) {
+    uint32_t u[16];
+    // the lane's two column blocks (transformed) out of the tile or memory
+    auto take = [&](float (&wa)[16], float (&wb)[16]) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         if constexpr (XF32) {
@@ -763,29 +791,26 @@ __global__ __launch_bounds__(kThreads) void k_tile(
         rht16(wa, sw);
         rht16(wb, sw);
       }
-      if (ROUNDING != kRTN) {
-        // element (row, col) has flat index g = row*cols + col; the pair (gc, gc+1) shares a
-        // Philox call because gc is even and cols is a multiple of 4
+    };
+    auto random_words = [&](int column, uint32_t (&uu)[16]) {           // 0 or 1 of the pair
+      if (kWords) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const uint64_t g = (uint64_t)(gr + i) * (uint64_t)cols + (uint64_t)gc;
-          uint32_t uu[4];
-          sr_words4(sr_seed, g >> 2, uu);
-          uua[i] = (g & 2u) ? uu[2] : uu[0];
-          uub[i] = (g & 2u) ? uu[3] : uu[1];
-        }
+        for (int i = 0; i < 16; ++i)
+          uu[i] = reinterpret_cast<const uint32_t *>(words)[(rb * 16 + i) * TC + 2 * cp + column];
       }
     };
-    take(va, vb, ua, ub);
-    BlockResult ra = quantize_block<ROUNDING, SELECT>(va, ua, sc, tab, [&](float (&w)[16], uint32_t (&uu)[16]) {
+    take(va, vb);
+    random_words(0, u);
+    BlockResult ra = quantize_block<ROUNDING, SELECT>(va, u, sc, tab, [&](float (&w)[16], uint32_t (&uu)[16]) {
       float other[16];
-      uint32_t other_u[16];
-      take(w, other, uu, other_u);
+      take(w, other);
+      random_words(0, uu);
     });
-    BlockResult rbk = quantize_block<ROUNDING, SELECT>(vb, ub, sc, tab, [&](float (&w)[16], uint32_t (&uu)[16]) {
+    random_words(1, u);
+    BlockResult rbk = quantize_block<ROUNDING, SELECT>(vb, u, sc, tab, [&](float (&w)[16], uint32_t (&uu)[16]) {
       float other[16];
-      uint32_t other_u[16];
-      take(other, w, other_u, uu);
+      take(other, w);
+      random_words(1, uu);
     });
     if (OUT == kOutCodes) {
       const int ia = (2 * cp) * kColBlockRows + rb, ib = ia + kColBlockRows;
