@@ -25,6 +25,8 @@
 // and never meets a barrier).
 #include <hip/hip_runtime.h>
 
+#include <cmath>
+
 #include "codec.hpp"
 #include "launch.hpp"
 #include "nvfp4_46.h"
@@ -34,6 +36,23 @@ namespace nvfp4_46 {
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// Which tile of C a workgroup takes.  Workgroups go to the eight dies in turn and each die has its
+// own L2, so the tiles are put in an order -- strips `strip` tiles wide, each row by row -- of
+// which every die takes one contiguous eighth: with strip_of() about a square of C, whose operand
+// rows are the fewest that its L2 has to fetch.
+struct TileAt {
+  uint32_t m, n;
+};
+NV_DEV TileAt tile_of_workgroup(uint32_t tiles_m, uint32_t tiles_n, uint32_t strip) {
+  const uint32_t tiles = tiles_m * tiles_n, xcd = blockIdx.x & 7u, seq = blockIdx.x >> 3;
+  const uint32_t per = tiles >> 3, extra = tiles & 7u;
+  const uint32_t tile = xcd * per + (xcd < extra ? xcd : extra) + seq;
+  const uint32_t s = tile / (strip * tiles_m), left = tile - s * strip * tiles_m;
+  const uint32_t width = tiles_n - s * strip < strip ? tiles_n - s * strip : strip;
+  const uint32_t m = left / width;
+  return TileAt{m, s * strip + (left - m * width)};
+}
 
 constexpr int kGemmThreads = 256;
 constexpr int GT = 256;                  // rows of A (and of B) per workgroup tile
@@ -533,7 +552,7 @@ __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 
     const float *__restrict__ alpha_a, const uint8_t *__restrict__ codes_b,
     const uint8_t *__restrict__ scales_b, const float *__restrict__ alpha_b,
     void *__restrict__ out, int64_t M, int64_t N, uint32_t K, uint32_t tiles_m, uint32_t tiles_n,
-    uint32_t sha, uint32_t shb) {
+    uint32_t strip, uint32_t sha, uint32_t shb) {
   constexpr int WM = S::WM, WN = S::WN, KS = S::KS, HPW = S::HPW, NST = S::NST, U = S::U, T = S::T;
   typedef uint32_t v4 __attribute__((ext_vector_type(4)));
   extern __shared__ __align__(16) uint8_t lds_raw[];
@@ -543,13 +562,8 @@ __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 
   const uint32_t kg = wave / (S::SM * S::SN), spatial = wave % (S::SM * S::SN);
   const uint32_t wm = spatial / S::SN, wn = spatial % S::SN;
 
-  // Workgroups go to the eight dies in turn; consecutive tiles (row by row of C) stay on one die
-  // so that its L2 holds the operand rows they share.
-  const uint32_t tiles = tiles_m * tiles_n, xcd = blockIdx.x & 7u, seq = blockIdx.x >> 3;
-  const uint32_t per = tiles >> 3, extra = tiles & 7u;
-  const uint32_t tile = xcd * per + (xcd < extra ? xcd : extra) + seq;
-  const uint32_t tile_m = tile / tiles_n, tile_n = tile - tile_m * tiles_n;
-  const int64_t m0 = (int64_t)tile_m * S::BM, n0 = (int64_t)tile_n * S::BN;
+  const TileAt at = tile_of_workgroup(tiles_m, tiles_n, strip);
+  const int64_t m0 = (int64_t)at.m * S::BM, n0 = (int64_t)at.n * S::BN;
   const uint32_t row_codes = K / 2, row_scales = K / 16;
   const uint32_t rows_a = (uint32_t)(M - m0 < S::BM ? M - m0 : S::BM);     // rows the tile really has
   const uint32_t rows_b = (uint32_t)(N - n0 < S::BN ? N - n0 : S::BN);
@@ -1187,6 +1201,19 @@ static int launch_with_lds(Kernel kernel, dim3 grid, dim3 block, size_t lds_byte
   return launch(kernel, grid, block, lds_bytes, s, args...);
 }
 
+// Strip width (in tiles) that makes an eighth of the tiles about square: h x w tiles of BM x BN with
+// h w = tiles / 8 touch the fewest operand rows, BM h + BN w, at w = sqrt(tiles / 8 * BM / BN).
+// Row by row / in strips: 1536 x 4096 x 8192 106 / 102 us, 8000 x 8000 x 2080 314 / 306, 768 x 4096
+// x 8192 56 / 55.  Operands that fit the 4 MB of one die's L2 whole stay row by row (2880 x 1440 x
+// 1056: 19.9 / 20.2), and so do k_gemm_dma's tiles (8192 x 8192 x 8192: 841 / 849).
+template <int BM, int BN>
+static uint32_t strip_of(const GemmArgs &a) {
+  const double tm = (double)((a.M + BM - 1) / BM), tn = (double)((a.N + BN - 1) / BN);
+  if ((double)(a.M + a.N) * (double)a.K * 0.5625 <= 4.0 * 1024 * 1024) return (uint32_t)tn;
+  const double w = std::sqrt(tm * tn / 8.0 * BM / BN) + 0.5;
+  return (uint32_t)(w < 1.0 ? 1.0 : w > tn ? tn : w);
+}
+
 static dim3 tile_grid(const GemmArgs &a) {
   const int64_t tiles_m = (a.M + GT - 1) / GT, tiles_n = (a.N + GT - 1) / GT;
   return dim3((uint32_t)(tiles_m * tiles_n));
@@ -1263,7 +1290,8 @@ int run_gemm_tile(const GemmArgs &a) {
                            a.stream, a.codes_a, a.scales_a, a.alpha_a, a.codes_b, a.scales_b,
                            a.alpha_b, a.out, a.M, a.N, (uint32_t)a.K,
                            (uint32_t)((a.M + S::BM - 1) / S::BM),
-                           (uint32_t)((a.N + S::BN - 1) / S::BN), a.sha, a.shb);
+                           (uint32_t)((a.N + S::BN - 1) / S::BN), strip_of<S::BM, S::BN>(a), a.sha,
+                           a.shb);
   };
   if (a.K % S::CK == 0) return a.f32 ? go(k_gemm_tile<S, true, true>) : go(k_gemm_tile<S, true, false>);
   return a.f32 ? go(k_gemm_tile<S, false, true>) : go(k_gemm_tile<S, false, false>);

@@ -147,6 +147,9 @@ TILE_SHAPES = [
     (701, 799, 32, ""), (705, 769, 512, ""), (704, 784, 800, "ab"),
     # 128 x 128
     (1901, 1920, 288, "b"), (1793, 1921, 256, ""),
+    # operands past one die's L2: the tiles in strips, the last one narrower (64 x 64, 128 x 128,
+    # 256 x 128)
+    (1100, 1500, 4128, ""), (1857, 1930, 2592, ""), (2050, 2944, 1824, "b"),
     # 256 x 128
     (2049, 2945, 96, ""), (2304, 2944, 128, "b"), (2064, 2931, 416, "a")]
 
