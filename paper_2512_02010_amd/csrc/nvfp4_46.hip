@@ -624,13 +624,13 @@ struct TileCoord {
 // 8192 x 8192.)
 struct TileMap {
   uint32_t sx, sy;      // super-tile width and height in tiles
-  uint32_t backwards;   // take the tiles last to first (see kLastLevelBytes)
+  uint32_t last;        // the grid's last workgroup where tiles go last to first (kLastLevelBytes), or 0
 };
 
 NV_DEV TileCoord tile_of_workgroup(int64_t rows, int64_t cols, TileMap m) {
   const uint32_t nt_r = (uint32_t)((rows + TR - 1) / TR), nt_c = (uint32_t)((cols + TC - 1) / TC);
   const uint32_t per = m.sx * m.sy, nsx = (nt_c + m.sx - 1) / m.sx;
-  const uint32_t id = m.backwards ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
+  const uint32_t id = m.last ? m.last - blockIdx.x : blockIdx.x;
   const uint32_t xcd = id & 7u, slot = id >> 3;
   const uint32_t round = slot / per, within = slot - round * per;
   const uint32_t S = round * 8u + xcd;                      // super-tile, row-major
@@ -1339,9 +1339,9 @@ struct TileArgs {
 
 // Super-tiles of 8 x 16 tiles, smaller along an axis that has fewer tiles (a small tensor
 // would otherwise launch mostly workgroups without a tile).
-static TileMap tile_map(int64_t rows, int64_t cols, uint32_t backwards = 0) {
+static TileMap tile_map(int64_t rows, int64_t cols) {
   const int64_t nt_r = (rows + TR - 1) / TR, nt_c = (cols + TC - 1) / TC;
-  return TileMap{(uint32_t)(nt_c < 8 ? nt_c : 8), (uint32_t)(nt_r < 16 ? nt_r : 16), backwards};
+  return TileMap{(uint32_t)(nt_c < 8 ? nt_c : 8), (uint32_t)(nt_r < 16 ? nt_r : 16), 0u};
 }
 
 // Whole turns over the eight XCDs, each turn one super-tile per XCD.
@@ -1354,11 +1354,12 @@ static int tile_grid(int64_t rows, int64_t cols) {
 
 template <bool XF32, int ROUNDING, int SELECT, bool RHT, bool WANT_ROW, int OUT>
 static int launch_tile(const TileArgs &a) {
-  return launch(k_tile<XF32, ROUNDING, SELECT, RHT, WANT_ROW, OUT>, dim3(tile_grid(a.rows, a.cols)),
-                dim3(kThreads), a.stream, a.x, a.alpha, a.codes_row, a.scales_row, a.choice_row,
-                a.codes_col, a.scales_col, a.choice_col, a.out, a.rows, a.cols, a.sr_seed,
-                a.rht_seed,
-                tile_map(a.rows, a.cols, runs_backwards(a.rows * a.cols, XF32)));
+  const int grid = tile_grid(a.rows, a.cols);
+  TileMap map = tile_map(a.rows, a.cols);
+  if (runs_backwards(a.rows * a.cols, XF32)) map.last = (uint32_t)grid - 1u;
+  return launch(k_tile<XF32, ROUNDING, SELECT, RHT, WANT_ROW, OUT>, dim3(grid), dim3(kThreads), a.stream,
+                a.x, a.alpha, a.codes_row, a.scales_row, a.choice_row, a.codes_col, a.scales_col,
+                a.choice_col, a.out, a.rows, a.cols, a.sr_seed, a.rht_seed, map);
 }
 
 // variant: 0 = columnwise codes, 1 = columnwise codes + rht, 2 = both orientations,
