@@ -73,7 +73,7 @@ SHAPES = [(32, 32, 32), (1, 1, 64), (100, 70, 160), (256, 256, 128), (257, 255, 
           (128, 257, 512), (129, 64, 512),
           # at most 16 rows of A: the 16-row variant of that kernel
           (7, 45, 256), (16, 64, 768), (9, 1000, 2304), (3, 17, 4096), (17, 33, 256),
-          # up to 512 rows of A in slabs of 128 rows through the same kernel
+          # more rows of A, ragged tiles
           (257, 255, 768), (384, 300, 256), (511, 40, 1024), (513, 40, 512)]
 
 
