@@ -28,6 +28,7 @@
 #include <cmath>
 
 #include "codec.hpp"
+#include "gemm_shapes.hpp"
 #include "launch.hpp"
 #include "nvfp4_46.h"
 
@@ -55,8 +56,6 @@ NV_DEV TileAt tile_of_workgroup(uint32_t tiles_m, uint32_t tiles_n, uint32_t str
 }
 
 constexpr int kGemmThreads = 256;
-constexpr int GT = 256;                  // rows of A (and of B) per workgroup tile
-constexpr int GK = 128;                  // contraction steps per LDS chunk
 constexpr int kCodeRow = GK / 2 + 16;    // bytes per operand row in LDS: 64 of codes + 16 of padding,
                                          // so that 16 lanes reading 16 bytes from 16 rows hit 16
                                          // different bank groups (80 = 5 * 16, 5 coprime to 16)
@@ -518,29 +517,6 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm_dma(
 // of one LDS access pass hit all banks.  One barrier per chunk: it comes after the wait for the
 // own copies of the chunk, so behind it the chunk is complete and the stage of the chunk before is
 // free for the next copies.  K <= 2^24 (32-bit lane offsets).
-template <int WM_, int WN_, int SM_, int SN_, int KS_, int HPW_, int NST_>
-struct TileShape {
-  static constexpr int WM = WM_, WN = WN_, SM = SM_, SN = SN_, KS = KS_, HPW = HPW_, NST = NST_;
-  static constexpr int kWaves = SM * SN * KS, kThreads = 64 * kWaves;
-  static constexpr int BM = 32 * WM * SM, BN = 32 * WN * SN, ROWS = BM + BN;
-  static constexpr int CK = 64 * KS * HPW;                // contraction steps per chunk
-  static constexpr int U = CK / 32;                       // 16-byte units of codes (= scale pairs) per row
-  static constexpr int kCopies = ROWS * U / 64;           // copy instructions per chunk, codes (and scales)
-  static constexpr int NC = (kCopies + kWaves - 1) / kWaves;
-  static constexpr uint32_t kScaleBase = ROWS * U * 16, STAGE = ROWS * U * 20;
-  static constexpr int T = WM + WN, kTiles = WM * WN;
-  // partial sums of the KS groups: each owns kOwn instruction tiles, exchanged in PH phases
-  static constexpr int kOwn = KS == 1 ? kTiles : kTiles >= KS ? kTiles / KS : 1;
-  static constexpr int kPartialTile = (KS - 1) * SM * SN * 4096;
-  static constexpr int kPerPhaseMax = KS == 1 ? kTiles : 160 * 1024 / kPartialTile;
-  static constexpr int PER = kPerPhaseMax < kTiles ? kPerPhaseMax : kTiles;
-  static constexpr int LDS_STAGES = NST * STAGE, LDS_PART = KS == 1 ? 0 : PER * kPartialTile;
-  static constexpr int LDS = LDS_STAGES > LDS_PART ? LDS_STAGES : LDS_PART;
-  static_assert(ROWS * U % 64 == 0 && BM % (64 / U) == 0 && U <= 16, "a copy instruction stays within one operand");
-  static_assert(LDS <= 160 * 1024, "the stages must fit the LDS");
-  static_assert(kTiles % KS == 0 || KS % kTiles == 0, "whole tiles per owner");
-  static_assert((NST - 1) * 2 * NC < 63, "vmcnt counts to 63");
-};
 // as NV_DMA16, two bytes per lane, each into a 32-bit word of LDS
 #define NV_DMA2(lds_sgpr, voff, gbase)                                                        \
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_ushort %1, %2"                           \
@@ -801,7 +777,6 @@ __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 
 // while a chunk is multiplied; otherwise the next chunk's copy overlaps this chunk's
 // arithmetic and the other waves' work.
 // MT = number of 32-row tiles of A (1 or 2).  K must be a multiple of 256 and <= 2^24.
-constexpr int SK = 256;          // contraction indices per chunk
 // Waves per workgroup and staging pieces per wave, for 1 and 2 tiles of A.  Four waves were
 // fastest on every weight shape timed (8192 x 8192, 28672 x 8192, 8192 x 28672, 4096 x 4096;
 // 2 to 10 waves and 1 to 4 pieces were tried): with one tile of A the workgroup then needs
@@ -1269,24 +1244,11 @@ int run_gemm_skinny(const GemmArgs &a) {
 }
 #endif
 
-// The shapes of k_gemm_tile that are in use.  (Timed against these: 64 x 64 with three stages, 128
-// x 64 and 128 x 128 in two copies, 32 x 64, 32 x 32 in four copies, 256 x 256.)
-using Tile32 = TileShape<1, 1, 1, 1, 8, 1, 2>;         // 32 x 32, 8 waves, each an eighth of K
-using Tile64x32 = TileShape<2, 1, 1, 1, 4, 1, 2>;      // 64 x 32, 4 waves
-using Tile64 = TileShape<2, 2, 1, 1, 4, 1, 2>;         // 64 x 64, 4 waves; four workgroups per CU
-using Tile128 = TileShape<2, 2, 2, 2, 4, 1, 2>;        // 128 x 128, 16 waves
-using Tile256x128 = TileShape<4, 2, 2, 2, 2, 1, 4>;    // 256 x 128, 8 waves
-
-template <typename S>
-static int64_t tiles_of(const GemmArgs &a) {
-  return ((a.M + S::BM - 1) / S::BM) * ((a.N + S::BN - 1) / S::BN);
-}
-
 #if NVFP4_46_GEMM_HAS(6)
 template <typename S>
 int run_gemm_tile(const GemmArgs &a) {
   auto go = [&](auto kernel) {
-    return launch_with_lds(kernel, dim3((uint32_t)tiles_of<S>(a)), dim3(S::kThreads), S::LDS,
+    return launch_with_lds(kernel, dim3((uint32_t)tiles_of<S>(a.M, a.N)), dim3(S::kThreads), S::LDS,
                            a.stream, a.codes_a, a.scales_a, a.alpha_a, a.codes_b, a.scales_b,
                            a.alpha_b, a.out, a.M, a.N, (uint32_t)a.K,
                            (uint32_t)((a.M + S::BM - 1) / S::BM),
@@ -1342,39 +1304,18 @@ extern "C" int nvfp4_46_gemm(const void *codes_a, const void *scales_a, const fl
                    (flags & NVFP4_GEMM_A_TILE_SCALES) ? 4u : 0u,
                    (flags & NVFP4_GEMM_B_TILE_SCALES) ? 4u : 0u, out_dtype == NVFP4_OUT_F32,
                    static_cast<hipStream_t>(stream)};
-  const bool offsets_fit = K <= ((int64_t)1 << 24);     // 32-bit lane offsets of the copies
-  if (!offsets_fit)
-    return (K % GK) == 0
-               ? (a.f32 ? run_gemm_staged<true, true>(a) : run_gemm_staged<true, false>(a))
-               : (a.f32 ? run_gemm_staged<false, true>(a) : run_gemm_staged<false, false>(a));
-
-  // Which kernel: times in us, BF16 out, back to back on one card, M x N x K.
-  //
-  // Few rows of A against a large weight: the kernels that stream B, one workgroup per 32 columns.
-  // Up to 32 rows always (16 x 8192 x 8192: 9.5, in 32 x 32 tiles 12.1; 32 x 8192 x 28672: 27.8 /
-  // 34.4); from 33 to 64 rows only between the widths whose 32 x 32 tiles are at most one
-  // per compute unit (64 x 4096 x 4096: 10.2, tiles 7.6) and those that fill the chip in 64 x 64
-  // tiles (64 x 28672 x 8192: 49.7, tiles 37.7; between them 64 x 8192 x 8192: 16.8 / 17.9).
-  constexpr int64_t kCus = 256;
-  const int64_t t32 = tiles_of<Tile32>(a), t64 = tiles_of<Tile64>(a);
-  if ((K % SK) == 0 && (M <= 32 || (M <= 64 && t32 > kCus && t64 <= kCus))) return run_gemm_skinny(a);
-
-  // The largest tiles (the fewest expansions and copies per product) whose last turn over the chip
-  // leaves little of it idle.  256 x 256 tiles of the copy-based kernel from 62 % (2816 x 4096 x
-  // 4096, 176 tiles: 96, in 64 x 64 tiles 111; but 4352 x 4096 x 2048, 272 tiles: 106 / 90);
-  // 256 x 128 tiles from 80 % (2048 x 4096 x 4096: 80 in 256 x 256, 65; 2048 x 3072 x 4096, 75 %:
-  // 59, in 64 x 64 tiles 55); 128 x 128 from 87 % (1000 x 4096 x 4096: 76 in 256 x 256, 35, in
-  // 64 x 64 38; 2048 x 3072 x 4096, 75 %: 63).
-  auto fill = [&](int64_t tiles) { return (double)tiles / (double)((tiles + kCus - 1) / kCus * kCus); };
-  if ((K % GK) == 0 && fill(tiles_m * tiles_n) >= 0.62) return run_gemm_dma(a);
-  if (fill(tiles_of<Tile256x128>(a)) >= 0.8) return run_gemm_tile<Tile256x128>(a);
-  if (fill(tiles_of<Tile128>(a)) >= 0.87) return run_gemm_tile<Tile128>(a);
-  // Small products: the smallest tiles that are at most one per compute unit (64 x 1024 x 4096:
-  // 7.6 in 32 x 32, 9.9 in 64 x 32, 13.0 in 64 x 64; 128 x 4096 x 4096: 11.4 / 10.6 / 13.1; 200 x
-  // 4096 x 4096: 18.8 / 15.1 / 13.9); 32 rows or columns would leave larger tiles half empty.
-  if (M <= 32 || t32 <= kCus) return run_gemm_tile<Tile32>(a);
-  if (N <= 32 || tiles_of<Tile64x32>(a) <= kCus) return run_gemm_tile<Tile64x32>(a);
-  return run_gemm_tile<Tile64>(a);
+  switch (choose_gemm(M, N, K)) {
+    case kGemmStaged:
+      return (K % GK) == 0 ? (a.f32 ? run_gemm_staged<true, true>(a) : run_gemm_staged<true, false>(a))
+                           : (a.f32 ? run_gemm_staged<false, true>(a) : run_gemm_staged<false, false>(a));
+    case kGemmDma: return run_gemm_dma(a);
+    case kGemmSkinny: return run_gemm_skinny(a);
+    case kGemmTile32: return run_gemm_tile<Tile32>(a);
+    case kGemmTile64x32: return run_gemm_tile<Tile64x32>(a);
+    case kGemmTile64: return run_gemm_tile<Tile64>(a);
+    case kGemmTile128: return run_gemm_tile<Tile128>(a);
+    default: return run_gemm_tile<Tile256x128>(a);
+  }
 }
 
 #endif

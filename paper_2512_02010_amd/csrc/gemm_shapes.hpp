@@ -1,0 +1,104 @@
+// Host side of the matrix product: the tile shapes of its kernels and which kernel a product takes.
+// Plain C++ without HIP, so that the choice and the budgets can be checked where there is no GPU.
+#pragma once
+
+#include <cstddef>
+#include <cstdint>
+
+namespace nvfp4_46 {
+
+constexpr int GT = 256;                  // k_gemm, k_gemm_dma: rows of A (and of B) per workgroup tile
+constexpr int GK = 128;                  // ... and contraction steps per chunk
+constexpr int SK = 256;                  // k_gemm_skinny, k_gemm_skinny16: contraction steps per chunk
+constexpr int64_t kCus = 256;
+
+// k_gemm_tile's shapes (described at the kernel).
+template <int WM_, int WN_, int SM_, int SN_, int KS_, int HPW_, int NST_>
+struct TileShape {
+  static constexpr int WM = WM_, WN = WN_, SM = SM_, SN = SN_, KS = KS_, HPW = HPW_, NST = NST_;
+  static constexpr int kWaves = SM * SN * KS, kThreads = 64 * kWaves;
+  static constexpr int BM = 32 * WM * SM, BN = 32 * WN * SN, ROWS = BM + BN;
+  static constexpr int CK = 64 * KS * HPW;                // contraction steps per chunk
+  static constexpr int U = CK / 32;                       // 16-byte units of codes (= scale pairs) per row
+  static constexpr int kCopies = ROWS * U / 64;           // copy instructions per chunk, codes (and scales)
+  static constexpr int NC = (kCopies + kWaves - 1) / kWaves;
+  static constexpr uint32_t kScaleBase = ROWS * U * 16, STAGE = ROWS * U * 20;
+  static constexpr int T = WM + WN, kTiles = WM * WN;
+  // partial sums of the KS groups: each owns kOwn instruction tiles, exchanged in PH phases
+  static constexpr int kOwn = KS == 1 ? kTiles : kTiles >= KS ? kTiles / KS : 1;
+  static constexpr int kPartialTile = (KS - 1) * SM * SN * 4096;
+  static constexpr int kPerPhaseMax = KS == 1 ? kTiles : 160 * 1024 / kPartialTile;
+  static constexpr int PER = kPerPhaseMax < kTiles ? kPerPhaseMax : kTiles;
+  static constexpr int LDS_STAGES = NST * STAGE, LDS_PART = KS == 1 ? 0 : PER * kPartialTile;
+  static constexpr int LDS = LDS_STAGES > LDS_PART ? LDS_STAGES : LDS_PART;
+  static_assert(ROWS * U % 64 == 0 && BM % (64 / U) == 0 && U <= 16, "a copy instruction stays within one operand");
+  static_assert(LDS <= 160 * 1024, "the stages must fit the LDS");
+  static_assert(kTiles % KS == 0 || KS % kTiles == 0, "whole tiles per owner");
+  static_assert((NST - 1) * 2 * NC < 63, "vmcnt counts to 63");
+};
+
+// The shapes of k_gemm_tile that are in use.  (Timed against these: 64 x 64 with three stages, 128
+// x 64 and 128 x 128 in two copies, 32 x 64, 32 x 32 in four copies, 256 x 256.)
+using Tile32 = TileShape<1, 1, 1, 1, 8, 1, 2>;         // 32 x 32, 8 waves, each an eighth of K
+using Tile64x32 = TileShape<2, 1, 1, 1, 4, 1, 2>;      // 64 x 32, 4 waves
+using Tile64 = TileShape<2, 2, 1, 1, 4, 1, 2>;         // 64 x 64, 4 waves; four workgroups per CU
+using Tile128 = TileShape<2, 2, 2, 2, 4, 1, 2>;        // 128 x 128, 16 waves
+using Tile256x128 = TileShape<4, 2, 2, 2, 2, 1, 4>;    // 256 x 128, 8 waves
+
+constexpr int64_t tiles_of(int64_t M, int64_t N, int BM, int BN) {
+  return ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
+}
+template <typename S>
+constexpr int64_t tiles_of(int64_t M, int64_t N) { return tiles_of(M, N, S::BM, S::BN); }
+
+enum GemmKernel {
+  kGemmStaged, kGemmDma, kGemmSkinny, kGemmTile32, kGemmTile64x32, kGemmTile64, kGemmTile128, kGemmTile256x128
+};
+
+// How much of the chip's time a product in tiles of BM x BN uses: what tiles of 64 x 64 would cover
+// of C over what whole turns of 256 workgroups could hold.  The last turn's empty places count as
+// idle, and so does what lies past the end of C: 64 x 28672 has 224 tiles of 256 x 128, which seem
+// to fill the chip but hold 64 of 256 rows each (22 %; at K = 8192 110 us, in 64 x 64 tiles 45).
+// 64 x 64 is the measure because that is the other choice, with padding of its own: 196 rows
+// pad to 256 in either (196 x 29536 x 4096: 63 in 256 x 128, 72 in 64 x 64).
+inline double use_of_chip(int64_t M, int64_t N, int BM, int BN) {
+  const int64_t turns = (tiles_of(M, N, BM, BN) + kCus - 1) / kCus;
+  return (double)tiles_of<Tile64>(M, N) * Tile64::BM * Tile64::BN / ((double)turns * kCus * BM * BN);
+}
+template <typename S>
+inline double use_of_chip(int64_t M, int64_t N) { return use_of_chip(M, N, S::BM, S::BN); }
+
+// Which kernel: times in us, BF16 out, on one card, M x N x K; operands as the calls before left
+// them (all in the memory-side cache), or B from memory where it says so.
+inline GemmKernel choose_gemm(int64_t M, int64_t N, int64_t K) {
+  if (K > ((int64_t)1 << 24)) return kGemmStaged;       // 32-bit lane offsets of the others' copies
+
+  // Few rows of A against a large weight: the kernels that stream B, one workgroup per 32 columns.
+  // Up to 32 rows always (16 x 8192 x 8192: 9.5, in 32 x 32 tiles 12.1; 32 x 8192 x 28672: 27.8 /
+  // 34.4; B from memory, 16 x 28672 x 8192: 33 / 40, 32 x 28672 x 8192: 41 / 42); from 33 to 64 rows
+  // only between the widths whose 32 x 32 tiles are at most one per compute unit (64 x 4096 x 4096:
+  // 10.2, tiles 7.6) and those that fill the chip in 64 x 64 tiles (B from memory, 33 / 64 x 28672 x
+  // 8192: 52 / 57, tiles 43 / 45; 33 / 64 x 128256 x 4096: 110 / 123, tiles 85 / 93; between them
+  // 64 x 8192 x 8192: 19 / 28).
+  const int64_t t32 = tiles_of<Tile32>(M, N), t64 = tiles_of<Tile64>(M, N);
+  if ((K % SK) == 0 && (M <= 32 || (M <= 64 && t32 > kCus && t64 <= kCus))) return kGemmSkinny;
+
+  // The largest tiles (the fewest expansions and copies per product) that leave little of the chip
+  // idle.  256 x 256 tiles of the copy-based kernel from 62 % (2816 x 4096 x 4096, 176 tiles: 96, in
+  // 64 x 64 tiles 111; but 4352 x 4096 x 2048, 272 tiles: 106 / 90); 256 x 128 tiles from 80 % (2048 x
+  // 4096 x 4096: 80 in 256 x 256, 65; 2048 x 3072 x 4096, 75 %: 59, in 64 x 64 tiles 55); 128 x 128
+  // from 87 % (1000 x 4096 x 4096: 76 in 256 x 256, 35, in 64 x 64 38; 2048 x 3072 x 4096, 75 %: 63;
+  // B from memory, 65 / 128 x 28672 x 8192: 116 / 117 in
+  // 256 x 128, 66 / 68, in 64 x 64 74 / 76).
+  if ((K % GK) == 0 && use_of_chip(M, N, GT, GT) >= 0.62) return kGemmDma;
+  if (use_of_chip<Tile256x128>(M, N) >= 0.8) return kGemmTile256x128;
+  if (use_of_chip<Tile128>(M, N) >= 0.87) return kGemmTile128;
+  // Small products: the smallest tiles that are at most one per compute unit (64 x 1024 x 4096:
+  // 7.6 in 32 x 32, 9.9 in 64 x 32, 13.0 in 64 x 64; 128 x 4096 x 4096: 11.4 / 10.6 / 13.1; 200 x
+  // 4096 x 4096: 18.8 / 15.1 / 13.9); 32 rows or columns would leave larger tiles half empty (B from
+  // memory, 16 x 28672 x 8256: 43 / 59 / 49, and 120 in 256 x 128).
+  if (M <= 32 || t32 <= kCus) return kGemmTile32;
+  if (N <= 32 || tiles_of<Tile64x32>(M, N) <= kCus) return kGemmTile64x32;
+  return kGemmTile64;
+}
+}  // namespace nvfp4_46

@@ -1,7 +1,8 @@
 """The kernels' per-block code compiled for the host (tests/host_model/), behind ctypes.
 
 Test infrastructure.  ``csrc/block.hpp`` and ``csrc/codec.hpp`` -- the code every quantizing
-kernel runs per block -- are compiled with the host compiler, the gfx950 conversion
+kernel runs per block -- and ``csrc/gemm_shapes.hpp`` -- the choice of the matrix product's
+kernel -- are compiled with the host compiler, the gfx950 conversion
 instructions replaced by plain definitions of what they compute, so that CPU tests can put
 the GPU path's block logic next to the oracle on inputs of any range without a GPU.
 """
@@ -19,9 +20,13 @@ _HERE = Path(__file__).resolve().parent / "host_model"
 _ROOT = _HERE.parent.parent
 _CSRC = _ROOT / "paper_2512_02010_amd" / "csrc"
 _SO = _HERE / "_build" / "libhost_model.so"
-_SOURCES = [_HERE / "model.cpp", _HERE / "gfx950_on_host.hpp", _CSRC / "block.hpp", _CSRC / "codec.hpp"]
+_SOURCES = [_HERE / "model.cpp", _HERE / "gfx950_on_host.hpp", _CSRC / "block.hpp", _CSRC / "codec.hpp",
+            _CSRC / "gemm_shapes.hpp"]
 
 RTN, SR, SR_AFTER_RTN_SELECT = 0, 1, 2
+
+# enum GemmKernel
+GEMM_KERNELS = ("staged", "dma", "skinny", "tile32", "tile64x32", "tile64", "tile128", "tile256x128")
 
 
 def _compiler() -> str:
@@ -69,6 +74,10 @@ def lib() -> C.CDLL:
         L.hm_philox.argtypes = [u32p, C.c_uint32, C.c_uint32, u32p]
         L.hm_rht16.restype = None
         L.hm_rht16.argtypes = [f32p, C.c_uint32]
+        L.hm_choose_gemm.restype = C.c_int
+        L.hm_choose_gemm.argtypes = [C.c_int64, C.c_int64, C.c_int64]
+        L.hm_tile_shape.restype = None
+        L.hm_tile_shape.argtypes = [C.c_int, C.POINTER(C.c_int32)]
         _lib = L
     return _lib
 
@@ -145,3 +154,15 @@ def rht16(v, sign_word: int) -> np.ndarray:
     a = np.array(v, dtype=np.float32).copy()
     lib().hm_rht16(_p(a, C.c_float), sign_word)
     return a
+
+
+def choose_gemm(M: int, N: int, K: int) -> str:
+    """Name of the kernel that nvfp4_46_gemm runs for an M x N x K product."""
+    return GEMM_KERNELS[lib().hm_choose_gemm(M, N, K)]
+
+
+def tile_shape(kernel: str):
+    """(BM, BN, threads, LDS bytes) of a tile shape of k_gemm_tile."""
+    v = (C.c_int32 * 4)()
+    lib().hm_tile_shape(GEMM_KERNELS.index(kernel), v)
+    return tuple(v)

@@ -1,8 +1,10 @@
-// Test infrastructure: the kernels' per-block code (csrc/block.hpp) compiled for the host and
-// exported with a C interface.  See gfx950_on_host.hpp.
+// Test infrastructure: the kernels' per-block code (csrc/block.hpp) and the matrix product's choice of
+// kernel (csrc/gemm_shapes.hpp) compiled for the host and exported with a C interface.  See
+// gfx950_on_host.hpp.
 #include "gfx950_on_host.hpp"
 
 #include "block.hpp"
+#include "gemm_shapes.hpp"
 
 using namespace nvfp4_46;
 
@@ -159,6 +161,25 @@ void hm_rht16(float *v, uint32_t sign_word) {
   for (int i = 0; i < 16; ++i) a[i] = v[i];
   rht16(a, sign_word);
   for (int i = 0; i < 16; ++i) v[i] = a[i];
+}
+
+// the kernel (enum GemmKernel) that a product of these sizes takes
+int hm_choose_gemm(int64_t M, int64_t N, int64_t K) { return choose_gemm(M, N, K); }
+
+// rows and columns of a workgroup's tile, threads and LDS bytes of one of k_gemm_tile's shapes
+void hm_tile_shape(int kernel, int32_t *out) {
+  auto of = [&](auto shape) {
+    typedef decltype(shape) S;
+    const int32_t v[4] = {S::BM, S::BN, S::kThreads, S::LDS};
+    for (int i = 0; i < 4; ++i) out[i] = v[i];
+  };
+  switch (kernel) {
+    case kGemmTile32: return of(Tile32{});
+    case kGemmTile64x32: return of(Tile64x32{});
+    case kGemmTile64: return of(Tile64{});
+    case kGemmTile128: return of(Tile128{});
+    default: return of(Tile256x128{});
+  }
 }
 
 }  // extern "C"
