@@ -1268,6 +1268,7 @@ int run_gemm_tile(const GemmArgs &a) {
 NVFP4_46_TILE(Tile32)
 NVFP4_46_TILE(Tile64x32)
 NVFP4_46_TILE(Tile64)
+NVFP4_46_TILE(Tile64Long)
 NVFP4_46_TILE(Tile128)
 NVFP4_46_TILE(Tile256x128)
 #endif
@@ -1313,6 +1314,7 @@ extern "C" int nvfp4_46_gemm(const void *codes_a, const void *scales_a, const fl
     case kGemmTile32: return run_gemm_tile<Tile32>(a);
     case kGemmTile64x32: return run_gemm_tile<Tile64x32>(a);
     case kGemmTile64: return run_gemm_tile<Tile64>(a);
+    case kGemmTile64Long: return run_gemm_tile<Tile64Long>(a);
     case kGemmTile128: return run_gemm_tile<Tile128>(a);
     default: return run_gemm_tile<Tile256x128>(a);
   }

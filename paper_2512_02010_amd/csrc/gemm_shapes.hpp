@@ -42,6 +42,7 @@ struct TileShape {
 using Tile32 = TileShape<1, 1, 1, 1, 8, 1, 2>;         // 32 x 32, 8 waves, each an eighth of K
 using Tile64x32 = TileShape<2, 1, 1, 1, 4, 1, 2>;      // 64 x 32, 4 waves
 using Tile64 = TileShape<2, 2, 1, 1, 4, 1, 2>;         // 64 x 64, 4 waves; four workgroups per CU
+using Tile64Long = TileShape<2, 2, 1, 1, 8, 1, 2>;     // 64 x 64, 8 waves
 using Tile128 = TileShape<2, 2, 2, 2, 4, 1, 2>;        // 128 x 128, 16 waves
 using Tile256x128 = TileShape<4, 2, 2, 2, 2, 1, 4>;    // 256 x 128, 8 waves
 
@@ -52,7 +53,8 @@ template <typename S>
 constexpr int64_t tiles_of(int64_t M, int64_t N) { return tiles_of(M, N, S::BM, S::BN); }
 
 enum GemmKernel {
-  kGemmStaged, kGemmDma, kGemmSkinny, kGemmTile32, kGemmTile64x32, kGemmTile64, kGemmTile128, kGemmTile256x128
+  kGemmStaged, kGemmDma, kGemmSkinny, kGemmTile32, kGemmTile64x32, kGemmTile64, kGemmTile64Long,
+  kGemmTile128, kGemmTile256x128
 };
 
 // How much of the chip's time a product in tiles of BM x BN uses: what tiles of 64 x 64 would cover
@@ -79,26 +81,39 @@ inline GemmKernel choose_gemm(int64_t M, int64_t N, int64_t K) {
   // only between the widths whose 32 x 32 tiles are at most one per compute unit (64 x 4096 x 4096:
   // 10.2, tiles 7.6) and those that fill the chip in 64 x 64 tiles (B from memory, 33 / 64 x 28672 x
   // 8192: 52 / 57, tiles 43 / 45; 33 / 64 x 128256 x 4096: 110 / 123, tiles 85 / 93; between them
-  // 64 x 8192 x 8192: 19 / 28).
+  // 64 x 8192 x 8192: 19 / 28); with up to 48 rows and narrower weights where the stream is long,
+  // which the tiles' one workgroup per compute unit does not keep up with (B from memory, 33 / 48 / 64
+  // rows x 4096 x 28672: 38 / 39 / 45, tiles 42; 33 x 2048 x 53248: 66 / 72; but 33 x 1024 x 16384: 23 /
+  // 20, 33 x 4096 x 8192: 15.5 / 14.6).
   const int64_t t32 = tiles_of<Tile32>(M, N), t64 = tiles_of<Tile64>(M, N);
-  if ((K % SK) == 0 && (M <= 32 || (M <= 64 && t32 > kCus && t64 <= kCus))) return kGemmSkinny;
+  const bool stream_64 = t32 > kCus || (M <= 48 && N * K > ((int64_t)1 << 25));
+  if ((K % SK) == 0 && (M <= 32 || (M <= 64 && t64 <= kCus && stream_64))) return kGemmSkinny;
 
   // The largest tiles (the fewest expansions and copies per product) that leave little of the chip
   // idle.  256 x 256 tiles of the copy-based kernel from 62 % (2816 x 4096 x 4096, 176 tiles: 96, in
   // 64 x 64 tiles 111; but 4352 x 4096 x 2048, 272 tiles: 106 / 90); 256 x 128 tiles from 80 % (2048 x
   // 4096 x 4096: 80 in 256 x 256, 65; 2048 x 3072 x 4096, 75 %: 59, in 64 x 64 tiles 55); 128 x 128
   // from 87 % (1000 x 4096 x 4096: 76 in 256 x 256, 35, in 64 x 64 38; 2048 x 3072 x 4096, 75 %: 63;
-  // B from memory, 65 / 128 x 28672 x 8192: 116 / 117 in
-  // 256 x 128, 66 / 68, in 64 x 64 74 / 76).
+  // B from memory, 65 / 128 x 28672 x 8192: 116 / 117 in 256 x 128, 66 / 68, in 64 x 64 74 / 76).
   if ((K % GK) == 0 && use_of_chip(M, N, GT, GT) >= 0.62) return kGemmDma;
   if (use_of_chip<Tile256x128>(M, N) >= 0.8) return kGemmTile256x128;
   if (use_of_chip<Tile128>(M, N) >= 0.87) return kGemmTile128;
   // Small products: the smallest tiles that are at most one per compute unit (64 x 1024 x 4096:
   // 7.6 in 32 x 32, 9.9 in 64 x 32, 13.0 in 64 x 64; 128 x 4096 x 4096: 11.4 / 10.6 / 13.1; 200 x
   // 4096 x 4096: 18.8 / 15.1 / 13.9); 32 rows or columns would leave larger tiles half empty (B from
-  // memory, 16 x 28672 x 8256: 43 / 59 / 49, and 120 in 256 x 128).
-  if (M <= 32 || t32 <= kCus) return kGemmTile32;
-  if (N <= 32 || tiles_of<Tile64x32>(M, N) <= kCus) return kGemmTile64x32;
+  // memory, 16 x 28672 x 8256: 43 / 59 / 49, and 120 in 256 x 128).  Along a long K two tiles of
+  // 32 x 32 per compute unit still beat fewer larger ones (B from memory, 65 x 5120 x 8192: 18 / 25 /
+  // 27; 128 x 4096 x 28672: 55 / 75 / 84; 256 x 2048 x 28672: 59 / 76 / 82; but 128 x 4096 x 4096: 11.5 /
+  // 11.4 / 13.6, and with K no whole number of their chunks 256 x 2048 x 11008: 25 / 22).
+  const int64_t t64x32 = tiles_of<Tile64x32>(M, N);
+  const bool two_of_32 = K >= 8192 && (K % Tile32::CK == 0 || t64x32 > kCus);
+  if (M <= 32 || t32 <= (two_of_32 ? 2 : 1) * kCus) return kGemmTile32;
+  if (N <= 32 || t64x32 <= kCus) return kGemmTile64x32;
+  // 64 x 64 tiles, at most one per compute unit: along a long K in eight copies, since four waves wait
+  // for most of every chunk (four / eight copies, B from memory, 128 x 8192 x 8192: 27.6 / 23.1; 192 x
+  // 4096 x 11008: 33.8 / 30.9; 128 x 8192 x 28672: 86 / 72).  Their chunks are twice as long, and a shorter
+  // K may leave the last one half empty (141 x 4652 x 4352: 15.2 / 16.3).
+  if (K >= 8192 && t64 <= kCus) return kGemmTile64Long;
   return kGemmTile64;
 }
 }  // namespace nvfp4_46

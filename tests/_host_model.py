@@ -26,7 +26,8 @@ _SOURCES = [_HERE / "model.cpp", _HERE / "gfx950_on_host.hpp", _CSRC / "block.hp
 RTN, SR, SR_AFTER_RTN_SELECT = 0, 1, 2
 
 # enum GemmKernel
-GEMM_KERNELS = ("staged", "dma", "skinny", "tile32", "tile64x32", "tile64", "tile128", "tile256x128")
+GEMM_KERNELS = ("staged", "dma", "skinny", "tile32", "tile64x32", "tile64", "tile64long",
+                "tile128", "tile256x128")
 
 
 def _compiler() -> str:

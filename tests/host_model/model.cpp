@@ -177,6 +177,7 @@ void hm_tile_shape(int kernel, int32_t *out) {
     case kGemmTile32: return of(Tile32{});
     case kGemmTile64x32: return of(Tile64x32{});
     case kGemmTile64: return of(Tile64{});
+    case kGemmTile64Long: return of(Tile64Long{});
     case kGemmTile128: return of(Tile128{});
     default: return of(Tile256x128{});
   }

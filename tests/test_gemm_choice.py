@@ -22,7 +22,16 @@ EXPECTED = {
     # few rows
     (1, 8192, 8192): "skinny", (16, 8192, 8192): "skinny", (32, 28672, 8192): "skinny",
     (33, 8192, 8192): "skinny", (64, 8192, 8192): "skinny", (64, 4096, 4096): "tile32",
-    (16, 8192, 2880): "tile32", (128, 4096, 4096): "tile64x32", (128, 8192, 8192): "tile64",
+    (16, 8192, 2880): "tile32", (128, 4096, 4096): "tile64x32", (128, 8192, 8192): "tile64long",
+    (200, 4096, 4096): "tile64",
+    # ... along a long K
+    (33, 4096, 28672): "skinny", (48, 2048, 53248): "skinny", (64, 4096, 28672): "tile32",
+    (33, 4096, 8192): "tile32", (33, 4096, 4128): "tile32", (33, 1024, 16384): "tile32",
+    (65, 5120, 28672): "tile32", (96, 5120, 8192): "tile32", (65, 4096, 53248): "tile32",
+    (256, 2048, 28672): "tile32", (384, 1024, 53248): "tile32", (65, 5120, 11008): "tile32",
+    (256, 2048, 11008): "tile64x32", (65, 5120, 8160): "tile64", (65, 8192, 28672): "tile64long",
+    (128, 8192, 28672): "tile64long", (256, 4096, 28672): "tile64long", (512, 2048, 53248): "tile64long",
+    (128, 8192, 2880): "tile64", (192, 8192, 8192): "tile64",
     # large and middling products
     (8192, 8192, 8192): "dma", (2816, 4096, 4096): "dma", (192, 128256, 4096): "dma",
     (512, 28672, 8192): "dma", (4352, 4096, 2048): "tile64", (2048, 4096, 4096): "tile256x128",

@@ -145,6 +145,8 @@ TILE_SHAPES = [
     (304, 848, 96, "ab"), (301, 833, 256, ""), (320, 831, 288, "a"), (2111, 31, 992, ""),
     # 64 x 64
     (701, 799, 32, ""), (705, 769, 512, ""), (704, 784, 800, "ab"),
+    # 64 x 64 in eight copies
+    (129, 4203, 8192, ""), (144, 4208, 8224, "ab"), (705, 1300, 9696, ""),
     # 128 x 128
     (1901, 1920, 288, "b"), (1793, 1921, 256, ""),
     # operands past one die's L2: the tiles in strips, the last one narrower (64 x 64, 128 x 128,
@@ -156,9 +158,9 @@ TILE_SHAPES = [
 
 @pytest.mark.parametrize("M,N,K,tiled", TILE_SHAPES)
 def test_tile_shapes_are_exact_when_every_partial_sum_is_representable(M, N, K, tiled):
-    """Scales 0.5 .. 4 as above: every product is a multiple of 1/8 of magnitude at most 288, so
-    all sums over K <= 4128 are exact in fp32 (2^21 / 2^-3 = 2^24) in any order and the result is
-    the oracle's bit for bit."""
+    """Scales 0.5 .. 4 as above: every product is a multiple of 1/8, and the magnitudes of an element's
+    products add up to less than 2^21 (checked), so all partial sums are exact in fp32 (2^21 / 2^-3 =
+    2^24) in any order and the result is the oracle's bit for bit."""
     _log(f"gemm tile case M={M} N={N} K={K} tiled={tiled!r}")
     rng = np.random.default_rng(M * 7919 + N * 31 + K)
     ca = rng.integers(0, 256, (M, K // 2), dtype=np.uint8)
@@ -178,8 +180,9 @@ def test_tile_shapes_are_exact_when_every_partial_sum_is_representable(M, N, K, 
         s = np.repeat(np.vectorize(value.get)(scales), 16, axis=1)
         return v * (np.repeat(s, 16, axis=0) if lines != codes.shape[0] else s)
 
-    want = decoded(ca, sa, la) @ decoded(cb, sb, lb).T
-    assert np.abs(want).max() < 2.0 ** 21
+    da, db = decoded(ca, sa, la), decoded(cb, sb, lb)
+    want = da @ db.T
+    assert (np.abs(da) @ np.abs(db).T).max() < 2.0 ** 21
     assert np.array_equal(got.cpu().numpy().astype(np.float64), want)
     got16 = B.nvfp4_46_gemm(_dev(ca), _dev(sa), _alpha(1.0), _dev(cb), _dev(sb), _alpha(1.0),
                             out_dtype=B.OUT_BF16, flags=flags)
