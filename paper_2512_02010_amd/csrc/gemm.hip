@@ -55,7 +55,6 @@ NV_DEV TileAt tile_of_workgroup(uint32_t tiles_m, uint32_t tiles_n, uint32_t str
   return TileAt{m, s * strip + (left - m * width)};
 }
 
-constexpr int kGemmThreads = 256;
 constexpr int kCodeRow = GK / 2 + 16;    // bytes per operand row in LDS: 64 of codes + 16 of padding,
                                          // so that 16 lanes reading 16 bytes from 16 rows hit 16
                                          // different bank groups (80 = 5 * 16, 5 coprime to 16)
@@ -796,6 +795,7 @@ constexpr size_t skinny_lds_bytes(int mt) {
   return stages > partials ? stages : partials;
 }
 
+static_assert(64 * skinny_waves(1) == kGemmThreads && 64 * skinny_waves(2) == kGemmThreads, "lanes_of");
 static_assert(skinny_lds_bytes(1) <= 160 * 1024 && skinny_lds_bytes(2) <= 160 * 1024,
               "the stages must fit the LDS");
 
@@ -981,6 +981,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr uint32_t kSkinny16Rows = 48, kSkinny16Stage = kSkinny16Rows * 128 + 64 * 16;   // 7168
 constexpr int kSkinny16Waves = 4, kSkinny16Stages = 2;
 constexpr size_t kSkinny16LdsBytes = (size_t)kSkinny16Waves * kSkinny16Stages * kSkinny16Stage;
+static_assert(64 * kSkinny16Waves == kGemmThreads, "lanes_of");
 static_assert(kSkinny16LdsBytes <= 160 * 1024 && kSkinny16Stages >= 1, "stages must fit the LDS");
 static_assert((size_t)(kSkinny16Waves - 1) * 2 * 4 * 64 * sizeof(float) <= kSkinny16LdsBytes,
               "the partial sums reuse the stages");

@@ -72,7 +72,7 @@ inline double use_of_chip(int64_t M, int64_t N) { return use_of_chip(M, N, S::BM
 
 // Which kernel: times in us, BF16 out, on one card, M x N x K; operands as the calls before left
 // them (all in the memory-side cache), or B from memory where it says so.
-inline GemmKernel choose_gemm(int64_t M, int64_t N, int64_t K) {
+inline GemmKernel fastest_gemm(int64_t M, int64_t N, int64_t K) {
   if (K > ((int64_t)1 << 24)) return kGemmStaged;       // 32-bit lane offsets of the others' copies
 
   // Few rows of A against a large weight: the kernels that stream B, one workgroup per 32 columns.
@@ -115,5 +115,27 @@ inline GemmKernel choose_gemm(int64_t M, int64_t N, int64_t K) {
   // K may leave the last one half empty (141 x 4652 x 4352: 15.2 / 16.3).
   if (K >= 8192 && t64 <= kCus) return kGemmTile64Long;
   return kGemmTile64;
+}
+
+constexpr int kGemmThreads = 256;        // k_gemm, k_gemm_dma, k_gemm_skinny and k_gemm_skinny16
+inline int64_t lanes_of(GemmKernel kernel, int64_t M, int64_t N) {
+  switch (kernel) {
+    case kGemmSkinny: return (N + 31) / 32 * kGemmThreads;
+    case kGemmTile32: return tiles_of<Tile32>(M, N) * Tile32::kThreads;
+    case kGemmTile64x32: return tiles_of<Tile64x32>(M, N) * Tile64x32::kThreads;
+    case kGemmTile64: return tiles_of<Tile64>(M, N) * Tile64::kThreads;
+    case kGemmTile64Long: return tiles_of<Tile64Long>(M, N) * Tile64Long::kThreads;
+    case kGemmTile128: return tiles_of<Tile128>(M, N) * Tile128::kThreads;
+    case kGemmTile256x128: return tiles_of<Tile256x128>(M, N) * Tile256x128::kThreads;
+    default: return tiles_of(M, N, GT, GT) * kGemmThreads;
+  }
+}
+
+// A launch holds fewer than 2^32 lanes: where one row or column of C is that long, the kernels of the
+// fewest lanes per element take it.
+inline GemmKernel choose_gemm(int64_t M, int64_t N, int64_t K) {
+  const GemmKernel fastest = fastest_gemm(M, N, K);
+  if (lanes_of(fastest, M, N) >> 32 == 0) return fastest;
+  return (K % GK) == 0 && K <= ((int64_t)1 << 24) ? kGemmDma : kGemmStaged;
 }
 }  // namespace nvfp4_46

@@ -166,6 +166,9 @@ void hm_rht16(float *v, uint32_t sign_word) {
 // the kernel (enum GemmKernel) that a product of these sizes takes
 int hm_choose_gemm(int64_t M, int64_t N, int64_t K) { return choose_gemm(M, N, K); }
 
+// lanes that such a launch of `kernel` has
+int64_t hm_gemm_lanes(int kernel, int64_t M, int64_t N) { return lanes_of((GemmKernel)kernel, M, N); }
+
 // rows and columns of a workgroup's tile, threads and LDS bytes of one of k_gemm_tile's shapes
 void hm_tile_shape(int kernel, int32_t *out) {
   auto of = [&](auto shape) {

@@ -56,3 +56,20 @@ def test_large_tiles_are_mostly_filled():
             bm, bn = (256, 256) if kernel == "dma" else hm.tile_shape(kernel)[:2]
             assert (-(-M // 64) * 64) * (-(-N // 64) * 64) > 0.61 * (-(-M // bm) * bm) * (-(-N // bn) * bn), (
                 M, N, K, kernel)
+
+
+def test_no_launch_is_too_large():
+    """A launch holds fewer than 2^32 lanes; every size that 256 x 256 tiles of 256 lanes could cover
+    within that is covered, by any kernel."""
+    sizes = [(1, 1 << 31, 32), ((1 << 31), 1, 32), (1, 3 * 10 ** 8, 32), (1, (1 << 30) + 32, 256),
+             (32, 1 << 30, 128), (3 * 10 ** 8, 17, 96), (200, 1 << 31, 160)]
+    rng = random.Random(4649)
+    while len(sizes) < 20000:
+        M, N = (int(2 ** rng.uniform(0, 31)) for _ in range(2))
+        K = 32 * int(2 ** rng.uniform(0, 20))
+        if -(-M // 256) * -(-N // 256) * 256 < 1 << 32:
+            sizes.append((M, N, K))
+    for M, N, K in sizes:
+        kernel = hm.choose_gemm(M, N, K)
+        assert hm.gemm_lanes(kernel, M, N) < 1 << 32, (M, N, K, kernel)
+        assert kernel != "dma" or (K % 128 == 0 and K <= 1 << 24), (M, N, K)

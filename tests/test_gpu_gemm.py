@@ -440,6 +440,25 @@ def test_gemm_operand_larger_than_four_gibibytes():
     assert (np.abs(gsel - c_ref) <= _tolerance(c_ref, c_abs, K, B.OUT_F32)).all()
 
 
+def test_gemm_with_more_columns_than_a_launch_of_small_tiles_holds():
+    """One row of A against 2^28 + 96 rows of B, K = 32: in 32 x 32 tiles the launch would need 2^32 lanes.
+    Every scale is 1, so each element is a sum of 32 multiples of 0.25, exact in any order."""
+    N, K = (1 << 28) + 96, 32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4652)
+    ca = torch.randint(0, 256, (1, K // 2), dtype=torch.uint8, device="cuda", generator=g)
+    cb = torch.randint(0, 256, (N, K // 2), dtype=torch.uint8, device="cuda", generator=g)
+    sa = torch.full((1, K // 16), 0x38, dtype=torch.uint8, device="cuda")
+    sb = torch.full((N, K // 16), 0x38, dtype=torch.uint8, device="cuda")
+    _log(f"gemm case M=1 N={N} K={K}")
+    got = B.nvfp4_46_gemm(ca, sa, _alpha(1.0), cb, sb, _alpha(1.0), out_dtype=B.OUT_F32)
+    torch.cuda.synchronize()
+    cols = np.concatenate([np.arange(0, N, 99991), [255, 256, N - 257, N - 2, N - 1]])
+    rows = cb[torch.from_numpy(cols).cuda()].cpu().numpy()
+    want = ref.gemm(ca.cpu().numpy(), sa.cpu().numpy(), 1.0, rows, np.full((len(cols), K // 16), 0x38, np.uint8), 1.0)
+    assert np.array_equal(got[0, torch.from_numpy(cols).cuda()].double().cpu().numpy(), want[0])
+
+
 @pytest.mark.parametrize("block2d", [True, False])
 def test_linear_layer_module(block2d):
     """paper_2512_02010_amd.linear strings the library calls together as Fig. 3 does; each
