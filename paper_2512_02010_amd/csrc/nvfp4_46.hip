@@ -663,7 +663,13 @@ __global__ __launch_bounds__(kThreads) void k_tile(
   // place every call was made twice and its other half dropped, and the words of both columns sat in
   // registers (224 of them, two waves per SIMD).  Columnwise Hadamard + SR on 8192 x 8192:
   // 138 -> 110 us with its tensor scale, both orientations with SR 200 -> 166.
-  constexpr bool kWords = ROUNDING != kRTN;
+  // Fake-quant of fp32 keeps its tile in LDS as well, 32 KiB that with 32 KiB of words leave two
+  // workgroups per compute unit: that pays for the squared-error rule alone, whose calls are the most
+  // to hide (columnwise, 8192 x 8192, words from LDS / drawn by their lane: 4/6 115 / 120 us, with the
+  // transform 123 / 131; by absolute error 113 / 101, always 6 96 / 86, with the transform 102 / 90).
+  // There the lane draws the words of its two columns itself, half of every call for nothing.
+  constexpr bool kWords = ROUNDING != kRTN && !(XF32 && OUT == kOutFake && SELECT != kSel46);
+  constexpr bool kDrawn = ROUNDING != kRTN && !kWords;
   __shared__ uint4 words[kWords ? TR * TC / 4 : 1];                   // [TR][TC / 4]
 
   const TileCoord tcd = tile_of_workgroup(rows, cols, map);
@@ -768,7 +774,7 @@ __global__ __launch_bounds__(kThreads) void k_tile(
     const int64_t gc = c0 + 2 * cp;               // even column of the pair
     if (gr >= rows || gc >= cols) continue;       // (cols is even, so the pair is in or out together)
     float va[16], vb[16];
-    uint32_t u[16];
+    uint32_t ua[16], ub[16];
     // the lane's two column blocks (transformed) out of the tile or memory
     auto take = [&](float (&wa)[16], float (&wb)[16]) {
 #pragma unroll
@@ -799,17 +805,34 @@ __global__ __launch_bounds__(kThreads) void k_tile(
           uu[i] = reinterpret_cast<const uint32_t *>(words)[(rb * 16 + i) * TC + 2 * cp + column];
       }
     };
+    auto draw = [&](uint32_t (&uua)[16], uint32_t (&uub)[16]) {         // both columns of the pair
+      // element (row, col) has flat index g = row*cols + col; gc is even and cols a multiple of 4,
+      // so the pair's words come from one call
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const uint64_t g = (uint64_t)(gr + i) * (uint64_t)cols + (uint64_t)gc;
+        uint32_t w[4];
+        sr_words4(sr_seed, g >> 2, w);
+        uua[i] = (g & 2u) ? w[2] : w[0];
+        uub[i] = (g & 2u) ? w[3] : w[1];
+      }
+    };
     take(va, vb);
-    random_words(0, u);
-    BlockResult ra = quantize_block<ROUNDING, SELECT>(va, u, sc, tab, [&](float (&w)[16], uint32_t (&uu)[16]) {
+    if (kDrawn) draw(ua, ub);
+    random_words(0, ua);
+    BlockResult ra = quantize_block<ROUNDING, SELECT>(va, ua, sc, tab, [&](float (&w)[16], uint32_t (&uu)[16]) {
       float other[16];
+      uint32_t other_u[16];
       take(w, other);
+      if (kDrawn) draw(uu, other_u);
       random_words(0, uu);
     });
-    random_words(1, u);
-    BlockResult rbk = quantize_block<ROUNDING, SELECT>(vb, u, sc, tab, [&](float (&w)[16], uint32_t (&uu)[16]) {
+    random_words(1, ub);
+    BlockResult rbk = quantize_block<ROUNDING, SELECT>(vb, ub, sc, tab, [&](float (&w)[16], uint32_t (&uu)[16]) {
       float other[16];
+      uint32_t other_u[16];
       take(other, w);
+      if (kDrawn) draw(other_u, uu);
       random_words(1, uu);
     });
     if (OUT == kOutCodes) {

@@ -27,7 +27,7 @@ def _report(source: str, part_macro: str, part: int):
         if m:
             cur = kernels.setdefault(m.group(1), {})
             continue
-        m = re.search(r"remark:\s+(VGPRs|AGPRs|ScratchSize \[bytes/lane\]|Occupancy \[waves/SIMD\]): (\d+)", line)
+        m = re.search(r"remark:\s+(VGPRs|AGPRs|ScratchSize \[bytes/lane\]|Occupancy \[waves/SIMD\]|LDS Size \[bytes/block\]): (\d+)", line)
         if m and cur is not None:
             cur[m.group(1).split(" ")[0]] = int(m.group(2))
     return kernels
@@ -55,3 +55,16 @@ def test_tile_kernel_budgets():
     assert len(tile) == 6 * 4, list(tile)          # six shapes x (K whole or ragged) x output type
     assert all(v["ScratchSize"] == 0 for v in tile.values()), tile
     assert all(v["Occupancy"] >= (2 if "ILi4ELi2E" in k else 4) for k, v in tile.items()), tile
+
+
+def test_fp32_stochastic_fake_quant_leaves_room_for_four_workgroups():
+    """The random words of a tile take 32 KiB of LDS.  Next to fp32 fake-quant's own 32 KiB they would leave
+    two workgroups per compute unit, which pays for the squared-error rule alone."""
+    tile = {k: v for k, v in _report("nvfp4_46.hip", "NVFP4_46_PART", 5).items() if "6k_tileI" in k}
+    assert len(tile) == 5 * 5, list(tile)          # five selection rules x five variants
+    for name, v in tile.items():
+        m = re.search(r"6k_tileILb(\d)ELi(\d)ELi(\d)ELb(\d)ELb(\d)ELi(\d)E", name)
+        xf32, rounding, select, rht, want_row, out = map(int, m.groups())
+        assert (xf32, rounding) == (1, 1) and v["ScratchSize"] == 0
+        if out == 1 and select != 0:               # kOutFake, not kSel46
+            assert v["LDS"] <= 160 * 1024 // 4, (name, v)
