@@ -23,6 +23,7 @@
 #include "launch.hpp"
 #include "nvfp4_46.h"
 #include "nvfp4_46_fused.h"
+#include "small_tensors.hpp"
 
 // The quantizing kernels exist once per (input type, rounding mode, selection rule, ...):
 // several hundred instantiations.  To compile them side by side this file can be built in
@@ -269,7 +270,7 @@ __global__ __launch_bounds__(kThreads) void k_amax_plain(const uint4 *__restrict
 
 // A small tensor, one workgroup for all of it: nothing has to be agreed on between workgroups, so
 // no scratch words, no atomics and no launches before and after.  Sixteen waves with eight
-// loads each in flight take what one compute unit can (256 KiB in 3.3 us); kOneWgBytes says
+// loads each in flight take what one compute unit can (256 KiB in 3.3 us); small_tensors.hpp says
 // where that ends.
 constexpr int kSmallThreads = 1024;
 template <bool XF32>
@@ -545,8 +546,8 @@ __global__ __launch_bounds__(kThreads) void k_flat(
 
 // Tensor scale and rowwise codes of a small tensor in one launch: every workgroup reads the whole
 // tensor for its maximum (it comes out of the L2 after the first), then quantizes its own 1024
-// blocks, one per lane.  16 x 8192 BF16: 6.4 us, where the two kernels took 4.8 + 4.0 and the gap
-// between them; kScaleQuantizeBytes says where that ends.
+// blocks, one per lane.  16 x 8192 BF16: 6.9 us, where the two kernels and the gap between them took
+// 8.1 (in a replayed graph); small_tensors.hpp says where that ends.
 template <bool XF32, int SELECT>
 __global__ __launch_bounds__(kSmallThreads) void k_scale_quantize_small(
     const uint4 *__restrict__ x, float *__restrict__ alpha_out, uint2 *__restrict__ codes,
@@ -1538,15 +1539,6 @@ static int check_workspace(const void *workspace, size_t bytes) {
   return aligned16(workspace) ? NVFP4_OK : NVFP4_ERR_ALIGN;
 }
 
-// Where the small-tensor kernels end, by kernel durations (BF16 rows of 8192; a gap of 1 to 2 us
-// passes between dependent kernels, and a launch costs the host 3.3 us):
-//   k_scale_small          128 KiB 2.7 us, 256 KiB 3.3, 512 KiB 5.1, 1 MiB 8.7, 2 MiB 15.6
-//   instead, three launches    1.4 + 3.6 + 1.4 us and two gaps: up to 1 MiB
-//   instead, k_amax_plain with scratch words    4.8 to 5.0 us throughout: up to 256 KiB
-//   k_scale_quantize_small 256 KiB 6.4 us, 512 KiB 8.0, 1 MiB 11.6
-//   instead, scale and k_flat  3.3 to 5.0 + 3.9 us and a gap: up to 512 KiB
-constexpr int64_t kOneWgBytes = 1 << 20, kOneWgBytesWs = 256 << 10, kScaleQuantizeBytes = 512 << 10;
-
 // Eq. (1) for all three entry points.  scratch == nullptr: the reduction runs on the caller's
 // alpha word between a zeroing launch and a finishing launch.  Otherwise scratch points at
 // kScratchWords zeroed words and one launch does it all (see AmaxFinish).
@@ -1561,7 +1553,7 @@ static int tensor_scale(const void *x, const nvfp4_46_params *p, float *alpha, u
   const bool xf32 = p->x_dtype == NVFP4_X_F32;
   const uint4 *x4 = static_cast<const uint4 *>(x);
   const int64_t bytes = n * (xf32 ? 4 : 2);
-  if (!p->rht && bytes <= (scratch ? kOneWgBytesWs : kOneWgBytes)) {
+  if (!p->rht && scale_in_one_workgroup(bytes, scratch != nullptr)) {
     const uint32_t n16 = (uint32_t)(bytes / 16);       // n is a multiple of 8 by the shape checks
     return xf32 ? launch(k_scale_small<true>, dim3(1), dim3(kSmallThreads), s, x4, n16, alpha, p->fp8_max)
                 : launch(k_scale_small<false>, dim3(1), dim3(kSmallThreads), s, x4, n16, alpha, p->fp8_max);
@@ -1690,7 +1682,7 @@ int nvfp4_46_scale_quantize(const void *x, const nvfp4_46_params *p, float *alph
   const bool xf32 = p->x_dtype == NVFP4_X_F32;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (p->layout == NVFP4_ROWWISE && p->rounding == NVFP4_RTN && !p->rht && !p->block2d &&
-      p->rows * p->cols * (xf32 ? 4 : 2) <= kScaleQuantizeBytes) {
+      scale_and_codes_in_one_launch(p->rows * p->cols * (xf32 ? 4 : 2), xf32, workspace != nullptr)) {
     FlatArgs a{xf32, static_cast<const uint4 *>(x), nullptr, static_cast<uint2 *>(codes_row),
                static_cast<uint8_t *>(scales_row), static_cast<uint8_t *>(choice_row), nullptr,
                nullptr, p->rows * p->cols / 16, (uint32_t)(p->cols / 16), 0, 0, s,

@@ -1,8 +1,8 @@
 """The kernels' per-block code compiled for the host (tests/host_model/), behind ctypes.
 
 Test infrastructure.  ``csrc/block.hpp`` and ``csrc/codec.hpp`` -- the code every quantizing
-kernel runs per block -- and ``csrc/gemm_shapes.hpp`` -- the choice of the matrix product's
-kernel -- are compiled with the host compiler, the gfx950 conversion
+kernel runs per block -- and ``csrc/gemm_shapes.hpp`` and ``csrc/small_tensors.hpp`` -- the host
+side's choices of kernel -- are compiled with the host compiler, the gfx950 conversion
 instructions replaced by plain definitions of what they compute, so that CPU tests can put
 the GPU path's block logic next to the oracle on inputs of any range without a GPU.
 """
@@ -21,7 +21,7 @@ _ROOT = _HERE.parent.parent
 _CSRC = _ROOT / "paper_2512_02010_amd" / "csrc"
 _SO = _HERE / "_build" / "libhost_model.so"
 _SOURCES = [_HERE / "model.cpp", _HERE / "gfx950_on_host.hpp", _CSRC / "block.hpp", _CSRC / "codec.hpp",
-            _CSRC / "gemm_shapes.hpp"]
+            _CSRC / "gemm_shapes.hpp", _CSRC / "small_tensors.hpp"]
 
 RTN, SR, SR_AFTER_RTN_SELECT = 0, 1, 2
 
@@ -79,6 +79,10 @@ def lib() -> C.CDLL:
         L.hm_choose_gemm.argtypes = [C.c_int64, C.c_int64, C.c_int64]
         L.hm_gemm_lanes.restype = C.c_int64
         L.hm_gemm_lanes.argtypes = [C.c_int, C.c_int64, C.c_int64]
+        L.hm_scale_in_one_workgroup.restype = C.c_int
+        L.hm_scale_in_one_workgroup.argtypes = [C.c_int64, C.c_int]
+        L.hm_scale_and_codes_in_one_launch.restype = C.c_int
+        L.hm_scale_and_codes_in_one_launch.argtypes = [C.c_int64, C.c_int, C.c_int]
         L.hm_tile_shape.restype = None
         L.hm_tile_shape.argtypes = [C.c_int, C.POINTER(C.c_int32)]
         _lib = L
@@ -173,3 +177,11 @@ def tile_shape(kernel: str):
     v = (C.c_int32 * 4)()
     lib().hm_tile_shape(GEMM_KERNELS.index(kernel), v)
     return tuple(v)
+
+
+def scale_in_one_workgroup(nbytes: int, has_scratch: bool) -> bool:
+    return bool(lib().hm_scale_in_one_workgroup(nbytes, has_scratch))
+
+
+def scale_and_codes_in_one_launch(nbytes: int, xf32: bool, has_scratch: bool) -> bool:
+    return bool(lib().hm_scale_and_codes_in_one_launch(nbytes, xf32, has_scratch))

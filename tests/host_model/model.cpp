@@ -1,10 +1,11 @@
-// Test infrastructure: the kernels' per-block code (csrc/block.hpp) and the matrix product's choice of
-// kernel (csrc/gemm_shapes.hpp) compiled for the host and exported with a C interface.  See
+// Test infrastructure: the kernels' per-block code (csrc/block.hpp) and the host side's choices of
+// kernel (csrc/gemm_shapes.hpp, csrc/small_tensors.hpp) compiled for the host and exported with a C interface.  See
 // gfx950_on_host.hpp.
 #include "gfx950_on_host.hpp"
 
 #include "block.hpp"
 #include "gemm_shapes.hpp"
+#include "small_tensors.hpp"
 
 using namespace nvfp4_46;
 
@@ -165,6 +166,14 @@ void hm_rht16(float *v, uint32_t sign_word) {
 
 // the kernel (enum GemmKernel) that a product of these sizes takes
 int hm_choose_gemm(int64_t M, int64_t N, int64_t K) { return choose_gemm(M, N, K); }
+
+// whether a tensor's scale (with or without scratch words), its scale and codes, take one launch
+int hm_scale_in_one_workgroup(int64_t bytes, int has_scratch) {
+  return scale_in_one_workgroup(bytes, has_scratch != 0);
+}
+int hm_scale_and_codes_in_one_launch(int64_t bytes, int xf32, int has_scratch) {
+  return scale_and_codes_in_one_launch(bytes, xf32 != 0, has_scratch != 0);
+}
 
 // lanes that such a launch of `kernel` has
 int64_t hm_gemm_lanes(int kernel, int64_t M, int64_t N) { return lanes_of((GemmKernel)kernel, M, N); }

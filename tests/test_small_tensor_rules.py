@@ -1,0 +1,29 @@
+"""CPU: up to which size a tensor takes the small-tensor kernels (csrc/small_tensors.hpp, compiled for the
+host), on both sides of every line, at sizes where both were timed."""
+import pytest
+
+from . import _host_model as hm
+
+KIB = 1024
+
+
+@pytest.mark.parametrize("kib,with_scratch,without", [(16, True, True), (128, True, True), (160, False, True),
+                                                      (256, False, True), (512, False, True),
+                                                      (640, False, False), (1024, False, False)])
+def test_tensor_scale_in_one_workgroup(kib, with_scratch, without):
+    """One workgroup reads at what one compute unit can: 768 KiB take it 8.9 us (15 from memory), three
+    launches 7.2 (7.7); with scratch words, where it saves no launch, 160 KiB from memory 5.7 / 5.1."""
+    assert hm.scale_in_one_workgroup(kib * KIB, True) == with_scratch
+    assert hm.scale_in_one_workgroup(kib * KIB, False) == without
+
+
+@pytest.mark.parametrize("kib,bf16,f32", [(64, True, True), (256, True, True), (320, True, False),
+                                          (384, True, False), (448, False, False), (512, False, False),
+                                          (640, False, False)])
+def test_scale_and_codes_in_one_launch(kib, bf16, f32):
+    """Every workgroup reads the whole tensor: 512 KiB take 9.5 us, the two launches with scratch words
+    8.1, the four without 9.8."""
+    assert hm.scale_and_codes_in_one_launch(kib * KIB, False, True) == bf16
+    assert hm.scale_and_codes_in_one_launch(kib * KIB, True, True) == f32
+    for xf32 in (False, True):
+        assert hm.scale_and_codes_in_one_launch(kib * KIB, xf32, False) == (kib <= 512)
