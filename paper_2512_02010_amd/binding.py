@@ -28,7 +28,7 @@ STATUS_NAMES = {0: "NVFP4_OK", 1: "NVFP4_ERR_NULL", 2: "NVFP4_ERR_SHAPE", 3: "NV
 
 EXPORTS = (
     "nvfp4_46_tensor_scale", "nvfp4_46_tensor_scale_ws", "nvfp4_46_tensor_scale_static",
-    "nvfp4_46_quantize", "nvfp4_46_dequantize", "nvfp4_46_fake_quant",
+    "nvfp4_46_quantize", "nvfp4_46_scale_quantize", "nvfp4_46_dequantize", "nvfp4_46_fake_quant",
     "nvfp4_46_gemm", "nvfp4_46_status_string", "nvfp4_46_debug_e2m1_rtn_range", "nvfp4_46_debug_e4m3_range",
     "nvfp4_46_debug_decode_tables", "nvfp4_46_debug_bf16_range", "nvfp4_46_debug_e2m1_sr",
     "nvfp4_46_debug_philox",
@@ -178,6 +178,14 @@ def quantize_raw(x, params, alpha, codes_row, scales_row, codes_col, scales_col,
                                    _stream(stream))
 
 
+def scale_quantize_raw(x, params, alpha, workspace, workspace_bytes: int, codes_row, scales_row,
+                       codes_col, scales_col, choice_row, choice_col, stream=None) -> int:
+    return lib().nvfp4_46_scale_quantize(_ptr(x), C.byref(params) if params is not None else None,
+                                         _ptr(alpha), _ptr(workspace), workspace_bytes, _ptr(codes_row),
+                                         _ptr(scales_row), _ptr(codes_col), _ptr(scales_col),
+                                         _ptr(choice_row), _ptr(choice_col), _stream(stream))
+
+
 def dequantize_raw(codes, scales, alpha, rows, cols, layout, out, stream=None) -> int:
     return lib().nvfp4_46_dequantize(_ptr(codes), _ptr(scales), _ptr(alpha), rows, cols, layout,
                                      _ptr(out), _stream(stream))
@@ -286,11 +294,9 @@ def nvfp4_46_scale_quantize(x: torch.Tensor, workspace: torch.Tensor | None = No
     o = alloc_outputs(rows, cols, layout, x.device, want_choice, block2d)
     p = make_params(rows, cols, layout, rounding, select, rht, sr_seed, rht_seed, fp8_max,
                     block2d, x_dtype_of(x))
-    _check(lib().nvfp4_46_scale_quantize(
-        _ptr(x), C.byref(p), _ptr(alpha), _ptr(workspace),
-        workspace.numel() if workspace is not None else 0, _ptr(o["codes_row"]),
-        _ptr(o["scales_row"]), _ptr(o["codes_col"]), _ptr(o["scales_col"]), _ptr(o["choice_row"]),
-        _ptr(o["choice_col"]), _stream(stream)), "nvfp4_46_scale_quantize")
+    _check(scale_quantize_raw(x, p, alpha, workspace, workspace.numel() if workspace is not None else 0,
+                              o["codes_row"], o["scales_row"], o["codes_col"], o["scales_col"],
+                              o["choice_row"], o["choice_col"], stream), "nvfp4_46_scale_quantize")
     o["alpha"] = alpha
     return o
 

@@ -1673,11 +1673,12 @@ int nvfp4_46_scale_quantize(const void *x, const nvfp4_46_params *p, float *alph
                             void *workspace, size_t workspace_bytes, void *codes_row,
                             void *scales_row, void *codes_col, void *scales_col,
                             void *choice_row, void *choice_col, void *stream) {
-  if (!alpha) return NVFP4_ERR_NULL;
-  int rc = check_params(x, p, false);
+  // in the order of the two calls
+  int rc = workspace ? check_workspace(workspace, workspace_bytes) : NVFP4_OK;
+  if (rc == NVFP4_OK && !alpha) rc = NVFP4_ERR_NULL;
+  if (rc == NVFP4_OK) rc = check_params(x, p, false);
   if (rc == NVFP4_OK)
     rc = check_outputs(p, codes_row, scales_row, codes_col, scales_col, choice_row, choice_col);
-  if (rc == NVFP4_OK && workspace) rc = check_workspace(workspace, workspace_bytes);
   if (rc != NVFP4_OK) return rc;
   const bool xf32 = p->x_dtype == NVFP4_X_F32;
   hipStream_t s = static_cast<hipStream_t>(stream);

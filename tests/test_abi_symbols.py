@@ -11,17 +11,23 @@ from paper_2512_02010_amd import binding as B
 
 ROOT = Path(__file__).resolve().parent.parent
 HEADER = (ROOT / "include" / "nvfp4_46.h").read_text()
+FUSED_HEADER = (ROOT / "include" / "nvfp4_46_fused.h").read_text()
 
 
-def _declared():
-    names = re.findall(r"^(?:int|const char \*)\s*(nvfp4_46_\w+)\s*\(", HEADER, flags=re.M)
+def _declared(header=HEADER + FUSED_HEADER):
+    names = re.findall(r"^(?:int|const char \*)\s*(nvfp4_46_\w+)\s*\(", header, flags=re.M)
     return sorted(set(names))
+
+
+def test_every_header_is_covered():
+    assert sorted(p.name for p in (ROOT / "include").glob("*.h")) == ["nvfp4_46.h", "nvfp4_46_fused.h"]
+    assert _declared(FUSED_HEADER) == ["nvfp4_46_scale_quantize"]
 
 
 def test_library_exports_every_declared_symbol():
     L = B.lib()
     names = _declared()
-    assert len(names) == 14
+    assert len(_declared(HEADER)) == 14 and len(names) == 15
     assert sorted(B.EXPORTS) == names
     for n in names:
         assert hasattr(L, n), n
@@ -112,6 +118,39 @@ def test_other_entry_points_validation_codes():
     L = B.lib()
     assert L.nvfp4_46_debug_e2m1_rtn_range(0, 16, None, None) == 1
     assert L.nvfp4_46_debug_e4m3_range(0, 0, C.c_void_p(P), None) == 2
+
+
+def _sq(params, x=P, alpha=P, ws=P, ws_bytes=4352, cr=P, sr=P, cc=None, sc=None, hr=None, hc=None):
+    return B.scale_quantize_raw(x, params, alpha, ws, ws_bytes, cr, sr, cc, sc, hr, hc, stream=0)
+
+
+def test_joined_call_has_the_errors_of_its_two_calls():
+    """nvfp4_46_scale_quantize refuses what nvfp4_46_tensor_scale(_ws) or nvfp4_46_quantize would; where
+    several arguments are wrong, with the status of the call, and the check, that comes first."""
+    ok = B.make_params(32, 64)
+    both = B.make_params(32, 64, layout=B.BOTH)
+    for ws, n in ((P, 4352), (None, 0)):
+        w = dict(ws=ws, ws_bytes=n)
+        assert _sq(None, **w) == 1 and _sq(ok, x=None, **w) == 1 and _sq(ok, alpha=None, **w) == 1
+        assert _sq(B.make_params(0, 64), **w) == 2 and _sq(B.make_params(32, 72), **w) == 2
+        assert _sq(B.make_params(1 << 30, 1 << 12), **w) == 2
+        assert _sq(B.make_params(40, 64, block2d=1), **w) == 2
+        assert _sq(ok, x=P + 2, **w) == 3
+        assert _sq(B.make_params(32, 64, layout=0), **w) == 4 and _sq(B.make_params(32, 64, select=9), **w) == 4
+        assert _sq(B.make_params(32, 64, fp8_max=0.0), **w) == 4
+        assert _sq(B.make_params(32, 64, layout=B.BOTH, rht=1), cc=P, sc=P, **w) == 5
+        assert _sq(B.make_params(32, 64, block2d=1, rht=1), **w) == 5
+        # the quantizer's own checks
+        assert _sq(ok, cr=None, **w) == 1 and _sq(ok, sr=None, **w) == 1 and _sq(both, **w) == 1
+        assert _sq(ok, cr=P + 8, **w) == 3 and _sq(ok, hr=P + 1, **w) == 3
+        assert _sq(ok, cc=P, sc=P, **w) == 4 and _sq(ok, hc=P, **w) == 4
+        # ... come after those of the tensor scale
+        assert _sq(B.make_params(32, 72), cr=None, **w) == 2 and _sq(ok, x=P + 2, cc=P, sc=P, **w) == 3
+    # the workspace, and its checks first
+    assert _sq(ok, ws_bytes=4096) == 4 and _sq(ok, ws=P + 4) == 3
+    for more in (dict(x=None), dict(alpha=None), dict(cr=None), dict(x=P + 2)):
+        assert _sq(ok, ws_bytes=4096, **more) == B.tensor_scale_ws_raw(P, ok, None, P, 4096, stream=0) == 4
+        assert _sq(ok, ws=P + 4, **more) == B.tensor_scale_ws_raw(P, ok, None, P + 4, 4352, stream=0) == 3
 
 
 def test_missing_library_fails_loudly(monkeypatch, tmp_path):
