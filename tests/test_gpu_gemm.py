@@ -14,6 +14,7 @@ import torch
 from oracle import ref
 from paper_2512_02010_amd import binding as B
 from paper_2512_02010_amd import workloads as wl
+from tests import _host_model as hm
 
 pytestmark = pytest.mark.gpu
 
@@ -68,10 +69,10 @@ def check_gemm(A, Bm, out_dtype, tag):
 
 SHAPES = [(32, 32, 32), (1, 1, 64), (100, 70, 160), (256, 256, 128), (257, 255, 384),
           (300, 520, 1056), (512, 768, 2048), (200, 300, 256),
-          # few rows of A and K a multiple of 256: the kernel that streams B
+          # few rows of A and K a multiple of 256: up to 32 rows the kernels that stream B (up to 16 the
+          # 16-row one), then 32 x 32 tiles
           (1, 40, 256), (16, 32, 512), (33, 100, 1024), (64, 1000, 2304), (100, 96, 768),
           (128, 257, 512), (129, 64, 512),
-          # at most 16 rows of A: the 16-row variant of that kernel
           (7, 45, 256), (16, 64, 768), (9, 1000, 2304), (3, 17, 4096), (17, 33, 256),
           # more rows of A, ragged tiles
           (257, 255, 768), (384, 300, 256), (511, 40, 1024), (513, 40, 512)]
@@ -119,8 +120,8 @@ def test_gemm_is_exact_when_every_partial_sum_is_representable():
 
 @pytest.mark.parametrize("M", [1, 5, 16, 17, 30, 64, 128, 200, 512])
 def test_small_batch_gemm_is_exact_when_every_partial_sum_is_representable(M):
-    """The same argument for the kernels that take few rows of A (16-row, 32-row, 64-row and
-    128-row variants): scales 0.5 .. 4, so every sum is exact in fp32 in any order."""
+    """The same argument for few rows of A (the 16-row and 32-row streaming kernels, then 32 x 32 tiles):
+    scales 0.5 .. 4, so every sum is exact in fp32 in any order."""
     rng = np.random.default_rng(4600 + M)
     N, K = 77, 768
     ca = rng.integers(0, 256, (M, K // 2), dtype=np.uint8)
@@ -134,34 +135,36 @@ def test_small_batch_gemm_is_exact_when_every_partial_sum_is_representable(M):
     assert np.array_equal(got.cpu().numpy().astype(np.float64), c_ref)
 
 
-# Every tile shape of the kernel for smaller tiles (the dispatch picks it by the sizes), at the
-# edges of tiles and of the chunks of the contraction axis (512, 256 and 128 indices), with K
-# whole and ragged; the operands in `tiled` carry one scale line per 16 rows.
-TILE_SHAPES = [
-    # 32 x 32
-    (1, 1, 32, ""), (31, 33, 64, ""), (32, 64, 512, "ab"), (33, 32, 544, "b"), (250, 997, 1056, ""),
-    (7, 9001, 4128, ""),
-    # 64 x 32
-    (304, 848, 96, "ab"), (301, 833, 256, ""), (320, 831, 288, "a"), (2111, 31, 992, ""),
-    # 64 x 64
-    (701, 799, 32, ""), (705, 769, 512, ""), (704, 784, 800, "ab"),
-    # 64 x 64 in eight copies
-    (129, 4203, 8192, ""), (144, 4208, 8224, "ab"), (705, 1300, 9696, ""),
-    # 128 x 128
-    (1901, 1920, 288, "b"), (1793, 1921, 256, ""),
-    # operands past one die's L2: the tiles in strips, the last one narrower (64 x 64, 128 x 128,
-    # 256 x 128)
-    (1100, 1500, 4128, ""), (1857, 1930, 2592, ""), (2050, 2944, 1824, "b"),
-    # 256 x 128
-    (2049, 2945, 96, ""), (2304, 2944, 128, "b"), (2064, 2931, 416, "a")]
+# Every kernel that is picked by the sizes, at the edges of its tiles and of its chunks of the
+# contraction axis (128 to 512 indices), with K whole and, where it may be, ragged; the operands
+# in `tiled` carry one scale line per 16 rows.
+TILE_SHAPES = {
+    "tile32": [(1, 1, 32, ""), (31, 33, 64, ""), (48, 64, 512, "ab"), (33, 32, 544, "b"),
+               (250, 997, 1056, ""), (7, 9001, 4128, ""), (2111, 31, 992, ""), (66, 4100, 8192, "")],
+    "tile64x32": [(304, 848, 96, "ab"), (301, 833, 256, ""), (320, 831, 288, "a"), (17000, 31, 992, "")],
+    "tile64": [(701, 799, 32, ""), (705, 769, 512, ""), (704, 784, 800, "ab"), (64, 17008, 96, "ab"),
+               (1100, 1500, 4128, "")],          # (operands past one die's L2: the tiles in strips, the last narrower)
+    "tile64long": [(129, 4203, 8192, ""), (144, 4208, 8224, "ab"), (705, 1300, 9696, "")],
+    "tile128": [(1901, 1920, 288, "b"), (1793, 1921, 256, ""), (1857, 1930, 2592, ""), (100, 28677, 320, "")],
+    "tile256x128": [(2177, 2945, 96, ""), (2304, 2944, 128, "b"), (2192, 2945, 416, "a"),
+                    (2177, 2960, 1824, "b")],
+    # the kernels that stream B: 16 rows, 32 rows, 64 rows
+    "skinny": [(16, 1008, 512, "ab"), (5, 4099, 768, ""), (32, 64, 512, "ab"), (31, 4099, 256, ""),
+               (33, 4100, 256, ""), (50, 8203, 768, ""), (64, 4112, 768, "ab"), (48, 16384, 256, "a"),
+               (63, 5008, 512, "b")],
+    # 256 x 256 tiles by copies: one, two and three chunks
+    "dma": [(3300, 3400, 128, ""), (3300, 3400, 256, ""), (3311, 3393, 384, ""), (3312, 3400, 256, "a"),
+            (3300, 3408, 384, "b"), (3312, 3408, 128, "ab")]}
+TILE_SHAPES = [(kernel, *size) for kernel, sizes in TILE_SHAPES.items() for size in sizes]
 
 
-@pytest.mark.parametrize("M,N,K,tiled", TILE_SHAPES)
-def test_tile_shapes_are_exact_when_every_partial_sum_is_representable(M, N, K, tiled):
+@pytest.mark.parametrize("kernel,M,N,K,tiled", TILE_SHAPES)
+def test_tile_shapes_are_exact_when_every_partial_sum_is_representable(kernel, M, N, K, tiled):
     """Scales 0.5 .. 4 as above: every product is a multiple of 1/8, and the magnitudes of an element's
     products add up to less than 2^21 (checked), so all partial sums are exact in fp32 (2^21 / 2^-3 =
     2^24) in any order and the result is the oracle's bit for bit."""
-    _log(f"gemm tile case M={M} N={N} K={K} tiled={tiled!r}")
+    assert hm.choose_gemm(M, N, K) == kernel
+    _log(f"gemm {kernel} case M={M} N={N} K={K} tiled={tiled!r}")
     rng = np.random.default_rng(M * 7919 + N * 31 + K)
     ca = rng.integers(0, 256, (M, K // 2), dtype=np.uint8)
     cb = rng.integers(0, 256, (N, K // 2), dtype=np.uint8)
@@ -321,11 +324,12 @@ def test_linear_layer_three_products_of_figure_3():
             "WGRAD", 0.25)
 
 
-@pytest.mark.parametrize("K", [512, 544])      # the copy-based and the register-staged kernel
-def test_gemm_can_be_captured_in_a_graph_and_replayed(K):
-    A, Bm = _operand("c3", 320, K), _operand("c2", 272, K)
+@pytest.mark.parametrize("M,N,K", [(320, 272, 512), (320, 272, 544),        # small tiles, K whole and ragged
+                                   (20, 272, 512), (3300, 3400, 256)])       # streaming B; 256 x 256 tiles
+def test_gemm_can_be_captured_in_a_graph_and_replayed(M, N, K):
+    A, Bm = _operand("c3", M, K), _operand("c2", N, K)
     args = [_dev(A[0]), _dev(A[1]), _alpha(A[2]), _dev(Bm[0]), _dev(Bm[1]), _alpha(Bm[2])]
-    out = torch.empty((320, 272), dtype=torch.float32, device="cuda")
+    out = torch.empty((M, N), dtype=torch.float32, device="cuda")
     want = B.nvfp4_46_gemm(*args, out_dtype=B.OUT_F32).clone()
     s = torch.cuda.Stream()
     with torch.cuda.stream(s):
@@ -342,7 +346,7 @@ def test_gemm_can_be_captured_in_a_graph_and_replayed(K):
         assert torch.equal(out, want)
 
 
-@pytest.mark.parametrize("K", [256, 416])      # the copy-based and the register-staged kernel
+@pytest.mark.parametrize("K", [256, 416])      # whole chunks of 256, and none
 def test_gemm_with_weights_quantized_in_16x16_tiles(K):
     """FPROP and DGRAD with a weight matrix quantized once in 16x16 tiles (Section 4.1): the
     row packing multiplies activations, the packing for W^T multiplies gradients, and the
@@ -438,6 +442,36 @@ def test_gemm_operand_larger_than_four_gibibytes():
                             sb.cpu().numpy(), 0.5, want_abs=True)
     gsel = got[idx].double().cpu().numpy()
     assert (np.abs(gsel - c_ref) <= _tolerance(c_ref, c_abs, K, B.OUT_F32)).all()
+
+
+@pytest.mark.parametrize("tail", [32, 128])
+@pytest.mark.parametrize("M,N", [(3, 5), (257, 258)])
+def test_gemm_with_a_contraction_axis_past_the_32_bit_offsets(M, N, tail):
+    """K = 2^24 + 32 (a last chunk of one unit) and 2^24 + 128 (a whole one): the kernel that stages chunks
+    through registers, which no smaller K takes.  The codes are 0 but for 4096 indices, the last 64 and
+    some around every power of two among them; scales 1 and multiples of 0.25 below 2^22: exact in any
+    order."""
+    K = (1 << 24) + tail
+    assert hm.choose_gemm(M, N, K) == "staged"
+    _log(f"gemm staged case M={M} N={N} K={K}")
+    rng = np.random.default_rng(4653 + tail)
+    special = [k + d for k in 2 ** np.arange(1, 25) for d in (-1, 0, 1) if k + d < K]
+    at = np.unique(np.concatenate([rng.integers(0, K, 4096 - 160), special, np.arange(K - 64, K)]))
+    codes, ops = {}, []
+    for name, rows in (("a", M), ("b", N)):
+        codes[name] = rng.integers(0, 16, (rows, len(at)), dtype=np.uint8)
+        c = torch.zeros((rows, K // 2), dtype=torch.uint8, device="cuda")
+        for parity in (0, 1):                    # even index: low nibble
+            pick = at % 2 == parity
+            c[:, torch.from_numpy(at[pick] // 2).cuda()] += _dev(codes[name][:, pick] << (4 * parity))
+        ops += [c, torch.full((rows, K // 16), 0x38, dtype=torch.uint8, device="cuda"), _alpha(1.0)]
+    grid = np.array([0, .5, 1, 1.5, 2, 3, 4, 6, 0, -.5, -1, -1.5, -2, -3, -4, -6])
+    da, db = grid[codes["a"]], grid[codes["b"]]
+    assert (np.abs(da) @ np.abs(db).T).max() < 2.0 ** 22
+    for out_dtype in (B.OUT_F32, B.OUT_BF16):
+        got = B.nvfp4_46_gemm(*ops, out_dtype=out_dtype)
+        want = torch.from_numpy((da @ db.T).astype(np.float32))
+        assert torch.equal(got.cpu(), want if out_dtype == B.OUT_F32 else want.to(torch.bfloat16))
 
 
 def test_gemm_with_more_columns_than_a_launch_of_small_tiles_holds():
