@@ -57,18 +57,23 @@ enum GemmKernel {
   kGemmTile128, kGemmTile256x128
 };
 
-// How much of the chip's time a product in tiles of BM x BN uses: what tiles of 64 x 64 would cover
-// of C over what whole turns of 256 workgroups could hold.  The last turn's empty places count as
-// idle, and so does what lies past the end of C: 64 x 28672 has 224 tiles of 256 x 128, which seem
-// to fill the chip but hold 64 of 256 rows each (22 %; at K = 8192 110 us, in 64 x 64 tiles 45).
-// 64 x 64 is the measure because that is the other choice, with padding of its own: 196 rows
-// pad to 256 in either (196 x 29536 x 4096: 63 in 256 x 128, 72 in 64 x 64).
-inline double use_of_chip(int64_t M, int64_t N, int BM, int BN) {
-  const int64_t turns = (tiles_of(M, N, BM, BN) + kCus - 1) / kCus;
-  return (double)tiles_of<Tile64>(M, N) * Tile64::BM * Tile64::BN / ((double)turns * kCus * BM * BN);
+// How evenly tiles of BM x BN divide over whole turns of one workgroup per compute unit ...
+inline double turns_filled(int64_t M, int64_t N, int BM, int BN) {
+  const int64_t tiles = tiles_of(M, N, BM, BN);
+  return (double)tiles / (double)((tiles + kCus - 1) / kCus * kCus);
+}
+// ... and how much of them there is to do: what tiles of 64 x 64 would cover of C over what these do.
+// 64 x 28672 has 224 tiles of 256 x 128, which fill a turn to 87 %, but hold 64 of 256 rows each (at
+// K = 8192 110 us, in 64 x 64 tiles 45).  64 x 64 is the measure because that is the other choice, with
+// padding of its own: 196 rows pad to 256 in either (196 x 29536 x 4096: 63 in 256 x 128, 72 in 64 x 64).
+inline double tiles_covered(int64_t M, int64_t N, int BM, int BN) {
+  return (double)tiles_of<Tile64>(M, N) * Tile64::BM * Tile64::BN /
+         ((double)tiles_of(M, N, BM, BN) * BM * BN);
 }
 template <typename S>
-inline double use_of_chip(int64_t M, int64_t N) { return use_of_chip(M, N, S::BM, S::BN); }
+inline bool fills_chip(int64_t M, int64_t N, double turns) {
+  return turns_filled(M, N, S::BM, S::BN) >= turns && tiles_covered(M, N, S::BM, S::BN) >= 0.8;
+}
 
 // Which kernel: times in us, BF16 out, on one card, M x N x K; operands as the calls before left
 // them (all in the memory-side cache), or B from memory where it says so.
@@ -90,14 +95,17 @@ inline GemmKernel fastest_gemm(int64_t M, int64_t N, int64_t K) {
   if ((K % SK) == 0 && (M <= 32 || (M <= 64 && t64 <= kCus && stream_64))) return kGemmSkinny;
 
   // The largest tiles (the fewest expansions and copies per product) that leave little of the chip
-  // idle.  256 x 256 tiles of the copy-based kernel from 62 % (2816 x 4096 x 4096, 176 tiles: 96, in
-  // 64 x 64 tiles 111; but 4352 x 4096 x 2048, 272 tiles: 106 / 90); 256 x 128 tiles from 80 % (2048 x
-  // 4096 x 4096: 80 in 256 x 256, 65; 2048 x 3072 x 4096, 75 %: 59, in 64 x 64 tiles 55); 128 x 128
-  // from 87 % (1000 x 4096 x 4096: 76 in 256 x 256, 35, in 64 x 64 38; 2048 x 3072 x 4096, 75 %: 63;
-  // B from memory, 65 / 128 x 28672 x 8192: 116 / 117 in 256 x 128, 66 / 68, in 64 x 64 74 / 76).
-  if ((K % GK) == 0 && use_of_chip(M, N, GT, GT) >= 0.62) return kGemmDma;
-  if (use_of_chip<Tile256x128>(M, N) >= 0.8) return kGemmTile256x128;
-  if (use_of_chip<Tile128>(M, N) >= 0.87) return kGemmTile128;
+  // idle.  256 x 256 tiles of the copy-based kernel from 62 %, padding counted as idle (2816 x 4096 x
+  // 4096, 176 tiles: 96, in 64 x 64 tiles 111; but 4352 x 4096 x 2048, 272 tiles: 106 / 90, and 5834 x
+  // 1600 x 1024, 161 tiles of which 11 % is padding: 34 / 28); 256 x 128 tiles from 80 % (2048 x 4096 x
+  // 4096: 80 in 256 x 256, 65; 2048 x 3072 x 4096, 75 %: 59, in 64 x 64 tiles 55); 128 x 128 from 87 %
+  // (1000 x 4096 x 4096: 76 in 256 x 256, 35, in 64 x 64 38; 2048 x 3072 x 4096, 75 %: 63; B from memory,
+  // 65 / 128 x 28672 x 8192: 116 / 117 in 256 x 128, 66 / 68, in 64 x 64 74 / 76); the last two only where
+  // they cover 80 % of it (192 x 28672 x 8192, 75 %: 120 in 256 x 128, 107 in 64 x 64; 1340 x 4464 x 5504,
+  // 87 %: 76 / 83).
+  if ((K % GK) == 0 && turns_filled(M, N, GT, GT) * tiles_covered(M, N, GT, GT) >= 0.62) return kGemmDma;
+  if (fills_chip<Tile256x128>(M, N, 0.8)) return kGemmTile256x128;
+  if (fills_chip<Tile128>(M, N, 0.87)) return kGemmTile128;
   // Small products: the smallest tiles that are at most one per compute unit (64 x 1024 x 4096:
   // 7.6 in 32 x 32, 9.9 in 64 x 32, 13.0 in 64 x 64; 128 x 4096 x 4096: 11.4 / 10.6 / 13.1; 200 x
   // 4096 x 4096: 18.8 / 15.1 / 13.9); 32 rows or columns would leave larger tiles half empty (B from

@@ -36,6 +36,7 @@ EXPECTED = {
     (8192, 8192, 8192): "dma", (2816, 4096, 4096): "dma", (192, 128256, 4096): "dma",
     (512, 28672, 8192): "dma", (4352, 4096, 2048): "tile64", (2048, 4096, 4096): "tile256x128",
     (8192, 8192, 8160): "tile256x128", (1000, 4096, 4096): "tile128", (2880, 1440, 1056): "tile64",
+    (1340, 4464, 5504): "tile256x128", (431, 7440, 2048): "tile128", (5834, 1600, 1024): "tile64",
     (1, 1, 1 << 25): "staged",
 }
 
