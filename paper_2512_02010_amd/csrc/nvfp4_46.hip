@@ -665,11 +665,15 @@ __global__ __launch_bounds__(kThreads) void k_tile(
   // registers (224 of them, two waves per SIMD).  Columnwise Hadamard + SR on 8192 x 8192:
   // 138 -> 110 us with its tensor scale, both orientations with SR 200 -> 166.
   // Fake-quant of fp32 keeps its tile in LDS as well, 32 KiB that with 32 KiB of words leave two
-  // workgroups per compute unit: that pays for the squared-error rule alone, whose calls are the most
-  // to hide (columnwise, 8192 x 8192, words from LDS / drawn by their lane: 4/6 115 / 120 us, with the
-  // transform 123 / 131; by absolute error 113 / 101, always 6 96 / 86, with the transform 102 / 90).
-  // There the lane draws the words of its two columns itself, half of every call for nothing.
-  constexpr bool kWords = ROUNDING != kRTN && !(XF32 && OUT == kOutFake && SELECT != kSel46);
+  // workgroups per compute unit.  That pays where registers allow no third one anyway: the squared-error
+  // rule, and with the transform the other two that compare errors (columnwise, 8192 x 8192, words from
+  // LDS / drawn by their lane: 4/6 115 / 120 us, with the transform 123 / 131; by absolute error with the
+  // transform 121 / 134, without 113 / 101; always 6 96 / 86, with the transform 102 / 90; absolute error on
+  // nearest-rounded candidates with the transform 113 / 104).  Elsewhere the lane draws the words of
+  // its two columns itself, half of every call for nothing.
+  constexpr bool kTwoWavesAnyway =
+      SELECT == kSel46 || (RHT && ROUNDING == kSR && (SELECT == kSel46Mae || SELECT == kSel46AbsMax));
+  constexpr bool kWords = ROUNDING != kRTN && (!XF32 || OUT != kOutFake || kTwoWavesAnyway);
   constexpr bool kDrawn = ROUNDING != kRTN && !kWords;
   __shared__ uint4 words[kWords ? TR * TC / 4 : 1];                   // [TR][TC / 4]
 
