@@ -502,11 +502,14 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm_dma(
 //
 // What bounds it.  A wave of 2 x 2 instruction tiles issues 8 vector instructions (the
 // expansion, 4 cycles each) per matrix instruction (32 cycles): both pipes are equally busy and
-// must run at once, which takes several waves per SIMD (the bare loop, no memory accesses: 206
-// cycles per 4 matrix instructions with one wave per SIMD, 188 with two, 142 with four; the
-// matrix pipe alone 128).  So the small tiles keep to 128 registers and 40 KiB of LDS per four
-// waves.  Waves of 4 x 2 expand less per matrix instruction (6 vector instructions) and hold 256
-// registers; they pay only where their larger tiles fill the chip.
+// must run at once, which takes several waves per SIMD (the bare loop, no memory accesses: 208
+// cycles per 4 matrix instructions with one wave per SIMD, 189 with two, 142 with four; the
+// matrix pipe alone 128).  So the small tiles keep to 128 registers, and LDS leaves a compute unit four
+// workgroups of Tile32 (eight waves each) and five of Tile64x32, but three of Tile64: its stages
+// take 40 KiB, its partial sums 48.  (In two phases the sums fit 36 KiB and four workgroups a unit:
+// 1536 x 4096 x 8192 113 -> 110 us, but 128 x 8192 x 2880 14.6 -> 15.4 and 300 x 2000 x 1056 7.7 -> 8.1, for
+// the second exchange; not adopted.)  Waves of 4 x 2 expand less per matrix instruction (6 vector
+// instructions) and hold 256 registers; they pay only where their larger tiles fill the chip.
 //
 // Chunks arrive by asynchronous global -> LDS copies, all waves of the workgroup together: codes
 // 16 bytes and scale pairs 2 bytes per lane (a pair lands as one 32-bit word), which asks nothing

@@ -41,7 +41,7 @@ struct TileShape {
 // x 64 and 128 x 128 in two copies, 32 x 64, 32 x 32 in four copies, 256 x 256.)
 using Tile32 = TileShape<1, 1, 1, 1, 8, 1, 2>;         // 32 x 32, 8 waves, each an eighth of K
 using Tile64x32 = TileShape<2, 1, 1, 1, 4, 1, 2>;      // 64 x 32, 4 waves
-using Tile64 = TileShape<2, 2, 1, 1, 4, 1, 2>;         // 64 x 64, 4 waves; four workgroups per CU
+using Tile64 = TileShape<2, 2, 1, 1, 4, 1, 2>;         // 64 x 64, 4 waves; three workgroups per CU
 using Tile64Long = TileShape<2, 2, 1, 1, 8, 1, 2>;     // 64 x 64, 8 waves
 using Tile128 = TileShape<2, 2, 2, 2, 4, 1, 2>;        // 128 x 128, 16 waves
 using Tile256x128 = TileShape<4, 2, 2, 2, 2, 1, 4>;    // 256 x 128, 8 waves

@@ -55,10 +55,17 @@ constexpr int kAmaxRhtColWgPerCu = 8;   // k_amax_rht_col
 // The pass for the tensor scale reads x just before the quantizing pass, both usually first to
 // last.  A tensor larger than what the 256 MB memory-side cache holds of it has then always just
 // lost the part that is read next; read last to first, the quantizing pass finds most of a
-// cacheful.  Scale + quantize, forwards / backwards: fp32 8192 x 8192 into both packings of 16x16
-// tiles 130 / 111 us, rowwise 97 / 93, both orientations 122 / 114; BF16 16384 x 8192 columnwise
-// 121 / 112, rowwise 110 / 104.  Below the line everything is found either way (BF16 8192 x 8192:
-// 16x16 tiles 70 / 71, both orientations 81 / 82), so small tensors keep their order.
+// cacheful.  Scale + quantize, us, forwards / backwards, (a) on seven tensors in turn, (b) on one that a
+// kernel has just written, (c) on the same one again (the next scale pass then finds its head):
+//                                                       (a)        (b)          (c)
+//   fp32 8192 x 8192, both packings of 16x16 tiles   137 / 116   143 / 130   121 / 116
+//                     rowwise                        103 / 98    115 / 113    92 / 92
+//                     both orientations              128 / 120   138 / 134   118 / 115
+//   BF16 16384 x 8192, columnwise                    127 / 119   136 / 131   113 / 113
+//                      rowwise                       118 / 114   126 / 126   103 / 104
+// (d) On a tensor whose last write the host has waited for the orders differ little (tiles 124 / 124,
+// BF16 columnwise 138 / 136, fp32 rowwise 99 / 100).  Below the line everything is found either way (BF16
+// 8192 x 8192: 16x16 tiles 70 / 71, both orientations 81 / 82), so small tensors keep their order.
 constexpr int64_t kLastLevelBytes = (int64_t)192 << 20;
 constexpr uint32_t runs_backwards(int64_t elements, bool xf32) {
   return elements * (xf32 ? 4 : 2) > kLastLevelBytes;

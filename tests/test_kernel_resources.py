@@ -14,6 +14,8 @@ from concurrent.futures import ThreadPoolExecutor
 
 from paper_2512_02010_amd import build
 
+from . import _host_model as hm
+
 
 def _report(source: str, part_macro: str, part: int):
     flags = [f for f in build.HIPCC_FLAGS if f != "-shared"]
@@ -50,11 +52,23 @@ def test_register_and_scratch_budgets():
 
 
 def test_tile_kernel_budgets():
-    """k_gemm_tile counts its copies by hand too, and its small shapes need four waves per SIMD."""
+    """k_gemm_tile counts its copies by hand too, and its small shapes leave room for four waves per SIMD in
+    registers (the compiler's figure, which does not know the dynamic LDS of the next test)."""
     tile = {k: v for k, v in _report("gemm.hip", "NVFP4_46_GEMM_PART", 6).items() if "k_gemm_tile" in k}
     assert len(tile) == 6 * 4, list(tile)          # six shapes x (K whole or ragged) x output type
     assert all(v["ScratchSize"] == 0 for v in tile.values()), tile
     assert all(v["Occupancy"] >= (2 if "ILi4ELi2E" in k else 4) for k, v in tile.items()), tile
+
+
+def test_tile_kernel_workgroups_per_compute_unit():
+    """What the LDS that each shape asks for at launch (stages or partial sums, the larger) leaves of a
+    compute unit's 160 KiB."""
+    fits = {k: 160 * 1024 // hm.tile_shape(k)[3] for k in hm.GEMM_KERNELS if k.startswith("tile")}
+    assert fits == {"tile32": 4, "tile64x32": 5, "tile64": 3, "tile64long": 1, "tile128": 1,
+                    "tile256x128": 1}, fits
+    waves = {k: fits[k] * hm.tile_shape(k)[2] // 64 / 4 for k in fits}         # per SIMD, by LDS alone
+    assert waves == {"tile32": 8, "tile64x32": 5, "tile64": 3, "tile64long": 2, "tile128": 4,
+                     "tile256x128": 2}, waves
 
 
 def test_fp32_stochastic_fake_quant_leaves_room_for_four_workgroups():
