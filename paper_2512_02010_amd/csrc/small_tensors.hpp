@@ -17,11 +17,13 @@ namespace nvfp4_46 {
 //   256     4.2/3.9   4.8/4.7       6.1/6.0       6.5/6.2     5.1/5.1       6.4/6.4
 //   512     6.6/6.1   4.8/4.8       6.6/6.6       10.9/10.5   5.2/5.1       7.1/7.0
 //   768     8.9/8.3   4.9/4.8       7.2/7.1       15.2/14.7   5.2/5.1       7.7/7.7
+//   1024    11.2/10.4 4.9/4.8       7.7/7.7       19.6/18.7   5.2/5.1       8.3/8.3
 // With scratch words it replaces one launch by one: as far as it is ahead in both columns.  Without,
-// it replaces three, whose launches the host pays for (called one by one, 512 KiB in the cache 7.0
-// against 10.7 us, in memory 11.1 against 10.6): as far as it is not behind with x in the cache.
+// it replaces three, which the host pays for: as far as it is not behind when called one by one with x
+// in the cache (us per call among others: 512 KiB 7.0 / 10.7, 768 KiB 9.3 / 10.7, 1 MiB 11.8 / 10.8; first
+// read from memory 11.1 / 10.6, 15.5 / 10.8 and 20.1 / 10.8; programs that replay graphs have scratch words).
 constexpr bool scale_in_one_workgroup(int64_t bytes, bool has_scratch) {
-  return bytes <= (int64_t)(has_scratch ? 128 : 512) << 10;
+  return bytes <= (int64_t)(has_scratch ? 128 : 768) << 10;
 }
 
 // Scale and rowwise codes in one launch (k_scale_quantize_small), against codes in a launch of their
