@@ -20,9 +20,8 @@
 // the same for A and for B, which is all the sum needs.
 //
 // Two kernels share this plan: k_gemm (the workgroup stages chunks through registers into
-// shared LDS buffers, one barrier per chunk; only for K > 2^24, beyond the others' 32-bit
-// offsets) and k_gemm_dma (K a multiple of 128; every wave fills its own LDS with asynchronous global -> LDS copies
-// and never meets a barrier).
+// shared LDS buffers; only for K > 2^24, beyond the others' 32-bit offsets) and k_gemm_dma (the workgroup
+// fills a ring of four LDS stages with asynchronous global -> LDS copies).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -294,12 +293,10 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm(
 }
 
 // ----------------------------------------------------------------------------------------
-// The same product with wave-private LDS filled by asynchronous global -> LDS loads
-// (global_load_lds_dwordx4): no staging registers, no LDS write instructions and no
-// workgroup barrier at all.  Each wave copies the 128 rows of A and the 128 rows of B that its
-// own quarter of the tile needs (the two waves that share rows each fetch them; operand
-// bytes are small) into its own 2 x 18 KiB of LDS:
-//   per stage: A codes [128][64 B], B codes [128][64 B], A scales [128][8 B], B scales [128][8 B]
+// The same product with LDS filled by asynchronous global -> LDS loads (global_load_lds_dwordx4): no
+// staging registers and no LDS write instructions.  The four waves of the workgroup copy each
+// chunk of 128 contraction steps together, a quarter each, into a ring of four stages:
+//   per stage: A codes [256][64 B], B codes [256][64 B], A scales [256], B scales [256]
 // A load instruction writes its 64 lanes' 16 (or 4) bytes to consecutive LDS addresses, so
 // the LDS layout is plain row-major; to keep the later 16-byte reads of 16 lanes on 16
 // different bank groups, lane (row, position p) of a copy fetches the row's 16-byte unit
@@ -307,10 +304,28 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm(
 // The copies are issued with inline assembly (the compiler then neither reorders LDS reads
 // around them nor waits for all of them at every LDS read) and waited for with explicit
 // s_waitcnt vmcnt: the kernel issues no other vector-memory loads inside the loop.
-// Only for K a multiple of 128 (whole chunks) and K <= 2^24 (32-bit lane offsets).
-constexpr uint32_t kDmaStage = 2 * 128 * 64 + 2 * 128 * 8;   // 18432 bytes per wave and stage
-constexpr uint32_t kDmaWave = 2 * kDmaStage;
-constexpr size_t kGemmDmaLdsBytes = 4 * kDmaWave;   // 147456
+//
+// Slot s of a wave's 64 columns' worth of B (two instruction tiles) holds column 2 (s % 32) + s / 32, so a
+// lane ends with two neighbouring columns of C and stores them together, 128 contiguous bytes of a row
+// per 32 lanes (BF16), where single columns took twice the stores of half a line each.
+//
+// Scales: K a multiple of 128 (KFULL) 4 bytes per lane, the 8 of a row in two words; any other K (a multiple of
+// 32) 2 bytes per lane, each pair in a word of its own, which asks nothing of the alignment of scale
+// lines.  There the last chunk sticks out of the rows: the lanes past the end of K copy the row's last unit
+// instead, and the scales they would meet count as zero.  K <= 2^24 (32-bit lane offsets).
+//
+// What bounds it: the chip's power (8192 x 8192 x 8192: 833 us with every wave copying its own rows in a burst;
+// 788 to 826 with shared copies spread over the chunk; builds with parts left out, timing only: 715 without the
+// expansions, 690 without the scales' copies either, 655 matrix instructions alone; the vendor's FP16 product
+// of the expanded operands 684).  The barrier per chunk costs nothing that shows (655 with it, too).
+// Expanding each operand once per workgroup into FP16 in LDS, which halves the expansions, takes
+// 835 to 854: a quarter more LDS traffic than the matrix instructions leave room for.
+// Ragged K, in 256 x 128 tiles of k_gemm_tile / here: 8192 x 8192 x 8160 1018 / 811, 4096 x 4096 x 4128 145 / 116,
+// 5000 x 6000 x 2080 152 / 124, 2816 x 4096 x 4064 108 / 88.
+constexpr uint32_t kDmaCodes = 2 * GT * 64;                             // bytes of codes per stage
+constexpr uint32_t dma_stage(bool kfull) { return kDmaCodes + 2 * GT * (kfull ? 8 : 16); }
+constexpr int kDmaStages = 4;
+static_assert(kDmaStages * dma_stage(false) <= 160 * 1024, "the stages must fit the LDS");
 
 // M0 = LDS byte address of lane 0's piece; %1 = the lane's 32-bit byte offset (vector
 // register), %2 = the 64-bit base address (scalar register pair).
@@ -320,13 +335,17 @@ constexpr size_t kGemmDmaLdsBytes = 4 * kDmaWave;   // 147456
 #define NV_DMA4(lds_sgpr, voff, gbase)                                                        \
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2"                            \
                :: "s"(lds_sgpr), "v"(voff), "s"(gbase) : "memory", "m0")
+// as NV_DMA16, two bytes per lane, each into a 32-bit word of LDS
+#define NV_DMA2(lds_sgpr, voff, gbase)                                                        \
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_ushort %1, %2"                           \
+               :: "s"(lds_sgpr), "v"(voff), "s"(gbase) : "memory", "m0")
 
-template <bool OUTF32>
+template <bool KFULL, bool OUTF32>
 __global__ __launch_bounds__(kGemmThreads) void k_gemm_dma(
     const uint8_t *__restrict__ codes_a, const uint8_t *__restrict__ scales_a,
     const float *__restrict__ alpha_a, const uint8_t *__restrict__ codes_b,
     const uint8_t *__restrict__ scales_b, const float *__restrict__ alpha_b,
-    void *__restrict__ out, int64_t M, int64_t N, int64_t K, uint32_t tiles_n, uint32_t sha,
+    void *__restrict__ out, int64_t M, int64_t N, uint32_t K, uint32_t tiles_n, uint32_t sha,
     uint32_t shb) {
   extern __shared__ __align__(16) uint8_t lds_raw[];
   const uint32_t t = threadIdx.x, lane = t & 63u;
@@ -334,17 +353,16 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm_dma(
   const uint32_t r = lane & 31u, g = lane >> 5;
   const uint32_t wm = wave >> 1, wn = wave & 1u;
   const uint32_t tile_m = blockIdx.x / tiles_n, tile_n = blockIdx.x - tile_m * tiles_n;
-  const int64_t m0 = (int64_t)tile_m * GT + wm * 128, n0 = (int64_t)tile_n * GT + wn * 128;
-  const int64_t row_codes = K / 2, row_scales = K / 16;
+  const int64_t m0 = (int64_t)tile_m * GT, n0 = (int64_t)tile_n * GT;
+  const uint32_t row_codes = K / 2, row_scales = K / 16;
+  constexpr uint32_t STAGE = dma_stage(KFULL);
+  constexpr int NS = KFULL ? 2 : 4;               // scale copies per wave, chunk and operand
+  const uint32_t rows_a = (uint32_t)(M - m0 < GT ? M - m0 : GT);     // rows the tile really has
+  const uint32_t rows_b = (uint32_t)(N - n0 < GT ? N - n0 : GT);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds_raw;
 
-  const uint8_t *wl = lds_raw + wave * kDmaWave;   // the wave's LDS, for reading
-  const uint32_t lds_wave =
-      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds_raw + wave * kDmaWave;
-
-  // first rows of the wave's operand slices (a slice that starts past the end re-reads the
-  // last row; nothing of it is stored), and each lane's byte offset from there for every
-  // copy instruction of a chunk
-  const int64_t a_base = m0 < M ? m0 : M - 1, b_base = n0 < N ? n0 : N - 1;
+  // first rows of the workgroup's operand slices, and each lane's byte offset from there for
+  // every copy instruction of a chunk (a row past the end of its operand re-reads the last one)
   // (wave-uniform by construction; read through readfirstlane so that they live in scalar
   // registers, which is where the copy instruction takes its base address from)
   auto uniform = [](const uint8_t *p) {
@@ -353,56 +371,95 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm_dma(
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
     return reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);
   };
-  const uint8_t *gca = uniform(codes_a + a_base * row_codes), *gcb = uniform(codes_b + b_base * row_codes);
+  const uint8_t *gca = uniform(codes_a + m0 * row_codes), *gcb = uniform(codes_b + n0 * row_codes);
   // (a row's scale line: the row itself, or row / 16 for an operand quantized in 16x16 tiles)
-  const uint8_t *gsa = uniform(scales_a + (a_base >> sha) * row_scales);
-  const uint8_t *gsb = uniform(scales_b + (b_base >> shb) * row_scales);
-  uint32_t oca[8], ocb[8], osa[4], osb[4];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const uint32_t row = 16 * q + (lane >> 2), unit = (lane & 3u) ^ ((row >> 2) & 3u);
-    const int64_t ra = a_base + row < M ? row : M - 1 - a_base;
-    const int64_t rb = b_base + row < N ? row : N - 1 - b_base;
-    oca[q] = (uint32_t)(ra * row_codes) + unit * 16;
-    ocb[q] = (uint32_t)(rb * row_codes) + unit * 16;
-  }
+  const uint8_t *gsa = uniform(scales_a + (m0 >> sha) * row_scales);
+  const uint8_t *gsb = uniform(scales_b + (n0 >> shb) * row_scales);
+  // the operand row in slot `slot` of the 256 of A, or of B (see the kernel's comment)
+  auto line_a = [&](uint32_t slot) { return slot < rows_a ? slot : rows_a - 1; };
+  auto line_b = [&](uint32_t slot) {
+    const uint32_t l = (slot & ~63u) + 2 * (slot & 31u) + ((slot >> 5) & 1u);
+    return l < rows_b ? l : rows_b - 1;
+  };
+  // wave w issues code copies w, w + 4, ... of the 16 of each operand (16 rows each), and scale
+  // copies w, w + 4, ... of the 8 (32 rows each, 4 bytes per lane) or 16 (16 rows, 2 bytes)
+  auto unit_at = [&](int q) __attribute__((always_inline)) {                              // the lane's 16-byte unit of its row, 0..3
+    const uint32_t slot = 16 * (4 * q + wave) + (lane >> 2);
+    return (lane & 3u) ^ ((slot >> 2) & 3u);
+  };
+  auto pair_at = [&](int q) __attribute__((always_inline)) {                              // the pair of scales, 0..3 (two of them if KFULL)
+    const uint32_t slot = 16 * (4 * q + wave) + (lane >> 2);
+    return KFULL ? 2 * (lane & 1u) : (lane & 3u) ^ (((slot >> 4) & 1u) << 1);
+  };
+  uint32_t oca[4], ocb[4], osa[NS], osb[NS];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const uint32_t row = 32 * q + (lane >> 1), half = lane & 1u;
-    const int64_t ra = a_base + row < M ? row : M - 1 - a_base;
-    const int64_t rb = b_base + row < N ? row : N - 1 - b_base;
-    osa[q] = (uint32_t)((((a_base + ra) >> sha) - (a_base >> sha)) * row_scales) + half * 4;
-    osb[q] = (uint32_t)((((b_base + rb) >> shb) - (b_base >> shb)) * row_scales) + half * 4;
+    const uint32_t slot = 16 * (4 * q + wave) + (lane >> 2);
+    oca[q] = line_a(slot) * row_codes + unit_at(q) * 16;
+    ocb[q] = line_b(slot) * row_codes + unit_at(q) * 16;
   }
-  // the 24 copy instructions of a chunk, numbered so that they can be issued one at a time
-  auto copy_one = [&](int64_t c, uint32_t stage, int n) {
-    const uint32_t lds = lds_wave + stage * kDmaStage;
-    if (n < 8) NV_DMA16(lds + n * 1024, oca[n], gca + c * (GK / 2));
-    else if (n < 16) NV_DMA16(lds + 8192 + (n - 8) * 1024, ocb[n - 8], gcb + c * (GK / 2));
-    else if (n < 20) NV_DMA4(lds + 16384 + (n - 16) * 256, osa[n - 16], gsa + c * (GK / 16));
-    else NV_DMA4(lds + 17408 + (n - 20) * 256, osb[n - 20], gsb + c * (GK / 16));
-  };
-  auto copy_chunk = [&](int64_t c, uint32_t stage) {
 #pragma unroll
-    for (int n = 0; n < 24; ++n) copy_one(c, stage, n);
+  for (int q = 0; q < NS; ++q) {
+    const uint32_t slot = KFULL ? 32 * (4 * q + wave) + (lane >> 1) : 16 * (4 * q + wave) + (lane >> 2);
+    osa[q] = (line_a(slot) >> sha) * row_scales + pair_at(q) * 2;
+    osb[q] = (line_b(slot) >> shb) * row_scales + pair_at(q) * 2;
+  }
+  // the wave's copy instructions of a chunk, numbered so that they can be issued one at a time
+  constexpr int kCopies = 8 + 2 * NS;
+  auto copy_one = [&](uint32_t c, uint32_t stage, int n) __attribute__((always_inline)) {
+    const uint32_t codes = lds0 + stage * STAGE + wave * 1024, scales = lds0 + stage * STAGE + kDmaCodes + wave * 256;
+    if (n < 4) NV_DMA16(codes + n * 4096, oca[n], gca + c * (GK / 2));
+    else if (n < 8) NV_DMA16(codes + GT * 64 + (n - 4) * 4096, ocb[n - 4], gcb + c * (GK / 2));
+    else {
+      const int q = (n - 8) % NS;
+      const uint32_t to = scales + (n - 8) * 1024, from = n < 8 + NS ? osa[q] : osb[q];
+      const uint8_t *base = (n < 8 + NS ? gsa : gsb) + c * (GK / 16);
+      if (KFULL) NV_DMA4(to, from, base);
+      else NV_DMA2(to, from, base);
+    }
+  };
+  // KFULL = false: the last chunk sticks out of the rows; the lanes that would read past the end of K
+  // read the row's last unit instead (and its scales count as zero, below)
+  const uint32_t nchunks = (K + GK - 1) / GK;
+  auto pull_in = [&](uint32_t c) __attribute__((always_inline)) {
+    if (!KFULL && c + 1 == nchunks) {
+      const uint32_t last = (K - c * GK) / 32 - 1;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint32_t slot = 16 * (4 * q + wave) + (lane >> 2);
+        const uint32_t u = unit_at(q) < last ? unit_at(q) : last, p = pair_at(q) < last ? pair_at(q) : last;
+        oca[q] = line_a(slot) * row_codes + u * 16;
+        ocb[q] = line_b(slot) * row_codes + u * 16;
+        osa[q % NS] = (line_a(slot) >> sha) * row_scales + p * 2;
+        osb[q % NS] = (line_b(slot) >> shb) * row_scales + p * 2;
+      }
+    }
+  };
+  auto copy_chunk = [&](uint32_t c, uint32_t stage) __attribute__((always_inline)) {
+    pull_in(c);
+#pragma unroll
+    for (int n = 0; n < kCopies; ++n) copy_one(c, stage, n);
   };
 
   // ---- LDS -> registers, one operand tile at a time (u = 0..3: A tiles, 4..7: B tiles)
   const uint32_t swz = (r >> 2) & 3u;
-  auto read_tile = [&](uint32_t stage, int half, int u, RawHalf &h) {
-    const uint8_t *st = wl + stage * kDmaStage + (u < 4 ? 0 : 8192);
-    const uint8_t *sc = wl + stage * kDmaStage + (u < 4 ? 16384 : 17408);
-    const uint32_t row = 32 * (u & 3) + r, pos = ((2 * half + g) ^ swz) * 16;
+  auto read_tile = [&](uint32_t stage, int half, int u, RawHalf &h) __attribute__((always_inline)) {
+    const uint8_t *st = lds_raw + stage * STAGE + (u < 4 ? 0 : GT * 64);
+    const uint8_t *sc = lds_raw + stage * STAGE + kDmaCodes + (u < 4 ? 0 : GT * (KFULL ? 8 : 16));
+    const uint32_t row = (u < 4 ? wm : wn) * 128 + 32 * (u & 3) + r, pos = ((2 * half + g) ^ swz) * 16;
     const uint4 codes = *reinterpret_cast<const uint4 *>(st + row * 64 + pos);
     // the lane's two scale bytes of this half (blocks 4*half + 2*g and + 1), still raw
-    const uint32_t two = *reinterpret_cast<const uint16_t *>(sc + row * 8 + 4 * half + 2 * g);
+    const uint32_t two = KFULL ? *reinterpret_cast<const uint16_t *>(sc + row * 8 + 4 * half + 2 * g)
+                               : *reinterpret_cast<const uint32_t *>(
+                                     sc + row * 16 + (((2 * half + g) ^ (((r >> 4) & 1u) << 1)) * 4));
     if (u < 4) { h.a[u] = codes; h.sa[u] = two; } else { h.b[u - 4] = codes; h.sb[u - 4] = two; }
   };
   // operands of step s (0..3) of a half for tile u; at s == 0 the two scale bytes are turned
   // into two FP16 bit patterns (byte << 7) in one word
-  auto expand_tile = [&](RawHalf &h, int s, int u, Frags &f) {
+  auto expand_tile = [&](RawHalf &h, int s, int u, Frags &f, uint32_t k) __attribute__((always_inline)) {
     const uint4 &w4 = u < 4 ? h.a[u] : h.b[u - 4];
     uint32_t &sc = u < 4 ? h.sa[u] : h.sb[u - 4];
+    if (!KFULL && s == 0 && k + 32 * g >= K) sc = 0u;      // k: where the half begins
     if (s == 0) sc = __builtin_amdgcn_perm(0u, sc, 0x0c010c00u) << 7;
     const uint32_t w = s == 0 ? w4.x : s == 1 ? w4.y : s == 2 ? w4.z : w4.w;
     const h2 pair = __builtin_bit_cast(h2, sc);
@@ -418,40 +475,44 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm_dma(
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
-  const int64_t nchunks = K / GK;
   RawHalf h0, h1;
   Frags f0, f1;
-  copy_chunk(0, 0);
-  copy_chunk(nchunks > 1 ? 1 : 0, 1);
-  asm volatile("s_waitcnt vmcnt(24)" ::: "memory");      // chunk 0 is in LDS
+  // past the end: a harmless re-read  (readfirstlane: the copies' base addresses stay in scalar registers)
+  auto at_most = [&](uint32_t c) { return (uint32_t)__builtin_amdgcn_readfirstlane(c < nchunks ? c : nchunks - 1); };
+#pragma unroll
+  for (int c = 0; c < kDmaStages - 1; ++c) copy_chunk(at_most(c), c);
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((kDmaStages - 2) * kCopies) : "memory");   // chunk 0 is in LDS
 #pragma unroll
   for (int u = 0; u < 8; ++u) read_tile(0, 0, u, h0);
 #pragma unroll
-  for (int u = 0; u < 8; ++u) expand_tile(h0, 0, u, f0);
+  for (int u = 0; u < 8; ++u) expand_tile(h0, 0, u, f0, 0u);
 
-  // Chunk c sits in stage c & 1.  A step is eight units of two matrix instructions; unit u
+  // Chunk c sits in stage c % 4.  A step is eight units of two matrix instructions; unit u
   // also expands operand tile u for the next step and carries the step's share of LDS
   // reads and copy instructions, so that everything issues in the matrix unit's shadow:
-  //   step 1        reads the chunk's second half (then the stage is free);
-  //   steps 3-5     start the 24 copies of chunk c + 2 into this stage, one per unit;
-  //   step 6        waits until only those 24 are outstanding (chunk c + 1 has landed in the
-  //                 other stage) and reads its first half;
+  //   steps 0-5     start the wave's copies of chunk c + 3, two per step, into the stage that chunk c - 1
+  //                 left: every wave had read all of that when it came to the barrier of chunk c - 1;
+  //   step 1        reads the chunk's second half;
+  //   step 6        waits until only the copies of chunks c + 2 and c + 3 are outstanding, meets the other
+  //                 waves (chunk c + 1 has landed whole) and reads its first half;
   //   step 7        expands the next chunk's first step.
-  auto chunk = [&](int64_t c, bool last) {
-    const uint32_t cur = (uint32_t)c & 1u, nxt = cur ^ 1u;
-    const int64_t c2 = c + 2 < nchunks ? c + 2 : nchunks - 1;   // past the end: a harmless re-read
+  auto chunk = [&](uint32_t c, bool last) __attribute__((always_inline)) {
+    const uint32_t cur = c & 3u, nxt = (cur + 1u) & 3u;
+    const uint32_t c3 = at_most(c + kDmaStages - 1);
+    if (!last) pull_in(c3);
 #pragma unroll
     for (int st = 0; st < 8; ++st) {
       Frags &fc = (st & 1) ? f1 : f0, &fn = (st & 1) ? f0 : f1;
-      if (st == 3 && !last) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      if (st == 6 && !last) asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
+      if (st == 6 && !last)
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((kDmaStages - 2) * kCopies) : "memory");
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         if (st == 1) read_tile(cur, 1, u, h1);
-        if (st >= 3 && st <= 5 && !last) copy_one(c2, cur, 8 * (st - 3) + u);
+        if (st < 6 && (u == 2 || u == 6) && !last) copy_one(c3, (cur + 3u) & 3u, 2 * st + u / 4);
+        if (!KFULL && st < 4 && u == 4 && !last) copy_one(c3, (cur + 3u) & 3u, 12 + st);
         if (st == 6 && !last) read_tile(nxt, 0, u, h0);
-        if (st < 7) expand_tile(st < 3 ? h0 : h1, (st + 1) & 3, u, fn);
-        else if (!last) expand_tile(h0, 0, u, fn);
+        if (st < 7) expand_tile(st < 3 ? h0 : h1, (st + 1) & 3, u, fn, c * GK + 64);
+        else if (!last) expand_tile(h0, 0, u, fn, (c + 1) * GK);
 #pragma unroll
         for (int q = 2 * u; q < 2 * u + 2; ++q)
           acc[q >> 2][q & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fc.a[q >> 2], fc.b[q & 3],
@@ -467,25 +528,42 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm_dma(
       }
     }
   };
-  for (int64_t c = 0; c + 1 < nchunks; ++c) chunk(c, false);
+  for (uint32_t c = 0; c + 1 < nchunks; ++c) chunk(c, false);
   chunk(nchunks - 1, true);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // nothing may still be writing LDS
 
+  // ---- store: instruction tiles 2 jp and 2 jp + 1 hold the even and the odd columns of 64
   const float scale = alpha_a[0] * alpha_b[0];
+  const bool whole = (N & 1) == 0;              // a lane's two columns exist together and are aligned
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int64_t col = n0 + 32 * j + r;
+    for (int jp = 0; jp < 2; ++jp) {
+      const uint32_t col = wn * 128 + 64 * jp + 2 * r;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int64_t row = m0 + 32 * i + 8 * (v / 4) + 4 * g + (v % 4);
-        if (row < M && col < N) {
-          const float c = acc[i][j][v] * scale;
-          if (OUTF32)
-            static_cast<float *>(out)[row * N + col] = c;
-          else
-            static_cast<uint16_t *>(out)[row * N + col] = (uint16_t)pack_bf16x2(c, 0.0f);
+        const uint32_t row = wm * 128 + 32 * i + 8 * (v / 4) + 4 * g + v % 4;
+        if (row < rows_a && col < rows_b) {
+          const float x = acc[i][2 * jp][v] * scale, y = acc[i][2 * jp + 1][v] * scale;
+          const int64_t at = (m0 + row) * N + n0 + col;
+          if (OUTF32) {
+            float *o = static_cast<float *>(out) + at;
+            if (whole) {
+              *reinterpret_cast<float2 *>(o) = make_float2(x, y);
+            } else {
+              o[0] = x;
+              if (col + 1 < rows_b) o[1] = y;
+            }
+          } else {
+            uint16_t *o = static_cast<uint16_t *>(out) + at;
+            const uint32_t w = pack_bf16x2(x, y);
+            if (whole) {
+              *reinterpret_cast<uint32_t *>(o) = w;
+            } else {
+              o[0] = (uint16_t)w;
+              if (col + 1 < rows_b) o[1] = (uint16_t)(w >> 16);
+            }
+          }
         }
       }
     }
@@ -519,11 +597,6 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm_dma(
 // of one LDS access pass hit all banks.  One barrier per chunk: it comes after the wait for the
 // own copies of the chunk, so behind it the chunk is complete and the stage of the chunk before is
 // free for the next copies.  K <= 2^24 (32-bit lane offsets).
-// as NV_DMA16, two bytes per lane, each into a 32-bit word of LDS
-#define NV_DMA2(lds_sgpr, voff, gbase)                                                        \
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_ushort %1, %2"                           \
-               :: "s"(lds_sgpr), "v"(voff), "s"(gbase) : "memory", "m0")
-
 template <typename S, bool KFULL, bool OUTF32>
 __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 : 4) void k_gemm_tile(
     const uint8_t *__restrict__ codes_a, const uint8_t *__restrict__ scales_a,
@@ -1219,11 +1292,12 @@ template int run_gemm_staged<((NVFP4_46_GEMM_PART - 1) / 2 != 0), ((NVFP4_46_GEM
 int run_gemm_dma(const GemmArgs &a) {
   const uint32_t tiles_n = (uint32_t)((a.N + GT - 1) / GT);
   auto go = [&](auto kernel) {
-    return launch_with_lds(kernel, tile_grid(a), dim3(kGemmThreads), kGemmDmaLdsBytes, a.stream,
-                           a.codes_a, a.scales_a, a.alpha_a, a.codes_b, a.scales_b, a.alpha_b,
-                           a.out, a.M, a.N, a.K, tiles_n, a.sha, a.shb);
+    return launch_with_lds(kernel, tile_grid(a), dim3(kGemmThreads), kDmaStages * dma_stage(a.K % GK == 0),
+                           a.stream, a.codes_a, a.scales_a, a.alpha_a, a.codes_b, a.scales_b, a.alpha_b,
+                           a.out, a.M, a.N, (uint32_t)a.K, tiles_n, a.sha, a.shb);
   };
-  return a.f32 ? go(k_gemm_dma<true>) : go(k_gemm_dma<false>);
+  if (a.K % GK == 0) return a.f32 ? go(k_gemm_dma<true, true>) : go(k_gemm_dma<true, false>);
+  return a.f32 ? go(k_gemm_dma<false, true>) : go(k_gemm_dma<false, false>);
 }
 #endif
 
@@ -1309,7 +1383,7 @@ extern "C" int nvfp4_46_gemm(const void *codes_a, const void *scales_a, const fl
                    (flags & NVFP4_GEMM_A_TILE_SCALES) ? 4u : 0u,
                    (flags & NVFP4_GEMM_B_TILE_SCALES) ? 4u : 0u, out_dtype == NVFP4_OUT_F32,
                    static_cast<hipStream_t>(stream)};
-  switch (choose_gemm(M, N, K)) {
+  switch (gemm_kernel(M, N, K)) {
     case kGemmStaged:
       return (K % GK) == 0 ? (a.f32 ? run_gemm_staged<true, true>(a) : run_gemm_staged<true, false>(a))
                            : (a.f32 ? run_gemm_staged<false, true>(a) : run_gemm_staged<false, false>(a));

@@ -146,4 +146,16 @@ inline GemmKernel choose_gemm(int64_t M, int64_t N, int64_t K) {
   if (lanes_of(fastest, M, N) >> 32 == 0) return fastest;
   return (K % GK) == 0 && K <= ((int64_t)1 << 24) ? kGemmDma : kGemmStaged;
 }
+
+// The kernel that a product runs: choose_gemm()'s, whose 256 x 256 tiles are for whole chunks of 128, or those
+// tiles with a ragged K as well, from the same fill of the chip on.  256 x 256 / choose_gemm()'s: 6144 x 6400 x
+// 1056 (78 %) 112 / 114, 2816 x 4096 x 4064 (69 %) 88 / 108; below the line 3072 x 3072 x 992 (56 %) 33 / 31,
+// 4096 x 4608 x 3040 (56 %) 147 / 136, though 3072 x 3072 x 2080 52 / 58.
+inline GemmKernel gemm_kernel(int64_t M, int64_t N, int64_t K) {
+  const bool ragged = (K % GK) != 0 && M > 64 && K <= ((int64_t)1 << 24);
+  if (ragged && lanes_of(kGemmDma, M, N) >> 32 == 0 &&
+      turns_filled(M, N, GT, GT) * tiles_covered(M, N, GT, GT) >= 0.62)
+    return kGemmDma;
+  return choose_gemm(M, N, K);
+}
 }  // namespace nvfp4_46
