@@ -11,7 +11,7 @@ from . import _host_model as hm
 
 @pytest.mark.parametrize("size,kernel", [
     ((8192, 8192, 8160), "dma"), ((6000, 8000, 96), "dma"), ((2816, 4096, 4064), "dma"),
-    ((6144, 6400, 1056), "dma"), ((3072, 3072, 992), "tile64"), ((4096, 4608, 3040), "tile256x128"),
+    ((6144, 6400, 1056), "dma"), ((3072, 3072, 992), "tile64"), ((4096, 4608, 3040), "tile128"),
     ((2880, 1440, 1056), "tile64"), ((1, 1, (1 << 24) + 32), "staged"), ((16, 8192, 2880), "tile32"),
     ((8192, 8192, 8192), "dma"), ((4096, 8192, (1 << 24) + 32), "staged")])
 def test_kernel_of_a_product(size, kernel):
