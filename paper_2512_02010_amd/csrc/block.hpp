@@ -73,6 +73,15 @@ NV_DEV uint32_t e2m1_sr_code_fast_sel(uint32_t old, float y, uint32_t not_w, flo
     default: return e2m1_sr_code_fast<3>(old, y, not_w, wf, margin);
   }
 }
+NV_DEV void e2m1_sr_code_fast2_sel(uint32_t &old_a, uint32_t &old_b, float ya, float yb, uint32_t not_w, float wf,
+                                   float &margin, int sel) {
+  switch (sel) {
+    case 0: return e2m1_sr_code_fast2<0>(old_a, old_b, ya, yb, not_w, wf, margin);
+    case 1: return e2m1_sr_code_fast2<1>(old_a, old_b, ya, yb, not_w, wf, margin);
+    case 2: return e2m1_sr_code_fast2<2>(old_a, old_b, ya, yb, not_w, wf, margin);
+    default: return e2m1_sr_code_fast2<3>(old_a, old_b, ya, yb, not_w, wf, margin);
+  }
+}
 template <int SEL>
 NV_DEV f32x2 hw_pk_f32_fp4(uint32_t src) {
   return __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(src, 1.0f, SEL);
@@ -113,58 +122,17 @@ NV_DEV void grid8(uint32_t codes, float (&g)[8]) {
   }
 }
 
-// Quantize the block with scale (dec, enc): codes (element i in nibble i of lo for
-// i < 8, of hi for i >= 8).  Also returns a cheap estimate E' of the block's squared
-// error: d' = fma(g, dec, -v) and a running fma(d', d', E'), i.e. two instructions per
-// element where the defining sequence (product, difference, square, tree sum, each
-// rounded) takes four.  E' is only ever used through decide_from_estimates() below.
-// Stochastic rounding (not_w, wf: the complement of each element's random word, and the word
-// rounded to a float) comes in two forms: FAST_SR = true rounds with the conversion
-// instruction and lowers `sr_margin` (see e2m1_sr_code_fast: the codes are only valid if
-// sr_margin stays above kSrMarginAtRisk); FAST_SR = false applies the rule in software and is
-// always valid.
-template <int ROUNDING, int ERR, bool FAST_SR>
-NV_DEV float candidate_as(const float (&v)[16], const uint32_t (&not_w)[16], const float (&wf)[16],
-                          float dec, float enc, uint32_t &lo, uint32_t &hi, float &sr_margin) {
-  uint32_t c[2] = {0u, 0u};
+// What a candidate's error comes out as, eight elements at a time.  kErrMseEstimate is a cheap estimate E'
+// of the block's squared error: d' = fma(g, dec, -v) and a running fma(d', d', E'), i.e. two
+// instructions per element where the defining sequence (product, difference, square, tree sum, each
+// rounded) takes four; E' is only ever used through decide_from_estimates() below.  The other two rules
+// of Section 3.1 are cheap enough to evaluate as defined: D = fl(g*dec), d = fl(D - v), then the
+// fixed-order sum of |d| or the largest |d|.
+template <int ERR>
+struct CandidateError {
   float acc[2] = {0.0f, 0.0f};
   f32x2 sq = {0.0f, 0.0f};
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    float g[8];
-    if (ROUNDING == kRTN) {
-      // v_cvt_scalef32_pk_fp4_f32 fills byte j of the word (first source in the low
-      // nibble); the word is complete before v_cvt_scalef32_pk_f32_fp4 reads the bytes
-      // back, so no partial copies of it have to be kept.
-      uint32_t w = any_register();   // all four bytes are written below
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        w = hw_pk_fp4_sel(w, v[8 * h + 2 * j] * enc, v[8 * h + 2 * j + 1] * enc, j);
-      if (ERR != kErrNone) grid8(w, g);
-      c[h] = w;
-    } else if (FAST_SR) {
-      // one conversion per element (only the first source position rounds as defined):
-      // even elements into the bytes of one word, odd ones into another
-      uint32_t we = 0u, wo = 0u;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int e = 8 * h + 2 * j, o = e + 1;
-        we = e2m1_sr_code_fast_sel(we, v[e] * enc, not_w[e], wf[e], sr_margin, j);
-        wo = e2m1_sr_code_fast_sel(wo, v[o] * enc, not_w[o], wf[o], sr_margin, j);
-      }
-      const uint32_t w = (we & 0x0f0f0f0fu) | ((wo << 4) & 0xf0f0f0f0u);
-      if (ERR != kErrNone) grid8(w, g);
-      c[h] = w;
-    } else {
-      // the rounded values are on the grid, so the conversion that packs them is exact
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        g[j] = e2m1_sr_value(v[8 * h + j] * enc, sr_uniform_of_word(~not_w[8 * h + j]));
-      uint32_t w = 0u;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) w = hw_pk_fp4_sel(w, g[2 * j], g[2 * j + 1], j);
-      c[h] = w;
-    }
+  NV_DEV void add8(const float (&g)[8], const float (&v)[16], int h, float dec) {
     if (ERR == kErrMseEstimate) {
       // A three-source instruction issues at half rate when all three sources sit in registers
       // of the same parity (measured), which d * d + acc is whenever d and acc do.  The two
@@ -180,8 +148,6 @@ NV_DEV float candidate_as(const float (&v)[16], const uint32_t (&not_w)[16], con
       }
     }
     if (ERR == kErrMae || ERR == kErrAbsMax) {
-      // the other two rules of Section 3.1 are cheap enough to evaluate as defined:
-      // D = fl(g*dec), d = fl(D - v), then the fixed-order sum of |d| or the largest |d|
       float e[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
@@ -196,34 +162,134 @@ NV_DEV float candidate_as(const float (&v)[16], const uint32_t (&not_w)[16], con
       }
     }
   }
+  NV_DEV float value() const {
+    if (ERR == kErrMseEstimate) return sq.x + sq.y;
+    return ERR == kErrAbsMax ? fmaxf(acc[0], acc[1]) : acc[0] + acc[1];
+  }
+};
+
+// Quantize the block with scale (dec, enc), round to nearest: codes (element i in nibble i of lo for
+// i < 8, of hi for i >= 8) and the error.
+template <int ERR>
+NV_DEV float rtn_candidate(const float (&v)[16], float dec, float enc, uint32_t &lo, uint32_t &hi) {
+  uint32_t c[2] = {0u, 0u};
+  CandidateError<ERR> error;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    float g[8];
+    // v_cvt_scalef32_pk_fp4_f32 fills byte j of the word (first source in the low
+    // nibble); the word is complete before v_cvt_scalef32_pk_f32_fp4 reads the bytes
+    // back, so no partial copies of it have to be kept.
+    uint32_t w = any_register();   // all four bytes are written below
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      w = hw_pk_fp4_sel(w, v[8 * h + 2 * j] * enc, v[8 * h + 2 * j + 1] * enc, j);
+    if (ERR != kErrNone) grid8(w, g);
+    c[h] = w;
+    error.add8(g, v, h, dec);
+  }
   lo = c[0];
   hi = c[1];
-  if (ERR == kErrMseEstimate) return sq.x + sq.y;
-  return ERR == kErrAbsMax ? fmaxf(acc[0], acc[1]) : acc[0] + acc[1];
+  return error.value();
 }
 
-// The candidate as the kernels use it: stochastic rounding by the conversion instruction,
-// redone in software for the rare block in which an element came too close to the one case
-// where the instruction's answer may differ.
+// The random words of elements 4q .. 4q + 3 of a block, from all sixteen or from whatever draws them.
+NV_DEV void four_words(const uint32_t (&words)[16], int q, uint32_t (&w)[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) w[i] = words[4 * q + i];
+}
+template <typename Words>
+NV_DEV void four_words(const Words &words, int q, uint32_t (&w)[4]) { words(q, w); }
+
+// One scale to round a block under, and what comes of it.
+struct SrCandidate {
+  float dec, enc;
+  uint32_t code[2];
+  float error;
+};
+
+// Quantize the block stochastically under both scales (TWO) or under the first, four elements at a time:
+// their random words are drawn, used for both candidates and forgotten.  What bounds the stochastic
+// kernels is their vector arithmetic (some 700 instructions per block), and how much of its rate they get
+// is a question of waves per SIMD: with one candidate after the other the sixteen words, their complements
+// and their floats stayed in registers for the second (172, two waves).
+// FAST = true rounds with the conversion instruction and lowers `margin` (see e2m1_sr_code_fast: the
+// codes are only valid if it stays above kSrMarginAtRisk); FAST = false applies the rule in software and
+// is always valid.
+template <bool TWO, int ERR, bool FAST, typename Words>
+NV_DEV void sr_candidates(const float (&v)[16], const Words &words, SrCandidate &a, SrCandidate &b, float &margin) {
+  CandidateError<ERR> error_a, error_b;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    float ga[8], gb[8];
+    if (FAST) {
+      // one conversion per element (only the first source position rounds as defined): even
+      // elements into the bytes of one word, odd ones into another
+      uint32_t ea = any_register(), oa = any_register(), eb = any_register(), ob = any_register();
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        uint32_t w[4];
+        four_words(words, 2 * h + q, w);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float x = v[8 * h + 4 * q + i], wf = (float)w[i];
+          const uint32_t not_w = ~w[i];
+          uint32_t &ca = i & 1 ? oa : ea, &cb = i & 1 ? ob : eb;
+          if (TWO) e2m1_sr_code_fast2_sel(ca, cb, x * a.enc, x * b.enc, not_w, wf, margin, 2 * q + i / 2);
+          else ca = e2m1_sr_code_fast_sel(ca, x * a.enc, not_w, wf, margin, 2 * q + i / 2);
+        }
+      }
+      a.code[h] = (ea & 0x0f0f0f0fu) | ((oa << 4) & 0xf0f0f0f0u);
+      if (TWO) b.code[h] = (eb & 0x0f0f0f0fu) | ((ob << 4) & 0xf0f0f0f0u);
+      in_register(a.code[h]);                 // (and not as the four words it is made of)
+      if (TWO) in_register(b.code[h]);
+      if (ERR != kErrNone) {
+        grid8(a.code[h], ga);
+        if (TWO) grid8(b.code[h], gb);
+      }
+    } else {
+      // the rounded values are on the grid, so the conversion that packs them is exact
+      uint32_t wa = 0u, wb = 0u;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        uint32_t w[4];
+        four_words(words, 2 * h + q, w);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float x = v[8 * h + 4 * q + i], u = sr_uniform_of_word(w[i]);
+          ga[4 * q + i] = e2m1_sr_value(x * a.enc, u);
+          if (TWO) gb[4 * q + i] = e2m1_sr_value(x * b.enc, u);
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        wa = hw_pk_fp4_sel(wa, ga[2 * j], ga[2 * j + 1], j);
+        if (TWO) wb = hw_pk_fp4_sel(wb, gb[2 * j], gb[2 * j + 1], j);
+      }
+      a.code[h] = wa;
+      if (TWO) b.code[h] = wb;
+    }
+    error_a.add8(ga, v, h, a.dec);
+    if (TWO) error_b.add8(gb, v, h, b.dec);
+  }
+  a.error = error_a.value();
+  if (TWO) b.error = error_b.value();
+}
+
+// One candidate on its own, for callers that compare candidates across lanes: stochastic rounding by the
+// conversion instruction, redone in software for the rare block in which an element came too close to the
+// one case where the instruction's answer may differ.
 template <int ROUNDING, int ERR>
 NV_DEV float candidate(const float (&v)[16], const uint32_t (&rw)[16], float dec, float enc,
                        uint32_t &lo, uint32_t &hi) {
-  // (the same for every scale the block is tried under: computed once after inlining, and
-  // the words themselves need not stay in registers)
-  uint32_t not_w[16];
-  float wf[16];
-  if (ROUNDING != kRTN) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      not_w[i] = ~rw[i];
-      wf[i] = (float)rw[i];
-    }
-  }
+  if (ROUNDING == kRTN) return rtn_candidate<ERR>(v, dec, enc, lo, hi);
+  SrCandidate c{dec, enc, {0u, 0u}, 0.0f}, none{};
   float margin = __builtin_inff();
-  float E = candidate_as<ROUNDING, ERR, true>(v, not_w, wf, dec, enc, lo, hi, margin);
-  if (ROUNDING != kRTN && !(margin > kSrMarginAtRisk))
-    E = candidate_as<ROUNDING, ERR, false>(v, not_w, wf, dec, enc, lo, hi, margin);
-  return E;
+  sr_candidates<false, ERR, true>(v, rw, c, none, margin);
+  if (!(margin > kSrMarginAtRisk)) sr_candidates<false, ERR, false>(v, rw, c, none, margin);
+  lo = c.code[0];
+  hi = c.code[1];
+  return c.error;
 }
 
 // The block's squared error exactly as it is defined (Table 3 lines 5-6 / 11-12 in fp32):
@@ -307,14 +373,23 @@ NV_DEV bool same_dequantized(uint32_t lo6, uint32_t hi6, uint32_t lo4, uint32_t 
 enum : int { kKeepSix = 0, kKeepFour = 1, kUndecided = 2 };
 
 // kKeepFour / kKeepSix when the estimates (or the codes, for exact ties) settle Table 3
-// line 13, kUndecided when only the defined errors can.
+// line 13, kUndecided when only the defined errors can.  STRAIGHT looks the ties up without a branch: a
+// branch here makes the compiler keep some fifty registers more alive in the stochastic kernels (152
+// against 101, three waves per SIMD instead of four; the instructions it saves are 18 of 700), while
+// the round-to-nearest kernels are faster with it.
+template <bool STRAIGHT>
 NV_DEV int decide_from_estimates(float E6p, float E4p, float dec6, float dec4, float dec6_squared,
                                  float dec4_squared, uint32_t lo6, uint32_t hi6, uint32_t lo4,
                                  uint32_t hi4) {
   const float tol = decision_tolerance(dec6_squared, E6p, dec4_squared, E4p);
   const float diff = E4p - E6p;
-  if (fabsf(diff) > tol) return diff < 0.0f ? kKeepFour : kKeepSix;
   // identical dequantized values: equal errors, and ties keep 6
+  if (STRAIGHT) {
+    const bool sure = fabsf(diff) > tol, same = same_dequantized(lo6, hi6, lo4, hi4, dec6, dec4);
+    const int keep = diff < 0.0f ? kKeepFour : kKeepSix;
+    return sure ? keep : (same ? kKeepSix : kUndecided);
+  }
+  if (fabsf(diff) > tol) return diff < 0.0f ? kKeepFour : kKeepSix;
   return same_dequantized(lo6, hi6, lo4, hi4, dec6, dec4) ? kKeepSix : kUndecided;
 }
 
@@ -367,20 +442,22 @@ NV_DEV void block_scales(float b, const ScaleConsts &k, uint32_t &S6, uint32_t &
   }
 }
 
-// The per-block procedure (Table 3 lines 1-14) in one pass.  DEFINED_ERRORS = false: the
-// squared-error rule compares the cheap estimates and reports through `undecided` when they
-// cannot tell (the result is then provisional).  DEFINED_ERRORS = true: the errors are
-// evaluated exactly as defined.  The other rules are always evaluated as defined.
-template <int ROUNDING, int SELECT, bool DEFINED_ERRORS>
-NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const uint32_t (&rw)[16],
+// The per-block procedure (Table 3 lines 1-14) in one pass.  DEFINED = false: the squared-error rule
+// compares the cheap estimates, stochastic rounding uses the conversion instruction, and where either
+// cannot be sure of its answer that is reported through `undecided` (the result is then provisional).
+// DEFINED = true: errors and roundings are evaluated exactly as defined.  The other rules always
+// evaluate the defined errors.
+template <int ROUNDING, int SELECT, bool DEFINED, typename Words>
+NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
                                        const ScaleConsts &k, const ScaleTable &tab,
                                        bool &undecided) {
   float b = 0.0f;
 #pragma unroll
   for (int i = 0; i < 16; i += 2) b = fmaxf(fmaxf(b, fabsf(v[i])), fabsf(v[i + 1]));
 
+  constexpr bool kSix = SELECT != kSelForce4, kFour = SELECT != kSelForce6, kBoth = kSix && kFour;
   uint32_t S6 = 0u, S4 = 0u;
-  if (SELECT == kSelForce4 || SELECT == kSelForce6) {
+  if (!kBoth) {
     // one candidate only: the same multiply-then-guard for its scale alone
     const float c = SELECT == kSelForce4 ? k.c4 : k.c6, q = b * (SELECT == kSelForce4 ? k.rc4 : k.rc6);
     uint32_t S = e4m3_encode(q);
@@ -390,34 +467,47 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const uint32_t (&rw
     block_scales(b, k, S6, S4);
   }
 
-  constexpr int kErr = SELECT == kSel46 ? (DEFINED_ERRORS ? kErrNone : kErrMseEstimate)
+  constexpr int kErr = SELECT == kSel46 ? (DEFINED ? kErrNone : kErrMseEstimate)
                        : SELECT == kSel46Mae ? kErrMae
                        : SELECT == kSel46AbsMax ? kErrAbsMax : kErrNone;
-  // Appendix A.3's second alternative compares round-to-nearest candidates and rounds
-  // only the winner stochastically.
-  constexpr int kCandRounding = ROUNDING == kSRAfterRtnSelect ? kRTN : ROUNDING;
   BlockResult r6{}, r4{};
   float E6p = 0.0f, E4p = 0.0f, enc6 = 0.0f, enc4 = 0.0f, m6 = 0.0f, m4 = 0.0f;
-  if (SELECT != kSelForce4) {
-    const float4 t = tab.e[S6];
-    m6 = t.z;
-    r6.scale = S6;
-    r6.dec = t.x;
-    r6.four = 0u;
-    enc6 = t.y;
-    if (!(ROUNDING == kSRAfterRtnSelect && SELECT == kSelForce6))
-      E6p = candidate<kCandRounding, kErr>(v, rw, t.x, t.y, r6.lo, r6.hi);
+  float margin = __builtin_inff();
+  auto look_up = [&](uint32_t S, BlockResult &r, float &enc, float &m) {
+    const float4 t = tab.e[S];
+    r.scale = S;
+    r.dec = t.x;
+    enc = t.y;
+    m = t.z;
+  };
+  if (ROUNDING == kSR) {
+    if (kSix) look_up(S6, r6, enc6, m6);
+    if (kFour) look_up(S4, r4, enc4, m4);
+    SrCandidate c{kSix ? r6.dec : r4.dec, kSix ? enc6 : enc4, {0u, 0u}, 0.0f}, d{r4.dec, enc4, {0u, 0u}, 0.0f};
+    sr_candidates<kBoth, kErr, !DEFINED>(v, words, c, d, margin);
+    E6p = c.error;
+    E4p = d.error;
+    BlockResult &first = kSix ? r6 : r4;
+    first.lo = c.code[0];
+    first.hi = c.code[1];
+    if (kBoth) {
+      r4.lo = d.code[0];
+      r4.hi = d.code[1];
+    }
+  } else {
+    // Appendix A.3's second alternative compares round-to-nearest candidates and rounds only the
+    // winner stochastically; a single candidate need not be rounded to nearest for that.
+    constexpr bool kRound = ROUNDING == kRTN || kBoth;
+    if (kSix) {
+      look_up(S6, r6, enc6, m6);
+      if (kRound) E6p = rtn_candidate<kErr>(v, r6.dec, enc6, r6.lo, r6.hi);
+    }
+    if (kFour) {
+      look_up(S4, r4, enc4, m4);
+      if (kRound) E4p = rtn_candidate<kErr>(v, r4.dec, enc4, r4.lo, r4.hi);
+    }
   }
-  if (SELECT != kSelForce6) {
-    const float4 t = tab.e[S4];
-    m4 = t.z;
-    r4.scale = S4;
-    r4.dec = t.x;
-    r4.four = 1u;
-    enc4 = t.y;
-    if (!(ROUNDING == kSRAfterRtnSelect && SELECT == kSelForce4))
-      E4p = candidate<kCandRounding, kErr>(v, rw, t.x, t.y, r4.lo, r4.hi);
-  }
+  r4.four = 1u;
   bool four;
   if (SELECT == kSelForce6) {
     four = false;
@@ -425,30 +515,37 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const uint32_t (&rw
     four = true;
   } else if (SELECT == kSel46Mae || SELECT == kSel46AbsMax) {
     four = E4p < E6p;   // as defined
-  } else if (DEFINED_ERRORS) {
+  } else if (DEFINED) {
     four = exact_error(v, r4.lo, r4.hi, r4.dec) < exact_error(v, r6.lo, r6.hi, r6.dec);
   } else {
-    const int d = decide_from_estimates(E6p, E4p, r6.dec, r4.dec, m6, m4, r6.lo, r6.hi, r4.lo, r4.hi);
+    const int d = decide_from_estimates<ROUNDING == kSR>(E6p, E4p, r6.dec, r4.dec, m6, m4, r6.lo, r6.hi, r4.lo,
+                                                         r4.hi);
     four = d == kKeepFour;
     undecided = d == kUndecided;
   }
   BlockResult r = four ? r4 : r6;
-  if (ROUNDING == kSRAfterRtnSelect)
-    (void)candidate<kSR, kErrNone>(v, rw, r.dec, four ? enc4 : enc6, r.lo, r.hi);
+  if (ROUNDING == kSRAfterRtnSelect) {
+    SrCandidate c{r.dec, four ? enc4 : enc6, {0u, 0u}, 0.0f}, none{};
+    sr_candidates<false, kErrNone, !DEFINED>(v, words, c, none, margin);
+    r.lo = c.code[0];
+    r.hi = c.code[1];
+  }
+  if (ROUNDING != kRTN && !DEFINED) undecided |= !(margin > kSrMarginAtRisk);
   return r;
 }
 
-// The whole per-block procedure.  `again(w, ww)` must produce the block's values (and its
-// stochastic-rounding words) once more: the rare block that the estimates cannot decide
-// is redone from those with the defined errors, so that nothing of the first pass has to
-// stay in registers for it -- keeping the sixteen values and both candidates alive across
-// the common path cost the rowwise kernel three of its eight waves per SIMD.
-template <int ROUNDING, int SELECT, typename Again>
-NV_DEV BlockResult quantize_block(const float (&v)[16], const uint32_t (&rw)[16],
+// The whole per-block procedure.  `words` is the block's sixteen stochastic-rounding words or a function
+// that gives four of them at a time.  `again(w, ww)` must produce the block's values (and all its words)
+// once more: the rare block whose first pass is not sure of its answer is redone from those as it is
+// defined, so that nothing of the first pass has to stay in registers for it -- keeping the sixteen
+// values and both candidates alive across the common path cost the rowwise kernel three of its
+// eight waves per SIMD.
+template <int ROUNDING, int SELECT, typename Words, typename Again>
+NV_DEV BlockResult quantize_block(const float (&v)[16], const Words &words,
                                   const ScaleConsts &k, const ScaleTable &tab, Again &&again) {
   bool undecided = false;
-  BlockResult r = quantize_block_pass<ROUNDING, SELECT, false>(v, rw, k, tab, undecided);
-  if (SELECT == kSel46 && undecided) {
+  BlockResult r = quantize_block_pass<ROUNDING, SELECT, false>(v, words, k, tab, undecided);
+  if ((SELECT == kSel46 || ROUNDING != kRTN) && undecided) {
     float w[16];
     uint32_t ww[16];
     again(w, ww);

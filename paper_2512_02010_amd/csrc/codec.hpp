@@ -107,6 +107,13 @@ NV_DEV void in_register_pair(f32x2 &p) {
 #endif
 }
 
+// Makes the compiler have the word computed at this point.
+NV_DEV void in_register(uint32_t &w) {
+#ifndef NVFP4_46_CVT_SR_PK_FP4_ON_HOST
+  asm("" : "+v"(w));
+#endif
+}
+
 // A constant the compiler must keep in a vector register, and in an odd-numbered one: it would
 // otherwise put a literal used this often into a scalar register, and an fp32 instruction with
 // a scalar-register source issues at half the rate (measured: v_fma_f32 2.4 against 4.2 cycles
@@ -159,6 +166,32 @@ NV_DEV uint32_t e2m1_sr_code_fast(uint32_t old, float y, uint32_t not_w, float w
   return cvt_sr_pk_fp4<SEL>(old, src, not_w);
 }
 constexpr float kSrMarginAtRisk = 2048.0f;
+
+// The same element rounded under two scales: byte SEL of both words, the others kept.  The two conversions
+// stand in one piece of assembly, so that the wait state after them is one for both.
+template <int SEL>
+NV_DEV void e2m1_sr_code_fast2(uint32_t &old_a, uint32_t &old_b, float ya, float yb, uint32_t not_w, float wf,
+                               float &margin) {
+#ifdef NVFP4_46_CVT_SR_PK_FP4_ON_HOST
+  old_a = e2m1_sr_code_fast<SEL>(old_a, ya, not_w, wf, margin);
+  old_b = e2m1_sr_code_fast<SEL>(old_b, yb, not_w, wf, margin);
+#else
+  const float c = in_odd_vector_register(0x1p33f);
+  const float ta = __builtin_fmaf(fabsf(ya), c, -wf), tb = __builtin_fmaf(fabsf(yb), c, -wf);
+  margin = fminf(fminf(margin, fabsf(ta)), fabsf(ta - 0x1p32f));   // one v_min3_f32
+  margin = fminf(fminf(margin, fabsf(tb)), fabsf(tb - 0x1p32f));
+  const f32x2 sa = {ya, ta}, sb = {yb, tb};
+#define NV_SR2(op_sel)                                                                             \
+  asm("v_cvt_scalef32_sr_pk_fp4_f32 %0, %2, %4, 1.0" op_sel                                        \
+      "\n\tv_cvt_scalef32_sr_pk_fp4_f32 %1, %3, %4, 1.0" op_sel "\n\ts_nop 0"                      \
+      : "+&v"(old_a), "+&v"(old_b) : "v"(sa), "v"(sb), "v"(not_w))
+  if constexpr (SEL == 0) NV_SR2("");
+  else if constexpr (SEL == 1) NV_SR2(" op_sel:[0,0,1,0]");
+  else if constexpr (SEL == 2) NV_SR2(" op_sel:[0,0,0,1]");
+  else NV_SR2(" op_sel:[0,0,1,1]");
+#undef NV_SR2
+#endif
+}
 
 // Code of a value that is already on the grid (sign included).
 NV_DEV uint32_t e2m1_code_of_grid_value(float r) {
@@ -223,6 +256,42 @@ NV_DEV void sr_words4(uint64_t seed, uint64_t q, uint32_t w[4]) {
                             (uint32_t)(seed >> 32));
 #pragma unroll
   for (int j = 0; j < 4; ++j) w[j] = p.w[j];
+}
+// The same for a group whose upper counter word is the same for the whole wave (in a scalar register):
+// the first two of the ten rounds meet the two zero counter words and that one, so of their four
+// multiplications two are left to the vector unit.
+NV_DEV void sr_words4_in_wave(uint64_t seed, uint32_t q_lo, uint32_t q_hi, uint32_t w[4]) {
+  uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+  auto next_key = [&] { k0 += 0x9E3779B9u; k1 += 0xBB67AE85u; };
+  uint64_t p0 = (uint64_t)0xD2511F53u * q_lo;
+  const uint32_t s0 = q_hi ^ k0;                                        // round 1
+  uint32_t c2 = (uint32_t)(p0 >> 32) ^ k1, c3 = (uint32_t)p0;
+  next_key();
+  const uint64_t q0 = (uint64_t)0xD2511F53u * s0;                       // round 2
+  uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
+  uint32_t c0 = (uint32_t)(p1 >> 32) ^ k0, c1 = (uint32_t)p1;
+  c2 = c3 ^ ((uint32_t)(q0 >> 32) ^ k1);
+  next_key();
+  p0 = (uint64_t)0xD2511F53u * c0;                                      // round 3
+  p1 = (uint64_t)0xCD9E8D57u * c2;
+  c0 = xor3((uint32_t)(p1 >> 32), c1, k0);
+  c1 = (uint32_t)p1;
+  c2 = (uint32_t)(p0 >> 32) ^ ((uint32_t)q0 ^ k1);
+  c3 = (uint32_t)p0;
+#pragma unroll
+  for (int r = 3; r < 10; ++r) {
+    next_key();
+    p0 = (uint64_t)0xD2511F53u * c0;
+    p1 = (uint64_t)0xCD9E8D57u * c2;
+    c0 = xor3((uint32_t)(p1 >> 32), c1, k0);
+    c1 = (uint32_t)p1;
+    c2 = xor3((uint32_t)(p0 >> 32), c3, k1);
+    c3 = (uint32_t)p0;
+  }
+  w[0] = c0;
+  w[1] = c1;
+  w[2] = c2;
+  w[3] = c3;
 }
 NV_DEV float sr_uniform_of_word(uint32_t w) { return (float)(w >> 8) * 0x1p-24f; }
 

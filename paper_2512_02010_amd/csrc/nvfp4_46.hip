@@ -437,7 +437,6 @@ __global__ __launch_bounds__(kThreads) void k_flat(
   auto work = [&](uint32_t r, uint32_t live, const Raw &raw) {
     const int64_t base = (int64_t)r * kThreads;
     float v[16];
-    uint32_t u[16];
     unpack16(raw, v);
     if (RHT) {
       // the sign word depends on the block's position in its row only; with the usual
@@ -459,12 +458,12 @@ __global__ __launch_bounds__(kThreads) void k_flat(
       for (int i = 0; i < 16; ++i) amax = fmaxf(amax, fabsf(v[i]));
       return;
     }
-    auto random_words = [&](uint32_t (&uu)[16]) {
-      const uint64_t q0 = ((uint64_t)base + tid) * 4u;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) sr_words4(sr_seed, q0 + j, &uu[4 * j]);
+    // four words of the block at a time; base is a multiple of 256 blocks, 1024 groups of four, so a
+    // lane's own part of the counter never carries out of the lower word
+    const uint64_t q0 = (uint64_t)base * 4u;
+    auto words = [&](int q, uint32_t (&w)[4]) {
+      sr_words4_in_wave(sr_seed, (uint32_t)q0 + (4u * tid + q), (uint32_t)(q0 >> 32), w);
     };
-    if (ROUNDING != kRTN) random_words(u);
     // the block once more, from memory (a lane without a block of its own holds a copy of
     // the round's last block, as fetch() gave it)
     auto again = [&](float (&w)[16], uint32_t (&uu)[16]) {
@@ -472,9 +471,12 @@ __global__ __launch_bounds__(kThreads) void k_flat(
       load_block<XF32>(x + Raw::kPieces * (base + (tid < live ? tid : live - 1)), r2);
       unpack16(r2, w);
       if (RHT) transform(w);
-      if (ROUNDING != kRTN) random_words(uu);
+      if (ROUNDING != kRTN) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sr_words4(sr_seed, q0 + 4u * tid + j, &uu[4 * j]);
+      }
     };
-    const BlockResult res = quantize_block<ROUNDING, SELECT>(v, u, sc, tab, again);
+    const BlockResult res = quantize_block<ROUNDING, SELECT>(v, words, sc, tab, again);
     if (OUT == kOutCodes) {
       store_as<kNtCodes>(codes + base + tid, make_uint2(res.lo, res.hi));
       store_as<kNtCodes>(scales + base + tid, (uint8_t)res.scale);
@@ -746,28 +748,36 @@ __global__ __launch_bounds__(kThreads) void k_tile(
       const int64_t gr = r0 + row, gc = c0 + rbk * 16;
       if (gr < rows && gc < cols) {
         float v[16];
-        uint32_t u[16];
         const int64_t k = gr * nb_per_row + (gc >> 4);
-        // the lane's block out of the tile, with its random words
-        auto take = [&](float (&w)[16], uint32_t (&uu)[16]) {
+        // the lane's block out of the tile, and its random words (WANT_ROW is for codes: words are in LDS)
+        auto block = [&](float (&w)[16]) {
           const uint4 *own = reinterpret_cast<const uint4 *>(tile) + unit * Raw::kPieces;
           Raw mine;
 #pragma unroll
           for (int q = 0; q < Raw::kPieces; ++q) mine.w[q] = own[q];
           unpack16(mine, w);
+        };
+        auto four = [&](int q, uint32_t (&w)[4]) {
+          const uint4 w4 = words[kWords ? row * (TC / 4) + rbk * 4 + q : 0];
+          w[0] = w4.x;
+          w[1] = w4.y;
+          w[2] = w4.z;
+          w[3] = w4.w;
+        };
+        auto take = [&](float (&w)[16], uint32_t (&uu)[16]) {
+          block(w);
           if (kWords) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              const uint4 w4 = words[row * (TC / 4) + rbk * 4 + q];
-              uu[4 * q] = w4.x;
-              uu[4 * q + 1] = w4.y;
-              uu[4 * q + 2] = w4.z;
-              uu[4 * q + 3] = w4.w;
+              uint32_t w4[4];
+              four(q, w4);
+#pragma unroll
+              for (int i = 0; i < 4; ++i) uu[4 * q + i] = w4[i];
             }
           }
         };
-        take(v, u);
-        BlockResult r = quantize_block<ROUNDING, SELECT>(v, u, sc, tab, take);
+        block(v);
+        BlockResult r = quantize_block<ROUNDING, SELECT>(v, four, sc, tab, take);
         reinterpret_cast<uint2 *>(codes_row)[k] = make_uint2(r.lo, r.hi);
         scales_row[k] = (uint8_t)r.scale;
         if (choice_row) choice_row[k] = (uint8_t)r.four;
@@ -786,7 +796,6 @@ __global__ __launch_bounds__(kThreads) void k_tile(
     const int64_t gc = c0 + 2 * cp;               // even column of the pair
     if (gr >= rows || gc >= cols) continue;       // (cols is even, so the pair is in or out together)
     float va[16], vb[16];
-    uint32_t ua[16], ub[16];
     // the lane's two column blocks (transformed) out of the tile or memory
     auto take = [&](float (&wa)[16], float (&wb)[16]) {
 #pragma unroll
@@ -810,11 +819,13 @@ __global__ __launch_bounds__(kThreads) void k_tile(
         rht16(wb, sw);
       }
     };
-    auto random_words = [&](int column, uint32_t (&uu)[16]) {           // 0 or 1 of the pair
+    auto word_at = [&](int i, int column) {                             // row i, column 0 or 1 of the pair
+      return reinterpret_cast<const uint32_t *>(words)[kWords ? (rb * 16 + i) * TC + 2 * cp + column : 0];
+    };
+    auto random_words = [&](int column, uint32_t (&uu)[16]) {
       if (kWords) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-          uu[i] = reinterpret_cast<const uint32_t *>(words)[(rb * 16 + i) * TC + 2 * cp + column];
+        for (int i = 0; i < 16; ++i) uu[i] = word_at(i, column);
       }
     };
     auto draw = [&](uint32_t (&uua)[16], uint32_t (&uub)[16]) {         // both columns of the pair
@@ -830,23 +841,36 @@ __global__ __launch_bounds__(kThreads) void k_tile(
       }
     };
     take(va, vb);
-    if (kDrawn) draw(ua, ub);
-    random_words(0, ua);
-    BlockResult ra = quantize_block<ROUNDING, SELECT>(va, ua, sc, tab, [&](float (&w)[16], uint32_t (&uu)[16]) {
+    auto first = [&](float (&w)[16], uint32_t (&uu)[16]) {
       float other[16];
       uint32_t other_u[16];
       take(w, other);
       if (kDrawn) draw(uu, other_u);
       random_words(0, uu);
-    });
-    random_words(1, ub);
-    BlockResult rbk = quantize_block<ROUNDING, SELECT>(vb, ub, sc, tab, [&](float (&w)[16], uint32_t (&uu)[16]) {
+    };
+    auto second = [&](float (&w)[16], uint32_t (&uu)[16]) {
       float other[16];
       uint32_t other_u[16];
       take(other, w);
       if (kDrawn) draw(other_u, uu);
       random_words(1, uu);
-    });
+    };
+    BlockResult ra, rbk;
+    if constexpr (kDrawn) {
+      uint32_t ua[16], ub[16];
+      draw(ua, ub);
+      ra = quantize_block<ROUNDING, SELECT>(va, ua, sc, tab, first);
+      rbk = quantize_block<ROUNDING, SELECT>(vb, ub, sc, tab, second);
+    } else {
+      auto four_of = [&](int column) {
+        return [&, column](int q, uint32_t (&w)[4]) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) w[i] = word_at(4 * q + i, column);
+        };
+      };
+      ra = quantize_block<ROUNDING, SELECT>(va, four_of(0), sc, tab, first);
+      rbk = quantize_block<ROUNDING, SELECT>(vb, four_of(1), sc, tab, second);
+    }
     if (OUT == kOutCodes) {
       const int ia = (2 * cp) * kColBlockRows + rb, ib = ia + kColBlockRows;
       stage_codes[ia] = make_uint2(ra.lo, ra.hi);
