@@ -1,13 +1,16 @@
-"""Thin Python binding of ``libnvfp4_46.so`` (ctypes; argument marshalling only).
+"""Thin Python binding of ``libnvfp4_46.so`` (argument marshalling only).
 
 Every function has the name of the C entry point it calls (``include/nvfp4_46.h``)
-and does no arithmetic of its own.  PyTorch supplies device memory and the
+and does no arithmetic of its own.  The functions that allocate outputs and check statuses
+go through ``nvfp4_46_python.so`` (``csrc/python.cpp``), the raw ones through ctypes.  PyTorch supplies device memory and the
 stream; tensors passed in must live on the current CUDA (ROCm) device.  There
 is no CPU fallback: if the shared library has not been built, loading fails.
 """
 from __future__ import annotations
 
 import ctypes as C
+import importlib.machinery
+import importlib.util
 import os
 from pathlib import Path
 
@@ -100,6 +103,29 @@ def lib() -> C.CDLL:
         L.nvfp4_46_debug_philox.argtypes = [vp, u32, u32, i64, vp, vp]
         _lib = L
     return _lib
+
+
+NATIVE_ENTRY_POINTS = ("tensor_scale", "tensor_scale_ws", "quantize", "scale_quantize", "dequantize", "fake_quant",
+                       "gemm")
+_native = None
+
+
+def native():
+    """The module of ``csrc/python.cpp``, connected to the library (raises if either has not been built)."""
+    global _native
+    if _native is None:
+        path = _PKG / "nvfp4_46_python.so"
+        if not path.exists():
+            raise FileNotFoundError(
+                f"{path} is missing: build it with `python -m paper_2512_02010_amd.build`")
+        loader = importlib.machinery.ExtensionFileLoader("nvfp4_46_python", str(path))
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("nvfp4_46_python", loader))
+        loader.exec_module(module)
+        L = lib()
+        module.connect(Nvfp4Error, *(C.cast(getattr(L, "nvfp4_46_" + name), C.c_void_p).value
+                                     for name in NATIVE_ENTRY_POINTS))
+        _native = module
+    return _native
 
 
 def status_string(status: int) -> str:
@@ -204,6 +230,7 @@ def gemm_raw(codes_a, scales_a, alpha_a, codes_b, scales_b, alpha_b, M, N, K, ou
 
 
 # ---- the same calls with output allocation and error checking ---------------------------
+# (`None` where an output goes lets the native module allocate it, as _device_empty would)
 
 def _shape_of(x):
     assert x.dim() == 2 and x.dtype in (torch.bfloat16, torch.float32)
@@ -214,16 +241,20 @@ def x_dtype_of(x: torch.Tensor) -> int:
     return X_F32 if x.dtype == torch.float32 else X_BF16
 
 
+def _alpha_for(x, out):
+    if out is None and OUTPUT_ALLOCATOR is not _device_empty:
+        _shape_of(x)
+        return _new((1,), torch.float32, x.device)
+    return out
+
+
 def nvfp4_46_tensor_scale(x: torch.Tensor, layout: int = ROWWISE, rht: int = 0, rht_seed: int = 0,
                           fp8_max: float = 256.0, out: torch.Tensor | None = None,
                           stream=None) -> torch.Tensor:
     """alpha (1-element fp32 device tensor) of a BF16 or fp32 device tensor."""
-    rows, cols = _shape_of(x)
-    alpha = out if out is not None else _new((1,), torch.float32, x.device)
-    p = make_params(rows, cols, layout=layout, rht=rht, rht_seed=rht_seed, fp8_max=fp8_max,
-                    x_dtype=x_dtype_of(x))
-    _check(tensor_scale_raw(x, p, alpha, stream), "nvfp4_46_tensor_scale")
-    return alpha
+    return (_native or native()).tensor_scale(
+        x, _alpha_for(x, out), None if stream is None else _stream(stream),
+        layout, RTN, SEL_46_MSE, rht, 0, rht_seed, fp8_max, 0)
 
 
 def new_workspace(device="cuda") -> torch.Tensor:
@@ -235,13 +266,9 @@ def nvfp4_46_tensor_scale_ws(x: torch.Tensor, workspace: torch.Tensor, layout: i
                              rht: int = 0, rht_seed: int = 0, fp8_max: float = 256.0,
                              out: torch.Tensor | None = None, stream=None) -> torch.Tensor:
     """nvfp4_46_tensor_scale in one launch, with a caller-owned zeroed workspace."""
-    rows, cols = _shape_of(x)
-    alpha = out if out is not None else _new((1,), torch.float32, x.device)
-    p = make_params(rows, cols, layout=layout, rht=rht, rht_seed=rht_seed, fp8_max=fp8_max,
-                    x_dtype=x_dtype_of(x))
-    _check(tensor_scale_ws_raw(x, p, alpha, workspace, workspace.numel(), stream),
-           "nvfp4_46_tensor_scale_ws")
-    return alpha
+    return (_native or native()).tensor_scale_ws(
+        x, workspace, _alpha_for(x, out), None if stream is None else _stream(stream),
+        layout, RTN, SEL_46_MSE, rht, 0, rht_seed, fp8_max, 0)
 
 
 def alloc_outputs(rows: int, cols: int, layout: int, device, want_choice: bool = True,
@@ -272,15 +299,11 @@ def nvfp4_46_quantize(x: torch.Tensor, alpha: torch.Tensor, layout: int = ROWWIS
                       sr_seed: int = 0, rht_seed: int = 0, fp8_max: float = 256.0,
                       want_choice: bool = True, out: dict | None = None, stream=None,
                       block2d: int = 0) -> dict:
-    rows, cols = _shape_of(x)
-    o = out if out is not None else alloc_outputs(rows, cols, layout, x.device, want_choice,
-                                                  block2d)
-    p = make_params(rows, cols, layout, rounding, select, rht, sr_seed, rht_seed, fp8_max,
-                    block2d, x_dtype_of(x))
-    _check(quantize_raw(x, p, alpha, o["codes_row"], o["scales_row"], o["codes_col"],
-                        o["scales_col"], o["choice_row"], o["choice_col"], stream),
-           "nvfp4_46_quantize")
-    return o
+    if out is None and OUTPUT_ALLOCATOR is not _device_empty:
+        out = alloc_outputs(*_shape_of(x), layout, x.device, want_choice, block2d)
+    return (_native or native()).quantize(
+        x, alpha, out, want_choice, None if stream is None else _stream(stream),
+        layout, rounding, select, rht, sr_seed, rht_seed, fp8_max, block2d)
 
 
 def nvfp4_46_scale_quantize(x: torch.Tensor, workspace: torch.Tensor | None = None,
@@ -289,26 +312,22 @@ def nvfp4_46_scale_quantize(x: torch.Tensor, workspace: torch.Tensor | None = No
                             fp8_max: float = 256.0, want_choice: bool = True, stream=None,
                             block2d: int = 0) -> dict:
     """nvfp4_46_tensor_scale(_ws) and nvfp4_46_quantize in one call; the scale comes as "alpha"."""
-    rows, cols = _shape_of(x)
-    alpha = _new((1,), torch.float32, x.device)
-    o = alloc_outputs(rows, cols, layout, x.device, want_choice, block2d)
-    p = make_params(rows, cols, layout, rounding, select, rht, sr_seed, rht_seed, fp8_max,
-                    block2d, x_dtype_of(x))
-    _check(scale_quantize_raw(x, p, alpha, workspace, workspace.numel() if workspace is not None else 0,
-                              o["codes_row"], o["scales_row"], o["codes_col"], o["scales_col"],
-                              o["choice_row"], o["choice_col"], stream), "nvfp4_46_scale_quantize")
-    o["alpha"] = alpha
-    return o
+    alpha = _alpha_for(x, None)
+    out = None
+    if OUTPUT_ALLOCATOR is not _device_empty:
+        out = alloc_outputs(*_shape_of(x), layout, x.device, want_choice, block2d)
+    return (_native or native()).scale_quantize(
+        x, workspace, alpha, out, want_choice, None if stream is None else _stream(stream),
+        layout, rounding, select, rht, sr_seed, rht_seed, fp8_max, block2d)
 
 
 def nvfp4_46_dequantize(codes: torch.Tensor, scales: torch.Tensor, alpha: torch.Tensor, rows: int,
                         cols: int, layout: int = ROWWISE, out: torch.Tensor | None = None,
                         stream=None) -> torch.Tensor:
-    if out is None:
+    if out is None and OUTPUT_ALLOCATOR is not _device_empty:
         out = _new((rows, cols), torch.bfloat16, codes.device)
-    _check(dequantize_raw(codes, scales, alpha, rows, cols, layout, out, stream),
-           "nvfp4_46_dequantize")
-    return out
+    return (_native or native()).dequantize(codes, scales, alpha, rows, cols, layout, out,
+                                            None if stream is None else _stream(stream))
 
 
 def nvfp4_46_fake_quant(x: torch.Tensor, alpha: torch.Tensor, layout: int = ROWWISE,
@@ -316,13 +335,11 @@ def nvfp4_46_fake_quant(x: torch.Tensor, alpha: torch.Tensor, layout: int = ROWW
                         sr_seed: int = 0, rht_seed: int = 0, fp8_max: float = 256.0,
                         out: torch.Tensor | None = None, stream=None,
                         block2d: int = 0) -> torch.Tensor:
-    rows, cols = _shape_of(x)
-    if out is None:
-        out = _new(tuple(x.shape), torch.bfloat16, x.device)
-    p = make_params(rows, cols, layout, rounding, select, rht, sr_seed, rht_seed, fp8_max,
-                    block2d, x_dtype_of(x))
-    _check(fake_quant_raw(x, p, alpha, out, stream), "nvfp4_46_fake_quant")
-    return out
+    if out is None and OUTPUT_ALLOCATOR is not _device_empty:
+        out = _new(_shape_of(x), torch.bfloat16, x.device)
+    return (_native or native()).fake_quant(
+        x, alpha, out, None if stream is None else _stream(stream),
+        layout, rounding, select, rht, sr_seed, rht_seed, fp8_max, block2d)
 
 
 def nvfp4_46_gemm(codes_a: torch.Tensor, scales_a: torch.Tensor, alpha_a: torch.Tensor,
@@ -331,15 +348,11 @@ def nvfp4_46_gemm(codes_a: torch.Tensor, scales_a: torch.Tensor, alpha_a: torch.
                   stream=None, flags: int = 0) -> torch.Tensor:
     """C [M][N] = alpha_a alpha_b A B^T of two rowwise-quantized operands A [M][K], B [N][K];
     `flags` marks operands whose scales come per 16x16 tile ([rows/16][K/16])."""
-    M, N, K = int(codes_a.shape[0]), int(codes_b.shape[0]), int(codes_a.shape[1]) * 2
-    assert codes_b.shape[1] * 2 == K
-    assert tuple(scales_a.shape) == (M // 16 if flags & GEMM_A_TILE_SCALES else M, K // 16)
-    assert tuple(scales_b.shape) == (N // 16 if flags & GEMM_B_TILE_SCALES else N, K // 16)
-    if out is None:
-        out = _new((M, N), torch.float32 if out_dtype == OUT_F32 else torch.bfloat16, codes_a.device)
-    _check(gemm_raw(codes_a, scales_a, alpha_a, codes_b, scales_b, alpha_b, M, N, K, out_dtype,
-                    out, stream, flags), "nvfp4_46_gemm")
-    return out
+    if out is None and OUTPUT_ALLOCATOR is not _device_empty:
+        out = _new((int(codes_a.shape[0]), int(codes_b.shape[0])),
+                   torch.float32 if out_dtype == OUT_F32 else torch.bfloat16, codes_a.device)
+    return (_native or native()).gemm(codes_a, scales_a, alpha_a, codes_b, scales_b, alpha_b, out_dtype, out,
+                                      None if stream is None else _stream(stream), flags)
 
 
 # ---- scalar codecs ------------------------------------------------------------------------

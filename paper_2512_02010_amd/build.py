@@ -1,4 +1,5 @@
-"""Compile the HIP library in-tree: ``paper_2512_02010_amd/libnvfp4_46.so`` (gfx950 only)."""
+"""Compile the HIP library in-tree, ``paper_2512_02010_amd/libnvfp4_46.so`` (gfx950 only), and the module through
+which Python calls it, ``nvfp4_46_python.so`` (host code)."""
 from __future__ import annotations
 
 import os
@@ -19,6 +20,7 @@ UNITS += [(PKG / "csrc" / "gemm.hip", {"NVFP4_46_GEMM_PART": part}, f"gemm.part{
           for part in (5, 6, 0)]
 UNITS.append((PKG / "csrc" / "nvfp4_46.hip", {"NVFP4_46_PART": 0}, "nvfp4_46.part0"))
 SO = PKG / "libnvfp4_46.so"
+PYTHON_SO = PKG / "nvfp4_46_python.so"
 
 # -ffp-contract=off: the method's arithmetic is one rounding per operation.
 # -packed-fp32-ops off: never let the compiler form v_pk_*_f32 from scalar float code.
@@ -30,7 +32,6 @@ HIPCC_FLAGS = [
     # m0 is a reserved register
     "-Wno-inline-asm",
 ]
-
 
 
 def hipcc() -> str:
@@ -69,5 +70,27 @@ def build(out: Path | None = None, defines: dict | None = None, extra: list | No
     return out
 
 
+def build_python() -> Path:
+    """Compile csrc/python.cpp against the installed torch and interpreter."""
+    import sysconfig
+
+    import torch
+    home = Path(torch.__file__).resolve().parent
+    cxx = os.environ.get("CXX") or shutil.which("g++") or shutil.which("c++")
+    if not cxx:
+        raise RuntimeError("no host C++ compiler found")
+    include = [home / "include", home / "include" / "torch" / "csrc" / "api" / "include",
+               Path(hipcc()).resolve().parent.parent / "include", sysconfig.get_paths()["include"]]
+    tmp = PYTHON_SO.with_suffix(f".tmp{os.getpid()}.so")
+    subprocess.run([cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", f"-I{ROOT / 'include'}",
+                    *(f for d in include for f in ("-isystem", str(d))), str(PKG / "csrc" / "python.cpp"),
+                    "-o", str(tmp), f"-L{home / 'lib'}", "-ltorch_python", "-ltorch", "-lc10", "-lc10_hip"],
+                   check=True)
+    os.replace(tmp, PYTHON_SO)
+    return PYTHON_SO
+
+
 if __name__ == "__main__":
     print(build())
+    print(build_python())

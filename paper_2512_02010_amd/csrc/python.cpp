@@ -1,0 +1,314 @@
+// Python's way to the C ABI (include/nvfp4_46.h): output allocation, argument marshalling and the call in
+// one C function per entry point.  binding.py hands in the entry points of the library that it loaded and the
+// exception for statuses other than NVFP4_OK.
+//
+// Through ctypes and torch.empty a call spent more time in the interpreter than in the launch (per call
+// among others, 256 x 1024: quantize with its three outputs 12.5 us, of which launch 3.6, three torch.empty 4.8;
+// three calls of a round trip 26.4; here 7.2, of which launch 4, and 16.4).  Nothing is kept between calls.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+
+#include <cstring>
+
+#include <ATen/ATen.h>
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include "nvfp4_46.h"
+
+namespace {
+
+// The library's entry points, in the order of binding.py's NATIVE_ENTRY_POINTS.
+struct EntryPoints {
+  int (*tensor_scale)(const void *, const nvfp4_46_params *, float *, void *);
+  int (*tensor_scale_ws)(const void *, const nvfp4_46_params *, float *, void *, size_t, void *);
+  int (*quantize)(const void *, const nvfp4_46_params *, const float *, void *, void *, void *, void *, void *,
+                  void *, void *);
+  int (*scale_quantize)(const void *, const nvfp4_46_params *, float *, void *, size_t, void *, void *, void *,
+                        void *, void *, void *, void *);
+  int (*dequantize)(const void *, const void *, const float *, int64_t, int64_t, uint32_t, void *, void *);
+  int (*fake_quant)(const void *, const nvfp4_46_params *, const float *, void *, void *);
+  int (*gemm)(const void *, const void *, const float *, const void *, const void *, const float *, int64_t,
+              int64_t, int64_t, uint32_t, uint32_t, void *, void *);
+};
+EntryPoints entry;
+PyObject *error_class;     // Nvfp4Error(status, name of the entry point)
+
+struct Failed {};          // a Python exception is set
+
+[[noreturn]] void fail(PyObject *type, const char *text) {
+  PyErr_SetString(type, text);
+  throw Failed{};
+}
+
+// ---- arguments, as ctypes takes them: integers wrap to their width
+
+uint64_t word(PyObject *o) {
+  if (!PyLong_Check(o)) fail(PyExc_TypeError, "int expected");
+  return PyLong_AsUnsignedLongLongMask(o);
+}
+float number(PyObject *o) {
+  const double d = PyFloat_AsDouble(o);
+  if (d == -1.0 && PyErr_Occurred()) throw Failed{};
+  return (float)d;
+}
+const at::Tensor &tensor(PyObject *o) {
+  if (!THPVariable_Check(o)) fail(PyExc_AttributeError, "tensor expected");
+  return THPVariable_Unpack(o);
+}
+// None, an address, or a contiguous device tensor
+void *pointer(PyObject *o) {
+  if (o == Py_None) return nullptr;
+  if (PyLong_Check(o)) return reinterpret_cast<void *>(PyLong_AsUnsignedLongLongMask(o));
+  const at::Tensor &t = tensor(o);
+  if (!t.is_cuda() || !t.is_contiguous())
+    fail(PyExc_AssertionError, "tensors must be contiguous device tensors");
+  return t.data_ptr();
+}
+// None: the current stream of the current device
+void *stream(PyObject *o) {
+  if (o == Py_None) return c10::hip::getCurrentHIPStream().stream();
+  return reinterpret_cast<void *>(word(o));
+}
+
+PyObject *new_tensor(at::IntArrayRef shape, at::ScalarType type, const at::Tensor &like) {
+  return THPVariable_Wrap(at::empty(shape, at::TensorOptions().dtype(type).device(like.device())));
+}
+
+// A reference that is given up unless it is released.
+struct Owned {
+  PyObject *o;
+  explicit Owned(PyObject *p) : o(p) {
+    if (!o) throw Failed{};
+  }
+  Owned(const Owned &) = delete;
+  ~Owned() { Py_XDECREF(o); }
+  PyObject *release() {
+    PyObject *r = o;
+    o = nullptr;
+    return r;
+  }
+};
+Owned given_or_new(PyObject *given, at::IntArrayRef shape, at::ScalarType type, const at::Tensor &like) {
+  if (given == Py_None) return Owned(new_tensor(shape, type, like));
+  Py_INCREF(given);
+  return Owned(given);
+}
+
+// x [rows][cols], BF16 or fp32
+void set_shape(nvfp4_46_params &p, const at::Tensor &x) {
+  const bool f32 = x.scalar_type() == at::kFloat;
+  if (x.dim() != 2 || !(f32 || x.scalar_type() == at::kBFloat16))
+    fail(PyExc_AssertionError, "x must be a matrix of BF16 or fp32");
+  p.rows = x.size(0);
+  p.cols = x.size(1);
+  p.x_dtype = f32 ? NVFP4_X_F32 : NVFP4_X_BF16;
+}
+// layout, rounding, select, rht, sr_seed, rht_seed, fp8_max, block2d
+nvfp4_46_params params_of(const at::Tensor &x, PyObject *const *a) {
+  nvfp4_46_params p{};
+  set_shape(p, x);
+  p.layout = (uint32_t)word(a[0]);
+  p.rounding = (uint32_t)word(a[1]);
+  p.select = (uint32_t)word(a[2]);
+  p.rht = (uint32_t)word(a[3]);
+  p.sr_seed = word(a[4]);
+  p.rht_seed = word(a[5]);
+  p.fp8_max = number(a[6]);
+  p.block2d = (uint32_t)word(a[7]);
+  return p;
+}
+
+// The call itself, without the interpreter's lock.
+template <typename Call>
+void run(const char *where, Call &&call) {
+  int rc;
+  Py_BEGIN_ALLOW_THREADS
+  rc = call();
+  Py_END_ALLOW_THREADS
+  if (rc == NVFP4_OK) return;
+  PyObject *e = PyObject_CallFunction(error_class, "is", rc, where);
+  if (e) {
+    PyErr_SetObject(error_class, e);
+    Py_DECREF(e);
+  }
+  throw Failed{};
+}
+
+const char *const kCodeNames[6] = {"codes_row", "scales_row", "choice_row", "codes_col", "scales_col", "choice_col"};
+
+// The dictionary of a quantizer's outputs: those that its layout has as new tensors, None for the others.
+PyObject *new_codes(const at::Tensor &x, const nvfp4_46_params &p, bool want_choice) {
+  Owned d(PyDict_New());
+  for (int i = 0; i < 6; ++i) {
+    const bool col = i >= 3, codes = i % 3 == 0, choice = i % 3 == 2;
+    Owned v(Py_NewRef(Py_None));
+    if ((p.layout & (col ? NVFP4_COLWISE : NVFP4_ROWWISE)) && (!choice || want_choice)) {
+      const int64_t lines = col ? p.cols : p.rows, along = col ? p.rows : p.cols;
+      const int64_t shape[2] = {codes || !p.block2d ? lines : lines / 16, codes ? along / 2 : along / 16};
+      Owned t(new_tensor(shape, at::kByte, x));
+      std::swap(v.o, t.o);
+    }
+    if (PyDict_SetItemString(d.o, kCodeNames[i], v.o) < 0) throw Failed{};
+  }
+  return d.release();
+}
+struct CodePointers {
+  void *p[6];
+  explicit CodePointers(PyObject *codes) {
+    for (int i = 0; i < 6; ++i) {
+      PyObject *key = PyUnicode_FromString(kCodeNames[i]);
+      if (!key) throw Failed{};
+      PyObject *v = PyObject_GetItem(codes, key);         // (any mapping)
+      Py_DECREF(key);
+      if (!v) throw Failed{};
+      Owned held(v);
+      p[i] = pointer(v);
+    }
+  }
+};
+
+void expect(Py_ssize_t n, Py_ssize_t want) {
+  if (n != want) fail(PyExc_TypeError, "wrong number of arguments");
+}
+
+template <PyObject *(*F)(PyObject *const *, Py_ssize_t)>
+PyObject *guarded(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
+  try {
+    return F(a, n);
+  } catch (const Failed &) {
+    return nullptr;
+  }
+  END_HANDLE_TH_ERRORS
+}
+
+// ---- one function per entry point; None stands for an output to be allocated
+
+// x, out, stream, then params
+PyObject *tensor_scale(PyObject *const *a, Py_ssize_t n) {
+  expect(n, 11);
+  const at::Tensor &x = tensor(a[0]);
+  const nvfp4_46_params p = params_of(x, a + 3);
+  Owned alpha = given_or_new(a[1], {1}, at::kFloat, x);
+  void *const px = pointer(a[0]), *const s = stream(a[2]);
+  float *const pa = static_cast<float *>(pointer(alpha.o));
+  run("nvfp4_46_tensor_scale", [&] { return entry.tensor_scale(px, &p, pa, s); });
+  return alpha.release();
+}
+
+// x, workspace, out, stream, then params
+PyObject *tensor_scale_ws(PyObject *const *a, Py_ssize_t n) {
+  expect(n, 12);
+  const at::Tensor &x = tensor(a[0]);
+  const nvfp4_46_params p = params_of(x, a + 4);
+  Owned alpha = given_or_new(a[2], {1}, at::kFloat, x);
+  const size_t bytes = (size_t)tensor(a[1]).numel();
+  void *const px = pointer(a[0]), *const w = pointer(a[1]), *const s = stream(a[3]);
+  float *const pa = static_cast<float *>(pointer(alpha.o));
+  run("nvfp4_46_tensor_scale_ws", [&] { return entry.tensor_scale_ws(px, &p, pa, w, bytes, s); });
+  return alpha.release();
+}
+
+// x, alpha, out, want_choice, stream, then params
+PyObject *quantize(PyObject *const *a, Py_ssize_t n) {
+  expect(n, 13);
+  const at::Tensor &x = tensor(a[0]);
+  const nvfp4_46_params p = params_of(x, a + 5);
+  const int choice = PyObject_IsTrue(a[3]);
+  if (choice < 0) return nullptr;
+  Owned codes(a[2] == Py_None ? new_codes(x, p, choice) : Py_NewRef(a[2]));
+  const CodePointers c(codes.o);
+  void *const px = pointer(a[0]), *const s = stream(a[4]);
+  const float *const pa = static_cast<const float *>(pointer(a[1]));
+  run("nvfp4_46_quantize", [&] { return entry.quantize(px, &p, pa, c.p[0], c.p[1], c.p[3], c.p[4], c.p[2], c.p[5], s); });
+  return codes.release();
+}
+
+// x, workspace or None, alpha, out, want_choice, stream, then params; alpha joins the dictionary
+PyObject *scale_quantize(PyObject *const *a, Py_ssize_t n) {
+  expect(n, 14);
+  const at::Tensor &x = tensor(a[0]);
+  const nvfp4_46_params p = params_of(x, a + 6);
+  const int choice = PyObject_IsTrue(a[4]);
+  if (choice < 0) return nullptr;
+  Owned alpha = given_or_new(a[2], {1}, at::kFloat, x);
+  Owned codes(a[3] == Py_None ? new_codes(x, p, choice) : Py_NewRef(a[3]));
+  const CodePointers c(codes.o);
+  void *const px = pointer(a[0]), *const w = pointer(a[1]), *const s = stream(a[5]);
+  const size_t bytes = w ? (size_t)tensor(a[1]).numel() : 0;
+  float *const pa = static_cast<float *>(pointer(alpha.o));
+  run("nvfp4_46_scale_quantize", [&] {
+    return entry.scale_quantize(px, &p, pa, w, bytes, c.p[0], c.p[1], c.p[3], c.p[4], c.p[2], c.p[5], s);
+  });
+  if (PyObject_SetItem(codes.o, Owned(PyUnicode_FromString("alpha")).o, alpha.o) < 0) return nullptr;
+  return codes.release();
+}
+
+// codes, scales, alpha, rows, cols, layout, out, stream
+PyObject *dequantize(PyObject *const *a, Py_ssize_t n) {
+  expect(n, 8);
+  const int64_t rows = (int64_t)word(a[3]), cols = (int64_t)word(a[4]);
+  const uint32_t layout = (uint32_t)word(a[5]);
+  Owned out = a[6] == Py_None ? Owned(new_tensor({rows, cols}, at::kBFloat16, tensor(a[0])))
+                              : Owned(Py_NewRef(a[6]));
+  void *const c = pointer(a[0]), *const sc = pointer(a[1]), *const o = pointer(out.o), *const s = stream(a[7]);
+  const float *const pa = static_cast<const float *>(pointer(a[2]));
+  run("nvfp4_46_dequantize", [&] { return entry.dequantize(c, sc, pa, rows, cols, layout, o, s); });
+  return out.release();
+}
+
+// x, alpha, out, stream, then params
+PyObject *fake_quant(PyObject *const *a, Py_ssize_t n) {
+  expect(n, 12);
+  const at::Tensor &x = tensor(a[0]);
+  const nvfp4_46_params p = params_of(x, a + 4);
+  Owned out = given_or_new(a[2], {p.rows, p.cols}, at::kBFloat16, x);
+  void *const px = pointer(a[0]), *const o = pointer(out.o), *const s = stream(a[3]);
+  const float *const pa = static_cast<const float *>(pointer(a[1]));
+  run("nvfp4_46_fake_quant", [&] { return entry.fake_quant(px, &p, pa, o, s); });
+  return out.release();
+}
+
+// codes_a, scales_a, alpha_a, codes_b, scales_b, alpha_b, out_dtype, out, stream, flags
+PyObject *gemm(PyObject *const *a, Py_ssize_t n) {
+  expect(n, 10);
+  const at::Tensor &ca = tensor(a[0]), &sa = tensor(a[1]), &cb = tensor(a[3]), &sb = tensor(a[4]);
+  const uint32_t out_dtype = (uint32_t)word(a[6]), flags = (uint32_t)word(a[9]);
+  if (ca.dim() < 2 || cb.dim() < 2) fail(PyExc_IndexError, "tuple index out of range");
+  const int64_t M = ca.size(0), N = cb.size(0), K = ca.size(1) * 2;
+  auto is = [](const at::Tensor &t, int64_t rows, int64_t cols) {
+    return t.dim() == 2 && t.size(0) == rows && t.size(1) == cols;
+  };
+  if (cb.size(1) * 2 != K || !is(sa, flags & NVFP4_GEMM_A_TILE_SCALES ? M / 16 : M, K / 16) ||
+      !is(sb, flags & NVFP4_GEMM_B_TILE_SCALES ? N / 16 : N, K / 16))
+    fail(PyExc_AssertionError, "operands that do not fit together");
+  Owned out = given_or_new(a[7], {M, N}, out_dtype == NVFP4_OUT_F32 ? at::kFloat : at::kBFloat16, ca);
+  void *const pca = pointer(a[0]), *const psa = pointer(a[1]), *const pcb = pointer(a[3]), *const psb = pointer(a[4]);
+  const float *const paa = static_cast<const float *>(pointer(a[2])), *const pab = static_cast<const float *>(pointer(a[5]));
+  void *const o = pointer(out.o), *const s = stream(a[8]);
+  run("nvfp4_46_gemm", [&] { return entry.gemm(pca, psa, paa, pcb, psb, pab, M, N, K, out_dtype, flags, o, s); });
+  return out.release();
+}
+
+// The exception class, then the addresses of the entry points, one integer each.
+PyObject *connect(PyObject *const *a, Py_ssize_t n) {
+  constexpr Py_ssize_t kEntries = sizeof(EntryPoints) / sizeof(void *);
+  expect(n, 1 + kEntries);
+  void *to[kEntries];
+  for (Py_ssize_t i = 0; i < kEntries; ++i) to[i] = reinterpret_cast<void *>(word(a[1 + i]));
+  std::memcpy(&entry, to, sizeof entry);
+  error_class = Py_NewRef(a[0]);
+  Py_RETURN_NONE;
+}
+
+#define NV_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(guarded<f>)), METH_FASTCALL, nullptr}
+PyMethodDef methods[] = {NV_METHOD(connect),    NV_METHOD(tensor_scale), NV_METHOD(tensor_scale_ws), NV_METHOD(quantize),
+                         NV_METHOD(scale_quantize), NV_METHOD(dequantize), NV_METHOD(fake_quant), NV_METHOD(gemm),
+                         {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "nvfp4_46_python", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit_nvfp4_46_python() { return PyModule_Create(&module); }
