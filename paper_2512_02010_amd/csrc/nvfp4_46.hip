@@ -158,9 +158,13 @@ NV_DEV float wave_max(float m) {
 // Device-scope atomics on one address are carried out one after the other at the memory side
 // (about 15-35 ns each here: 256 workgroups that all finish together queued up for 9 of the
 // 27 us of a pass over 8192 x 8192).  So the workgroups report in a two-level tree: sixteen
-// groups, each with its own maximum and ticket words on cache lines of their own, and the
-// last workgroup of a group reports to the top pair.  Two chains of at most ~grid/16 + 16
-// atomics replace one of 2 x grid.
+// groups, each with its own maximum and ticket words on cache lines of their own; the last workgroup of a
+// group draws a top ticket, and who draws the last of those collects the sixteen maxima at once.  Two
+// chains of at most ~grid/16 + 16 atomics replace one of 2 x grid.  What a pass over a small tensor then waits
+// for is the last workgroup's dependent trips to the memory side, about a quarter of a microsecond each: its
+// maximum, two tickets, the collection (us in a replayed graph, x in the memory-side cache, against eight
+// trips where each maximum was looked at first, fetched from its group and raised at the top: 256 KiB 4.65 ->
+// 3.9, 1 MiB 4.9 -> 4.1, 16 MiB 5.4 -> 4.7, 2 MiB with the columnwise transform 6.5 -> 5.7).
 struct AmaxFinish {
   uint32_t *scratch;   // kScratchWords words, or nullptr
   float *alpha;
@@ -168,8 +172,9 @@ struct AmaxFinish {
 };
 constexpr uint32_t kAmaxGroups = 16;
 constexpr uint32_t kScratchStride = 32;   // words between two slots: one 128-byte line each
-// slot g: maximum of group g; slot 16 + g: its ticket; slot 32: top maximum; slot 33: top ticket
+// slot g: maximum of group g; slot 16 + g: its ticket; slot 32 is not used; slot 33: top ticket
 constexpr uint32_t kScratchWords = (2 * kAmaxGroups + 2) * kScratchStride;
+constexpr uint32_t kGroupMayQueue = 32;   // members from which on a group's maximum is looked at before it is raised
 NV_DEV uint32_t *scratch_slot(uint32_t *scratch, uint32_t i) { return scratch + i * kScratchStride; }
 
 // Eq. (1): alpha = amax / (6 * fp8_max); an all-zero tensor gets alpha = 1.
@@ -177,48 +182,58 @@ NV_DEV float alpha_of(float amax, float fp8_max) {
   return (amax == 0.0f) ? 1.0f : amax / (6.0f * fp8_max);
 }
 
-// max into *word, skipped when a plain read already shows a value at least as large (the
-// value only ever grows); the returning form, waited for, so that the maximum is in before
-// anything the caller does next.
-NV_DEV void atomic_max_now(uint32_t *word, uint32_t bits) {
-  if (bits > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-    uint32_t old = __hip_atomic_fetch_max(word, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    asm volatile("s_waitcnt vmcnt(0)" : "+v"(old) : : "memory");
-  }
+// max into *word; the returning form, waited for, so that the maximum is in before anything the
+// caller does next.  `look`: skipped when a read already shows a value at least as large (the value only
+// ever grows), for words that many workgroups queue for.
+NV_DEV void atomic_max_now(uint32_t *word, uint32_t bits, bool look) {
+  if (look && bits <= __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+  uint32_t old = __hip_atomic_fetch_max(word, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("s_waitcnt vmcnt(0)" : "+v"(old) : : "memory");
 }
 
 // Fold a workgroup's maximum magnitude into the global one.  Bit patterns of non-negative
 // floats order like the values, so an integer atomic max is exact and order-free.
 // Device-scope atomics are carried out at the one place all compute dies share, so "carried
 // out before" needs no cache maintenance, only program order: a workgroup's maximum is in
-// before its ticket is drawn, and whoever draws a group's (the grid's) last ticket reads the
-// maximum after that.
+// before its ticket is drawn, a group's last ticket before the top one, and whoever draws the grid's last
+// ticket collects the maxima after that.
 NV_DEV void publish_amax(float m, uint32_t *amax_bits, const AmaxFinish &fin) {
   __shared__ float wave_part[kThreads / 64];
   m = wave_max(m);
   if ((threadIdx.x & 63) == 0) wave_part[threadIdx.x >> 6] = m;
   __syncthreads();
-  if (threadIdx.x != 0) return;
+  if (threadIdx.x >= 64) return;
 #pragma unroll
-  for (int w = 1; w < kThreads / 64; ++w) m = fmaxf(m, wave_part[w]);
+  for (int w = 0; w < kThreads / 64; ++w) m = fmaxf(m, wave_part[w]);
   const uint32_t bits = f2u(m);
   if (!fin.scratch) {
-    atomic_max_now(amax_bits, bits);
+    if (threadIdx.x == 0) atomic_max_now(amax_bits, bits, true);
     return;
   }
   const uint32_t groups = gridDim.x < kAmaxGroups ? gridDim.x : kAmaxGroups;
   const uint32_t g = blockIdx.x % groups;
   const uint32_t members = (gridDim.x - g + groups - 1) / groups;     // workgroups b with b % groups == g
-  uint32_t *gmax = scratch_slot(fin.scratch, g), *gticket = scratch_slot(fin.scratch, kAmaxGroups + g);
-  uint32_t *top = scratch_slot(fin.scratch, 2 * kAmaxGroups), *top_ticket = scratch_slot(fin.scratch, 2 * kAmaxGroups + 1);
-  atomic_max_now(gmax, bits);
-  if (__hip_atomic_fetch_add(gticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != members - 1) return;
-  // last of its group: hand the group's maximum on and leave the group's words zero
-  const uint32_t group_bits = __hip_atomic_exchange(gmax, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_store(gticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  atomic_max_now(top, group_bits);
-  if (__hip_atomic_fetch_add(top_ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != groups - 1) return;
-  const uint32_t all = __hip_atomic_exchange(top, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  uint32_t *gticket = scratch_slot(fin.scratch, kAmaxGroups + g);
+  uint32_t *top_ticket = scratch_slot(fin.scratch, 2 * kAmaxGroups + 1);
+  uint32_t last = 0;
+  if (threadIdx.x == 0) {
+    atomic_max_now(scratch_slot(fin.scratch, g), bits, members >= kGroupMayQueue);
+    if (__hip_atomic_fetch_add(gticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == members - 1) {
+      __hip_atomic_store(gticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      last = __hip_atomic_fetch_add(top_ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == groups - 1;
+    }
+  }
+  if (!__builtin_amdgcn_readfirstlane(last)) return;
+  // last of all: the groups' maxima, one per lane, and all words zero again
+  uint32_t all = 0;
+  if (threadIdx.x < groups)
+    all = __hip_atomic_exchange(scratch_slot(fin.scratch, threadIdx.x), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+  for (uint32_t off = kAmaxGroups / 2; off > 0; off >>= 1) {
+    const uint32_t other = (uint32_t)__shfl_xor((int)all, (int)off, 64);
+    all = other > all ? other : all;
+  }
+  if (threadIdx.x != 0) return;
   __hip_atomic_store(top_ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   *fin.alpha = alpha_of(u2f(all), fin.fp8_max);
 }
