@@ -193,13 +193,29 @@ NV_DEV float rtn_candidate(const float (&v)[16], float dec, float enc, uint32_t 
   return error.value();
 }
 
-// The random words of elements 4q .. 4q + 3 of a block, from all sixteen or from whatever draws them.
-NV_DEV void four_words(const uint32_t (&words)[16], int q, uint32_t (&w)[4]) {
+// The random words of a block: all sixteen, or a function f(q, w) that draws or fetches the words of
+// elements STEP q .. STEP q + STEP - 1 into w[0 .. STEP - 1] when the first of them is needed.
+template <int STEP, typename F>
+struct WordsOnDemand {
+  F f;
+};
+template <int STEP, typename F>
+NV_DEV WordsOnDemand<STEP, F> words_on_demand(F f) { return WordsOnDemand<STEP, F>{f}; }
+NV_DEV void words_from(const uint32_t (&words)[16], int e, uint32_t (&w)[16]) {
+  if (e == 0) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) w[i] = words[4 * q + i];
+    for (int i = 0; i < 16; ++i) w[i] = words[i];
+  }
 }
-template <typename Words>
-NV_DEV void four_words(const Words &words, int q, uint32_t (&w)[4]) { words(q, w); }
+template <int STEP, typename F>
+NV_DEV void words_from(const WordsOnDemand<STEP, F> &words, int e, uint32_t (&w)[16]) {
+  if (e % STEP == 0) {
+    uint32_t got[STEP];
+    words.f(e / STEP, got);
+#pragma unroll
+    for (int i = 0; i < STEP; ++i) w[e + i] = got[i];
+  }
+}
 
 // One scale to round a block under, and what comes of it.
 struct SrCandidate {
@@ -208,8 +224,8 @@ struct SrCandidate {
   float error;
 };
 
-// Quantize the block stochastically under both scales (TWO) or under the first, four elements at a time:
-// their random words are drawn, used for both candidates and forgotten.  What bounds the stochastic
+// Quantize the block stochastically under both scales (TWO) or under the first, element
+// by element: a random word is used for both candidates and forgotten.  What bounds the stochastic
 // kernels is their vector arithmetic (some 700 instructions per block), and how much of its rate they get
 // is a question of waves per SIMD: with one candidate after the other the sixteen words, their complements
 // and their floats stayed in registers for the second (172, two waves).
@@ -219,6 +235,7 @@ struct SrCandidate {
 template <bool TWO, int ERR, bool FAST, typename Words>
 NV_DEV void sr_candidates(const float (&v)[16], const Words &words, SrCandidate &a, SrCandidate &b, float &margin) {
   CandidateError<ERR> error_a, error_b;
+  uint32_t w[16];
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     float ga[8], gb[8];
@@ -227,17 +244,13 @@ NV_DEV void sr_candidates(const float (&v)[16], const Words &words, SrCandidate 
       // elements into the bytes of one word, odd ones into another
       uint32_t ea = any_register(), oa = any_register(), eb = any_register(), ob = any_register();
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        uint32_t w[4];
-        four_words(words, 2 * h + q, w);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float x = v[8 * h + 4 * q + i], wf = (float)w[i];
-          const uint32_t not_w = ~w[i];
-          uint32_t &ca = i & 1 ? oa : ea, &cb = i & 1 ? ob : eb;
-          if (TWO) e2m1_sr_code_fast2_sel(ca, cb, x * a.enc, x * b.enc, not_w, wf, margin, 2 * q + i / 2);
-          else ca = e2m1_sr_code_fast_sel(ca, x * a.enc, not_w, wf, margin, 2 * q + i / 2);
-        }
+      for (int i = 0; i < 8; ++i) {
+        words_from(words, 8 * h + i, w);
+        const float x = v[8 * h + i], wf = (float)w[8 * h + i];
+        const uint32_t not_w = ~w[8 * h + i];
+        uint32_t &ca = i & 1 ? oa : ea, &cb = i & 1 ? ob : eb;
+        if (TWO) e2m1_sr_code_fast2_sel(ca, cb, x * a.enc, x * b.enc, not_w, wf, margin, i / 2);
+        else ca = e2m1_sr_code_fast_sel(ca, x * a.enc, not_w, wf, margin, i / 2);
       }
       a.code[h] = (ea & 0x0f0f0f0fu) | ((oa << 4) & 0xf0f0f0f0u);
       if (TWO) b.code[h] = (eb & 0x0f0f0f0fu) | ((ob << 4) & 0xf0f0f0f0u);
@@ -251,15 +264,11 @@ NV_DEV void sr_candidates(const float (&v)[16], const Words &words, SrCandidate 
       // the rounded values are on the grid, so the conversion that packs them is exact
       uint32_t wa = 0u, wb = 0u;
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        uint32_t w[4];
-        four_words(words, 2 * h + q, w);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float x = v[8 * h + 4 * q + i], u = sr_uniform_of_word(w[i]);
-          ga[4 * q + i] = e2m1_sr_value(x * a.enc, u);
-          if (TWO) gb[4 * q + i] = e2m1_sr_value(x * b.enc, u);
-        }
+      for (int i = 0; i < 8; ++i) {
+        words_from(words, 8 * h + i, w);
+        const float x = v[8 * h + i], u = sr_uniform_of_word(w[8 * h + i]);
+        ga[i] = e2m1_sr_value(x * a.enc, u);
+        if (TWO) gb[i] = e2m1_sr_value(x * b.enc, u);
       }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -443,14 +452,14 @@ NV_DEV void block_scales(float b, const ScaleConsts &k, uint32_t &S6, uint32_t &
 }
 
 // The per-block procedure (Table 3 lines 1-14) in one pass.  DEFINED = false: the squared-error rule
-// compares the cheap estimates, stochastic rounding uses the conversion instruction, and where either
-// cannot be sure of its answer that is reported through `undecided` (the result is then provisional).
-// DEFINED = true: errors and roundings are evaluated exactly as defined.  The other rules always
-// evaluate the defined errors.
-template <int ROUNDING, int SELECT, bool DEFINED, typename Words>
+// compares the cheap estimates and reports through `undecided` when they cannot tell (the result is then
+// provisional); true: the errors are evaluated exactly as defined.  The other rules always evaluate the
+// defined errors.  FAST = true: stochastic rounding uses the conversion instruction and reports through
+// `risky` when its answer may not be the rule's; false: the rule itself.
+template <int ROUNDING, int SELECT, bool DEFINED, bool FAST, typename Words>
 NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
                                        const ScaleConsts &k, const ScaleTable &tab,
-                                       bool &undecided) {
+                                       bool &undecided, bool &risky) {
   float b = 0.0f;
 #pragma unroll
   for (int i = 0; i < 16; i += 2) b = fmaxf(fmaxf(b, fabsf(v[i])), fabsf(v[i + 1]));
@@ -484,7 +493,7 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
     if (kSix) look_up(S6, r6, enc6, m6);
     if (kFour) look_up(S4, r4, enc4, m4);
     SrCandidate c{kSix ? r6.dec : r4.dec, kSix ? enc6 : enc4, {0u, 0u}, 0.0f}, d{r4.dec, enc4, {0u, 0u}, 0.0f};
-    sr_candidates<kBoth, kErr, !DEFINED>(v, words, c, d, margin);
+    sr_candidates<kBoth, kErr, FAST>(v, words, c, d, margin);
     E6p = c.error;
     E4p = d.error;
     BlockResult &first = kSix ? r6 : r4;
@@ -526,30 +535,35 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
   BlockResult r = four ? r4 : r6;
   if (ROUNDING == kSRAfterRtnSelect) {
     SrCandidate c{r.dec, four ? enc4 : enc6, {0u, 0u}, 0.0f}, none{};
-    sr_candidates<false, kErrNone, !DEFINED>(v, words, c, none, margin);
+    sr_candidates<false, kErrNone, FAST>(v, words, c, none, margin);
     r.lo = c.code[0];
     r.hi = c.code[1];
   }
-  if (ROUNDING != kRTN && !DEFINED) undecided |= !(margin > kSrMarginAtRisk);
+  if (ROUNDING != kRTN && FAST) risky = !(margin > kSrMarginAtRisk);
   return r;
 }
 
-// The whole per-block procedure.  `words` is the block's sixteen stochastic-rounding words or a function
-// that gives four of them at a time.  `again(w, ww)` must produce the block's values (and all its words)
+// The whole per-block procedure.  `words` is the block's sixteen stochastic-rounding words, or how to
+// get them (WordsOnDemand).  `again(w, ww)` must produce the block's values (and all its words)
 // once more: the rare block whose first pass is not sure of its answer is redone from those as it is
 // defined, so that nothing of the first pass has to stay in registers for it -- keeping the sixteen
 // values and both candidates alive across the common path cost the rowwise kernel three of its
-// eight waves per SIMD.
+// eight waves per SIMD.  A block whose estimates were too close is rounded by the instruction once more (one
+// wave in some hundreds is in the case, and in a small launch all wait for it: with the rule in
+// software 1008 x 4096 took 8.1 us instead of 7.5), a risky one by the rule.
 template <int ROUNDING, int SELECT, typename Words, typename Again>
 NV_DEV BlockResult quantize_block(const float (&v)[16], const Words &words,
                                   const ScaleConsts &k, const ScaleTable &tab, Again &&again) {
-  bool undecided = false;
-  BlockResult r = quantize_block_pass<ROUNDING, SELECT, false>(v, words, k, tab, undecided);
-  if ((SELECT == kSel46 || ROUNDING != kRTN) && undecided) {
+  bool undecided = false, risky = false;
+  BlockResult r = quantize_block_pass<ROUNDING, SELECT, false, true>(v, words, k, tab, undecided, risky);
+  if ((SELECT == kSel46 && undecided) || (ROUNDING != kRTN && risky)) {
     float w[16];
     uint32_t ww[16];
     again(w, ww);
-    r = quantize_block_pass<ROUNDING, SELECT, true>(w, ww, k, tab, undecided);
+    if (ROUNDING != kRTN && risky)
+      r = quantize_block_pass<ROUNDING, SELECT, true, false>(w, ww, k, tab, undecided, risky);
+    else if (SELECT == kSel46)
+      r = quantize_block_pass<ROUNDING, SELECT, true, true>(w, ww, k, tab, undecided, risky);
   }
   return r;
 }

@@ -257,41 +257,51 @@ NV_DEV void sr_words4(uint64_t seed, uint64_t q, uint32_t w[4]) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) w[j] = p.w[j];
 }
-// The same for a group whose upper counter word is the same for the whole wave (in a scalar register):
-// the first two of the ten rounds meet the two zero counter words and that one, so of their four
-// multiplications two are left to the vector unit.
-NV_DEV void sr_words4_in_wave(uint64_t seed, uint32_t q_lo, uint32_t q_hi, uint32_t w[4]) {
+// The same for G groups that follow each other, their upper counter word the same for the whole wave (in a
+// scalar register): the first two of the ten rounds meet the two zero counter words and that one, so of
+// their four multiplications two are left to the vector unit.  The groups go through the rounds side by
+// side: one alone is a chain of twenty dependent instructions.
+template <int G>
+NV_DEV void sr_words_in_wave(uint64_t seed, uint32_t q_lo, uint32_t q_hi, uint32_t (&w)[4 * G]) {
   uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+  uint32_t c0[G], c1[G], c2[G], c3[G];
   auto next_key = [&] { k0 += 0x9E3779B9u; k1 += 0xBB67AE85u; };
-  uint64_t p0 = (uint64_t)0xD2511F53u * q_lo;
-  const uint32_t s0 = q_hi ^ k0;                                        // round 1
-  uint32_t c2 = (uint32_t)(p0 >> 32) ^ k1, c3 = (uint32_t)p0;
-  next_key();
-  const uint64_t q0 = (uint64_t)0xD2511F53u * s0;                       // round 2
-  uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-  uint32_t c0 = (uint32_t)(p1 >> 32) ^ k0, c1 = (uint32_t)p1;
-  c2 = c3 ^ ((uint32_t)(q0 >> 32) ^ k1);
-  next_key();
-  p0 = (uint64_t)0xD2511F53u * c0;                                      // round 3
-  p1 = (uint64_t)0xCD9E8D57u * c2;
-  c0 = xor3((uint32_t)(p1 >> 32), c1, k0);
-  c1 = (uint32_t)p1;
-  c2 = (uint32_t)(p0 >> 32) ^ ((uint32_t)q0 ^ k1);
-  c3 = (uint32_t)p0;
+  const uint32_t s0 = q_hi ^ k0;
 #pragma unroll
-  for (int r = 3; r < 10; ++r) {
-    next_key();
-    p0 = (uint64_t)0xD2511F53u * c0;
-    p1 = (uint64_t)0xCD9E8D57u * c2;
-    c0 = xor3((uint32_t)(p1 >> 32), c1, k0);
-    c1 = (uint32_t)p1;
-    c2 = xor3((uint32_t)(p0 >> 32), c3, k1);
-    c3 = (uint32_t)p0;
+  for (int j = 0; j < G; ++j) {                                         // round 1
+    const uint64_t p0 = (uint64_t)0xD2511F53u * (q_lo + j);
+    c2[j] = (uint32_t)(p0 >> 32) ^ k1;
+    c3[j] = (uint32_t)p0;
   }
-  w[0] = c0;
-  w[1] = c1;
-  w[2] = c2;
-  w[3] = c3;
+  next_key();
+  const uint64_t s = (uint64_t)0xD2511F53u * s0;
+#pragma unroll
+  for (int j = 0; j < G; ++j) {                                         // round 2
+    const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2[j];
+    c0[j] = (uint32_t)(p1 >> 32) ^ k0;
+    c1[j] = (uint32_t)p1;
+    c2[j] = c3[j] ^ ((uint32_t)(s >> 32) ^ k1);
+  }
+  next_key();
+#pragma unroll
+  for (int r = 2; r < 10; ++r) {
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+      const uint64_t p0 = (uint64_t)0xD2511F53u * c0[j], p1 = (uint64_t)0xCD9E8D57u * c2[j];
+      c0[j] = xor3((uint32_t)(p1 >> 32), c1[j], k0);
+      c1[j] = (uint32_t)p1;
+      c2[j] = r == 2 ? (uint32_t)(p0 >> 32) ^ ((uint32_t)s ^ k1) : xor3((uint32_t)(p0 >> 32), c3[j], k1);
+      c3[j] = (uint32_t)p0;
+    }
+    next_key();
+  }
+#pragma unroll
+  for (int j = 0; j < G; ++j) {
+    w[4 * j] = c0[j];
+    w[4 * j + 1] = c1[j];
+    w[4 * j + 2] = c2[j];
+    w[4 * j + 3] = c3[j];
+  }
 }
 NV_DEV float sr_uniform_of_word(uint32_t w) { return (float)(w >> 8) * 0x1p-24f; }
 
@@ -299,6 +309,23 @@ NV_DEV float sr_uniform_of_word(uint32_t w) { return (float)(w >> 8) * 0x1p-24f;
 NV_DEV uint32_t rht_sign_word(uint64_t seed, uint64_t B) {
   return philox4x32_10((uint32_t)B, (uint32_t)(B >> 32), 0u, 1u, (uint32_t)seed,
                        (uint32_t)(seed >> 32)).w[0];
+}
+
+// The same for a position that the whole wave shares: plain exclusive-ors, so that all of it stays on the
+// scalar unit (xor3() is a vector instruction).
+NV_DEV uint32_t rht_sign_word_of_wave(uint64_t seed, uint32_t B_lo, uint32_t B_hi) {
+  uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32), c0 = B_lo, c1 = B_hi, c2 = 0u, c3 = 1u;
+#pragma unroll
+  for (int r = 0; r < 10; ++r) {
+    const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
+    c0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
+    c1 = (uint32_t)p1;
+    c2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+    c3 = (uint32_t)p0;
+    k0 += 0x9E3779B9u;
+    k1 += 0xBB67AE85u;
+  }
+  return c0;
 }
 
 // ------------------------------------------------------------ Hadamard

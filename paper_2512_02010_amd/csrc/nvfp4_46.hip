@@ -473,12 +473,14 @@ __global__ __launch_bounds__(kThreads) void k_flat(
       for (int i = 0; i < 16; ++i) amax = fmaxf(amax, fabsf(v[i]));
       return;
     }
-    // four words of the block at a time; base is a multiple of 256 blocks, 1024 groups of four, so a
-    // lane's own part of the counter never carries out of the lower word
+    // base is a multiple of 256 blocks, 1024 groups of four words, so a lane's own part of the counter
+    // never carries out of the lower word.  Eight words at a time: 8192 x 8192 with the transform
+    // takes 80.3 / 80.4 / 82.5 us with four / eight / sixteen, 1008 x 4096 without 7.5 / 7.5 / 7.9.
     const uint64_t q0 = (uint64_t)base * 4u;
-    auto words = [&](int q, uint32_t (&w)[4]) {
-      sr_words4_in_wave(sr_seed, (uint32_t)q0 + (4u * tid + q), (uint32_t)(q0 >> 32), w);
-    };
+    constexpr int kStep = 8;
+    auto words = words_on_demand<kStep>([&](int q, uint32_t (&w)[kStep]) {
+      sr_words_in_wave<kStep / 4>(sr_seed, (uint32_t)q0 + (4u * tid + kStep / 4 * q), (uint32_t)(q0 >> 32), w);
+    });
     // the block once more, from memory (a lane without a block of its own holds a copy of
     // the round's last block, as fetch() gave it)
     auto again = [&](float (&w)[16], uint32_t (&uu)[16]) {
@@ -491,7 +493,15 @@ __global__ __launch_bounds__(kThreads) void k_flat(
         for (int j = 0; j < 4; ++j) sr_words4(sr_seed, q0 + 4u * tid + j, &uu[4 * j]);
       }
     };
-    const BlockResult res = quantize_block<ROUNDING, SELECT>(v, words, sc, tab, again);
+    BlockResult res;
+    if constexpr (ROUNDING == kSRAfterRtnSelect) {
+      // needed at the very end only: drawn ahead, beside the candidates, not behind them
+      uint32_t u[16];
+      sr_words_in_wave<4>(sr_seed, (uint32_t)q0 + 4u * tid, (uint32_t)(q0 >> 32), u);
+      res = quantize_block<ROUNDING, SELECT>(v, u, sc, tab, again);
+    } else {
+      res = quantize_block<ROUNDING, SELECT>(v, words, sc, tab, again);
+    }
     if (OUT == kOutCodes) {
       store_as<kNtCodes>(codes + base + tid, make_uint2(res.lo, res.hi));
       store_as<kNtCodes>(scales + base + tid, (uint8_t)res.scale);
@@ -708,16 +718,22 @@ __global__ __launch_bounds__(kThreads) void k_tile(
 
   if (kWords) {
     // (cols is a multiple of 8, so four columns are in or out together and share a call)
+    auto draw_all = [&](auto &&draw4) {
 #pragma unroll 2
-    for (int j = 0; j < TR * TC / 4 / kThreads; ++j) {
-      const int idx = t + j * kThreads;
-      const int64_t gr = r0 + idx / (TC / 4), gc = c0 + idx % (TC / 4) * 4;
-      if (gr < rows && gc < cols) {
-        uint32_t w[4];
-        sr_words4(sr_seed, ((uint64_t)gr * (uint64_t)cols + (uint64_t)gc) >> 2, w);
-        words[idx] = make_uint4(w[0], w[1], w[2], w[3]);
+      for (int j = 0; j < TR * TC / 4 / kThreads; ++j) {
+        const int idx = t + j * kThreads;
+        const int64_t gr = r0 + idx / (TC / 4), gc = c0 + idx % (TC / 4) * 4;
+        if (gr < rows && gc < cols) {
+          uint32_t w[4];
+          draw4(((uint64_t)gr * (uint64_t)cols + (uint64_t)gc) >> 2, w);
+          words[idx] = make_uint4(w[0], w[1], w[2], w[3]);
+        }
       }
-    }
+    };
+    if (((uint64_t)rows * (uint64_t)cols >> 34) == 0)       // the upper counter word is 0 throughout
+      draw_all([&](uint64_t q, uint32_t (&w)[4]) { sr_words_in_wave<1>(sr_seed, (uint32_t)q, 0u, w); });
+    else
+      draw_all([&](uint64_t q, uint32_t (&w)[4]) { sr_words4(sr_seed, q, w); });
   }   // (the barrier at the end of the scale table comes before the first use)
 
   // Only columnwise codes wanted: nothing needs the tile in LDS -- a lane reads its two columns
@@ -772,27 +788,31 @@ __global__ __launch_bounds__(kThreads) void k_tile(
           for (int q = 0; q < Raw::kPieces; ++q) mine.w[q] = own[q];
           unpack16(mine, w);
         };
-        auto four = [&](int q, uint32_t (&w)[4]) {
-          const uint4 w4 = words[kWords ? row * (TC / 4) + rbk * 4 + q : 0];
-          w[0] = w4.x;
-          w[1] = w4.y;
-          w[2] = w4.z;
-          w[3] = w4.w;
+        constexpr int kStep = 16;
+        auto some = [&](int s, uint32_t (&w)[kStep]) {
+#pragma unroll
+          for (int q = 0; q < kStep / 4; ++q) {
+            const uint4 w4 = words[kWords ? row * (TC / 4) + rbk * 4 + kStep / 4 * s + q : 0];
+            w[4 * q] = w4.x;
+            w[4 * q + 1] = w4.y;
+            w[4 * q + 2] = w4.z;
+            w[4 * q + 3] = w4.w;
+          }
         };
         auto take = [&](float (&w)[16], uint32_t (&uu)[16]) {
           block(w);
           if (kWords) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              uint32_t w4[4];
-              four(q, w4);
+            for (int s = 0; s < 16 / kStep; ++s) {
+              uint32_t got[kStep];
+              some(s, got);
 #pragma unroll
-              for (int i = 0; i < 4; ++i) uu[4 * q + i] = w4[i];
+              for (int i = 0; i < kStep; ++i) uu[kStep * s + i] = got[i];
             }
           }
         };
         block(v);
-        BlockResult r = quantize_block<ROUNDING, SELECT>(v, four, sc, tab, take);
+        BlockResult r = quantize_block<ROUNDING, SELECT>(v, words_on_demand<kStep>(some), sc, tab, take);
         reinterpret_cast<uint2 *>(codes_row)[k] = make_uint2(r.lo, r.hi);
         scales_row[k] = (uint8_t)r.scale;
         if (choice_row) choice_row[k] = (uint8_t)r.four;
@@ -803,35 +823,42 @@ __global__ __launch_bounds__(kThreads) void k_tile(
   // ---- phase 2: every lane takes two adjacent columns x 16 rows.  A (column pair, row
   // block) unit is read and, for the fake-quant output, rewritten in place by its owner
   // lane only, so no barrier is needed inside this phase.
+  static_assert(kColPairs == 64, "a wave's lanes are the column pairs of one row block");
 #pragma unroll 1
   for (int j = 0; j < kPairUnitsPerLane; ++j) {
-    const int pu = t + j * kThreads;
-    const int cp = pu % kColPairs, rb = pu / kColPairs;
+    // (the row block is the wave's: what follows from it stays on the scalar unit)
+    const int cp = t % kColPairs, rb = __builtin_amdgcn_readfirstlane(t / kColPairs) + j * (kThreads / kColPairs);
     const int64_t gr = r0 + rb * 16;              // first row of the block
     const int64_t gc = c0 + 2 * cp;               // even column of the pair
     if (gr >= rows || gc >= cols) continue;       // (cols is even, so the pair is in or out together)
     float va[16], vb[16];
     // the lane's two column blocks (transformed) out of the tile or memory
     auto take = [&](float (&wa)[16], float (&wb)[16]) {
+      const uint32_t sw = RHT ? rht_sign_word_of_wave(rht_seed, (uint32_t)(gr >> 4), (uint32_t)(gr >> 36)) : 0u;
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
+        const int64_t row = ((gr + i) * cols + c0) >> 1;   // pairs before the tile's first in row i of the block
+        const uint32_t flip = 0u - ((sw >> i) & 1u);       // the transform's sign: one per row
         if constexpr (XF32) {
-          const uint2 pair = kDirect
-              ? static_cast<const uint2 *>(x_any)[((gr + i) * cols + gc) >> 1]
-              : reinterpret_cast<const uint2 *>(tile)[(rb * 16 + i) * kColPairs + cp];
+          uint2 pair = kDirect ? (static_cast<const uint2 *>(x_any) + row)[cp]
+                               : reinterpret_cast<const uint2 *>(tile)[(rb * 16 + i) * kColPairs + cp];
+          if (RHT) {
+            pair.x ^= flip & 0x80000000u;
+            pair.y ^= flip & 0x80000000u;
+          }
           wa[i] = u2f(pair.x);
           wb[i] = u2f(pair.y);
         } else {
-          const uint32_t pair = kDirect ? static_cast<const uint32_t *>(x_any)[((gr + i) * cols + gc) >> 1]
-                                        : tile[(rb * 16 + i) * kColPairs + cp];
+          uint32_t pair = kDirect ? (static_cast<const uint32_t *>(x_any) + row)[cp]
+                                  : tile[(rb * 16 + i) * kColPairs + cp];
+          if (RHT) pair ^= flip & 0x80008000u;
           wa[i] = bf16_lo(pair);
           wb[i] = bf16_hi(pair);
         }
       }
       if (RHT) {
-        const uint32_t sw = rht_sign_word(rht_seed, (uint64_t)(gr >> 4));
-        rht16(wa, sw);
-        rht16(wb, sw);
+        hadamard16_quarter(wa);
+        hadamard16_quarter(wb);
       }
     };
     auto word_at = [&](int i, int column) {                             // row i, column 0 or 1 of the pair
@@ -877,14 +904,15 @@ __global__ __launch_bounds__(kThreads) void k_tile(
       ra = quantize_block<ROUNDING, SELECT>(va, ua, sc, tab, first);
       rbk = quantize_block<ROUNDING, SELECT>(vb, ub, sc, tab, second);
     } else {
-      auto four_of = [&](int column) {
-        return [&, column](int q, uint32_t (&w)[4]) {
+      constexpr int kStep = 16;
+      auto words_of = [&](int column) {
+        return words_on_demand<kStep>([&, column](int q, uint32_t (&w)[kStep]) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) w[i] = word_at(4 * q + i, column);
-        };
+          for (int i = 0; i < kStep; ++i) w[i] = word_at(kStep * q + i, column);
+        });
       };
-      ra = quantize_block<ROUNDING, SELECT>(va, four_of(0), sc, tab, first);
-      rbk = quantize_block<ROUNDING, SELECT>(vb, four_of(1), sc, tab, second);
+      ra = quantize_block<ROUNDING, SELECT>(va, words_of(0), sc, tab, first);
+      rbk = quantize_block<ROUNDING, SELECT>(vb, words_of(1), sc, tab, second);
     }
     if (OUT == kOutCodes) {
       const int ia = (2 * cp) * kColBlockRows + rb, ib = ia + kColBlockRows;
