@@ -295,6 +295,7 @@ __global__ __launch_bounds__(kThreads) void k_amax_plain(const uint4 *__restrict
 // loads each in flight take what one compute unit can (256 KiB in 3.3 us); small_tensors.hpp says
 // where that ends.
 constexpr int kSmallThreads = 1024;
+constexpr int kSmallBlocks = 256;             // blocks per workgroup of k_scale_quantize_small
 template <bool XF32>
 NV_DEV float small_tensor_alpha(const uint4 *__restrict__ x, uint32_t n16, float fp8_max) {
   __shared__ float wave_part[kSmallThreads / 64];
@@ -579,22 +580,25 @@ __global__ __launch_bounds__(kThreads) void k_flat(
 }
 
 // Tensor scale and rowwise codes of a small tensor in one launch: every workgroup reads the whole
-// tensor for its maximum (it comes out of the L2 after the first), then quantizes its own 1024
-// blocks, one per lane.  16 x 8192 BF16: 6.9 us, where the two kernels and the gap between them took
-// 8.1 (in a replayed graph); small_tensors.hpp says where that ends.
+// tensor for its maximum (it comes out of the L2 after the first), then its first four waves, one per SIMD,
+// quantize its own 256 blocks, one per lane (with a block for each of the 1024 lanes four waves of a SIMD queue
+// for its vector unit: us in a replayed graph, x in the memory-side cache, BF16 / fp32, 1024 and 256 blocks:
+// 128 KiB 4.8 / 5.0 and 4.1 / 3.8, 256 KiB 5.6 / 6.0 and 5.0 / 4.7, 384 KiB 6.9 / 7.1 and 6.2 / 5.7; two kernels
+// and the gap between them 7 to 8).  small_tensors.hpp says where that ends.
 template <bool XF32, int SELECT>
 __global__ __launch_bounds__(kSmallThreads) void k_scale_quantize_small(
     const uint4 *__restrict__ x, float *__restrict__ alpha_out, uint2 *__restrict__ codes,
     uint8_t *__restrict__ scales, uint8_t *__restrict__ choice, uint32_t nblocks, float fp8_max) {
   __shared__ ScaleTable tab;
   using Raw = RawBlock<XF32>;
-  const uint32_t k = blockIdx.x * kSmallThreads + threadIdx.x;
+  const bool mine = threadIdx.x < kSmallBlocks;
+  const uint32_t k = blockIdx.x * kSmallBlocks + threadIdx.x;
   Raw raw;
-  load_block<XF32>(x + Raw::kPieces * (k < nblocks ? k : nblocks - 1), raw);
+  if (mine) load_block<XF32>(x + Raw::kPieces * (k < nblocks ? k : nblocks - 1), raw);
   const float alpha = small_tensor_alpha<XF32>(x, nblocks * Raw::kPieces, fp8_max);
-  if (k == 0) *alpha_out = alpha;
+  if (mine && k == 0) *alpha_out = alpha;
   const ScaleConsts sc = build_scale_table(tab, alpha);
-  if (k >= nblocks) return;
+  if (!mine || k >= nblocks) return;
   float v[16];
   const uint32_t u[16] = {};
   unpack16(raw, v);
@@ -1406,7 +1410,7 @@ static int launch_flat_variant(const FlatArgs &a, bool rht, int out) {
   if constexpr (ROUNDING == kRTN) {
     if (out == kOutScaleAndCodes)
       return launch(k_scale_quantize_small<XF32, SELECT>,
-                    dim3((uint32_t)((a.nblocks + kSmallThreads - 1) / kSmallThreads)), dim3(kSmallThreads),
+                    dim3((uint32_t)((a.nblocks + kSmallBlocks - 1) / kSmallBlocks)), dim3(kSmallThreads),
                     a.stream, a.x, a.fin.alpha, a.codes, a.scales, a.choice, (uint32_t)a.nblocks,
                     a.fin.fp8_max);
   }
