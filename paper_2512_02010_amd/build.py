@@ -9,15 +9,15 @@ from pathlib import Path
 
 PKG = Path(__file__).resolve().parent
 ROOT = PKG.parent
-# (source, extra defines, object name).  Both sources are compiled in seven parts each, side
-# by side: part 0 holds the entry points, parts 1..6 one group of kernels each (see the
+# (source, extra defines, object name).  Both sources are compiled in parts, side
+# by side: part 0 holds the entry points, the others one group of kernels each (see the
 # sources for the grouping).  The slowest parts come first so that they start first.
 UNITS = [(PKG / "csrc" / "gemm.hip", {"NVFP4_46_GEMM_PART": part}, f"gemm.part{part}")
-         for part in range(1, 5)]
+         for part in (5, 1, 2, 3, 4)]
 UNITS += [(PKG / "csrc" / "nvfp4_46.hip", {"NVFP4_46_PART": part}, f"nvfp4_46.part{part}")
           for part in range(1, 7)]
 UNITS += [(PKG / "csrc" / "gemm.hip", {"NVFP4_46_GEMM_PART": part}, f"gemm.part{part}")
-          for part in (5, 6, 0)]
+          for part in (6, 0)]
 UNITS.append((PKG / "csrc" / "nvfp4_46.hip", {"NVFP4_46_PART": 0}, "nvfp4_46.part0"))
 SO = PKG / "libnvfp4_46.so"
 PYTHON_SO = PKG / "nvfp4_46_python.so"

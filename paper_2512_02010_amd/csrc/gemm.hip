@@ -25,6 +25,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <type_traits>
 
 #include "codec.hpp"
 #include "gemm_shapes.hpp"
@@ -294,77 +295,85 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm(
 
 // ----------------------------------------------------------------------------------------
 // The same product with LDS filled by asynchronous global -> LDS loads (global_load_lds_dwordx4): no
-// staging registers and no LDS write instructions.  The four waves of the workgroup copy each
-// chunk of 128 contraction steps together, a quarter each, into a ring of four stages:
-//   per stage: A codes [256][64 B], B codes [256][64 B], A scales [256], B scales [256]
+// staging registers and no LDS write instructions.  Four waves, one per SIMD, hold 4 x 4 instruction tiles
+// (128 x 128, 256 accumulators per lane) each and share a tile of C and the contraction axis in one of three ways
+// (DmaShape): 256 x 256, 256 x 128 in two halves of K, 128 x 128 in four quarters.  Splitting K inside the
+// workgroup keeps the largest wave tile, with the fewest expansions and LDS reads per matrix instruction,
+// for products whose 256 x 256 tiles would leave compute units idle.  The waves copy each chunk together into a
+// ring of NST stages: codes [BM + BN rows][U units of 16 bytes], then scales.
 // A load instruction writes its 64 lanes' 16 (or 4) bytes to consecutive LDS addresses, so
 // the LDS layout is plain row-major; to keep the later 16-byte reads of 16 lanes on 16
-// different bank groups, lane (row, position p) of a copy fetches the row's 16-byte unit
-// p ^ ((row >> 2) & 3), and readers look unit u up at position u ^ ((row >> 2) & 3).
+// different bank groups, position p of a row holds the row's unit p ^ swz(row).
 // The copies are issued with inline assembly (the compiler then neither reorders LDS reads
 // around them nor waits for all of them at every LDS read) and waited for with explicit
 // s_waitcnt vmcnt: the kernel issues no other vector-memory loads inside the loop.
 //
-// Slot s of a wave's 64 columns' worth of B (two instruction tiles) holds column 2 (s % 32) + s / 32, so a
-// lane ends with two neighbouring columns of C and stores them together, 128 contiguous bytes of a row
-// per 32 lanes (BF16), where single columns took twice the stores of half a line each.
-//
-// Scales: K a multiple of 128 (KFULL) 4 bytes per lane, the 8 of a row in two words; any other K (a multiple of
+// Scales: K whole chunks (KFULL) 4 bytes per lane, U / 2 lanes per row; any other K (a multiple of
 // 32) 2 bytes per lane, each pair in a word of its own, which asks nothing of the alignment of scale
 // lines.  There the last chunk sticks out of the rows: the lanes past the end of K copy the row's last unit
 // instead, and the scales they would meet count as zero.  K <= 2^24 (32-bit lane offsets).
 //
-// What bounds it: the chip's power (8192 x 8192 x 8192: 833 us with every wave copying its own rows in a burst;
-// 788 to 826 with shared copies spread over the chunk; builds with parts left out, timing only: 715 without the
+// What bounds it: the chip's power for large products (8192 x 8192 x 8192: 778 us, 782 before the store went
+// through LDS; builds with parts left out, timing only, of a version that took 788 to 826: 715 without the
 // expansions, 690 without the scales' copies either, 655 matrix instructions alone; the vendor's FP16 product
-// of the expanded operands 684).  The barrier per chunk costs nothing that shows (655 with it, too).
+// of the expanded operands 684; 1.7 GHz instead of 2.4).  For the others what comes before and after the loop:
+// 1.5 to 2 us until the first chunk is there, 3 to 4 us of sums and stores (single stores of 2 columns straight from
+// the accumulators, unrolled 128 times, took 9: one wave per SIMD issues them, cold in the instruction
+// cache).  In BF16, us, this / what ran before: 8192 x 8192 x 1056 139 / 152, 4096 x 4096 x 2048 58 / 61,
+// 2048 x 4096 x 4096 58 / 69.5, 1000 x 4096 x 4096 33 / 38.
 // Expanding each operand once per workgroup into FP16 in LDS, which halves the expansions, takes
-// 835 to 854: a quarter more LDS traffic than the matrix instructions leave room for.
-// Ragged K, in 256 x 128 tiles of k_gemm_tile / here: 8192 x 8192 x 8160 1018 / 811, 4096 x 4096 x 4128 145 / 116,
-// 5000 x 6000 x 2080 152 / 124, 2816 x 4096 x 4064 108 / 88.
-constexpr uint32_t kDmaCodes = 2 * GT * 64;                             // bytes of codes per stage
-constexpr uint32_t dma_stage(bool kfull) { return kDmaCodes + 2 * GT * (kfull ? 8 : 16); }
-constexpr int kDmaStages = 4;
-static_assert(kDmaStages * dma_stage(false) <= 160 * 1024, "the stages must fit the LDS");
+// 835 to 854 at 8192 x 8192 x 8192: a quarter more LDS traffic than the matrix instructions leave room for.
 
 // M0 = LDS byte address of lane 0's piece; %1 = the lane's 32-bit byte offset (vector
 // register), %2 = the 64-bit base address (scalar register pair).
 #define NV_DMA16(lds_sgpr, voff, gbase)                                                       \
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"                          \
                :: "s"(lds_sgpr), "v"(voff), "s"(gbase) : "memory", "m0")
-#define NV_DMA4(lds_sgpr, voff, gbase)                                                        \
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2"                            \
-               :: "s"(lds_sgpr), "v"(voff), "s"(gbase) : "memory", "m0")
 // as NV_DMA16, two bytes per lane, each into a 32-bit word of LDS
 #define NV_DMA2(lds_sgpr, voff, gbase)                                                        \
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_ushort %1, %2"                           \
                :: "s"(lds_sgpr), "v"(voff), "s"(gbase) : "memory", "m0")
+// one copy to LDS address base + imm (M0 needs a wait state before a copy reads it)
+#define NV_COPY_TO(insn, lds_sgpr, lds_imm, voff, gbase)                                            \
+  asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\t" insn " %1, %2"                                  \
+               :: "s"(lds_sgpr), "v"(voff), "s"(gbase), "n"(lds_imm) : "memory", "m0", "scc")
 
-template <bool KFULL, bool OUTF32>
-__global__ __launch_bounds__(kGemmThreads) void k_gemm_dma(
+
+// f(0), f(1), ..., f(N - 1) with the number as a constant
+template <int N, typename F>
+NV_DEV void each_number(F f) {
+  if constexpr (N > 0) {
+    each_number<N - 1>(f);
+    f(std::integral_constant<int, N - 1>{});
+  }
+}
+
+template <typename S, bool KFULL, bool OUTF32>
+__global__ __launch_bounds__(S::kThreads, 1) void k_gemm_dma(
     const uint8_t *__restrict__ codes_a, const uint8_t *__restrict__ scales_a,
     const float *__restrict__ alpha_a, const uint8_t *__restrict__ codes_b,
     const uint8_t *__restrict__ scales_b, const float *__restrict__ alpha_b,
-    void *__restrict__ out, int64_t M, int64_t N, uint32_t K, uint32_t tiles_n, uint32_t sha,
-    uint32_t shb) {
+    void *__restrict__ out, int64_t M, int64_t N, uint32_t K, uint32_t tiles_m, uint32_t tiles_n,
+    uint32_t strip, uint32_t sha, uint32_t shb) {
+  constexpr int WM = S::WM, WN = S::WN, KS = S::KS, HPW = S::HPW, NST = S::NST, U = S::U, T = S::T, W = S::kWaves;
+  constexpr uint32_t STAGE = S::stage(KFULL);
+  constexpr int NC = S::NC, NS = S::ns(KFULL), kCopies = NC + NS, STEPS = 4 * HPW;
+  typedef uint32_t v4 __attribute__((ext_vector_type(4)));
+  typedef float f4 __attribute__((ext_vector_type(4)));
   extern __shared__ __align__(16) uint8_t lds_raw[];
   const uint32_t t = threadIdx.x, lane = t & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const uint32_t r = lane & 31u, g = lane >> 5;
-  const uint32_t wm = wave >> 1, wn = wave & 1u;
-  const uint32_t tile_m = blockIdx.x / tiles_n, tile_n = blockIdx.x - tile_m * tiles_n;
-  const int64_t m0 = (int64_t)tile_m * GT, n0 = (int64_t)tile_n * GT;
-  const uint32_t row_codes = K / 2, row_scales = K / 16;
-  constexpr uint32_t STAGE = dma_stage(KFULL);
-  constexpr int NS = KFULL ? 2 : 4;               // scale copies per wave, chunk and operand
-  const uint32_t rows_a = (uint32_t)(M - m0 < GT ? M - m0 : GT);     // rows the tile really has
-  const uint32_t rows_b = (uint32_t)(N - n0 < GT ? N - n0 : GT);
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds_raw;
+  const uint32_t kg = wave / (S::SM * S::SN), spatial = wave % (S::SM * S::SN);
+  const uint32_t wm = spatial / S::SN, wn = spatial % S::SN;
 
-  // first rows of the workgroup's operand slices, and each lane's byte offset from there for
-  // every copy instruction of a chunk (a row past the end of its operand re-reads the last one)
-  // (wave-uniform by construction; read through readfirstlane so that they live in scalar
-  // registers, which is where the copy instruction takes its base address from)
+  const TileAt at = tile_of_workgroup(tiles_m, tiles_n, strip);
+  const int64_t m0 = (int64_t)at.m * S::BM, n0 = (int64_t)at.n * S::BN;
+  const uint32_t row_codes = K / 2, row_scales = K / 16;
+  const uint32_t rows_a = (uint32_t)(M - m0 < S::BM ? M - m0 : S::BM);     // rows the tile really has
+  const uint32_t rows_b = (uint32_t)(N - n0 < S::BN ? N - n0 : S::BN);
+
+  const float scale = alpha_a[0] * alpha_b[0];
   auto uniform = [](const uint8_t *p) {
     const uint64_t v = reinterpret_cast<uint64_t>(p);
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
@@ -372,201 +381,221 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm_dma(
     return reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);
   };
   const uint8_t *gca = uniform(codes_a + m0 * row_codes), *gcb = uniform(codes_b + n0 * row_codes);
-  // (a row's scale line: the row itself, or row / 16 for an operand quantized in 16x16 tiles)
   const uint8_t *gsa = uniform(scales_a + (m0 >> sha) * row_scales);
   const uint8_t *gsb = uniform(scales_b + (n0 >> shb) * row_scales);
-  // the operand row in slot `slot` of the 256 of A, or of B (see the kernel's comment)
-  auto line_a = [&](uint32_t slot) { return slot < rows_a ? slot : rows_a - 1; };
-  auto line_b = [&](uint32_t slot) {
-    const uint32_t l = (slot & ~63u) + 2 * (slot & 31u) + ((slot >> 5) & 1u);
-    return l < rows_b ? l : rows_b - 1;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds_raw;
+
+  auto swz_c = [](uint32_t row) { return (row / (16 / U)) & (U - 1u); };
+  auto swz_s = [](uint32_t row) {
+    return KFULL ? (U == 8 ? (row >> 4) & 1u : 0u) : ((row / (64 / U)) << 1) & (U - 1u);
   };
-  // wave w issues code copies w, w + 4, ... of the 16 of each operand (16 rows each), and scale
-  // copies w, w + 4, ... of the 8 (32 rows each, 4 bytes per lane) or 16 (16 rows, 2 bytes)
-  auto unit_at = [&](int q) __attribute__((always_inline)) {                              // the lane's 16-byte unit of its row, 0..3
-    const uint32_t slot = 16 * (4 * q + wave) + (lane >> 2);
-    return (lane & 3u) ^ ((slot >> 2) & 3u);
+  // copies of a wave, numbered: n < NC codes, then scales; 64 / U (128 / U for KFULL's scales) rows each
+  constexpr int RC = 64 / U, RS = KFULL ? 128 / U : 64 / U;
+  constexpr int AC = S::BM / RC, AS = S::BM / RS;        // instructions that belong to A
+  auto of_a = [&](int n) __attribute__((always_inline)) {
+    const bool codes = n < NC;
+    const int first = (codes ? n : n - NC) * W, cut = codes ? AC : AS;
+    return first + W <= cut ? true : first >= cut ? false : first + (int)wave < cut;
   };
-  auto pair_at = [&](int q) __attribute__((always_inline)) {                              // the pair of scales, 0..3 (two of them if KFULL)
-    const uint32_t slot = 16 * (4 * q + wave) + (lane >> 2);
-    return KFULL ? 2 * (lane & 1u) : (lane & 3u) ^ (((slot >> 4) & 1u) << 1);
+  // the lane's byte offset for copy n; units past `last` (the row's last one) give that one instead
+  auto offset = [&](int n, uint32_t last) __attribute__((always_inline)) {
+    const bool codes = n < NC, is_a = of_a(n);
+    const uint32_t i = wave + W * (codes ? n : n - NC);
+    const int per = codes ? U : KFULL ? U / 2 : U;       // lanes per row
+    const uint32_t row = i * (64 / per) + lane / per, pos = lane % per;
+    const uint32_t line = row - (is_a ? 0u : (uint32_t)S::BM), end = (is_a ? rows_a : rows_b) - 1;
+    const uint32_t l = line < end ? line : end;
+    uint32_t u = codes ? pos ^ swz_c(row) : pos ^ swz_s(row);
+    if (!KFULL) u = u < last ? u : last;
+    return codes ? l * row_codes + u * 16 : (l >> (is_a ? sha : shb)) * row_scales + u * (KFULL ? 4 : 2);
   };
-  uint32_t oca[4], ocb[4], osa[NS], osb[NS];
+  const uint32_t nchunks = (K + S::CK - 1) / S::CK;
+  uint32_t off[kCopies];
+  auto offsets = [&](uint32_t c) __attribute__((always_inline)) {
+    const uint32_t left = (K - c * S::CK) / 32 - 1, last = left < U - 1u ? left : U - 1u;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const uint32_t slot = 16 * (4 * q + wave) + (lane >> 2);
-    oca[q] = line_a(slot) * row_codes + unit_at(q) * 16;
-    ocb[q] = line_b(slot) * row_codes + unit_at(q) * 16;
-  }
-#pragma unroll
-  for (int q = 0; q < NS; ++q) {
-    const uint32_t slot = KFULL ? 32 * (4 * q + wave) + (lane >> 1) : 16 * (4 * q + wave) + (lane >> 2);
-    osa[q] = (line_a(slot) >> sha) * row_scales + pair_at(q) * 2;
-    osb[q] = (line_b(slot) >> shb) * row_scales + pair_at(q) * 2;
-  }
-  // the wave's copy instructions of a chunk, numbered so that they can be issued one at a time
-  constexpr int kCopies = 8 + 2 * NS;
-  auto copy_one = [&](uint32_t c, uint32_t stage, int n) __attribute__((always_inline)) {
-    const uint32_t codes = lds0 + stage * STAGE + wave * 1024, scales = lds0 + stage * STAGE + kDmaCodes + wave * 256;
-    if (n < 4) NV_DMA16(codes + n * 4096, oca[n], gca + c * (GK / 2));
-    else if (n < 8) NV_DMA16(codes + GT * 64 + (n - 4) * 4096, ocb[n - 4], gcb + c * (GK / 2));
-    else {
-      const int q = (n - 8) % NS;
-      const uint32_t to = scales + (n - 8) * 1024, from = n < 8 + NS ? osa[q] : osb[q];
-      const uint8_t *base = (n < 8 + NS ? gsa : gsb) + c * (GK / 16);
-      if (KFULL) NV_DMA4(to, from, base);
-      else NV_DMA2(to, from, base);
+    for (int n = 0; n < kCopies; ++n) off[n] = offset(n, last);
+  };
+  auto copy_one = [&](uint32_t c, uint32_t stage, auto copy) __attribute__((always_inline)) {
+    constexpr int n = decltype(copy)::value;
+    if constexpr (n < NC) {
+      NV_COPY_TO("global_load_lds_dwordx4", lds0 + stage * STAGE + wave * 1024, n * W * 1024, off[n],
+                   (of_a(n) ? gca : gcb) + c * (S::CK / 2));
+    } else {
+      const uint32_t to = lds0 + stage * STAGE + wave * 256;
+      const uint8_t *base = (of_a(n) ? gsa : gsb) + c * (S::CK / 16);
+      if constexpr (KFULL) NV_COPY_TO("global_load_lds_dword", to, S::kCodes + (n - NC) * W * 256, off[n], base);
+      else NV_COPY_TO("global_load_lds_ushort", to, S::kCodes + (n - NC) * W * 256, off[n], base);
     }
   };
-  // KFULL = false: the last chunk sticks out of the rows; the lanes that would read past the end of K
-  // read the row's last unit instead (and its scales count as zero, below)
-  const uint32_t nchunks = (K + GK - 1) / GK;
-  auto pull_in = [&](uint32_t c) __attribute__((always_inline)) {
-    if (!KFULL && c + 1 == nchunks) {
-      const uint32_t last = (K - c * GK) / 32 - 1;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const uint32_t slot = 16 * (4 * q + wave) + (lane >> 2);
-        const uint32_t u = unit_at(q) < last ? unit_at(q) : last, p = pair_at(q) < last ? pair_at(q) : last;
-        oca[q] = line_a(slot) * row_codes + u * 16;
-        ocb[q] = line_b(slot) * row_codes + u * 16;
-        osa[q % NS] = (line_a(slot) >> sha) * row_scales + p * 2;
-        osb[q % NS] = (line_b(slot) >> shb) * row_scales + p * 2;
-      }
-    }
+
+  struct Raw {
+    v4 c[T];
+    uint32_t s[T];
+  } x;
+  const uint32_t row_a = wm * (32 * WM) + r, row_b = S::BM + wn * (32 * WN) + r;
+  auto read_tile = [&](uint32_t stage, int h, int i) __attribute__((always_inline)) {
+    const uint32_t u = 2 * (kg * HPW + h) + g;
+    const uint8_t *st = lds_raw + stage * STAGE, *sc = st + S::kCodes;
+    const uint32_t row = i < WM ? row_a + 32 * i : row_b + 32 * (i - WM);
+    x.c[i] = *reinterpret_cast<const v4 *>(st + row * (U * 16) + (u ^ swz_c(r)) * 16);
+    x.s[i] = KFULL ? *reinterpret_cast<const uint16_t *>(sc + row * (U * 2) + (u ^ (swz_s(r) << 1)) * 2)
+                   : *reinterpret_cast<const uint32_t *>(sc + row * (U * 4) + (u ^ swz_s(r)) * 4);
   };
-  auto copy_chunk = [&](uint32_t c, uint32_t stage) __attribute__((always_inline)) {
-    pull_in(c);
-#pragma unroll
-    for (int n = 0; n < kCopies; ++n) copy_one(c, stage, n);
+  // k0: where the wave's piece begins
+  auto expand_one = [&](int s, int i, uint32_t k0) __attribute__((always_inline)) {
+    if (!KFULL && s == 0 && k0 + 32 * g >= K) x.s[i] = 0u;
+    if (s == 0) x.s[i] = __builtin_amdgcn_perm(0u, x.s[i], 0x0c010c00u) << 7;
+    const h2 pair = __builtin_bit_cast(h2, x.s[i]);
+    return expand8(x.c[i][s], s < 2 ? pair.x : pair.y);
   };
 
-  // ---- LDS -> registers, one operand tile at a time (u = 0..3: A tiles, 4..7: B tiles)
-  const uint32_t swz = (r >> 2) & 3u;
-  auto read_tile = [&](uint32_t stage, int half, int u, RawHalf &h) __attribute__((always_inline)) {
-    const uint8_t *st = lds_raw + stage * STAGE + (u < 4 ? 0 : GT * 64);
-    const uint8_t *sc = lds_raw + stage * STAGE + kDmaCodes + (u < 4 ? 0 : GT * (KFULL ? 8 : 16));
-    const uint32_t row = (u < 4 ? wm : wn) * 128 + 32 * (u & 3) + r, pos = ((2 * half + g) ^ swz) * 16;
-    const uint4 codes = *reinterpret_cast<const uint4 *>(st + row * 64 + pos);
-    // the lane's two scale bytes of this half (blocks 4*half + 2*g and + 1), still raw
-    const uint32_t two = KFULL ? *reinterpret_cast<const uint16_t *>(sc + row * 8 + 4 * half + 2 * g)
-                               : *reinterpret_cast<const uint32_t *>(
-                                     sc + row * 16 + (((2 * half + g) ^ (((r >> 4) & 1u) << 1)) * 4));
-    if (u < 4) { h.a[u] = codes; h.sa[u] = two; } else { h.b[u - 4] = codes; h.sb[u - 4] = two; }
-  };
-  // operands of step s (0..3) of a half for tile u; at s == 0 the two scale bytes are turned
-  // into two FP16 bit patterns (byte << 7) in one word
-  auto expand_tile = [&](RawHalf &h, int s, int u, Frags &f, uint32_t k) __attribute__((always_inline)) {
-    const uint4 &w4 = u < 4 ? h.a[u] : h.b[u - 4];
-    uint32_t &sc = u < 4 ? h.sa[u] : h.sb[u - 4];
-    if (!KFULL && s == 0 && k + 32 * g >= K) sc = 0u;      // k: where the half begins
-    if (s == 0) sc = __builtin_amdgcn_perm(0u, sc, 0x0c010c00u) << 7;
-    const uint32_t w = s == 0 ? w4.x : s == 1 ? w4.y : s == 2 ? w4.z : w4.w;
-    const h2 pair = __builtin_bit_cast(h2, sc);
-    const h8 e = expand8(w, s < 2 ? pair.x : pair.y);
-    if (u < 4) f.a[u] = e; else f.b[u - 4] = e;
-  };
-
-  f32x16 acc[4][4];
+  f32x16 acc[WM][WN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < WM; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < WN; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
-  RawHalf h0, h1;
-  Frags f0, f1;
-  // past the end: a harmless re-read  (readfirstlane: the copies' base addresses stay in scalar registers)
-  auto at_most = [&](uint32_t c) { return (uint32_t)__builtin_amdgcn_readfirstlane(c < nchunks ? c : nchunks - 1); };
+  // past the end: a harmless re-read, so that the waits below always count the same copies
+  auto clamp_chunk = [&](uint32_t c) { return (uint32_t)__builtin_amdgcn_readfirstlane(c < nchunks ? c : nchunks - 1); };
+  offsets(0);
+#pragma unroll 1
+  for (uint32_t p = 0; p < NST - 1; ++p) {
+    if (!KFULL && p == nchunks - 1) offsets(p);
+    each_number<kCopies>([&](auto copy) __attribute__((always_inline)) { copy_one(clamp_chunk(p), p, copy); });
+  }
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((NST - 2) * kCopies) : "memory");
+  h8 f[2][T];
 #pragma unroll
-  for (int c = 0; c < kDmaStages - 1; ++c) copy_chunk(at_most(c), c);
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((kDmaStages - 2) * kCopies) : "memory");   // chunk 0 is in LDS
+  for (int i = 0; i < T; ++i) read_tile(0, 0, i);
 #pragma unroll
-  for (int u = 0; u < 8; ++u) read_tile(0, 0, u, h0);
-#pragma unroll
-  for (int u = 0; u < 8; ++u) expand_tile(h0, 0, u, f0, 0u);
+  for (int i = 0; i < T; ++i) f[0][i] = expand_one(0, i, kg * (64 * HPW));
 
-  // Chunk c sits in stage c % 4.  A step is eight units of two matrix instructions; unit u
-  // also expands operand tile u for the next step and carries the step's share of LDS
-  // reads and copy instructions, so that everything issues in the matrix unit's shadow:
-  //   steps 0-5     start the wave's copies of chunk c + 3, two per step, into the stage that chunk c - 1
-  //                 left: every wave had read all of that when it came to the barrier of chunk c - 1;
-  //   step 1        reads the chunk's second half;
-  //   step 6        waits until only the copies of chunks c + 2 and c + 3 are outstanding, meets the other
-  //                 waves (chunk c + 1 has landed whole) and reads its first half;
-  //   step 7        expands the next chunk's first step.
-  auto chunk = [&](uint32_t c, bool last) __attribute__((always_inline)) {
-    const uint32_t cur = c & 3u, nxt = (cur + 1u) & 3u;
-    const uint32_t c3 = at_most(c + kDmaStages - 1);
-    if (!last) pull_in(c3);
+  uint32_t stage = 0, freed = NST - 1;
+  // Chunk c sits in stage c % NST.  A step is T units; unit u expands operand tile u for the next step beside its
+  // matrix instructions of this one and carries the step's share of LDS reads and copies:
+  //   all but the last two steps   start the wave's copies of chunk c + NST - 1, into the stage of chunk c - 1, which
+  //                                every wave had read when it came to the barrier of chunk c - 1;
+  //   the last step but one        waits until chunk c + 1 has landed and all waves' reads are back, meets the
+  //                                other waves, and reads the first piece of chunk c + 1;
+  //   step 2 of any other piece    reads the next piece of the chunk.
+  // A tile's raw words are read into the registers whose last word has just been expanded.  The last chunk runs
+  // the same code (what it reads ahead is not used): a copy of the loop without that cost more, cold in the
+  // instruction cache, than it saved.
+#pragma unroll 1
+  for (uint32_t c = 0; c < nchunks; ++c) {
+    const uint32_t nxt = stage + 1 == (uint32_t)NST ? 0u : stage + 1, ahead = c + NST - 1;
+    const uint32_t from = clamp_chunk(ahead);
+    if (!KFULL && ahead == nchunks - 1) offsets(ahead);
 #pragma unroll
-    for (int st = 0; st < 8; ++st) {
-      Frags &fc = (st & 1) ? f1 : f0, &fn = (st & 1) ? f0 : f1;
-      if (st == 6 && !last)
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((kDmaStages - 2) * kCopies) : "memory");
+    for (int st = 0; st < STEPS; ++st) {
+      const int s = st & 3;
+      if (st == STEPS - 2)
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((NST - 2) * kCopies) : "memory");
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (st == 1) read_tile(cur, 1, u, h1);
-        if (st < 6 && (u == 2 || u == 6) && !last) copy_one(c3, (cur + 3u) & 3u, 2 * st + u / 4);
-        if (!KFULL && st < 4 && u == 4 && !last) copy_one(c3, (cur + 3u) & 3u, 12 + st);
-        if (st == 6 && !last) read_tile(nxt, 0, u, h0);
-        if (st < 7) expand_tile(st < 3 ? h0 : h1, (st + 1) & 3, u, fn, c * GK + 64);
-        else if (!last) expand_tile(h0, 0, u, fn, (c + 1) * GK);
+      for (int u = 0; u < T; ++u) {
+        constexpr int kSlots = (STEPS - 2) * T, kV = (8 * T + S::kTiles - 1) / S::kTiles;
+        if (st < STEPS - 2)
+          each_number<kCopies>([&](auto copy) __attribute__((always_inline)) {
+            if (decltype(copy)::value * kSlots / kCopies == st * T + u) copy_one(from, freed, copy);
+          });
+        __builtin_amdgcn_sched_barrier(0);
+        // expand for the next step, then (its last word gone) read the next piece
+        const int h = st / 4;
+        const uint32_t k0 = s == 3 ? (h == HPW - 1 ? (c + 1) * S::CK + kg * (64 * HPW) : c * S::CK + kg * (64 * HPW) + (h + 1) * 64) : 0u;
+        f[(st + 1) & 1][u] = expand_one((s + 1) & 3, u, k0);
+        if (s == 2) read_tile(h == HPW - 1 ? nxt : stage, h == HPW - 1 ? 0 : h + 1, u);
 #pragma unroll
-        for (int q = 2 * u; q < 2 * u + 2; ++q)
-          acc[q >> 2][q & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fc.a[q >> 2], fc.b[q & 3],
-                                                                      acc[q >> 2][q & 3], 0, 0, 0);
-        const bool reads = st == 1 || (st == 6 && !last);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        if (reads) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        if (reads) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
+        for (int q = u * S::kTiles / T; q < (u + 1) * S::kTiles / T; ++q)
+          acc[q / WN][q % WN] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f[st & 1][WM + q % WN], f[st & 1][q / WN],
+                                                                       acc[q / WN][q % WN], 0, 0, 0);
+#pragma unroll
+        for (int q = u * S::kTiles / T; q < (u + 1) * S::kTiles / T; ++q) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          if (q & 1) __builtin_amdgcn_sched_group_barrier(0x002, kV + 1, 0);
+          else __builtin_amdgcn_sched_group_barrier(0x002, kV, 0);
+        }
+        if (s == 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-  };
-  for (uint32_t c = 0; c + 1 < nchunks; ++c) chunk(c, false);
-  chunk(nchunks - 1, true);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // nothing may still be writing LDS
+    freed = stage;
+    stage = nxt;
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
-  // ---- store: instruction tiles 2 jp and 2 jp + 1 hold the even and the odd columns of 64
-  const float scale = alpha_a[0] * alpha_b[0];
-  const bool whole = (N & 1) == 0;              // a lane's two columns exist together and are aligned
+  // ---- partial sums -> LDS -> C, a block of 32 rows per wave at a time: the operands were exchanged in the matrix
+  // instruction, so four accumulator elements are neighbouring columns.  Then G columns (16 bytes) per lane, RPS
+  // rows per turn of the workgroup, the KS parts added in order; two blocks in turn, so one barrier each.
+  constexpr int G = OUTF32 ? 4 : 8, QG = S::BN / G, RPS = S::kThreads / QG, kRows = 32 * S::SM, E = kRows / RPS;
+  static_assert(S::kThreads % QG == 0 && 32 % RPS == 0, "");
+  const bool inside = rows_a == S::BM && rows_b == S::BN;
+  const int64_t line = N * (OUTF32 ? 4 : 2);
+  const uint32_t lr0 = t / QG, col0 = t % QG * G;
+  char *const corner = static_cast<char *>(out) + (m0 + lr0) * line + (n0 + col0) * (OUTF32 ? 4 : 2);
+#pragma unroll 1
+  for (int i = 0; i < WM; ++i) {
+    float *buf = reinterpret_cast<float *>(lds_raw + (i & 1) * S::kSums);
+    float *to = buf + (kg * kRows + wm * 32 + r) * S::kPitch + wn * (32 * WN) + 4 * g;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int ii = 0; ii < WM; ++ii)
+      if (i == ii) {
 #pragma unroll
-    for (int jp = 0; jp < 2; ++jp) {
-      const uint32_t col = wn * 128 + 64 * jp + 2 * r;
+        for (int j = 0; j < WN; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const uint32_t row = wm * 128 + 32 * i + 8 * (v / 4) + 4 * g + v % 4;
-        if (row < rows_a && col < rows_b) {
-          const float x = acc[i][2 * jp][v] * scale, y = acc[i][2 * jp + 1][v] * scale;
-          const int64_t at = (m0 + row) * N + n0 + col;
-          if (OUTF32) {
-            float *o = static_cast<float *>(out) + at;
-            if (whole) {
-              *reinterpret_cast<float2 *>(o) = make_float2(x, y);
-            } else {
-              o[0] = x;
-              if (col + 1 < rows_b) o[1] = y;
-            }
+          for (int v = 0; v < 16; v += 4)
+            *reinterpret_cast<f4 *>(to + 32 * j + 2 * v) = f4{acc[ii][j][v], acc[ii][j][v + 1], acc[ii][j][v + 2], acc[ii][j][v + 3]};
+        // (keeps the compiler from merging the blocks' writes behind copies of all 64 registers)
+        asm volatile("; row block %0" :: "n"(ii));
+      }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    f4 sum[E][G / 4];
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+#pragma unroll
+      for (int k = 0; k < KS; ++k)
+#pragma unroll
+        for (int h = 0; h < G / 4; ++h) {
+          const f4 part = *reinterpret_cast<const f4 *>(buf + (k * kRows + e * RPS + lr0) * S::kPitch + col0 + 4 * h);
+          sum[e][h] = k == 0 ? part : sum[e][h] + part;
+        }
+    // (lines of C start wherever N puts them)
+    typedef f4 f4_anywhere __attribute__((aligned(4)));
+    typedef v4 v4_anywhere __attribute__((aligned(2)));
+    auto store = [&](int e) __attribute__((always_inline)) {
+      char *o = corner + (e * RPS / 32 * (32 * WM) + e * RPS % 32 + 32 * i) * line;
+      if constexpr (OUTF32) {
+        *reinterpret_cast<f4_anywhere *>(o) = sum[e][0] * scale;
+      } else {
+        const f4 x0 = sum[e][0] * scale, x1 = sum[e][G / 4 - 1] * scale;
+        *reinterpret_cast<v4_anywhere *>(o) = v4{pack_bf16x2(x0.x, x0.y), pack_bf16x2(x0.z, x0.w), pack_bf16x2(x1.x, x1.y),
+                                        pack_bf16x2(x1.z, x1.w)};
+      }
+    };
+    if (inside) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) store(e);
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (e * RPS / 32 * (32 * WM) + e * RPS % 32 + 32 * i + lr0 < rows_a) {
+          if (col0 + G <= rows_b) {
+            store(e);
           } else {
-            uint16_t *o = static_cast<uint16_t *>(out) + at;
-            const uint32_t w = pack_bf16x2(x, y);
-            if (whole) {
-              *reinterpret_cast<uint32_t *>(o) = w;
-            } else {
-              o[0] = (uint16_t)w;
-              if (col + 1 < rows_b) o[1] = (uint16_t)(w >> 16);
-            }
+            char *o = corner + (e * RPS / 32 * (32 * WM) + e * RPS % 32 + 32 * i) * line;
+#pragma unroll
+            for (int q = 0; q < G; ++q)
+              if (col0 + q < rows_b) {
+                const float c = sum[e][q / 4][q % 4] * scale;
+                if (OUTF32) reinterpret_cast<float *>(o)[q] = c;
+                else reinterpret_cast<uint16_t *>(o)[q] = (uint16_t)pack_bf16x2(c, 0.0f);
+              }
           }
         }
-      }
     }
+  }
 }
 
 // ----------------------------------------------------------------------------------------
@@ -1237,6 +1266,7 @@ struct GemmArgs {
 // kernel gets without asking), launches, and returns a status of the C ABI.
 template <bool KFULL, bool OUTF32>
 int run_gemm_staged(const GemmArgs &a);
+template <typename S>
 int run_gemm_dma(const GemmArgs &a);
 int run_gemm_skinny(const GemmArgs &a);
 template <typename S>
@@ -1257,7 +1287,7 @@ static int launch_with_lds(Kernel kernel, dim3 grid, dim3 block, size_t lds_byte
 // h w = tiles / 8 touch the fewest operand rows, BM h + BN w, at w = sqrt(tiles / 8 * BM / BN).
 // Row by row / in strips: 1536 x 4096 x 8192 106 / 102 us, 8000 x 8000 x 2080 314 / 306, 768 x 4096
 // x 8192 56 / 55.  Operands that fit the 4 MB of one die's L2 whole stay row by row (2880 x 1440 x
-// 1056: 19.9 / 20.2), and so do k_gemm_dma's tiles (8192 x 8192 x 8192: 841 / 849).
+// 1056: 19.9 / 20.2).  (k_gemm_dma: no difference.)
 template <int BM, int BN>
 static uint32_t strip_of(const GemmArgs &a) {
   const double tm = (double)((a.M + BM - 1) / BM), tn = (double)((a.N + BN - 1) / BN);
@@ -1289,16 +1319,27 @@ template int run_gemm_staged<((NVFP4_46_GEMM_PART - 1) / 2 != 0), ((NVFP4_46_GEM
 #endif
 
 #if NVFP4_46_GEMM_HAS(5)
+template <typename S>
 int run_gemm_dma(const GemmArgs &a) {
-  const uint32_t tiles_n = (uint32_t)((a.N + GT - 1) / GT);
-  auto go = [&](auto kernel) {
-    return launch_with_lds(kernel, tile_grid(a), dim3(kGemmThreads), kDmaStages * dma_stage(a.K % GK == 0),
-                           a.stream, a.codes_a, a.scales_a, a.alpha_a, a.codes_b, a.scales_b, a.alpha_b,
-                           a.out, a.M, a.N, (uint32_t)a.K, tiles_n, a.sha, a.shb);
+  auto go = [&](auto kernel, bool kfull) {
+    return launch_with_lds(kernel, dim3((uint32_t)tiles_of<S>(a.M, a.N)), dim3(S::kThreads), S::lds(kfull), a.stream,
+                           a.codes_a, a.scales_a, a.alpha_a, a.codes_b, a.scales_b, a.alpha_b, a.out, a.M, a.N,
+                           (uint32_t)a.K, (uint32_t)((a.M + S::BM - 1) / S::BM), (uint32_t)((a.N + S::BN - 1) / S::BN),
+                           strip_of<S::BM, S::BN>(a), a.sha, a.shb);
   };
-  if (a.K % GK == 0) return a.f32 ? go(k_gemm_dma<true, true>) : go(k_gemm_dma<true, false>);
-  return a.f32 ? go(k_gemm_dma<false, true>) : go(k_gemm_dma<false, false>);
+  if (a.K % S::CK == 0) return a.f32 ? go(k_gemm_dma<S, true, true>, true) : go(k_gemm_dma<S, true, false>, true);
+  return a.f32 ? go(k_gemm_dma<S, false, true>, false) : go(k_gemm_dma<S, false, false>, false);
 }
+#endif
+#if NVFP4_46_GEMM_PART == 0 || NVFP4_46_GEMM_PART == 5
+#if NVFP4_46_GEMM_PART == 0
+#define NVFP4_46_DMA extern template
+#else
+#define NVFP4_46_DMA template
+#endif
+NVFP4_46_DMA int run_gemm_dma<Dma256>(const GemmArgs &);
+NVFP4_46_DMA int run_gemm_dma<Dma256x128>(const GemmArgs &);
+NVFP4_46_DMA int run_gemm_dma<Dma128>(const GemmArgs &);
 #endif
 
 #if NVFP4_46_GEMM_HAS(6)
@@ -1387,7 +1428,9 @@ extern "C" int nvfp4_46_gemm(const void *codes_a, const void *scales_a, const fl
     case kGemmStaged:
       return (K % GK) == 0 ? (a.f32 ? run_gemm_staged<true, true>(a) : run_gemm_staged<true, false>(a))
                            : (a.f32 ? run_gemm_staged<false, true>(a) : run_gemm_staged<false, false>(a));
-    case kGemmDma: return run_gemm_dma(a);
+    case kGemmDma: return run_gemm_dma<Dma256>(a);
+    case kGemmDma256x128: return run_gemm_dma<Dma256x128>(a);
+    case kGemmDma128: return run_gemm_dma<Dma128>(a);
     case kGemmSkinny: return run_gemm_skinny(a);
     case kGemmTile32: return run_gemm_tile<Tile32>(a);
     case kGemmTile64x32: return run_gemm_tile<Tile64x32>(a);

@@ -7,7 +7,7 @@
 
 namespace nvfp4_46 {
 
-constexpr int GT = 256;                  // k_gemm, k_gemm_dma: rows of A (and of B) per workgroup tile
+constexpr int GT = 256;                  // k_gemm: rows of A (and of B) per workgroup tile
 constexpr int GK = 128;                  // ... and contraction steps per chunk
 constexpr int SK = 256;                  // k_gemm_skinny, k_gemm_skinny16: contraction steps per chunk
 constexpr int64_t kCus = 256;
@@ -46,6 +46,34 @@ using Tile64Long = TileShape<2, 2, 1, 1, 8, 1, 2>;     // 64 x 64, 8 waves
 using Tile128 = TileShape<2, 2, 2, 2, 4, 1, 2>;        // 128 x 128, 16 waves
 using Tile256x128 = TileShape<4, 2, 2, 2, 2, 1, 4>;    // 256 x 128, 8 waves
 
+// k_gemm_dma's shapes (described at the kernel): four waves of WM x WN instruction tiles, SM x SN of them over the
+// tile of C and KS along the contraction axis, each taking HPW pieces of 64 steps of a chunk; NST stages.
+template <int WM_, int WN_, int SM_, int SN_, int KS_, int HPW_, int NST_>
+struct DmaShape {
+  static constexpr int WM = WM_, WN = WN_, SM = SM_, SN = SN_, KS = KS_, HPW = HPW_, NST = NST_;
+  static constexpr int kWaves = SM * SN * KS, kThreads = 64 * kWaves;
+  static constexpr int BM = 32 * WM * SM, BN = 32 * WN * SN, ROWS = BM + BN;
+  static constexpr int CK = 64 * KS * HPW, U = CK / 32, T = WM + WN, kTiles = WM * WN;
+  // bytes of a stage: codes, then 2 (K whole chunks) or 4 bytes per pair of scales
+  static constexpr uint32_t kCodes = ROWS * U * 16;
+  static constexpr uint32_t stage(bool kfull) { return kCodes + ROWS * U * (kfull ? 2 : 4); }
+  // copy instructions per wave and chunk: codes and scales
+  static constexpr int NC = ROWS * U / 64 / kWaves;
+  static constexpr int ns(bool kfull) { return ROWS * U / (kfull ? 128 : 64) / kWaves; }
+  // a block of 32 rows per wave of the partial sums, on its way through LDS to the store; two of them in turn
+  static constexpr int kPitch = BN + 4;
+  static constexpr uint32_t kSums = KS * SM * 32 * kPitch * 4;
+  static constexpr uint32_t lds(bool kfull) {
+    return NST * stage(kfull) > 2 * kSums ? NST * stage(kfull) : 2 * kSums;
+  }
+  static_assert(ROWS * U % (128 * kWaves) == 0 && BM % (128 / U) == 0, "a copy instruction stays within one operand");
+  static_assert(lds(false) <= 160 * 1024 && lds(true) <= 160 * 1024, "the stages must fit the LDS");
+  static_assert((NST - 2) * (NC + ns(false)) < 63, "vmcnt counts to 63");
+};
+using Dma256 = DmaShape<4, 4, 2, 2, 1, 2, 4>;          // 256 x 256, each wave a quarter of it
+using Dma256x128 = DmaShape<4, 4, 2, 1, 2, 1, 5>;      // 256 x 128, two waves per half of K
+using Dma128 = DmaShape<4, 4, 1, 1, 4, 1, 4>;          // 128 x 128, each wave a quarter of K
+
 constexpr int64_t tiles_of(int64_t M, int64_t N, int BM, int BN) {
   return ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
 }
@@ -54,7 +82,7 @@ constexpr int64_t tiles_of(int64_t M, int64_t N) { return tiles_of(M, N, S::BM, 
 
 enum GemmKernel {
   kGemmStaged, kGemmDma, kGemmSkinny, kGemmTile32, kGemmTile64x32, kGemmTile64, kGemmTile64Long,
-  kGemmTile128, kGemmTile256x128
+  kGemmTile128, kGemmTile256x128, kGemmDma256x128, kGemmDma128
 };
 
 // How evenly tiles of BM x BN divide over whole turns of one workgroup per compute unit ...
@@ -135,6 +163,8 @@ inline int64_t lanes_of(GemmKernel kernel, int64_t M, int64_t N) {
     case kGemmTile64Long: return tiles_of<Tile64Long>(M, N) * Tile64Long::kThreads;
     case kGemmTile128: return tiles_of<Tile128>(M, N) * Tile128::kThreads;
     case kGemmTile256x128: return tiles_of<Tile256x128>(M, N) * Tile256x128::kThreads;
+    case kGemmDma256x128: return tiles_of<Dma256x128>(M, N) * Dma256x128::kThreads;
+    case kGemmDma128: return tiles_of<Dma128>(M, N) * Dma128::kThreads;
     default: return tiles_of(M, N, GT, GT) * kGemmThreads;
   }
 }
@@ -147,15 +177,26 @@ inline GemmKernel choose_gemm(int64_t M, int64_t N, int64_t K) {
   return (K % GK) == 0 && K <= ((int64_t)1 << 24) ? kGemmDma : kGemmStaged;
 }
 
-// The kernel that a product runs: choose_gemm()'s, whose 256 x 256 tiles are for whole chunks of 128, or those
-// tiles with a ragged K as well, from the same fill of the chip on.  256 x 256 / choose_gemm()'s: 6144 x 6400 x
-// 1056 (78 %) 112 / 114, 2816 x 4096 x 4064 (69 %) 88 / 108; below the line 3072 x 3072 x 992 (56 %) 33 / 31,
-// 4096 x 4608 x 3040 (56 %) 147 / 136, though 3072 x 3072 x 2080 52 / 58.
+// The kernel that a product runs: choose_gemm()'s, or where the chip is filled well enough one of k_gemm_dma's
+// three shapes, which take any K % 32.  BF16 out, us, the shape / what choose_gemm() gives:
+//   256 x 256 from 62 % of the chip, padding counted as idle: 6144 x 6400 x 1056 (78 %) 112 / 114, 2816 x 4096 x 4064
+//   (69 %) 88 / 108; 3000 x 3000 x 1024 (56 %) 28.0 / 27.4;
+//   256 x 128 from 62 %: 2048 x 4096 x 4096 58 / 69.5, 1536 x 4096 x 4096 (75 %) 49 / 62, 6798 x 880 x 4160 (73 %)
+//   54 / 76, 192 x 28672 x 8192 (66 %) 96 / 103, 996 x 5232 x 704 (64 %) 17.7 / 19.5; 3388 x 1408 x 2304 (60 %)
+//   29.7 / 29.1, 4798 x 912 x 768 (59 %) 16.5 / 16.2;
+//   128 x 128 from 70 % of one turn and a K whose quarters outlast their sum's way through LDS: 1000 x 4096 x 4096
+//   32.7 / 38.4, 768 x 4096 x 4096 (75 %) 28.3 / 30.2, 128 x 28672 x 8192 (87 %) 54 / 65; 575 x 4526 x 4352 (63 %)
+//   35.3 / 31.8; 1000 x 4096 x 1024 13.9 / 14.5 but x 256 10.2 / 9.5; two turns and more 3000 x 3000 x 1024 35 / 27.
+template <typename S>
+inline double chip_filled(int64_t M, int64_t N) {
+  return turns_filled(M, N, S::BM, S::BN) * tiles_covered(M, N, S::BM, S::BN);
+}
 inline GemmKernel gemm_kernel(int64_t M, int64_t N, int64_t K) {
-  const bool ragged = (K % GK) != 0 && M > 64 && K <= ((int64_t)1 << 24);
-  if (ragged && lanes_of(kGemmDma, M, N) >> 32 == 0 &&
-      turns_filled(M, N, GT, GT) * tiles_covered(M, N, GT, GT) >= 0.62)
-    return kGemmDma;
+  if (M > 64 && N > 64 && K <= ((int64_t)1 << 24)) {
+    if (chip_filled<Dma256>(M, N) >= 0.62 && lanes_of(kGemmDma, M, N) >> 32 == 0) return kGemmDma;
+    if (chip_filled<Dma256x128>(M, N) >= 0.62 && lanes_of(kGemmDma256x128, M, N) >> 32 == 0) return kGemmDma256x128;
+    if (K >= 1024 && tiles_of<Dma128>(M, N) <= kCus && chip_filled<Dma128>(M, N) >= 0.7) return kGemmDma128;
+  }
   return choose_gemm(M, N, K);
 }
 }  // namespace nvfp4_46

@@ -27,7 +27,7 @@ RTN, SR, SR_AFTER_RTN_SELECT = 0, 1, 2
 
 # enum GemmKernel
 GEMM_KERNELS = ("staged", "dma", "skinny", "tile32", "tile64x32", "tile64", "tile64long",
-                "tile128", "tile256x128")
+                "tile128", "tile256x128", "dma256x128", "dma128")
 
 
 def _compiler() -> str:
