@@ -72,8 +72,20 @@ void *stream(PyObject *o) {
   return reinterpret_cast<void *>(word(o));
 }
 
+// Other threads of the interpreter run while this lives, also when an exception ends it.
+struct WithoutLock {
+  PyThreadState *const state = PyEval_SaveThread();
+  ~WithoutLock() { PyEval_RestoreThread(state); }
+};
+
+// (an allocation may wait for the device, so it is made without the interpreter's lock, as torch.empty does)
 PyObject *new_tensor(at::IntArrayRef shape, at::ScalarType type, const at::Tensor &like) {
-  return THPVariable_Wrap(at::empty(shape, at::TensorOptions().dtype(type).device(like.device())));
+  at::Tensor t;
+  {
+    WithoutLock others;
+    t = at::empty(shape, at::TensorOptions().dtype(type).device(like.device()));
+  }
+  return THPVariable_Wrap(t);
 }
 
 // A reference that is given up unless it is released.
@@ -124,9 +136,10 @@ nvfp4_46_params params_of(const at::Tensor &x, PyObject *const *a) {
 template <typename Call>
 void run(const char *where, Call &&call) {
   int rc;
-  Py_BEGIN_ALLOW_THREADS
-  rc = call();
-  Py_END_ALLOW_THREADS
+  {
+    WithoutLock others;
+    rc = call();
+  }
   if (rc == NVFP4_OK) return;
   PyObject *e = PyObject_CallFunction(error_class, "is", rc, where);
   if (e) {
