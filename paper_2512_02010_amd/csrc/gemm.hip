@@ -325,19 +325,18 @@ __global__ __launch_bounds__(kGemmThreads) void k_gemm(
 // 835 to 854 at 8192 x 8192 x 8192: a quarter more LDS traffic than the matrix instructions leave room for.
 
 // M0 = LDS byte address of lane 0's piece; %1 = the lane's 32-bit byte offset (vector
-// register), %2 = the 64-bit base address (scalar register pair).
+// register), %2 = the 64-bit base address (scalar register pair).  M0 needs a wait state before a copy reads it.
 #define NV_DMA16(lds_sgpr, voff, gbase)                                                       \
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"                          \
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"                          \
                :: "s"(lds_sgpr), "v"(voff), "s"(gbase) : "memory", "m0")
 // as NV_DMA16, two bytes per lane, each into a 32-bit word of LDS
 #define NV_DMA2(lds_sgpr, voff, gbase)                                                        \
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_ushort %1, %2"                           \
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_ushort %1, %2"                           \
                :: "s"(lds_sgpr), "v"(voff), "s"(gbase) : "memory", "m0")
-// one copy to LDS address base + imm (M0 needs a wait state before a copy reads it)
+// a copy by any of the instructions to the LDS address lds_sgpr + lds_imm
 #define NV_COPY_TO(insn, lds_sgpr, lds_imm, voff, gbase)                                            \
   asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\t" insn " %1, %2"                                  \
                :: "s"(lds_sgpr), "v"(voff), "s"(gbase), "n"(lds_imm) : "memory", "m0", "scc")
-
 
 // f(0), f(1), ..., f(N - 1) with the number as a constant
 template <int N, typename F>
@@ -967,7 +966,7 @@ __global__ __launch_bounds__(64 * skinny_waves(MT)) void k_gemm_skinny(
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
       const uint8_t *src = ps[j] + cc * (SK / 16);
-      asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                    :: "s"(lds + ROWS * 128 + j * 1024), "v"(src) : "memory", "m0");
     }
   };
@@ -1145,7 +1144,7 @@ __global__ __launch_bounds__(64 * kSkinny16Waves) void k_gemm_skinny16(
       else NV_DMA16(lds + q * 1024, oc[q], pa);
     }
     const uint8_t *src = ps + cc * (SK / 16);
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                  :: "s"(lds + ROWS * 128), "v"(src) : "memory", "m0");
   };
   constexpr int kCopies = NC + 1;
