@@ -21,7 +21,7 @@
 //
 // Two kernels share this plan: k_gemm (the workgroup stages chunks through registers into
 // shared LDS buffers; only for K > 2^24, beyond the others' 32-bit offsets) and k_gemm_dma (the workgroup
-// fills a ring of four LDS stages with asynchronous global -> LDS copies).
+// fills a ring of LDS stages with asynchronous global -> LDS copies).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -599,8 +599,7 @@ __global__ __launch_bounds__(S::kThreads, 1) void k_gemm_dma(
 
 // ----------------------------------------------------------------------------------------
 // k_gemm_tile: C in tiles of any of several shapes (TileShape), for the many products whose
-// 256 x 256 tiles would leave most compute units idle, and for every K that is not a multiple of
-// 128.  A workgroup has SM x SN waves over its tile of C, each holding WM x WN instruction tiles
+// large tiles (k_gemm_dma's) would leave compute units idle.  A workgroup has SM x SN waves over its tile of C, each holding WM x WN instruction tiles
 // (32 x 32), in KS copies that share the contraction axis: copy kg takes HPW pieces of 64 steps of
 // every chunk, and the copies' partial tiles are added through LDS at the end, always in the same
 // order.  Splitting the contraction axis inside the workgroup is what fills the chip when C is

@@ -44,7 +44,7 @@ using Tile64x32 = TileShape<2, 1, 1, 1, 4, 1, 2>;      // 64 x 32, 4 waves
 using Tile64 = TileShape<2, 2, 1, 1, 4, 1, 2>;         // 64 x 64, 4 waves; three workgroups per CU
 using Tile64Long = TileShape<2, 2, 1, 1, 8, 1, 2>;     // 64 x 64, 8 waves
 using Tile128 = TileShape<2, 2, 2, 2, 4, 1, 2>;        // 128 x 128, 16 waves
-using Tile256x128 = TileShape<4, 2, 2, 2, 2, 1, 4>;    // 256 x 128, 8 waves
+using Tile256x128 = TileShape<4, 2, 2, 2, 2, 1, 4>;    // 256 x 128, 8 waves (Dma256x128 takes all that it would)
 
 // k_gemm_dma's shapes (described at the kernel): four waves of WM x WN instruction tiles, SM x SN of them over the
 // tile of C and KS along the contraction axis, each taking HPW pieces of 64 steps of a chunk; NST stages.
