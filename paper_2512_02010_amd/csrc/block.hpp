@@ -536,6 +536,9 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
   if (ROUNDING == kSRAfterRtnSelect) {
     SrCandidate c{r.dec, four ? enc4 : enc6, {0u, 0u}, 0.0f}, none{};
     sr_candidates<false, kErrNone, FAST>(v, words, c, none, margin);
+    // (only the pass that settles the winner can settle its rounding: the other candidate has its own risk)
+    if (DEFINED && FAST && !(margin > kSrMarginAtRisk))
+      sr_candidates<false, kErrNone, false>(v, words, c, none, margin);
     r.lo = c.code[0];
     r.hi = c.code[1];
   }
@@ -550,7 +553,10 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
 // values and both candidates alive across the common path cost the rowwise kernel three of its
 // eight waves per SIMD.  A block whose estimates were too close is rounded by the instruction once more (one
 // wave in some hundreds is in the case, and in a small launch all wait for it: with the rule in
-// software 1008 x 4096 took 8.1 us instead of 7.5), a risky one by the rule.
+// software 1008 x 4096 took 8.1 us instead of 7.5), a risky one by the rule.  Under kSR the first pass's margin
+// covers both candidates, whichever the second pass keeps; under kSRAfterRtnSelect it covers the
+// provisional winner alone, so there the second pass looks at its own (1008 x 4096, rowwise / both layouts: 7.33
+// / 19.3 us, with a second pass that always rounds by the rule 7.57 / 20.1).
 template <int ROUNDING, int SELECT, typename Words, typename Again>
 NV_DEV BlockResult quantize_block(const float (&v)[16], const Words &words,
                                   const ScaleConsts &k, const ScaleTable &tab, Again &&again) {

@@ -73,14 +73,16 @@ BLOCK_STEPS = (-64, -16, -4, -3, -2, -1, 0, 1, 2, 3, 4, 5, 16, 64)
 
 
 def block_crossings(n_trials, seed, tree, alpha, select=None, rounding=ref.RTN, uniforms=None,
-                    samples=48, elements=8):
+                    samples=48, elements=8, place=None):
     """The same for one block of sixteen values under the tensor scale alpha: yields
     (block, i, first_pattern, S6, S4); block[i] set to the patterns first_pattern + BLOCK_STEPS
     walks across a crossing of the two candidates' block errors (here one fp32 step of the
     element moves an error by about one last bit, so the crossing is a few steps wide).
     `select` None: squared errors; ref.SEL_46_MAE: sums of absolute errors.  With stochastic
     rounding, `uniforms(k)` gives the sixteen uniforms of the k-th block yielded (they belong
-    to its place in the caller's tensor); a failed search tries again for the same place."""
+    to its place in the caller's tensor); a failed search tries again for the same place.
+    `place(k, v, S6, S4)` may set one element of the k-th block first (not its maximum), which then stays,
+    and returns its index."""
     rng = np.random.default_rng(seed)
     yielded = 0
     for trial in range(n_trials):
@@ -89,6 +91,7 @@ def block_crossings(n_trials, seed, tree, alpha, select=None, rounding=ref.RTN, 
         b = float(np.abs(v).max())
         S6, S4 = ref.block_scale(b, alpha, 6.0), ref.block_scale(b, alpha, 4.0)
         u = None if uniforms is None else uniforms(yielded)
+        fixed = -1 if place is None else place(yielded, v, S6, S4)
 
         def at(i, pattern):
             w = v.copy()
@@ -102,7 +105,7 @@ def block_crossings(n_trials, seed, tree, alpha, select=None, rounding=ref.RTN, 
         found = None
         for i in rng.permutation(16)[:elements]:
             i = int(i)
-            if not 0.02 * b < abs(v[i]) < 0.6 * b:
+            if i == fixed or not 0.02 * b < abs(v[i]) < 0.6 * b:
                 continue
             prev = None
             for k in range(samples):

@@ -409,6 +409,71 @@ def test_stochastically_rounded_blocks_within_a_step_of_a_tie():
     assert np.array_equal(_np(out["codes_row"]), c_ref)
 
 
+def _near_ties_at_a_threshold(n, seed, alpha, index):
+    """n fp32 blocks whose two round-to-nearest candidates' errors cross within a few steps of one element, each with
+    another element where its uniform (that of flat index index(k, j) for element j of block k) sets the
+    threshold of the stochastic rounding under the scale to 4: the defined errors choose, and under the scale
+    that they choose in about a third of the blocks the conversion instruction may not answer as the rule."""
+    from tests._near_ties import block_crossings
+    from tests.test_oracle_order_transcriptions import _tree_of_halves
+    rng = np.random.default_rng(seed)
+
+    def place(k, v, S6, S4):
+        e = int(rng.integers(0, 16))
+        if abs(v[e]) == np.abs(v).max():
+            e = (e + 1) % 16
+        word = round(ref.sr_uniform(SR_SEED, index(k, e)) * 2.0 ** 24)
+        y = np.float32(max(word + int(rng.integers(-1, 4)), 0) * 2.0 ** -25)      # below 0.5
+        v[e] = np.copysign(y * (np.float32(ref.e4m3_decode(S4)) * np.float32(alpha)), v[e])
+        return e
+
+    blocks = []
+    for v, i, first, _, _ in block_crossings(40 * n, seed + 1, _tree_of_halves, alpha, samples=24, elements=4,
+                                             place=place):
+        w = v.copy()
+        w[i] = np.uint32(first + (-1, 0, 1, 2)[len(blocks) % 4]).view(np.float32)
+        blocks.append(w)
+        if len(blocks) == n:
+            return np.stack(blocks)
+    raise AssertionError(len(blocks))
+
+
+@pytest.mark.parametrize("layout", [B.ROWWISE, B.COLWISE, B.BOTH])
+def test_winner_rounded_at_its_threshold_after_a_near_tie(layout):
+    """Stochastic rounding of the winner of the round-to-nearest candidates, in blocks that the error estimates
+    cannot decide and whose winner has an element at its rounding threshold; codes, fake-quant and the
+    one-call form."""
+    alpha, lines, n = float(np.float32(1.0) / np.float32(1536.0)), 32, 512
+    per = n // lines
+    if layout == B.ROWWISE:               # block k: row k // 16, columns 16 (k % 16) ...
+        x = _near_ties_at_a_threshold(n, 4700, alpha, lambda k, j: (k // per) * 16 * per + 16 * (k % per) + j)
+        x = x.reshape(lines, 16 * per)
+    else:                                 # the same along the columns
+        x = _near_ties_at_a_threshold(n, 4702, alpha, lambda k, j: (16 * (k % per) + j) * lines + k // per)
+        x = np.ascontiguousarray(x.reshape(lines, 16 * per).T)
+    kw = dict(rounding=B.SR_AFTER_RTN_SELECT, sr_seed=SR_SEED)
+    sides = [l for l in (B.ROWWISE, B.COLWISE) if layout & l]
+    xd, ad = torch.from_numpy(x).cuda(), torch.tensor([alpha], dtype=torch.float32, device="cuda")
+    _log(f"near ties at a threshold: layout={layout} {x.shape}")
+    out = B.nvfp4_46_quantize(xd, ad, layout=layout, **kw)
+    for side in sides:
+        sfx = "row" if side == B.ROWWISE else "col"
+        c_ref, s_ref, f_ref = ref.quantize(x, alpha, layout=side, **kw)
+        if side == sides[-1]:             # (the side that the blocks are built for)
+            assert 0.25 < f_ref.mean() < 0.75
+        assert np.array_equal(_np(out[f"choice_{sfx}"]), f_ref)
+        assert np.array_equal(_np(out[f"scales_{sfx}"]), s_ref)
+        assert np.array_equal(_np(out[f"codes_{sfx}"]), c_ref)
+        fq = B.nvfp4_46_fake_quant(xd, ad, layout=side, **kw)
+        assert np.array_equal(_bits(fq), ref.fake_quant(x, alpha, layout=side, **kw))
+    both = B.nvfp4_46_scale_quantize(xd, _workspace(), layout=layout, **kw)
+    a = float(both["alpha"].item())
+    for side in sides:
+        sfx = "row" if side == B.ROWWISE else "col"
+        c_ref, s_ref, _ = ref.quantize(x, a, layout=side, **kw)
+        assert np.array_equal(_np(both[f"codes_{sfx}"]), c_ref) and np.array_equal(_np(both[f"scales_{sfx}"]), s_ref)
+
+
 def test_block2d_tiles_within_a_few_steps_of_a_tie():
     """Tiles whose two candidates' errors cross between two adjacent fp32 values of one element
     (tests/_near_ties.py), eighteen steps around each crossing, one tile each, under one common

@@ -216,3 +216,59 @@ def test_philox_and_hadamard_match_oracle():
         v = (rng.normal(0, 1, 16) * 2.0 ** rng.integers(-30, 30)).astype(np.float32)
         sw = int(rng.integers(0, 1 << 32))
         assert np.array_equal(hm.rht16(v, sw).view(np.uint32), ref.rht16(v, sw).view(np.uint32))
+
+
+def _uniform_at_threshold(y: float, d: int):
+    """The uniform d steps of 2^-24 from where the rounding of |y| < 1 turns (there the conversion
+    instruction, which compares two bits less, may answer differently); None outside [0, 1)."""
+    a = abs(float(y))
+    if not 0.0 < a < 1.0:
+        return None
+    k = int(np.floor(a * 2.0 ** 25)) - (1 << 24 if a >= 0.5 else 0) + d
+    return np.float32(k * 2.0 ** -24) if 0 <= k < 1 << 24 else None
+
+
+@pytest.mark.parametrize("rounding", [ref.SR, ref.SR_AFTER_RTN_SELECT])
+def test_near_ties_with_an_element_at_its_rounding_threshold(rounding):
+    """Blocks whose two candidates' errors are within a few fp32 steps of a tie, with one uniform within
+    four steps of the threshold that its element has under the scale to 4 or to 6.  The first pass
+    cannot decide them, and the scale that the defined errors choose may be the one under which the
+    instruction's answer is not the rule's."""
+    from tests._near_ties import block_crossings
+    from tests.test_oracle_order_transcriptions import _tree_of_halves
+    alpha = np.float32(1.0) / np.float32(1536.0)
+    rng = np.random.default_rng(4698)
+    base = rng.integers(0, 1 << 24, (4096, 16)).astype(np.float32) * np.float32(2.0 ** -24)
+    near = (dict(rounding=ref.SR, uniforms=lambda k: base[k], samples=24, elements=4)
+            if rounding == ref.SR else {})
+    blocks, us, ys = [], [], []
+    for k, (v, i, first, S6, S4) in enumerate(
+            block_crossings(3000 if near else 300, 4699, _tree_of_halves, float(alpha), **near)):
+        for step in (-3, -1, 0, 1, 2, 4):
+            w = v.copy()
+            w[i] = np.uint32(first + step).view(np.float32)
+            for S in (S6, S4):
+                y = w * (np.float32(1.0) / (np.float32(ref.e4m3_decode(S)) * alpha))
+                for e in rng.permutation(16)[:6]:
+                    u = base[k].copy()
+                    at = _uniform_at_threshold(y[e], int(rng.integers(-4, 3)))
+                    if e != i and at is not None:
+                        u[e] = at
+                        blocks.append(w)
+                        us.append(u)
+                        ys.append((y[e], at, S == S4))
+    v, u = np.stack(blocks), np.stack(us)
+    passes = hm.second_passes()
+    codes, scale, four = hm.quantize_blocks(v, float(alpha), rounding, ref.SEL_46_MSE, u)
+    assert hm.second_passes() - passes > 0.5 * len(v)
+    # how many have the element at risk under the scale that is chosen, and would come out wrong by the instruction
+    y, at, under4 = (np.array(a) for a in zip(*ys))
+    rule, fast = hm.e2m1_sr(y.astype(np.float32), at.astype(np.float32))
+    wrong = ((fast & 0x0F) != rule) & (under4 == (four == 1))
+    assert (wrong & (four == 1)).sum() > 100 and (wrong & (four == 0)).sum() > 100, (len(v), wrong.sum())
+    bad = 0
+    for n in range(len(v)):
+        want = ref.quantize_block(v[n], float(alpha), rounding, ref.SEL_46_MSE, u[n])
+        got = np.stack((codes[n] & 15, codes[n] >> 4), axis=1).reshape(16)
+        bad += not (np.array_equal(got, want["codes"]) and scale[n] == want["S"] and four[n] == want["four"])
+    assert bad == 0, (bad, len(v))
