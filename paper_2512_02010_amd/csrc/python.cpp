@@ -42,11 +42,12 @@ struct Failed {};          // a Python exception is set
   throw Failed{};
 }
 
-// ---- arguments, as ctypes takes them: integers wrap to their width
+// ---- arguments, as ctypes takes them: whatever is an integer by __index__ (NumPy's among them), wrapped to its width
 
 uint64_t word(PyObject *o) {
-  if (!PyLong_Check(o)) fail(PyExc_TypeError, "int expected");
-  return PyLong_AsUnsignedLongLongMask(o);
+  const uint64_t w = PyLong_AsUnsignedLongLongMask(o);
+  if (w == ~(uint64_t)0 && PyErr_Occurred()) throw Failed{};
+  return w;
 }
 float number(PyObject *o) {
   const double d = PyFloat_AsDouble(o);

@@ -1,5 +1,6 @@
 """The native side of the binding (csrc/python.cpp): what it refuses (CPU), and that outputs which it allocates
 itself hold what the same calls leave in outputs of a caller's allocator (GPU)."""
+import numpy as np
 import pytest
 import torch
 
@@ -25,6 +26,34 @@ def test_refusals_without_a_device():
     assert e.value.status == 2 and "nvfp4_46_dequantize: NVFP4_ERR_SHAPE" in str(e.value)
 
 
+class _Index:
+    def __init__(self, value):
+        self.value = value
+
+    def __index__(self):
+        return self.value
+
+
+@pytest.mark.parametrize("as_int", [np.int64, np.uint8, torch.tensor, _Index])
+def test_integers_of_other_types(as_int):
+    """Every integer argument may be anything with __index__, as NumPy's integers (a drawn seed) are; the calls end
+    at what is wrong with them afterwards: tensors that are on no device, a shape."""
+    x, one = torch.zeros((16, 16), dtype=torch.bfloat16), as_int(1)
+    for call in (lambda: B.nvfp4_46_tensor_scale(x, layout=one, rht=one, rht_seed=one, fp8_max=256, out=16),
+                 lambda: B.nvfp4_46_tensor_scale_ws(x, x, layout=one, rht=one, rht_seed=one, out=16),
+                 lambda: B.nvfp4_46_quantize(x, 16, layout=one, rounding=one, select=one, rht=one, sr_seed=one,
+                                             rht_seed=one, block2d=one),
+                 lambda: B.nvfp4_46_scale_quantize(x, None, layout=one, rounding=one, select=one, rht=one,
+                                                   sr_seed=one, rht_seed=one, block2d=one),
+                 lambda: B.nvfp4_46_fake_quant(x, 16, layout=one, rounding=one, select=one, rht=one, sr_seed=one,
+                                               rht_seed=one, block2d=one, out=16)):
+        with pytest.raises(AssertionError, match="device tensors"):
+            call()
+    with pytest.raises(B.Nvfp4Error) as e:
+        B.nvfp4_46_dequantize(16, 16, 16, one, one, layout=one, out=16, stream=0)
+    assert e.value.status == 2
+
+
 def _calls():
     g = torch.Generator(device="cuda")
     g.manual_seed(4670)
@@ -37,7 +66,7 @@ def _calls():
     for layout in (B.ROWWISE, B.COLWISE, B.BOTH):
         for choice in (False, True):
             yield lambda: B.nvfp4_46_quantize(x, alpha, layout=layout, want_choice=choice, rounding=B.SR,
-                                              sr_seed=(1 << 64) - 5)
+                                              sr_seed=np.uint64((1 << 64) - 5))
     yield lambda: B.nvfp4_46_quantize(w, alpha, layout=B.BOTH, block2d=1)
     yield lambda: B.nvfp4_46_scale_quantize(w, ws, layout=B.BOTH, block2d=1, want_choice=False)
     yield lambda: B.nvfp4_46_scale_quantize(x)
