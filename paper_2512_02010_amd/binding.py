@@ -122,8 +122,8 @@ def native():
         module = importlib.util.module_from_spec(importlib.util.spec_from_loader("nvfp4_46_python", loader))
         loader.exec_module(module)
         L = lib()
-        module.connect(Nvfp4Error, *(C.cast(getattr(L, "nvfp4_46_" + name), C.c_void_p).value
-                                     for name in NATIVE_ENTRY_POINTS))
+        module.connect(Nvfp4Error, _device_empty, *(C.cast(getattr(L, "nvfp4_46_" + name), C.c_void_p).value
+                                                    for name in NATIVE_ENTRY_POINTS))
         _native = module
     return _native
 

@@ -12,6 +12,8 @@
 
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Dtype.h>
+#include <torch/csrc/DynamicTypes.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -34,6 +36,7 @@ struct EntryPoints {
 };
 EntryPoints entry;
 PyObject *error_class;     // Nvfp4Error(status, name of the entry point)
+PyObject *empty;           // (shape, dtype, device) -> tensor
 
 struct Failed {};          // a Python exception is set
 
@@ -54,41 +57,6 @@ float number(PyObject *o) {
   if (d == -1.0 && PyErr_Occurred()) throw Failed{};
   return (float)d;
 }
-const at::Tensor &tensor(PyObject *o) {
-  if (!THPVariable_Check(o)) fail(PyExc_AttributeError, "tensor expected");
-  return THPVariable_Unpack(o);
-}
-// None, an address, or a contiguous device tensor
-void *pointer(PyObject *o) {
-  if (o == Py_None) return nullptr;
-  if (PyLong_Check(o)) return reinterpret_cast<void *>(PyLong_AsUnsignedLongLongMask(o));
-  const at::Tensor &t = tensor(o);
-  if (!t.is_cuda() || !t.is_contiguous())
-    fail(PyExc_AssertionError, "tensors must be contiguous device tensors");
-  return t.data_ptr();
-}
-// None: the current stream of the current device
-void *stream(PyObject *o) {
-  if (o == Py_None) return c10::hip::getCurrentHIPStream().stream();
-  return reinterpret_cast<void *>(word(o));
-}
-
-// Other threads of the interpreter run while this lives, also when an exception ends it.
-struct WithoutLock {
-  PyThreadState *const state = PyEval_SaveThread();
-  ~WithoutLock() { PyEval_RestoreThread(state); }
-};
-
-// (an allocation may wait for the device, so it is made without the interpreter's lock, as torch.empty does)
-PyObject *new_tensor(at::IntArrayRef shape, at::ScalarType type, const at::Tensor &like) {
-  at::Tensor t;
-  {
-    WithoutLock others;
-    t = at::empty(shape, at::TensorOptions().dtype(type).device(like.device()));
-  }
-  return THPVariable_Wrap(t);
-}
-
 // A reference that is given up unless it is released.
 struct Owned {
   PyObject *o;
@@ -103,23 +71,92 @@ struct Owned {
     return r;
   }
 };
-Owned given_or_new(PyObject *given, at::IntArrayRef shape, at::ScalarType type, const at::Tensor &like) {
+
+// A plain tensor is read directly; a subclass of its own mind, or any other object with a tensor's
+// attributes, is asked for them in Python.
+const at::Tensor *plain(PyObject *o) { return THPVariable_CheckExact(o) ? &THPVariable_Unpack(o) : nullptr; }
+bool truth(const Owned &v) {
+  const int t = PyObject_IsTrue(v.o);
+  if (t < 0) throw Failed{};
+  return t;
+}
+c10::SmallVector<int64_t, 4> shape_of(PyObject *o) {
+  if (const at::Tensor *t = plain(o)) return {t->sizes().begin(), t->sizes().end()};
+  const Owned attribute(PyObject_GetAttrString(o, "shape")), shape(PySequence_Tuple(attribute.o));
+  c10::SmallVector<int64_t, 4> sizes;
+  for (Py_ssize_t i = 0; i < PyTuple_GET_SIZE(shape.o); ++i) sizes.push_back((int64_t)word(PyTuple_GET_ITEM(shape.o, i)));
+  return sizes;
+}
+size_t numel(PyObject *o) {
+  if (const at::Tensor *t = plain(o)) return (size_t)t->numel();
+  return (size_t)word(Owned(PyObject_CallMethod(o, "numel", nullptr)).o);
+}
+// None, an address, or a contiguous device tensor
+void *pointer(PyObject *o) {
+  if (o == Py_None) return nullptr;
+  if (PyLong_Check(o)) return reinterpret_cast<void *>(PyLong_AsUnsignedLongLongMask(o));
+  const at::Tensor *t = plain(o);
+  if (t ? !t->is_cuda() || !t->is_contiguous()
+        : !truth(Owned(PyObject_GetAttrString(o, "is_cuda"))) ||
+              !truth(Owned(PyObject_CallMethod(o, "is_contiguous", nullptr))))
+    fail(PyExc_AssertionError, "tensors must be contiguous device tensors");
+  if (t) return t->data_ptr();
+  const Owned address(PyObject_CallMethod(o, "data_ptr", nullptr));
+  return address.o == Py_None ? nullptr : reinterpret_cast<void *>(word(address.o));
+}
+// None: the current stream of the current device
+void *stream(PyObject *o) {
+  if (o == Py_None) return c10::hip::getCurrentHIPStream().stream();
+  return reinterpret_cast<void *>(word(o));
+}
+
+// Other threads of the interpreter run while this lives, also when an exception ends it.
+struct WithoutLock {
+  PyThreadState *const state = PyEval_SaveThread();
+  ~WithoutLock() { PyEval_RestoreThread(state); }
+};
+
+// (an allocation may wait for the device, so it is made without the interpreter's lock, as torch.empty does)
+PyObject *new_tensor(at::IntArrayRef shape, at::ScalarType type, PyObject *like) {
+  if (const at::Tensor *l = plain(like)) {
+    at::Tensor t;
+    {
+      WithoutLock others;
+      t = at::empty(shape, at::TensorOptions().dtype(type).device(l->device()));
+    }
+    return THPVariable_Wrap(t);
+  }
+  const Owned device(PyObject_GetAttrString(like, "device")), sizes(PyTuple_New((Py_ssize_t)shape.size()));
+  for (size_t i = 0; i < shape.size(); ++i)
+    PyTuple_SET_ITEM(sizes.o, (Py_ssize_t)i, Owned(PyLong_FromLongLong(shape[i])).release());
+  return PyObject_CallFunctionObjArgs(empty, sizes.o, torch::getTHPDtype(type), device.o, nullptr);
+}
+
+Owned given_or_new(PyObject *given, at::IntArrayRef shape, at::ScalarType type, PyObject *like) {
   if (given == Py_None) return Owned(new_tensor(shape, type, like));
   Py_INCREF(given);
   return Owned(given);
 }
 
 // x [rows][cols], BF16 or fp32
-void set_shape(nvfp4_46_params &p, const at::Tensor &x) {
-  const bool f32 = x.scalar_type() == at::kFloat;
-  if (x.dim() != 2 || !(f32 || x.scalar_type() == at::kBFloat16))
+void set_shape(nvfp4_46_params &p, PyObject *x) {
+  const at::Tensor *t = plain(x);
+  const auto dims = t ? t->dim() : (int64_t)word(Owned(PyObject_CallMethod(x, "dim", nullptr)).o);
+  at::ScalarType type = t ? t->scalar_type() : at::kByte;
+  if (!t) {
+    const Owned dtype(PyObject_GetAttrString(x, "dtype"));
+    if (THPDtype_Check(dtype.o)) type = reinterpret_cast<THPDtype *>(dtype.o)->scalar_type;
+  }
+  if (dims != 2 || !(type == at::kFloat || type == at::kBFloat16))
     fail(PyExc_AssertionError, "x must be a matrix of BF16 or fp32");
-  p.rows = x.size(0);
-  p.cols = x.size(1);
-  p.x_dtype = f32 ? NVFP4_X_F32 : NVFP4_X_BF16;
+  const auto shape = shape_of(x);
+  if (shape.size() < 2) fail(PyExc_IndexError, "tuple index out of range");
+  p.rows = shape[0];
+  p.cols = shape[1];
+  p.x_dtype = type == at::kFloat ? NVFP4_X_F32 : NVFP4_X_BF16;
 }
 // layout, rounding, select, rht, sr_seed, rht_seed, fp8_max, block2d
-nvfp4_46_params params_of(const at::Tensor &x, PyObject *const *a) {
+nvfp4_46_params params_of(PyObject *x, PyObject *const *a) {
   nvfp4_46_params p{};
   set_shape(p, x);
   p.layout = (uint32_t)word(a[0]);
@@ -153,7 +190,7 @@ void run(const char *where, Call &&call) {
 const char *const kCodeNames[6] = {"codes_row", "scales_row", "choice_row", "codes_col", "scales_col", "choice_col"};
 
 // The dictionary of a quantizer's outputs: those that its layout has as new tensors, None for the others.
-PyObject *new_codes(const at::Tensor &x, const nvfp4_46_params &p, bool want_choice) {
+PyObject *new_codes(PyObject *x, const nvfp4_46_params &p, bool want_choice) {
   Owned d(PyDict_New());
   for (int i = 0; i < 6; ++i) {
     const bool col = i >= 3, codes = i % 3 == 0, choice = i % 3 == 2;
@@ -203,7 +240,7 @@ PyObject *guarded(PyObject *, PyObject *const *a, Py_ssize_t n) {
 // x, out, stream, then params
 PyObject *tensor_scale(PyObject *const *a, Py_ssize_t n) {
   expect(n, 11);
-  const at::Tensor &x = tensor(a[0]);
+  PyObject *const x = a[0];
   const nvfp4_46_params p = params_of(x, a + 3);
   Owned alpha = given_or_new(a[1], {1}, at::kFloat, x);
   void *const px = pointer(a[0]), *const s = stream(a[2]);
@@ -215,10 +252,10 @@ PyObject *tensor_scale(PyObject *const *a, Py_ssize_t n) {
 // x, workspace, out, stream, then params
 PyObject *tensor_scale_ws(PyObject *const *a, Py_ssize_t n) {
   expect(n, 12);
-  const at::Tensor &x = tensor(a[0]);
+  PyObject *const x = a[0];
   const nvfp4_46_params p = params_of(x, a + 4);
   Owned alpha = given_or_new(a[2], {1}, at::kFloat, x);
-  const size_t bytes = (size_t)tensor(a[1]).numel();
+  const size_t bytes = numel(a[1]);
   void *const px = pointer(a[0]), *const w = pointer(a[1]), *const s = stream(a[3]);
   float *const pa = static_cast<float *>(pointer(alpha.o));
   run("nvfp4_46_tensor_scale_ws", [&] { return entry.tensor_scale_ws(px, &p, pa, w, bytes, s); });
@@ -228,7 +265,7 @@ PyObject *tensor_scale_ws(PyObject *const *a, Py_ssize_t n) {
 // x, alpha, out, want_choice, stream, then params
 PyObject *quantize(PyObject *const *a, Py_ssize_t n) {
   expect(n, 13);
-  const at::Tensor &x = tensor(a[0]);
+  PyObject *const x = a[0];
   const nvfp4_46_params p = params_of(x, a + 5);
   const int choice = PyObject_IsTrue(a[3]);
   if (choice < 0) return nullptr;
@@ -243,7 +280,7 @@ PyObject *quantize(PyObject *const *a, Py_ssize_t n) {
 // x, workspace or None, alpha, out, want_choice, stream, then params; alpha joins the dictionary
 PyObject *scale_quantize(PyObject *const *a, Py_ssize_t n) {
   expect(n, 14);
-  const at::Tensor &x = tensor(a[0]);
+  PyObject *const x = a[0];
   const nvfp4_46_params p = params_of(x, a + 6);
   const int choice = PyObject_IsTrue(a[4]);
   if (choice < 0) return nullptr;
@@ -251,7 +288,7 @@ PyObject *scale_quantize(PyObject *const *a, Py_ssize_t n) {
   Owned codes(a[3] == Py_None ? new_codes(x, p, choice) : Py_NewRef(a[3]));
   const CodePointers c(codes.o);
   void *const px = pointer(a[0]), *const w = pointer(a[1]), *const s = stream(a[5]);
-  const size_t bytes = w ? (size_t)tensor(a[1]).numel() : 0;
+  const size_t bytes = a[1] == Py_None ? 0 : numel(a[1]);
   float *const pa = static_cast<float *>(pointer(alpha.o));
   run("nvfp4_46_scale_quantize", [&] {
     return entry.scale_quantize(px, &p, pa, w, bytes, c.p[0], c.p[1], c.p[3], c.p[4], c.p[2], c.p[5], s);
@@ -265,7 +302,7 @@ PyObject *dequantize(PyObject *const *a, Py_ssize_t n) {
   expect(n, 8);
   const int64_t rows = (int64_t)word(a[3]), cols = (int64_t)word(a[4]);
   const uint32_t layout = (uint32_t)word(a[5]);
-  Owned out = a[6] == Py_None ? Owned(new_tensor({rows, cols}, at::kBFloat16, tensor(a[0])))
+  Owned out = a[6] == Py_None ? Owned(new_tensor({rows, cols}, at::kBFloat16, a[0]))
                               : Owned(Py_NewRef(a[6]));
   void *const c = pointer(a[0]), *const sc = pointer(a[1]), *const o = pointer(out.o), *const s = stream(a[7]);
   const float *const pa = static_cast<const float *>(pointer(a[2]));
@@ -276,7 +313,7 @@ PyObject *dequantize(PyObject *const *a, Py_ssize_t n) {
 // x, alpha, out, stream, then params
 PyObject *fake_quant(PyObject *const *a, Py_ssize_t n) {
   expect(n, 12);
-  const at::Tensor &x = tensor(a[0]);
+  PyObject *const x = a[0];
   const nvfp4_46_params p = params_of(x, a + 4);
   Owned out = given_or_new(a[2], {p.rows, p.cols}, at::kBFloat16, x);
   void *const px = pointer(a[0]), *const o = pointer(out.o), *const s = stream(a[3]);
@@ -288,17 +325,17 @@ PyObject *fake_quant(PyObject *const *a, Py_ssize_t n) {
 // codes_a, scales_a, alpha_a, codes_b, scales_b, alpha_b, out_dtype, out, stream, flags
 PyObject *gemm(PyObject *const *a, Py_ssize_t n) {
   expect(n, 10);
-  const at::Tensor &ca = tensor(a[0]), &sa = tensor(a[1]), &cb = tensor(a[3]), &sb = tensor(a[4]);
+  const auto ca = shape_of(a[0]), sa = shape_of(a[1]), cb = shape_of(a[3]), sb = shape_of(a[4]);
   const uint32_t out_dtype = (uint32_t)word(a[6]), flags = (uint32_t)word(a[9]);
-  if (ca.dim() < 2 || cb.dim() < 2) fail(PyExc_IndexError, "tuple index out of range");
-  const int64_t M = ca.size(0), N = cb.size(0), K = ca.size(1) * 2;
-  auto is = [](const at::Tensor &t, int64_t rows, int64_t cols) {
-    return t.dim() == 2 && t.size(0) == rows && t.size(1) == cols;
+  if (ca.size() < 2 || cb.size() < 2) fail(PyExc_IndexError, "tuple index out of range");
+  const int64_t M = ca[0], N = cb[0], K = ca[1] * 2;
+  auto is = [](const auto &shape, int64_t rows, int64_t cols) {
+    return shape.size() == 2 && shape[0] == rows && shape[1] == cols;
   };
-  if (cb.size(1) * 2 != K || !is(sa, flags & NVFP4_GEMM_A_TILE_SCALES ? M / 16 : M, K / 16) ||
+  if (cb[1] * 2 != K || !is(sa, flags & NVFP4_GEMM_A_TILE_SCALES ? M / 16 : M, K / 16) ||
       !is(sb, flags & NVFP4_GEMM_B_TILE_SCALES ? N / 16 : N, K / 16))
     fail(PyExc_AssertionError, "operands that do not fit together");
-  Owned out = given_or_new(a[7], {M, N}, out_dtype == NVFP4_OUT_F32 ? at::kFloat : at::kBFloat16, ca);
+  Owned out = given_or_new(a[7], {M, N}, out_dtype == NVFP4_OUT_F32 ? at::kFloat : at::kBFloat16, a[0]);
   void *const pca = pointer(a[0]), *const psa = pointer(a[1]), *const pcb = pointer(a[3]), *const psb = pointer(a[4]);
   const float *const paa = static_cast<const float *>(pointer(a[2])), *const pab = static_cast<const float *>(pointer(a[5]));
   void *const o = pointer(out.o), *const s = stream(a[8]);
@@ -306,14 +343,16 @@ PyObject *gemm(PyObject *const *a, Py_ssize_t n) {
   return out.release();
 }
 
-// The exception class, then the addresses of the entry points, one integer each.
+// The exception class, torch.empty as (shape, dtype, device), then the addresses of the entry points, one integer
+// each.
 PyObject *connect(PyObject *const *a, Py_ssize_t n) {
   constexpr Py_ssize_t kEntries = sizeof(EntryPoints) / sizeof(void *);
-  expect(n, 1 + kEntries);
+  expect(n, 2 + kEntries);
   void *to[kEntries];
-  for (Py_ssize_t i = 0; i < kEntries; ++i) to[i] = reinterpret_cast<void *>(word(a[1 + i]));
+  for (Py_ssize_t i = 0; i < kEntries; ++i) to[i] = reinterpret_cast<void *>(word(a[2 + i]));
   std::memcpy(&entry, to, sizeof entry);
   error_class = Py_NewRef(a[0]);
+  empty = Py_NewRef(a[1]);
   Py_RETURN_NONE;
 }
 

@@ -1,5 +1,7 @@
 """The native side of the binding (csrc/python.cpp): what it refuses (CPU), and that outputs which it allocates
 itself hold what the same calls leave in outputs of a caller's allocator (GPU)."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -54,6 +56,81 @@ def test_integers_of_other_types(as_int):
     assert e.value.status == 2
 
 
+class _Like:
+    """Not a tensor, but with a tensor's attributes (on a pretended device, if it is on none)."""
+    is_cuda = True
+
+    def __init__(self, t):
+        self.t = t
+
+    def __getattr__(self, name):
+        return getattr(self.t, name)
+
+
+class _Mind(torch.Tensor):
+    """A subclass that answers for itself where its memory is."""
+    is_cuda = True
+
+    def data_ptr(self):
+        return super().data_ptr() + 64
+
+
+@pytest.fixture
+def calls_seen():
+    """The module connected to entry points that only note their name, arguments and what `watch` says at that time."""
+    module, seen, kept = B.native(), [], []
+    watch = {"now": lambda: None}
+
+    def noting(name, argtypes):
+        def note(*a):
+            seen.append((name, a, watch["now"]()))
+            return 0
+        kept.append(C.CFUNCTYPE(C.c_int, *argtypes)(note))
+        return C.cast(kept[-1], C.c_void_p).value
+
+    L = B.lib()
+    real = [getattr(L, "nvfp4_46_" + name) for name in B.NATIVE_ENTRY_POINTS]
+    types = [[C.c_void_p if t is C.POINTER(B.Params) else t for t in f.argtypes] for f in real]
+    module.connect(B.Nvfp4Error, B._device_empty, *map(noting, B.NATIVE_ENTRY_POINTS, types))
+    try:
+        yield seen, watch
+    finally:
+        module.connect(B.Nvfp4Error, B._device_empty, *(C.cast(f, C.c_void_p).value for f in real))
+
+
+@pytest.mark.parametrize("like", [_Like, lambda t: t.as_subclass(_Mind)])
+def test_objects_with_a_tensors_attributes(like, calls_seen):
+    seen, _ = calls_seen
+    t = [torch.zeros(s, dtype=d) for s, d in (((32, 48), torch.bfloat16), ((1,), torch.float32), ((32, 24), torch.uint8),
+                                              ((32, 3), torch.uint8), ((64,), torch.uint8), ((32, 48), torch.float32))]
+    x, alpha, codes, scales, ws, out = (like(v) for v in t)
+    px, pa, pc, ps, pw, po = (v.data_ptr() for v in (x, alpha, codes, scales, ws, out))
+    assert (px == t[0].data_ptr()) == (like is _Like)
+    full = dict(codes_row=codes, scales_row=scales, choice_row=None, codes_col=None, scales_col=None, choice_col=None)
+    assert B.nvfp4_46_tensor_scale(x, out=alpha, stream=0) is alpha
+    assert B.nvfp4_46_tensor_scale_ws(x, ws, out=alpha, stream=0) is alpha
+    assert B.nvfp4_46_quantize(x, alpha, out=full, stream=0) is full
+    assert B.nvfp4_46_dequantize(codes, scales, alpha, 32, 48, out=out, stream=0) is out
+    assert B.nvfp4_46_fake_quant(x, alpha, out=out, stream=0) is out
+    # (as operands 32 x 48 of a product of that contraction length: the scales' shape is right, the library is not asked)
+    assert B.nvfp4_46_gemm(codes, scales, alpha, codes, scales, alpha, out=out, stream=0) is out
+    assert [name for name, _, _ in seen] == ["tensor_scale", "tensor_scale_ws", "quantize", "dequantize", "fake_quant", "gemm"]
+    a = [a for _, a, _ in seen]
+    assert (a[0][0], a[0][2]) == (px, pa)
+    assert (a[1][0], a[1][2], a[1][3], a[1][4]) == (px, pa, pw, 64)
+    assert (a[2][0], a[2][2], a[2][3], a[2][4], a[2][5]) == (px, pa, pc, ps, None)
+    assert a[3][:7] == (pc, ps, pa, 32, 48, 1, po)
+    assert (a[4][0], a[4][2], a[4][3]) == (px, pa, po)
+    assert a[5][:11] == (pc, ps, pa, pc, ps, pa, 32, 32, 48, 0, 0) and a[5][11] == po
+    for call in (lambda: B.nvfp4_46_tensor_scale(like(t[0][0])), lambda: B.nvfp4_46_tensor_scale(like(t[2])),
+                 lambda: B.nvfp4_46_quantize(like(t[0].t()), alpha, out=full),
+                 lambda: B.nvfp4_46_gemm(codes, codes, alpha, codes, scales, alpha, out=out)):
+        with pytest.raises(AssertionError):
+            call()
+    with pytest.raises(AttributeError):
+        B.nvfp4_46_tensor_scale_ws(x, 16, out=alpha)
+
+
 def _calls():
     g = torch.Generator(device="cuda")
     g.manual_seed(4670)
@@ -77,6 +154,11 @@ def _calls():
         yield lambda: B.nvfp4_46_gemm(q["codes_row"], q["scales_row"], alpha, q["codes_row"], q["scales_row"],
                                       alpha, out_dtype=out)
     yield lambda: L.fprop(x, L.quantize_weight(w, workspace=ws), workspace=ws)
+    # (outputs like an object that is only like a tensor)
+    yield lambda: B.nvfp4_46_tensor_scale(_Like(x))
+    yield lambda: B.nvfp4_46_quantize(_Like(x), _Like(alpha), layout=B.BOTH)
+    yield lambda: B.nvfp4_46_fake_quant(_Like(x), _Like(alpha))
+    yield lambda: B.nvfp4_46_gemm(*(_Like(v) for v in (q["codes_row"], q["scales_row"], alpha) * 2))
 
 
 @pytest.mark.gpu
