@@ -205,18 +205,28 @@ PyObject *new_codes(PyObject *x, const nvfp4_46_params &p, bool want_choice) {
   }
   return d.release();
 }
+// Their addresses; what a mapping returned is held as long, for nothing else may (an allocator would hand the
+// memory of an output that is gone before its launch to the next).
 struct CodePointers {
   void *p[6];
+  PyObject *held[6] = {};
   explicit CodePointers(PyObject *codes) {
-    for (int i = 0; i < 6; ++i) {
-      PyObject *key = PyUnicode_FromString(kCodeNames[i]);
-      if (!key) throw Failed{};
-      PyObject *v = PyObject_GetItem(codes, key);         // (any mapping)
-      Py_DECREF(key);
-      if (!v) throw Failed{};
-      Owned held(v);
-      p[i] = pointer(v);
+    try {
+      for (int i = 0; i < 6; ++i) {
+        const Owned key(PyUnicode_FromString(kCodeNames[i]));
+        Owned v(PyObject_GetItem(codes, key.o));          // (any mapping)
+        p[i] = pointer(v.o);
+        held[i] = v.release();
+      }
+    } catch (...) {
+      let_go();
+      throw;
     }
+  }
+  CodePointers(const CodePointers &) = delete;
+  ~CodePointers() { let_go(); }
+  void let_go() {
+    for (PyObject *&v : held) Py_CLEAR(v);
   }
 };
 

@@ -131,6 +131,33 @@ def test_objects_with_a_tensors_attributes(like, calls_seen):
         B.nvfp4_46_tensor_scale_ws(x, 16, out=alpha)
 
 
+def test_outputs_that_a_mapping_makes_live_until_the_launch(calls_seen):
+    """A mapping may make what it returns; nothing else holds it while the call runs without the lock."""
+    seen, watch = calls_seen
+    gone = []
+
+    class Made(_Like):
+        def __del__(self):
+            gone.append(self)
+
+    class Mapping:
+        def __init__(self):
+            self.alpha = None
+
+        def __getitem__(self, name):
+            return Made(torch.zeros((16, 8), dtype=torch.uint8))
+
+        def __setitem__(self, name, value):
+            self.alpha = value
+
+    watch["now"] = lambda: len(gone)
+    x, alpha = _Like(torch.zeros((16, 16), dtype=torch.bfloat16)), _Like(torch.zeros(1))
+    B.nvfp4_46_quantize(x, alpha, out=Mapping(), stream=0)
+    B.native().scale_quantize(x, None, alpha, Mapping(), True, 0, 1, 0, 0, 0, 0, 0, 256.0, 0)
+    assert [now for _, _, now in seen] == [0, 6] and len(gone) == 12
+    assert len(set(a for a in seen[0][1][3:9])) == 6       # (six outputs, none in another's memory)
+
+
 def _calls():
     g = torch.Generator(device="cuda")
     g.manual_seed(4670)
