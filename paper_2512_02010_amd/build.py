@@ -70,25 +70,26 @@ def build(out: Path | None = None, defines: dict | None = None, extra: list | No
     return out
 
 
-def build_python() -> Path:
-    """Compile csrc/python.cpp against the installed torch and interpreter."""
+def build_python(out: Path | None = None) -> Path:
+    """Compile csrc/python.cpp against the installed torch and interpreter: with the host compiler, or, where there
+    is none, with the compiler that the library takes anyway."""
     import sysconfig
 
     import torch
     home = Path(torch.__file__).resolve().parent
+    out = Path(out) if out else PYTHON_SO
     cxx = os.environ.get("CXX") or shutil.which("g++") or shutil.which("c++")
-    if not cxx:
-        raise RuntimeError("no host C++ compiler found")
+    host = ["-x", "c++"] if not cxx else []
     include = [home / "include", home / "include" / "torch" / "csrc" / "api" / "include",
                Path(hipcc()).resolve().parent.parent / "include", sysconfig.get_paths()["include"]]
-    tmp = PYTHON_SO.with_suffix(f".tmp{os.getpid()}.so")
-    subprocess.run([cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+    tmp = out.with_suffix(f".tmp{os.getpid()}.so")
+    subprocess.run([cxx or hipcc(), *host, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
                     f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", f"-I{ROOT / 'include'}",
                     *(f for d in include for f in ("-isystem", str(d))), str(PKG / "csrc" / "python.cpp"),
                     "-o", str(tmp), f"-L{home / 'lib'}", "-ltorch_python", "-ltorch", "-lc10", "-lc10_hip"],
                    check=True)
-    os.replace(tmp, PYTHON_SO)
-    return PYTHON_SO
+    os.replace(tmp, out)
+    return out
 
 
 if __name__ == "__main__":

@@ -1,12 +1,16 @@
 """The native side of the binding (csrc/python.cpp): what it refuses (CPU), and that outputs which it allocates
 itself hold what the same calls leave in outputs of a caller's allocator (GPU)."""
 import ctypes as C
+import importlib.machinery
+import importlib.util
+import shutil
 
 import numpy as np
 import pytest
 import torch
 
 from paper_2512_02010_amd import binding as B
+from paper_2512_02010_amd import build
 from paper_2512_02010_amd import linear as L
 
 
@@ -26,6 +30,18 @@ def test_refusals_without_a_device():
     with pytest.raises(B.Nvfp4Error) as e:
         B.nvfp4_46_dequantize(16, 16, 16, 16, 17, out=16, stream=0)
     assert e.value.status == 2 and "nvfp4_46_dequantize: NVFP4_ERR_SHAPE" in str(e.value)
+
+
+def test_module_builds_without_a_host_compiler(monkeypatch, tmp_path):
+    """Whoever can compile the library can compile the module."""
+    which = shutil.which
+    monkeypatch.delenv("CXX", raising=False)
+    monkeypatch.setattr(shutil, "which", lambda name, *a, **k: None if name in ("g++", "c++") else which(name, *a, **k))
+    so = build.build_python(tmp_path / "nvfp4_46_python.so")
+    loader = importlib.machinery.ExtensionFileLoader("nvfp4_46_python", str(so))
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("nvfp4_46_python", loader))
+    loader.exec_module(module)
+    assert all(callable(getattr(module, name)) for name in B.NATIVE_ENTRY_POINTS)
 
 
 class _Index:
