@@ -51,6 +51,8 @@ SIZES = [("dma", *size) for size in SIZES] + [
     ("dma256x128", 961, 5248, 512, "b"), ("dma256x128", 1000, 5227, 544, ""), ("dma256x128", 1000, 5232, 640, ""),
     ("dma256x128", 1001, 5230, 672, ""), ("dma256x128", 1000, 5236, 896, ""), ("dma256x128", 1008, 5232, 1184, "ab"),
     ("dma256x128", 130, 32768, 128, ""),
+    # ... and every remainder of N by the 8 (BF16) or 4 (fp32) columns that a lane stores
+    ("dma256x128", 1000, 5226, 64, ""), ("dma256x128", 992, 5229, 96, ""), ("dma256x128", 1000, 5240, 96, ""),
     # 128 x 128 (four stages of 256, each wave a quarter of them)
     ("dma128", 1000, 3000, 1024, ""), ("dma128", 1024, 3071, 1056, ""), ("dma128", 897, 3072, 1120, ""),
     ("dma128", 992, 2945, 1152, "a"), ("dma128", 1001, 3056, 1248, "b"), ("dma128", 1000, 3001, 1280, ""),
