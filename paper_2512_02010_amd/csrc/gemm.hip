@@ -20,8 +20,9 @@
 // the same for A and for B, which is all the sum needs.
 //
 // Two kernels share this plan: k_gemm (the workgroup stages chunks through registers into
-// shared LDS buffers; only for K > 2^24, beyond the others' 32-bit offsets) and k_gemm_dma (the workgroup
-// fills a ring of LDS stages with asynchronous global -> LDS copies).
+// shared LDS buffers; for K > 2^24, beyond the others' 32-bit offsets, and a ragged K where C is too long for a
+// launch of smaller tiles) and k_gemm_dma (the workgroup fills a ring of LDS stages with asynchronous
+// global -> LDS copies).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -1438,7 +1439,7 @@ extern "C" int nvfp4_46_gemm(const void *codes_a, const void *scales_a, const fl
                    (flags & NVFP4_GEMM_A_TILE_SCALES) ? 4u : 0u,
                    (flags & NVFP4_GEMM_B_TILE_SCALES) ? 4u : 0u, out_dtype == NVFP4_OUT_F32,
                    static_cast<hipStream_t>(stream)};
-  switch (gemm_kernel(M, N, K)) {
+  switch (choose_gemm(M, N, K, a.f32)) {
     case kGemmStaged:
       return (K % GK) == 0 ? (a.f32 ? run_gemm_staged<true, true>(a) : run_gemm_staged<true, false>(a))
                            : (a.f32 ? run_gemm_staged<false, true>(a) : run_gemm_staged<false, false>(a));

@@ -44,7 +44,7 @@ using Tile64x32 = TileShape<2, 1, 1, 1, 4, 1, 2>;      // 64 x 32, 4 waves
 using Tile64 = TileShape<2, 2, 1, 1, 4, 1, 2>;         // 64 x 64, 4 waves; three workgroups per CU
 using Tile64Long = TileShape<2, 2, 1, 1, 8, 1, 2>;     // 64 x 64, 8 waves
 using Tile128 = TileShape<2, 2, 2, 2, 4, 1, 2>;        // 128 x 128, 16 waves
-using Tile256x128 = TileShape<4, 2, 2, 2, 2, 1, 4>;    // 256 x 128, 8 waves (Dma256x128 takes all that it would)
+using Tile256x128 = TileShape<4, 2, 2, 2, 2, 1, 4>;    // 256 x 128, 8 waves
 
 // k_gemm_dma's shapes (described at the kernel): four waves of WM x WN instruction tiles, SM x SN of them over the
 // tile of C and KS along the contraction axis, each taking HPW pieces of 64 steps of a chunk; NST stages.
@@ -102,10 +102,15 @@ template <typename S>
 inline bool fills_chip(int64_t M, int64_t N, double turns) {
   return turns_filled(M, N, S::BM, S::BN) >= turns && tiles_covered(M, N, S::BM, S::BN) >= 0.8;
 }
+// Both in one figure: the share of the chip that is busy with what exists.
+template <typename S>
+inline double chip_filled(int64_t M, int64_t N) {
+  return turns_filled(M, N, S::BM, S::BN) * tiles_covered(M, N, S::BM, S::BN);
+}
 
 // Which kernel: times in us, BF16 out, on one card, M x N x K; operands as the calls before left
-// them (all in the memory-side cache), or B from memory where it says so.
-inline GemmKernel fastest_gemm(int64_t M, int64_t N, int64_t K) {
+// them (all in the memory-side cache), or B from memory where it says so.  `f32`: C is fp32, not BF16.
+inline GemmKernel fastest_gemm(int64_t M, int64_t N, int64_t K, bool f32) {
   if (K > ((int64_t)1 << 24)) return kGemmStaged;       // 32-bit lane offsets of the others' copies
 
   // Few rows of A against a large weight: the kernels that stream B, one workgroup per 32 columns.
@@ -122,16 +127,30 @@ inline GemmKernel fastest_gemm(int64_t M, int64_t N, int64_t K) {
   const bool stream_64 = t32 > kCus || (M <= 48 && N * K > ((int64_t)1 << 25));
   if ((K % SK) == 0 && (M <= 32 || (M <= 64 && t64 <= kCus && stream_64))) return kGemmSkinny;
 
-  // The largest tiles (the fewest expansions and copies per product) that leave little of the chip
-  // idle.  256 x 256 tiles of the copy-based kernel from 62 %, padding counted as idle (2816 x 4096 x
-  // 4096, 176 tiles: 96, in 64 x 64 tiles 111; but 4352 x 4096 x 2048, 272 tiles: 106 / 90, and 5834 x
-  // 1600 x 1024, 161 tiles of which 11 % is padding: 34 / 28); 256 x 128 tiles from 80 % (2048 x 4096 x
-  // 4096: 80 in 256 x 256, 65; 2048 x 3072 x 4096, 75 %: 59, in 64 x 64 tiles 55); 128 x 128 from 87 %
-  // (1000 x 4096 x 4096: 76 in 256 x 256, 35, in 64 x 64 38; 2048 x 3072 x 4096, 75 %: 63; B from memory,
-  // 65 / 128 x 28672 x 8192: 116 / 117 in 256 x 128, 66 / 68, in 64 x 64 74 / 76); the last two only where
-  // they cover 80 % of it (192 x 28672 x 8192, 75 %: 120 in 256 x 128, 107 in 64 x 64; 1340 x 4464 x 5504,
-  // 87 %: 76 / 83).
-  if ((K % GK) == 0 && turns_filled(M, N, GT, GT) * tiles_covered(M, N, GT, GT) >= 0.62) return kGemmDma;
+  // The largest tiles (the fewest expansions and copies per product) that leave little of the chip idle, padding
+  // counted as idle.  k_gemm_dma's three shapes (the shape / what would run else):
+  //   256 x 256 from 62 %: 6144 x 6400 x 1056 (78 %) 112 / 114, 2816 x 4096 x 4064 (69 %) 88 / 108, x 32 13.2 / 19.8,
+  //   8192 x 8192 x 96 44 / 69; 3000 x 3000 x 1024 (56 %) 28.0 / 27.4;
+  //   256 x 128 from 62 % of one turn, 72 % of several: 2048 x 4096 x 4096 58 / 69.5, 1536 x 4096 x 4096 (75 %) 49 / 62,
+  //   6798 x 880 x 4160 (73 %) 54 / 76, 192 x 28672 x 8192 (66 %) 96 / 103, 996 x 5232 x 704 (64 %) 17.7 / 19.5; 3388 x
+  //   1408 x 2304 (60 %) 29.7 / 29.1, 4798 x 912 x 768 (59 %) 16.5 / 16.2; three turns: 8324 x 1925 x 256 (66 %) 22 % and
+  //   6496 x 2681 x 256 (70 %) 19 % longer than in 64 x 64;
+  //   128 x 128 from 70 % of one turn and a K whose quarters outlast their sum's way through LDS: 1000 x 4096 x 4096
+  //   32.7 / 38.4, 768 x 4096 x 4096 (75 %) 28.3 / 30.2, 128 x 28672 x 8192 (87 %) 54 / 65; 575 x 4526 x 4352 (63 %)
+  //   35.3 / 31.8; 1000 x 4096 x 1024 13.9 / 14.5 but x 256 10.2 / 9.5; two turns and more 3000 x 3000 x 1024 35 / 27.
+  // They store 16 bytes per lane, which takes a quarter longer (3 to 5 us of one turn) where the lines of C do not
+  // begin at multiples of 16 bytes.  The smaller two shapes are then ahead of k_gemm_tile, which stores column by
+  // column, only along a longer K (2048 x 4095: K = 32 14.0 / 11.7, 256 16.3 / 13.0, 640 21.4 / 19.5; 1654 x 4428 x 128
+  // 17 % longer; 128 x 128: 4055 x 738 x 1536, fp32, 19 % longer).
+  const bool skewed = N * (f32 ? 4 : 2) % 16 != 0, one_turn = tiles_of<Dma256x128>(M, N) <= kCus;
+  if (chip_filled<Dma256>(M, N) >= 0.62) return kGemmDma;
+  if (chip_filled<Dma256x128>(M, N) >= (one_turn ? 0.62 : 0.72) && !(one_turn && skewed && K < 1024))
+    return kGemmDma256x128;
+  if (K >= (skewed ? 2048 : 1024) && tiles_of<Dma128>(M, N) <= kCus && chip_filled<Dma128>(M, N) >= 0.7)
+    return kGemmDma128;
+  // ... and k_gemm_tile's: 256 x 128 from 80 % (2048 x 3072 x 4096, 75 %: 59, in 64 x 64 tiles 55), 128 x 128 from 87 %
+  // (1000 x 4096 x 4096: 35, in 64 x 64 38; 2048 x 3072 x 4096, 75 %: 63), both only where they cover 80 % of it (192 x
+  // 28672 x 8192, 75 %: 120 in 256 x 128, 107 in 64 x 64; 1340 x 4464 x 5504, 87 %: 76 / 83).
   if (fills_chip<Tile256x128>(M, N, 0.8)) return kGemmTile256x128;
   if (fills_chip<Tile128>(M, N, 0.87)) return kGemmTile128;
   // Small products: the smallest tiles that are at most one per compute unit (64 x 1024 x 4096:
@@ -171,32 +190,9 @@ inline int64_t lanes_of(GemmKernel kernel, int64_t M, int64_t N) {
 
 // A launch holds fewer than 2^32 lanes: where one row or column of C is that long, the kernels of the
 // fewest lanes per element take it.
-inline GemmKernel choose_gemm(int64_t M, int64_t N, int64_t K) {
-  const GemmKernel fastest = fastest_gemm(M, N, K);
+inline GemmKernel choose_gemm(int64_t M, int64_t N, int64_t K, bool f32) {
+  const GemmKernel fastest = fastest_gemm(M, N, K, f32);
   if (lanes_of(fastest, M, N) >> 32 == 0) return fastest;
   return (K % GK) == 0 && K <= ((int64_t)1 << 24) ? kGemmDma : kGemmStaged;
-}
-
-// The kernel that a product runs: choose_gemm()'s, or where the chip is filled well enough one of k_gemm_dma's
-// three shapes, which take any K % 32.  BF16 out, us, the shape / what choose_gemm() gives:
-//   256 x 256 from 62 % of the chip, padding counted as idle: 6144 x 6400 x 1056 (78 %) 112 / 114, 2816 x 4096 x 4064
-//   (69 %) 88 / 108; 3000 x 3000 x 1024 (56 %) 28.0 / 27.4;
-//   256 x 128 from 62 %: 2048 x 4096 x 4096 58 / 69.5, 1536 x 4096 x 4096 (75 %) 49 / 62, 6798 x 880 x 4160 (73 %)
-//   54 / 76, 192 x 28672 x 8192 (66 %) 96 / 103, 996 x 5232 x 704 (64 %) 17.7 / 19.5; 3388 x 1408 x 2304 (60 %)
-//   29.7 / 29.1, 4798 x 912 x 768 (59 %) 16.5 / 16.2;
-//   128 x 128 from 70 % of one turn and a K whose quarters outlast their sum's way through LDS: 1000 x 4096 x 4096
-//   32.7 / 38.4, 768 x 4096 x 4096 (75 %) 28.3 / 30.2, 128 x 28672 x 8192 (87 %) 54 / 65; 575 x 4526 x 4352 (63 %)
-//   35.3 / 31.8; 1000 x 4096 x 1024 13.9 / 14.5 but x 256 10.2 / 9.5; two turns and more 3000 x 3000 x 1024 35 / 27.
-template <typename S>
-inline double chip_filled(int64_t M, int64_t N) {
-  return turns_filled(M, N, S::BM, S::BN) * tiles_covered(M, N, S::BM, S::BN);
-}
-inline GemmKernel gemm_kernel(int64_t M, int64_t N, int64_t K) {
-  if (M > 64 && N > 64 && K <= ((int64_t)1 << 24)) {
-    if (chip_filled<Dma256>(M, N) >= 0.62 && lanes_of(kGemmDma, M, N) >> 32 == 0) return kGemmDma;
-    if (chip_filled<Dma256x128>(M, N) >= 0.62 && lanes_of(kGemmDma256x128, M, N) >> 32 == 0) return kGemmDma256x128;
-    if (K >= 1024 && tiles_of<Dma128>(M, N) <= kCus && chip_filled<Dma128>(M, N) >= 0.7) return kGemmDma128;
-  }
-  return choose_gemm(M, N, K);
 }
 }  // namespace nvfp4_46

@@ -76,9 +76,7 @@ def lib() -> C.CDLL:
         L.hm_rht16.restype = None
         L.hm_rht16.argtypes = [f32p, C.c_uint32]
         L.hm_choose_gemm.restype = C.c_int
-        L.hm_choose_gemm.argtypes = [C.c_int64, C.c_int64, C.c_int64]
-        L.hm_gemm_kernel.restype = C.c_int
-        L.hm_gemm_kernel.argtypes = [C.c_int64, C.c_int64, C.c_int64]
+        L.hm_choose_gemm.argtypes = [C.c_int64, C.c_int64, C.c_int64, C.c_int]
         L.hm_gemm_lanes.restype = C.c_int64
         L.hm_gemm_lanes.argtypes = [C.c_int, C.c_int64, C.c_int64]
         L.hm_scale_in_one_workgroup.restype = C.c_int
@@ -165,15 +163,9 @@ def rht16(v, sign_word: int) -> np.ndarray:
     return a
 
 
-def choose_gemm(M: int, N: int, K: int) -> str:
-    """Name of the kernel that an M x N x K product would run if 256 x 256 tiles were for whole chunks of 128
-    contraction steps only."""
-    return GEMM_KERNELS[lib().hm_choose_gemm(M, N, K)]
-
-
-def gemm_kernel(M: int, N: int, K: int) -> str:
-    """Name of the kernel that nvfp4_46_gemm runs for an M x N x K product."""
-    return GEMM_KERNELS[lib().hm_gemm_kernel(M, N, K)]
+def choose_gemm(M: int, N: int, K: int, f32: bool = False) -> str:
+    """Name of the kernel that nvfp4_46_gemm runs for an M x N x K product (C in BF16, or fp32)."""
+    return GEMM_KERNELS[lib().hm_choose_gemm(M, N, K, f32)]
 
 
 def gemm_lanes(kernel: str, M: int, N: int) -> int:

@@ -165,8 +165,7 @@ void hm_rht16(float *v, uint32_t sign_word) {
 }
 
 // the kernel (enum GemmKernel) that a product of these sizes takes
-int hm_choose_gemm(int64_t M, int64_t N, int64_t K) { return choose_gemm(M, N, K); }
-int hm_gemm_kernel(int64_t M, int64_t N, int64_t K) { return gemm_kernel(M, N, K); }
+int hm_choose_gemm(int64_t M, int64_t N, int64_t K, int f32) { return choose_gemm(M, N, K, f32 != 0); }
 
 // whether a tensor's scale (with or without scratch words), its scale and codes, take one launch
 int hm_scale_in_one_workgroup(int64_t bytes, int has_scratch) {

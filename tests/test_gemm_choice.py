@@ -10,13 +10,13 @@ EXPECTED = {
     # a wide weight and few rows: the tiles are many, but most of their rows do not exist
     (33, 28672, 8192): "tile64", (64, 28672, 8192): "tile64", (64, 28672, 4096): "tile64",
     (48, 32768, 8192): "tile64", (64, 57344, 8192): "tile64", (48, 128256, 4096): "tile64",
-    (64, 151936, 3584): "tile64", (65, 28672, 8192): "tile128", (96, 128256, 4096): "tile128",
-    (128, 28672, 8192): "tile128", (128, 57344, 8192): "tile128", (128, 128256, 4096): "tile128",
-    (192, 28672, 8192): "tile64", (196, 29536, 4096): "tile256x128", (199, 14464, 14336): "tile128",
-    (256, 28672, 8192): "tile256x128",
+    (64, 151936, 3584): "tile64", (65, 28672, 8192): "dma128", (96, 128256, 4096): "tile128",
+    (128, 28672, 8192): "dma128", (128, 57344, 8192): "tile128", (128, 128256, 4096): "tile128",
+    (192, 28672, 8192): "dma256x128", (196, 29536, 4096): "dma256x128", (199, 14464, 14336): "dma128",
+    (256, 28672, 8192): "dma256x128",
     # ... and with K not a multiple of 256
     (1, 28672, 8256): "tile32", (16, 28672, 8256): "tile32", (32, 201088, 2880): "tile32",
-    (48, 28672, 8256): "tile64", (128, 28672, 8256): "tile128", (256, 28672, 8256): "tile256x128",
+    (48, 28672, 8256): "tile64", (128, 28672, 8256): "dma128", (256, 28672, 8256): "dma256x128",
     # the same with A and B exchanged
     (28672, 64, 4128): "tile64", (201088, 31, 2880): "tile64x32",
     # few rows
@@ -34,29 +34,58 @@ EXPECTED = {
     (128, 8192, 2880): "tile64", (192, 8192, 8192): "tile64",
     # large and middling products
     (8192, 8192, 8192): "dma", (2816, 4096, 4096): "dma", (192, 128256, 4096): "dma",
-    (512, 28672, 8192): "dma", (4352, 4096, 2048): "tile64", (2048, 4096, 4096): "tile256x128",
-    (8192, 8192, 8160): "tile256x128", (1000, 4096, 4096): "tile128", (2880, 1440, 1056): "tile64",
-    (1340, 4464, 5504): "tile256x128", (431, 7440, 2048): "tile128", (5834, 1600, 1024): "tile64",
-    (1, 1, 1 << 25): "staged",
+    (512, 28672, 8192): "dma", (4352, 4096, 2048): "tile64", (2048, 4096, 4096): "dma256x128",
+    (8192, 8192, 8160): "dma", (1000, 4096, 4096): "dma128", (2880, 1440, 1056): "tile64",
+    (1340, 4464, 5504): "dma256x128", (431, 7440, 2048): "dma128", (5834, 1600, 1024): "tile64",
+    (6000, 8000, 96): "dma", (2816, 4096, 4064): "dma", (6144, 6400, 1056): "dma", (3072, 3072, 992): "tile64",
+    (4096, 4608, 3040): "dma256x128", (6798, 880, 4160): "dma256x128", (1000, 4096, 992): "tile128",
+    (3000, 3000, 1024): "tile64", (1000, 5232, 32): "dma256x128", (2048, 4096, 256): "dma256x128",
+    # ... several turns of 256 x 128 tiles, filled to 66 %, 70 %, 74 %
+    (8324, 1925, 256): "tile64", (6496, 2681, 2688): "tile64", (8328, 2176, 256): "dma256x128",
+    (1344, 13184, 1824): "tile256x128",
+    # lines of C that do not begin at multiples of 16 bytes: in BF16 and fp32 ...
+    (2048, 4095, 32): "tile256x128", (2048, 4095, 992): "tile256x128", (2048, 4095, 1024): "dma256x128",
+    (5727, 954, 256): "tile64", (4055, 738, 1536): "tile64", (4055, 738, 2048): "dma128", (2816, 4095, 128): "dma",
+    # beyond 32-bit lane offsets
+    (1, 1, 1 << 25): "staged", (1, 1, (1 << 24) + 32): "staged", (4096, 8192, (1 << 24) + 32): "staged",
+}
+# ... and in BF16 only
+EXPECTED_BF16_F32 = {
+    (2048, 4092, 256): ("tile256x128", "dma256x128"), (1000, 4092, 1056): ("tile128", "dma128"),
+    (2816, 4092, 256): ("dma", "dma"),
 }
 
 
 @pytest.mark.parametrize("size", EXPECTED, ids=lambda s: "x".join(map(str, s)))
 def test_expected_kernel(size):
-    assert hm.choose_gemm(*size) == EXPECTED[size]
+    assert (hm.choose_gemm(*size), hm.choose_gemm(*size, f32=True)) == (EXPECTED[size],) * 2
+
+
+@pytest.mark.parametrize("size", EXPECTED_BF16_F32, ids=lambda s: "x".join(map(str, s)))
+def test_expected_kernel_by_type(size):
+    assert (hm.choose_gemm(*size), hm.choose_gemm(*size, f32=True)) == EXPECTED_BF16_F32[size]
+
+
+LARGE = {"dma": (256, 256), "dma256x128": (256, 128), "dma128": (128, 128), "tile256x128": (256, 128),
+         "tile128": (128, 128)}
 
 
 def test_large_tiles_are_mostly_filled():
-    """No drawn product gets large tiles that hold more than 1 / 0.62 of what tiles of 64 x 64 do."""
+    """No drawn product gets large tiles that hold more than 1 / 0.62 of what tiles of 64 x 64 do, or that are so few
+    that most of the chip is idle."""
     rng = random.Random(4648)
-    for _ in range(20000):
+    seen = dict.fromkeys(LARGE, 0)
+    for _ in range(40000):
         M, N = (int(2 ** rng.uniform(0, 18)) for _ in range(2))
         K = int(2 ** rng.uniform(0, 10)) * rng.choice((32, 128, 256))
-        kernel = hm.choose_gemm(M, N, K)
-        if kernel in ("dma", "tile128", "tile256x128"):
-            bm, bn = (256, 256) if kernel == "dma" else hm.tile_shape(kernel)[:2]
-            assert (-(-M // 64) * 64) * (-(-N // 64) * 64) > 0.61 * (-(-M // bm) * bm) * (-(-N // bn) * bn), (
-                M, N, K, kernel)
+        kernel = hm.choose_gemm(M, N, K, rng.random() < 0.5)
+        if kernel in LARGE:
+            bm, bn = LARGE[kernel]
+            tm, tn = -(-M // bm), -(-N // bn)
+            assert (-(-M // 64) * 64) * (-(-N // 64) * 64) > 0.61 * tm * bm * tn * bn, (M, N, K, kernel)
+            assert tm * tn >= 0.62 * 256 and M > 64 and N > 64 and K <= 1 << 24, (M, N, K, kernel)
+            seen[kernel] += 1
+    assert min(seen.values()) > 10, seen
 
 
 def test_no_launch_is_too_large():
@@ -70,7 +99,14 @@ def test_no_launch_is_too_large():
         K = 32 * int(2 ** rng.uniform(0, 20))
         if -(-M // 256) * -(-N // 256) * 256 < 1 << 32:
             sizes.append((M, N, K))
+    seen = set()
     for M, N, K in sizes:
-        kernel = hm.choose_gemm(M, N, K)
-        assert hm.gemm_lanes(kernel, M, N) < 1 << 32, (M, N, K, kernel)
-        assert kernel != "dma" or (K % 128 == 0 and K <= 1 << 24), (M, N, K)
+        for f32 in (False, True):
+            kernel = hm.choose_gemm(M, N, K, f32)
+            assert hm.gemm_lanes(kernel, M, N) < 1 << 32, (M, N, K, kernel)
+            assert kernel != "dma" or K <= 1 << 24, (M, N, K)
+            # (what the sizes alone would choose and a launch does not hold)
+            if kernel in ("dma", "staged") and (-(-M // 64) * 64) * (-(-N // 64) * 64) <= 0.61 * (
+                    -(-M // 256) * -(-N // 256) * 65536):
+                seen.add(kernel)
+    assert seen == {"dma", "staged"}

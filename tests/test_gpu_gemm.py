@@ -145,14 +145,15 @@ TILE_SHAPES = {
     "tile64": [(701, 799, 32, ""), (705, 769, 512, ""), (704, 784, 800, "ab"), (64, 17008, 96, "ab"),
                (1100, 1500, 4128, "")],          # (operands past one die's L2: the tiles in strips, the last narrower)
     "tile64long": [(129, 4203, 8192, ""), (144, 4208, 8224, "ab"), (705, 1300, 9696, "")],
-    "tile128": [(1901, 1920, 288, "b"), (1793, 1921, 256, ""), (1857, 1930, 2592, ""), (100, 28677, 320, "")],
-    "tile256x128": [(2177, 2945, 96, ""), (2304, 2944, 128, "b"), (2192, 2945, 416, "a"),
-                    (2177, 2960, 1824, "b")],
+    "tile128": [(1901, 1920, 288, "b"), (1793, 1921, 256, ""), (100, 28677, 320, ""), (1904, 1920, 768, "ab"),
+                (1901, 1928, 992, ""), (1793, 1921, 1888, "")],
+    "tile256x128": [(2177, 2945, 96, ""), (2192, 2945, 416, "a"), (2177, 2947, 928, ""), (1344, 13184, 128, "ab"),
+                    (1338, 13184, 1824, "b")],
     # the kernels that stream B: 16 rows, 32 rows, 64 rows
     "skinny": [(16, 1008, 512, "ab"), (5, 4099, 768, ""), (32, 64, 512, "ab"), (31, 4099, 256, ""),
                (33, 4100, 256, ""), (50, 8203, 768, ""), (64, 4112, 768, "ab"), (48, 16384, 256, "a"),
                (63, 5008, 512, "b")],
-    # 256 x 256 tiles by copies: one, two and three chunks
+    # 256 x 256 tiles by copies: one, two and three chunks (test_gemm_large_tiles.py has more)
     "dma": [(3300, 3400, 128, ""), (3300, 3400, 256, ""), (3311, 3393, 384, ""), (3312, 3400, 256, "a"),
             (3300, 3408, 384, "b"), (3312, 3408, 128, "ab")]}
 TILE_SHAPES = [(kernel, *size) for kernel, sizes in TILE_SHAPES.items() for size in sizes]
@@ -163,7 +164,7 @@ def test_tile_shapes_are_exact_when_every_partial_sum_is_representable(kernel, M
     """Scales 0.5 .. 4 as above: every product is a multiple of 1/8, and the magnitudes of an element's
     products add up to less than 2^21 (checked), so all partial sums are exact in fp32 (2^21 / 2^-3 =
     2^24) in any order and the result is the oracle's bit for bit."""
-    assert hm.choose_gemm(M, N, K) == kernel
+    assert (hm.choose_gemm(M, N, K), hm.choose_gemm(M, N, K, f32=True)) == (kernel, kernel)
     _log(f"gemm {kernel} case M={M} N={N} K={K} tiled={tiled!r}")
     rng = np.random.default_rng(M * 7919 + N * 31 + K)
     ca = rng.integers(0, 256, (M, K // 2), dtype=np.uint8)
