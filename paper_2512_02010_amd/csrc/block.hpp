@@ -285,17 +285,16 @@ NV_DEV void sr_candidates(const float (&v)[16], const Words &words, SrCandidate 
   if (TWO) b.error = error_b.value();
 }
 
-// One candidate on its own, for callers that compare candidates across lanes: stochastic rounding by the
-// conversion instruction, redone in software for the rare block in which an element came too close to the
-// one case where the instruction's answer may differ.
-template <int ROUNDING, int ERR>
-NV_DEV float candidate(const float (&v)[16], const uint32_t (&rw)[16], float dec, float enc,
+// One candidate on its own: stochastic rounding by the conversion instruction, redone in software for the rare
+// block in which an element came too close to the one case where the instruction's answer may differ.
+template <int ROUNDING, int ERR, typename Words>
+NV_DEV float candidate(const float (&v)[16], const Words &words, float dec, float enc,
                        uint32_t &lo, uint32_t &hi) {
   if (ROUNDING == kRTN) return rtn_candidate<ERR>(v, dec, enc, lo, hi);
   SrCandidate c{dec, enc, {0u, 0u}, 0.0f}, none{};
   float margin = __builtin_inff();
-  sr_candidates<false, ERR, true>(v, rw, c, none, margin);
-  if (!(margin > kSrMarginAtRisk)) sr_candidates<false, ERR, false>(v, rw, c, none, margin);
+  sr_candidates<false, ERR, true>(v, words, c, none, margin);
+  if (!(margin > kSrMarginAtRisk)) sr_candidates<false, ERR, false>(v, words, c, none, margin);
   lo = c.code[0];
   hi = c.code[1];
   return c.error;
@@ -454,8 +453,14 @@ NV_DEV void block_scales(float b, const ScaleConsts &k, uint32_t &S6, uint32_t &
 // The per-block procedure (Table 3 lines 1-14) in one pass.  DEFINED = false: the squared-error rule
 // compares the cheap estimates and reports through `undecided` when they cannot tell (the result is then
 // provisional); true: the errors are evaluated exactly as defined.  The other rules always evaluate the
-// defined errors.  FAST = true: stochastic rounding uses the conversion instruction and reports through
-// `risky` when its answer may not be the rule's; false: the rule itself.
+// defined errors.  Where stochastic rounding takes both candidates at once (kTogether), FAST = true uses the
+// conversion instruction and reports through `risky` when its answer may not be the rule's, and false is the rule
+// itself.  A candidate that is rounded on its own is settled at once, which needs no more registers than a second
+// pass there and spares a small launch the wait for it (1008 x 4096 without transform, the winner of the absolute
+// errors rounded: second pass 7.1 us, at once 6.2; both candidates of the absolute errors: second pass 95
+// registers, at once 138).
+template <int ROUNDING, int SELECT>
+constexpr bool kTogether = ROUNDING == kSR && SELECT != kSelForce4 && SELECT != kSelForce6;
 template <int ROUNDING, int SELECT, bool DEFINED, bool FAST, typename Words>
 NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
                                        const ScaleConsts &k, const ScaleTable &tab,
@@ -481,7 +486,6 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
                        : SELECT == kSel46AbsMax ? kErrAbsMax : kErrNone;
   BlockResult r6{}, r4{};
   float E6p = 0.0f, E4p = 0.0f, enc6 = 0.0f, enc4 = 0.0f, m6 = 0.0f, m4 = 0.0f;
-  float margin = __builtin_inff();
   auto look_up = [&](uint32_t S, BlockResult &r, float &enc, float &m) {
     const float4 t = tab.e[S];
     r.scale = S;
@@ -489,31 +493,31 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
     enc = t.y;
     m = t.z;
   };
-  if (ROUNDING == kSR) {
-    if (kSix) look_up(S6, r6, enc6, m6);
-    if (kFour) look_up(S4, r4, enc4, m4);
-    SrCandidate c{kSix ? r6.dec : r4.dec, kSix ? enc6 : enc4, {0u, 0u}, 0.0f}, d{r4.dec, enc4, {0u, 0u}, 0.0f};
-    sr_candidates<kBoth, kErr, FAST>(v, words, c, d, margin);
+  if (kTogether<ROUNDING, SELECT>) {
+    look_up(S6, r6, enc6, m6);
+    look_up(S4, r4, enc4, m4);
+    SrCandidate c{r6.dec, enc6, {0u, 0u}, 0.0f}, d{r4.dec, enc4, {0u, 0u}, 0.0f};
+    float margin = __builtin_inff();
+    sr_candidates<true, kErr, FAST>(v, words, c, d, margin);
+    if (FAST) risky = !(margin > kSrMarginAtRisk);
     E6p = c.error;
     E4p = d.error;
-    BlockResult &first = kSix ? r6 : r4;
-    first.lo = c.code[0];
-    first.hi = c.code[1];
-    if (kBoth) {
-      r4.lo = d.code[0];
-      r4.hi = d.code[1];
-    }
+    r6.lo = c.code[0];
+    r6.hi = c.code[1];
+    r4.lo = d.code[0];
+    r4.hi = d.code[1];
   } else {
     // Appendix A.3's second alternative compares round-to-nearest candidates and rounds only the
     // winner stochastically; a single candidate need not be rounded to nearest for that.
-    constexpr bool kRound = ROUNDING == kRTN || kBoth;
+    constexpr bool kRound = ROUNDING != kSRAfterRtnSelect || kBoth;
+    constexpr int kCandidate = ROUNDING == kSR ? kSR : kRTN;
     if (kSix) {
       look_up(S6, r6, enc6, m6);
-      if (kRound) E6p = rtn_candidate<kErr>(v, r6.dec, enc6, r6.lo, r6.hi);
+      if (kRound) E6p = candidate<kCandidate, kErr>(v, words, r6.dec, enc6, r6.lo, r6.hi);
     }
     if (kFour) {
       look_up(S4, r4, enc4, m4);
-      if (kRound) E4p = rtn_candidate<kErr>(v, r4.dec, enc4, r4.lo, r4.hi);
+      if (kRound) E4p = candidate<kCandidate, kErr>(v, words, r4.dec, enc4, r4.lo, r4.hi);
     }
   }
   r4.four = 1u;
@@ -534,15 +538,8 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
   }
   BlockResult r = four ? r4 : r6;
   if (ROUNDING == kSRAfterRtnSelect) {
-    SrCandidate c{r.dec, four ? enc4 : enc6, {0u, 0u}, 0.0f}, none{};
-    sr_candidates<false, kErrNone, FAST>(v, words, c, none, margin);
-    // (only the pass that settles the winner can settle its rounding: the other candidate has its own risk)
-    if (DEFINED && FAST && !(margin > kSrMarginAtRisk))
-      sr_candidates<false, kErrNone, false>(v, words, c, none, margin);
-    r.lo = c.code[0];
-    r.hi = c.code[1];
+    (void)candidate<kSR, kErrNone>(v, words, r.dec, four ? enc4 : enc6, r.lo, r.hi);
   }
-  if (ROUNDING != kRTN && FAST) risky = !(margin > kSrMarginAtRisk);
   return r;
 }
 
@@ -553,20 +550,19 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
 // values and both candidates alive across the common path cost the rowwise kernel three of its
 // eight waves per SIMD.  A block whose estimates were too close is rounded by the instruction once more (one
 // wave in some hundreds is in the case, and in a small launch all wait for it: with the rule in
-// software 1008 x 4096 took 8.1 us instead of 7.5), a risky one by the rule.  Under kSR the first pass's margin
-// covers both candidates, whichever the second pass keeps; under kSRAfterRtnSelect it covers the
-// provisional winner alone, so there the second pass looks at its own (1008 x 4096, rowwise / both layouts: 7.33
-// / 19.3 us, with a second pass that always rounds by the rule 7.57 / 20.1).
+// software 1008 x 4096 took 8.1 us instead of 7.5), a risky one by the rule; the margin of the first pass covers
+// both candidates, whichever the second keeps.
 template <int ROUNDING, int SELECT, typename Words, typename Again>
 NV_DEV BlockResult quantize_block(const float (&v)[16], const Words &words,
                                   const ScaleConsts &k, const ScaleTable &tab, Again &&again) {
   bool undecided = false, risky = false;
   BlockResult r = quantize_block_pass<ROUNDING, SELECT, false, true>(v, words, k, tab, undecided, risky);
-  if ((SELECT == kSel46 && undecided) || (ROUNDING != kRTN && risky)) {
+  constexpr bool kMayBeRisky = kTogether<ROUNDING, SELECT>;
+  if ((SELECT == kSel46 && undecided) || (kMayBeRisky && risky)) {
     float w[16];
     uint32_t ww[16];
     again(w, ww);
-    if (ROUNDING != kRTN && risky)
+    if (kMayBeRisky && risky)
       r = quantize_block_pass<ROUNDING, SELECT, true, false>(w, ww, k, tab, undecided, risky);
     else if (SELECT == kSel46)
       r = quantize_block_pass<ROUNDING, SELECT, true, true>(w, ww, k, tab, undecided, risky);

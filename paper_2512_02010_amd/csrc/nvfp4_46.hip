@@ -482,6 +482,10 @@ __global__ __launch_bounds__(kThreads) void k_flat(
     auto words = words_on_demand<kStep>([&](int q, uint32_t (&w)[kStep]) {
       sr_words_in_wave<kStep / 4>(sr_seed, (uint32_t)q0 + (4u * tid + kStep / 4 * q), (uint32_t)(q0 >> 32), w);
     });
+    // words that are needed for one candidate alone, at the very end: drawn ahead, beside the candidates
+    constexpr bool kAhead = ROUNDING != kRTN && !kTogether<ROUNDING, SELECT>;
+    uint32_t u[kAhead ? 16 : 1];
+    if constexpr (kAhead) sr_words_in_wave<4>(sr_seed, (uint32_t)q0 + 4u * tid, (uint32_t)(q0 >> 32), u);
     // the block once more, from memory (a lane without a block of its own holds a copy of
     // the round's last block, as fetch() gave it)
     auto again = [&](float (&w)[16], uint32_t (&uu)[16]) {
@@ -489,20 +493,19 @@ __global__ __launch_bounds__(kThreads) void k_flat(
       load_block<XF32>(x + Raw::kPieces * (base + (tid < live ? tid : live - 1)), r2);
       unpack16(r2, w);
       if (RHT) transform(w);
-      if (ROUNDING != kRTN) {
+      if constexpr (kAhead && !RHT) {
+        // (there is room to keep them: 111 registers instead of 84, and the one wave in some hundreds that comes here
+        // ends sooner, 1008 x 4096 7.7 -> 6.9 us; with the transform 123 instead of 98 cost 4 % of any size)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) uu[i] = u[i];
+      } else if constexpr (ROUNDING != kRTN) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) sr_words4(sr_seed, q0 + 4u * tid + j, &uu[4 * j]);
       }
     };
     BlockResult res;
-    if constexpr (ROUNDING == kSRAfterRtnSelect) {
-      // needed at the very end only: drawn ahead, beside the candidates, not behind them
-      uint32_t u[16];
-      sr_words_in_wave<4>(sr_seed, (uint32_t)q0 + 4u * tid, (uint32_t)(q0 >> 32), u);
-      res = quantize_block<ROUNDING, SELECT>(v, u, sc, tab, again);
-    } else {
-      res = quantize_block<ROUNDING, SELECT>(v, words, sc, tab, again);
-    }
+    if constexpr (kAhead) res = quantize_block<ROUNDING, SELECT>(v, u, sc, tab, again);
+    else res = quantize_block<ROUNDING, SELECT>(v, words, sc, tab, again);
     if (OUT == kOutCodes) {
       store_as<kNtCodes>(codes + base + tid, make_uint2(res.lo, res.hi));
       store_as<kNtCodes>(scales + base + tid, (uint8_t)res.scale);
