@@ -73,6 +73,10 @@ def lib() -> C.CDLL:
         L.hm_block_scale.argtypes = [C.c_float, C.c_float, C.c_int, C.c_int]
         L.hm_philox.restype = None
         L.hm_philox.argtypes = [u32p, C.c_uint32, C.c_uint32, u32p]
+        L.hm_sr_words_in_wave.restype = None
+        L.hm_sr_words_in_wave.argtypes = [C.c_uint64, C.c_uint64, C.c_int, u32p]
+        L.hm_rht_sign_word_of_wave.restype = C.c_uint32
+        L.hm_rht_sign_word_of_wave.argtypes = [C.c_uint64, C.c_uint64]
         L.hm_rht16.restype = None
         L.hm_rht16.argtypes = [f32p, C.c_uint32]
         L.hm_choose_gemm.restype = C.c_int
@@ -155,6 +159,17 @@ def philox(ctr, key):
     o = (C.c_uint32 * 4)()
     lib().hm_philox(c, key[0], key[1], o)
     return tuple(int(x) for x in o)
+
+
+def sr_words_in_wave(seed: int, q: int, groups: int):
+    """The stochastic-rounding words of elements 4 q .. 4 (q + groups) - 1, by the wave's generator."""
+    o = (C.c_uint32 * (4 * groups))()
+    lib().hm_sr_words_in_wave(seed, q, groups, o)
+    return [int(x) for x in o]
+
+
+def rht_sign_word_of_wave(seed: int, B: int) -> int:
+    return lib().hm_rht_sign_word_of_wave(seed, B)
 
 
 def rht16(v, sign_word: int) -> np.ndarray:

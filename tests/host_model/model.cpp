@@ -157,6 +157,22 @@ void hm_philox(const uint32_t *ctr, uint32_t k0, uint32_t k1, uint32_t *out) {
   for (int j = 0; j < 4; ++j) out[j] = p.w[j];
 }
 
+// the generators for counters that a wave shares in part or whole: the words of `groups` (1, 2 or 4) groups of four
+// elements from group q on, and the sign word of block position B
+void hm_sr_words_in_wave(uint64_t seed, uint64_t q, int groups, uint32_t *out) {
+  auto of = [&](auto &w, auto draw) {
+    draw(seed, (uint32_t)q, (uint32_t)(q >> 32), w);
+    for (size_t i = 0; i < sizeof w / sizeof w[0]; ++i) out[i] = w[i];
+  };
+  uint32_t w4[4], w8[8], w16[16];
+  if (groups == 1) of(w4, sr_words_in_wave<1>);
+  else if (groups == 2) of(w8, sr_words_in_wave<2>);
+  else of(w16, sr_words_in_wave<4>);
+}
+uint32_t hm_rht_sign_word_of_wave(uint64_t seed, uint64_t B) {
+  return rht_sign_word_of_wave(seed, (uint32_t)B, (uint32_t)(B >> 32));
+}
+
 void hm_rht16(float *v, uint32_t sign_word) {
   float a[16];
   for (int i = 0; i < 16; ++i) a[i] = v[i];

@@ -232,6 +232,49 @@ def test_outputs_allocated_natively(monkeypatch):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("given", [False, True])
+def test_launches_on_the_stream_that_is_meant(monkeypatch, given):
+    """Each call is made while the stream it belongs to is still busy with what comes before its inputs (some
+    milliseconds of products, then a copy into x): launched on any other stream it would read the inputs of before.
+    `given`: the stream is named in the call instead of being the current one."""
+    monkeypatch.setattr(B, "OUTPUT_ALLOCATOR", B._device_empty)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4671)
+    new = torch.randn((64, 160), generator=g, device="cuda").bfloat16()
+    alpha = B.nvfp4_46_tensor_scale(new)
+    q = B.nvfp4_46_quantize(new, alpha)
+    busy = torch.randn((4096, 4096), generator=g, device="cuda")
+    ws, side = B.new_workspace(), torch.cuda.Stream()
+    x, a, codes, scales = (torch.zeros_like(t) for t in (new, alpha, q["codes_row"], q["scales_row"]))
+    for i, call in enumerate((lambda **s: B.nvfp4_46_tensor_scale(x, **s),
+                              lambda **s: B.nvfp4_46_tensor_scale_ws(x, ws, **s),
+                              lambda **s: B.nvfp4_46_quantize(x, a, **s)["codes_row"],
+                              lambda **s: B.nvfp4_46_scale_quantize(x, ws, **s)["codes_row"],
+                              lambda **s: B.nvfp4_46_fake_quant(x, a, **s),
+                              lambda **s: B.nvfp4_46_dequantize(codes, scales, a, 64, 160, **s),
+                              lambda **s: B.nvfp4_46_gemm(codes, scales, a, codes, scales, a, **s))):
+        print(f"stream case {i}", flush=True)
+        for t, n in ((x, new), (a, alpha), (codes, q["codes_row"]), (scales, q["scales_row"])):
+            t.copy_(n)
+        want = call().clone()
+        for t in (x, a, codes, scales):
+            t.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            for _ in range(4):
+                busy @ busy
+            for t, n in ((x, new), (a, alpha), (codes, q["codes_row"]), (scales, q["scales_row"])):
+                t.copy_(n)
+            if not given:
+                got = call()
+        if given:
+            got = call(stream=side)
+        busy_then = not side.query()
+        torch.cuda.synchronize()
+        assert busy_then and torch.equal(got.view(torch.uint8), want.view(torch.uint8)), i
+
+
+@pytest.mark.gpu
 def test_given_outputs_and_statuses(monkeypatch):
     monkeypatch.setattr(B, "OUTPUT_ALLOCATOR", B._device_empty)
     x = torch.ones((32, 32), dtype=torch.bfloat16, device="cuda")

@@ -218,6 +218,24 @@ def test_philox_and_hadamard_match_oracle():
         assert np.array_equal(hm.rht16(v, sw).view(np.uint32), ref.rht16(v, sw).view(np.uint32))
 
 
+def test_generators_of_a_wave_match_oracle():
+    """The stochastic-rounding words and sign words drawn with part of the arithmetic on the scalar unit, for upper
+    counter words other than 0 as well (tensors of more than 2^34 elements), and next to a carry."""
+    rng = np.random.default_rng(6)
+    for i in range(300):
+        seed = int(rng.integers(0, 1 << 64, dtype=np.uint64))
+        hi = (0, 1, int(rng.integers(0, 1 << 29)))[i % 3]      # (element numbers have 63 bits)
+        lo = (0, (1 << 32) - 4, int(rng.integers(0, (1 << 32) - 4)))[i // 3 % 3]
+        q, key = (hi << 32) | lo, (seed & 0xFFFFFFFF, seed >> 32)
+        for groups in (1, 2, 4):
+            want = [w for j in range(groups) for w in ref.philox4x32_10((lo + j, hi, 0, 0), key)]
+            assert hm.sr_words_in_wave(seed, q, groups) == want, (seed, q, groups)
+        for j, w in enumerate(want[:8]):
+            assert ref.sr_uniform(seed, 4 * q + j) == np.float32((w >> 8) * 2.0 ** -24)
+        B = (hi << 32) | lo
+        assert hm.rht_sign_word_of_wave(seed, B) == ref.rht_sign_word(seed, B)
+
+
 def _uniform_at_threshold(y: float, d: int):
     """The uniform d steps of 2^-24 from where the rounding of |y| < 1 turns (there the conversion
     instruction, which compares two bits less, may answer differently); None outside [0, 1)."""
