@@ -1768,7 +1768,7 @@ int nvfp4_46_scale_quantize(const void *x, const nvfp4_46_params *p, float *alph
   const bool xf32 = p->x_dtype == NVFP4_X_F32;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (p->layout == NVFP4_ROWWISE && p->rounding == NVFP4_RTN && !p->rht && !p->block2d &&
-      scale_and_codes_in_one_launch(p->rows * p->cols * (xf32 ? 4 : 2), xf32, workspace != nullptr)) {
+      scale_and_codes_in_one_launch(p->rows * p->cols * (xf32 ? 4 : 2), workspace != nullptr)) {
     FlatArgs a{xf32, static_cast<const uint4 *>(x), nullptr, static_cast<uint2 *>(codes_row),
                static_cast<uint8_t *>(scales_row), static_cast<uint8_t *>(choice_row), nullptr,
                nullptr, p->rows * p->cols / 16, (uint32_t)(p->cols / 16), 0, 0, s,

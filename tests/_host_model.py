@@ -86,7 +86,7 @@ def lib() -> C.CDLL:
         L.hm_scale_in_one_workgroup.restype = C.c_int
         L.hm_scale_in_one_workgroup.argtypes = [C.c_int64, C.c_int]
         L.hm_scale_and_codes_in_one_launch.restype = C.c_int
-        L.hm_scale_and_codes_in_one_launch.argtypes = [C.c_int64, C.c_int, C.c_int]
+        L.hm_scale_and_codes_in_one_launch.argtypes = [C.c_int64, C.c_int]
         L.hm_tile_shape.restype = None
         L.hm_tile_shape.argtypes = [C.c_int, C.POINTER(C.c_int32)]
         _lib = L
@@ -198,5 +198,5 @@ def scale_in_one_workgroup(nbytes: int, has_scratch: bool) -> bool:
     return bool(lib().hm_scale_in_one_workgroup(nbytes, has_scratch))
 
 
-def scale_and_codes_in_one_launch(nbytes: int, xf32: bool, has_scratch: bool) -> bool:
-    return bool(lib().hm_scale_and_codes_in_one_launch(nbytes, xf32, has_scratch))
+def scale_and_codes_in_one_launch(nbytes: int, has_scratch: bool) -> bool:
+    return bool(lib().hm_scale_and_codes_in_one_launch(nbytes, has_scratch))

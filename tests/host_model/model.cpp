@@ -187,8 +187,8 @@ int hm_choose_gemm(int64_t M, int64_t N, int64_t K, int f32) { return choose_gem
 int hm_scale_in_one_workgroup(int64_t bytes, int has_scratch) {
   return scale_in_one_workgroup(bytes, has_scratch != 0);
 }
-int hm_scale_and_codes_in_one_launch(int64_t bytes, int xf32, int has_scratch) {
-  return scale_and_codes_in_one_launch(bytes, xf32 != 0, has_scratch != 0);
+int hm_scale_and_codes_in_one_launch(int64_t bytes, int has_scratch) {
+  return scale_and_codes_in_one_launch(bytes, has_scratch != 0);
 }
 
 // lanes that such a launch of `kernel` has

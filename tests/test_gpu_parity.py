@@ -761,13 +761,14 @@ def test_workload_c5_full_rht_sr():
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("rows,cols", [(1, 16), (1, 8192), (3, 5456), (4, 8192), (5, 8192), (8, 8192),
-                                       (9, 8192), (16, 8192), (17, 8192), (24, 8192), (25, 8192),
+                                       (9, 8192), (12, 8192), (13, 8192), (16, 8192), (17, 8192), (24, 8192),
+                                       (25, 8192),
                                        (31, 8192 + 16), (32, 8192), (33, 8192), (48, 8192), (49, 8192),
                                        (64, 8192), (65, 8192), (129, 4096)])
 def test_small_tensors_scale_and_codes(rows, cols, dtype):
     """Both sides of the sizes at which one workgroup takes the tensor scale (128 KiB with scratch
-    words, 768 KiB without) and at which scale and codes come from one launch (384 KiB of BF16, 256 of
-    fp32, 512 without a workspace), with rest counts of the 1024-lane kernels: the oracle's scale and
+    words, 768 KiB without) and at which scale and codes come from one launch (384 KiB, 768 without a
+    workspace), with rest counts of the 1024-lane kernels and of their 256 blocks: the oracle's scale and
     codes, from every call."""
     g = torch.Generator().manual_seed(rows * 16384 + cols)
     x = (torch.randn(rows, cols, generator=g) * torch.exp(torch.randn(rows, 1, generator=g))).to(dtype)
