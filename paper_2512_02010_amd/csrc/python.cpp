@@ -140,19 +140,30 @@ Owned given_or_new(PyObject *given, at::IntArrayRef shape, at::ScalarType type, 
 
 // x [rows][cols], BF16 or fp32
 void set_shape(nvfp4_46_params &p, PyObject *x) {
-  const at::Tensor *t = plain(x);
-  const auto dims = t ? t->dim() : (int64_t)word(Owned(PyObject_CallMethod(x, "dim", nullptr)).o);
-  at::ScalarType type = t ? t->scalar_type() : at::kByte;
-  if (!t) {
+  int64_t dims, rows = 0, cols = 0;
+  at::ScalarType type = at::kByte;
+  if (const at::Tensor *t = plain(x)) {
+    dims = t->dim();
+    type = t->scalar_type();
+    if (dims == 2) {
+      rows = t->size(0);
+      cols = t->size(1);
+    }
+  } else {
+    dims = (int64_t)word(Owned(PyObject_CallMethod(x, "dim", nullptr)).o);
     const Owned dtype(PyObject_GetAttrString(x, "dtype"));
     if (THPDtype_Check(dtype.o)) type = reinterpret_cast<THPDtype *>(dtype.o)->scalar_type;
+    if (dims == 2) {
+      const auto shape = shape_of(x);
+      if (shape.size() < 2) fail(PyExc_IndexError, "tuple index out of range");
+      rows = shape[0];
+      cols = shape[1];
+    }
   }
   if (dims != 2 || !(type == at::kFloat || type == at::kBFloat16))
     fail(PyExc_AssertionError, "x must be a matrix of BF16 or fp32");
-  const auto shape = shape_of(x);
-  if (shape.size() < 2) fail(PyExc_IndexError, "tuple index out of range");
-  p.rows = shape[0];
-  p.cols = shape[1];
+  p.rows = rows;
+  p.cols = cols;
   p.x_dtype = type == at::kFloat ? NVFP4_X_F32 : NVFP4_X_BF16;
 }
 // layout, rounding, select, rht, sr_seed, rht_seed, fp8_max, block2d
