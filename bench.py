@@ -39,13 +39,13 @@ HBM_PEAK_GBS = 8000.0
 # FP4/FP8 packing conversions eight and the stochastic-rounding FP4 conversion twelve.
 VALU_PEAK_TOPS = 256 * 128 * 2.4e9 / 1e12
 # VALU wave-instructions per block of 16 elements in the rowwise 4/6 kernel, from
-# rocprofv3 --pmc SQ_INSTS_VALU (profiles/c2_step_counters.txt): 14,730,144 per 4,194,304/64 wave-blocks
-VALU_INSTS_PER_BLOCK_46 = 14730144.0 / (4194304.0 / 64.0)
+# rocprofv3 --pmc SQ_INSTS_VALU (profiles/c2_step_counters.txt): 14,430,273 per 4,194,304/64 wave-blocks
+VALU_INSTS_PER_BLOCK_46 = 14430273.0 / (4194304.0 / 64.0)
 # the same for the kernels of c4 (both orientations, per 16 elements;
 # profiles/c4_both_and_fake_quant_counters.txt) and c5 (Hadamard + stochastic rounding;
 # profiles/c5_rowwise_rht_sr_counters.txt)
-VALU_INSTS_PER_BLOCK_C4 = 31557668.0 / (4194304.0 / 64.0)
-VALU_INSTS_PER_BLOCK_C5 = 46169804.0 / (4194304.0 / 64.0)
+VALU_INSTS_PER_BLOCK_C4 = 30962205.0 / (4194304.0 / 64.0)
+VALU_INSTS_PER_BLOCK_C5 = 45355285.0 / (4194304.0 / 64.0)
 # HBM bytes per element of the same kernel from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, scaled
 # by a plain copy's readings (same file): (65665.8 * 2.000 + 36891.5 * 1.000) KiB per 67,108,864
 HBM_TRAFFIC_PER_ELEM_46 = (65665.8 * 2.0 + 36891.5) * 1024.0 / 67108864.0
@@ -235,8 +235,8 @@ def cpu_baseline(x_host):
 
 MFMA_F16_PEAK_TFLOPS = 2500.0
 # HBM-side bytes of one 8192^3 product from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE
-# (profiles/gemm_8192_counters.txt): (221,602.7 KiB x 2.000 + 131,120.0 KiB x 1.000)
-GEMM_8192_TRAFFIC_BYTES = (221602.7 * 2.0 + 131120.0) * 1024.0
+# (profiles/gemm_8192_counters.txt): (268,567.0 KiB x 2.000 + 131,072.0 KiB x 1.000)
+GEMM_8192_TRAFFIC_BYTES = (268567.0 * 2.0 + 131072.0) * 1024.0
 
 
 def time_gemm(w_host, iters=20):

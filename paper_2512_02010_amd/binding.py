@@ -2,8 +2,8 @@
 
 Every function has the name of the C entry point it calls (``include/nvfp4_46.h``)
 and does no arithmetic of its own.  The functions that allocate outputs and check statuses
-go through ``nvfp4_46_python.so`` (``csrc/python.cpp``), the raw ones through ctypes.  PyTorch supplies device memory and the
-stream; tensors passed in must live on the current CUDA (ROCm) device.  There
+go through ``nvfp4_46_python.so`` (``csrc/python.cpp``), the raw ones through ctypes.
+PyTorch supplies device memory and the stream; tensors passed in must live on the current CUDA (ROCm) device.  There
 is no CPU fallback: if the shared library has not been built, loading fails.
 """
 from __future__ import annotations
