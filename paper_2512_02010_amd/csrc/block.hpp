@@ -450,17 +450,19 @@ NV_DEV void block_scales(float b, const ScaleConsts &k, uint32_t &S6, uint32_t &
   }
 }
 
+// Whether stochastic rounding takes both candidates at once, element by element, and leaves what is at risk to a
+// second pass.  A candidate that is rounded on its own is settled at once, which needs no more registers than a
+// second pass there and spares a small launch the wait for it (1008 x 4096 without transform, the winner of the
+// absolute errors rounded: second pass 7.1 us, at once 6.2; both candidates of the absolute errors: second pass
+// 95 registers, at once 138).
+template <int ROUNDING, int SELECT>
+constexpr bool kTogether = ROUNDING == kSR && SELECT != kSelForce4 && SELECT != kSelForce6;
+
 // The per-block procedure (Table 3 lines 1-14) in one pass.  DEFINED = false: the squared-error rule
 // compares the cheap estimates and reports through `undecided` when they cannot tell (the result is then
 // provisional); true: the errors are evaluated exactly as defined.  The other rules always evaluate the
-// defined errors.  Where stochastic rounding takes both candidates at once (kTogether), FAST = true uses the
-// conversion instruction and reports through `risky` when its answer may not be the rule's, and false is the rule
-// itself.  A candidate that is rounded on its own is settled at once, which needs no more registers than a second
-// pass there and spares a small launch the wait for it (1008 x 4096 without transform, the winner of the absolute
-// errors rounded: second pass 7.1 us, at once 6.2; both candidates of the absolute errors: second pass 95
-// registers, at once 138).
-template <int ROUNDING, int SELECT>
-constexpr bool kTogether = ROUNDING == kSR && SELECT != kSelForce4 && SELECT != kSelForce6;
+// defined errors.  With kTogether, FAST = true uses the conversion instruction and reports through `risky` when
+// its answer may not be the rule's, and false is the rule itself.
 template <int ROUNDING, int SELECT, bool DEFINED, bool FAST, typename Words>
 NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
                                        const ScaleConsts &k, const ScaleTable &tab,
