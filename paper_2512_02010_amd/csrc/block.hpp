@@ -73,13 +73,13 @@ NV_DEV uint32_t e2m1_sr_code_fast_sel(uint32_t old, float y, uint32_t not_w, flo
     default: return e2m1_sr_code_fast<3>(old, y, not_w, wf, margin);
   }
 }
-NV_DEV void e2m1_sr_code_fast2_sel(uint32_t &old_a, uint32_t &old_b, float ya, float yb, uint32_t not_w, float wf,
-                                   float &margin, int sel) {
+// the codes of two values held times 2^-126
+NV_DEV uint32_t hw_pk_fp4_of_scaled_sel(uint32_t old, float a, float b, int sel) {
   switch (sel) {
-    case 0: return e2m1_sr_code_fast2<0>(old_a, old_b, ya, yb, not_w, wf, margin);
-    case 1: return e2m1_sr_code_fast2<1>(old_a, old_b, ya, yb, not_w, wf, margin);
-    case 2: return e2m1_sr_code_fast2<2>(old_a, old_b, ya, yb, not_w, wf, margin);
-    default: return e2m1_sr_code_fast2<3>(old_a, old_b, ya, yb, not_w, wf, margin);
+    case 0: return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(old, a, b, 0x1p-126f, 0);
+    case 1: return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(old, a, b, 0x1p-126f, 1);
+    case 2: return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(old, a, b, 0x1p-126f, 2);
+    default: return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(old, a, b, 0x1p-126f, 3);
   }
 }
 template <int SEL>
@@ -132,20 +132,22 @@ template <int ERR>
 struct CandidateError {
   float acc[2] = {0.0f, 0.0f};
   f32x2 sq = {0.0f, 0.0f};
+  // A three-source instruction issues at half rate when all three sources sit in registers
+  // of the same parity (measured), which d * d + acc is whenever d and acc do.  The two
+  // differences of a pair of elements are therefore kept in an aligned register pair (even,
+  // odd) and each is added into the accumulator of the other parity.
+  NV_DEV void add_pair(float d0, float d1) {
+    f32x2 d = {d0, d1};
+    in_register_pair(d);
+    sq.y = __builtin_fmaf(d.x, d.x, sq.y);
+    sq.x = __builtin_fmaf(d.y, d.y, sq.x);
+    in_register_pair(sq);
+  }
   NV_DEV void add8(const float (&g)[8], const float (&v)[16], int h, float dec) {
     if (ERR == kErrMseEstimate) {
-      // A three-source instruction issues at half rate when all three sources sit in registers
-      // of the same parity (measured), which d * d + acc is whenever d and acc do.  The two
-      // differences of a pair of elements are therefore kept in an aligned register pair (even,
-      // odd) and each is added into the accumulator of the other parity.
 #pragma unroll
-      for (int j = 0; j < 8; j += 2) {
-        f32x2 d = {__builtin_fmaf(g[j], dec, -v[8 * h + j]), __builtin_fmaf(g[j + 1], dec, -v[8 * h + j + 1])};
-        in_register_pair(d);
-        sq.y = __builtin_fmaf(d.x, d.x, sq.y);
-        sq.x = __builtin_fmaf(d.y, d.y, sq.x);
-        in_register_pair(sq);
-      }
+      for (int j = 0; j < 8; j += 2)
+        add_pair(__builtin_fmaf(g[j], dec, -v[8 * h + j]), __builtin_fmaf(g[j + 1], dec, -v[8 * h + j + 1]));
     }
     if (ERR == kErrMae || ERR == kErrAbsMax) {
       float e[8];
@@ -224,65 +226,119 @@ struct SrCandidate {
   float error;
 };
 
-// Quantize the block stochastically under both scales (TWO) or under the first, element
-// by element: a random word is used for both candidates and forgotten.  What bounds the stochastic
-// kernels is their vector arithmetic (some 700 instructions per block), and how much of its rate they get
-// is a question of waves per SIMD: with one candidate after the other the sixteen words, their complements
-// and their floats stayed in registers for the second (172, two waves).
-// FAST = true rounds with the conversion instruction and lowers `margin` (see e2m1_sr_code_fast: the
-// codes are only valid if it stays above kSrMarginAtRisk); FAST = false applies the rule in software and
-// is always valid.
-template <bool TWO, int ERR, bool FAST, typename Words>
-NV_DEV void sr_candidates(const float (&v)[16], const Words &words, SrCandidate &a, SrCandidate &b, float &margin) {
+// Quantize the block stochastically under both scales (TWO) or under the first, element by element, on fp32's
+// subnormal grid (see sr_sum): a random word is used for both candidates and forgotten.  What bounds the
+// stochastic kernels is their vector arithmetic, and how much of its rate they get is a question of waves per SIMD:
+// with one candidate after the other the sixteen words stayed in registers for the second (172, two waves).
+// The codes are only valid if `risk` stays above 0, and those of the second candidate, and its error, if no
+// magnitude is above 6 under its scale (for the estimate the first one's values are read back from the codes, where 6
+// is the largest; the second one's come for nothing).  kErrMseEstimate is here in units of dec^2, E' = the
+// running sum of fma(d, d, ..) of d = fl(fl(v enc) - g): see decision_tolerance.
+template <bool TWO, int ERR, typename Words>
+NV_DEV void sr_candidates(const float (&v)[16], const Words &words, SrCandidate &a, SrCandidate &b, uint32_t &risk) {
   CandidateError<ERR> error_a, error_b;
   uint32_t w[16];
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    float ga[8], gb[8];
-    if (FAST) {
-      // one conversion per element (only the first source position rounds as defined): even
-      // elements into the bytes of one word, odd ones into another
-      uint32_t ea = any_register(), oa = any_register(), eb = any_register(), ob = any_register();
+    uint32_t ca = any_register(), cb = any_register();   // all four bytes are written below
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        words_from(words, 8 * h + i, w);
-        const float x = v[8 * h + i], wf = (float)w[8 * h + i];
-        const uint32_t not_w = ~w[8 * h + i];
-        uint32_t &ca = i & 1 ? oa : ea, &cb = i & 1 ? ob : eb;
-        if (TWO) e2m1_sr_code_fast2_sel(ca, cb, x * a.enc, x * b.enc, not_w, wf, margin, i / 2);
-        else ca = e2m1_sr_code_fast_sel(ca, x * a.enc, not_w, wf, margin, i / 2);
-      }
-      a.code[h] = (ea & 0x0f0f0f0fu) | ((oa << 4) & 0xf0f0f0f0u);
-      if (TWO) b.code[h] = (eb & 0x0f0f0f0fu) | ((ob << 4) & 0xf0f0f0f0u);
-      in_register(a.code[h]);                 // (and not as the four words it is made of)
-      if (TWO) in_register(b.code[h]);
-      if (ERR != kErrNone) {
-        grid8(a.code[h], ga);
-        if (TWO) grid8(b.code[h], gb);
-      }
-    } else {
-      // the rounded values are on the grid, so the conversion that packs them is exact
-      uint32_t wa = 0u, wb = 0u;
+    for (int i = 0; i < 8; i += 2) {
+      float za[2], zb[2], db[2];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        words_from(words, 8 * h + i, w);
-        const float x = v[8 * h + i], u = sr_uniform_of_word(w[8 * h + i]);
-        ga[i] = e2m1_sr_value(x * a.enc, u);
-        if (TWO) gb[i] = e2m1_sr_value(x * b.enc, u);
+      for (int j = 0; j < 2; ++j) {
+        const int e = 8 * h + i + j;
+        words_from(words, e, w);
+        const uint32_t noise = sr_noise(w[e]);
+        const uint32_t sa = sr_sum(v[e] * a.enc, noise);
+        za[j] = u2f(sa & kSrKept);
+        uint32_t low = sa & kSrAtRisk;
+        if (TWO) {
+          const float yb = v[e] * b.enc;
+          const uint32_t sb = sr_sum(yb, noise), low_b = sb & kSrAtRisk;
+          zb[j] = u2f(sb & kSrKept);
+          low = low < low_b ? low : low_b;               // one v_min3_u32 with the line below
+          if (ERR == kErrMseEstimate) db[j] = sr_difference(zb[j], yb);
+        }
+        risk = risk < low ? risk : low;
       }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        wa = hw_pk_fp4_sel(wa, ga[2 * j], ga[2 * j + 1], j);
-        if (TWO) wb = hw_pk_fp4_sel(wb, gb[2 * j], gb[2 * j + 1], j);
-      }
-      a.code[h] = wa;
-      if (TWO) b.code[h] = wb;
+      ca = hw_pk_fp4_of_scaled_sel(ca, za[0], za[1], i / 2);
+      if (TWO) cb = hw_pk_fp4_of_scaled_sel(cb, zb[0], zb[1], i / 2);
+      if (TWO && ERR == kErrMseEstimate) error_b.add_pair(db[0], db[1]);
     }
+    a.code[h] = ca;
+    if (TWO) {
+      b.code[h] = cb;
+      if (ERR != kErrNone) {
+        float ga[8];
+        grid8(ca, ga);
+        error_a.add8(ga, v, h, a.dec);
+        if (ERR != kErrMseEstimate) {
+          float gb[8];
+          grid8(cb, gb);
+          error_b.add8(gb, v, h, b.dec);
+        }
+      }
+    }
+  }
+  a.error = error_a.value();
+  if (TWO) b.error = error_b.value();
+}
+
+// The same by the rule in software, which is always valid, with no error or the error as it is defined.
+template <bool TWO, int ERR, typename Words>
+NV_DEV void sr_candidates_by_rule(const float (&v)[16], const Words &words, SrCandidate &a, SrCandidate &b) {
+  CandidateError<ERR> error_a, error_b;
+  uint32_t w[16];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    // the rounded values are on the grid, so the conversion that packs them is exact
+    float ga[8], gb[8];
+    uint32_t wa = 0u, wb = 0u;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      words_from(words, 8 * h + i, w);
+      const float x = v[8 * h + i], u = sr_uniform_of_word(w[8 * h + i]);
+      ga[i] = e2m1_sr_value(x * a.enc, u);
+      if (TWO) gb[i] = e2m1_sr_value(x * b.enc, u);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      wa = hw_pk_fp4_sel(wa, ga[2 * j], ga[2 * j + 1], j);
+      if (TWO) wb = hw_pk_fp4_sel(wb, gb[2 * j], gb[2 * j + 1], j);
+    }
+    a.code[h] = wa;
+    if (TWO) b.code[h] = wb;
     error_a.add8(ga, v, h, a.dec);
     if (TWO) error_b.add8(gb, v, h, b.dec);
   }
   a.error = error_a.value();
   if (TWO) b.error = error_b.value();
+}
+
+// One candidate by the conversion instruction, which lowers `margin` (see e2m1_sr_code_fast: the codes are only valid
+// if it stays above kSrMarginAtRisk).
+template <int ERR, typename Words>
+NV_DEV void sr_candidate_by_conversion(const float (&v)[16], const Words &words, SrCandidate &a, float &margin) {
+  CandidateError<ERR> error;
+  uint32_t w[16];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    // one conversion per element (only the first source position rounds as defined): even
+    // elements into the bytes of one word, odd ones into another
+    uint32_t even = any_register(), odd = any_register();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      words_from(words, 8 * h + i, w);
+      uint32_t &c = i & 1 ? odd : even;
+      c = e2m1_sr_code_fast_sel(c, v[8 * h + i] * a.enc, ~w[8 * h + i], (float)w[8 * h + i], margin, i / 2);
+    }
+    a.code[h] = (even & 0x0f0f0f0fu) | ((odd << 4) & 0xf0f0f0f0u);
+    in_register(a.code[h]);                 // (and not as the two words it is made of)
+    float g[8];
+    if (ERR != kErrNone) grid8(a.code[h], g);
+    error.add8(g, v, h, a.dec);
+  }
+  a.error = error.value();
 }
 
 // One candidate on its own: stochastic rounding by the conversion instruction, redone in software for the rare
@@ -293,11 +349,22 @@ NV_DEV float candidate(const float (&v)[16], const Words &words, float dec, floa
   if (ROUNDING == kRTN) return rtn_candidate<ERR>(v, dec, enc, lo, hi);
   SrCandidate c{dec, enc, {0u, 0u}, 0.0f}, none{};
   float margin = __builtin_inff();
-  sr_candidates<false, ERR, true>(v, words, c, none, margin);
-  if (!(margin > kSrMarginAtRisk)) sr_candidates<false, ERR, false>(v, words, c, none, margin);
+  sr_candidate_by_conversion<ERR>(v, words, c, margin);
+  if (!(margin > kSrMarginAtRisk)) sr_candidates_by_rule<false, ERR>(v, words, c, none);
   lo = c.code[0];
   hi = c.code[1];
   return c.error;
+}
+
+// The same on the subnormal grid, for a candidate whose error nobody asks for.
+template <typename Words>
+NV_DEV void sr_alone(const float (&v)[16], const Words &words, float dec, float enc, uint32_t &lo, uint32_t &hi) {
+  SrCandidate c{dec, enc, {0u, 0u}, 0.0f}, none{};
+  uint32_t risk = ~0u;
+  sr_candidates<false, kErrNone>(v, words, c, none, risk);
+  if (risk == 0u) sr_candidates_by_rule<false, kErrNone>(v, words, c, none);
+  lo = c.code[0];
+  hi = c.code[1];
 }
 
 // The block's squared error exactly as it is defined (Table 3 lines 5-6 / 11-12 in fp32):
@@ -332,6 +399,11 @@ NV_DEV float exact_error(const float (&v)[16], uint32_t lo, uint32_t hi, float d
 //   estimate E':  one rounding in d', at most 9 more per term in the accumulation:
 //     |E' - S| <= 18.1 u S.
 // Hence |E - E'| <= 48.1 u m + 25.2 u S <= 48.1 u dec^2 + 73.3 u S < 64 u (dec^2 + 2 E').
+// The estimate that stochastic rounding on the subnormal grid gives the scale to 4, dec^2 times the sum of (y_i - g_i)^2
+// with y_i = fl(v_i enc), is off by more: y_i dec = v_i (1 + 2.01 u) and |v_i| <= 6 dec + |t_i|, so
+//     |E' - S| <= 96.8 u dec sqrt(S) + 17.5 u S,
+// and with the defined value's own (48.1 u dec sqrt(S) + 7.1 u S) and dec sqrt(S) <= (0.85 dec^2 + S / 0.85) / 2
+// |E - E'| <= 61.6 u dec^2 + 110 u S, still within 64 u (dec^2 + 2 E').
 // Underflow adds absolute errors that no relative bound covers: the contract keeps
 // dec >= 2^-109, so products g*dec and the differences are never inexact for being small,
 // but each of the 16 squares of the defined value and each of the 16 accumulation steps of
@@ -461,8 +533,8 @@ constexpr bool kTogether = ROUNDING == kSR && SELECT != kSelForce4 && SELECT != 
 // The per-block procedure (Table 3 lines 1-14) in one pass.  DEFINED = false: the squared-error rule
 // compares the cheap estimates and reports through `undecided` when they cannot tell (the result is then
 // provisional); true: the errors are evaluated exactly as defined.  The other rules always evaluate the
-// defined errors.  With kTogether, FAST = true uses the conversion instruction and reports through `risky` when
-// its answer may not be the rule's, and false is the rule itself.
+// defined errors.  With kTogether, FAST = true rounds on the subnormal grid (sr_candidates) and reports through `risky`
+// when its answer may not be the rule's, and false is the rule itself.
 template <int ROUNDING, int SELECT, bool DEFINED, bool FAST, typename Words>
 NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
                                        const ScaleConsts &k, const ScaleTable &tab,
@@ -499,11 +571,18 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
     look_up(S6, r6, enc6, m6);
     look_up(S4, r4, enc4, m4);
     SrCandidate c{r6.dec, enc6, {0u, 0u}, 0.0f}, d{r4.dec, enc4, {0u, 0u}, 0.0f};
-    float margin = __builtin_inff();
-    sr_candidates<true, kErr, FAST>(v, words, c, d, margin);
-    if (FAST) risky = !(margin > kSrMarginAtRisk);
+    if constexpr (FAST) {
+      uint32_t risk = ~0u;
+      sr_candidates<true, kErr>(v, words, c, d, risk);
+      // (no scale to 4 that follows from the tensor's own alpha leaves a magnitude above 6)
+      risky = (risk == 0u) | (kErr == kErrMseEstimate && !(b * enc4 <= 6.0f));
+    } else {
+      sr_candidates_by_rule<true, kErr>(v, words, c, d);
+    }
     E6p = c.error;
     E4p = d.error;
+    // (a scale to 4 that is 0 has none for its units to be of; the one to 6 is 0 too then)
+    if (FAST && kErr == kErrMseEstimate) E4p = enc4 == 0.0f ? E6p : E4p * m4;
     r6.lo = c.code[0];
     r6.hi = c.code[1];
     r4.lo = d.code[0];
@@ -512,14 +591,21 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
     // Appendix A.3's second alternative compares round-to-nearest candidates and rounds only the
     // winner stochastically; a single candidate need not be rounded to nearest for that.
     constexpr bool kRound = ROUNDING != kSRAfterRtnSelect || kBoth;
-    constexpr int kCandidate = ROUNDING == kSR ? kSR : kRTN;
+    auto round = [&](const BlockResult &r, float enc, uint32_t &lo, uint32_t &hi) {
+      if constexpr (ROUNDING == kSR) {
+        sr_alone(v, words, r.dec, enc, lo, hi);
+        return 0.0f;
+      } else {
+        return candidate<kRTN, kErr>(v, words, r.dec, enc, lo, hi);
+      }
+    };
     if (kSix) {
       look_up(S6, r6, enc6, m6);
-      if (kRound) E6p = candidate<kCandidate, kErr>(v, words, r6.dec, enc6, r6.lo, r6.hi);
+      if (kRound) E6p = round(r6, enc6, r6.lo, r6.hi);
     }
     if (kFour) {
       look_up(S4, r4, enc4, m4);
-      if (kRound) E4p = candidate<kCandidate, kErr>(v, words, r4.dec, enc4, r4.lo, r4.hi);
+      if (kRound) E4p = round(r4, enc4, r4.lo, r4.hi);
     }
   }
   r4.four = 1u;
@@ -550,7 +636,7 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
 // once more: the rare block whose first pass is not sure of its answer is redone from those as it is
 // defined, so that nothing of the first pass has to stay in registers for it -- keeping the sixteen
 // values and both candidates alive across the common path cost the rowwise kernel three of its
-// eight waves per SIMD.  A block whose estimates were too close is rounded by the instruction once more (one
+// eight waves per SIMD.  A block whose estimates were too close is rounded on the subnormal grid once more (one
 // wave in some hundreds is in the case, and in a small launch all wait for it: with the rule in
 // software 1008 x 4096 took 8.1 us instead of 7.5), a risky one by the rule; the margin of the first pass covers
 // both candidates, whichever the second keeps.

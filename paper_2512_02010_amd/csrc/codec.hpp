@@ -167,29 +167,43 @@ NV_DEV uint32_t e2m1_sr_code_fast(uint32_t old, float y, uint32_t not_w, float w
 }
 constexpr float kSrMarginAtRisk = 2048.0f;
 
-// The same element rounded under two scales: byte SEL of both words, the others kept.  The two conversions
-// stand in one piece of assembly, so that the wait state after them is one for both.
-template <int SEL>
-NV_DEV void e2m1_sr_code_fast2(uint32_t &old_a, uint32_t &old_b, float ya, float yb, uint32_t not_w, float wf,
-                               float &margin) {
+// The same rounding without the conversion instruction, on a grid that fp32 has of its own.  Scaled by
+// 2^-126 the magnitudes below 1 are subnormal, so that as integers the bits of y * 2^-126 rise by 2^22 from each
+// E2M1 magnitude to the next, all the way from 0 to 6: code index = bits >> 22, and what lies above it is
+// the 22 bits below.  With k = w >> 8 as above the sum with 2^22 - (k >> 2) carries into the code iff
+// k >> 2 <= (low 22 bits); the kept bits are the rounded value times 2^-126, sign included.
+//   |y| >= 1: the product is exact, and one step up is right iff k >> 2 < (low 22 bits): the sum is wrong only
+//             where the two are equal, and then its own low 22 bits are 0;
+//   |y| < 1 : the product is rounded to the nearest multiple of 2^-149, so 4 P, P the low 22 bits, is within 2 of
+//             A = frac(2|y|) * 2^24, and k < A can only differ from k < 4 P where k >> 2 is P - 1 or P (modulo
+//             2^22, which also covers a product rounded up to the next grid magnitude): then the sum's
+//             low 22 bits are 1 or 0.
+// So a sum of which bits 1 to 21 are not all zero has the right code, and about one rounding in two million is
+// redone with e2m1_sr_value().  Magnitudes from 6 up may come out as 8 or more (the packing conversion takes those to 6).
+// Cycles per wave and SIMD by the issue rates of the instructions, per rounding of one of two candidates: 16
+// for product, sum, kept bits, risk and half a packing conversion, against 21 for the stochastic conversion
+// and its risk; and the value comes with it, instead of by a conversion back.
+constexpr uint32_t kSrKept = 0xffc00000u, kSrAtRisk = 0x003ffffeu;
+NV_DEV uint32_t sr_noise(uint32_t w) { return 0x00400000u - (w >> 10); }
+// (literals inside the instructions: from a scalar register, where the compiler puts constants this common, both issue
+// at half the rate)
+NV_DEV uint32_t sr_sum(float y, uint32_t noise) {
+  float scaled;
 #ifdef NVFP4_46_CVT_SR_PK_FP4_ON_HOST
-  old_a = e2m1_sr_code_fast<SEL>(old_a, ya, not_w, wf, margin);
-  old_b = e2m1_sr_code_fast<SEL>(old_b, yb, not_w, wf, margin);
+  scaled = y * 0x1p-126f;
 #else
-  const float c = in_odd_vector_register(0x1p33f);
-  const float ta = __builtin_fmaf(fabsf(ya), c, -wf), tb = __builtin_fmaf(fabsf(yb), c, -wf);
-  margin = fminf(fminf(margin, fabsf(ta)), fabsf(ta - 0x1p32f));   // one v_min3_f32
-  margin = fminf(fminf(margin, fabsf(tb)), fabsf(tb - 0x1p32f));
-  const f32x2 sa = {ya, ta}, sb = {yb, tb};
-#define NV_SR2(op_sel)                                                                             \
-  asm("v_cvt_scalef32_sr_pk_fp4_f32 %0, %2, %4, 1.0" op_sel                                        \
-      "\n\tv_cvt_scalef32_sr_pk_fp4_f32 %1, %3, %4, 1.0" op_sel "\n\ts_nop 0"                      \
-      : "+&v"(old_a), "+&v"(old_b) : "v"(sa), "v"(sb), "v"(not_w))
-  if constexpr (SEL == 0) NV_SR2("");
-  else if constexpr (SEL == 1) NV_SR2(" op_sel:[0,0,1,0]");
-  else if constexpr (SEL == 2) NV_SR2(" op_sel:[0,0,0,1]");
-  else NV_SR2(" op_sel:[0,0,1,1]");
-#undef NV_SR2
+  asm("v_mul_f32 %0, 0x00800000, %1" : "=v"(scaled) : "v"(y));
+#endif
+  return f2u(scaled) + noise;
+}
+// y - (kept bits * 2^126)
+NV_DEV float sr_difference(float kept, float y) {
+#ifdef NVFP4_46_CVT_SR_PK_FP4_ON_HOST
+  return __builtin_fmaf(kept, -0x1p126f, y);
+#else
+  float d;
+  asm("v_fmamk_f32 %0, %1, 0xfe800000, %2" : "=v"(d) : "v"(kept), "v"(y));
+  return d;
 #endif
 }
 

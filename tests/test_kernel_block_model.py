@@ -290,3 +290,33 @@ def test_near_ties_with_an_element_at_its_rounding_threshold(rounding):
         got = np.stack((codes[n] & 15, codes[n] >> 4), axis=1).reshape(16)
         bad += not (np.array_equal(got, want["codes"]) and scale[n] == want["S"] and four[n] == want["four"])
     assert bad == 0, (bad, len(v))
+
+
+@pytest.mark.parametrize("select", [ref.SEL_46_MSE, ref.SEL_FORCE6, ref.SEL_FORCE4, ref.SEL_46_MAE, ref.SEL_46_ABSMAX])
+@pytest.mark.parametrize("fit", ["tiny", "subnormal", "own", "saturated", "huge"])
+def test_stochastic_rounding_under_scales_at_the_ends_of_their_range(select, fit):
+    """Stochastic rounding takes its codes from sums on fp32's subnormal grid and one error estimate in units
+    of the scale: block maxima about the smallest scale byte (both bytes 0, one of them 0, both 1 and
+    up), the tensor's own range, and an alpha so small that bytes saturate and magnitudes lie far above 6."""
+    rng = np.random.default_rng(4707)
+    alpha = np.float32(0.37 * 2.0 ** -9)
+    lo, hi = {"tiny": (-13, -8), "subnormal": (-9, -4), "own": (0, 8.5), "saturated": (8, 11), "huge": (11, 60)}[fit]
+    n = 1500
+    b = (np.float32(alpha) * 6.0 * 2.0 ** rng.uniform(lo, hi, (n, 1))).astype(np.float32)
+    v = (b * rng.uniform(-1, 1, (n, 16)) ** 3).astype(np.float32)
+    v[np.arange(n), rng.integers(0, 16, n)] = b[:, 0]
+    v[rng.random((n, 16)) < 0.1] *= np.float32(0.0)                    # zeros of both signs
+    u = (rng.integers(0, 1 << 24, (n, 16)) * 2.0 ** -24).astype(np.float32)
+    u[rng.random((n, 16)) < 0.02] = 0.0                                # the uniform that rounds all but grid values up
+    codes, scale, four = hm.quantize_blocks(v, float(alpha), ref.SR, select, u)
+    zero_scales = chose_four = 0
+    for k in range(n):
+        want = ref.quantize_block(v[k], float(alpha), ref.SR, select, u[k])
+        got = np.stack((codes[k] & 15, codes[k] >> 4), axis=1).reshape(16)
+        assert np.array_equal(got, want["codes"]) and scale[k] == want["S"] and four[k] == want["four"], (k, v[k])
+        zero_scales += scale[k] == 0
+        chose_four += int(four[k])
+    if select == ref.SEL_46_MSE and fit != "huge":
+        assert 0 < chose_four < n
+    if fit == "tiny":
+        assert 0 < zero_scales < n
