@@ -367,16 +367,16 @@ NV_DEV void rht16(float (&v)[16], uint32_t sign_word) {
   hadamard16_quarter(v);
 }
 
-// The same with the sign flips given as sixteen XOR masks (0 or 0x80000000), for callers
-// that meet the same sign word block after block.
+// The sign flips as XOR masks, for callers that meet the same sign word block after block: sixteen, or eight
+// for BF16 elements still packed two to a word (element 2 j in the low half of word j).
 NV_DEV void rht_sign_masks(uint32_t sign_word, uint32_t (&mask)[16]) {
 #pragma unroll
   for (int j = 0; j < 16; ++j) mask[j] = ((sign_word >> j) & 1u) << 31;
 }
-NV_DEV void rht16_masked(float (&v)[16], const uint32_t (&mask)[16]) {
+NV_DEV void rht_sign_masks(uint32_t sign_word, uint32_t (&mask)[8]) {
 #pragma unroll
-  for (int j = 0; j < 16; ++j) v[j] = u2f(f2u(v[j]) ^ mask[j]);
-  hadamard16_quarter(v);
+  for (int j = 0; j < 8; ++j)
+    mask[j] = ((sign_word >> 2 * j) & 1u) << 15 | ((sign_word >> (2 * j + 1)) & 1u) << 31;
 }
 
 }  // namespace nvfp4_46

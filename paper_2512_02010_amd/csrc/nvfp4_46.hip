@@ -424,23 +424,28 @@ __global__ __launch_bounds__(kThreads) void k_flat(
   const uint32_t tid = threadIdx.x;
   const uint32_t rounds = (uint32_t)((nblocks + kThreads - 1) / kThreads);
   const uint32_t tail = (uint32_t)(nblocks - (int64_t)(rounds - 1) * kThreads);  // 1..256
-  // The sign flips of the transform as sixteen XOR masks per lane, in LDS (piece q of lane t at
+  // The sign flips of the transform as one XOR mask per word of a block and lane, in LDS (piece q of lane t at
   // [q][t]: a wave's 128-bit reads are conflict-free).  A lane writes and reads only its own
   // slots, and the LDS operations of one wave execute in order, so no barrier is involved.
-  __shared__ uint4 sign_masks[RHT ? 4 : 1][RHT ? kThreads : 1];
+  using Raw = RawBlock<XF32>;
+  __shared__ uint4 sign_masks[RHT ? Raw::kPieces : 1][RHT ? kThreads : 1];
   uint32_t B_lane = 0, sign_B = 0xffffffffu;
   if (RHT) B_lane = tid % nb_per_row;
-  auto transform = [&](float (&w)[16]) {
-    uint32_t mask[16];
+  // the values of a block as it arrived; BF16 pairs are flipped before they are unpacked (eight instructions
+  // and two LDS reads a block instead of sixteen and four; Hadamard + SR 98 -> 89 registers, five waves per SIMD)
+  auto values = [&](const Raw &raw, float (&w)[16]) {
+    if constexpr (!RHT) {
+      unpack16(raw, w);
+    } else {
+      Raw flipped;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const uint4 m = sign_masks[q][tid];
-      mask[4 * q] = m.x;
-      mask[4 * q + 1] = m.y;
-      mask[4 * q + 2] = m.z;
-      mask[4 * q + 3] = m.w;
+      for (int q = 0; q < Raw::kPieces; ++q) {
+        const uint4 m = sign_masks[q][tid];
+        flipped.w[q] = make_uint4(raw.w[q].x ^ m.x, raw.w[q].y ^ m.y, raw.w[q].z ^ m.z, raw.w[q].w ^ m.w);
+      }
+      unpack16(flipped, w);
+      hadamard16_quarter(w);
     }
-    rht16_masked(w, mask);
   };
   float amax = 0.0f;
   ScaleConsts sc{};
@@ -449,11 +454,8 @@ __global__ __launch_bounds__(kThreads) void k_flat(
 
   // one block, already loaded; `live` = lanes of this round that hold a block (fewer than
   // 256 only in the last round of a ragged tensor)
-  using Raw = RawBlock<XF32>;
   auto work = [&](uint32_t r, uint32_t live, const Raw &raw) {
     const int64_t base = (int64_t)r * kThreads;
-    float v[16];
-    unpack16(raw, v);
     if (RHT) {
       // the sign word depends on the block's position in its row only; with the usual
       // shapes a lane meets the same position in every round and keeps its masks
@@ -461,14 +463,15 @@ __global__ __launch_bounds__(kThreads) void k_flat(
       if (B >= nb_per_row) B -= nb_per_row;
       if (B != sign_B) {
         sign_B = B;
-        uint32_t mask[16];
+        uint32_t mask[4 * Raw::kPieces];
         rht_sign_masks(rht_sign_word(rht_seed, B), mask);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (int q = 0; q < Raw::kPieces; ++q)
           sign_masks[q][tid] = make_uint4(mask[4 * q], mask[4 * q + 1], mask[4 * q + 2], mask[4 * q + 3]);
       }
-      transform(v);
     }
+    float v[16];
+    values(raw, v);
     if (OUT == kOutAmax) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) amax = fmaxf(amax, fabsf(v[i]));
@@ -491,8 +494,7 @@ __global__ __launch_bounds__(kThreads) void k_flat(
     auto again = [&](float (&w)[16], uint32_t (&uu)[16]) {
       Raw r2;
       load_block<XF32>(x + Raw::kPieces * (base + (tid < live ? tid : live - 1)), r2);
-      unpack16(r2, w);
-      if (RHT) transform(w);
+      values(r2, w);
       if constexpr (kAhead && !RHT) {
         // (there is room to keep them: 111 registers instead of 84, and the one wave in some hundreds that comes here
         // ends sooner, 1008 x 4096 7.7 -> 6.9 us; with the transform 123 instead of 98 cost 4 % of any size)
@@ -1377,6 +1379,11 @@ static int launch_flat(const FlatArgs &a) {
   const int64_t rounds = (a.nblocks + kThreads - 1) / kThreads;
   const int cus = compute_units();
   int64_t n_long = 0, rounds_long = 0, grid;
+  // With the transform a workgroup first draws its lanes' sign words, so a tensor of fewer rounds leaves fewer of them to
+  // one-round workgroups, an eighth (Hadamard + SR, us with sixteen rounds per compute unit / an eighth:
+  // 4096 x 4096 24.8 / 23.5, 16384 x 2048 46.9 / 43.3, 8192 x 8192 70.3 / 68.3; from 16384 x 8192 on the same).
+  int64_t short_rounds = (int64_t)cus * kFlatShortRoundsPerCu;
+  if (RHT && short_rounds > rounds / 8) short_rounds = rounds / 8;
   if (OUT == kOutAmax) {
     // the amax pass ends with one access per workgroup to the one result word: few,
     // long-lived workgroups that stride over the whole tensor
@@ -1384,7 +1391,7 @@ static int launch_flat(const FlatArgs &a) {
     if (grid > rounds) grid = rounds;
   } else {
     n_long = (int64_t)cus * kFlatLongWgPerCu;
-    rounds_long = (rounds - (int64_t)cus * kFlatShortRoundsPerCu) / n_long;
+    rounds_long = (rounds - short_rounds) / n_long;
     if (rounds_long < 2) n_long = rounds_long = 0;   // a small tensor: one round per workgroup
     grid = n_long + (rounds - n_long * rounds_long);
   }
@@ -1398,7 +1405,7 @@ static int launch_flat(const FlatArgs &a) {
       if (period <= grid / 2) grid -= grid % period;
     } else if (n_long && period <= n_long / 2) {
       n_long -= n_long % period;
-      rounds_long = (rounds - (int64_t)cus * kFlatShortRoundsPerCu) / n_long;
+      rounds_long = (rounds - short_rounds) / n_long;
       grid = n_long + (rounds - n_long * rounds_long);
     }
   }
