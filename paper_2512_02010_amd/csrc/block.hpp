@@ -534,8 +534,9 @@ constexpr bool kTogether = ROUNDING == kSR && SELECT != kSelForce4 && SELECT != 
 // compares the cheap estimates and reports through `undecided` when they cannot tell (the result is then
 // provisional); true: the errors are evaluated exactly as defined.  The other rules always evaluate the
 // defined errors.  With kTogether, FAST = true rounds on the subnormal grid (sr_candidates) and reports through `risky`
-// when its answer may not be the rule's, and false is the rule itself.
-template <int ROUNDING, int SELECT, bool DEFINED, bool FAST, typename Words>
+// when its answer may not be the rule's, and false is the rule itself.  CONVERSION = true rounds a candidate on its own
+// by the conversion instruction (see quantize_block).
+template <int ROUNDING, int SELECT, bool DEFINED, bool FAST, bool CONVERSION, typename Words>
 NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
                                        const ScaleConsts &k, const ScaleTable &tab,
                                        bool &undecided, bool &risky) {
@@ -592,11 +593,11 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
     // winner stochastically; a single candidate need not be rounded to nearest for that.
     constexpr bool kRound = ROUNDING != kSRAfterRtnSelect || kBoth;
     auto round = [&](const BlockResult &r, float enc, uint32_t &lo, uint32_t &hi) {
-      if constexpr (ROUNDING == kSR) {
+      if constexpr (ROUNDING == kSR && !CONVERSION) {
         sr_alone(v, words, r.dec, enc, lo, hi);
         return 0.0f;
       } else {
-        return candidate<kRTN, kErr>(v, words, r.dec, enc, lo, hi);
+        return candidate<ROUNDING == kSR ? kSR : kRTN, kErr>(v, words, r.dec, enc, lo, hi);
       }
     };
     if (kSix) {
@@ -640,20 +641,22 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
 // wave in some hundreds is in the case, and in a small launch all wait for it: with the rule in
 // software 1008 x 4096 took 8.1 us instead of 7.5), a risky one by the rule; the margin of the first pass covers
 // both candidates, whichever the second keeps.
-template <int ROUNDING, int SELECT, typename Words, typename Again>
+// CONVERSION is for lanes that draw the words of two blocks at once: the words are in registers anyway there, the
+// conversion instruction needs nothing besides.
+template <int ROUNDING, int SELECT, bool CONVERSION = false, typename Words, typename Again>
 NV_DEV BlockResult quantize_block(const float (&v)[16], const Words &words,
                                   const ScaleConsts &k, const ScaleTable &tab, Again &&again) {
   bool undecided = false, risky = false;
-  BlockResult r = quantize_block_pass<ROUNDING, SELECT, false, true>(v, words, k, tab, undecided, risky);
+  BlockResult r = quantize_block_pass<ROUNDING, SELECT, false, true, CONVERSION>(v, words, k, tab, undecided, risky);
   constexpr bool kMayBeRisky = kTogether<ROUNDING, SELECT>;
   if ((SELECT == kSel46 && undecided) || (kMayBeRisky && risky)) {
     float w[16];
     uint32_t ww[16];
     again(w, ww);
     if (kMayBeRisky && risky)
-      r = quantize_block_pass<ROUNDING, SELECT, true, false>(w, ww, k, tab, undecided, risky);
+      r = quantize_block_pass<ROUNDING, SELECT, true, false, CONVERSION>(w, ww, k, tab, undecided, risky);
     else if (SELECT == kSel46)
-      r = quantize_block_pass<ROUNDING, SELECT, true, true>(w, ww, k, tab, undecided, risky);
+      r = quantize_block_pass<ROUNDING, SELECT, true, true, CONVERSION>(w, ww, k, tab, undecided, risky);
   }
   return r;
 }

@@ -910,8 +910,8 @@ __global__ __launch_bounds__(kThreads) void k_tile(
     if constexpr (kDrawn) {
       uint32_t ua[16], ub[16];
       draw(ua, ub);
-      ra = quantize_block<ROUNDING, SELECT>(va, ua, sc, tab, first);
-      rbk = quantize_block<ROUNDING, SELECT>(vb, ub, sc, tab, second);
+      ra = quantize_block<ROUNDING, SELECT, true>(va, ua, sc, tab, first);
+      rbk = quantize_block<ROUNDING, SELECT, true>(vb, ub, sc, tab, second);
     } else {
       constexpr int kStep = 16;
       auto words_of = [&](int column) {
