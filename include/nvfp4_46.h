@@ -9,8 +9,9 @@
  *
  * General conventions (all entry points)
  *   - Every data pointer is a DEVICE pointer owned by the caller.  The library
- *     allocates no memory and keeps no state between calls (the one exception is the
- *     fixed scratch array of nvfp4_46_tensor_scale_static, described there).
+ *     allocates no memory and keeps no state between calls (the one exception is a
+ *     fixed array of scratch words, for nvfp4_46_tensor_scale_static and, apart from those,
+ *     for tensor scales on the default stream; both are zero between calls).
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     Work is enqueued on it and the call returns without synchronising; a call
  *     that fails validation enqueues nothing.
@@ -125,6 +126,8 @@ typedef struct {
  * rht, rht_seed and fp8_max of `p`.
  *   x      in   [rows][cols] BF16 (fp32 with x_dtype = NVFP4_X_F32)
  *   alpha  out  1 float (device); also used as scratch while the kernels run
+ * On the default stream (NULL), whose work is never concurrent and never captured, one launch on scratch words
+ * of the library's own; on any other one launch for a small tensor, else three.
  * Errors: NULL x/p/alpha -> ERR_NULL; bad dims -> ERR_SHAPE; x misaligned -> ERR_ALIGN;
  * bad fp8_max / layout / x_dtype -> ERR_PARAM; rht with both layouts -> ERR_UNSUPPORTED.        */
 int nvfp4_46_tensor_scale(const void *x, const nvfp4_46_params *p, float *alpha,
@@ -148,7 +151,7 @@ int nvfp4_46_tensor_scale_ws(const void *x, const nvfp4_46_params *p, float *alp
 
 /* nvfp4_46_tensor_scale_ws for callers that can neither allocate device memory nor lend any:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  The
- * scratch words live in a 4352-byte static device array inside the library (one copy per
+ * scratch words live in a static device array, 4352 bytes for these calls, inside the library (one copy per
  * GPU, held until the process ends); the call allocates nothing.  The scratch need does not
  * grow with the tensor, so every shape the other entry points accept is accepted (rows, cols
  * <= 2^31, rows * cols <= 2^40; beyond that ERR_SHAPE as everywhere).  Same result as

@@ -1631,7 +1631,7 @@ static int check_workspace(const void *workspace, size_t bytes) {
   return aligned16(workspace) ? NVFP4_OK : NVFP4_ERR_ALIGN;
 }
 
-// Eq. (1) for all three entry points.  scratch == nullptr: the reduction runs on the caller's
+// Eq. (1) for all entry points.  scratch == nullptr: the reduction runs on the caller's
 // alpha word between a zeroing launch and a finishing launch.  Otherwise scratch points at
 // kScratchWords zeroed words and one launch does it all (see AmaxFinish).
 static int tensor_scale(const void *x, const nvfp4_46_params *p, float *alpha, uint32_t *scratch,
@@ -1688,8 +1688,45 @@ using namespace nvfp4_46;
 
 extern "C" {
 
+// Two sets of scratch words, the maximum and ticket words of the one-launch reduction (see AmaxFinish), 4352
+// bytes each; every GPU the library runs on holds its own copy until the process ends.  The first belongs to
+// nvfp4_46_tensor_scale_static, the second to calls on the default stream that bring no workspace.
+// In host code the array's name only stands for the symbol: the device address is looked up once per device
+// and that pointer is what kernels get.
+static __device__ __align__(256) uint32_t scratch[2 * kScratchWords];
+static_assert(kScratchWords * sizeof(uint32_t) == NVFP4_46_TENSOR_SCALE_WS_BYTES, "header and kernels agree on the scratch size");
+
+namespace {
+constexpr int kMaxDevices = 64;
+std::mutex g_scratch_mutex;
+uint32_t *g_scratch_ptr[kMaxDevices];   // per device; nullptr until that device's first call
+
+uint32_t *scratch_of_device() {
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
+  std::lock_guard<std::mutex> lock(g_scratch_mutex);
+  if (!g_scratch_ptr[dev]) {
+    void *sym = nullptr;
+    if (hipGetSymbolAddress(&sym, HIP_SYMBOL(scratch)) != hipSuccess || !sym) return nullptr;
+    g_scratch_ptr[dev] = static_cast<uint32_t *>(sym);
+  }
+  return g_scratch_ptr[dev];
+}
+
+// Scratch words for a call that brings none.  Work on a device's default stream (handle 0, one for all threads) runs in
+// the order of its calls and is never captured into a graph, so one set serves all of it; any other
+// stream gets nullptr, the form of three launches (us per call from Python among others, three / one: BF16 1 MiB
+// 10.0 / 4.8, 8 MiB 9.6 / 4.8, 32 MiB 10.8 / 5.3, 128 MiB 23.6 / 22.0, with the columnwise transform 9.9 / 5.9,
+// 9.8 / 6.0, 12.1 / 7.3 and 26.9 / 23.6; 512 KiB, one workgroup before, 5.4 / 4.7).
+uint32_t *lent_words(void *stream) {
+  if (stream) return nullptr;
+  uint32_t *const words = scratch_of_device();
+  return words ? words + kScratchWords : nullptr;
+}
+}  // namespace
+
 int nvfp4_46_tensor_scale(const void *x, const nvfp4_46_params *p, float *alpha, void *stream) {
-  return tensor_scale(x, p, alpha, nullptr, static_cast<hipStream_t>(stream));
+  return tensor_scale(x, p, alpha, lent_words(stream), static_cast<hipStream_t>(stream));
 }
 
 int nvfp4_46_tensor_scale_ws(const void *x, const nvfp4_46_params *p, float *alpha,
@@ -1700,33 +1737,10 @@ int nvfp4_46_tensor_scale_ws(const void *x, const nvfp4_46_params *p, float *alp
   return tensor_scale(x, p, alpha, static_cast<uint32_t *>(workspace), static_cast<hipStream_t>(stream));
 }
 
-// Scratch of nvfp4_46_tensor_scale_static: the maximum and ticket words of the one-launch
-// reduction (see AmaxFinish), 4352 bytes; every GPU the library runs on holds its own copy
-// until the process ends.  In host code the array's name only stands for the symbol:
-// the device address is looked up once per device and that pointer is what kernels get.
-static __device__ __align__(256) uint32_t scratch[kScratchWords];
-static_assert(kScratchWords * sizeof(uint32_t) == NVFP4_46_TENSOR_SCALE_WS_BYTES, "header and kernels agree on the scratch size");
-
-namespace {
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mutex;
-uint32_t *g_scratch_ptr[kMaxDevices];   // per device; nullptr until that device's first call
-}  // namespace
-
 int nvfp4_46_tensor_scale_static(const void *x, const nvfp4_46_params *p, float *alpha, void *stream) {
-  int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return NVFP4_ERR_HIP;
-  uint32_t *ptr;
-  {
-    std::lock_guard<std::mutex> lock(g_scratch_mutex);
-    if (!g_scratch_ptr[dev]) {
-      void *sym = nullptr;
-      if (hipGetSymbolAddress(&sym, HIP_SYMBOL(scratch)) != hipSuccess || !sym) return NVFP4_ERR_HIP;
-      g_scratch_ptr[dev] = static_cast<uint32_t *>(sym);
-    }
-    ptr = g_scratch_ptr[dev];
-  }
-  return tensor_scale(x, p, alpha, ptr, static_cast<hipStream_t>(stream));
+  uint32_t *const words = scratch_of_device();
+  if (!words) return NVFP4_ERR_HIP;
+  return tensor_scale(x, p, alpha, words, static_cast<hipStream_t>(stream));
 }
 
 int nvfp4_46_quantize(const void *x, const nvfp4_46_params *p, const float *alpha,
@@ -1774,6 +1788,7 @@ int nvfp4_46_scale_quantize(const void *x, const nvfp4_46_params *p, float *alph
   if (rc != NVFP4_OK) return rc;
   const bool xf32 = p->x_dtype == NVFP4_X_F32;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  uint32_t *const words = workspace ? static_cast<uint32_t *>(workspace) : lent_words(stream);
   if (p->layout == NVFP4_ROWWISE && p->rounding == NVFP4_RTN && !p->rht && !p->block2d &&
       scale_and_codes_in_one_launch(p->rows * p->cols * (xf32 ? 4 : 2), workspace != nullptr)) {
     FlatArgs a{xf32, static_cast<const uint4 *>(x), nullptr, static_cast<uint2 *>(codes_row),
@@ -1782,7 +1797,7 @@ int nvfp4_46_scale_quantize(const void *x, const nvfp4_46_params *p, float *alph
                AmaxFinish{nullptr, alpha, p->fp8_max}};
     return dispatch_flat(a, p->rounding, p->select, false, kOutScaleAndCodes);
   }
-  rc = tensor_scale(x, p, alpha, static_cast<uint32_t *>(workspace), s);
+  rc = tensor_scale(x, p, alpha, words, s);
   if (rc != NVFP4_OK) return rc;
   return nvfp4_46_quantize(x, p, alpha, codes_row, scales_row, codes_col, scales_col, choice_row,
                            choice_col, stream);

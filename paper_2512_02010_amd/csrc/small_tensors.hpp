@@ -18,7 +18,8 @@ namespace nvfp4_46 {
 //   512     6.6/6.1   3.9/3.8       6.8/6.6       11.1/10.6   4.4/4.3       7.2/7.1
 //   768     8.9/8.2   4.0/3.9       7.3/7.2       15.5/14.9   4.5/4.4       7.9/7.8
 //   1024    11.2/10.4 4.1/3.9       7.9/7.9       19.9/19.2   4.5/4.4       8.6/8.5
-// With scratch words it replaces one launch by one: as far as it is ahead in the cache and not behind in memory.
+// With scratch words (a workspace, or the library's own on the default stream) it replaces one launch by one: as
+// far as it is ahead in the cache and not behind in memory.
 // Without, it replaces three, which the host pays for: as far as it is not behind when called one by one with x
 // in the cache (us per call among others from Python, BF16: 512 KiB 6.5 / 11.1, 768 KiB 8.9 / 8.7 to 11.4, 896 KiB
 // 9.9 / 8.8 to 12, 1 MiB 11.2 / 11.2; first read from memory 10.7 / 9.5, 15.2 / 8.5, 17.3 / 10.1 and 19.8 / 9.9;
@@ -38,7 +39,9 @@ constexpr bool scale_in_one_workgroup(int64_t bytes, bool has_scratch) {
 //   512     8.1/7.7   7.3/6.9       10.0/9.0       8.5/8.1    8.1/7.5       14.8/13.8
 //   768     10.4/9.9  7.5/7.0       12.5/11.4      10.9/10.3  8.2/7.7       19.5/18.9
 //   896     11.6/10.8 7.6/7.1       11.0/10.4      12.0/11.3  8.3/7.8       11.9/11.4
-// As far as it is ahead in both columns.  (FP32 ended at 256 KiB and the calls without scratch words at 512 while a
+// As far as it is ahead in both columns.  The library's own scratch words on the default stream count as none
+// here: such calls come one by one, where a second launch costs the host more than the reading (us per call from Python,
+// BF16 512 KiB: one launch 8.5, two 10.8).  (FP32 ended at 256 KiB and the calls without scratch words at 512 while a
 // workgroup quantized 1024 blocks.)
 constexpr bool scale_and_codes_in_one_launch(int64_t bytes, bool has_scratch) {
   return bytes <= (int64_t)(has_scratch ? 384 : 768) << 10;
