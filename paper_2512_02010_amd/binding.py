@@ -87,6 +87,8 @@ def lib() -> C.CDLL:
         L.nvfp4_46_fake_quant.argtypes = [vp, pp, vp, vp, vp]
         L.nvfp4_46_gemm.restype = C.c_int
         L.nvfp4_46_gemm.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, i64, u32, u32, vp, vp]
+        L.nvfp4_46_few_rows.restype = C.c_int
+        L.nvfp4_46_few_rows.argtypes = [vp, C.c_float, vp, vp, vp, i64, i64, i64, u32, vp, vp]
         L.nvfp4_46_status_string.restype = C.c_char_p
         L.nvfp4_46_status_string.argtypes = [C.c_int]
         L.nvfp4_46_debug_e2m1_rtn_range.restype = C.c_int
@@ -106,7 +108,7 @@ def lib() -> C.CDLL:
 
 
 NATIVE_ENTRY_POINTS = ("tensor_scale", "tensor_scale_ws", "quantize", "scale_quantize", "dequantize", "fake_quant",
-                       "gemm")
+                       "gemm", "few_rows")
 _native = None
 
 
@@ -353,6 +355,15 @@ def nvfp4_46_gemm(codes_a: torch.Tensor, scales_a: torch.Tensor, alpha_a: torch.
                    torch.float32 if out_dtype == OUT_F32 else torch.bfloat16, codes_a.device)
     return (_native or native()).gemm(codes_a, scales_a, alpha_a, codes_b, scales_b, alpha_b, out_dtype, out,
                                       None if stream is None else _stream(stream), flags)
+
+
+def few_rows(x: torch.Tensor, codes_b: torch.Tensor, scales_b: torch.Tensor, alpha_b: torch.Tensor,
+             flags: int = 0, stream=None) -> torch.Tensor | None:
+    """What ``nvfp4_46_scale_quantize(x)`` and ``nvfp4_46_gemm`` with it as operand A give, in one launch and in BF16,
+    where x is small enough for that to be the faster way; None where it is not."""
+    return (_native or native()).few_rows(
+        x, codes_b, scales_b, alpha_b, None if OUTPUT_ALLOCATOR is _device_empty else OUTPUT_ALLOCATOR,
+        None if stream is None else _stream(stream), flags)
 
 
 # ---- scalar codecs ------------------------------------------------------------------------

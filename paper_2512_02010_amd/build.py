@@ -84,7 +84,7 @@ def build_python(out: Path | None = None) -> Path:
                Path(hipcc()).resolve().parent.parent / "include", sysconfig.get_paths()["include"]]
     tmp = out.with_suffix(f".tmp{os.getpid()}.so")
     subprocess.run([cxx or hipcc(), *host, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", f"-I{ROOT / 'include'}",
+                    f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", f"-I{ROOT / 'include'}", f"-I{PKG / 'csrc'}",
                     *(f for d in include for f in ("-isystem", str(d))), str(PKG / "csrc" / "python.cpp"),
                     "-o", str(tmp), f"-L{home / 'lib'}", "-ltorch_python", "-ltorch", "-lc10", "-lc10_hip"],
                    check=True)

@@ -29,25 +29,26 @@ struct ScaleConsts {
 };
 
 // Fills the table (entry 127, which is no scale byte, carries the two reciprocals
-// of ScaleConsts) and returns the constants.  Ends with a barrier.
-NV_DEV ScaleConsts build_scale_table(ScaleTable &tab, float alpha) {
-  ScaleConsts k;
-  k.c6 = alpha * 6.0f;
-  k.c4 = alpha * 4.0f;
+// of ScaleConsts); after a barrier every lane takes the constants from it.
+NV_DEV void fill_scale_table(ScaleTable &tab, float alpha) {
   for (uint32_t s = threadIdx.x; s < 128u; s += blockDim.x) {
     if (s < 127u) {
       float dec = e4m3_decode(s) * alpha;
       float enc = (dec == 0.0f) ? 0.0f : 1.0f / dec;
       tab.e[s] = make_float4(dec, enc, dec * dec, 0.0f);
     } else {
-      tab.e[s] = make_float4(1.0f / k.c6, 1.0f / k.c4, 0.0f, 0.0f);
+      tab.e[s] = make_float4(1.0f / (alpha * 6.0f), 1.0f / (alpha * 4.0f), 0.0f, 0.0f);
     }
   }
-  __syncthreads();
+}
+NV_DEV ScaleConsts scale_consts(const ScaleTable &tab, float alpha) {
   const float4 r = tab.e[127];
-  k.rc6 = r.x;
-  k.rc4 = r.y;
-  return k;
+  return ScaleConsts{alpha * 6.0f, alpha * 4.0f, r.x, r.y};
+}
+NV_DEV ScaleConsts build_scale_table(ScaleTable &tab, float alpha) {
+  fill_scale_table(tab, alpha);
+  __syncthreads();
+  return scale_consts(tab, alpha);
 }
 
 // The packed FP4 conversions take the destination / source byte as an immediate.

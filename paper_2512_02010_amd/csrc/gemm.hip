@@ -28,10 +28,12 @@
 #include <cmath>
 #include <type_traits>
 
+#include "block.hpp"
 #include "codec.hpp"
 #include "gemm_shapes.hpp"
 #include "launch.hpp"
 #include "nvfp4_46.h"
+#include "tensor.hpp"
 
 namespace nvfp4_46 {
 
@@ -1281,6 +1283,237 @@ __global__ __launch_bounds__(64 * kSkinny16Waves) void k_gemm_skinny16(
   }
 }
 
+// ----------------------------------------------------------------------------------------
+// Few values of x against a quantized weight, in one launch: tensor scale, rowwise round-to-nearest 4/6
+// codes and the product, for at most 16 rows (FewRows says how many values).  Decoding spends its time in launches: the
+// scale and codes of 4096 values take as long as those of 400,000, and the product waits for
+// them.  Here every workgroup quantizes all of x for itself, a few blocks per lane, while its first chunks of B are
+// on their way into LDS, and keeps the codes there; x and B come from memory once, and from the L2 for all
+// workgroups but the first.  What bounds it: the launch, x's way (its maximum comes before anything else), then the
+// quantizing (220 vector instructions per block; a lane has up to four, which take 4 us).  From Python, two calls / this:
+// 1 x 512 x 512 11.5 / 5.3 us, 8 x 2048 x 2048 11.8 / 5.9, 4 x 4096 x 4096 10.9 / 6.7; gemm_shapes.hpp has both in a graph.
+//
+// The product's plan is k_gemm_skinny16's with eight waves: wave w takes the chunks of 256 indices with chunk % 8 == w,
+// B through its own ring of stages (rows of 128 code bytes, 16-byte units swizzled, then the scales two bytes to a
+// word: any K that is a multiple of 32), A's fragments straight from the codes in LDS, whose rows are padded to whole
+// chunks with zeros and 16 bytes, for the banks.  Past the end of K the copies repeat a row's last unit and meet zeros.
+template <int NT>
+struct FewRows {
+  static constexpr int kWaves = 8, kThreads = 64 * kWaves, NST = 2;
+  static constexpr int kBlocks = 4;                          // blocks per lane at most
+  static constexpr int COLS = 16 * NT, NC = COLS / 8;        // copies of codes, and of scales, per chunk
+  static constexpr uint32_t STAGE = COLS * (128 + 32);
+  static constexpr uint32_t padded(uint32_t K) { return (K + SK - 1) / SK * SK; }
+  static constexpr uint32_t code_pitch(uint32_t K) { return padded(K) / 2 + 16; }
+  static constexpr uint32_t scale_pitch(uint32_t K) { return padded(K) / 16 + 4; }
+  static constexpr uint32_t lds(uint32_t M, uint32_t K) {
+    return kWaves * NST * STAGE + M * (code_pitch(K) + scale_pitch(K));
+  }
+};
+static_assert(FewRows<1>::kBlocks * FewRows<1>::kThreads * 16 >= kFewValues, "a block per lane and turn");
+static_assert(FewRows<2>::NST * FewRows<2>::STAGE >= 2 * 4 * 64 * sizeof(float), "a wave's sums fit its stages");
+
+template <int NT>
+__global__ __launch_bounds__(FewRows<NT>::kThreads) void k_few_rows(
+    const uint4 *__restrict__ x, const uint8_t *__restrict__ codes_b, const uint8_t *__restrict__ scales_b,
+    const float *__restrict__ alpha_b, uint16_t *__restrict__ out, uint32_t M, int64_t N, uint32_t K, uint32_t shb,
+    float fp8_max) {
+  typedef FewRows<NT> S;
+  constexpr int W = S::kWaves, NST = S::NST, NC = S::NC, COLS = S::COLS;
+  extern __shared__ __align__(16) uint8_t lds_raw[];
+  __shared__ ScaleTable tab;
+  __shared__ float wave_part[W];
+  const uint32_t t = threadIdx.x, lane = t & 63u;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const uint32_t rr = lane & 15u, g = lane >> 4;
+  // (the compiler's barrier would wait for the copies)
+  auto barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+  // ---- x, and its maximum
+  const uint32_t per_row = K / 16, nblocks = M * per_row;
+  RawBlock<false> raw[S::kBlocks];
+  PlainAmax<false> largest;
+#pragma unroll
+  for (int j = 0; j < S::kBlocks; ++j) {
+    if (j * S::kThreads < nblocks) {                         // the same for all lanes
+      const uint32_t k = t + j * S::kThreads;
+      load_block<false>(x + 2 * (k < nblocks ? k : nblocks - 1), raw[j]);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < S::kBlocks; ++j) {
+    if (j * S::kThreads < nblocks) {
+      largest.fold(raw[j].w[0]);
+      largest.fold(raw[j].w[1]);
+    }
+  }
+  float m = largest.value();
+  // x is there before the first copy, and known to be: a wait for a register of it would wait for the copies too
+  asm volatile("" : "+v"(m));
+  __builtin_amdgcn_s_waitcnt(0x0f70);                        // vmcnt(0)
+
+  // ---- copies of B
+  auto uniform = [](const uint8_t *p) {
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);
+  };
+  const int64_t n0 = (int64_t)blockIdx.x * COLS;
+  const uint32_t row_codes = K / 2, row_scales = K / 16;
+  const uint8_t *gcb = uniform(codes_b + n0 * row_codes), *gsb = uniform(scales_b + (n0 >> shb) * row_scales);
+  const uint32_t lds_wave = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds_raw +
+                            wave * (NST * S::STAGE);
+  uint32_t code_row[NC], code_unit[NC], scale_row[NC];
+#pragma unroll
+  for (int q = 0; q < NC; ++q) {
+    const uint32_t row = 8 * q + (lane >> 3);
+    const uint32_t line = n0 + row < N ? row : (uint32_t)(N - 1 - n0);        // relative to n0
+    code_row[q] = line * row_codes;
+    code_unit[q] = ((lane & 7u) ^ ((row >> 1) & 7u)) * 16u;
+    scale_row[q] = (uint32_t)(((n0 + line) >> shb) - (n0 >> shb)) * row_scales;
+  }
+  auto copy_chunk = [&](uint32_t c, uint32_t stage) {
+    const uint32_t lds = lds_wave + stage * S::STAGE;
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      const uint32_t at = c * (SK / 2) + code_unit[q], last = row_codes - 16u;
+      NV_DMA16(lds + q * 1024, code_row[q] + (at < last ? at : last), gcb);
+    }
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      const uint32_t at = c * (SK / 16) + (lane & 7u) * 2u, last = row_scales - 2u;
+      NV_DMA2(lds + COLS * 128 + q * 256, scale_row[q] + (at < last ? at : last), gsb);
+    }
+  };
+  constexpr int kCopies = 2 * NC;
+  const uint32_t nchunks = (K + SK - 1) / SK;
+  uint32_t c = wave;
+#pragma unroll
+  for (int p = 0; p < NST; ++p)
+    if (c + W * p < nchunks) copy_chunk(c + W * p, p);
+
+  // ---- scale and codes of x
+  m = wave_max(m);
+  if (lane == 0) wave_part[wave] = m;
+  barrier();
+#pragma unroll
+  for (int w = 0; w < W; ++w) m = fmaxf(m, wave_part[w]);
+  const float alpha = alpha_of(m, fp8_max);
+  fill_scale_table(tab, alpha);
+  barrier();
+  const ScaleConsts sc = scale_consts(tab, alpha);
+  const uint32_t code_pitch = S::code_pitch(K), scale_pitch = S::scale_pitch(K);
+  uint8_t *const ca = lds_raw + W * NST * S::STAGE, *const sa = ca + M * code_pitch;
+#pragma unroll
+  for (int j = 0; j < S::kBlocks; ++j) {
+    if (j * S::kThreads < nblocks) {
+      const uint32_t k = t + j * S::kThreads;
+      if (k < nblocks) {
+        float v[16];
+        const uint32_t u[16] = {};
+        unpack16(raw[j], v);
+        auto again = [&](float (&w)[16], uint32_t (&)[16]) { unpack16(raw[j], w); };
+        const BlockResult r = quantize_block<kRTN, kSel46>(v, u, sc, tab, again);
+        const uint32_t row = k / per_row, b = k - row * per_row;
+        *reinterpret_cast<uint2 *>(ca + row * code_pitch + b * 8) = make_uint2(r.lo, r.hi);
+        sa[row * scale_pitch + b] = (uint8_t)r.scale;
+      }
+    }
+  }
+  const uint32_t tail = S::padded(K) / 16 - per_row;          // blocks past the end of a row, at most 14
+  if (t < M * tail) {
+    const uint32_t row = t / tail, b = per_row + t - row * tail;
+    *reinterpret_cast<uint2 *>(ca + row * code_pitch + b * 8) = make_uint2(0u, 0u);
+    sa[row * scale_pitch + b] = 0;
+  }
+  barrier();
+
+  // ---- the product: a lane's share of one operand row for one chunk, as in k_gemm_skinny16
+  struct Raw {
+    uint4 c[2];
+    uint32_t s[2];
+  };
+  const uint32_t ra = rr < M ? rr : M - 1;
+  auto read_a = [&](Raw &f) {
+    const uint8_t *p = ca + ra * code_pitch + c * (SK / 2) + g * 32;
+    f.c[0] = reinterpret_cast<const uint4 *>(p)[0];
+    f.c[1] = reinterpret_cast<const uint4 *>(p)[1];
+    const uint32_t s = *reinterpret_cast<const uint32_t *>(sa + ra * scale_pitch + c * (SK / 16) + g * 4);
+    f.s[0] = __builtin_amdgcn_perm(0u, s, 0x0c010c00u) << 7;
+    f.s[1] = __builtin_amdgcn_perm(0u, s, 0x0c030c02u) << 7;
+  };
+  auto read_b = [&](uint32_t stage, uint32_t row, Raw &f) {
+    const uint8_t *st = lds_raw + (wave * NST + stage) * S::STAGE;
+    const uint32_t swz = (row >> 1) & 7u;
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      f.c[q] = *reinterpret_cast<const uint4 *>(st + row * 128 + (((2 * g + q) ^ swz) * 16));
+    const uint2 s = *reinterpret_cast<const uint2 *>(st + COLS * 128 + row * 32 + g * 8);
+    f.s[0] = __builtin_amdgcn_perm(0u, s.x, 0x0c010c00u) << 7;
+    f.s[1] = __builtin_amdgcn_perm(0u, s.y, 0x0c010c00u) << 7;
+  };
+  auto expand = [&](const Raw &f, int s) {                         // matrix step s = 0..7
+    const uint4 &q = f.c[s >> 2];
+    const uint32_t w = (s & 3) == 0 ? q.x : (s & 3) == 1 ? q.y : (s & 3) == 2 ? q.z : q.w;
+    const h2 pair = __builtin_bit_cast(h2, f.s[s >> 2]);
+    return expand8(w, (s & 2) ? pair.y : pair.x);
+  };
+  f32x4 acc[NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[j][v] = 0.0f;
+  uint32_t stage = 0;
+  auto chunk = [&](auto after) {
+    Raw fa, fb[NT];
+    read_a(fa);
+#pragma unroll
+    for (int j = 0; j < NT; ++j) read_b(stage, 16 * j + rr, fb[j]);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    after();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const h8 a = expand(fa, s);
+#pragma unroll
+      for (int j = 0; j < NT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, expand(fb[j], s), acc[j], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    c += W;
+    stage = stage + 1 == (uint32_t)NST ? 0u : stage + 1;
+  };
+  while (c + W * NST < nchunks) {
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"((NST - 1) * kCopies) : "memory");
+    chunk([&] { copy_chunk(c + W * NST, stage); });
+  }
+  each_number_down<NST>([&](auto p) {
+    if (c + W * decltype(p)::value < nchunks) {
+      asm volatile("s_waitcnt vmcnt(%0)" :: "n"(decltype(p)::value * kCopies) : "memory");
+      chunk([] {});
+    }
+  });
+
+  // ---- each wave's sums into its own (spent) stages; one lane per element adds them in the waves' order
+  float *const own = reinterpret_cast<float *>(lds_raw + wave * (NST * S::STAGE));
+#pragma unroll
+  for (int j = 0; j < NT; ++j)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) own[(4 * j + v) * 64 + lane] = acc[j][v];
+  barrier();
+  const uint32_t e = t >> 6, j = e >> 2, v = e & 3u;
+  if (e < 4 * NT) {
+    float sum = 0.0f;
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+      sum += reinterpret_cast<const float *>(lds_raw + w * (NST * S::STAGE))[e * 64 + lane];
+    const uint32_t row = 4 * g + v;
+    const int64_t col = n0 + 16 * j + rr;
+    if (row < M && col < N)
+      out[row * N + col] = (uint16_t)pack_bf16x2(sum * (alpha * alpha_b[0]), 0.0f);
+  }
+}
+
 static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // The kernels compile side by side when this file is built in parts: NVFP4_46_GEMM_PART =
@@ -1305,6 +1538,17 @@ struct GemmArgs {
   hipStream_t stream;
 };
 
+struct FewRowsArgs {
+  const uint4 *x;
+  const uint8_t *codes_b, *scales_b;
+  const float *alpha_b;
+  uint16_t *out;
+  int64_t M, N, K;
+  uint32_t shb;
+  float fp8_max;
+  hipStream_t stream;
+};
+
 // Every run_* raises the kernel's dynamic LDS limit (most need more than the 64 KiB a
 // kernel gets without asking), launches, and returns a status of the C ABI.
 template <bool KFULL, bool OUTF32>
@@ -1314,6 +1558,7 @@ int run_gemm_dma(const GemmArgs &a);
 int run_gemm_skinny(const GemmArgs &a);
 template <typename S>
 int run_gemm_tile(const GemmArgs &a);
+int run_few_rows(const FewRowsArgs &a);
 
 template <typename Kernel, typename... Args>
 static int launch_with_lds(Kernel kernel, dim3 grid, dim3 block, size_t lds_bytes, hipStream_t s,
@@ -1407,6 +1652,20 @@ int run_gemm_skinny(const GemmArgs &a) {
 #endif
 
 #if NVFP4_46_GEMM_HAS(6)
+int run_few_rows(const FewRowsArgs &a) {
+  auto go = [&](auto kernel, auto shape) {
+    typedef decltype(shape) S;
+    return launch_with_lds(kernel, dim3((uint32_t)((a.N + S::COLS - 1) / S::COLS)), dim3(S::kThreads),
+                           S::lds((uint32_t)a.M, (uint32_t)a.K), a.stream, a.x, a.codes_b, a.scales_b, a.alpha_b,
+                           a.out, (uint32_t)a.M, a.N, (uint32_t)a.K, a.shb, a.fp8_max);
+  };
+  // at most one workgroup per compute unit, in the narrower of the two
+  if ((a.N + 15) / 16 <= kCus) return go(k_few_rows<1>, FewRows<1>{});
+  return go(k_few_rows<2>, FewRows<2>{});
+}
+#endif
+
+#if NVFP4_46_GEMM_HAS(6)
 template <typename S>
 int run_gemm_tile(const GemmArgs &a) {
   auto go = [&](auto kernel) {
@@ -1440,6 +1699,25 @@ NVFP4_46_TILE(Tile256x128)
 #if NVFP4_46_GEMM_PART <= 0
 
 using namespace nvfp4_46;
+
+// Not part of the C ABI: what paper_2512_02010_amd/linear.py runs where few_rows_in_one_launch() says so.  The same
+// codes as nvfp4_46_scale_quantize (rowwise, to nearest, 4/6 by squared error) finds for x [M][K] BF16, their product with B
+// as nvfp4_46_gemm takes it, C in BF16; the same checks and statuses, ERR_UNSUPPORTED for any other size.
+extern "C" int nvfp4_46_few_rows(const void *x, float fp8_max, const void *codes_b, const void *scales_b,
+                                 const float *alpha_b, int64_t M, int64_t N, int64_t K, uint32_t flags, void *out,
+                                 void *stream) {
+  if (!x || !codes_b || !scales_b || !alpha_b || !out) return NVFP4_ERR_NULL;
+  if (M <= 0 || N <= 0 || K <= 0 || K % 32 != 0) return NVFP4_ERR_SHAPE;
+  if (flags & ~(uint32_t)NVFP4_GEMM_B_TILE_SCALES) return NVFP4_ERR_PARAM;
+  if ((flags & NVFP4_GEMM_B_TILE_SCALES) && N % 16 != 0) return NVFP4_ERR_SHAPE;
+  if (!aligned16(x) || !aligned16(codes_b) || !aligned16(scales_b) || !aligned16(out)) return NVFP4_ERR_ALIGN;
+  if (!(fp8_max > 0.0f) || !(fp8_max <= 448.0f)) return NVFP4_ERR_PARAM;
+  if (!few_rows_in_one_launch(M, N, K)) return NVFP4_ERR_UNSUPPORTED;
+  return run_few_rows(FewRowsArgs{static_cast<const uint4 *>(x), static_cast<const uint8_t *>(codes_b),
+                                  static_cast<const uint8_t *>(scales_b), alpha_b, static_cast<uint16_t *>(out), M, N, K,
+                                  (flags & NVFP4_GEMM_B_TILE_SCALES) ? 4u : 0u, fp8_max,
+                                  static_cast<hipStream_t>(stream)});
+}
 
 extern "C" int nvfp4_46_gemm(const void *codes_a, const void *scales_a, const float *alpha_a,
                              const void *codes_b, const void *scales_b, const float *alpha_b,

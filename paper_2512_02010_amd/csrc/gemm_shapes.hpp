@@ -195,4 +195,14 @@ inline GemmKernel choose_gemm(int64_t M, int64_t N, int64_t K, bool f32) {
   if (lanes_of(fastest, M, N) >> 32 == 0) return fastest;
   return (K % GK) == 0 && K <= ((int64_t)1 << 24) ? kGemmDma : kGemmStaged;
 }
+
+// Up to which size x and its product with a quantized weight take one launch (k_few_rows): as far as it is not behind the
+// two launches in a replayed graph (us, two launches / one: 1 x 512 x 512 5.8 / 3.9, 8 x 2048 x 2048 7.8 / 5.6, 12 x 2048
+// x 8192 7.8 / 7.4, 14 x 2048 x 8192 8.2 / 8.1 but 16 x 2048 x 8192 8.0 / 8.7; 7 x 4096 x 4096 9.1 / 8.1, 1 x 8192 x 8192
+// 12.4 / 9.5), and one workgroup per compute unit (1 x 2048 x 28672: 10.7 / 16.0).  Called one by one the two launches
+// take 11 to 12 us at all these sizes, the one 5 to 9.
+constexpr int64_t kFewValues = 28672, kFewColumns = 32 * kCus;
+inline bool few_rows_in_one_launch(int64_t M, int64_t N, int64_t K) {
+  return M <= 16 && M * K <= kFewValues && N <= kFewColumns;
+}
 }  // namespace nvfp4_46

@@ -17,6 +17,7 @@
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include "gemm_shapes.hpp"
 #include "nvfp4_46.h"
 
 namespace {
@@ -33,6 +34,8 @@ struct EntryPoints {
   int (*fake_quant)(const void *, const nvfp4_46_params *, const float *, void *, void *);
   int (*gemm)(const void *, const void *, const float *, const void *, const void *, const float *, int64_t,
               int64_t, int64_t, uint32_t, uint32_t, void *, void *);
+  int (*few_rows)(const void *, float, const void *, const void *, const float *, int64_t, int64_t, int64_t, uint32_t,
+                  void *, void *);
 };
 EntryPoints entry;
 PyObject *error_class;     // Nvfp4Error(status, name of the entry point)
@@ -117,8 +120,8 @@ struct WithoutLock {
 };
 
 // (an allocation may wait for the device, so it is made without the interpreter's lock, as torch.empty does)
-PyObject *new_tensor(at::IntArrayRef shape, at::ScalarType type, PyObject *like) {
-  if (const at::Tensor *l = plain(like)) {
+PyObject *new_tensor(at::IntArrayRef shape, at::ScalarType type, PyObject *like, PyObject *allocate = Py_None) {
+  if (const at::Tensor *l = allocate == Py_None ? plain(like) : nullptr) {
     at::Tensor t;
     {
       WithoutLock others;
@@ -129,7 +132,8 @@ PyObject *new_tensor(at::IntArrayRef shape, at::ScalarType type, PyObject *like)
   const Owned device(PyObject_GetAttrString(like, "device")), sizes(PyTuple_New((Py_ssize_t)shape.size()));
   for (size_t i = 0; i < shape.size(); ++i)
     PyTuple_SET_ITEM(sizes.o, (Py_ssize_t)i, Owned(PyLong_FromLongLong(shape[i])).release());
-  return PyObject_CallFunctionObjArgs(empty, sizes.o, torch::getTHPDtype(type), device.o, nullptr);
+  return PyObject_CallFunctionObjArgs(allocate == Py_None ? empty : allocate, sizes.o, torch::getTHPDtype(type), device.o,
+                                      nullptr);
 }
 
 Owned given_or_new(PyObject *given, at::IntArrayRef shape, at::ScalarType type, PyObject *like) {
@@ -364,6 +368,34 @@ PyObject *gemm(PyObject *const *a, Py_ssize_t n) {
   return out.release();
 }
 
+// x, codes_b, scales_b, alpha_b, allocate, stream, flags: x quantized and multiplied in one launch where that is the
+// faster way and the operands are plain contiguous tensors that fit together; None for anything else, also for what
+// the calls one by one refuse.  `allocate` makes the output, as binding.py's OUTPUT_ALLOCATOR (None: as torch.empty).
+PyObject *few_rows(PyObject *const *a, Py_ssize_t n) {
+  expect(n, 7);
+  const at::Tensor *x = plain(a[0]), *cb = plain(a[1]), *sb = plain(a[2]), *alpha = plain(a[3]);
+  if (!x || x->dim() != 2 || x->scalar_type() != at::kBFloat16) Py_RETURN_NONE;
+  const int64_t M = x->size(0), K = x->size(1);
+  if (M <= 0 || K <= 0 || K % 32 != 0 || !nvfp4_46::few_rows_in_one_launch(M, 1, K)) Py_RETURN_NONE;
+  if (!cb || !sb || !alpha || cb->dim() != 2 || sb->dim() != 2) Py_RETURN_NONE;
+  const int64_t N = cb->size(0);
+  const uint32_t flags = (uint32_t)word(a[6]);
+  const bool tiles = flags & NVFP4_GEMM_B_TILE_SCALES;
+  if (N <= 0 || !nvfp4_46::few_rows_in_one_launch(M, N, K) || cb->size(1) * 2 != K || (tiles && N % 16 != 0) ||
+      sb->size(0) != (tiles ? N / 16 : N) || sb->size(1) != K / 16)
+    Py_RETURN_NONE;
+  for (const at::Tensor *t : {x, cb, sb, alpha})
+    if (!t->is_cuda() || !t->is_contiguous()) Py_RETURN_NONE;
+  for (const at::Tensor *t : {x, cb, sb})
+    if (reinterpret_cast<uintptr_t>(t->data_ptr()) % 16 != 0) Py_RETURN_NONE;
+  Owned out(new_tensor({M, N}, at::kBFloat16, a[0], a[4]));
+  void *const o = pointer(out.o), *const s = stream(a[5]);
+  const void *const px = x->data_ptr(), *const pc = cb->data_ptr(), *const ps = sb->data_ptr();
+  const float *const pa = static_cast<const float *>(alpha->data_ptr());
+  run("nvfp4_46_few_rows", [&] { return entry.few_rows(px, 256.0f, pc, ps, pa, M, N, K, flags, o, s); });
+  return out.release();
+}
+
 // The exception class, torch.empty as (shape, dtype, device), then the addresses of the entry points, one integer
 // each.
 PyObject *connect(PyObject *const *a, Py_ssize_t n) {
@@ -380,6 +412,7 @@ PyObject *connect(PyObject *const *a, Py_ssize_t n) {
 #define NV_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(guarded<f>)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {NV_METHOD(connect),    NV_METHOD(tensor_scale), NV_METHOD(tensor_scale_ws), NV_METHOD(quantize),
                          NV_METHOD(scale_quantize), NV_METHOD(dequantize), NV_METHOD(fake_quant), NV_METHOD(gemm),
+                         NV_METHOD(few_rows),
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "nvfp4_46_python", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

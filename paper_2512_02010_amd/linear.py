@@ -47,8 +47,12 @@ def _columnwise(t, stream, workspace, rht_seed, **kw):
 def fprop(x: torch.Tensor, qw: dict, select: int = B.SEL_46_MSE, stream=None,
           workspace: torch.Tensor | None = None) -> torch.Tensor:
     """y [T][N] BF16 = x W^T."""
-    cx, sx, ax = _rowwise(x, stream, workspace, select=select)
     flags = B.GEMM_B_TILE_SCALES if qw["block2d"] else 0
+    if select == B.SEL_46_MSE:
+        y = B.few_rows(x, qw["codes_row"], qw["scales_row"], qw["alpha"], flags, stream)
+        if y is not None:
+            return y
+    cx, sx, ax = _rowwise(x, stream, workspace, select=select)
     return B.nvfp4_46_gemm(cx, sx, ax, qw["codes_row"], qw["scales_row"], qw["alpha"],
                            out_dtype=B.OUT_BF16, flags=flags, stream=stream)
 

@@ -1,0 +1,95 @@
+"""GPU: scale, codes and product of a few rows in one launch, against the oracle and against the calls one by one."""
+import pytest
+import torch
+
+from oracle import ref
+from paper_2512_02010_amd import binding as B
+from paper_2512_02010_amd import linear as L
+from paper_2512_02010_amd import workloads as wl
+from tests.test_gpu_gemm import _bf16_to_f64, _dev, _alpha, _tolerance
+
+pytestmark = pytest.mark.gpu
+
+
+def _weight(N, K, tiles):
+    bits = wl.bf16_bits(wl.make("c2", N, K))
+    alpha = ref.tensor_scale(bits)
+    codes, scales = (ref.quantize_2d if tiles else ref.quantize)(bits, alpha)[:2]
+    return codes, scales, alpha
+
+
+# rows: one, an odd number, a whole instruction tile; K: below one chunk of 256, ragged, whole chunks, more chunks
+# than the eight waves hold at once (a second turn of the ring, waves without a chunk), the most values there may be;
+# N: less than a workgroup's columns, ragged, and either side of the wider workgroups (256 of 16 columns)
+@pytest.mark.parametrize("M,K", [(1, 32), (1, 256), (3, 160), (16, 96), (5, 2048), (14, 2048), (1, 4384), (6, 4640), (1, 16384),
+                                 (1, 28672)])
+@pytest.mark.parametrize("N,tiles", [(1, False), (17, False), (48, True), (160, True)])
+def test_few_rows_match_the_oracle(M, K, N, tiles):
+    if tiles and K % 16:
+        pytest.skip("16x16 tiles need whole tiles")
+    cb, sb, ab = _weight(N, K, tiles)
+    bits = wl.bf16_bits(wl.make("c3", M, K))
+    aa = ref.tensor_scale(bits)
+    ca, sa, _ = ref.quantize(bits, aa)
+    sb_rows = sb.repeat(16, axis=0) if tiles else sb
+    want, total = ref.gemm(ca, sa, aa, cb, sb_rows, ab, want_abs=True)
+    x = wl.make("c3", M, K).cuda()
+    flags = B.GEMM_B_TILE_SCALES if tiles else 0
+    got = B.few_rows(x, _dev(cb), _dev(sb), _alpha(ab), flags)
+    assert got is not None and got.shape == (M, N) and got.dtype == torch.bfloat16
+    err = abs(_bf16_to_f64(got) - want)
+    assert (err <= _tolerance(want, total, K, B.OUT_BF16)).all(), err.max()
+
+
+@pytest.mark.parametrize("N", [4096, 4097, 8192])
+def test_wide_weights_match_the_calls_one_by_one(N):
+    """Whole chunks: the same sums in the same order but for the number of waves, one rounding to BF16 apart."""
+    w = wl.make("c2", N, 512).cuda()
+    qw = L.quantize_weight(w) if N % 16 == 0 else dict(B.nvfp4_46_scale_quantize(w), block2d=False)
+    x = wl.make("c3", 16, 512).cuda()
+    q = B.nvfp4_46_scale_quantize(x)
+    flags = B.GEMM_B_TILE_SCALES if qw["block2d"] else 0
+    exact = B.nvfp4_46_gemm(q["codes_row"], q["scales_row"], q["alpha"], qw["codes_row"], qw["scales_row"], qw["alpha"],
+                            out_dtype=B.OUT_F32, flags=flags)
+    y = L.fprop(x, qw)
+    assert ((y.float() - exact).abs() <= exact.abs() * 2.0 ** -8 + exact.abs().max() * 2.0 ** -18).all()
+
+
+def test_zeros_and_what_is_left_to_the_calls_one_by_one():
+    qw = L.quantize_weight(wl.make("c2", 64, 256).cuda())
+    zero = torch.zeros((4, 256), dtype=torch.bfloat16, device="cuda")
+    assert not L.fprop(zero, qw).any()
+    args = qw["codes_row"], qw["scales_row"], qw["alpha"], B.GEMM_B_TILE_SCALES
+    x = wl.make("c1", 16, 256).cuda()
+    assert B.few_rows(x, *args) is not None
+    for other in (wl.make("c1", 17, 256).cuda(),                        # too many rows
+                  x.float(),                                            # fp32
+                  wl.make("c1", 16, 512).cuda()[:, ::2],                # not contiguous
+                  wl.make("c1", 16, 512).cuda(),                        # another K
+                  x.reshape(-1), x.cpu()):
+        assert B.few_rows(other, *args) is None
+    for rows, cols, out, one in ((7, 4096, 64, True), (8, 4096, 64, False),         # values: 28672 and more
+                                 (2, 256, 8192, True), (2, 256, 8208, False)):      # columns: 8192 and more
+        w = L.quantize_weight(wl.make("c2", out, cols).cuda())
+        x = wl.make("c1", rows, cols).cuda()
+        y = B.few_rows(x, w["codes_row"], w["scales_row"], w["alpha"], B.GEMM_B_TILE_SCALES)
+        assert (y is not None) == one and L.fprop(x, w).shape == (rows, out)
+
+
+def test_few_rows_on_a_side_stream_and_in_a_graph():
+    qw = L.quantize_weight(wl.make("c2", 96, 512).cuda())
+    x = wl.make("c1", 8, 512).cuda()
+    want = L.fprop(x, qw).clone()
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        assert torch.equal(L.fprop(x, qw, stream=s), want)
+    s.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        y = L.fprop(x, qw)
+    for scale in (1.0, 2.0, -4.0):                                      # exact: a power of two scales x's own scale
+        x.copy_(wl.make("c1", 8, 512).cuda() * scale)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, L.fprop(x, qw)) and torch.equal(y, want * scale)
