@@ -1382,16 +1382,29 @@ struct TileArgs {
   hipStream_t stream;
 };
 
-// Super-tiles of 8 x 16 tiles, smaller along an axis that has fewer tiles (a small tensor
-// would otherwise launch mostly workgroups without a tile).
+// Super-tiles of 8 x 16 tiles where that gives every die about its share, else the largest smaller ones that do (a
+// tensor of few tiles would otherwise be one super-tile, all on one die; us in a replayed graph, 8 x 16 / this:
+// columnwise Hadamard + SR 736 x 1024 11.0 / 8.3, 1008 x 4096 13.2 / 9.6, 4096 x 1024 12.7 / 9.8, 1344 x 2208 13.1 / 9.4; both
+// orientations 8.9 / 5.9, 11.2 / 7.9, 11.3 / 7.8, 11.5 / 7.9).
 static TileMap tile_map(int64_t rows, int64_t cols) {
   const int64_t nt_r = (rows + TR - 1) / TR, nt_c = (cols + TC - 1) / TC;
-  return TileMap{(uint32_t)(nt_c < 8 ? nt_c : 8), (uint32_t)(nt_r < 16 ? nt_r : 16), 0u};
+  TileMap best{1u, 1u, 0u};
+  int64_t best_most = INT64_MAX;
+  for (uint32_t area = 128; area > 0; area /= 2) {     // 8 x 16, 8 x 8, 4 x 8, 4 x 4, ... 1 x 2, 1 x 1
+    const uint32_t sx = area >= 64 ? 8 : area >= 16 ? 4 : area >= 4 ? 2 : 1, sy = area / sx;
+    // tiles of the die that has most, counting places without a tile; fine within a quarter (and one) of its share
+    const int64_t supers = ((nt_c + sx - 1) / sx) * ((nt_r + sy - 1) / sy), most = (supers + 7) / 8 * area;
+    if (most < best_most) {
+      best = TileMap{sx, sy, 0u};
+      best_most = most;
+    }
+    if (most * 32 <= nt_r * nt_c * 5 + 32) break;
+  }
+  return best;
 }
 
 // Whole turns over the eight XCDs, each turn one super-tile per XCD.
-static int tile_grid(int64_t rows, int64_t cols) {
-  const TileMap m = tile_map(rows, cols);
+static int tile_grid(int64_t rows, int64_t cols, TileMap m) {
   const int64_t nt_r = (rows + TR - 1) / TR, nt_c = (cols + TC - 1) / TC;
   const int64_t supers = ((nt_c + m.sx - 1) / m.sx) * ((nt_r + m.sy - 1) / m.sy);
   return (int)(8 * ((supers + 7) / 8) * m.sx * m.sy);
@@ -1399,8 +1412,8 @@ static int tile_grid(int64_t rows, int64_t cols) {
 
 template <bool XF32, int ROUNDING, int SELECT, bool RHT, bool WANT_ROW, int OUT>
 static int launch_tile(const TileArgs &a) {
-  const int grid = tile_grid(a.rows, a.cols);
   TileMap map = tile_map(a.rows, a.cols);
+  const int grid = tile_grid(a.rows, a.cols, map);
   if (runs_backwards(a.rows * a.cols, XF32)) map.last = (uint32_t)grid - 1u;
   return launch(k_tile<XF32, ROUNDING, SELECT, RHT, WANT_ROW, OUT>, dim3(grid), dim3(kThreads), a.stream,
                 a.x, a.alpha, a.codes_row, a.scales_row, a.choice_row, a.codes_col, a.scales_col,
@@ -1756,11 +1769,13 @@ int nvfp4_46_dequantize(const void *codes, const void *scales, const float *alph
     return launch(k_dequant_flat, dim3(grid_for(n8, 16)), dim3(kThreads), s,
                   static_cast<const uint32_t *>(codes), s8, alpha, static_cast<uint4 *>(out_bf16),
                   n8);
+  const TileMap map = tile_map(rows, cols);
+  const dim3 grid(tile_grid(rows, cols, map));
   if (layout == NVFP4_COLWISE)
-    return launch(k_dequant_col<false>, dim3(tile_grid(rows, cols)), dim3(kThreads), s, c8, s8,
-                  alpha, static_cast<uint16_t *>(out_bf16), rows, cols, tile_map(rows, cols));
-  return launch(k_dequant_col<true>, dim3(tile_grid(rows, cols)), dim3(kThreads), s, c8, s8, alpha,
-                static_cast<uint16_t *>(out_bf16), rows, cols, tile_map(rows, cols));
+    return launch(k_dequant_col<false>, grid, dim3(kThreads), s, c8, s8, alpha, static_cast<uint16_t *>(out_bf16), rows,
+                  cols, map);
+  return launch(k_dequant_col<true>, grid, dim3(kThreads), s, c8, s8, alpha, static_cast<uint16_t *>(out_bf16), rows, cols,
+                map);
 }
 
 int nvfp4_46_fake_quant(const void *x, const nvfp4_46_params *p, const float *alpha,
