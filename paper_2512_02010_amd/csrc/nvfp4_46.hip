@@ -1011,7 +1011,7 @@ __global__ __launch_bounds__(kThreads) void k_block2d(
     const void *__restrict__ x_any, const float *__restrict__ alpha_p, uint8_t *__restrict__ codes,
     uint8_t *__restrict__ scales, uint8_t *__restrict__ choice, uint8_t *__restrict__ codes_col,
     uint8_t *__restrict__ scales_col, uint8_t *__restrict__ choice_col,
-    uint16_t *__restrict__ out_bf16, int64_t rows, int64_t cols, uint64_t sr_seed, uint32_t backwards) {
+    uint16_t *__restrict__ out_bf16, int64_t rows, int64_t cols, uint64_t sr_seed, uint32_t steps_log, uint32_t backwards) {
   __shared__ ScaleTable tab;
   const ScaleConsts sc = build_scale_table(tab, *alpha_p);
   const uint32_t tid = threadIdx.x, r_in_tile = tid & 15u, grp = tid >> 4;
@@ -1029,19 +1029,20 @@ __global__ __launch_bounds__(kThreads) void k_block2d(
   //    time by the workgroup;
   //  * with the packing for the transposed matrix as well, whose codes are 8 bytes per lane 4 KiB
   //    and more apart (stored like that they cost 1.9x their bytes in HBM writes and 35 us on
-  //    8192 x 8192): workgroup id -> a unit of 16 tile rows x 4 tile columns, taken in four
+  //    8192 x 8192): workgroup id -> a unit of 4 or 8 tile rows (see the launcher) x 4 tile columns, taken in
   //    steps of 4 x 4 tiles (wave w: tile row 4 * step + w; its four groups: the tile columns).
-  //    The unit's transposed codes (64 rows of the transposed matrix x 16 pieces of 8 bytes) are
-  //    gathered in LDS and leave as whole 128-byte lines; row codes leave as 32 contiguous bytes
-  //    per store instruction, and id -> unit keeps the four units that share their 128-byte
-  //    lines on one die's L2 (ids 8 apart).
+  //    The unit's transposed codes (64 rows of the transposed matrix x 4 or 8 pieces of 8 bytes) are
+  //    gathered in LDS and leave as runs of 32 or 64 bytes; row codes leave as 32 contiguous bytes
+  //    per store instruction, and id -> unit keeps the four units that share the 128-byte
+  //    lines of row codes on one die's L2 (ids 8 apart).
   constexpr bool by_units = BY_UNITS;
   static_assert(!BY_UNITS || OUT == kOutCodes, "units are for the transposed packing");
   __shared__ uint2 col_stage[BY_UNITS ? 64 * kColStagePitch : 1];
   const uint32_t wave = tid >> 6, g4 = grp & 3u;
-  const uint32_t ncq = (ncb + 3u) / 4u, n_units = ((nrb + 15u) / 16u) * ncq;
+  const uint32_t ncq = (ncb + 3u) / 4u, unit_rows = 4u << steps_log;
+  const uint32_t n_units = ((nrb + unit_rows - 1u) / unit_rows) * ncq;
   const uint32_t n_ids = by_units ? ((n_units + 31u) / 32u) * 32u : (uint32_t)((n_tiles + 15u) / 16u);
-  const uint32_t n_steps = by_units ? 4u : 1u;
+  const uint32_t n_steps = by_units ? 1u << steps_log : 1u;
   auto tile_body = [&](uint32_t tr, uint32_t tc, uint32_t trl) {
     const uint64_t row = (uint64_t)tr * 16 + r_in_tile;
     const uint64_t first = row * (uint64_t)cols + tc * 16u;  // flat index of the lane's first element
@@ -1155,7 +1156,7 @@ __global__ __launch_bounds__(kThreads) void k_block2d(
       uint32_t tr, tc, trl = step * 4u + wave;
       bool live;
       if (by_units) {
-        tr = mr * 16u + trl;
+        tr = mr * unit_rows + trl;
         tc = cq * 4u + g4;
         live = unit < n_units && tr < nrb && tc < ncb;
       } else {
@@ -1165,16 +1166,16 @@ __global__ __launch_bounds__(kThreads) void k_block2d(
         live = (uint64_t)id * 16u + grp < n_tiles;
       }
       if (live) tile_body(tr, tc, trl);
-      if (by_units && step == 3u) {
-        // the unit's 64 rows of the transposed matrix, 16 pieces of 8 bytes each: sixteen
-        // consecutive lanes store one 128-byte line
+      if (by_units && step == n_steps - 1u) {
+        // the unit's 64 rows of the transposed matrix, 4 or 8 pieces of 8 bytes each, which as many
+        // consecutive lanes store
         __syncthreads();
         if (unit < n_units) {
 #pragma unroll 1
-          for (uint32_t j = 0; j < 4; ++j) {
-            const uint32_t piece = tid + j * kThreads, line = piece >> 4, k = piece & 15u;
+          for (uint32_t j = 0; j < n_steps; ++j) {
+            const uint32_t piece = tid + j * kThreads, line = piece >> (2u + steps_log), k = piece & (unit_rows - 1u);
             const uint64_t col = ((uint64_t)cq * 4 + (line >> 4)) * 16 + (line & 15u);
-            const uint32_t tr_k = mr * 16u + k;
+            const uint32_t tr_k = mr * unit_rows + k;
             if (col < (uint64_t)cols && tr_k < nrb)
               *reinterpret_cast<uint2 *>(codes_col + col * (uint64_t)(rows / 2) + tr_k * 8u) =
                   col_stage[line * kColStagePitch + k];
@@ -1459,13 +1460,18 @@ static int launch_block2d(const Block2dArgs &a, int out) {
   // ids as the kernel counts them: sixteen tiles each, or - with the transposed packing - units
   // of 16 x 4 tiles in whole groups of 32
   const int64_t tiles = (a.rows / 16) * (a.cols / 16);
-  const int64_t units = ((a.rows / 16 + 15) / 16) * ((a.cols / 16 + 3) / 4);
+  // Units are 4 tile rows high where those are at most four workgroups per compute unit, else 8: a unit's steps follow
+  // each other (fp32, us in a replayed graph, 16 / 8 / 4 tile rows: 512 x 512 8.4 / 5.5 / 4.0, 1024 x 1024 8.6 / 5.7 / 4.2,
+  // 2048 x 2048 9.1 / 6.7 / 6.0, 4096 x 2048 11.4 / 9.7 / 11.3, 4096 x 4096 20.1 / 19.3 / 18.2, 8192 x 8192 80.7 / 78.5 / 80.8).
+  auto units_of = [&](uint32_t log) { return ((a.rows / 16 + (4 << log) - 1) / (4 << log)) * ((a.cols / 16 + 3) / 4); };
+  const uint32_t steps_log = units_of(0) <= 4 * (int64_t)compute_units() ? 0u : 1u;
+  const int64_t units = units_of(steps_log);
   const int64_t ids = out == kOutCodes && a.codes_col ? ((units + 31) / 32) * 32 : (tiles + 15) / 16;
   const int grid = grid_for(ids * kThreads, 16);
   auto go = [&](auto kernel) {
     return launch(kernel, dim3(grid), dim3(kThreads), a.stream, a.x, a.alpha, a.codes, a.scales,
                   a.choice, a.codes_col, a.scales_col, a.choice_col, a.out, a.rows, a.cols,
-                  a.sr_seed, runs_backwards(a.rows * a.cols, XF32));
+                  a.sr_seed, steps_log, runs_backwards(a.rows * a.cols, XF32));
   };
   if (out == kOutCodes && a.codes_col) return go(k_block2d<XF32, ROUNDING, SELECT, kOutCodes, true>);
   if (out == kOutCodes) return go(k_block2d<XF32, ROUNDING, SELECT, kOutCodes, false>);
