@@ -267,13 +267,12 @@ __global__ __launch_bounds__(kSmallThreads) void k_scale_small(const uint4 *__re
 #endif
 
 // max|y| over the Hadamard-transformed column blocks (16 consecutive rows of one column),
-// without LDS: a lane loads one 16-byte piece from each of the 16 rows of a row block -- 8
-// BF16 or 4 fp32 columns, a wave's loads cover 1 KiB of each row -- and transforms every
-// column in registers.  The signs depend on the row only, so they are flipped in the packed
+// without LDS: a lane loads WORDS words (one, or four: 8 BF16 or 4 fp32 columns, a wave's loads cover 1 KiB of each
+// row) from each of the 16 rows of a row block and transforms every column in registers.  The signs depend on the row only, so they are flipped in the packed
 // words; the factor 1/4 of the transform is applied once to the maximum (scaling by a power
 // of two is monotonic, so the maximum of the scaled values is the scaled maximum).
-template <bool XF32>
-__global__ __launch_bounds__(kThreads) void k_amax_rht_col(const uint4 *__restrict__ x,
+template <bool XF32, int WORDS>
+__global__ __launch_bounds__(kThreads) void k_amax_rht_col(const uint32_t *__restrict__ x,
                                                            int64_t row_blocks, int64_t pieces_per_row,
                                                            uint64_t rht_seed, uint32_t *amax_bits,
                                                            AmaxFinish fin) {
@@ -282,32 +281,27 @@ __global__ __launch_bounds__(kThreads) void k_amax_rht_col(const uint4 *__restri
   float m = 0.0f;
   for (int64_t item = (int64_t)blockIdx.x * kThreads + threadIdx.x; item < items; item += stride) {
     const int64_t rb = item / pieces_per_row, piece = item - rb * pieces_per_row;
-    const uint4 *src = x + rb * 16 * pieces_per_row + piece;
-    uint4 w[16];
+    const uint32_t *src = x + (rb * 16 * pieces_per_row + piece) * WORDS;
+    struct alignas(4 * WORDS) Piece {
+      uint32_t w[WORDS];
+    } p[16];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) w[j] = load_stream(src + j * pieces_per_row);
+    for (int j = 0; j < 16; ++j) p[j] = *reinterpret_cast<const Piece *>(src + j * pieces_per_row * WORDS);
     const uint32_t sw = rht_sign_word(rht_seed, (uint64_t)rb);
     constexpr uint32_t kSignBits = XF32 ? 0x80000000u : 0x80008000u;
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       const uint32_t flip = (0u - ((sw >> j) & 1u)) & kSignBits;    // row j of the block
-      w[j].x ^= flip;
-      w[j].y ^= flip;
-      w[j].z ^= flip;
-      w[j].w ^= flip;
+#pragma unroll
+      for (int q = 0; q < WORDS; ++q) p[j].w[q] ^= flip;
     }
 #pragma unroll
-    for (int c = 0; c < (XF32 ? 4 : 8); ++c) {
+    for (int c = 0; c < (XF32 ? WORDS : 2 * WORDS); ++c) {
       float v[16];
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
-        if constexpr (XF32) {
-          v[j] = u2f(c == 0 ? w[j].x : c == 1 ? w[j].y : c == 2 ? w[j].z : w[j].w);
-        } else {
-          const uint32_t word = (c >> 1) == 0 ? w[j].x : (c >> 1) == 1 ? w[j].y
-                              : (c >> 1) == 2 ? w[j].z : w[j].w;
-          v[j] = u2f((c & 1) ? (word & 0xffff0000u) : (word << 16));
-        }
+        const uint32_t word = p[j].w[XF32 ? c : c >> 1];
+        v[j] = u2f(XF32 || (c & 1) ? (XF32 ? word : word & 0xffff0000u) : word << 16);
       }
       // the butterflies of rht16() (strides 1, 2, 4, 8), signs already applied, no scaling
 #pragma unroll
@@ -1614,13 +1608,19 @@ static int tensor_scale(const void *x, const nvfp4_46_params *p, float *alpha, u
     rc = xf32 ? launch_flat<true, kRTN, kSel46, true, kOutAmax>(a)
               : launch_flat<false, kRTN, kSel46, true, kOutAmax>(a);
   } else {
-    // columnwise blocks (rows % 16 == 0, cols % 8 == 0): 16-byte pieces of 8 BF16 / 4 fp32 columns
-    const int64_t row_blocks = p->rows / 16, pieces = xf32 ? p->cols / 4 : p->cols / 8;
-    const dim3 grid(grid_for(row_blocks * pieces, kAmaxRhtColWgPerCu));
-    rc = xf32 ? launch(k_amax_rht_col<true>, grid, dim3(kThreads), s, x4, row_blocks, pieces,
-                       p->rht_seed, amax, fin)
-              : launch(k_amax_rht_col<false>, grid, dim3(kThreads), s, x4, row_blocks, pieces,
-                       p->rht_seed, amax, fin);
+    // columnwise blocks (rows % 16 == 0, cols % 8 == 0): 16 bytes of a row per lane, or 4 where those are still
+    // no more than two waves per SIMD (a lane's columns follow each other: us in a replayed graph, 16 / 4 bytes, BF16 256 x
+    // 512 5.5 / 4.65, 736 x 1024 5.75 / 4.65, 1344 x 2208 5.8 / 5.2, 1008 x 4096 5.85 / 5.5, 2048 x 4096 6.25 / 6.8, 4096 x 4096
+    // 7.5 / 9.0; fp32 736 x 1024 5.0 / 4.5, 4096 x 4096 14.8 / 16.4; 8 bytes lie between)
+    const int64_t row_blocks = p->rows / 16, words = p->cols / (xf32 ? 1 : 2);
+    auto go = [&](auto kernel, int64_t pieces) {
+      return launch(kernel, dim3(grid_for(row_blocks * pieces, kAmaxRhtColWgPerCu)), dim3(kThreads), s,
+                    static_cast<const uint32_t *>(x), row_blocks, pieces, p->rht_seed, amax, fin);
+    };
+    if (row_blocks * words <= (int64_t)1 << 17)
+      rc = xf32 ? go(k_amax_rht_col<true, 1>, words) : go(k_amax_rht_col<false, 1>, words);
+    else
+      rc = xf32 ? go(k_amax_rht_col<true, 4>, words / 4) : go(k_amax_rht_col<false, 4>, words / 4);
   }
   if (rc != NVFP4_OK || scratch) return rc;
   return launch(k_finish_alpha, dim3(1), dim3(1), s, alpha, p->fp8_max);
