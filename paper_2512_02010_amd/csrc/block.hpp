@@ -29,26 +29,32 @@ struct ScaleConsts {
 };
 
 // Fills the table (entry 127, which is no scale byte, carries the two reciprocals
-// of ScaleConsts); after a barrier every lane takes the constants from it.
-NV_DEV void fill_scale_table(ScaleTable &tab, float alpha) {
+// of ScaleConsts); after a barrier every lane takes those from it.
+NV_DEV ScaleConsts fill_scale_table(ScaleTable &tab, float alpha) {
+  ScaleConsts k;
+  k.c6 = alpha * 6.0f;
+  k.c4 = alpha * 4.0f;
   for (uint32_t s = threadIdx.x; s < 128u; s += blockDim.x) {
     if (s < 127u) {
       float dec = e4m3_decode(s) * alpha;
       float enc = (dec == 0.0f) ? 0.0f : 1.0f / dec;
       tab.e[s] = make_float4(dec, enc, dec * dec, 0.0f);
     } else {
-      tab.e[s] = make_float4(1.0f / (alpha * 6.0f), 1.0f / (alpha * 4.0f), 0.0f, 0.0f);
+      tab.e[s] = make_float4(1.0f / k.c6, 1.0f / k.c4, 0.0f, 0.0f);
     }
   }
+  return k;
 }
-NV_DEV ScaleConsts scale_consts(const ScaleTable &tab, float alpha) {
+NV_DEV void take_reciprocals(const ScaleTable &tab, ScaleConsts &k) {
   const float4 r = tab.e[127];
-  return ScaleConsts{alpha * 6.0f, alpha * 4.0f, r.x, r.y};
+  k.rc6 = r.x;
+  k.rc4 = r.y;
 }
 NV_DEV ScaleConsts build_scale_table(ScaleTable &tab, float alpha) {
-  fill_scale_table(tab, alpha);
+  ScaleConsts k = fill_scale_table(tab, alpha);
   __syncthreads();
-  return scale_consts(tab, alpha);
+  take_reciprocals(tab, k);
+  return k;
 }
 
 // The packed FP4 conversions take the destination / source byte as an immediate.

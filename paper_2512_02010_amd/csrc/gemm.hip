@@ -1400,9 +1400,9 @@ __global__ __launch_bounds__(FewRows<NT>::kThreads) void k_few_rows(
 #pragma unroll
   for (int w = 0; w < W; ++w) m = fmaxf(m, wave_part[w]);
   const float alpha = alpha_of(m, fp8_max);
-  fill_scale_table(tab, alpha);
+  ScaleConsts sc = fill_scale_table(tab, alpha);
   barrier();
-  const ScaleConsts sc = scale_consts(tab, alpha);
+  take_reciprocals(tab, sc);
   const uint32_t code_pitch = S::code_pitch(K), scale_pitch = S::scale_pitch(K);
   uint8_t *const ca = lds_raw + W * NST * S::STAGE, *const sa = ca + M * code_pitch;
 #pragma unroll

@@ -1023,10 +1023,10 @@ __global__ __launch_bounds__(kThreads) void k_block2d(
   //    time by the workgroup;
   //  * with the packing for the transposed matrix as well, whose codes are 8 bytes per lane 4 KiB
   //    and more apart (stored like that they cost 1.9x their bytes in HBM writes and 35 us on
-  //    8192 x 8192): workgroup id -> a unit of 4 or 8 tile rows (see the launcher) x 4 tile columns, taken in
+  //    8192 x 8192): workgroup id -> a unit of 4, 8 or 16 tile rows (see the launcher) x 4 tile columns, taken in
   //    steps of 4 x 4 tiles (wave w: tile row 4 * step + w; its four groups: the tile columns).
-  //    The unit's transposed codes (64 rows of the transposed matrix x 4 or 8 pieces of 8 bytes) are
-  //    gathered in LDS and leave as runs of 32 or 64 bytes; row codes leave as 32 contiguous bytes
+  //    The unit's transposed codes (64 rows of the transposed matrix x 4 to 16 pieces of 8 bytes) are
+  //    gathered in LDS and leave as runs of 32 to 128 bytes; row codes leave as 32 contiguous bytes
   //    per store instruction, and id -> unit keeps the four units that share the 128-byte
   //    lines of row codes on one die's L2 (ids 8 apart).
   constexpr bool by_units = BY_UNITS;
@@ -1161,7 +1161,7 @@ __global__ __launch_bounds__(kThreads) void k_block2d(
       }
       if (live) tile_body(tr, tc, trl);
       if (by_units && step == n_steps - 1u) {
-        // the unit's 64 rows of the transposed matrix, 4 or 8 pieces of 8 bytes each, which as many
+        // the unit's 64 rows of the transposed matrix, 4 to 16 pieces of 8 bytes each, which as many
         // consecutive lanes store
         __syncthreads();
         if (unit < n_units) {
@@ -1377,23 +1377,31 @@ struct TileArgs {
   hipStream_t stream;
 };
 
-// Super-tiles of 8 x 16 tiles where that gives every die about its share, else the largest smaller ones that do (a
-// tensor of few tiles would otherwise be one super-tile, all on one die; us in a replayed graph, 8 x 16 / this:
-// columnwise Hadamard + SR 736 x 1024 11.0 / 8.3, 1008 x 4096 13.2 / 9.6, 4096 x 1024 12.7 / 9.8, 1344 x 2208 13.1 / 9.4; both
-// orientations 8.9 / 5.9, 11.2 / 7.9, 11.3 / 7.8, 11.5 / 7.9).
+// Super-tiles of 8 x 16 tiles (no larger than the tensor) where that gives every die about its share, or no die more
+// tiles than its 32 compute units, else the largest smaller ones that do: a tensor of few tiles would otherwise be one
+// super-tile, all on one die (us in a replayed graph, 8 x 16 / this: columnwise Hadamard + SR 736 x 1024 11.0 / 8.3, 1008 x
+// 4096 13.2 / 9.6, 1344 x 2208 13.1 / 9.4; both orientations 336 x 1184 6.7 / 5.9, 736 x 1024 8.9 / 5.9, 1008 x 4096 11.2 / 7.9,
+// 5248 x 6192 38.5 / 34.4; one tile per compute unit of one die or spread over all: 848 x 208 5.8 / 6.0).
 static TileMap tile_map(int64_t rows, int64_t cols) {
   const int64_t nt_r = (rows + TR - 1) / TR, nt_c = (cols + TC - 1) / TC;
   TileMap best{1u, 1u, 0u};
   int64_t best_most = INT64_MAX;
   for (uint32_t area = 128; area > 0; area /= 2) {     // 8 x 16, 8 x 8, 4 x 8, 4 x 4, ... 1 x 2, 1 x 1
-    const uint32_t sx = area >= 64 ? 8 : area >= 16 ? 4 : area >= 4 ? 2 : 1, sy = area / sx;
-    // tiles of the die that has most, counting places without a tile; fine within a quarter (and one) of its share
-    const int64_t supers = ((nt_c + sx - 1) / sx) * ((nt_r + sy - 1) / sy), most = (supers + 7) / 8 * area;
+    const uint32_t wide = area >= 64 ? 8 : area >= 16 ? 4 : area >= 4 ? 2 : 1, high = area / wide;
+    const uint32_t sx = nt_c < wide ? (uint32_t)nt_c : wide, sy = nt_r < high ? (uint32_t)nt_r : high;
+    const int64_t across = (nt_c + sx - 1) / sx, supers = across * ((nt_r + sy - 1) / sy);
+    if (supers > 64) return TileMap{sx, sy, 0u};       // more than eight turns even out
+    int64_t tiles[8] = {}, most = 0;                   // of each die
+    for (int64_t S = 0; S < supers; ++S) {
+      const int64_t right = nt_c - S % across * sx, down = nt_r - S / across * sy;
+      tiles[S & 7] += (right < sx ? right : sx) * (down < sy ? down : sy);
+    }
+    for (int64_t t : tiles) most = t > most ? t : most;
     if (most < best_most) {
       best = TileMap{sx, sy, 0u};
       best_most = most;
     }
-    if (most * 32 <= nt_r * nt_c * 5 + 32) break;
+    if (most <= 32 || most * 32 <= nt_r * nt_c * 5) break;      // within a quarter of an eighth
   }
   return best;
 }
@@ -1454,11 +1462,13 @@ static int launch_block2d(const Block2dArgs &a, int out) {
   // ids as the kernel counts them: sixteen tiles each, or - with the transposed packing - units
   // of 16 x 4 tiles in whole groups of 32
   const int64_t tiles = (a.rows / 16) * (a.cols / 16);
-  // Units are 4 tile rows high where those are at most four workgroups per compute unit, else 8: a unit's steps follow
-  // each other (fp32, us in a replayed graph, 16 / 8 / 4 tile rows: 512 x 512 8.4 / 5.5 / 4.0, 1024 x 1024 8.6 / 5.7 / 4.2,
-  // 2048 x 2048 9.1 / 6.7 / 6.0, 4096 x 2048 11.4 / 9.7 / 11.3, 4096 x 4096 20.1 / 19.3 / 18.2, 8192 x 8192 80.7 / 78.5 / 80.8).
+  // Units are 4 tile rows high where those are at most four workgroups per compute unit, 8 where at most eight, else 16: a
+  // unit's steps follow each other, a high unit stores longer runs (fp32, us in a replayed graph, 16 / 8 / 4 tile rows:
+  // 512 x 512 8.4 / 5.5 / 4.0, 1024 x 1024 8.6 / 5.7 / 4.2, 2048 x 2048 9.1 / 6.7 / 6.0, 4096 x 2048 11.4 / 9.7 / 11.3, 4096 x 4096
+  // 20.1 / 19.3 / 18.2; with its scale before it 8192 x 8192 110.0 / 111.5 / -).
   auto units_of = [&](uint32_t log) { return ((a.rows / 16 + (4 << log) - 1) / (4 << log)) * ((a.cols / 16 + 3) / 4); };
-  const uint32_t steps_log = units_of(0) <= 4 * (int64_t)compute_units() ? 0u : 1u;
+  const int64_t cus = compute_units();
+  const uint32_t steps_log = units_of(0) <= 4 * cus ? 0u : units_of(1) <= 8 * cus ? 1u : 2u;
   const int64_t units = units_of(steps_log);
   const int64_t ids = out == kOutCodes && a.codes_col ? ((units + 31) / 32) * 32 : (tiles + 15) / 16;
   const int grid = grid_for(ids * kThreads, 16);
