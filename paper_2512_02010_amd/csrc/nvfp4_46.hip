@@ -131,7 +131,8 @@ struct AmaxFinish {
 };
 constexpr uint32_t kAmaxGroups = 16;
 constexpr uint32_t kScratchStride = 32;   // words between two slots: one 128-byte line each
-// slot g: maximum of group g; slot 16 + g: its ticket; slot 32 is not used; slot 33: top ticket
+// slot g: maximum of group g; slot 16 + g: its ticket; slot 33: top ticket.  Two tensors in one launch: the second has
+// the upper eight groups and slot 32 for its top ticket.
 constexpr uint32_t kScratchWords = (2 * kAmaxGroups + 2) * kScratchStride;
 constexpr uint32_t kGroupMayQueue = 32;   // members from which on a group's maximum is looked at before it is raised
 NV_DEV uint32_t *scratch_slot(uint32_t *scratch, uint32_t i) { return scratch + i * kScratchStride; }
@@ -151,7 +152,12 @@ NV_DEV void atomic_max_now(uint32_t *word, uint32_t bits, bool look) {
 // out before" needs no cache maintenance, only program order: a workgroup's maximum is in
 // before its ticket is drawn, a group's last ticket before the top one, and whoever draws the grid's last
 // ticket collects the maxima after that.
-NV_DEV void publish_amax(float m, uint32_t *amax_bits, const AmaxFinish &fin) {
+// `share`: which of a launch's workgroups belong to the tensor, and which half of the words, if not all.
+struct AmaxShare {
+  uint32_t block, blocks, half, halves;
+};
+NV_DEV AmaxShare whole_launch() { return AmaxShare{blockIdx.x, gridDim.x, 0u, 1u}; }
+NV_DEV void publish_amax(float m, uint32_t *amax_bits, const AmaxFinish &fin, const AmaxShare share) {
   __shared__ float wave_part[kThreads / 64];
   m = wave_max(m);
   if ((threadIdx.x & 63) == 0) wave_part[threadIdx.x >> 6] = m;
@@ -164,14 +170,15 @@ NV_DEV void publish_amax(float m, uint32_t *amax_bits, const AmaxFinish &fin) {
     if (threadIdx.x == 0) atomic_max_now(amax_bits, bits, true);
     return;
   }
-  const uint32_t groups = gridDim.x < kAmaxGroups ? gridDim.x : kAmaxGroups;
-  const uint32_t g = blockIdx.x % groups;
-  const uint32_t members = (gridDim.x - g + groups - 1) / groups;     // workgroups b with b % groups == g
-  uint32_t *gticket = scratch_slot(fin.scratch, kAmaxGroups + g);
-  uint32_t *top_ticket = scratch_slot(fin.scratch, 2 * kAmaxGroups + 1);
+  const uint32_t most = kAmaxGroups / share.halves, first = most * share.half;
+  const uint32_t groups = share.blocks < most ? share.blocks : most;
+  const uint32_t g = share.block % groups;
+  const uint32_t members = (share.blocks - g + groups - 1) / groups;  // workgroups b with b % groups == g
+  uint32_t *gticket = scratch_slot(fin.scratch, kAmaxGroups + first + g);
+  uint32_t *top_ticket = scratch_slot(fin.scratch, 2 * kAmaxGroups + 1 - share.half);
   uint32_t last = 0;
   if (threadIdx.x == 0) {
-    atomic_max_now(scratch_slot(fin.scratch, g), bits, members >= kGroupMayQueue);
+    atomic_max_now(scratch_slot(fin.scratch, first + g), bits, members >= kGroupMayQueue);
     if (__hip_atomic_fetch_add(gticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == members - 1) {
       __hip_atomic_store(gticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       last = __hip_atomic_fetch_add(top_ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == groups - 1;
@@ -181,7 +188,7 @@ NV_DEV void publish_amax(float m, uint32_t *amax_bits, const AmaxFinish &fin) {
   // last of all: the groups' maxima, one per lane, and all words zero again
   uint32_t all = 0;
   if (threadIdx.x < groups)
-    all = __hip_atomic_exchange(scratch_slot(fin.scratch, threadIdx.x), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    all = __hip_atomic_exchange(scratch_slot(fin.scratch, first + threadIdx.x), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
   for (uint32_t off = kAmaxGroups / 2; off > 0; off >>= 1) {
     const uint32_t other = (uint32_t)__shfl_xor((int)all, (int)off, 64);
@@ -216,7 +223,7 @@ __global__ __launch_bounds__(kThreads) void k_amax_plain(const uint4 *__restrict
     for (int j = 0; j < U; ++j) m.fold(w[j]);
   }
   for (; i < n16; i += stride) m.fold(load_stream(x + i));
-  publish_amax(m.value(), amax_bits, fin);
+  publish_amax(m.value(), amax_bits, fin, whole_launch());
 }
 
 // A small tensor, one workgroup for all of it: nothing has to be agreed on between workgroups, so
@@ -272,14 +279,12 @@ __global__ __launch_bounds__(kSmallThreads) void k_scale_small(const uint4 *__re
 // words; the factor 1/4 of the transform is applied once to the maximum (scaling by a power
 // of two is monotonic, so the maximum of the scaled values is the scaled maximum).
 template <bool XF32, int WORDS>
-__global__ __launch_bounds__(kThreads) void k_amax_rht_col(const uint32_t *__restrict__ x,
-                                                           int64_t row_blocks, int64_t pieces_per_row,
-                                                           uint64_t rht_seed, uint32_t *amax_bits,
-                                                           AmaxFinish fin) {
+NV_DEV float amax_rht_col(const uint32_t *__restrict__ x, int64_t row_blocks, int64_t pieces_per_row, uint64_t rht_seed,
+                          uint32_t block, uint32_t blocks) {
   const int64_t items = row_blocks * pieces_per_row;
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
+  const int64_t stride = (int64_t)blocks * kThreads;
   float m = 0.0f;
-  for (int64_t item = (int64_t)blockIdx.x * kThreads + threadIdx.x; item < items; item += stride) {
+  for (int64_t item = (int64_t)block * kThreads + threadIdx.x; item < items; item += stride) {
     const int64_t rb = item / pieces_per_row, piece = item - rb * pieces_per_row;
     const uint32_t *src = x + (rb * 16 * pieces_per_row + piece) * WORDS;
     struct alignas(4 * WORDS) Piece {
@@ -319,7 +324,31 @@ __global__ __launch_bounds__(kThreads) void k_amax_rht_col(const uint32_t *__res
       for (int j = 0; j < 16; j += 2) m = fmaxf(m, fmaxf(fabsf(v[j]), fabsf(v[j + 1])));
     }
   }
-  publish_amax(m * 0.25f, amax_bits, fin);
+  return m * 0.25f;
+}
+template <bool XF32, int WORDS>
+__global__ __launch_bounds__(kThreads) void k_amax_rht_col(const uint32_t *__restrict__ x,
+                                                           int64_t row_blocks, int64_t pieces_per_row,
+                                                           uint64_t rht_seed, uint32_t *amax_bits,
+                                                           AmaxFinish fin) {
+  const float m = amax_rht_col<XF32, WORDS>(x, row_blocks, pieces_per_row, rht_seed, blockIdx.x, gridDim.x);
+  publish_amax(m, amax_bits, fin, whole_launch());
+}
+
+// The maxima of two BF16 tensors after the columnwise transform, in one launch: the operands of a weight gradient, whose
+// blocks share their rows and signs.  The first `blocks_a` workgroups take a, the others b.
+struct AmaxPair {
+  const uint32_t *x[2];
+  int64_t pieces_per_row[2];
+  float *alpha[2];
+};
+template <int WORDS>
+__global__ __launch_bounds__(kThreads) void k_amax_rht_col_pair(AmaxPair p, int64_t row_blocks, uint64_t rht_seed,
+                                                                uint32_t blocks_a, uint32_t *scratch, float fp8_max) {
+  const uint32_t i = blockIdx.x >= blocks_a;
+  const uint32_t block = blockIdx.x - (i ? blocks_a : 0u), blocks = i ? gridDim.x - blocks_a : blocks_a;
+  const float m = amax_rht_col<false, WORDS>(p.x[i], row_blocks, p.pieces_per_row[i], rht_seed, block, blocks);
+  publish_amax(m, nullptr, AmaxFinish{scratch, p.alpha[i], fp8_max}, AmaxShare{block, blocks, i, 2u});
 }
 
 // -------------------------------------------------------- rowwise (flat)
@@ -504,7 +533,7 @@ __global__ __launch_bounds__(kThreads) void k_flat(
     run(r, b);
     r += step;
   }
-  if (OUT == kOutAmax) publish_amax(amax, amax_bits, fin);
+  if (OUT == kOutAmax) publish_amax(amax, amax_bits, fin, whole_launch());
 }
 
 // Tensor scale and rowwise codes of a small tensor in one launch: every workgroup reads the whole
@@ -594,10 +623,10 @@ struct TileMap {
   uint32_t last;        // the grid's last workgroup where tiles go last to first (kLastLevelBytes), or 0
 };
 
-NV_DEV TileCoord tile_of_workgroup(int64_t rows, int64_t cols, TileMap m) {
+NV_DEV TileCoord tile_of_workgroup(int64_t rows, int64_t cols, TileMap m, uint32_t block) {
   const uint32_t nt_r = (uint32_t)((rows + TR - 1) / TR), nt_c = (uint32_t)((cols + TC - 1) / TC);
   const uint32_t per = m.sx * m.sy, nsx = (nt_c + m.sx - 1) / m.sx;
-  const uint32_t id = m.last ? m.last - blockIdx.x : blockIdx.x;
+  const uint32_t id = m.last ? m.last - block : block;
   const uint32_t xcd = id & 7u, slot = id >> 3;
   const uint32_t round = slot / per, within = slot - round * per;
   const uint32_t S = round * 8u + xcd;                      // super-tile, row-major
@@ -607,24 +636,12 @@ NV_DEV TileCoord tile_of_workgroup(int64_t rows, int64_t cols, TileMap m) {
   return TileCoord{(int64_t)tr * TR, (int64_t)tc * TC, tc < nt_c && tr < nt_r};
 }
 
+// What a workgroup of k_tile keeps in LDS.
 template <bool XF32, int ROUNDING, int SELECT, bool RHT, bool WANT_ROW, int OUT>
-__global__ __launch_bounds__(kThreads) void k_tile(
-    const void *__restrict__ x_any, const float *__restrict__ alpha_p,
-    uint8_t *__restrict__ codes_row, uint8_t *__restrict__ scales_row,
-    uint8_t *__restrict__ choice_row, uint8_t *__restrict__ codes_col,
-    uint8_t *__restrict__ scales_col, uint8_t *__restrict__ choice_col,
-    uint16_t *__restrict__ out_bf16, int64_t rows, int64_t cols,
-    uint64_t sr_seed, uint64_t rht_seed, TileMap map) {
-  __shared__ ScaleTable tab;
-  // the tile, row-major: one 32-bit word (two BF16) or two (two fp32) per pair of columns
-  constexpr int kXW = XF32 ? 2 : 1;
-  using Raw = RawBlock<XF32>;
-  __shared__ __align__(16) uint32_t tile[TR * TC / 2 * kXW];
-  // columnwise results wait here until a whole column segment can leave at once
-  __shared__ uint2 stage_codes[OUT == kOutCodes ? kColItems : 1];     // [TC][TR/16]
-  __shared__ uint8_t stage_scale[OUT == kOutCodes ? kColItems : 1];   // [TC][TR/16]
-  __shared__ uint8_t stage_choice[OUT == kOutCodes ? kColItems : 1];  // [TC][TR/16]
-
+struct TileLds {
+  // Only columnwise codes wanted: nothing needs the tile in LDS -- a lane reads its two columns
+  // straight from memory, a row at a time (a wave's load covers 256 contiguous bytes of a row).
+  static constexpr bool kDirect = !WANT_ROW && OUT == kOutCodes;
   // The random words of the tile, one Philox call per four neighbouring elements of a row, as the
   // generator hands them out.  A lane of phase 2 owns two of the four columns, so without this
   // place every call was made twice and its other half dropped, and the words of both columns sat in
@@ -637,13 +654,46 @@ __global__ __launch_bounds__(kThreads) void k_tile(
   // transform 121 / 134, without 113 / 101; always 6 96 / 86, with the transform 102 / 90; absolute error on
   // nearest-rounded candidates with the transform 113 / 104).  Elsewhere the lane draws the words of
   // its two columns itself, half of every call for nothing.
-  constexpr bool kTwoWavesAnyway =
+  static constexpr bool kTwoWavesAnyway =
       SELECT == kSel46 || (RHT && ROUNDING == kSR && (SELECT == kSel46Mae || SELECT == kSel46AbsMax));
-  constexpr bool kWords = ROUNDING != kRTN && (!XF32 || OUT != kOutFake || kTwoWavesAnyway);
-  constexpr bool kDrawn = ROUNDING != kRTN && !kWords;
-  __shared__ uint4 words[kWords ? TR * TC / 4 : 1];                   // [TR][TC / 4]
+  static constexpr bool kWords = ROUNDING != kRTN && (!XF32 || OUT != kOutFake || kTwoWavesAnyway);
+  static constexpr bool kDrawn = ROUNDING != kRTN && !kWords;
+  // the tile, row-major: one 32-bit word (two BF16) or two (two fp32) per pair of columns
+  static constexpr int kXW = XF32 ? 2 : 1;
 
-  const TileCoord tcd = tile_of_workgroup(rows, cols, map);
+  typedef uint32_t Tile[kDirect ? 4 : TR * TC / 2 * kXW];
+  typedef uint4 Words[kWords ? TR * TC / 4 : 1];                 // [TR][TC / 4]
+  // columnwise results wait here until a whole column segment can leave at once: [TC][TR/16]
+  typedef uint2 Codes[OUT == kOutCodes ? kColItems : 1];
+  typedef uint8_t Bytes[OUT == kOutCodes ? kColItems : 1];
+  // (references to arrays of their own: the compiler then knows that they do not overlap)
+  ScaleTable &tab;
+  Tile &tile;
+  Words &words;
+  Codes &stage_codes;
+  Bytes &stage_scale, &stage_choice;
+};
+
+template <bool XF32, int ROUNDING, int SELECT, bool RHT, bool WANT_ROW, int OUT>
+NV_DEV void quantize_tile(
+    TileLds<XF32, ROUNDING, SELECT, RHT, WANT_ROW, OUT> lds, const void *__restrict__ x_any,
+    float alpha, uint8_t *__restrict__ codes_row, uint8_t *__restrict__ scales_row,
+    uint8_t *__restrict__ choice_row, uint8_t *__restrict__ codes_col,
+    uint8_t *__restrict__ scales_col, uint8_t *__restrict__ choice_col,
+    uint16_t *__restrict__ out_bf16, int64_t rows, int64_t cols,
+    uint64_t sr_seed, uint64_t rht_seed, TileMap map, uint32_t block) {
+  typedef TileLds<XF32, ROUNDING, SELECT, RHT, WANT_ROW, OUT> Lds;
+  constexpr bool kDirect = Lds::kDirect, kWords = Lds::kWords, kDrawn = Lds::kDrawn;
+  constexpr int kXW = Lds::kXW;
+  using Raw = RawBlock<XF32>;
+  ScaleTable &tab = lds.tab;
+  auto &tile = lds.tile;
+  auto &words = lds.words;
+  auto &stage_codes = lds.stage_codes;
+  auto &stage_scale = lds.stage_scale;
+  auto &stage_choice = lds.stage_choice;
+
+  const TileCoord tcd = tile_of_workgroup(rows, cols, map, block);
   if (!tcd.valid) return;  // uniform over the workgroup
   const int64_t r0 = tcd.r0, c0 = tcd.c0;
   const int t = threadIdx.x;
@@ -667,10 +717,6 @@ __global__ __launch_bounds__(kThreads) void k_tile(
     else
       draw_all([&](uint64_t q, uint32_t (&w)[4]) { sr_words4(sr_seed, q, w); });
   }   // (the barrier at the end of the scale table comes before the first use)
-
-  // Only columnwise codes wanted: nothing needs the tile in LDS -- a lane reads its two columns
-  // straight from memory, a row at a time (a wave's load covers 256 contiguous bytes of a row).
-  constexpr bool kDirect = !WANT_ROW && OUT == kOutCodes;
 
   // ---- phase 1: global -> LDS (and the rowwise outputs on the way); the loads go out
   // before the scale table is built
@@ -698,7 +744,7 @@ __global__ __launch_bounds__(kThreads) void k_tile(
       for (int q = 0; q < Raw::kPieces; ++q) dst[q] = w[j].w[q];
     }
   }
-  const ScaleConsts sc = build_scale_table(tab, *alpha_p);     // ends with a barrier
+  const ScaleConsts sc = build_scale_table(tab, alpha);     // ends with a barrier
 
   if (WANT_ROW) {
     // the lane's own row blocks, taken back from LDS one at a time (keeps the register
@@ -910,6 +956,50 @@ __global__ __launch_bounds__(kThreads) void k_tile(
   }
 }
 
+template <bool XF32, int ROUNDING, int SELECT, bool RHT, bool WANT_ROW, int OUT>
+__global__ __launch_bounds__(kThreads) void k_tile(
+    const void *__restrict__ x, const float *__restrict__ alpha, uint8_t *__restrict__ codes_row,
+    uint8_t *__restrict__ scales_row, uint8_t *__restrict__ choice_row, uint8_t *__restrict__ codes_col,
+    uint8_t *__restrict__ scales_col, uint8_t *__restrict__ choice_col, uint16_t *__restrict__ out_bf16, int64_t rows,
+    int64_t cols, uint64_t sr_seed, uint64_t rht_seed, TileMap map) {
+  typedef TileLds<XF32, ROUNDING, SELECT, RHT, WANT_ROW, OUT> Lds;
+  __shared__ ScaleTable tab;
+  __shared__ __align__(16) typename Lds::Tile tile;
+  __shared__ typename Lds::Words words;
+  __shared__ typename Lds::Codes stage_codes;
+  __shared__ typename Lds::Bytes stage_scale, stage_choice;
+  quantize_tile(Lds{tab, tile, words, stage_codes, stage_scale, stage_choice}, x, *alpha, codes_row, scales_row, choice_row, codes_col, scales_col, choice_col, out_bf16, rows, cols,
+                sr_seed, rht_seed, map, blockIdx.x);
+}
+
+// Both operands of a weight gradient in one launch: BF16 tensors of the same rows, columnwise with the transform, the
+// first (the gradient, its tiles the first `blocks_a` workgroups) rounded stochastically, the other to nearest.
+struct TilePair {
+  const void *x[2];
+  const float *alpha[2];
+  uint8_t *codes[2], *scales[2];
+  int64_t cols[2];
+  TileMap map[2];
+};
+template <int SELECT>
+__global__ __launch_bounds__(kThreads) void k_tile_pair(TilePair p, int64_t rows, uint64_t sr_seed, uint64_t rht_seed,
+                                                        uint32_t blocks_a) {
+  typedef TileLds<false, kSR, SELECT, true, false, kOutCodes> LdsA;
+  typedef TileLds<false, kRTN, SELECT, true, false, kOutCodes> LdsB;
+  // (the second kind has no words)
+  __shared__ ScaleTable tab;
+  __shared__ typename LdsA::Tile tile;
+  __shared__ typename LdsA::Words words;
+  __shared__ typename LdsA::Codes stage_codes;
+  __shared__ typename LdsA::Bytes stage_scale, stage_choice;
+  if (blockIdx.x < blocks_a)
+    quantize_tile(LdsA{tab, tile, words, stage_codes, stage_scale, stage_choice}, p.x[0], *p.alpha[0], nullptr, nullptr, nullptr, p.codes[0], p.scales[0],
+                  nullptr, nullptr, rows, p.cols[0], sr_seed, rht_seed, p.map[0], blockIdx.x);
+  else
+    quantize_tile(LdsB{tab, tile, reinterpret_cast<typename LdsB::Words &>(words), stage_codes, stage_scale, stage_choice}, p.x[1], *p.alpha[1], nullptr, nullptr, nullptr, p.codes[1], p.scales[1],
+                  nullptr, nullptr, rows, p.cols[1], sr_seed, rht_seed, p.map[1], blockIdx.x - blocks_a);
+}
+
 // Columnwise codes/scales -> row-major BF16, through an LDS tile.  TILE2D: the scales are
 // per 16x16 tile of the matrix, stored [cols/16][rows/16].
 template <bool TILE2D>
@@ -919,7 +1009,7 @@ __global__ __launch_bounds__(kThreads) void k_dequant_col(const uint8_t *__restr
                                                           uint16_t *__restrict__ out, int64_t rows,
                                                           int64_t cols, TileMap map) {
   __shared__ __align__(16) uint16_t tile16[TR * TC];
-  const TileCoord tcd = tile_of_workgroup(rows, cols, map);
+  const TileCoord tcd = tile_of_workgroup(rows, cols, map, blockIdx.x);
   if (!tcd.valid) return;
   const int64_t r0 = tcd.r0, c0 = tcd.c0;
   const int t = threadIdx.x;
@@ -1446,6 +1536,27 @@ int run_tile(const TileArgs &a, uint32_t select, int variant) {
   return launch_tile_variant<XF32, ROUNDING, kSel46AbsMax>(a, variant);
 }
 
+struct TilePairArgs {
+  TilePair p;
+  int64_t rows;
+  uint64_t sr_seed, rht_seed;
+  uint32_t blocks_a, blocks;
+  hipStream_t stream;
+};
+int run_tile_pair(const TilePairArgs &a, uint32_t select);
+#if NVFP4_46_PART == 2 || NVFP4_46_PART < 0
+int run_tile_pair(const TilePairArgs &a, uint32_t select) {
+  auto go = [&](auto kernel) {
+    return launch(kernel, dim3(a.blocks), dim3(kThreads), a.stream, a.p, a.rows, a.sr_seed, a.rht_seed, a.blocks_a);
+  };
+  if (select == NVFP4_SEL_46_MSE) return go(k_tile_pair<kSel46>);
+  if (select == NVFP4_SEL_FORCE6) return go(k_tile_pair<kSelForce6>);
+  if (select == NVFP4_SEL_FORCE4) return go(k_tile_pair<kSelForce4>);
+  if (select == NVFP4_SEL_46_MAE) return go(k_tile_pair<kSel46Mae>);
+  return go(k_tile_pair<kSel46AbsMax>);
+}
+#endif
+
 struct Block2dArgs {
   bool xf32;
   const void *x;
@@ -1759,6 +1870,59 @@ int nvfp4_46_scale_quantize(const void *x, const nvfp4_46_params *p, float *alph
   if (rc != NVFP4_OK) return rc;
   return nvfp4_46_quantize(x, p, alpha, codes_row, scales_row, codes_col, scales_col, choice_row,
                            choice_col, stream);
+}
+
+// Not part of the C ABI: both operands of paper_2512_02010_amd/linear.py's weight gradient, dy [rows][n] rounded
+// stochastically and x [rows][k] to nearest, BF16, columnwise with the transform: what two calls of
+// nvfp4_46_scale_quantize give, with their checks and statuses, in two launches instead of four where there are scratch words
+// for it.
+int nvfp4_46_wgrad_operands(const void *dy, const void *x, int64_t rows, int64_t n, int64_t k, uint32_t select,
+                            uint64_t sr_seed, uint64_t rht_seed, float *alpha_dy, void *codes_dy, void *scales_dy,
+                            float *alpha_x, void *codes_x, void *scales_x, void *workspace, size_t workspace_bytes,
+                            void *stream) {
+  const nvfp4_46_params pd{rows, n, NVFP4_COLWISE, NVFP4_SR, select, 1u, sr_seed, rht_seed, 256.0f, 0u, NVFP4_X_BF16};
+  const nvfp4_46_params px{rows, k, NVFP4_COLWISE, NVFP4_RTN, select, 1u, 0u, rht_seed, 256.0f, 0u, NVFP4_X_BF16};
+  int rc = workspace ? check_workspace(workspace, workspace_bytes) : NVFP4_OK;
+  if (rc == NVFP4_OK && (!alpha_dy || !alpha_x)) rc = NVFP4_ERR_NULL;
+  if (rc == NVFP4_OK) rc = check_params(dy, &pd, false);
+  if (rc == NVFP4_OK) rc = check_params(x, &px, false);
+  if (rc == NVFP4_OK) rc = check_outputs(&pd, nullptr, nullptr, codes_dy, scales_dy, nullptr, nullptr);
+  if (rc == NVFP4_OK) rc = check_outputs(&px, nullptr, nullptr, codes_x, scales_x, nullptr, nullptr);
+  if (rc != NVFP4_OK) return rc;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  uint32_t *const words = workspace ? static_cast<uint32_t *>(workspace) : lent_words(stream);
+  // (us in a replayed graph with the product, four launches / two: 64 tokens, 256 x 256 25.5 / 15.4, 736 tokens, 1024 x 1024
+  // 35.8 / 20.1, 2048 tokens, 2048 x 2048 59 / 43, 4096 x 4096 103 / 94, 8192 tokens 307 / 297; what no longer fits the
+  // memory-side cache goes one after the other, the second pass over a tensor last to first)
+  if (!words || rows * (n + k) * 2 > kLastLevelBytes) {
+    rc = nvfp4_46_scale_quantize(dy, &pd, alpha_dy, workspace, workspace_bytes, nullptr, nullptr, codes_dy, scales_dy,
+                                 nullptr, nullptr, stream);
+    if (rc != NVFP4_OK) return rc;
+    return nvfp4_46_scale_quantize(x, &px, alpha_x, workspace, workspace_bytes, nullptr, nullptr, codes_x, scales_x,
+                                   nullptr, nullptr, stream);
+  }
+  const TileMap map[2] = {tile_map(rows, n), tile_map(rows, k)};
+  const uint32_t tiles[2] = {(uint32_t)tile_grid(rows, n, map[0]), (uint32_t)tile_grid(rows, k, map[1])};
+  const int64_t row_blocks = rows / 16;
+  const bool narrow = row_blocks * (n + k) / 2 <= (int64_t)1 << 17;      // as in tensor_scale, of both together
+  const int64_t per_piece = narrow ? 2 : 8;
+  const AmaxPair both{{static_cast<const uint32_t *>(dy), static_cast<const uint32_t *>(x)},
+                      {n / per_piece, k / per_piece},
+                      {alpha_dy, alpha_x}};
+  const uint32_t blocks_a = (uint32_t)grid_for(row_blocks * both.pieces_per_row[0], kAmaxRhtColWgPerCu / 2);
+  const uint32_t blocks_b = (uint32_t)grid_for(row_blocks * both.pieces_per_row[1], kAmaxRhtColWgPerCu / 2);
+  auto maxima = [&](auto kernel) {
+    return launch(kernel, dim3(blocks_a + blocks_b), dim3(kThreads), s, both, row_blocks, rht_seed, blocks_a, words, 256.0f);
+  };
+  rc = narrow ? maxima(k_amax_rht_col_pair<1>) : maxima(k_amax_rht_col_pair<4>);
+  if (rc != NVFP4_OK) return rc;
+  const TilePair p{{dy, x},
+                   {alpha_dy, alpha_x},
+                   {static_cast<uint8_t *>(codes_dy), static_cast<uint8_t *>(codes_x)},
+                   {static_cast<uint8_t *>(scales_dy), static_cast<uint8_t *>(scales_x)},
+                   {n, k},
+                   {map[0], map[1]}};
+  return run_tile_pair(TilePairArgs{p, rows, sr_seed, rht_seed, tiles[0], tiles[0] + tiles[1], s}, select);
 }
 
 int nvfp4_46_dequantize(const void *codes, const void *scales, const float *alpha, int64_t rows,
