@@ -89,6 +89,9 @@ def lib() -> C.CDLL:
         L.nvfp4_46_gemm.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, i64, u32, u32, vp, vp]
         L.nvfp4_46_few_rows.restype = C.c_int
         L.nvfp4_46_few_rows.argtypes = [vp, C.c_float, vp, vp, vp, i64, i64, i64, u32, vp, vp]
+        L.nvfp4_46_wgrad_operands.restype = C.c_int
+        L.nvfp4_46_wgrad_operands.argtypes = [vp, vp, i64, i64, i64, u32, u64, u64, vp, vp, vp, vp, vp, vp, vp, C.c_size_t,
+                                              vp]
         L.nvfp4_46_status_string.restype = C.c_char_p
         L.nvfp4_46_status_string.argtypes = [C.c_int]
         L.nvfp4_46_debug_e2m1_rtn_range.restype = C.c_int
@@ -108,7 +111,8 @@ def lib() -> C.CDLL:
 
 
 NATIVE_ENTRY_POINTS = ("tensor_scale", "tensor_scale_ws", "quantize", "scale_quantize", "dequantize", "fake_quant",
-                       "gemm", "few_rows")
+                       "gemm")
+LAYER_ENTRY_POINTS = ("few_rows", "wgrad_operands")      # not part of the C ABI
 _native = None
 
 
@@ -124,8 +128,11 @@ def native():
         module = importlib.util.module_from_spec(importlib.util.spec_from_loader("nvfp4_46_python", loader))
         loader.exec_module(module)
         L = lib()
-        module.connect(Nvfp4Error, _device_empty, *(C.cast(getattr(L, "nvfp4_46_" + name), C.c_void_p).value
-                                                    for name in NATIVE_ENTRY_POINTS))
+        def addresses(names):
+            return (C.cast(getattr(L, "nvfp4_46_" + name), C.c_void_p).value for name in names)
+
+        module.connect(Nvfp4Error, _device_empty, *addresses(NATIVE_ENTRY_POINTS))
+        module.connect_layer(*addresses(LAYER_ENTRY_POINTS))
         _native = module
     return _native
 
@@ -357,13 +364,24 @@ def nvfp4_46_gemm(codes_a: torch.Tensor, scales_a: torch.Tensor, alpha_a: torch.
                                       None if stream is None else _stream(stream), flags)
 
 
-def few_rows(x: torch.Tensor, codes_b: torch.Tensor, scales_b: torch.Tensor, alpha_b: torch.Tensor,
-             flags: int = 0, stream=None) -> torch.Tensor | None:
-    """What ``nvfp4_46_scale_quantize(x)`` and ``nvfp4_46_gemm`` with it as operand A give, in one launch and in BF16,
-    where x is small enough for that to be the faster way; None where it is not."""
-    return (_native or native()).few_rows(
-        x, codes_b, scales_b, alpha_b, None if OUTPUT_ALLOCATOR is _device_empty else OUTPUT_ALLOCATOR,
-        None if stream is None else _stream(stream), flags)
+# ---- a linear layer's products in one call each (None: not with these operands, see csrc/python.cpp) -------
+
+def product_of_rows(x: torch.Tensor, codes_b: torch.Tensor, scales_b: torch.Tensor, alpha_b: torch.Tensor, flags: int = 0,
+                    rounding: int = RTN, select: int = SEL_46_MSE, sr_seed: int = 0,
+                    workspace: torch.Tensor | None = None) -> torch.Tensor | None:
+    """What ``nvfp4_46_scale_quantize(x)`` and ``nvfp4_46_gemm`` with it as operand A give, in BF16; few values of x take
+    one launch for it all."""
+    return (_native or native()).product_of_rows(
+        x, codes_b, scales_b, alpha_b, None if OUTPUT_ALLOCATOR is _device_empty else OUTPUT_ALLOCATOR, workspace, flags,
+        rounding, select, sr_seed)
+
+
+def product_of_columns(dy: torch.Tensor, x: torch.Tensor, sr_seed: int, rht_seed: int, select: int = SEL_46_MSE,
+                       workspace: torch.Tensor | None = None) -> torch.Tensor | None:
+    """dy^T x in fp32 of both operands quantized columnwise with the Hadamard transform, dy rounded stochastically; the
+    operands' scales take one launch, their codes another."""
+    return (_native or native()).product_of_columns(
+        dy, x, None if OUTPUT_ALLOCATOR is _device_empty else OUTPUT_ALLOCATOR, workspace, select, sr_seed, rht_seed)
 
 
 # ---- scalar codecs ------------------------------------------------------------------------

@@ -34,10 +34,16 @@ struct EntryPoints {
   int (*fake_quant)(const void *, const nvfp4_46_params *, const float *, void *, void *);
   int (*gemm)(const void *, const void *, const float *, const void *, const void *, const float *, int64_t,
               int64_t, int64_t, uint32_t, uint32_t, void *, void *);
-  int (*few_rows)(const void *, float, const void *, const void *, const float *, int64_t, int64_t, int64_t, uint32_t,
-                  void *, void *);
 };
 EntryPoints entry;
+// ... and of binding.py's LAYER_ENTRY_POINTS, which are no part of the C ABI.
+struct LayerEntryPoints {
+  int (*few_rows)(const void *, float, const void *, const void *, const float *, int64_t, int64_t, int64_t, uint32_t,
+                  void *, void *);
+  int (*wgrad_operands)(const void *, const void *, int64_t, int64_t, int64_t, uint32_t, uint64_t, uint64_t, float *,
+                        void *, void *, float *, void *, void *, void *, size_t, void *);
+};
+LayerEntryPoints layer;
 PyObject *error_class;     // Nvfp4Error(status, name of the entry point)
 PyObject *empty;           // (shape, dtype, device) -> tensor
 
@@ -368,51 +374,166 @@ PyObject *gemm(PyObject *const *a, Py_ssize_t n) {
   return out.release();
 }
 
-// x, codes_b, scales_b, alpha_b, allocate, stream, flags: x quantized and multiplied in one launch where that is the
-// faster way and the operands are plain contiguous tensors that fit together; None for anything else, also for what
-// the calls one by one refuse.  `allocate` makes the output, as binding.py's OUTPUT_ALLOCATOR (None: as torch.empty).
-PyObject *few_rows(PyObject *const *a, Py_ssize_t n) {
-  expect(n, 7);
+// ---- the products of a linear layer (linear.py), each in one call: the operands that it quantizes on the way live in
+// one buffer that is never a Python object.  They work on plain contiguous device tensors that fit together, on the
+// current stream; for anything else, also for what the calls one by one refuse, they return None and linear.py makes
+// those calls.  `allocate` makes buffers and outputs, as binding.py's OUTPUT_ALLOCATOR (None: as torch.empty).
+
+bool ready(const at::Tensor *t) {
+  return t && t->is_cuda() && t->is_contiguous() && reinterpret_cast<uintptr_t>(t->data_ptr()) % 16 == 0;
+}
+bool ready_matrix(const at::Tensor *t) {
+  return ready(t) && t->dim() == 2 && t->size(0) > 0 && t->size(1) > 0 &&
+         (t->scalar_type() == at::kBFloat16 || t->scalar_type() == at::kFloat);
+}
+// a workspace that the calls one by one would take, or none
+struct Workspace {
+  bool fits;
+  void *p = nullptr;
+  size_t bytes = 0;
+  explicit Workspace(PyObject *o) : fits(o == Py_None) {
+    if (fits) return;
+    const at::Tensor *t = plain(o);
+    fits = ready(t) && t->numel() >= NVFP4_46_TENSOR_SCALE_WS_BYTES;
+    if (fits) {
+      p = t->data_ptr();
+      bytes = (size_t)t->numel();
+    }
+  }
+};
+// Device memory for operands, `bytes` of it; parts of it begin at multiples of 256 bytes.
+constexpr int64_t round_up(int64_t bytes) { return (bytes + 255) / 256 * 256; }
+struct Buffer {
+  at::Tensor own;
+  PyObject *given = nullptr;
+  char *p;
+  Buffer(int64_t bytes, PyObject *like, PyObject *allocate) {
+    if (allocate == Py_None) {
+      WithoutLock others;
+      own = at::empty({bytes}, at::TensorOptions().dtype(at::kByte).device(plain(like)->device()));
+      p = static_cast<char *>(own.data_ptr());
+    } else {
+      Owned t(new_tensor({bytes}, at::kByte, like, allocate));
+      p = static_cast<char *>(pointer(t.o));
+      given = t.release();
+    }
+  }
+  Buffer(const Buffer &) = delete;
+  ~Buffer() { Py_XDECREF(given); }
+};
+// One quantized operand of `lines` lines of K values in a buffer.
+struct Operand {
+  int64_t lines, K;
+  int64_t bytes() const { return round_up(lines * K / 2) + round_up(lines * K / 16) + 256; }
+  char *codes(char *p) const { return p; }
+  char *scales(char *p) const { return p + round_up(lines * K / 2); }
+  float *alpha(char *p) const { return reinterpret_cast<float *>(scales(p) + round_up(lines * K / 16)); }
+};
+
+// x, codes_b, scales_b, alpha_b, allocate, workspace, flags, rounding, select, sr_seed: x quantized rowwise, times B^T, BF16
+PyObject *product_of_rows(PyObject *const *a, Py_ssize_t n) {
+  expect(n, 10);
   const at::Tensor *x = plain(a[0]), *cb = plain(a[1]), *sb = plain(a[2]), *alpha = plain(a[3]);
-  if (!x || x->dim() != 2 || x->scalar_type() != at::kBFloat16) Py_RETURN_NONE;
-  const int64_t M = x->size(0), K = x->size(1);
-  if (M <= 0 || K <= 0 || K % 32 != 0 || !nvfp4_46::few_rows_in_one_launch(M, 1, K)) Py_RETURN_NONE;
-  if (!cb || !sb || !alpha || cb->dim() != 2 || sb->dim() != 2) Py_RETURN_NONE;
-  const int64_t N = cb->size(0);
-  const uint32_t flags = (uint32_t)word(a[6]);
-  const bool tiles = flags & NVFP4_GEMM_B_TILE_SCALES;
-  if (N <= 0 || !nvfp4_46::few_rows_in_one_launch(M, N, K) || cb->size(1) * 2 != K || (tiles && N % 16 != 0) ||
-      sb->size(0) != (tiles ? N / 16 : N) || sb->size(1) != K / 16)
+  const Workspace ws(a[5]);
+  if (!ready_matrix(x) || !ready(cb) || !ready(sb) || !alpha || !alpha->is_cuda() || !alpha->is_contiguous() || !ws.fits ||
+      cb->dim() != 2 || sb->dim() != 2)
     Py_RETURN_NONE;
-  for (const at::Tensor *t : {x, cb, sb, alpha})
-    if (!t->is_cuda() || !t->is_contiguous()) Py_RETURN_NONE;
-  for (const at::Tensor *t : {x, cb, sb})
-    if (reinterpret_cast<uintptr_t>(t->data_ptr()) % 16 != 0) Py_RETURN_NONE;
-  Owned out(new_tensor({M, N}, at::kBFloat16, a[0], a[4]));
-  void *const o = pointer(out.o), *const s = stream(a[5]);
+  const int64_t M = x->size(0), K = x->size(1), N = cb->size(0);
+  const uint32_t flags = (uint32_t)word(a[6]), rounding = (uint32_t)word(a[7]), select = (uint32_t)word(a[8]);
+  const uint64_t sr_seed = word(a[9]);
+  const bool tiles = flags & NVFP4_GEMM_B_TILE_SCALES;
+  if (N <= 0 || K % 32 != 0 || cb->size(1) * 2 != K || (tiles && N % 16 != 0) || sb->size(0) != (tiles ? N / 16 : N) ||
+      sb->size(1) != K / 16)
+    Py_RETURN_NONE;
   const void *const px = x->data_ptr(), *const pc = cb->data_ptr(), *const ps = sb->data_ptr();
   const float *const pa = static_cast<const float *>(alpha->data_ptr());
-  run("nvfp4_46_few_rows", [&] { return entry.few_rows(px, 256.0f, pc, ps, pa, M, N, K, flags, o, s); });
+  void *const s = stream(Py_None);
+  if (x->scalar_type() == at::kBFloat16 && rounding == NVFP4_RTN && select == NVFP4_SEL_46_MSE &&
+      nvfp4_46::few_rows_in_one_launch(M, N, K)) {
+    Owned out(new_tensor({M, N}, at::kBFloat16, a[0], a[4]));
+    void *const o = pointer(out.o);
+    run("nvfp4_46_few_rows", [&] { return layer.few_rows(px, 256.0f, pc, ps, pa, M, N, K, flags, o, s); });
+    return out.release();
+  }
+  nvfp4_46_params p{};
+  set_shape(p, a[0]);
+  p.layout = NVFP4_ROWWISE;
+  p.rounding = rounding;
+  p.select = select;
+  p.sr_seed = sr_seed;
+  p.fp8_max = 256.0f;
+  const Operand q{M, K};
+  const Buffer buffer(q.bytes(), a[0], a[4]);
+  char *const b = buffer.p;
+  run("nvfp4_46_scale_quantize", [&] {
+    return entry.scale_quantize(px, &p, q.alpha(b), ws.p, ws.bytes, q.codes(b), q.scales(b), nullptr, nullptr, nullptr, nullptr,
+                                s);
+  });
+  Owned out(new_tensor({M, N}, at::kBFloat16, a[0], a[4]));
+  void *const o = pointer(out.o);
+  run("nvfp4_46_gemm", [&] {
+    return entry.gemm(q.codes(b), q.scales(b), q.alpha(b), pc, ps, pa, M, N, K, NVFP4_OUT_BF16, flags, o, s);
+  });
   return out.release();
 }
 
+// dy, x, allocate, workspace, select, sr_seed, rht_seed: dy^T x, fp32, both operands transformed along the rows
+PyObject *product_of_columns(PyObject *const *a, Py_ssize_t n) {
+  expect(n, 7);
+  const at::Tensor *dy = plain(a[0]), *x = plain(a[1]);
+  const Workspace ws(a[3]);
+  if (!ready_matrix(dy) || !ready_matrix(x) || !ws.fits || dy->scalar_type() != at::kBFloat16 ||
+      x->scalar_type() != at::kBFloat16 || dy->device() != x->device())
+    Py_RETURN_NONE;
+  const int64_t T = dy->size(0), N = dy->size(1), K = x->size(1);
+  if (x->size(0) != T || T % 32 != 0 || N % 8 != 0 || K % 8 != 0) Py_RETURN_NONE;
+  const uint32_t select = (uint32_t)word(a[4]);
+  const uint64_t sr_seed = word(a[5]), rht_seed = word(a[6]);
+  const Operand qd{N, T}, qx{K, T};
+  const Buffer buffer(qd.bytes() + qx.bytes(), a[0], a[2]);
+  char *const bd = buffer.p, *const bx = buffer.p + qd.bytes();
+  const void *const pd = dy->data_ptr(), *const px = x->data_ptr();
+  void *const s = stream(Py_None);
+  run("nvfp4_46_scale_quantize", [&] {
+    return layer.wgrad_operands(pd, px, T, N, K, select, sr_seed, rht_seed, qd.alpha(bd), qd.codes(bd), qd.scales(bd),
+                                qx.alpha(bx), qx.codes(bx), qx.scales(bx), ws.p, ws.bytes, s);
+  });
+  Owned out(new_tensor({N, K}, at::kFloat, a[0], a[2]));
+  void *const o = pointer(out.o);
+  run("nvfp4_46_gemm", [&] {
+    return entry.gemm(qd.codes(bd), qd.scales(bd), qd.alpha(bd), qx.codes(bx), qx.scales(bx), qx.alpha(bx), N, K, T,
+                      NVFP4_OUT_F32, 0, o, s);
+  });
+  return out.release();
+}
+
+template <typename Points>
+void take_addresses(Points &points, PyObject *const *a, Py_ssize_t n) {
+  constexpr Py_ssize_t kEntries = sizeof(Points) / sizeof(void *);
+  expect(n, kEntries);
+  void *to[kEntries];
+  for (Py_ssize_t i = 0; i < kEntries; ++i) to[i] = reinterpret_cast<void *>(word(a[i]));
+  std::memcpy(&points, to, sizeof points);
+}
 // The exception class, torch.empty as (shape, dtype, device), then the addresses of the entry points, one integer
 // each.
 PyObject *connect(PyObject *const *a, Py_ssize_t n) {
-  constexpr Py_ssize_t kEntries = sizeof(EntryPoints) / sizeof(void *);
-  expect(n, 2 + kEntries);
-  void *to[kEntries];
-  for (Py_ssize_t i = 0; i < kEntries; ++i) to[i] = reinterpret_cast<void *>(word(a[2 + i]));
-  std::memcpy(&entry, to, sizeof entry);
+  expect(n < 2 ? n : 2, 2);
+  take_addresses(entry, a + 2, n - 2);
   error_class = Py_NewRef(a[0]);
   empty = Py_NewRef(a[1]);
   Py_RETURN_NONE;
 }
+PyObject *connect_layer(PyObject *const *a, Py_ssize_t n) {
+  take_addresses(layer, a, n);
+  Py_RETURN_NONE;
+}
 
 #define NV_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void *>(guarded<f>)), METH_FASTCALL, nullptr}
-PyMethodDef methods[] = {NV_METHOD(connect),    NV_METHOD(tensor_scale), NV_METHOD(tensor_scale_ws), NV_METHOD(quantize),
+PyMethodDef methods[] = {NV_METHOD(connect), NV_METHOD(connect_layer),
+                           NV_METHOD(tensor_scale), NV_METHOD(tensor_scale_ws), NV_METHOD(quantize),
                          NV_METHOD(scale_quantize), NV_METHOD(dequantize), NV_METHOD(fake_quant), NV_METHOD(gemm),
-                         NV_METHOD(few_rows),
+                         NV_METHOD(product_of_rows), NV_METHOD(product_of_columns),
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "nvfp4_46_python", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

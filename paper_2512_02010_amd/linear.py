@@ -13,6 +13,10 @@ packing for W and for W^T with identical codes and scales.  Stochastic rounding 
 the gradient operands, the random Hadamard transform on both operands of WGRAD (same sign
 vector along the contraction axis, so it cancels in the product).
 
+On the current stream (``stream`` left out) a product is one call into the library's Python module, which runs the
+same kernels with the operands it quantizes in a buffer of its own; on any other stream, and for operands that are not plain
+contiguous tensors, it is those calls one by one.
+
 Every function takes an optional ``workspace`` (``binding.new_workspace()``): with it the five
 tensor scales of a step are one launch each (``nvfp4_46_tensor_scale_ws``) instead of three.
 One workspace serves all calls issued on one stream.
@@ -48,8 +52,8 @@ def fprop(x: torch.Tensor, qw: dict, select: int = B.SEL_46_MSE, stream=None,
           workspace: torch.Tensor | None = None) -> torch.Tensor:
     """y [T][N] BF16 = x W^T."""
     flags = B.GEMM_B_TILE_SCALES if qw["block2d"] else 0
-    if select == B.SEL_46_MSE:
-        y = B.few_rows(x, qw["codes_row"], qw["scales_row"], qw["alpha"], flags, stream)
+    if stream is None:
+        y = B.product_of_rows(x, qw["codes_row"], qw["scales_row"], qw["alpha"], flags, B.RTN, select, 0, workspace)
         if y is not None:
             return y
     cx, sx, ax = _rowwise(x, stream, workspace, select=select)
@@ -60,8 +64,12 @@ def fprop(x: torch.Tensor, qw: dict, select: int = B.SEL_46_MSE, stream=None,
 def dgrad(dy: torch.Tensor, qw: dict, sr_seed: int, select: int = B.SEL_46_MSE,
           stream=None, workspace: torch.Tensor | None = None) -> torch.Tensor:
     """dx [T][K] BF16 = dy W, the gradient rounded stochastically."""
-    cg, sg, ag = _rowwise(dy, stream, workspace, select=select, rounding=B.SR, sr_seed=sr_seed)
     flags = B.GEMM_B_TILE_SCALES if qw["block2d"] else 0
+    if stream is None:
+        dx = B.product_of_rows(dy, qw["codes_col"], qw["scales_col"], qw["alpha"], flags, B.SR, select, sr_seed, workspace)
+        if dx is not None:
+            return dx
+    cg, sg, ag = _rowwise(dy, stream, workspace, select=select, rounding=B.SR, sr_seed=sr_seed)
     return B.nvfp4_46_gemm(cg, sg, ag, qw["codes_col"], qw["scales_col"], qw["alpha"],
                            out_dtype=B.OUT_BF16, flags=flags, stream=stream)
 
@@ -70,6 +78,10 @@ def wgrad(dy: torch.Tensor, x: torch.Tensor, sr_seed: int, rht_seed: int,
           select: int = B.SEL_46_MSE, stream=None,
           workspace: torch.Tensor | None = None) -> torch.Tensor:
     """dW [N][K] FP32 = dy^T x, both operands Hadamard-transformed along the token axis."""
+    if stream is None:
+        dw = B.product_of_columns(dy, x, sr_seed, rht_seed, select, workspace)
+        if dw is not None:
+            return dw
     cg, sg, ag = _columnwise(dy, stream, workspace, rht_seed, select=select, rounding=B.SR,
                              sr_seed=sr_seed)
     cx, sx, ax = _columnwise(x, stream, workspace, rht_seed, select=select)

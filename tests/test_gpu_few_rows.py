@@ -35,7 +35,7 @@ def test_few_rows_match_the_oracle(M, K, N, tiles):
     want, total = ref.gemm(ca, sa, aa, cb, sb_rows, ab, want_abs=True)
     x = wl.make("c3", M, K).cuda()
     flags = B.GEMM_B_TILE_SCALES if tiles else 0
-    got = B.few_rows(x, _dev(cb), _dev(sb), _alpha(ab), flags)
+    got = B.product_of_rows(x, _dev(cb), _dev(sb), _alpha(ab), flags)
     assert got is not None and got.shape == (M, N) and got.dtype == torch.bfloat16
     err = abs(_bf16_to_f64(got) - want)
     assert (err <= _tolerance(want, total, K, B.OUT_BF16)).all(), err.max()
@@ -55,25 +55,42 @@ def test_wide_weights_match_the_calls_one_by_one(N):
     assert ((y.float() - exact).abs() <= exact.abs() * 2.0 ** -8 + exact.abs().max() * 2.0 ** -18).all()
 
 
-def test_zeros_and_what_is_left_to_the_calls_one_by_one():
+def _one_by_one(x, qw, **kw):
+    """The forward pass by the two calls that it was made of."""
+    q = B.nvfp4_46_scale_quantize(x, **kw)
+    flags = B.GEMM_B_TILE_SCALES if qw["block2d"] else 0
+    return B.nvfp4_46_gemm(q["codes_row"], q["scales_row"], q["alpha"], qw["codes_row"], qw["scales_row"], qw["alpha"],
+                           flags=flags)
+
+
+# either side of what takes one launch: rows, values, columns; BF16 and fp32, another selection rule
+@pytest.mark.parametrize("rows,cols,out", [(16, 256, 64), (17, 256, 64), (7, 4096, 64), (8, 4096, 64), (2, 256, 8192),
+                                           (2, 256, 8208)])
+def test_either_side_of_one_launch(rows, cols, out):
+    qw = L.quantize_weight(wl.make("c2", out, cols).cuda())
+    x = wl.make("c3", rows, cols).cuda()
+    assert torch.equal(L.fprop(x, qw), _one_by_one(x, qw))
+    assert torch.equal(L.fprop(x.float(), qw), _one_by_one(x.float(), qw))
+    assert torch.equal(L.fprop(x, qw, select=B.SEL_46_MAE), _one_by_one(x, qw, select=B.SEL_46_MAE))
+    assert not L.fprop(torch.zeros_like(x), qw).any()
+
+
+def test_what_is_left_to_the_calls_one_by_one():
     qw = L.quantize_weight(wl.make("c2", 64, 256).cuda())
-    zero = torch.zeros((4, 256), dtype=torch.bfloat16, device="cuda")
-    assert not L.fprop(zero, qw).any()
     args = qw["codes_row"], qw["scales_row"], qw["alpha"], B.GEMM_B_TILE_SCALES
     x = wl.make("c1", 16, 256).cuda()
-    assert B.few_rows(x, *args) is not None
-    for other in (wl.make("c1", 17, 256).cuda(),                        # too many rows
-                  x.float(),                                            # fp32
-                  wl.make("c1", 16, 512).cuda()[:, ::2],                # not contiguous
+    assert B.product_of_rows(x, *args) is not None
+    small = torch.zeros(16, dtype=torch.uint8, device="cuda")
+    for other in (wl.make("c1", 16, 512).cuda()[:, ::2],                # not contiguous
                   wl.make("c1", 16, 512).cuda(),                        # another K
-                  x.reshape(-1), x.cpu()):
-        assert B.few_rows(other, *args) is None
-    for rows, cols, out, one in ((7, 4096, 64, True), (8, 4096, 64, False),         # values: 28672 and more
-                                 (2, 256, 8192, True), (2, 256, 8208, False)):      # columns: 8192 and more
-        w = L.quantize_weight(wl.make("c2", out, cols).cuda())
-        x = wl.make("c1", rows, cols).cuda()
-        y = B.few_rows(x, w["codes_row"], w["scales_row"], w["alpha"], B.GEMM_B_TILE_SCALES)
-        assert (y is not None) == one and L.fprop(x, w).shape == (rows, out)
+                  x.half(), x.reshape(-1), x.cpu()):
+        assert B.product_of_rows(other, *args) is None
+    assert B.product_of_rows(x, *args, workspace=small) is None
+    assert B.product_of_rows(x, *args[:3], 0) is None                   # scales of another shape than these flags say
+    with pytest.raises(B.Nvfp4Error):
+        L.fprop(wl.make("c1", 64, 256).cuda(), qw, workspace=small)
+    with pytest.raises(AssertionError):
+        L.fprop(x.half(), qw)
 
 
 def test_few_rows_on_a_side_stream_and_in_a_graph():
