@@ -650,6 +650,14 @@ __global__ __launch_bounds__(S::kThreads, 1) void k_gemm_dma(
 // of one LDS access pass hit all banks.  One barrier per chunk: it comes after the wait for the
 // own copies of the chunk, so behind it the chunk is complete and the stage of the chunk before is
 // free for the next copies.  K <= 2^24 (32-bit lane offsets).
+//
+// Small products spend as long before and after the loop as in it.  So the last chunk stands by itself: no copy
+// is under way that the sums would wait for, and a copy of the tile whose piece of it is past K leaves the matrix unit to
+// the others.  The sums go through LDS in pieces of 16 bytes, every copy adding up and storing an equal share of
+// C (with a wave per 32 x 32 tile seven of Tile32's eight were idle meanwhile), and a tile inside C is stored without
+// looking at its edges.  In a replayed graph, us, before / after: 64 x 1024 x 4096 7.1 / 6.4, 128 x 2000 x 1056 5.3 / 4.0,
+// 128 x 4096 x 4096 10.3 / 9.1, 300 x 2000 x 1056 7.5 / 6.6, 2880 x 1440 x 1056 20.9 / 18.2, 192 x 4096 x 11008 30.7 / 26.6,
+// 1000 x 4096 x 800 14.5 / 12.5; no change where the loop is all (1536 x 4096 x 8192 91).
 template <typename S, bool KFULL, bool OUTF32>
 __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 : 4) void k_gemm_tile(
     const uint8_t *__restrict__ codes_a, const uint8_t *__restrict__ scales_a,
@@ -663,7 +671,10 @@ __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 
   const uint32_t t = threadIdx.x, lane = t & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const uint32_t r = lane & 31u, g = lane >> 5;
-  const uint32_t kg = wave / (S::SM * S::SN), spatial = wave % (S::SM * S::SN);
+  // (workgroups of one compute unit come a launch's turn apart; where K leaves copies without work in the last chunk they
+  // differ in which SIMD those are on)
+  const uint32_t turn = KFULL ? 0u : blockIdx.x / (uint32_t)kCus;
+  const uint32_t kg = (wave / (S::SM * S::SN) + turn) % KS, spatial = wave % (S::SM * S::SN);
   const uint32_t wm = spatial / S::SN, wn = spatial % S::SN;
 
   const TileAt at = tile_of_workgroup(tiles_m, tiles_n, strip);
@@ -688,39 +699,39 @@ __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 
   auto swz_c = [](uint32_t row) { return (row / (16 / U)) & (U - 1u); };
   auto swz_s = [](uint32_t row) { return ((row / (64 / U)) << 1) & (U - 1u); };
   // copy instruction i moves the 64 / U LDS rows from i * 64 / U on; wave w issues i = w, w +
-  // kWaves, ... (the last one again where they do not divide evenly: same bytes, same place).
+  // kWaves, ..., whose rows all have the same swizzle, so a lane copies units unit_c and pairs unit_s only.
   // A row past the end of its operand re-reads the last one (its products are never stored).
+  static_assert(S::kCopies % S::kWaves == 0 && 2 * S::kWaves % U == 0, "one swizzle per lane");
+  const uint32_t unit_c = lane % U ^ swz_c(wave * (64 / U) + lane / U);
+  const uint32_t unit_s = lane % U ^ swz_s(wave * (64 / U) + lane / U);
   uint32_t off_c[S::NC], off_s[S::NC];                    // the lane's byte offsets at chunk 0
 #pragma unroll
   for (int n = 0; n < S::NC; ++n) {
-    uint32_t i = wave + n * S::kWaves;
-    if (S::kCopies % S::kWaves != 0 && i >= (uint32_t)S::kCopies) i = S::kCopies - 1;
-    const uint32_t row = i * (64 / U) + lane / U, pos = lane % U;
+    const uint32_t i = wave + n * S::kWaves;
+    const uint32_t row = i * (64 / U) + lane / U;
     const bool is_a = i * (64 / U) < (uint32_t)S::BM;
     const uint32_t line = row - (is_a ? 0u : (uint32_t)S::BM), last = (is_a ? rows_a : rows_b) - 1;
     const uint32_t l = line < last ? line : last;
-    off_c[n] = l * row_codes + (pos ^ swz_c(row)) * 16;
-    off_s[n] = (l >> (is_a ? sha : shb)) * row_scales + (pos ^ swz_s(row)) * 2;
+    off_c[n] = l * row_codes + unit_c * 16;
+    off_s[n] = (l >> (is_a ? sha : shb)) * row_scales + unit_s * 2;
   }
   auto copy_chunk = [&](uint32_t c, uint32_t stage) {
     const uint32_t lds = lds0 + stage * S::STAGE;
     const uint32_t k0 = c * S::CK;
+    // units past the end of K: the row's last one instead
+    uint32_t past_c = 0, past_s = 0;
+    if constexpr (!KFULL) {
+      const uint32_t kc = k0 + unit_c * 32, ks = k0 + unit_s * 32;
+      past_c = kc >= K ? (kc - (K - 32)) / 2 : 0u;
+      past_s = ks >= K ? (ks - (K - 32)) / 16 : 0u;
+    }
 #pragma unroll
     for (int n = 0; n < S::NC; ++n) {
-      uint32_t i = wave + n * S::kWaves;
-      if (S::kCopies % S::kWaves != 0 && i >= (uint32_t)S::kCopies) i = S::kCopies - 1;
+      const uint32_t i = wave + n * S::kWaves;
       const bool is_a = i * (64 / U) < (uint32_t)S::BM;
       const uint8_t *bc = (is_a ? gca : gcb) + k0 / 2, *bs = (is_a ? gsa : gsb) + k0 / 16;
-      uint32_t oc = off_c[n], os = off_s[n];
-      if constexpr (!KFULL) {
-        // units past the end of K: the row's last one instead
-        const uint32_t row = i * (64 / U) + lane / U, pos = lane % U;
-        const uint32_t uc = pos ^ swz_c(row), us = pos ^ swz_s(row);
-        if (k0 + uc * 32 >= K) oc -= (k0 + uc * 32 - (K - 32)) / 2;
-        if (k0 + us * 32 >= K) os -= (k0 + us * 32 - (K - 32)) / 16;
-      }
-      NV_DMA16(lds + i * 1024, oc, bc);
-      NV_DMA2(lds + S::kScaleBase + i * 256, os, bs);
+      NV_DMA16(lds + i * 1024, off_c[n] - past_c, bc);
+      NV_DMA2(lds + S::kScaleBase + i * 256, off_s[n] - past_s, bs);
     }
   };
 
@@ -763,32 +774,36 @@ __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 
   auto clamp_chunk = [&](uint32_t c) { return c < nchunks ? c : nchunks - 1; };
   if constexpr (S::kTiles <= 4) {
     // four waves per SIMD hide each other's LDS reads and expansions: plain order, few registers
+    static_assert(S::kTiles > 4 || NST == 2, "every copy on its way belongs to the chunk that is waited for");
+    auto multiply_piece = [&](uint32_t c, uint32_t stage, int h) {
+      Raw x;
+      read_piece(c, stage, h, x);
 #pragma unroll
-    for (int p = 0; p < NST - 1; ++p) copy_chunk(clamp_chunk(p), p);
-    uint32_t stage = 0, freed = NST - 1;
-    for (uint32_t c = 0; c < nchunks; ++c) {
-      // chunk c is complete, and nobody reads the stage of chunk c - 1 any more
-      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((NST - 2) * 2 * S::NC) : "memory");
-      copy_chunk(clamp_chunk(c + NST - 1), freed);
+      for (int s = 0; s < 4; ++s) {
+        h8 f[T];
 #pragma unroll
-      for (int h = 0; h < HPW; ++h) {
-        Raw x;
-        read_piece(c, stage, h, x);
+        for (int i = 0; i < T; ++i) f[i] = expand_one(x, s, i);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          h8 f[T];
+        for (int i = 0; i < WM; ++i)
 #pragma unroll
-          for (int i = 0; i < T; ++i) f[i] = expand_one(x, s, i);
-#pragma unroll
-          for (int i = 0; i < WM; ++i)
-#pragma unroll
-            for (int j = 0; j < WN; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f[i], f[WM + j], acc[i][j], 0, 0, 0);
-        }
+          for (int j = 0; j < WN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f[i], f[WM + j], acc[i][j], 0, 0, 0);
       }
-      freed = stage;
-      stage = stage + 1 == (uint32_t)NST ? 0u : stage + 1;
+    };
+    copy_chunk(0, 0);
+    // chunk c is complete, and nobody reads the other stage, chunk c - 1's, any more
+    auto wait_for_chunk = [] { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    for (uint32_t c = 0; c + 1 < nchunks; ++c) {
+      wait_for_chunk();
+      copy_chunk(c + 1, (c + 1) & 1);
+#pragma unroll
+      for (int h = 0; h < HPW; ++h) multiply_piece(c, c & 1, h);
     }
+    // the last chunk by itself: no copy, which the sums would wait for, and nothing for copies whose pieces are past K
+    wait_for_chunk();
+#pragma unroll
+    for (int h = 0; h < HPW; ++h)
+      if (KFULL || (nchunks - 1) * S::CK + 64 * (kg * HPW + h) < K) multiply_piece(nchunks - 1, (nchunks - 1) & 1, h);
   } else {
 #pragma unroll
     for (int p = 0; p < NST; ++p) copy_chunk(clamp_chunk(p), p);
@@ -840,48 +855,75 @@ __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 
   }
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");       // nothing may still be writing LDS
 
-  if constexpr (KS > 1) {
-    typedef float Part[KS - 1][S::SM * S::SN][16][64];
-    Part *part = reinterpret_cast<Part *>(lds_raw);
+  // The copies' partial tiles, VW accumulators of a lane at a time: unit u belongs to copy u % KS, which adds the other
+  // copies' to its own, in an order that depends on the tile only, and stores the sum.
+  constexpr int VW = S::VW, kUnits = 16 / VW;
+  typedef float Sums __attribute__((ext_vector_type(VW)));
+  typedef Sums Part[kUnits][KS > 1 ? KS - 1 : 1][S::SM * S::SN][64];
+  Part *part = reinterpret_cast<Part *>(lds_raw);
+  auto sums_of = [&](int u) {
+    Sums x;
 #pragma unroll
-    for (int e0 = 0; e0 < S::kTiles; e0 += S::PER) {
-      if (e0 > 0) __syncthreads();
+    for (int i = 0; i < VW; ++i) x[i] = acc[u / kUnits / WN][u / kUnits % WN][u % kUnits * VW + i];
+    return x;
+  };
+  typedef std::conditional_t<OUTF32, float, uint16_t> Out;
+  const uint32_t row0 = wm * (32 * WM) + 4 * g, col0 = wn * (32 * WN) + r;
+  Out *const c00 = static_cast<Out *>(out) + (m0 + row0) * N + n0 + col0;
+  const bool whole = rows_a == (uint32_t)S::BM && rows_b == (uint32_t)S::BN;
 #pragma unroll
-      for (int e = e0; e < e0 + S::PER && e < S::kTiles; ++e) {
-        const uint32_t owner = e / S::kOwn;
-        if (owner != kg) {
-          const uint32_t slot = kg - (kg > owner ? 1u : 0u);
+  for (int e0 = 0; e0 < S::kTiles; e0 += S::PER) {
+    constexpr int kLast = S::kTiles * kUnits;
+    const int u0 = e0 * kUnits, u1 = u0 + S::PER * kUnits < kLast ? u0 + S::PER * kUnits : kLast;
+    if (e0 > 0) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    each_number<KS>([&](auto number) {
+      constexpr int self = decltype(number)::value;
+      if (kg != (uint32_t)self) return;
 #pragma unroll
-          for (int v = 0; v < 16; ++v) part[e - e0][slot][spatial][v][lane] = acc[e / WN][e % WN][v];
+      for (int u = u0; u < u1; ++u)
+        if (u % KS != self)
+          part[(u - u0) / kUnits][u % kUnits][self - (self > u % KS ? 1 : 0)][spatial][lane] = sums_of(u);
+    });
+    if (KS > 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    Sums sum[S::PER * kUnits / KS];
+    each_number<KS>([&](auto number) {
+      constexpr int self = decltype(number)::value;
+      if (kg != (uint32_t)self) return;
+#pragma unroll
+      for (int u = u0 + self; u < u1; u += KS) {
+        auto sums_from = [&](int copy) {
+          return copy == self ? sums_of(u)
+                              : part[(u - u0) / kUnits][u % kUnits][copy - (copy > self ? 1 : 0)][spatial][lane];
+        };
+        const int first = u / kUnits / S::kOwn;
+        Sums x = sums_from(first);
+#pragma unroll
+        for (int copy = 0; copy < KS; ++copy)
+          if (copy != first) x += sums_from(copy);
+        sum[(u - u0) / KS] = x;
+      }
+    });
+    auto store = [&](bool check) {
+#pragma unroll
+      for (int j = 0; j < (u1 - u0) / KS; ++j) {
+        const uint32_t u = u0 + j * KS + kg, e = u / kUnits, v = u % kUnits * VW;
+        const uint32_t row = 32 * (e / WN) + 8 * (v / 4) + v % 4, col = 32 * (e % WN);
+#pragma unroll
+        for (int i = 0; i < VW; ++i) {
+          if (check && !(row0 + row + i < rows_a && col0 + col < rows_b)) continue;
+          const float c = sum[j][i] * scale;
+          Out *const at = c00 + (int64_t)(row + i) * N + col;
+          if constexpr (OUTF32)
+            *at = c;
+          else
+            *at = (uint16_t)pack_bf16x2(c, 0.0f);
         }
       }
-      __syncthreads();
-#pragma unroll
-      for (int e = e0; e < e0 + S::PER && e < S::kTiles; ++e)
-        if ((uint32_t)(e / S::kOwn) == kg) {
-#pragma unroll
-          for (int v = 0; v < 16; ++v)
-#pragma unroll
-            for (int w = 0; w < KS - 1; ++w) acc[e / WN][e % WN][v] += part[e - e0][w][spatial][v][lane];
-        }
-    }
-  }
-
-#pragma unroll
-  for (int e = 0; e < S::kTiles; ++e) {
-    if (KS > 1 && (uint32_t)(e / S::kOwn) != kg) continue;
-    const uint32_t col = wn * (32 * WN) + 32 * (e % WN) + r;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const uint32_t row = wm * (32 * WM) + 32 * (e / WN) + 8 * (v / 4) + 4 * g + (v % 4);
-      if (row < rows_a && col < rows_b) {
-        const float c = acc[e / WN][e % WN][v] * scale;
-        if (OUTF32)
-          static_cast<float *>(out)[(m0 + row) * N + n0 + col] = c;
-        else
-          static_cast<uint16_t *>(out)[(m0 + row) * N + n0 + col] = (uint16_t)pack_bf16x2(c, 0.0f);
-      }
-    }
+    };
+    if (whole)
+      store(false);
+    else
+      store(true);
   }
 }
 

@@ -26,6 +26,7 @@ struct TileShape {
   static constexpr int T = WM + WN, kTiles = WM * WN;
   // partial sums of the KS groups: each owns kOwn instruction tiles, exchanged in PH phases
   static constexpr int kOwn = KS == 1 ? kTiles : kTiles >= KS ? kTiles / KS : 1;
+  static constexpr int VW = kTiles * 4 >= KS ? 4 : 2;      // accumulators of a lane that go together
   static constexpr int kPartialTile = (KS - 1) * SM * SN * 4096;
   static constexpr int kPerPhaseMax = KS == 1 ? kTiles : 160 * 1024 / kPartialTile;
   static constexpr int PER = kPerPhaseMax < kTiles ? kPerPhaseMax : kTiles;
@@ -33,7 +34,8 @@ struct TileShape {
   static constexpr int LDS = LDS_STAGES > LDS_PART ? LDS_STAGES : LDS_PART;
   static_assert(ROWS * U % 64 == 0 && BM % (64 / U) == 0 && U <= 16, "a copy instruction stays within one operand");
   static_assert(LDS <= 160 * 1024, "the stages must fit the LDS");
-  static_assert(kTiles % KS == 0 || KS % kTiles == 0, "whole tiles per owner");
+  static_assert(kTiles % KS == 0 || KS % kTiles == 0, "kOwn");
+  static_assert(kTiles * (16 / VW) % KS == 0, "as many units for every copy");
   static_assert((NST - 1) * 2 * NC < 63, "vmcnt counts to 63");
 };
 
