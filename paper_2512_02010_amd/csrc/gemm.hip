@@ -704,7 +704,9 @@ __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 
   static_assert(S::kCopies % S::kWaves == 0 && 2 * S::kWaves % U == 0, "one swizzle per lane");
   const uint32_t unit_c = lane % U ^ swz_c(wave * (64 / U) + lane / U);
   const uint32_t unit_s = lane % U ^ swz_s(wave * (64 / U) + lane / U);
-  uint32_t off_c[S::NC], off_s[S::NC];                    // the lane's byte offsets at chunk 0
+  constexpr bool PIECES = KFULL && S::kPieces;            // scales 16 bytes per lane: P such pieces to a row and chunk
+  constexpr int P = PIECES ? S::kPieces : 1;
+  uint32_t off_c[S::NC], off_s[PIECES ? 1 : S::NC];       // the lane's byte offsets at chunk 0
 #pragma unroll
   for (int n = 0; n < S::NC; ++n) {
     const uint32_t i = wave + n * S::kWaves;
@@ -713,7 +715,16 @@ __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 
     const uint32_t line = row - (is_a ? 0u : (uint32_t)S::BM), last = (is_a ? rows_a : rows_b) - 1;
     const uint32_t l = line < last ? line : last;
     off_c[n] = l * row_codes + unit_c * 16;
-    off_s[n] = (l >> (is_a ? sha : shb)) * row_scales + unit_s * 2;
+    if constexpr (!PIECES) off_s[n] = (l >> (is_a ? sha : shb)) * row_scales + unit_s * 2;
+  }
+  // one copy instruction of each of the first kScaleCopies waves
+  constexpr uint32_t kScaleCopiesA = S::BM * P / 64, kScaleCopies = S::ROWS * P / 64;
+  const bool scales_of_a = wave < kScaleCopiesA;
+  if constexpr (PIECES) {
+    static_assert(S::BM * P % 64 == 0 && S::BN * P % 64 == 0 && kScaleCopies <= S::kWaves, "copies of one operand each");
+    const uint32_t piece = (scales_of_a ? wave : wave - kScaleCopiesA) * 64 + lane, row = piece / P;
+    const uint32_t last = (scales_of_a ? rows_a : rows_b) - 1, l = row < last ? row : last;
+    off_s[0] = (l >> (scales_of_a ? sha : shb)) * row_scales + piece % P * 16;
   }
   auto copy_chunk = [&](uint32_t c, uint32_t stage) {
     const uint32_t lds = lds0 + stage * S::STAGE;
@@ -731,8 +742,11 @@ __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 
       const bool is_a = i * (64 / U) < (uint32_t)S::BM;
       const uint8_t *bc = (is_a ? gca : gcb) + k0 / 2, *bs = (is_a ? gsa : gsb) + k0 / 16;
       NV_DMA16(lds + i * 1024, off_c[n] - past_c, bc);
-      NV_DMA2(lds + S::kScaleBase + i * 256, off_s[n] - past_s, bs);
+      if constexpr (!PIECES) NV_DMA2(lds + S::kScaleBase + i * 256, off_s[n] - past_s, bs);
     }
+    if constexpr (PIECES)
+      if (wave < kScaleCopies)
+        NV_DMA16(lds + S::kScaleBase + wave * 1024, off_s[0], (scales_of_a ? gsa : gsb) + k0 / 16);
   };
 
   // a lane's share of one piece: 32 codes and their two scales per operand tile (WM of A, WN of B)
@@ -748,7 +762,10 @@ __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 
     for (int i = 0; i < T; ++i) {
       const uint32_t row = i < WM ? row_a + 32 * i : row_b + 32 * (i - WM);
       x.c[i] = *reinterpret_cast<const v4 *>(st + row * (U * 16) + (u ^ swz_c(r)) * 16);
-      x.s[i] = *reinterpret_cast<const uint32_t *>(st + S::kScaleBase + row * (U * 4) + (u ^ swz_s(r)) * 4);
+      if constexpr (PIECES)
+        x.s[i] = *reinterpret_cast<const uint16_t *>(st + S::kScaleBase + row * (16 * P) + u * 2);
+      else
+        x.s[i] = *reinterpret_cast<const uint32_t *>(st + S::kScaleBase + row * (U * 4) + (u ^ swz_s(r)) * 4);
     }
     if constexpr (!KFULL) {
       const uint32_t keep = c * S::CK + u * 32 < K ? 0xffffffffu : 0u;

@@ -23,6 +23,13 @@ struct TileShape {
   static constexpr int kCopies = ROWS * U / 64;           // copy instructions per chunk, codes (and scales)
   static constexpr int NC = (kCopies + kWaves - 1) / kWaves;
   static constexpr uint32_t kScaleBase = ROWS * U * 16, STAGE = ROWS * U * 20;
+  // Where K is whole chunks, scales are copied in pieces of 16 bytes, this many to a row and chunk, else (0) two bytes
+  // per lane: an eighth of the copy instructions, which the waves of 64 x 64 tiles would otherwise spend as many on as
+  // on codes (us, two bytes / 16: 200 x 4096 x 4096 13.7 / 12.9, 512 x 2048 x 1024 5.9 / 5.6, 3000 x 3000 x 1024 25.3 /
+  // 24.6, 192 x 4096 x 11264 24.9 / 23.8).  32 x 32 and 64 x 32 tiles are slower with it (64 x 1024 x 4096 6.4 / 6.7, 128 x
+  // 4096 x 4096 9.8 / 10.0: one wave's copy of 32 lines, for which all wait), 128 x 128 no faster (1000 x 4096 x 768
+  // 10.6 / 10.6); and where lines begin anywhere, two pieces to a row, 300 x 2000 x 1056 takes 7.4, not 6.5.
+  static constexpr int kPieces = WM * WN == 4 && SM * SN == 1 && CK % 256 == 0 ? CK / 256 : 0;
   static constexpr int T = WM + WN, kTiles = WM * WN;
   // partial sums of the KS groups: each owns kOwn instruction tiles, exchanged in PH phases
   static constexpr int kOwn = KS == 1 ? kTiles : kTiles >= KS ? kTiles / KS : 1;
