@@ -123,60 +123,62 @@ inline GemmKernel fastest_gemm(int64_t M, int64_t N, int64_t K, bool f32) {
   if (K > ((int64_t)1 << 24)) return kGemmStaged;       // 32-bit lane offsets of the others' copies
 
   // Few rows of A against a large weight: the kernels that stream B, one workgroup per 32 columns.
-  // Up to 32 rows always (16 x 8192 x 8192: 9.5, in 32 x 32 tiles 12.1; 32 x 8192 x 28672: 27.8 /
-  // 34.4; B from memory, 16 x 28672 x 8192: 33 / 40, 32 x 28672 x 8192: 41 / 42); from 33 to 64 rows
+  // Up to 32 rows always (16 x 8192 x 8192: 9.5, in 32 x 32 tiles 11.6; 32 x 8192 x 28672: 29.6 /
+  // 33.6; B from memory, 16 x 28672 x 8192: 32 / 40, 32 x 28672 x 8192: 40 / 43, 32 x 4096 x 4096 7.9 / 8.6; but 17 to 32
+  // rows along a short K, or with all operands in the memory-side cache, are as fast or faster in tiles: 32 x 4096 x
+  // 4096 6.8 / 6.5, 32 x 2048 x 1024 4.0 / 3.6, 32 x 512 x 256 3.8 / 3.0); from 33 to 64 rows
   // only between the widths whose 32 x 32 tiles are at most one per compute unit (64 x 4096 x 4096:
-  // 10.2, tiles 7.6) and those that fill the chip in 64 x 64 tiles (B from memory, 33 / 64 x 28672 x
-  // 8192: 52 / 57, tiles 43 / 45; 33 / 64 x 128256 x 4096: 110 / 123, tiles 85 / 93; between them
-  // 64 x 8192 x 8192: 19 / 28); with up to 48 rows and narrower weights where the stream is long,
+  // 9.6, tiles 6.6) and those that fill the chip in 64 x 64 tiles (B from memory, 33 / 64 x 28672 x
+  // 8192: 52 / 57, tiles 46 / 46; 33 / 64 x 128256 x 4096: 108 / 120, tiles 89 / 93; between them
+  // 64 x 8192 x 8192: 17 / 22); with up to 48 rows and narrower weights where the stream is long,
   // which the tiles' one workgroup per compute unit does not keep up with (B from memory, 33 / 48 / 64
-  // rows x 4096 x 28672: 38 / 39 / 45, tiles 42; 33 x 2048 x 53248: 66 / 72; but 33 x 1024 x 16384: 23 /
-  // 20, 33 x 4096 x 8192: 15.5 / 14.6).
+  // rows x 4096 x 28672: 38 / 39 / 45, tiles 41; 33 x 2048 x 53248: 65 / 73; but 33 x 4096 x 8192: 15.1 /
+  // 14.3).
   const int64_t t32 = tiles_of<Tile32>(M, N), t64 = tiles_of<Tile64>(M, N);
   const bool stream_64 = t32 > kCus || (M <= 48 && N * K > ((int64_t)1 << 25));
   if ((K % SK) == 0 && (M <= 32 || (M <= 64 && t64 <= kCus && stream_64))) return kGemmSkinny;
 
   // The largest tiles (the fewest expansions and copies per product) that leave little of the chip idle, padding
   // counted as idle.  k_gemm_dma's three shapes (the shape / what would run else):
-  //   256 x 256 from 62 %: 6144 x 6400 x 1056 (78 %) 112 / 114, 2816 x 4096 x 4064 (69 %) 88 / 108, x 32 13.2 / 19.8,
-  //   8192 x 8192 x 96 44 / 69; 3000 x 3000 x 1024 (56 %) 28.0 / 27.4;
-  //   256 x 128 from 62 % of one turn, 72 % of several: 2048 x 4096 x 4096 58 / 69.5, 1536 x 4096 x 4096 (75 %) 49 / 62,
-  //   6798 x 880 x 4160 (73 %) 54 / 76, 192 x 28672 x 8192 (66 %) 96 / 103, 996 x 5232 x 704 (64 %) 17.7 / 19.5; 3388 x
-  //   1408 x 2304 (60 %) 29.7 / 29.1, 4798 x 912 x 768 (59 %) 16.5 / 16.2; three turns: 8324 x 1925 x 256 (66 %) 22 % and
-  //   6496 x 2681 x 256 (70 %) 19 % longer than in 64 x 64;
+  //   256 x 256 from 62 %: 6144 x 6400 x 1056 (78 %) 104 / 108, 2816 x 4096 x 4064 (69 %) 93 / 107, x 32 12.8 / 15.6,
+  //   8192 x 8192 x 96 44 / 62; 3000 x 3000 x 1024 (56 %) 29.6 / 26.3;
+  //   256 x 128 from 62 % of one turn, 72 % of several: 2048 x 4096 x 4096 63 / 68.5, 1536 x 4096 x 4096 (75 %) 52 / 56,
+  //   6798 x 880 x 4160 (73 %) 55 / 63, 192 x 28672 x 8192 (66 %) 101 / 103, 1024 x 5000 x 1024 (62 %) 15.2 / 16.3, but the
+  //   shorter K of 996 x 5232 x 704 (64 %) 16.2 / 15.1 in 64 x 64; 3388 x 1408 x 2304 (60 %) 29.9 / 28.0, 4798 x 912 x 768
+  //   (59 %) 15.4 / 13.2; three turns: 8324 x 1925 x 256 (66 %) 30 / 22 and 6496 x 2681 x 256 (70 %) 31 / 22;
   //   128 x 128 from 70 % of one turn and a K whose quarters outlast their sum's way through LDS: 1000 x 4096 x 4096
-  //   32.7 / 38.4, 768 x 4096 x 4096 (75 %) 28.3 / 30.2, 128 x 28672 x 8192 (87 %) 54 / 65; 575 x 4526 x 4352 (63 %)
-  //   35.3 / 31.8; 1000 x 4096 x 1024 13.9 / 14.5 but x 256 10.2 / 9.5; two turns and more 3000 x 3000 x 1024 35 / 27.
+  //   33.5 / 36.6, 768 x 4096 x 4096 (75 %) 28.7 / 30.0, 128 x 28672 x 8192 (87 %) 56 / 68; 575 x 4526 x 4352 (63 %)
+  //   29.8 / 29.6; 1000 x 4096 x 1024 13.5 / 13.2 and x 256 9.3 / 7.4; two turns and more 3000 x 3000 x 1024 35 / 27.
   // They store 16 bytes per lane, which takes a quarter longer (3 to 5 us of one turn) where the lines of C do not
   // begin at multiples of 16 bytes.  The smaller two shapes are then ahead of k_gemm_tile, which stores column by
-  // column, only along a longer K (2048 x 4095: K = 32 14.0 / 11.7, 256 16.3 / 13.0, 640 21.4 / 19.5; 1654 x 4428 x 128
-  // 17 % longer; 128 x 128: 4055 x 738 x 1536, fp32, 19 % longer).
+  // column, only along a longer K (2048 x 4095: K = 32 13.2 / 11.1, 256 15.3 / 12.5, 640 20.3 / 17.9; 1654 x 4428 x 128
+  // 12.7 / 10.5; 128 x 128: 4055 x 738 x 1536, fp32, 19 % longer).
   const bool skewed = N * (f32 ? 4 : 2) % 16 != 0, one_turn = tiles_of<Dma256x128>(M, N) <= kCus;
   if (chip_filled<Dma256>(M, N) >= 0.62) return kGemmDma;
   if (chip_filled<Dma256x128>(M, N) >= (one_turn ? 0.62 : 0.72) && !(one_turn && skewed && K < 1024))
     return kGemmDma256x128;
   if (K >= (skewed ? 2048 : 1024) && tiles_of<Dma128>(M, N) <= kCus && chip_filled<Dma128>(M, N) >= 0.7)
     return kGemmDma128;
-  // ... and k_gemm_tile's: 256 x 128 from 80 % (2048 x 3072 x 4096, 75 %: 59, in 64 x 64 tiles 55), 128 x 128 from 87 %
-  // (1000 x 4096 x 4096: 35, in 64 x 64 38; 2048 x 3072 x 4096, 75 %: 63), both only where they cover 80 % of it (192 x
-  // 28672 x 8192, 75 %: 120 in 256 x 128, 107 in 64 x 64; 1340 x 4464 x 5504, 87 %: 76 / 83).
+  // ... and k_gemm_tile's: 256 x 128 from 80 % (2048 x 3072 x 4096, 75 %: 57, in 64 x 64 tiles 56), 128 x 128 from 87 %
+  // (1000 x 4096 x 800: 12.0, in 64 x 64 13.3; 2048 x 3072 x 4096, 75 %: 62), both only where they cover 80 % of it (192 x
+  // 28672 x 8192, 75 %: 116 in 256 x 128, 103 in 64 x 64).
   if (fills_chip<Tile256x128>(M, N, 0.8)) return kGemmTile256x128;
   if (fills_chip<Tile128>(M, N, 0.87)) return kGemmTile128;
   // Small products: the smallest tiles that are at most one per compute unit (64 x 1024 x 4096:
-  // 7.6 in 32 x 32, 9.9 in 64 x 32, 13.0 in 64 x 64; 128 x 4096 x 4096: 11.4 / 10.6 / 13.1; 200 x
-  // 4096 x 4096: 18.8 / 15.1 / 13.9); 32 rows or columns would leave larger tiles half empty (B from
-  // memory, 16 x 28672 x 8256: 43 / 59 / 49, and 120 in 256 x 128).  Along a long K two tiles of
-  // 32 x 32 per compute unit still beat fewer larger ones (B from memory, 65 x 5120 x 8192: 18 / 25 /
-  // 27; 128 x 4096 x 28672: 55 / 75 / 84; 256 x 2048 x 28672: 59 / 76 / 82; but 128 x 4096 x 4096: 11.5 /
-  // 11.4 / 13.6, and with K no whole number of their chunks 256 x 2048 x 11008: 25 / 22).
+  // 6.3 in 32 x 32, 8.9 in 64 x 32, 11.9 in 64 x 64; 128 x 4096 x 4096: 10.1 / 9.4 / 12.5; 200 x
+  // 4096 x 4096: 16.2 / 14.3 / 13.0); 32 rows or columns would leave larger tiles half empty (B from
+  // memory, 16 x 28672 x 8256: 40 / 54 / 49, and 124 in 256 x 128).  Along a long K two tiles of
+  // 32 x 32 per compute unit still beat fewer larger ones (B from memory, 65 x 5120 x 8192: 18 / 24 /
+  // 26; 128 x 4096 x 28672: 59 / 74 / 83; 256 x 2048 x 28672: 59 / 72 / 82; with K no whole number of their chunks 256 x
+  // 2048 x 11008 26 / 29 too; not from memory 128 x 4096 x 4096 10.1 / 9.4).
   const int64_t t64x32 = tiles_of<Tile64x32>(M, N);
   const bool two_of_32 = K >= 8192 && (K % Tile32::CK == 0 || t64x32 > kCus);
   if (M <= 32 || t32 <= (two_of_32 ? 2 : 1) * kCus) return kGemmTile32;
   if (N <= 32 || t64x32 <= kCus) return kGemmTile64x32;
   // 64 x 64 tiles, at most one per compute unit: along a long K in eight copies, since four waves wait
-  // for most of every chunk (four / eight copies, B from memory, 128 x 8192 x 8192: 27.6 / 23.1; 192 x
-  // 4096 x 11008: 33.8 / 30.9; 128 x 8192 x 28672: 86 / 72).  Their chunks are twice as long, and a shorter
-  // K may leave the last one half empty (141 x 4652 x 4352: 15.2 / 16.3).
+  // for most of every chunk (four / eight copies, B from memory, 128 x 8192 x 8192: 29.1 / 24.9; 192 x
+  // 4096 x 11008: 32.6 / 28.7; 128 x 8192 x 28672: 89 / 78).  Their chunks are twice as long, and a shorter
+  // K leaves the last one emptier, which costs less since the empty pieces are left out (141 x 4652 x 4352: 15.4 / 13.7).
   if (K >= 8192 && t64 <= kCus) return kGemmTile64Long;
   return kGemmTile64;
 }
