@@ -658,8 +658,8 @@ __global__ __launch_bounds__(S::kThreads, 1) void k_gemm_dma(
 // looking at its edges.  In a replayed graph, us, before / after: 64 x 1024 x 4096 7.1 / 6.4, 128 x 2000 x 1056 5.3 / 4.0,
 // 128 x 4096 x 4096 10.3 / 9.1, 300 x 2000 x 1056 7.5 / 6.6, 2880 x 1440 x 1056 20.9 / 18.2, 192 x 4096 x 11008 30.7 / 26.6,
 // 1000 x 4096 x 800 14.5 / 12.5; no change where the loop is all (1536 x 4096 x 8192 91).
-template <typename S, bool KFULL, bool OUTF32>
-__global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 : 4) void k_gemm_tile(
+template <typename S, bool KFULL, bool OUTF32, bool FIRST>
+NV_DEV void gemm_tile(
     const uint8_t *__restrict__ codes_a, const uint8_t *__restrict__ scales_a,
     const float *__restrict__ alpha_a, const uint8_t *__restrict__ codes_b,
     const uint8_t *__restrict__ scales_b, const float *__restrict__ alpha_b,
@@ -691,8 +691,11 @@ __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 
     return reinterpret_cast<const uint8_t *>(((uint64_t)hi << 32) | lo);
   };
   const uint8_t *gca = uniform(codes_a + m0 * row_codes), *gcb = uniform(codes_b + n0 * row_codes);
-  const uint8_t *gsa = uniform(scales_a + (m0 >> sha) * row_scales);
-  const uint8_t *gsb = uniform(scales_b + (n0 >> shb) * row_scales);
+  // the tiles' first scales (FIRST: the 16 bytes that hold them, and how far they are into those)
+  const int64_t at_a = (m0 >> sha) * row_scales, at_b = (n0 >> shb) * row_scales;
+  const uint32_t into_a = FIRST ? (uint32_t)at_a & 15u : 0u, into_b = FIRST ? (uint32_t)at_b & 15u : 0u;
+  const uint8_t *gsa = uniform(scales_a + (at_a - into_a)), *gsb = uniform(scales_b + (at_b - into_b));
+  constexpr uint32_t kStage = FIRST ? S::kScaleBase : S::STAGE;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds_raw;
 
   // 16 / U rows of codes, and 64 / U rows of pairs, fill the 256 bytes of all banks once
@@ -706,7 +709,7 @@ __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 
   const uint32_t unit_s = lane % U ^ swz_s(wave * (64 / U) + lane / U);
   constexpr bool PIECES = KFULL && S::kPieces;            // scales 16 bytes per lane: P such pieces to a row and chunk
   constexpr int P = PIECES ? S::kPieces : 1;
-  uint32_t off_c[S::NC], off_s[PIECES ? 1 : S::NC];       // the lane's byte offsets at chunk 0
+  uint32_t off_c[S::NC], off_s[PIECES || FIRST ? 1 : S::NC];       // the lane's byte offsets at chunk 0
 #pragma unroll
   for (int n = 0; n < S::NC; ++n) {
     const uint32_t i = wave + n * S::kWaves;
@@ -715,7 +718,7 @@ __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 
     const uint32_t line = row - (is_a ? 0u : (uint32_t)S::BM), last = (is_a ? rows_a : rows_b) - 1;
     const uint32_t l = line < last ? line : last;
     off_c[n] = l * row_codes + unit_c * 16;
-    if constexpr (!PIECES) off_s[n] = (l >> (is_a ? sha : shb)) * row_scales + unit_s * 2;
+    if constexpr (!PIECES && !FIRST) off_s[n] = (l >> (is_a ? sha : shb)) * row_scales + unit_s * 2;
   }
   // one copy instruction of each of the first kScaleCopies waves
   constexpr uint32_t kScaleCopiesA = S::BM * P / 64, kScaleCopies = S::ROWS * P / 64;
@@ -727,7 +730,7 @@ __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 
     off_s[0] = (l >> (scales_of_a ? sha : shb)) * row_scales + piece % P * 16;
   }
   auto copy_chunk = [&](uint32_t c, uint32_t stage) {
-    const uint32_t lds = lds0 + stage * S::STAGE;
+    const uint32_t lds = lds0 + stage * kStage;
     const uint32_t k0 = c * S::CK;
     // units past the end of K: the row's last one instead
     uint32_t past_c = 0, past_s = 0;
@@ -742,27 +745,52 @@ __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 
       const bool is_a = i * (64 / U) < (uint32_t)S::BM;
       const uint8_t *bc = (is_a ? gca : gcb) + k0 / 2, *bs = (is_a ? gsa : gsb) + k0 / 16;
       NV_DMA16(lds + i * 1024, off_c[n] - past_c, bc);
-      if constexpr (!PIECES) NV_DMA2(lds + S::kScaleBase + i * 256, off_s[n] - past_s, bs);
+      if constexpr (!PIECES && !FIRST) NV_DMA2(lds + S::kScaleBase + i * 256, off_s[n] - past_s, bs);
     }
     if constexpr (PIECES)
       if (wave < kScaleCopies)
         NV_DMA16(lds + S::kScaleBase + wave * 1024, off_s[0], (scales_of_a ? gsa : gsb) + k0 / 16);
   };
 
+  // FIRST: all scales of a tile, whose lines follow each other in memory, to LDS behind the stages
+  const uint32_t first_a = NST * kStage, first_b = first_a + S::first_scales(S::BM, row_scales);
+  auto copy_scales = [&](const uint8_t *from, uint32_t bytes, uint32_t to) {
+    for (uint32_t i = wave * 1024; i < bytes; i += S::kWaves * 1024) {
+      const uint32_t off = i + lane * 16;
+      if (off + 16 <= bytes) {
+        NV_DMA16(lds0 + to + i, off, from);
+      } else {
+        // an edge of C, in the middle of 16 bytes
+        uint16_t last[7];
+        auto place = [&](int j) { return off + 2 * j < bytes - 2 ? off + 2 * j : bytes - 2; };
+        if (off < bytes) {
+#pragma unroll
+          for (int j = 0; j < 7; ++j) last[j] = *reinterpret_cast<const uint16_t *>(from + place(j));
+#pragma unroll
+          for (int j = 0; j < 7; ++j) *reinterpret_cast<uint16_t *>(lds_raw + to + place(j)) = last[j];
+        }
+      }
+    }
+  };
   // a lane's share of one piece: 32 codes and their two scales per operand tile (WM of A, WN of B)
   struct Raw {
     v4 c[T];
     uint32_t s[T];
   };
   const uint32_t row_a = wm * (32 * WM) + r, row_b = S::BM + wn * (32 * WN) + r;
+  const uint32_t line_a = first_a + into_a + (row_a >> sha) * row_scales;
+  const uint32_t line_b = first_b + into_b + ((row_b - S::BM) >> shb) * row_scales;
   auto read_piece = [&](uint32_t c, uint32_t stage, uint32_t h, Raw &x) {
     const uint32_t u = 2 * (kg * HPW + h) + g;
-    const uint8_t *st = lds_raw + stage * S::STAGE;
+    const uint8_t *st = lds_raw + stage * kStage;
 #pragma unroll
     for (int i = 0; i < T; ++i) {
       const uint32_t row = i < WM ? row_a + 32 * i : row_b + 32 * (i - WM);
       x.c[i] = *reinterpret_cast<const v4 *>(st + row * (U * 16) + (u ^ swz_c(r)) * 16);
-      if constexpr (PIECES)
+      if constexpr (FIRST) {
+        const uint32_t line = i < WM ? line_a + (32 * i >> sha) * row_scales : line_b + (32 * (i - WM) >> shb) * row_scales;
+        x.s[i] = *reinterpret_cast<const uint16_t *>(lds_raw + line + (c * U + u) * 2);
+      } else if constexpr (PIECES)
         x.s[i] = *reinterpret_cast<const uint16_t *>(st + S::kScaleBase + row * (16 * P) + u * 2);
       else
         x.s[i] = *reinterpret_cast<const uint32_t *>(st + S::kScaleBase + row * (U * 4) + (u ^ swz_s(r)) * 4);
@@ -808,6 +836,10 @@ __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 
       }
     };
     copy_chunk(0, 0);
+    if constexpr (FIRST) {
+      copy_scales(gsa, into_a + (((rows_a - 1) >> sha) + 1) * row_scales, first_a);
+      copy_scales(gsb, into_b + (((rows_b - 1) >> shb) + 1) * row_scales, first_b);
+    }
     // chunk c is complete, and nobody reads the other stage, chunk c - 1's, any more
     auto wait_for_chunk = [] { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
     for (uint32_t c = 0; c + 1 < nchunks; ++c) {
@@ -942,6 +974,31 @@ __global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 
     else
       store(true);
   }
+}
+
+template <typename S, bool KFULL, bool OUTF32>
+__global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 : 4) void k_gemm_tile(
+    const uint8_t *__restrict__ codes_a, const uint8_t *__restrict__ scales_a,
+    const float *__restrict__ alpha_a, const uint8_t *__restrict__ codes_b,
+    const uint8_t *__restrict__ scales_b, const float *__restrict__ alpha_b,
+    void *__restrict__ out, int64_t M, int64_t N, uint32_t K, uint32_t tiles_m, uint32_t tiles_n,
+    uint32_t strip, uint32_t sha, uint32_t shb) {
+  gemm_tile<S, KFULL, OUTF32, false>(
+      codes_a, scales_a, alpha_a, codes_b, scales_b, alpha_b, out, M, N, K, tiles_m, tiles_n, strip,
+      sha, shb);
+}
+
+// The same with all scales copied before the first chunk: S::scales_first() (125 registers).
+template <typename S, bool OUTF32>
+__global__ __launch_bounds__(S::kThreads, S::kTiles > 8 ? 1 : S::kTiles > 4 ? 2 : 4) void k_gemm_scales_first(
+    const uint8_t *__restrict__ codes_a, const uint8_t *__restrict__ scales_a,
+    const float *__restrict__ alpha_a, const uint8_t *__restrict__ codes_b,
+    const uint8_t *__restrict__ scales_b, const float *__restrict__ alpha_b,
+    void *__restrict__ out, int64_t M, int64_t N, uint32_t K, uint32_t tiles_m, uint32_t tiles_n,
+    uint32_t strip, uint32_t sha, uint32_t shb) {
+  gemm_tile<S, false, OUTF32, true>(
+      codes_a, scales_a, alpha_a, codes_b, scales_b, alpha_b, out, M, N, K, tiles_m, tiles_n, strip,
+      sha, shb);
 }
 
 // ----------------------------------------------------------------------------------------
@@ -1736,6 +1793,8 @@ int run_gemm_tile(const GemmArgs &a) {
                            a.shb);
   };
   if (a.K % S::CK == 0) return a.f32 ? go(k_gemm_tile<S, true, true>) : go(k_gemm_tile<S, true, false>);
+  if constexpr (S::kFirst)
+    if (S::scales_first(a.K)) return a.f32 ? go(k_gemm_scales_first<S, true>) : go(k_gemm_scales_first<S, false>);
   return a.f32 ? go(k_gemm_tile<S, false, true>) : go(k_gemm_tile<S, false, false>);
 }
 #endif

@@ -31,6 +31,18 @@ struct TileShape {
   // 10.6 / 10.6); and where lines begin anywhere, two pieces to a row, 300 x 2000 x 1056 takes 7.4, not 6.5.
   static constexpr int kPieces = WM * WN == 4 && SM * SN == 1 && CK % 256 == 0 ? CK / 256 : 0;
   static constexpr int T = WM + WN, kTiles = WM * WN;
+  // 64 x 64 tiles: where K is no whole number of chunks but all scales of both tiles fit the LDS beside the stages, which is
+  // up to K = 2016, they are copied there before the first chunk, as one run of memory: `rows` lines, which may begin 14
+  // bytes into the first 16 (us, two bytes per lane and chunk / this: 2880 x 1440 x 1056 17.4 / 16.3, 575 x 2048 x 1056
+  // 9.1 / 8.5, 900 x 1600 x 2016 12.4 / 11.4, 1000 x 1000 x 1312 7.4 / 7.2).  Not below four chunks (501 x 1333 x 736 5.5 /
+  // 5.7: an edge's last bytes have a latency of their own), nor in the smaller tiles (128 x 2000 x 1056 4.15 / 4.15, 100 x
+  // 3000 x 544 4.2 / 4.3); 128 x 128 has no registers for it.
+  static constexpr uint32_t first_scales(int rows, uint32_t row_scales) { return (rows * row_scales + 31) & ~15u; }
+  static constexpr bool kFirst = WM * WN == 4 && SM * SN == 1 && KS == 4;
+  static constexpr bool scales_first(int64_t K) {
+    return kFirst && K % CK != 0 && K >= 4 * CK && K <= 8192 &&
+           NST * kScaleBase + first_scales(BM, (uint32_t)K / 16) + first_scales(BN, (uint32_t)K / 16) + 2 * U <= LDS;
+  }
   // partial sums of the KS groups: each owns kOwn instruction tiles, exchanged in PH phases
   static constexpr int kOwn = KS == 1 ? kTiles : kTiles >= KS ? kTiles / KS : 1;
   static constexpr int VW = kTiles * 4 >= KS ? 4 : 2;      // accumulators of a lane that go together
