@@ -1425,6 +1425,9 @@ struct FewRows {
   static constexpr uint32_t lds(uint32_t M, uint32_t K) {
     return kWaves * NST * STAGE + M * (code_pitch(K) + scale_pitch(K));
   }
+  // no size takes more: at most kFewValues values and as much padding, 16 bytes of code pitch and 4 of scale pitch as 16 rows have
+  static constexpr uint32_t kMostLds = kWaves * NST * STAGE + (kFewValues + 16 * (SK - 32)) / 16 * 9 + 16 * 20;
+  static_assert(kMostLds + sizeof(ScaleTable) + kWaves * sizeof(float) <= 160 * 1024, "the LDS of a compute unit");
 };
 static_assert(FewRows<1>::kBlocks * FewRows<1>::kThreads * 16 >= kFewValues, "a block per lane and turn");
 static_assert(FewRows<2>::NST * FewRows<2>::STAGE >= 2 * 4 * 64 * sizeof(float), "a wave's sums fit its stages");
@@ -1666,7 +1669,9 @@ struct FewRowsArgs {
 };
 
 // Every run_* raises the kernel's dynamic LDS limit (most need more than the 64 KiB a
-// kernel gets without asking), launches, and returns a status of the C ABI.
+// kernel gets without asking), launches, and returns a status of the C ABI.  The limit belongs to the
+// kernel and not to the call, so it is the same in every call: another thread's smaller one, set between
+// this thread's two steps, would refuse the launch.
 template <bool KFULL, bool OUTF32>
 int run_gemm_staged(const GemmArgs &a);
 template <typename S>
@@ -1677,14 +1682,20 @@ int run_gemm_tile(const GemmArgs &a);
 int run_few_rows(const FewRowsArgs &a);
 
 template <typename Kernel, typename... Args>
-static int launch_with_lds(Kernel kernel, dim3 grid, dim3 block, size_t lds_bytes, hipStream_t s,
-                           Args... args) {
+static int launch_with_lds_of(Kernel kernel, size_t most_lds_bytes, dim3 grid, dim3 block, size_t lds_bytes, hipStream_t s,
+                              Args... args) {
   if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                          (int)lds_bytes) != hipSuccess) {
+                          (int)most_lds_bytes) != hipSuccess) {
     return NVFP4_ERR_HIP;
   }
   return launch(kernel, grid, block, lds_bytes, s, args...);
+}
+// ... of a kernel that always has the same
+template <typename Kernel, typename... Args>
+static int launch_with_lds(Kernel kernel, dim3 grid, dim3 block, size_t lds_bytes, hipStream_t s,
+                           Args... args) {
+  return launch_with_lds_of(kernel, lds_bytes, grid, block, lds_bytes, s, args...);
 }
 
 // Strip width (in tiles) that makes an eighth of the tiles about square: h x w tiles of BM x BN with
@@ -1771,9 +1782,9 @@ int run_gemm_skinny(const GemmArgs &a) {
 int run_few_rows(const FewRowsArgs &a) {
   auto go = [&](auto kernel, auto shape) {
     typedef decltype(shape) S;
-    return launch_with_lds(kernel, dim3((uint32_t)((a.N + S::COLS - 1) / S::COLS)), dim3(S::kThreads),
-                           S::lds((uint32_t)a.M, (uint32_t)a.K), a.stream, a.x, a.codes_b, a.scales_b, a.alpha_b,
-                           a.out, (uint32_t)a.M, a.N, (uint32_t)a.K, a.shb, a.fp8_max);
+    return launch_with_lds_of(kernel, S::kMostLds, dim3((uint32_t)((a.N + S::COLS - 1) / S::COLS)), dim3(S::kThreads),
+                              S::lds((uint32_t)a.M, (uint32_t)a.K), a.stream, a.x, a.codes_b, a.scales_b, a.alpha_b,
+                              a.out, (uint32_t)a.M, a.N, (uint32_t)a.K, a.shb, a.fp8_max);
   };
   // at most one workgroup per compute unit, in the narrower of the two
   if ((a.N + 15) / 16 <= kCus) return go(k_few_rows<1>, FewRows<1>{});
