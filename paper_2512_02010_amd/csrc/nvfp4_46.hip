@@ -17,7 +17,7 @@
 //             staging loads, so x is read from HBM once.
 #include <hip/hip_runtime.h>
 
-#include <mutex>
+#include <atomic>
 
 #include "block.hpp"
 #include "launch.hpp"
@@ -1694,25 +1694,62 @@ static int check_workspace(const void *workspace, size_t bytes) {
   return aligned16(workspace) ? NVFP4_OK : NVFP4_ERR_ALIGN;
 }
 
+// Two sets of scratch words, the maximum and ticket words of the one-launch reduction (see AmaxFinish), 4352
+// bytes each; every GPU the library runs on holds its own copy until the process ends.  The first belongs to
+// nvfp4_46_tensor_scale_static, the second to calls on the default stream that bring no workspace.
+// In host code the array's name only stands for the symbol: the device address is looked up once per device
+// and that pointer is what kernels get (threads that look it up at the same time find the same).
+static __device__ __align__(256) uint32_t scratch[2 * kScratchWords];
+static_assert(kScratchWords * sizeof(uint32_t) == NVFP4_46_TENSOR_SCALE_WS_BYTES, "header and kernels agree on the scratch size");
+constexpr int kMaxDevices = 64;
+static std::atomic<uint32_t *> g_scratch_ptr[kMaxDevices];   // per device; nullptr until that device's first call
+
+static uint32_t *scratch_of_device() {
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
+  uint32_t *words = g_scratch_ptr[dev].load(std::memory_order_relaxed);
+  if (!words) {
+    void *sym = nullptr;
+    if (hipGetSymbolAddress(&sym, HIP_SYMBOL(scratch)) != hipSuccess || !sym) return nullptr;
+    words = static_cast<uint32_t *>(sym);
+    g_scratch_ptr[dev].store(words, std::memory_order_relaxed);
+  }
+  return words;
+}
+
+// Scratch words for a call that brings none.  Work on a device's default stream (handle 0, one for all threads) runs in
+// the order of its calls and is never captured into a graph, so one set serves all of it; any other
+// stream gets nullptr, the form of three launches (us per call from Python among others, three / one: BF16 1 MiB
+// 10.0 / 4.8, 8 MiB 9.6 / 4.8, 32 MiB 10.8 / 5.3, 128 MiB 23.6 / 22.0, with the columnwise transform 9.9 / 5.9,
+// 9.8 / 6.0, 12.1 / 7.3 and 26.9 / 23.6; 512 KiB, one workgroup before, 5.4 / 4.7).
+static uint32_t *lent_words(hipStream_t stream) {
+  if (stream) return nullptr;
+  uint32_t *const words = scratch_of_device();
+  return words ? words + kScratchWords : nullptr;
+}
+
 // Eq. (1) for all entry points.  scratch == nullptr: the reduction runs on the caller's
 // alpha word between a zeroing launch and a finishing launch.  Otherwise scratch points at
-// kScratchWords zeroed words and one launch does it all (see AmaxFinish).
-static int tensor_scale(const void *x, const nvfp4_46_params *p, float *alpha, uint32_t *scratch,
+// kScratchWords zeroed words and one launch does it all (see AmaxFinish).  `workspace`: the caller's words, or
+// nullptr for such as can be lent.
+static int tensor_scale(const void *x, const nvfp4_46_params *p, float *alpha, uint32_t *workspace,
                         hipStream_t s) {
   if (!alpha) return NVFP4_ERR_NULL;
   int rc = check_params(x, p, false);
   if (rc != NVFP4_OK) return rc;
-  uint32_t *amax = reinterpret_cast<uint32_t *>(alpha);      // the plain form's running maximum
-  const AmaxFinish fin{scratch, alpha, p->fp8_max};
   const int64_t n = p->rows * p->cols;
   const bool xf32 = p->x_dtype == NVFP4_X_F32;
   const uint4 *x4 = static_cast<const uint4 *>(x);
   const int64_t bytes = n * (xf32 ? 4 : 2);
-  if (!p->rht && scale_in_one_workgroup(bytes, scratch != nullptr)) {
+  // (a call on the default stream counts as one with scratch words)
+  if (!p->rht && scale_in_one_workgroup(bytes, workspace != nullptr || s == nullptr)) {
     const uint32_t n16 = (uint32_t)(bytes / 16);       // n is a multiple of 8 by the shape checks
     return xf32 ? launch(k_scale_small<true>, dim3(1), dim3(kSmallThreads), s, x4, n16, alpha, p->fp8_max)
                 : launch(k_scale_small<false>, dim3(1), dim3(kSmallThreads), s, x4, n16, alpha, p->fp8_max);
   }
+  uint32_t *const scratch = workspace ? workspace : lent_words(s);
+  uint32_t *amax = reinterpret_cast<uint32_t *>(alpha);      // the plain form's running maximum
+  const AmaxFinish fin{scratch, alpha, p->fp8_max};
   if (!scratch) {
     rc = launch(k_store_u32, dim3(1), dim3(1), s, amax, 0u);
     if (rc != NVFP4_OK) return rc;
@@ -1757,45 +1794,8 @@ using namespace nvfp4_46;
 
 extern "C" {
 
-// Two sets of scratch words, the maximum and ticket words of the one-launch reduction (see AmaxFinish), 4352
-// bytes each; every GPU the library runs on holds its own copy until the process ends.  The first belongs to
-// nvfp4_46_tensor_scale_static, the second to calls on the default stream that bring no workspace.
-// In host code the array's name only stands for the symbol: the device address is looked up once per device
-// and that pointer is what kernels get.
-static __device__ __align__(256) uint32_t scratch[2 * kScratchWords];
-static_assert(kScratchWords * sizeof(uint32_t) == NVFP4_46_TENSOR_SCALE_WS_BYTES, "header and kernels agree on the scratch size");
-
-namespace {
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mutex;
-uint32_t *g_scratch_ptr[kMaxDevices];   // per device; nullptr until that device's first call
-
-uint32_t *scratch_of_device() {
-  int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
-  std::lock_guard<std::mutex> lock(g_scratch_mutex);
-  if (!g_scratch_ptr[dev]) {
-    void *sym = nullptr;
-    if (hipGetSymbolAddress(&sym, HIP_SYMBOL(scratch)) != hipSuccess || !sym) return nullptr;
-    g_scratch_ptr[dev] = static_cast<uint32_t *>(sym);
-  }
-  return g_scratch_ptr[dev];
-}
-
-// Scratch words for a call that brings none.  Work on a device's default stream (handle 0, one for all threads) runs in
-// the order of its calls and is never captured into a graph, so one set serves all of it; any other
-// stream gets nullptr, the form of three launches (us per call from Python among others, three / one: BF16 1 MiB
-// 10.0 / 4.8, 8 MiB 9.6 / 4.8, 32 MiB 10.8 / 5.3, 128 MiB 23.6 / 22.0, with the columnwise transform 9.9 / 5.9,
-// 9.8 / 6.0, 12.1 / 7.3 and 26.9 / 23.6; 512 KiB, one workgroup before, 5.4 / 4.7).
-uint32_t *lent_words(void *stream) {
-  if (stream) return nullptr;
-  uint32_t *const words = scratch_of_device();
-  return words ? words + kScratchWords : nullptr;
-}
-}  // namespace
-
 int nvfp4_46_tensor_scale(const void *x, const nvfp4_46_params *p, float *alpha, void *stream) {
-  return tensor_scale(x, p, alpha, lent_words(stream), static_cast<hipStream_t>(stream));
+  return tensor_scale(x, p, alpha, nullptr, static_cast<hipStream_t>(stream));
 }
 
 int nvfp4_46_tensor_scale_ws(const void *x, const nvfp4_46_params *p, float *alpha,
@@ -1857,7 +1857,6 @@ int nvfp4_46_scale_quantize(const void *x, const nvfp4_46_params *p, float *alph
   if (rc != NVFP4_OK) return rc;
   const bool xf32 = p->x_dtype == NVFP4_X_F32;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  uint32_t *const words = workspace ? static_cast<uint32_t *>(workspace) : lent_words(stream);
   if (p->layout == NVFP4_ROWWISE && p->rounding == NVFP4_RTN && !p->rht && !p->block2d &&
       scale_and_codes_in_one_launch(p->rows * p->cols * (xf32 ? 4 : 2), workspace != nullptr)) {
     FlatArgs a{xf32, static_cast<const uint4 *>(x), nullptr, static_cast<uint2 *>(codes_row),
@@ -1866,7 +1865,7 @@ int nvfp4_46_scale_quantize(const void *x, const nvfp4_46_params *p, float *alph
                AmaxFinish{nullptr, alpha, p->fp8_max}};
     return dispatch_flat(a, p->rounding, p->select, false, kOutScaleAndCodes);
   }
-  rc = tensor_scale(x, p, alpha, words, s);
+  rc = tensor_scale(x, p, alpha, static_cast<uint32_t *>(workspace), s);
   if (rc != NVFP4_OK) return rc;
   return nvfp4_46_quantize(x, p, alpha, codes_row, scales_row, codes_col, scales_col, choice_row,
                            choice_col, stream);
@@ -1890,11 +1889,12 @@ int nvfp4_46_wgrad_operands(const void *dy, const void *x, int64_t rows, int64_t
   if (rc == NVFP4_OK) rc = check_outputs(&px, nullptr, nullptr, codes_x, scales_x, nullptr, nullptr);
   if (rc != NVFP4_OK) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  uint32_t *const words = workspace ? static_cast<uint32_t *>(workspace) : lent_words(stream);
+  const bool in_cache = rows * (n + k) * 2 <= kLastLevelBytes;
+  uint32_t *const words = !in_cache ? nullptr : workspace ? static_cast<uint32_t *>(workspace) : lent_words(s);
   // (us in a replayed graph with the product, four launches / two: 64 tokens, 256 x 256 25.5 / 15.4, 736 tokens, 1024 x 1024
   // 35.8 / 20.1, 2048 tokens, 2048 x 2048 59 / 43, 4096 x 4096 103 / 94, 8192 tokens 307 / 297; what no longer fits the
   // memory-side cache goes one after the other, the second pass over a tensor last to first)
-  if (!words || rows * (n + k) * 2 > kLastLevelBytes) {
+  if (!words) {
     rc = nvfp4_46_scale_quantize(dy, &pd, alpha_dy, workspace, workspace_bytes, nullptr, nullptr, codes_dy, scales_dy,
                                  nullptr, nullptr, stream);
     if (rc != NVFP4_OK) return rc;

@@ -24,3 +24,44 @@ result = calls()
     assert any(len(sizes) > 5 for sizes in launches.values())          # k_few_rows' own need varies
     for kernel, sizes in launches.items():
         assert len(limits[kernel]) == 1 and max(sizes) <= min(limits[kernel]), (limits[kernel], sizes)
+
+
+def test_refused_calls_make_no_hip_call():
+    made = _hip_calls.run("""
+bad = [params(0, 1024), params(16, 1000), params(16, 1024, layout=0), params(16, 1024, fp8_max=0.0), params(24, 1024, layout=2)]
+for p in bad:
+    assert L.nvfp4_46_tensor_scale(P, p, P, None) != 0
+    assert L.nvfp4_46_scale_quantize(P, p, P, None, 0, P, P, None, None, None, None, None) != 0
+assert L.nvfp4_46_tensor_scale(P + 2, params(16, 1024), P, None) != 0
+assert L.nvfp4_46_tensor_scale(None, params(16, 1024), P, None) != 0
+assert L.nvfp4_46_tensor_scale(P, params(16, 1024), None, None) != 0
+assert L.nvfp4_46_wgrad_operands(P, P, 24, 64, 64, 0, 1, 2, P, P, P, P, P, P, None, 0, None) != 0
+result = calls()
+""")
+    assert made == []
+
+
+def test_the_default_stream_is_only_asked_for_words_that_are_used():
+    """Calls that run the same kernels on every stream make the same HIP calls on every stream: no lookup of scratch
+    words that nobody uses (a host-bound call pays for it)."""
+    default, other = _hip_calls.run("""
+def on(stream):
+    assert L.nvfp4_46_tensor_scale(P, params(64, 1024), P, stream) == 0                       # one workgroup
+    assert L.nvfp4_46_tensor_scale(P, params(16, 1024, x_dtype=B.X_F32), P, stream) == 0
+    assert L.nvfp4_46_scale_quantize(P, params(256, 1024), P, None, 0, P, P, None, None, P, None, stream) == 0   # one launch
+    assert L.nvfp4_46_tensor_scale_ws(P, params(4096, 4096), P, P, 4352, stream) == 0
+    assert L.nvfp4_46_scale_quantize(P, params(4096, 4096, layout=2, rht=1), P, P, 4352, None, None, P, P, None, None, stream) == 0
+    assert L.nvfp4_46_wgrad_operands(P, P, 16384, 6144, 256, 0, 1, 2, P, P, P, P, P, P, P, 4352, stream) == 0    # one after the other
+    return [c[:4] for c in calls()]
+result = on(None), on(1 << 12)
+""")
+    assert default == other and len(default) >= 6
+
+
+def test_words_of_the_default_stream_are_looked_up_once():
+    kinds = _hip_calls.run("""
+for _ in range(3):
+    assert L.nvfp4_46_tensor_scale(P, params(4096, 4096), P, None) == 0
+result = [c[0] for c in calls()]
+""")
+    assert kinds.count("symbol_address") == 1 and kinds.count("launch") == 3
