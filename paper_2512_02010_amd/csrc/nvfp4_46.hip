@@ -1358,12 +1358,13 @@ static int compute_units() {
   return cus;
 }
 
-static int grid_for(int64_t work_items, int per_cu) {
+static int grid_for(int64_t work_items, int per_cu, int cus) {
   int64_t need = (work_items + kThreads - 1) / kThreads;
-  int64_t cap = (int64_t)compute_units() * per_cu;
+  int64_t cap = (int64_t)cus * per_cu;
   if (need < 1) need = 1;
   return (int)(need < cap ? need : cap);
 }
+static int grid_for(int64_t work_items, int per_cu) { return grid_for(work_items, per_cu, compute_units()); }
 
 // every kernel of this file uses static LDS only
 template <typename Kernel, typename... Args>
@@ -1578,11 +1579,11 @@ static int launch_block2d(const Block2dArgs &a, int out) {
   // 512 x 512 8.4 / 5.5 / 4.0, 1024 x 1024 8.6 / 5.7 / 4.2, 2048 x 2048 9.1 / 6.7 / 6.0, 4096 x 2048 11.4 / 9.7 / 11.3, 4096 x 4096
   // 20.1 / 19.3 / 18.2; with its scale before it 8192 x 8192 110.0 / 111.5 / -).
   auto units_of = [&](uint32_t log) { return ((a.rows / 16 + (4 << log) - 1) / (4 << log)) * ((a.cols / 16 + 3) / 4); };
-  const int64_t cus = compute_units();
-  const uint32_t steps_log = units_of(0) <= 4 * cus ? 0u : units_of(1) <= 8 * cus ? 1u : 2u;
+  const int cus = compute_units();
+  const uint32_t steps_log = units_of(0) <= (int64_t)4 * cus ? 0u : units_of(1) <= (int64_t)8 * cus ? 1u : 2u;
   const int64_t units = units_of(steps_log);
   const int64_t ids = out == kOutCodes && a.codes_col ? ((units + 31) / 32) * 32 : (tiles + 15) / 16;
-  const int grid = grid_for(ids * kThreads, 16);
+  const int grid = grid_for(ids * kThreads, 16, cus);
   auto go = [&](auto kernel) {
     return launch(kernel, dim3(grid), dim3(kThreads), a.stream, a.x, a.alpha, a.codes, a.scales,
                   a.choice, a.codes_col, a.scales_col, a.choice_col, a.out, a.rows, a.cols,
@@ -1909,8 +1910,9 @@ int nvfp4_46_wgrad_operands(const void *dy, const void *x, int64_t rows, int64_t
   const AmaxPair both{{static_cast<const uint32_t *>(dy), static_cast<const uint32_t *>(x)},
                       {n / per_piece, k / per_piece},
                       {alpha_dy, alpha_x}};
-  const uint32_t blocks_a = (uint32_t)grid_for(row_blocks * both.pieces_per_row[0], kAmaxRhtColWgPerCu / 2);
-  const uint32_t blocks_b = (uint32_t)grid_for(row_blocks * both.pieces_per_row[1], kAmaxRhtColWgPerCu / 2);
+  const int cus = compute_units();
+  const uint32_t blocks_a = (uint32_t)grid_for(row_blocks * both.pieces_per_row[0], kAmaxRhtColWgPerCu / 2, cus);
+  const uint32_t blocks_b = (uint32_t)grid_for(row_blocks * both.pieces_per_row[1], kAmaxRhtColWgPerCu / 2, cus);
   auto maxima = [&](auto kernel) {
     return launch(kernel, dim3(blocks_a + blocks_b), dim3(kThreads), s, both, row_blocks, rht_seed, blocks_a, words, 256.0f);
   };

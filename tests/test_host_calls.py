@@ -65,3 +65,21 @@ for _ in range(3):
 result = [c[0] for c in calls()]
 """)
     assert kinds.count("symbol_address") == 1 and kinds.count("launch") == 3
+
+
+def test_compute_units_are_asked_for_once_per_launch():
+    """(an attribute of the device costs the host a tenth of a microsecond, small calls are bound by the host)"""
+    calls = _hip_calls.run("""
+q = lambda **kw: L.nvfp4_46_quantize(P, params(1024, 2048, **kw), P, *((P, P) if kw.get("layout", 1) & 1 else (None, None)),
+                                     *((P, P) if kw.get("layout", 1) & 2 else (None, None)), None, None, None)
+result = []
+for call in (lambda: q(), lambda: q(rounding=1, rht=1), lambda: q(layout=2), lambda: q(layout=3), lambda: q(block2d=1),
+             lambda: q(layout=3, block2d=1), lambda: L.nvfp4_46_fake_quant(P, params(1024, 2048, block2d=1), P, P, None),
+             lambda: L.nvfp4_46_dequantize(P, P, P, 1024, 2048, 1, P, None),
+             lambda: L.nvfp4_46_tensor_scale_ws(P, params(1024, 2048, layout=2, rht=1), P, P, 4352, None),
+             lambda: L.nvfp4_46_wgrad_operands(P, P, 256, 512, 384, 0, 1, 2, P, P, P, P, P, P, P, 4352, None)):
+    assert call() == 0
+    result.append([c[0] for c in calls()])
+""")
+    for kinds in calls:
+        assert kinds.count("device_attribute") <= 1 <= kinds.count("launch"), kinds
