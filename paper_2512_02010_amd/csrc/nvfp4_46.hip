@@ -721,7 +721,7 @@ NV_DEV void quantize_tile(
   // ---- phase 1: global -> LDS (and the rowwise outputs on the way); the loads go out
   // before the scale table is built
   if (!kDirect) {
-    constexpr int kElemsPerPiece = XF32 ? 4 : 8;
+    constexpr int kElemsPerPiece = XF32 ? 4 : 8, kPiecesPerEight = 8 / kElemsPerPiece;
     Raw w[kRowBlocksPerLane];
 #pragma unroll
     for (int j = 0; j < kRowBlocksPerLane; ++j) {
@@ -730,10 +730,15 @@ NV_DEV void quantize_tile(
       const int64_t gr = r0 + row, gc = c0 + rbk * 16;
       // (gr * cols + gc) elements into x, counted in 128-bit pieces
       const uint4 *src = static_cast<const uint4 *>(x_any) + (gr * cols + gc) / kElemsPerPiece;
+      // (cols is a multiple of 8: the pieces of eight columns are in the tensor together, or outside, and then zeros)
 #pragma unroll
-      for (int q = 0; q < Raw::kPieces; ++q) {
-        w[j].w[q] = make_uint4(0, 0, 0, 0);   // outside the tensor: zeros
-        if (gr < rows && gc + q * kElemsPerPiece < cols) w[j].w[q] = src[q];
+      for (int q = 0; q < Raw::kPieces; q += kPiecesPerEight) {
+#pragma unroll
+        for (int i = q; i < q + kPiecesPerEight; ++i) w[j].w[i] = make_uint4(0, 0, 0, 0);
+        if (gr < rows && gc + q * kElemsPerPiece < cols) {
+#pragma unroll
+          for (int i = q; i < q + kPiecesPerEight; ++i) w[j].w[i] = src[i];
+        }
       }
     }
 #pragma unroll

@@ -85,3 +85,21 @@ def test_fp32_stochastic_fake_quant_leaves_room_for_four_workgroups():
             words = select == 0 or (rht == 1 and select in (3, 4))
             assert (v["LDS"] > 160 * 1024 // 4) == words, (name, v)
             assert words or v["Occupancy"] == 3, (name, v)
+
+
+def test_loads_of_a_tile_go_out_together():
+    """k_tile's lanes load their share of the tile (two row blocks, 16 bytes at a time) before they wait for any of it: a
+    wait in between, which the compiler put there to move a register of a piece that is zero outside the
+    tensor, cost fp32 fake-quant along the columns 7 to 11 %."""
+    flags = [f for f in build.HIPCC_FLAGS if f != "-shared"]
+    part = 4                                       # fp32, round to nearest
+    asm = subprocess.run([build.hipcc(), *flags, f"-I{build.ROOT / 'include'}", f"-I{build.PKG / 'csrc'}",
+                          f"-DNVFP4_46_PART={part}", "--offload-device-only", "-S", str(build.PKG / "csrc" / "nvfp4_46.hip"),
+                          "-o", "-"], capture_output=True, text=True, check=True).stdout
+    bodies = re.findall(r"^_ZN\S+6k_tileILb1ELi0ELi\dELb\dELb(\d)ELi(\d)E\S+:(.*?)^\.Lfunc_end", asm, flags=re.M | re.S)
+    staged = [body for want_row, out, body in bodies if (want_row, out) != ("0", "0")]     # the others load no tile
+    assert len(bodies) == 5 * 5 and len(staged) == 5 * 3
+    for body in staged:
+        ops = re.findall(r"global_load_dwordx4|s_waitcnt [^\n]*vmcnt", body)
+        first = ops.index("global_load_dwordx4")
+        assert ops[first:first + 8] == ["global_load_dwordx4"] * 8, ops[:12]
