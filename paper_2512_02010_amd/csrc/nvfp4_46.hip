@@ -25,6 +25,7 @@
 #include "nvfp4_46_fused.h"
 #include "small_tensors.hpp"
 #include "tensor.hpp"
+#include "tile_shapes.hpp"
 
 // The quantizing kernels exist once per (input type, rounding mode, selection rule, ...):
 // several hundred instantiations.  To compile them side by side this file can be built in
@@ -1118,7 +1119,7 @@ __global__ __launch_bounds__(kThreads) void k_block2d(
   //    time by the workgroup;
   //  * with the packing for the transposed matrix as well, whose codes are 8 bytes per lane 4 KiB
   //    and more apart (stored like that they cost 1.9x their bytes in HBM writes and 35 us on
-  //    8192 x 8192): workgroup id -> a unit of 4, 8 or 16 tile rows (see the launcher) x 4 tile columns, taken in
+  //    8192 x 8192): workgroup id -> a unit of 4, 8 or 16 tile rows (tile_unit_log()) x 4 tile columns, taken in
   //    steps of 4 x 4 tiles (wave w: tile row 4 * step + w; its four groups: the tile columns).
   //    The unit's transposed codes (64 rows of the transposed matrix x 4 to 16 pieces of 8 bytes) are
   //    gathered in LDS and leave as runs of 32 to 128 bytes; row codes leave as 32 contiguous bytes
@@ -1577,16 +1578,12 @@ struct Block2dArgs {
 template <bool XF32, int ROUNDING, int SELECT>
 static int launch_block2d(const Block2dArgs &a, int out) {
   // ids as the kernel counts them: sixteen tiles each, or - with the transposed packing - units
-  // of 16 x 4 tiles in whole groups of 32
+  // of 4, 8 or 16 x 4 tiles in whole groups of 32
   const int64_t tiles = (a.rows / 16) * (a.cols / 16);
-  // Units are 4 tile rows high where those are at most four workgroups per compute unit, 8 where at most eight, else 16: a
-  // unit's steps follow each other, a high unit stores longer runs (fp32, us in a replayed graph, 16 / 8 / 4 tile rows:
-  // 512 x 512 8.4 / 5.5 / 4.0, 1024 x 1024 8.6 / 5.7 / 4.2, 2048 x 2048 9.1 / 6.7 / 6.0, 4096 x 2048 11.4 / 9.7 / 11.3, 4096 x 4096
-  // 20.1 / 19.3 / 18.2; with its scale before it 8192 x 8192 110.0 / 111.5 / -).
-  auto units_of = [&](uint32_t log) { return ((a.rows / 16 + (4 << log) - 1) / (4 << log)) * ((a.cols / 16 + 3) / 4); };
   const int cus = compute_units();
-  const uint32_t steps_log = units_of(0) <= (int64_t)4 * cus ? 0u : units_of(1) <= (int64_t)8 * cus ? 1u : 2u;
-  const int64_t units = units_of(steps_log);
+  const uint32_t steps_log = tile_unit_log(a.rows, a.cols, XF32, cus);
+  const int64_t unit_rows = 4 << steps_log;
+  const int64_t units = ((a.rows / 16 + unit_rows - 1) / unit_rows) * ((a.cols / 16 + 3) / 4);
   const int64_t ids = out == kOutCodes && a.codes_col ? ((units + 31) / 32) * 32 : (tiles + 15) / 16;
   const int grid = grid_for(ids * kThreads, 16, cus);
   auto go = [&](auto kernel) {

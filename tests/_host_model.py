@@ -1,8 +1,8 @@
 """The kernels' per-block code compiled for the host (tests/host_model/), behind ctypes.
 
 Test infrastructure.  ``csrc/block.hpp`` and ``csrc/codec.hpp`` -- the code every quantizing
-kernel runs per block -- and ``csrc/gemm_shapes.hpp`` and ``csrc/small_tensors.hpp`` -- the host
-side's choices of kernel -- are compiled with the host compiler, the gfx950 conversion
+kernel runs per block -- and ``csrc/gemm_shapes.hpp``, ``csrc/small_tensors.hpp`` and ``csrc/tile_shapes.hpp`` -- the
+host side's choices of kernel -- are compiled with the host compiler, the gfx950 conversion
 instructions replaced by plain definitions of what they compute, so that CPU tests can put
 the GPU path's block logic next to the oracle on inputs of any range without a GPU.
 """
@@ -21,7 +21,7 @@ _ROOT = _HERE.parent.parent
 _CSRC = _ROOT / "paper_2512_02010_amd" / "csrc"
 _SO = _HERE / "_build" / "libhost_model.so"
 _SOURCES = [_HERE / "model.cpp", _HERE / "gfx950_on_host.hpp", _CSRC / "block.hpp", _CSRC / "codec.hpp",
-            _CSRC / "gemm_shapes.hpp", _CSRC / "small_tensors.hpp"]
+            _CSRC / "gemm_shapes.hpp", _CSRC / "small_tensors.hpp", _CSRC / "tile_shapes.hpp"]
 
 RTN, SR, SR_AFTER_RTN_SELECT = 0, 1, 2
 
@@ -87,6 +87,8 @@ def lib() -> C.CDLL:
         L.hm_scale_in_one_workgroup.argtypes = [C.c_int64, C.c_int]
         L.hm_scale_and_codes_in_one_launch.restype = C.c_int
         L.hm_scale_and_codes_in_one_launch.argtypes = [C.c_int64, C.c_int]
+        L.hm_tile_unit_log.restype = C.c_int
+        L.hm_tile_unit_log.argtypes = [C.c_int64, C.c_int64, C.c_int, C.c_int64]
         L.hm_tile_shape.restype = None
         L.hm_tile_shape.argtypes = [C.c_int, C.POINTER(C.c_int32)]
         _lib = L
@@ -200,3 +202,8 @@ def scale_in_one_workgroup(nbytes: int, has_scratch: bool) -> bool:
 
 def scale_and_codes_in_one_launch(nbytes: int, has_scratch: bool) -> bool:
     return bool(lib().hm_scale_and_codes_in_one_launch(nbytes, has_scratch))
+
+
+def tile_unit_rows(rows: int, cols: int, xf32: bool, compute_units: int = 256) -> int:
+    """Tile rows of the units in which a tensor gets both packings of its 16x16 tiles."""
+    return 4 << lib().hm_tile_unit_log(rows, cols, xf32, compute_units)

@@ -6,6 +6,7 @@
 #include "block.hpp"
 #include "gemm_shapes.hpp"
 #include "small_tensors.hpp"
+#include "tile_shapes.hpp"
 
 using namespace nvfp4_46;
 
@@ -189,6 +190,11 @@ int hm_scale_in_one_workgroup(int64_t bytes, int has_scratch) {
 }
 int hm_scale_and_codes_in_one_launch(int64_t bytes, int has_scratch) {
   return scale_and_codes_in_one_launch(bytes, has_scratch != 0);
+}
+
+// the height of the tiled quantizer's units, as the logarithm of a quarter of their tile rows
+int hm_tile_unit_log(int64_t rows, int64_t cols, int xf32, int64_t compute_units) {
+  return (int)tile_unit_log(rows, cols, xf32 != 0, compute_units);
 }
 
 // lanes that such a launch of `kernel` has
