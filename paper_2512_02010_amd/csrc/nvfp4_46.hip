@@ -587,8 +587,6 @@ __global__ __launch_bounds__(kThreads) void k_dequant_flat(const uint32_t *__res
 
 // ------------------------------------------------ columnwise / both (tiled)
 
-constexpr int TR = 64;    // tile rows    (multiple of 16)
-constexpr int TC = 128;   // tile columns (multiple of 16)
 constexpr int kRowBlocksPerTileRow = TC / 16;          // 16-element row blocks across a tile row
 constexpr int kRowBlocksPerTile = TR * TC / 16;
 constexpr int kRowBlocksPerLane = kRowBlocksPerTile / kThreads;
@@ -607,21 +605,6 @@ static_assert(kRowBlocksPerTile % kThreads == 0 && kPairUnits % kThreads == 0 &&
 struct TileCoord {
   int64_t r0, c0;
   bool valid;
-};
-
-// Workgroups are handed to the 8 XCDs round-robin by their index, and each XCD has its own
-// L2.  A tile writes only part of every output cache line it touches: 64 of the 128 bytes of
-// a row's codes, 32 bytes of a column's, 8 and 4 bytes of the scale lines.  The tiles that
-// complete those lines -- horizontal neighbours for the rowwise arrays, vertical neighbours
-// for the columnwise ones -- should therefore meet in one L2 while the lines are still
-// there.  So the tiles are grouped into super-tiles of sx x sy tiles (8 x 16 when the tensor
-// is that large: 1024 x 1024 elements), super-tile S goes to XCD S % 8, and the consecutive
-// workgroups of one XCD walk through one super-tile row by row.  (One XCD per tile column,
-// top to bottom, merged only the columnwise lines: 66.6 -> 58.6 us for both orientations of
-// 8192 x 8192.)
-struct TileMap {
-  uint32_t sx, sy;      // super-tile width and height in tiles
-  uint32_t last;        // the grid's last workgroup where tiles go last to first (kLastLevelBytes), or 0
 };
 
 NV_DEV TileCoord tile_of_workgroup(int64_t rows, int64_t cols, TileMap m, uint32_t block) {
@@ -1473,42 +1456,6 @@ struct TileArgs {
   uint64_t sr_seed, rht_seed;
   hipStream_t stream;
 };
-
-// Super-tiles of 8 x 16 tiles (no larger than the tensor) where that gives every die about its share, or no die more
-// tiles than its 32 compute units, else the largest smaller ones that do: a tensor of few tiles would otherwise be one
-// super-tile, all on one die (us in a replayed graph, 8 x 16 / this: columnwise Hadamard + SR 736 x 1024 11.0 / 8.3, 1008 x
-// 4096 13.2 / 9.6, 1344 x 2208 13.1 / 9.4; both orientations 336 x 1184 6.7 / 5.9, 736 x 1024 8.9 / 5.9, 1008 x 4096 11.2 / 7.9,
-// 5248 x 6192 38.5 / 34.4; one tile per compute unit of one die or spread over all: 848 x 208 5.8 / 6.0).
-static TileMap tile_map(int64_t rows, int64_t cols) {
-  const int64_t nt_r = (rows + TR - 1) / TR, nt_c = (cols + TC - 1) / TC;
-  TileMap best{1u, 1u, 0u};
-  int64_t best_most = INT64_MAX;
-  for (uint32_t area = 128; area > 0; area /= 2) {     // 8 x 16, 8 x 8, 4 x 8, 4 x 4, ... 1 x 2, 1 x 1
-    const uint32_t wide = area >= 64 ? 8 : area >= 16 ? 4 : area >= 4 ? 2 : 1, high = area / wide;
-    const uint32_t sx = nt_c < wide ? (uint32_t)nt_c : wide, sy = nt_r < high ? (uint32_t)nt_r : high;
-    const int64_t across = (nt_c + sx - 1) / sx, supers = across * ((nt_r + sy - 1) / sy);
-    if (supers > 64) return TileMap{sx, sy, 0u};       // more than eight turns even out
-    int64_t tiles[8] = {}, most = 0;                   // of each die
-    for (int64_t S = 0; S < supers; ++S) {
-      const int64_t right = nt_c - S % across * sx, down = nt_r - S / across * sy;
-      tiles[S & 7] += (right < sx ? right : sx) * (down < sy ? down : sy);
-    }
-    for (int64_t t : tiles) most = t > most ? t : most;
-    if (most < best_most) {
-      best = TileMap{sx, sy, 0u};
-      best_most = most;
-    }
-    if (most <= 32 || most * 32 <= nt_r * nt_c * 5) break;      // within a quarter of an eighth
-  }
-  return best;
-}
-
-// Whole turns over the eight XCDs, each turn one super-tile per XCD.
-static int tile_grid(int64_t rows, int64_t cols, TileMap m) {
-  const int64_t nt_r = (rows + TR - 1) / TR, nt_c = (cols + TC - 1) / TC;
-  const int64_t supers = ((nt_c + m.sx - 1) / m.sx) * ((nt_r + m.sy - 1) / m.sy);
-  return (int)(8 * ((supers + 7) / 8) * m.sx * m.sy);
-}
 
 template <bool XF32, int ROUNDING, int SELECT, bool RHT, bool WANT_ROW, int OUT>
 static int launch_tile(const TileArgs &a) {

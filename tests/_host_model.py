@@ -87,6 +87,8 @@ def lib() -> C.CDLL:
         L.hm_scale_in_one_workgroup.argtypes = [C.c_int64, C.c_int]
         L.hm_scale_and_codes_in_one_launch.restype = C.c_int
         L.hm_scale_and_codes_in_one_launch.argtypes = [C.c_int64, C.c_int]
+        L.hm_tile_map.restype = None
+        L.hm_tile_map.argtypes = [C.c_int64, C.c_int64, C.POINTER(C.c_int64)]
         L.hm_tile_unit_log.restype = C.c_int
         L.hm_tile_unit_log.argtypes = [C.c_int64, C.c_int64, C.c_int, C.c_int64]
         L.hm_tile_shape.restype = None
@@ -202,6 +204,13 @@ def scale_in_one_workgroup(nbytes: int, has_scratch: bool) -> bool:
 
 def scale_and_codes_in_one_launch(nbytes: int, has_scratch: bool) -> bool:
     return bool(lib().hm_scale_and_codes_in_one_launch(nbytes, has_scratch))
+
+
+def tile_map(rows: int, cols: int):
+    """(super-tile width, height, workgroups) of the tiled kernels' launch."""
+    v = (C.c_int64 * 3)()
+    lib().hm_tile_map(rows, cols, v)
+    return tuple(v)
 
 
 def tile_unit_rows(rows: int, cols: int, xf32: bool, compute_units: int = 256) -> int:

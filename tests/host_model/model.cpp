@@ -192,6 +192,14 @@ int hm_scale_and_codes_in_one_launch(int64_t bytes, int has_scratch) {
   return scale_and_codes_in_one_launch(bytes, has_scratch != 0);
 }
 
+// super-tile width and height in tiles, and the workgroups of the launch, of k_tile
+void hm_tile_map(int64_t rows, int64_t cols, int64_t *to) {
+  const TileMap m = tile_map(rows, cols);
+  to[0] = m.sx;
+  to[1] = m.sy;
+  to[2] = tile_grid(rows, cols, m);
+}
+
 // the height of the tiled quantizer's units, as the logarithm of a quarter of their tile rows
 int hm_tile_unit_log(int64_t rows, int64_t cols, int xf32, int64_t compute_units) {
   return (int)tile_unit_log(rows, cols, xf32 != 0, compute_units);

@@ -1,5 +1,7 @@
 """CPU: how tensors are dealt out to the workgroups of the tiled quantizers (csrc/tile_shapes.hpp, compiled for the
 host)."""
+import random
+
 import pytest
 
 from . import _host_model as hm
@@ -22,3 +24,57 @@ def test_height_of_units_follows_the_compute_units():
     for rows, cols in ((2048, 1024), (2048, 2048), (4096, 1024), (1152, 4096), (4096, 2064), (8192, 8192)):
         for xf32 in (False, True):
             assert hm.tile_unit_rows(rows, cols, xf32, 128) == hm.tile_unit_rows(2 * rows, cols, xf32, 256), (rows, cols)
+
+
+def _map(rows, cols):
+    """tile_map() as its comment has it: die S % 8 takes super-tile S, counted in rows of super-tiles."""
+    nt_r, nt_c = -(-rows // 64), -(-cols // 128)
+    best, best_most = None, None
+    for wide, high in ((8, 16), (8, 8), (4, 8), (4, 4), (2, 4), (2, 2), (1, 2), (1, 1)):
+        sx, sy = min(nt_c, wide), min(nt_r, high)
+        across = -(-nt_c // sx)
+        supers = across * -(-nt_r // sy)
+        if supers > 64:
+            return sx, sy
+        tiles = [0] * 8
+        for S in range(supers):
+            tiles[S % 8] += min(nt_c - S % across * sx, sx) * min(nt_r - S // across * sy, sy)
+        if best is None or max(tiles) < best_most:
+            best, best_most = (sx, sy), max(tiles)
+        if max(tiles) <= 32 or max(tiles) * 32 <= nt_r * nt_c * 5:
+            break
+    return best
+
+
+def _sizes():
+    rng = random.Random(46)
+    yield from ((1, 8), (64, 128), (65, 129), (16, 1 << 20), (1 << 20, 8), (736, 1024), (1008, 4096), (5248, 6192), (8192, 8192),
+                (1 << 31, 512), (512, 1 << 31))
+    for _ in range(3000):
+        yield int(2 ** rng.uniform(0, 15)), int(2 ** rng.uniform(3, 15)) // 8 * 8
+
+
+def test_map_of_tiles():
+    for rows, cols in _sizes():
+        sx, sy, _ = hm.tile_map(rows, cols)
+        assert (sx, sy) == _map(rows, cols), (rows, cols)
+
+
+def test_every_tile_has_one_workgroup():
+    """The kernel's way from a workgroup to its tile, over the whole launch."""
+    for rows, cols in _sizes():
+        nt_r, nt_c = -(-rows // 64), -(-cols // 128)
+        if nt_r * nt_c > 2000:
+            continue
+        sx, sy, grid = hm.tile_map(rows, cols)
+        nsx = -(-nt_c // sx)
+        seen = set()
+        for block in range(grid):
+            slot, xcd = divmod(block, 8)
+            round_, within = divmod(slot, sx * sy)
+            S = round_ * 8 + xcd
+            r, c = S // nsx * sy + within // sx, S % nsx * sx + within % sx
+            if r < nt_r and c < nt_c:
+                assert (r, c) not in seen, (rows, cols, block)
+                seen.add((r, c))
+        assert len(seen) == nt_r * nt_c, (rows, cols)
