@@ -1716,16 +1716,13 @@ static int tensor_scale(const void *x, const nvfp4_46_params *p, float *alpha, u
     rc = xf32 ? launch_flat<true, kRTN, kSel46, true, kOutAmax>(a)
               : launch_flat<false, kRTN, kSel46, true, kOutAmax>(a);
   } else {
-    // columnwise blocks (rows % 16 == 0, cols % 8 == 0): 16 bytes of a row per lane, or 4 where those are still
-    // no more than two waves per SIMD (a lane's columns follow each other: us in a replayed graph, 16 / 4 bytes, BF16 256 x
-    // 512 5.5 / 4.65, 736 x 1024 5.75 / 4.65, 1344 x 2208 5.8 / 5.2, 1008 x 4096 5.85 / 5.5, 2048 x 4096 6.25 / 6.8, 4096 x 4096
-    // 7.5 / 9.0; fp32 736 x 1024 5.0 / 4.5, 4096 x 4096 14.8 / 16.4; 8 bytes lie between)
+    // columnwise blocks (rows % 16 == 0, cols % 8 == 0): 16 or 4 bytes of a row per lane
     const int64_t row_blocks = p->rows / 16, words = p->cols / (xf32 ? 1 : 2);
     auto go = [&](auto kernel, int64_t pieces) {
       return launch(kernel, dim3(grid_for(row_blocks * pieces, kAmaxRhtColWgPerCu)), dim3(kThreads), s,
                     static_cast<const uint32_t *>(x), row_blocks, pieces, p->rht_seed, amax, fin);
     };
-    if (row_blocks * words <= (int64_t)1 << 17)
+    if (scale_by_words(row_blocks * words, xf32))
       rc = xf32 ? go(k_amax_rht_col<true, 1>, words) : go(k_amax_rht_col<false, 1>, words);
     else
       rc = xf32 ? go(k_amax_rht_col<true, 4>, words / 4) : go(k_amax_rht_col<false, 4>, words / 4);
@@ -1854,7 +1851,7 @@ int nvfp4_46_wgrad_operands(const void *dy, const void *x, int64_t rows, int64_t
   const TileMap map[2] = {tile_map(rows, n), tile_map(rows, k)};
   const uint32_t tiles[2] = {(uint32_t)tile_grid(rows, n, map[0]), (uint32_t)tile_grid(rows, k, map[1])};
   const int64_t row_blocks = rows / 16;
-  const bool narrow = row_blocks * (n + k) / 2 <= (int64_t)1 << 17;      // as in tensor_scale, of both together
+  const bool narrow = scale_by_words(row_blocks * (n + k) / 2, false);     // of both together
   const int64_t per_piece = narrow ? 2 : 8;
   const AmaxPair both{{static_cast<const uint32_t *>(dy), static_cast<const uint32_t *>(x)},
                       {n / per_piece, k / per_piece},

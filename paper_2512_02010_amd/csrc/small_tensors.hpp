@@ -47,4 +47,14 @@ constexpr bool scale_and_codes_in_one_launch(int64_t bytes, bool has_scratch) {
   return bytes <= (int64_t)(has_scratch ? 384 : 768) << 10;
 }
 
+// Tensor scale after the columnwise transform (k_amax_rht_col): whether a lane takes 4 bytes of each of a block's sixteen rows
+// instead of 16, for so many words of 4 bytes in a sixteenth of the rows.  A lane's columns follow each other, so 4 where
+// those are still no more than two waves per SIMD, in fp32 a little less (us in a replayed graph, 16 / 4 bytes, BF16 256 x
+// 512 5.5 / 4.65, 736 x 1024 5.75 / 4.65, 1344 x 2208 5.8 / 5.2, 1008 x 4096 5.85 / 5.5, 2048 x 2048 6.2 / 5.9, 2048 x 4096 6.25 /
+// 6.8, 4096 x 4096 7.5 / 9.0; fp32 736 x 1024 5.0 / 4.5, 480 x 4096 and 1920 x 1024 5.15 / 5.0, 1024 x 2048 and 256 x 8192
+// 5.1 / 5.3, 4096 x 4096 14.8 / 16.4; 8 bytes lie between).
+constexpr bool scale_by_words(int64_t words, bool xf32) {
+  return words <= (int64_t)(xf32 ? 15 : 16) << 13;
+}
+
 }  // namespace nvfp4_46

@@ -87,6 +87,8 @@ def lib() -> C.CDLL:
         L.hm_scale_in_one_workgroup.argtypes = [C.c_int64, C.c_int]
         L.hm_scale_and_codes_in_one_launch.restype = C.c_int
         L.hm_scale_and_codes_in_one_launch.argtypes = [C.c_int64, C.c_int]
+        L.hm_scale_by_words.restype = C.c_int
+        L.hm_scale_by_words.argtypes = [C.c_int64, C.c_int]
         L.hm_tile_map.restype = None
         L.hm_tile_map.argtypes = [C.c_int64, C.c_int64, C.POINTER(C.c_int64)]
         L.hm_tile_unit_log.restype = C.c_int
@@ -204,6 +206,10 @@ def scale_in_one_workgroup(nbytes: int, has_scratch: bool) -> bool:
 
 def scale_and_codes_in_one_launch(nbytes: int, has_scratch: bool) -> bool:
     return bool(lib().hm_scale_and_codes_in_one_launch(nbytes, has_scratch))
+
+
+def scale_by_words(words: int, xf32: bool) -> bool:
+    return bool(lib().hm_scale_by_words(words, xf32))
 
 
 def tile_map(rows: int, cols: int):

@@ -192,6 +192,8 @@ int hm_scale_and_codes_in_one_launch(int64_t bytes, int has_scratch) {
   return scale_and_codes_in_one_launch(bytes, has_scratch != 0);
 }
 
+int hm_scale_by_words(int64_t words, int xf32) { return scale_by_words(words, xf32 != 0); }
+
 // super-tile width and height in tiles, and the workgroups of the launch, of k_tile
 void hm_tile_map(int64_t rows, int64_t cols, int64_t *to) {
   const TileMap m = tile_map(rows, cols);
