@@ -1079,12 +1079,13 @@ NV_DEV void transpose_codes16(uint32_t &lo, uint32_t &hi) {
   stage(hi, 1u, 0x0f0f0f0fu, 4);
 }
 
-template <bool XF32, int ROUNDING, int SELECT, int OUT, bool BY_UNITS>
+// UNIT_ROWS: tile rows of a unit (4, 8 or 16; as a number of the launch they cost 1 to 2 %), or 0 for one packing.
+template <bool XF32, int ROUNDING, int SELECT, int OUT, int UNIT_ROWS>
 __global__ __launch_bounds__(kThreads) void k_block2d(
     const void *__restrict__ x_any, const float *__restrict__ alpha_p, uint8_t *__restrict__ codes,
     uint8_t *__restrict__ scales, uint8_t *__restrict__ choice, uint8_t *__restrict__ codes_col,
     uint8_t *__restrict__ scales_col, uint8_t *__restrict__ choice_col,
-    uint16_t *__restrict__ out_bf16, int64_t rows, int64_t cols, uint64_t sr_seed, uint32_t steps_log, uint32_t backwards) {
+    uint16_t *__restrict__ out_bf16, int64_t rows, int64_t cols, uint64_t sr_seed, uint32_t backwards) {
   __shared__ ScaleTable tab;
   const ScaleConsts sc = build_scale_table(tab, *alpha_p);
   const uint32_t tid = threadIdx.x, r_in_tile = tid & 15u, grp = tid >> 4;
@@ -1102,20 +1103,21 @@ __global__ __launch_bounds__(kThreads) void k_block2d(
   //    time by the workgroup;
   //  * with the packing for the transposed matrix as well, whose codes are 8 bytes per lane 4 KiB
   //    and more apart (stored like that they cost 1.9x their bytes in HBM writes and 35 us on
-  //    8192 x 8192): workgroup id -> a unit of 4, 8 or 16 tile rows (tile_unit_log()) x 4 tile columns, taken in
+  //    8192 x 8192): workgroup id -> a unit of 4, 8 or 16 tile rows (tile_unit_rows()) x 4 tile columns, taken in
   //    steps of 4 x 4 tiles (wave w: tile row 4 * step + w; its four groups: the tile columns).
   //    The unit's transposed codes (64 rows of the transposed matrix x 4 to 16 pieces of 8 bytes) are
   //    gathered in LDS and leave as runs of 32 to 128 bytes; row codes leave as 32 contiguous bytes
   //    per store instruction, and id -> unit keeps the four units that share the 128-byte
   //    lines of row codes on one die's L2 (ids 8 apart).
-  constexpr bool by_units = BY_UNITS;
-  static_assert(!BY_UNITS || OUT == kOutCodes, "units are for the transposed packing");
-  __shared__ uint2 col_stage[BY_UNITS ? 64 * kColStagePitch : 1];
+  constexpr bool by_units = UNIT_ROWS > 0;
+  static_assert(!by_units || OUT == kOutCodes, "units are for the transposed packing");
+  __shared__ uint2 col_stage[by_units ? 64 * kColStagePitch : 1];
   const uint32_t wave = tid >> 6, g4 = grp & 3u;
-  const uint32_t ncq = (ncb + 3u) / 4u, unit_rows = 4u << steps_log;
+  const uint32_t ncq = (ncb + 3u) / 4u;
+  constexpr uint32_t unit_rows = by_units ? UNIT_ROWS : 4;
   const uint32_t n_units = ((nrb + unit_rows - 1u) / unit_rows) * ncq;
   const uint32_t n_ids = by_units ? ((n_units + 31u) / 32u) * 32u : (uint32_t)((n_tiles + 15u) / 16u);
-  const uint32_t n_steps = by_units ? 1u << steps_log : 1u;
+  constexpr uint32_t n_steps = unit_rows / 4u;
   auto tile_body = [&](uint32_t tr, uint32_t tc, uint32_t trl) {
     const uint64_t row = (uint64_t)tr * 16 + r_in_tile;
     const uint64_t first = row * (uint64_t)cols + tc * 16u;  // flat index of the lane's first element
@@ -1197,7 +1199,7 @@ __global__ __launch_bounds__(kThreads) void k_block2d(
           if (choice) choice[T] = (uint8_t)res.four;
         }
       }
-      if (BY_UNITS) {
+      if (by_units) {
         // the same tile for the transposed matrix: column (tc*16 + lane) of x is its row
         uint32_t lo = res.lo, hi = res.hi;
         transpose_codes16(lo, hi);
@@ -1246,7 +1248,7 @@ __global__ __launch_bounds__(kThreads) void k_block2d(
         if (unit < n_units) {
 #pragma unroll 1
           for (uint32_t j = 0; j < n_steps; ++j) {
-            const uint32_t piece = tid + j * kThreads, line = piece >> (2u + steps_log), k = piece & (unit_rows - 1u);
+            const uint32_t piece = tid + j * kThreads, line = piece / unit_rows, k = piece % unit_rows;
             const uint64_t col = ((uint64_t)cq * 4 + (line >> 4)) * 16 + (line & 15u);
             const uint32_t tr_k = mr * unit_rows + k;
             if (col < (uint64_t)cols && tr_k < nrb)
@@ -1528,19 +1530,21 @@ static int launch_block2d(const Block2dArgs &a, int out) {
   // of 4, 8 or 16 x 4 tiles in whole groups of 32
   const int64_t tiles = (a.rows / 16) * (a.cols / 16);
   const int cus = compute_units();
-  const uint32_t steps_log = tile_unit_log(a.rows, a.cols, XF32, cus);
-  const int64_t unit_rows = 4 << steps_log;
+  const int64_t unit_rows = tile_unit_rows(a.rows, a.cols, XF32, cus);
   const int64_t units = ((a.rows / 16 + unit_rows - 1) / unit_rows) * ((a.cols / 16 + 3) / 4);
   const int64_t ids = out == kOutCodes && a.codes_col ? ((units + 31) / 32) * 32 : (tiles + 15) / 16;
   const int grid = grid_for(ids * kThreads, 16, cus);
   auto go = [&](auto kernel) {
     return launch(kernel, dim3(grid), dim3(kThreads), a.stream, a.x, a.alpha, a.codes, a.scales,
                   a.choice, a.codes_col, a.scales_col, a.choice_col, a.out, a.rows, a.cols,
-                  a.sr_seed, steps_log, runs_backwards(a.rows * a.cols, XF32));
+                  a.sr_seed, runs_backwards(a.rows * a.cols, XF32));
   };
-  if (out == kOutCodes && a.codes_col) return go(k_block2d<XF32, ROUNDING, SELECT, kOutCodes, true>);
-  if (out == kOutCodes) return go(k_block2d<XF32, ROUNDING, SELECT, kOutCodes, false>);
-  return go(k_block2d<XF32, ROUNDING, SELECT, kOutFake, false>);
+  if (out == kOutCodes && a.codes_col)
+    return unit_rows == 4   ? go(k_block2d<XF32, ROUNDING, SELECT, kOutCodes, 4>)
+           : unit_rows == 8 ? go(k_block2d<XF32, ROUNDING, SELECT, kOutCodes, 8>)
+                            : go(k_block2d<XF32, ROUNDING, SELECT, kOutCodes, 16>);
+  if (out == kOutCodes) return go(k_block2d<XF32, ROUNDING, SELECT, kOutCodes, 0>);
+  return go(k_block2d<XF32, ROUNDING, SELECT, kOutFake, 0>);
 }
 
 // All 16x16-tile kernels of one (input type, rounding mode) pair.

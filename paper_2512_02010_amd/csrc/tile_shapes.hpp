@@ -61,8 +61,7 @@ inline int tile_grid(int64_t rows, int64_t cols, TileMap m) {
   return (int)(8 * ((supers + 7) / 8) * m.sx * m.sy);
 }
 
-// Both packings of 16x16 tiles (k_block2d) are made in units of 4, 8 or 16 tile rows x 4 tile columns: the logarithm of a
-// quarter of the rows.  A unit's steps of 4 x 4 tiles follow each other in its workgroup, a high unit stores longer runs.
+// Both packings of 16x16 tiles (k_block2d) are made in units of 4, 8 or 16 tile rows x 4 tile columns.  A unit's steps of 4 x 4 tiles follow each other in its workgroup, a high unit stores longer runs.
 // High units pay where they fill the chip: what counts is how many of them there are for the four workgroups of a compute
 // unit that run at once, a turn.  Tensor scale and codes, us in a replayed graph, 16 / 8 / 4 tile rows:
 //                       fp32                    BF16
@@ -80,12 +79,12 @@ inline int tile_grid(int64_t rows, int64_t cols, TileMap m) {
 //   8192 x 8192      108.1 / 108.8 / 112.5   66.6 / 67.6 / 69.1     4096
 // In fp32 the last quarter of a turn is level on average and with units of 8 sometimes far ahead (8192 x 2048 34.3 / 31.3,
 // 6144 x 2064 28.5 / 26.1, but 2048 x 7792 30.2 / 31.6).
-constexpr uint32_t tile_unit_log(int64_t rows, int64_t cols, bool xf32, int64_t compute_units) {
+constexpr int tile_unit_rows(int64_t rows, int64_t cols, bool xf32, int64_t compute_units) {
   const int64_t across = (cols / 16 + 3) / 4, turn = 4 * compute_units;
   const int64_t of_4 = (rows / 16 + 3) / 4 * across, of_8 = (rows / 16 + 7) / 8 * across, of_16 = (rows / 16 + 15) / 16 * across;
-  if (of_4 <= turn) return 0;
-  if (of_8 <= turn) return 1;
-  return of_16 * 4 > (xf32 ? 3 : 4) * turn && of_16 * 8 <= 11 * turn ? 1 : 2;
+  if (of_4 <= turn) return 4;
+  if (of_8 <= turn) return 8;
+  return of_16 * 4 > (xf32 ? 3 : 4) * turn && of_16 * 8 <= 11 * turn ? 8 : 16;
 }
 
 }  // namespace nvfp4_46

@@ -91,8 +91,8 @@ def lib() -> C.CDLL:
         L.hm_scale_by_words.argtypes = [C.c_int64, C.c_int]
         L.hm_tile_map.restype = None
         L.hm_tile_map.argtypes = [C.c_int64, C.c_int64, C.POINTER(C.c_int64)]
-        L.hm_tile_unit_log.restype = C.c_int
-        L.hm_tile_unit_log.argtypes = [C.c_int64, C.c_int64, C.c_int, C.c_int64]
+        L.hm_tile_unit_rows.restype = C.c_int
+        L.hm_tile_unit_rows.argtypes = [C.c_int64, C.c_int64, C.c_int, C.c_int64]
         L.hm_tile_shape.restype = None
         L.hm_tile_shape.argtypes = [C.c_int, C.POINTER(C.c_int32)]
         _lib = L
@@ -221,4 +221,4 @@ def tile_map(rows: int, cols: int):
 
 def tile_unit_rows(rows: int, cols: int, xf32: bool, compute_units: int = 256) -> int:
     """Tile rows of the units in which a tensor gets both packings of its 16x16 tiles."""
-    return 4 << lib().hm_tile_unit_log(rows, cols, xf32, compute_units)
+    return lib().hm_tile_unit_rows(rows, cols, xf32, compute_units)

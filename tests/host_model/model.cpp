@@ -202,9 +202,9 @@ void hm_tile_map(int64_t rows, int64_t cols, int64_t *to) {
   to[2] = tile_grid(rows, cols, m);
 }
 
-// the height of the tiled quantizer's units, as the logarithm of a quarter of their tile rows
-int hm_tile_unit_log(int64_t rows, int64_t cols, int xf32, int64_t compute_units) {
-  return (int)tile_unit_log(rows, cols, xf32 != 0, compute_units);
+// the height of the tiled quantizer's units in tile rows
+int hm_tile_unit_rows(int64_t rows, int64_t cols, int xf32, int64_t compute_units) {
+  return tile_unit_rows(rows, cols, xf32 != 0, compute_units);
 }
 
 // lanes that such a launch of `kernel` has
