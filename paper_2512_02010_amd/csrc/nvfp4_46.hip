@@ -1675,7 +1675,7 @@ static uint32_t *scratch_of_device() {
 // the order of its calls and is never captured into a graph, so one set serves all of it; any other
 // stream gets nullptr, the form of three launches (us per call from Python among others, three / one: BF16 1 MiB
 // 10.0 / 4.8, 8 MiB 9.6 / 4.8, 32 MiB 10.8 / 5.3, 128 MiB 23.6 / 22.0, with the columnwise transform 9.9 / 5.9,
-// 9.8 / 6.0, 12.1 / 7.3 and 26.9 / 23.6; 512 KiB, one workgroup before, 5.4 / 4.7).
+// 9.8 / 6.0, 12.1 / 7.3 and 26.9 / 23.6).
 static uint32_t *lent_words(hipStream_t stream) {
   if (stream) return nullptr;
   uint32_t *const words = scratch_of_device();
@@ -1695,8 +1695,8 @@ static int tensor_scale(const void *x, const nvfp4_46_params *p, float *alpha, u
   const bool xf32 = p->x_dtype == NVFP4_X_F32;
   const uint4 *x4 = static_cast<const uint4 *>(x);
   const int64_t bytes = n * (xf32 ? 4 : 2);
-  // (a call on the default stream counts as one with scratch words)
-  if (!p->rht && scale_in_one_workgroup(bytes, workspace != nullptr || s == nullptr)) {
+  const ScratchWords words = workspace ? ScratchWords::kWorkspace : s ? ScratchWords::kNone : ScratchWords::kLent;
+  if (!p->rht && scale_in_one_workgroup(bytes, words)) {
     const uint32_t n16 = (uint32_t)(bytes / 16);       // n is a multiple of 8 by the shape checks
     return xf32 ? launch(k_scale_small<true>, dim3(1), dim3(kSmallThreads), s, x4, n16, alpha, p->fp8_max)
                 : launch(k_scale_small<false>, dim3(1), dim3(kSmallThreads), s, x4, n16, alpha, p->fp8_max);

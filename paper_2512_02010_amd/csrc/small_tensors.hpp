@@ -18,14 +18,23 @@ namespace nvfp4_46 {
 //   512     6.6/6.1   3.9/3.8       6.8/6.6       11.1/10.6   4.4/4.3       7.2/7.1
 //   768     8.9/8.2   4.0/3.9       7.3/7.2       15.5/14.9   4.5/4.4       7.9/7.8
 //   1024    11.2/10.4 4.1/3.9       7.9/7.9       19.9/19.2   4.5/4.4       8.6/8.5
-// With scratch words (a workspace, or the library's own on the default stream) it replaces one launch by one: as
-// far as it is ahead in the cache and not behind in memory.
+// With a workspace it replaces one launch by one: as far as it is ahead in the cache and not behind in memory.
 // Without, it replaces three, which the host pays for: as far as it is not behind when called one by one with x
 // in the cache (us per call among others from Python, BF16: 512 KiB 6.5 / 11.1, 768 KiB 8.9 / 8.7 to 11.4, 896 KiB
 // 9.9 / 8.8 to 12, 1 MiB 11.2 / 11.2; first read from memory 10.7 / 9.5, 15.2 / 8.5, 17.3 / 10.1 and 19.8 / 9.9;
-// programs that replay graphs have scratch words).
-constexpr bool scale_in_one_workgroup(int64_t bytes, bool has_scratch) {
-  return bytes <= (int64_t)(has_scratch ? 128 : 768) << 10;
+// programs that replay graphs have a workspace).
+// On the default stream, without a workspace, it replaces one launch on lent words, which costs the host 0.4 us more (the
+// device is asked for, and its compute units).  Such calls come one by one and have others after them that the host is busy
+// with while the one workgroup reads, so what counts is the whole pass (us among others from Python, BF16, one workgroup /
+// lent words; fp32 is within 0.3 of it):
+//   KiB     scale, codes, values    scale, fake-quant   scale, both orientations   scale alone
+//   256     15.7 / 16.1             8.9 / 9.5           12.1 / 12.5                4.3 / 4.7
+//   512     15.7 / 16.0             9.3 / 9.6           12.2 / 12.6                5.3 / 4.7
+//   640     15.5 / 15.9             9.9 / 9.4           12.1 / 12.5                6.2 / 4.7
+//   768     15.6 / 16.0             10.8 / 9.4          13.3 / 12.6                7.1 / 4.7
+enum class ScratchWords { kNone, kLent, kWorkspace };
+constexpr bool scale_in_one_workgroup(int64_t bytes, ScratchWords words) {
+  return bytes <= (int64_t)(words == ScratchWords::kWorkspace ? 128 : words == ScratchWords::kLent ? 512 : 768) << 10;
 }
 
 // Scale and rowwise codes in one launch (k_scale_quantize_small), against codes in a launch of their

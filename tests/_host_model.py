@@ -85,6 +85,8 @@ def lib() -> C.CDLL:
         L.hm_gemm_lanes.argtypes = [C.c_int, C.c_int64, C.c_int64]
         L.hm_scale_in_one_workgroup.restype = C.c_int
         L.hm_scale_in_one_workgroup.argtypes = [C.c_int64, C.c_int]
+        L.hm_scale_in_one_workgroup_lent.restype = C.c_int
+        L.hm_scale_in_one_workgroup_lent.argtypes = [C.c_int64]
         L.hm_scale_and_codes_in_one_launch.restype = C.c_int
         L.hm_scale_and_codes_in_one_launch.argtypes = [C.c_int64, C.c_int]
         L.hm_scale_by_words.restype = C.c_int
@@ -202,6 +204,11 @@ def tile_shape(kernel: str):
 
 def scale_in_one_workgroup(nbytes: int, has_scratch: bool) -> bool:
     return bool(lib().hm_scale_in_one_workgroup(nbytes, has_scratch))
+
+
+def scale_in_one_workgroup_lent(nbytes: int) -> bool:
+    """... on the default stream, without a workspace."""
+    return bool(lib().hm_scale_in_one_workgroup_lent(nbytes))
 
 
 def scale_and_codes_in_one_launch(nbytes: int, has_scratch: bool) -> bool:

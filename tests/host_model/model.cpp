@@ -184,10 +184,11 @@ void hm_rht16(float *v, uint32_t sign_word) {
 // the kernel (enum GemmKernel) that a product of these sizes takes
 int hm_choose_gemm(int64_t M, int64_t N, int64_t K, int f32) { return choose_gemm(M, N, K, f32 != 0); }
 
-// whether a tensor's scale (with or without scratch words), its scale and codes, take one launch
+// whether a tensor's scale (with or without a workspace, or on lent words), its scale and codes, take one launch
 int hm_scale_in_one_workgroup(int64_t bytes, int has_scratch) {
-  return scale_in_one_workgroup(bytes, has_scratch != 0);
+  return scale_in_one_workgroup(bytes, has_scratch ? ScratchWords::kWorkspace : ScratchWords::kNone);
 }
+int hm_scale_in_one_workgroup_lent(int64_t bytes) { return scale_in_one_workgroup(bytes, ScratchWords::kLent); }
 int hm_scale_and_codes_in_one_launch(int64_t bytes, int has_scratch) {
   return scale_and_codes_in_one_launch(bytes, has_scratch != 0);
 }

@@ -23,8 +23,9 @@ def _on_its_own_stream(call):
     return got
 
 
-# either side of 128 KiB (one workgroup), of 768 KiB (one workgroup without scratch words), the smallest tensor
-@pytest.mark.parametrize("rows,cols", [(1, 16), (64, 1024), (65, 1024), (384, 1024), (385, 1024), (1000, 2064)])
+# either side of 128 KiB, of 512 KiB (one workgroup on the default stream), of 768 KiB (one workgroup on any other), the
+# smallest tensor
+@pytest.mark.parametrize("rows,cols", [(1, 16), (64, 1024), (65, 1024), (256, 1024), (257, 1024), (384, 1024), (385, 1024), (1000, 2064)])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_scale_matches_the_other_forms(rows, cols, dtype):
     x = wl.make("c3", rows, cols, dtype=dtype)

@@ -58,6 +58,17 @@ result = on(None), on(1 << 12)
     assert default == other and len(default) >= 6
 
 
+def test_a_small_tensors_scale_is_one_bare_launch():
+    """512 KiB on the default stream: one workgroup, and no question to the runtime besides."""
+    small, larger = _hip_calls.run("""
+assert L.nvfp4_46_tensor_scale(P, params(256, 1024), P, None) == 0
+small = [(c[0], c[3]) for c in calls()]
+assert L.nvfp4_46_tensor_scale(P, params(320, 1024), P, None) == 0
+result = small, [(c[0], c[3]) for c in calls() if c[0] == "launch"]
+""")
+    assert small == [["launch", 1]] and len(larger) == 1 and larger[0][1] > 1
+
+
 def test_words_of_the_default_stream_are_looked_up_once():
     kinds = _hip_calls.run("""
 for _ in range(3):
