@@ -1386,10 +1386,14 @@ static int launch_flat(const FlatArgs &a) {
   const int cus = compute_units();
   int64_t n_long = 0, rounds_long = 0, grid;
   // With the transform a workgroup first draws its lanes' sign words, so a tensor of fewer rounds leaves fewer of them to
-  // one-round workgroups, an eighth (Hadamard + SR, us with sixteen rounds per compute unit / an eighth:
-  // 4096 x 4096 24.8 / 23.5, 16384 x 2048 46.9 / 43.3, 8192 x 8192 70.3 / 68.3; from 16384 x 8192 on the same).
+  // one-round workgroups, an eighth (us with sixteen rounds per compute unit / an eighth: Hadamard + SR
+  // 4096 x 4096 24.8 / 23.5, 16384 x 2048 46.9 / 43.3, 8192 x 8192 70.3 / 68.3; to nearest 1 to 15 % in BF16 and under the rules
+  // that compare in fp32; from 16384 x 8192 on the same).  Not the codes of one fp32 candidate rounded to nearest, which wait
+  // for memory: 5248 x 6192 23.2 / 23.8, 6144 x 6144 3.7 %, 8192 x 4096 2.5 %.
   int64_t short_rounds = (int64_t)cus * kFlatShortRoundsPerCu;
-  if (RHT && short_rounds > rounds / 8) short_rounds = rounds / 8;
+  constexpr bool kMemoryBound =
+      XF32 && ROUNDING == kRTN && OUT == kOutCodes && (SELECT == kSelForce6 || SELECT == kSelForce4);
+  if (RHT && !kMemoryBound && short_rounds > rounds / 8) short_rounds = rounds / 8;
   if (OUT == kOutAmax) {
     // the amax pass ends with one access per workgroup to the one result word: few,
     // long-lived workgroups that stride over the whole tensor
