@@ -377,19 +377,24 @@ __global__ __launch_bounds__(kThreads) void k_flat(
   const uint32_t tid = threadIdx.x;
   const uint32_t rounds = (uint32_t)((nblocks + kThreads - 1) / kThreads);
   const uint32_t tail = (uint32_t)(nblocks - (int64_t)(rounds - 1) * kThreads);  // 1..256
-  // The sign flips of the transform as one XOR mask per word of a block and lane, in LDS (piece q of lane t at
-  // [q][t]: a wave's 128-bit reads are conflict-free).  A lane writes and reads only its own
+  // The sign flips of the transform as XOR masks of a lane, in LDS (piece q of lane t at [q][t]: a wave's 128-bit
+  // reads are conflict-free): one per value, or, kPacked, one per word of two BF16 values, which are then flipped before
+  // they are unpacked.  The second is eight instructions and two LDS reads a block instead of sixteen and four,
+  // but they stand before everything else.  It pays under the squared-error rule, by registers (Hadamard + SR 98 -> 89, five
+  // waves per SIMD), and costs the others (BF16, us, per value / packed: 8192 x 8192 to nearest by mean absolute error
+  // 4.2 %, with SR 5.1 %, always 6 with SR 1.2 %; 20000 x 8192 5.5, 4.8 and 3.1 %).  A lane writes and reads only its own
   // slots, and the LDS operations of one wave execute in order, so no barrier is involved.
+  constexpr bool kPacked = !XF32 && SELECT == kSel46;
   using Raw = RawBlock<XF32>;
-  __shared__ uint4 sign_masks[RHT ? Raw::kPieces : 1][RHT ? kThreads : 1];
+  constexpr int kMaskPieces = kPacked ? Raw::kPieces : 4;
+  __shared__ uint4 sign_masks[RHT ? kMaskPieces : 1][RHT ? kThreads : 1];
   uint32_t B_lane = 0, sign_B = 0xffffffffu;
   if (RHT) B_lane = tid % nb_per_row;
-  // the values of a block as it arrived; BF16 pairs are flipped before they are unpacked (eight instructions
-  // and two LDS reads a block instead of sixteen and four; Hadamard + SR 98 -> 89 registers, five waves per SIMD)
+  // the values of a block as it arrived
   auto values = [&](const Raw &raw, float (&w)[16]) {
     if constexpr (!RHT) {
       unpack16(raw, w);
-    } else {
+    } else if constexpr (kPacked) {
       Raw flipped;
 #pragma unroll
       for (int q = 0; q < Raw::kPieces; ++q) {
@@ -397,6 +402,20 @@ __global__ __launch_bounds__(kThreads) void k_flat(
         flipped.w[q] = make_uint4(raw.w[q].x ^ m.x, raw.w[q].y ^ m.y, raw.w[q].z ^ m.z, raw.w[q].w ^ m.w);
       }
       unpack16(flipped, w);
+      hadamard16_quarter(w);
+    } else {
+      unpack16(raw, w);
+      uint32_t mask[16];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint4 m = sign_masks[q][tid];
+        mask[4 * q] = m.x;
+        mask[4 * q + 1] = m.y;
+        mask[4 * q + 2] = m.z;
+        mask[4 * q + 3] = m.w;
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) w[i] = u2f(f2u(w[i]) ^ mask[i]);
       hadamard16_quarter(w);
     }
   };
@@ -416,10 +435,10 @@ __global__ __launch_bounds__(kThreads) void k_flat(
       if (B >= nb_per_row) B -= nb_per_row;
       if (B != sign_B) {
         sign_B = B;
-        uint32_t mask[4 * Raw::kPieces];
+        uint32_t mask[4 * kMaskPieces];
         rht_sign_masks(rht_sign_word(rht_seed, B), mask);
 #pragma unroll
-        for (int q = 0; q < Raw::kPieces; ++q)
+        for (int q = 0; q < kMaskPieces; ++q)
           sign_masks[q][tid] = make_uint4(mask[4 * q], mask[4 * q + 1], mask[4 * q + 2], mask[4 * q + 3]);
       }
     }
@@ -1419,10 +1438,18 @@ static int launch_flat(const FlatArgs &a) {
       grid = n_long + (rounds - n_long * rounds_long);
     }
   }
-  return launch(k_flat<XF32, ROUNDING, SELECT, RHT, OUT>, dim3((uint32_t)grid), dim3(kThreads),
-                a.stream, a.x, a.alpha, a.codes, a.scales, a.choice, a.out, a.amax, a.nblocks,
-                a.nb_per_row, a.sr_seed, a.rht_seed, (uint32_t)n_long, (uint32_t)rounds_long,
-                runs_backwards(a.nblocks * 16, XF32), a.fin);
+  auto go = [&](auto kernel) {
+    return launch(kernel, dim3((uint32_t)grid), dim3(kThreads),
+                  a.stream, a.x, a.alpha, a.codes, a.scales, a.choice, a.out, a.amax, a.nblocks,
+                  a.nb_per_row, a.sr_seed, a.rht_seed, (uint32_t)n_long, (uint32_t)rounds_long,
+                  runs_backwards(a.nblocks * 16, XF32), a.fin);
+  };
+  // The transform's maximum of BF16 is taken with packed flips (the kernel's kPacked, which for a maximum is all that SELECT
+  // says) where a workgroup has at most two rounds: less to set up; else per value (us, per value / packed: 256 x 1024
+  // 4.7 / 4.6, 2048 x 2048 6.4 / 6.0; 2560 x 2048 6.1 / 6.5, 5248 x 6192 17.2 / 17.8, 32768 x 8192 94 / 97).
+  if constexpr (OUT == kOutAmax && !XF32)
+    if (rounds > (int64_t)2 * cus * kFlatAmaxWgPerCu) return go(k_flat<XF32, ROUNDING, kSelForce6, RHT, OUT>);
+  return go(k_flat<XF32, ROUNDING, SELECT, RHT, OUT>);
 }
 
 template <bool XF32, int ROUNDING, int SELECT>

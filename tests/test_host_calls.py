@@ -111,3 +111,15 @@ for kw in (dict(select=1), dict(select=2), dict(select=0), dict(select=1, x_dtyp
         assert transformed == plain
     for plain, transformed in grids[2:]:
         assert transformed < plain
+
+
+def test_maximum_after_the_rowwise_transform():
+    """BF16: one kernel where a workgroup has at most two rounds of 256 blocks (two workgroups per compute unit), another beyond."""
+    kernels = _hip_calls.run("""
+result = []
+for rows, cols in ((16, 1024), (2048, 2048), (2064, 2048), (2560, 2048), (8192, 8192)):
+    assert L.nvfp4_46_tensor_scale_ws(P, params(rows, cols, rht=1), P, P, 4352, None) == 0
+    result.append([c[1] for c in calls() if c[0] == "launch"])
+""")
+    small, large = kernels[0], kernels[-1]
+    assert small != large and kernels == [small, small, large, large, large]

@@ -103,3 +103,19 @@ def test_loads_of_a_tile_go_out_together():
         ops = re.findall(r"global_load_dwordx4|s_waitcnt [^\n]*vmcnt", body)
         first = ops.index("global_load_dwordx4")
         assert ops[first:first + 8] == ["global_load_dwordx4"] * 8, ops[:12]
+
+
+def test_packed_sign_flips_are_the_squared_error_rules():
+    """BF16 pairs are flipped before they are unpacked where that saves registers for a wave more; under the other rules it was 1 to
+    6 % slower.  The masks' LDS tells which a kernel does: 8 KiB, or 16 for one mask per value."""
+    with ThreadPoolExecutor(2) as pool:
+        kernels = [k for r in pool.map(lambda part: _report("nvfp4_46.hip", "NVFP4_46_PART", part), (1, 2)) for k in r.items()]
+    seen = 0
+    for name, v in kernels:
+        m = re.search(r"6k_flatILb0ELi(\d)ELi(\d)ELb1ELi(\d)E", name)
+        if not m:
+            continue
+        rounding, select, out = map(int, m.groups())
+        assert v["LDS"] == 2048 + (8192 if select == 0 else 16384) + (8192 if out == 1 else 0), (name, v)
+        seen += 1
+    assert seen == 2 * 5 * 2, seen                 # round to nearest and stochastic, five rules, codes and fake-quant
