@@ -80,6 +80,15 @@ NV_DEV uint32_t e2m1_sr_code_fast_sel(uint32_t old, float y, uint32_t not_w, flo
     default: return e2m1_sr_code_fast<3>(old, y, not_w, wf, margin);
   }
 }
+NV_DEV void e2m1_sr_code_fast2_sel(uint32_t &old_a, uint32_t &old_b, float ya, float yb, uint32_t not_w, float wf,
+                                   float &margin, int sel) {
+  switch (sel) {
+    case 0: return e2m1_sr_code_fast2<0>(old_a, old_b, ya, yb, not_w, wf, margin);
+    case 1: return e2m1_sr_code_fast2<1>(old_a, old_b, ya, yb, not_w, wf, margin);
+    case 2: return e2m1_sr_code_fast2<2>(old_a, old_b, ya, yb, not_w, wf, margin);
+    default: return e2m1_sr_code_fast2<3>(old_a, old_b, ya, yb, not_w, wf, margin);
+  }
+}
 // the codes of two values held times 2^-126
 NV_DEV uint32_t hw_pk_fp4_of_scaled_sel(uint32_t old, float a, float b, int sel) {
   switch (sel) {
@@ -322,30 +331,43 @@ NV_DEV void sr_candidates_by_rule(const float (&v)[16], const Words &words, SrCa
   if (TWO) b.error = error_b.value();
 }
 
-// One candidate by the conversion instruction, which lowers `margin` (see e2m1_sr_code_fast: the codes are only valid
-// if it stays above kSrMarginAtRisk).
-template <int ERR, typename Words>
-NV_DEV void sr_candidate_by_conversion(const float (&v)[16], const Words &words, SrCandidate &a, float &margin) {
-  CandidateError<ERR> error;
+// Both candidates, or the first, by the conversion instruction, which lowers `margin` (see e2m1_sr_code_fast: the codes are
+// only valid if it stays above kSrMarginAtRisk).
+template <bool TWO, int ERR, typename Words>
+NV_DEV void sr_candidates_by_conversion(const float (&v)[16], const Words &words, SrCandidate &a, SrCandidate &b,
+                                        float &margin) {
+  CandidateError<ERR> error_a, error_b;
   uint32_t w[16];
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     // one conversion per element (only the first source position rounds as defined): even
     // elements into the bytes of one word, odd ones into another
-    uint32_t even = any_register(), odd = any_register();
+    uint32_t even_a = any_register(), odd_a = any_register(), even_b = any_register(), odd_b = any_register();
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       words_from(words, 8 * h + i, w);
-      uint32_t &c = i & 1 ? odd : even;
-      c = e2m1_sr_code_fast_sel(c, v[8 * h + i] * a.enc, ~w[8 * h + i], (float)w[8 * h + i], margin, i / 2);
+      const float x = v[8 * h + i], wf = (float)w[8 * h + i];
+      const uint32_t not_w = ~w[8 * h + i];
+      uint32_t &ca = i & 1 ? odd_a : even_a, &cb = i & 1 ? odd_b : even_b;
+      if (TWO) e2m1_sr_code_fast2_sel(ca, cb, x * a.enc, x * b.enc, not_w, wf, margin, i / 2);
+      else ca = e2m1_sr_code_fast_sel(ca, x * a.enc, not_w, wf, margin, i / 2);
     }
-    a.code[h] = (even & 0x0f0f0f0fu) | ((odd << 4) & 0xf0f0f0f0u);
-    in_register(a.code[h]);                 // (and not as the two words it is made of)
-    float g[8];
-    if (ERR != kErrNone) grid8(a.code[h], g);
-    error.add8(g, v, h, a.dec);
+    a.code[h] = (even_a & 0x0f0f0f0fu) | ((odd_a << 4) & 0xf0f0f0f0u);
+    if (TWO) b.code[h] = (even_b & 0x0f0f0f0fu) | ((odd_b << 4) & 0xf0f0f0f0u);
+    in_register(a.code[h]);                 // (and not as the words it is made of)
+    if (TWO) in_register(b.code[h]);
+    if (ERR != kErrNone) {
+      float g[8];
+      grid8(a.code[h], g);
+      error_a.add8(g, v, h, a.dec);
+      if (TWO) {
+        grid8(b.code[h], g);
+        error_b.add8(g, v, h, b.dec);
+      }
+    }
   }
-  a.error = error.value();
+  a.error = error_a.value();
+  if (TWO) b.error = error_b.value();
 }
 
 // One candidate on its own: stochastic rounding by the conversion instruction, redone in software for the rare
@@ -356,7 +378,7 @@ NV_DEV float candidate(const float (&v)[16], const Words &words, float dec, floa
   if (ROUNDING == kRTN) return rtn_candidate<ERR>(v, dec, enc, lo, hi);
   SrCandidate c{dec, enc, {0u, 0u}, 0.0f}, none{};
   float margin = __builtin_inff();
-  sr_candidate_by_conversion<ERR>(v, words, c, margin);
+  sr_candidates_by_conversion<false, ERR>(v, words, c, none, margin);
   if (!(margin > kSrMarginAtRisk)) sr_candidates_by_rule<false, ERR>(v, words, c, none);
   lo = c.code[0];
   hi = c.code[1];
@@ -537,13 +559,16 @@ NV_DEV void block_scales(float b, const ScaleConsts &k, uint32_t &S6, uint32_t &
 template <int ROUNDING, int SELECT>
 constexpr bool kTogether = ROUNDING == kSR && SELECT != kSelForce4 && SELECT != kSelForce6;
 
+// What the conversion instruction rounds instead of sums on the subnormal grid (see quantize_block): a candidate on its
+// own, or both candidates together.
+enum : int { kNothing = 0, kSingles = 1, kPairs = 2 };
+
 // The per-block procedure (Table 3 lines 1-14) in one pass.  DEFINED = false: the squared-error rule
 // compares the cheap estimates and reports through `undecided` when they cannot tell (the result is then
 // provisional); true: the errors are evaluated exactly as defined.  The other rules always evaluate the
-// defined errors.  With kTogether, FAST = true rounds on the subnormal grid (sr_candidates) and reports through `risky`
-// when its answer may not be the rule's, and false is the rule itself.  CONVERSION = true rounds a candidate on its own
-// by the conversion instruction (see quantize_block).
-template <int ROUNDING, int SELECT, bool DEFINED, bool FAST, bool CONVERSION, typename Words>
+// defined errors.  With kTogether, FAST = true rounds on the subnormal grid (sr_candidates), or as CONVERSION says, and
+// reports through `risky` when its answer may not be the rule's, and false is the rule itself.
+template <int ROUNDING, int SELECT, bool DEFINED, bool FAST, int CONVERSION, typename Words>
 NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
                                        const ScaleConsts &k, const ScaleTable &tab,
                                        bool &undecided, bool &risky) {
@@ -579,7 +604,12 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
     look_up(S6, r6, enc6, m6);
     look_up(S4, r4, enc4, m4);
     SrCandidate c{r6.dec, enc6, {0u, 0u}, 0.0f}, d{r4.dec, enc4, {0u, 0u}, 0.0f};
-    if constexpr (FAST) {
+    if constexpr (FAST && CONVERSION == kPairs) {
+      static_assert(kErr != kErrMseEstimate, "the estimate is made on the subnormal grid");
+      float margin = __builtin_inff();
+      sr_candidates_by_conversion<true, kErr>(v, words, c, d, margin);
+      risky = !(margin > kSrMarginAtRisk);
+    } else if constexpr (FAST) {
       uint32_t risk = ~0u;
       sr_candidates<true, kErr>(v, words, c, d, risk);
       // (no scale to 4 that follows from the tensor's own alpha leaves a magnitude above 6)
@@ -600,7 +630,7 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
     // winner stochastically; a single candidate need not be rounded to nearest for that.
     constexpr bool kRound = ROUNDING != kSRAfterRtnSelect || kBoth;
     auto round = [&](const BlockResult &r, float enc, uint32_t &lo, uint32_t &hi) {
-      if constexpr (ROUNDING == kSR && !CONVERSION) {
+      if constexpr (ROUNDING == kSR && CONVERSION != kSingles) {
         sr_alone(v, words, r.dec, enc, lo, hi);
         return 0.0f;
       } else {
@@ -648,9 +678,12 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
 // wave in some hundreds is in the case, and in a small launch all wait for it: with the rule in
 // software 1008 x 4096 took 8.1 us instead of 7.5), a risky one by the rule; the margin of the first pass covers
 // both candidates, whichever the second keeps.
-// CONVERSION is for lanes that draw the words of two blocks at once: the words are in registers anyway there, the
-// conversion instruction needs nothing besides.
-template <int ROUNDING, int SELECT, bool CONVERSION = false, typename Words, typename Again>
+// CONVERSION: kSingles is for lanes that draw the words of two blocks at once: the words are in registers anyway there,
+// the conversion instruction needs nothing besides.  kPairs is for the rowwise kernel under the rules of absolute errors, which
+// read the rounded values back from the codes either way (us, subnormal grid / conversion, SR by mean absolute error: BF16 4096 x
+// 4096 20.7 / 19.5, 5248 x 6192 36.2 / 34.7, with the transform 3000 x 4096 5 %; fp32 3000 x 4096 4 %; by the largest error 0
+// to 4 %; in tiles the grid is ahead, 1 to 3 %).
+template <int ROUNDING, int SELECT, int CONVERSION = kNothing, typename Words, typename Again>
 NV_DEV BlockResult quantize_block(const float (&v)[16], const Words &words,
                                   const ScaleConsts &k, const ScaleTable &tab, Again &&again) {
   bool undecided = false, risky = false;

@@ -167,6 +167,32 @@ NV_DEV uint32_t e2m1_sr_code_fast(uint32_t old, float y, uint32_t not_w, float w
 }
 constexpr float kSrMarginAtRisk = 2048.0f;
 
+// The same element rounded under two scales: byte SEL of both words, the others kept.  The two conversions
+// stand in one piece of assembly, so that the wait state after them is one for both.
+template <int SEL>
+NV_DEV void e2m1_sr_code_fast2(uint32_t &old_a, uint32_t &old_b, float ya, float yb, uint32_t not_w, float wf,
+                               float &margin) {
+#ifdef NVFP4_46_CVT_SR_PK_FP4_ON_HOST
+  old_a = e2m1_sr_code_fast<SEL>(old_a, ya, not_w, wf, margin);
+  old_b = e2m1_sr_code_fast<SEL>(old_b, yb, not_w, wf, margin);
+#else
+  const float c = in_odd_vector_register(0x1p33f);
+  const float ta = __builtin_fmaf(fabsf(ya), c, -wf), tb = __builtin_fmaf(fabsf(yb), c, -wf);
+  margin = fminf(fminf(margin, fabsf(ta)), fabsf(ta - 0x1p32f));   // one v_min3_f32
+  margin = fminf(fminf(margin, fabsf(tb)), fabsf(tb - 0x1p32f));
+  const f32x2 sa = {ya, ta}, sb = {yb, tb};
+#define NV_SR2(op_sel)                                                                             \
+  asm("v_cvt_scalef32_sr_pk_fp4_f32 %0, %2, %4, 1.0" op_sel                                        \
+      "\n\tv_cvt_scalef32_sr_pk_fp4_f32 %1, %3, %4, 1.0" op_sel "\n\ts_nop 0"                      \
+      : "+&v"(old_a), "+&v"(old_b) : "v"(sa), "v"(sb), "v"(not_w))
+  if constexpr (SEL == 0) NV_SR2("");
+  else if constexpr (SEL == 1) NV_SR2(" op_sel:[0,0,1,0]");
+  else if constexpr (SEL == 2) NV_SR2(" op_sel:[0,0,0,1]");
+  else NV_SR2(" op_sel:[0,0,1,1]");
+#undef NV_SR2
+#endif
+}
+
 // The same rounding without the conversion instruction, on a grid that fp32 has of its own.  Scaled by
 // 2^-126 the magnitudes below 1 are subnormal, so that as integers the bits of y * 2^-126 rise by 2^22 from each
 // E2M1 magnitude to the next, all the way from 0 to 6: code index = bits >> 22, and what lies above it is

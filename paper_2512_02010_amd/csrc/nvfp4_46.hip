@@ -479,7 +479,7 @@ __global__ __launch_bounds__(kThreads) void k_flat(
     };
     BlockResult res;
     if constexpr (kAhead) res = quantize_block<ROUNDING, SELECT>(v, u, sc, tab, again);
-    else res = quantize_block<ROUNDING, SELECT>(v, words, sc, tab, again);
+    else res = quantize_block<ROUNDING, SELECT, (SELECT == kSel46 ? kNothing : kPairs)>(v, words, sc, tab, again);
     if (OUT == kOutCodes) {
       store_as<kNtCodes>(codes + base + tid, make_uint2(res.lo, res.hi));
       store_as<kNtCodes>(scales + base + tid, (uint8_t)res.scale);
@@ -887,8 +887,8 @@ NV_DEV void quantize_tile(
     if constexpr (kDrawn) {
       uint32_t ua[16], ub[16];
       draw(ua, ub);
-      ra = quantize_block<ROUNDING, SELECT, true>(va, ua, sc, tab, first);
-      rbk = quantize_block<ROUNDING, SELECT, true>(vb, ub, sc, tab, second);
+      ra = quantize_block<ROUNDING, SELECT, kSingles>(va, ua, sc, tab, first);
+      rbk = quantize_block<ROUNDING, SELECT, kSingles>(vb, ub, sc, tab, second);
     } else {
       constexpr int kStep = 16;
       auto words_of = [&](int column) {

@@ -3,6 +3,8 @@
 // gfx950_on_host.hpp.
 #include "gfx950_on_host.hpp"
 
+#include <type_traits>
+
 #include "block.hpp"
 #include "gemm_shapes.hpp"
 #include "small_tensors.hpp"
@@ -29,12 +31,27 @@ BlockResult run_block(const float (&v)[16], const uint32_t (&u)[16], const Scale
       uu[i] = u[i];
     }
   };
+  // the kernels' ways to round stochastically (quantize_block's CONVERSION) give the same, or no block has these codes
+  auto all_ways = [&](auto rule) {
+    constexpr int kRule = decltype(rule)::value;
+    BlockResult r = quantize_block<ROUNDING, kRule>(v, u, k, tab, again);
+    if constexpr (ROUNDING == kSR) {
+      const int second_passes = g_second_passes;
+      auto check = [&](const BlockResult &other) {
+        if (other.lo != r.lo || other.hi != r.hi || other.scale != r.scale || other.four != r.four) r.scale = 0xffu;
+      };
+      check(quantize_block<ROUNDING, kRule, kSingles>(v, u, k, tab, again));
+      if constexpr (kRule != kSel46) check(quantize_block<ROUNDING, kRule, kPairs>(v, u, k, tab, again));
+      g_second_passes = second_passes;
+    }
+    return r;
+  };
   switch (select) {
-    case kSel46: return quantize_block<ROUNDING, kSel46>(v, u, k, tab, again);
-    case kSelForce6: return quantize_block<ROUNDING, kSelForce6>(v, u, k, tab, again);
-    case kSelForce4: return quantize_block<ROUNDING, kSelForce4>(v, u, k, tab, again);
-    case kSel46Mae: return quantize_block<ROUNDING, kSel46Mae>(v, u, k, tab, again);
-    default: return quantize_block<ROUNDING, kSel46AbsMax>(v, u, k, tab, again);
+    case kSel46: return all_ways(std::integral_constant<int, kSel46>{});
+    case kSelForce6: return all_ways(std::integral_constant<int, kSelForce6>{});
+    case kSelForce4: return all_ways(std::integral_constant<int, kSelForce4>{});
+    case kSel46Mae: return all_ways(std::integral_constant<int, kSel46Mae>{});
+    default: return all_ways(std::integral_constant<int, kSel46AbsMax>{});
   }
 }
 

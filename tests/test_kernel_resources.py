@@ -87,15 +87,18 @@ def test_fp32_stochastic_fake_quant_leaves_room_for_four_workgroups():
             assert words or v["Occupancy"] == 3, (name, v)
 
 
+def _assembly(part: int) -> str:
+    flags = [f for f in build.HIPCC_FLAGS if f != "-shared"]
+    return subprocess.run([build.hipcc(), *flags, f"-I{build.ROOT / 'include'}", f"-I{build.PKG / 'csrc'}",
+                           f"-DNVFP4_46_PART={part}", "--offload-device-only", "-S", str(build.PKG / "csrc" / "nvfp4_46.hip"),
+                           "-o", "-"], capture_output=True, text=True, check=True).stdout
+
+
 def test_loads_of_a_tile_go_out_together():
     """k_tile's lanes load their share of the tile (two row blocks, 16 bytes at a time) before they wait for any of it: a
     wait in between, which the compiler put there to move a register of a piece that is zero outside the
     tensor, cost fp32 fake-quant along the columns 7 to 11 %."""
-    flags = [f for f in build.HIPCC_FLAGS if f != "-shared"]
-    part = 4                                       # fp32, round to nearest
-    asm = subprocess.run([build.hipcc(), *flags, f"-I{build.ROOT / 'include'}", f"-I{build.PKG / 'csrc'}",
-                          f"-DNVFP4_46_PART={part}", "--offload-device-only", "-S", str(build.PKG / "csrc" / "nvfp4_46.hip"),
-                          "-o", "-"], capture_output=True, text=True, check=True).stdout
+    asm = _assembly(4)                             # fp32, round to nearest
     bodies = re.findall(r"^_ZN\S+6k_tileILb1ELi0ELi\dELb\dELb(\d)ELi(\d)E\S+:(.*?)^\.Lfunc_end", asm, flags=re.M | re.S)
     staged = [body for want_row, out, body in bodies if (want_row, out) != ("0", "0")]     # the others load no tile
     assert len(bodies) == 5 * 5 and len(staged) == 5 * 3
@@ -119,3 +122,12 @@ def test_packed_sign_flips_are_the_squared_error_rules():
         assert v["LDS"] == 2048 + (8192 if select == 0 else 16384) + (8192 if out == 1 else 0), (name, v)
         seen += 1
     assert seen == 2 * 5 * 2, seen                 # round to nearest and stochastic, five rules, codes and fake-quant
+
+
+def test_stochastic_rounding_of_the_rowwise_kernel():
+    """Under the rules of absolute errors both candidates are rounded by the conversion instruction (on the subnormal grid 2 to 6 %
+    slower), under the squared-error rule, and one candidate, on the subnormal grid."""
+    bodies = re.findall(r"^_ZN\S+6k_flatILb0ELi1ELi(\d)ELb\dELi[01]E\S+:(.*?)^\.Lfunc_end", _assembly(2), flags=re.M | re.S)
+    assert len(bodies) == 5 * 4                    # five rules x transform or not x codes and fake-quant
+    for select, body in bodies:
+        assert ("v_cvt_scalef32_sr_pk_fp4_f32" in body) == (select in "34"), select
