@@ -560,7 +560,7 @@ template <int ROUNDING, int SELECT>
 constexpr bool kTogether = ROUNDING == kSR && SELECT != kSelForce4 && SELECT != kSelForce6;
 
 // What the conversion instruction rounds instead of sums on the subnormal grid (see quantize_block): a candidate on its
-// own, or both candidates together.
+// own, both candidates together, or either.
 enum : int { kNothing = 0, kSingles = 1, kPairs = 2 };
 
 // The per-block procedure (Table 3 lines 1-14) in one pass.  DEFINED = false: the squared-error rule
@@ -604,7 +604,7 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
     look_up(S6, r6, enc6, m6);
     look_up(S4, r4, enc4, m4);
     SrCandidate c{r6.dec, enc6, {0u, 0u}, 0.0f}, d{r4.dec, enc4, {0u, 0u}, 0.0f};
-    if constexpr (FAST && CONVERSION == kPairs) {
+    if constexpr (FAST && (CONVERSION & kPairs) != 0) {
       static_assert(kErr != kErrMseEstimate, "the estimate is made on the subnormal grid");
       float margin = __builtin_inff();
       sr_candidates_by_conversion<true, kErr>(v, words, c, d, margin);
@@ -630,7 +630,7 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
     // winner stochastically; a single candidate need not be rounded to nearest for that.
     constexpr bool kRound = ROUNDING != kSRAfterRtnSelect || kBoth;
     auto round = [&](const BlockResult &r, float enc, uint32_t &lo, uint32_t &hi) {
-      if constexpr (ROUNDING == kSR && CONVERSION != kSingles) {
+      if constexpr (ROUNDING == kSR && !(CONVERSION & kSingles)) {
         sr_alone(v, words, r.dec, enc, lo, hi);
         return 0.0f;
       } else {
@@ -678,11 +678,12 @@ NV_DEV BlockResult quantize_block_pass(const float (&v)[16], const Words &words,
 // wave in some hundreds is in the case, and in a small launch all wait for it: with the rule in
 // software 1008 x 4096 took 8.1 us instead of 7.5), a risky one by the rule; the margin of the first pass covers
 // both candidates, whichever the second keeps.
-// CONVERSION: kSingles is for lanes that draw the words of two blocks at once: the words are in registers anyway there,
-// the conversion instruction needs nothing besides.  kPairs is for the rowwise kernel under the rules of absolute errors, which
+// CONVERSION: either is for lanes that draw the words of two blocks at once: the words are in registers anyway there,
+// the conversion instruction needs nothing besides (fp32 fake-quant along the columns, 8192 x 8192, by mean absolute error
+// 98.9 us on the subnormal grid / 96.8).  kPairs is for the rowwise kernel under the rules of absolute errors, which
 // read the rounded values back from the codes either way (us, subnormal grid / conversion, SR by mean absolute error: BF16 4096 x
 // 4096 20.7 / 19.5, 5248 x 6192 36.2 / 34.7, with the transform 3000 x 4096 5 %; fp32 3000 x 4096 4 %; by the largest error 0
-// to 4 %; in tiles the grid is ahead, 1 to 3 %).
+// to 4 %; in tiles whose words wait in LDS the grid is ahead, 1 to 3 %).
 template <int ROUNDING, int SELECT, int CONVERSION = kNothing, typename Words, typename Again>
 NV_DEV BlockResult quantize_block(const float (&v)[16], const Words &words,
                                   const ScaleConsts &k, const ScaleTable &tab, Again &&again) {

@@ -887,8 +887,8 @@ NV_DEV void quantize_tile(
     if constexpr (kDrawn) {
       uint32_t ua[16], ub[16];
       draw(ua, ub);
-      ra = quantize_block<ROUNDING, SELECT, kSingles>(va, ua, sc, tab, first);
-      rbk = quantize_block<ROUNDING, SELECT, kSingles>(vb, ub, sc, tab, second);
+      ra = quantize_block<ROUNDING, SELECT, kSingles | kPairs>(va, ua, sc, tab, first);
+      rbk = quantize_block<ROUNDING, SELECT, kSingles | kPairs>(vb, ub, sc, tab, second);
     } else {
       constexpr int kStep = 16;
       auto words_of = [&](int column) {
