@@ -32,6 +32,7 @@
 #include "codec.hpp"
 #include "gemm_shapes.hpp"
 #include "launch.hpp"
+#include "layer.hpp"
 #include "nvfp4_46.h"
 #include "tensor.hpp"
 
@@ -1829,9 +1830,7 @@ NVFP4_46_TILE(Tile256x128)
 
 using namespace nvfp4_46;
 
-// Not part of the C ABI: what paper_2512_02010_amd/linear.py runs where few_rows_in_one_launch() says so.  The same
-// codes as nvfp4_46_scale_quantize (rowwise, to nearest, 4/6 by squared error) finds for x [M][K] BF16, their product with B
-// as nvfp4_46_gemm takes it, C in BF16; the same checks and statuses, ERR_UNSUPPORTED for any other size.
+// (see layer.hpp)
 extern "C" int nvfp4_46_few_rows(const void *x, float fp8_max, const void *codes_b, const void *scales_b,
                                  const float *alpha_b, int64_t M, int64_t N, int64_t K, uint32_t flags, void *out,
                                  void *stream) {

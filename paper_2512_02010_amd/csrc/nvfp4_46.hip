@@ -21,6 +21,7 @@
 
 #include "block.hpp"
 #include "launch.hpp"
+#include "layer.hpp"
 #include "nvfp4_46.h"
 #include "nvfp4_46_fused.h"
 #include "small_tensors.hpp"
@@ -1853,10 +1854,7 @@ int nvfp4_46_scale_quantize(const void *x, const nvfp4_46_params *p, float *alph
                            choice_col, stream);
 }
 
-// Not part of the C ABI: both operands of paper_2512_02010_amd/linear.py's weight gradient, dy [rows][n] rounded
-// stochastically and x [rows][k] to nearest, BF16, columnwise with the transform: what two calls of
-// nvfp4_46_scale_quantize give, with their checks and statuses, in two launches instead of four where there are scratch words
-// for it.
+// (see layer.hpp)
 int nvfp4_46_wgrad_operands(const void *dy, const void *x, int64_t rows, int64_t n, int64_t k, uint32_t select,
                             uint64_t sr_seed, uint64_t rht_seed, float *alpha_dy, void *codes_dy, void *scales_dy,
                             float *alpha_x, void *codes_x, void *scales_x, void *workspace, size_t workspace_bytes,

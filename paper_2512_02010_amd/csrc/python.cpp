@@ -18,30 +18,27 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "gemm_shapes.hpp"
+#include "layer.hpp"
 #include "nvfp4_46.h"
+#include "nvfp4_46_fused.h"
 
 namespace {
 
 // The library's entry points, in the order of binding.py's NATIVE_ENTRY_POINTS.
 struct EntryPoints {
-  int (*tensor_scale)(const void *, const nvfp4_46_params *, float *, void *);
-  int (*tensor_scale_ws)(const void *, const nvfp4_46_params *, float *, void *, size_t, void *);
-  int (*quantize)(const void *, const nvfp4_46_params *, const float *, void *, void *, void *, void *, void *,
-                  void *, void *);
-  int (*scale_quantize)(const void *, const nvfp4_46_params *, float *, void *, size_t, void *, void *, void *,
-                        void *, void *, void *, void *);
-  int (*dequantize)(const void *, const void *, const float *, int64_t, int64_t, uint32_t, void *, void *);
-  int (*fake_quant)(const void *, const nvfp4_46_params *, const float *, void *, void *);
-  int (*gemm)(const void *, const void *, const float *, const void *, const void *, const float *, int64_t,
-              int64_t, int64_t, uint32_t, uint32_t, void *, void *);
+  decltype(&nvfp4_46_tensor_scale) tensor_scale;
+  decltype(&nvfp4_46_tensor_scale_ws) tensor_scale_ws;
+  decltype(&nvfp4_46_quantize) quantize;
+  decltype(&nvfp4_46_scale_quantize) scale_quantize;
+  decltype(&nvfp4_46_dequantize) dequantize;
+  decltype(&nvfp4_46_fake_quant) fake_quant;
+  decltype(&nvfp4_46_gemm) gemm;
 };
 EntryPoints entry;
-// ... and of binding.py's LAYER_ENTRY_POINTS, which are no part of the C ABI.
+// ... and of binding.py's LAYER_ENTRY_POINTS.
 struct LayerEntryPoints {
-  int (*few_rows)(const void *, float, const void *, const void *, const float *, int64_t, int64_t, int64_t, uint32_t,
-                  void *, void *);
-  int (*wgrad_operands)(const void *, const void *, int64_t, int64_t, int64_t, uint32_t, uint64_t, uint64_t, float *,
-                        void *, void *, float *, void *, void *, void *, size_t, void *);
+  decltype(&nvfp4_46_few_rows) few_rows;
+  decltype(&nvfp4_46_wgrad_operands) wgrad_operands;
 };
 LayerEntryPoints layer;
 PyObject *error_class;     // Nvfp4Error(status, name of the entry point)

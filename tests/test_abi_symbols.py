@@ -3,6 +3,7 @@ and its host-side argument validation returns the documented codes without touch
 the GPU (every call below fails validation before any HIP call)."""
 import ctypes as C
 import re
+import subprocess
 from pathlib import Path
 
 import pytest
@@ -31,6 +32,15 @@ def test_library_exports_every_declared_symbol():
     assert sorted(B.EXPORTS) == names
     for n in names:
         assert hasattr(L, n), n
+
+
+def test_what_the_library_exports_besides_is_declared():
+    """Two entry points for the package's own Python module (csrc/layer.hpp, which that module is built with); not more."""
+    names = set(re.findall(r" T (nvfp4_46_\w+)$", subprocess.run(["nm", "-D", "--defined-only", str(B.library_path())], text=True,
+                                                                capture_output=True, check=True).stdout, flags=re.M))
+    layer = set(_declared((ROOT / "paper_2512_02010_amd" / "csrc" / "layer.hpp").read_text()))
+    assert layer == {"nvfp4_46_" + name for name in B.LAYER_ENTRY_POINTS}
+    assert names == layer | set(B.EXPORTS)
 
 
 def test_params_struct_layout_matches_header():
@@ -162,8 +172,7 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
 
 def test_every_hip_source_is_part_of_the_build():
     from pathlib import Path
-    from paper_2512_02010_amd import build
-    sources = {p.name for p in (Path(build.PKG) / "csrc").glob("*.hip")}
+        sources = {p.name for p in (Path(build.PKG) / "csrc").glob("*.hip")}
     assert sources == {Path(u[0]).name for u in build.UNITS}
     # each part number of a source compiled in parts appears exactly once
     for name in ("nvfp4_46.hip", "gemm.hip"):
