@@ -7,6 +7,12 @@
 
 #include "nvfp4_46.h"
 
+// The calls on the default stream of one device share scratch words (lent_words() in nvfp4_46.hip) since that stream, handle 0,
+// is one for all threads.  With a default stream per thread it would not be.
+#ifdef HIP_API_PER_THREAD_DEFAULT_STREAM
+#error "the library is built with the legacy default stream"
+#endif
+
 namespace nvfp4_46 {
 
 // Launches through hipLaunchKernel, whose return value belongs to this launch (the

@@ -9,6 +9,7 @@ from pathlib import Path
 import pytest
 
 from paper_2512_02010_amd import binding as B
+from paper_2512_02010_amd import build
 
 ROOT = Path(__file__).resolve().parent.parent
 HEADER = (ROOT / "include" / "nvfp4_46.h").read_text()
@@ -41,6 +42,17 @@ def test_what_the_library_exports_besides_is_declared():
     layer = set(_declared((ROOT / "paper_2512_02010_amd" / "csrc" / "layer.hpp").read_text()))
     assert layer == {"nvfp4_46_" + name for name in B.LAYER_ENTRY_POINTS}
     assert names == layer | set(B.EXPORTS)
+
+
+def test_the_default_stream_is_one_for_all_threads(tmp_path):
+    """Scratch words are lent to calls on the default stream; the sources do not compile with one per thread."""
+    source = tmp_path / "one.hip"
+    source.write_text('#include "launch.hpp"\n')
+    base = [build.hipcc(), "--offload-arch=gfx950", "--offload-host-only", "-std=c++17", "-fsyntax-only",
+            f"-I{build.ROOT / 'include'}", f"-I{build.PKG / 'csrc'}", str(source)]
+    assert subprocess.run(base, capture_output=True).returncode == 0
+    per_thread = subprocess.run([*base, "-fgpu-default-stream=per-thread"], capture_output=True, text=True)
+    assert per_thread.returncode != 0 and "legacy default stream" in per_thread.stderr
 
 
 def test_params_struct_layout_matches_header():
@@ -172,7 +184,8 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
 
 def test_every_hip_source_is_part_of_the_build():
     from pathlib import Path
-        sources = {p.name for p in (Path(build.PKG) / "csrc").glob("*.hip")}
+    from paper_2512_02010_amd import build
+    sources = {p.name for p in (Path(build.PKG) / "csrc").glob("*.hip")}
     assert sources == {Path(u[0]).name for u in build.UNITS}
     # each part number of a source compiled in parts appears exactly once
     for name in ("nvfp4_46.hip", "gemm.hip"):
