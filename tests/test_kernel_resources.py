@@ -8,6 +8,7 @@ code silently depends on them:
     hand-counted `s_waitcnt vmcnt(N)` use no scratch memory: a spill would add vector-memory
     instructions of the compiler's own and make those counts too small.
 """
+import functools
 import re
 import subprocess
 from concurrent.futures import ThreadPoolExecutor
@@ -17,6 +18,7 @@ from paper_2512_02010_amd import build
 from . import _host_model as hm
 
 
+@functools.lru_cache(maxsize=None)
 def _report(source: str, part_macro: str, part: int):
     flags = [f for f in build.HIPCC_FLAGS if f != "-shared"]
     r = subprocess.run([build.hipcc(), *flags, f"-I{build.ROOT / 'include'}", f"-I{build.PKG / 'csrc'}",
@@ -60,6 +62,25 @@ def test_tile_kernel_budgets():
     assert all(v["Occupancy"] >= (2 if "ILi4ELi2E" in k else 4) for k, v in tile.items()), tile
 
 
+def test_budgets_of_the_kernels_beside_them():
+    """k_few_rows and k_gemm_scales_first count their copies by hand as well, the second with room for four waves per SIMD;
+    k_tile_pair has the registers and the LDS of its stochastic half."""
+    products = _report("gemm.hip", "NVFP4_46_GEMM_PART", 6)
+    few = {k: v for k, v in products.items() if "k_few_rows" in k}
+    first = {k: v for k, v in products.items() if "k_gemm_scales_first" in k}
+    assert len(few) == 2 and len(first) == 2, list(products)
+    assert all(v["ScratchSize"] == 0 for v in (*few.values(), *first.values())), (few, first)
+    assert all(v["Occupancy"] >= 4 for v in first.values()), first
+    quant = _report("nvfp4_46.hip", "NVFP4_46_PART", 2)
+    pair = {re.search(r"k_tile_pairILi(\d)E", k).group(1): v for k, v in quant.items() if "k_tile_pair" in k}
+    tile = {re.search(r"6k_tileILb0ELi1ELi(\d)E", k).group(1): v for k, v in quant.items()
+            if re.search(r"6k_tileILb0ELi1ELi\dELb1ELb0ELi0E", k)}        # SR, transform, columnwise codes
+    assert sorted(pair) == sorted(tile) == list("01234")
+    for select, v in pair.items():
+        assert v["ScratchSize"] == 0 and v["LDS"] == tile[select]["LDS"], (select, v, tile[select])
+        assert v["Occupancy"] >= tile[select]["Occupancy"] - 1, (select, v, tile[select])
+
+
 def test_tile_kernel_workgroups_per_compute_unit():
     """What the LDS that each shape asks for at launch (stages or partial sums, the larger) leaves of a
     compute unit's 160 KiB."""
@@ -87,6 +108,7 @@ def test_fp32_stochastic_fake_quant_leaves_room_for_four_workgroups():
             assert words or v["Occupancy"] == 3, (name, v)
 
 
+@functools.lru_cache(maxsize=None)
 def _assembly(part: int) -> str:
     flags = [f for f in build.HIPCC_FLAGS if f != "-shared"]
     return subprocess.run([build.hipcc(), *flags, f"-I{build.ROOT / 'include'}", f"-I{build.PKG / 'csrc'}",
