@@ -1,4 +1,7 @@
 """GPU: scale, codes and product of a few rows in one launch, against the oracle and against the calls one by one."""
+import threading
+
+import numpy as np
 import pytest
 import torch
 
@@ -25,8 +28,6 @@ def _weight(N, K, tiles):
                                  (1, 28672)])
 @pytest.mark.parametrize("N,tiles", [(1, False), (17, False), (48, True), (160, True)])
 def test_few_rows_match_the_oracle(M, K, N, tiles):
-    if tiles and K % 16:
-        pytest.skip("16x16 tiles need whole tiles")
     cb, sb, ab = _weight(N, K, tiles)
     bits = wl.bf16_bits(wl.make("c3", M, K))
     aa = ref.tensor_scale(bits)
@@ -39,6 +40,51 @@ def test_few_rows_match_the_oracle(M, K, N, tiles):
     assert got is not None and got.shape == (M, N) and got.dtype == torch.bfloat16
     err = abs(_bf16_to_f64(got) - want)
     assert (err <= _tolerance(want, total, K, B.OUT_BF16)).all(), err.max()
+
+
+# the wider workgroups (more than 256 of 16 columns) along a longer K: a second stage of the ring (more than eight chunks of 256), its
+# refill (more than sixteen), whole and ragged chunks, a workgroup cut by the edge
+@pytest.mark.parametrize("M,K,N,tiles", [(1, 2080, 4097, False), (3, 2048, 8192, True), (3, 4640, 8192, False), (5, 4096, 4112, True),
+                                         (3, 8192, 8192, True), (1, 8224, 4128, False), (1, 16384, 4097, False),
+                                         (1, 28672, 4112, True)])
+def test_few_rows_against_wide_weights(M, K, N, tiles):
+    rng = np.random.default_rng(M * 7919 + N * 31 + K)
+    cb = rng.integers(0, 256, (N, K // 2), dtype=np.uint8)
+    sb = rng.integers(0x20, 0x48, (N // 16 if tiles else N, K // 16), dtype=np.uint8)
+    ab = np.float32(0.01)
+    bits = wl.bf16_bits(wl.make("c3", M, K))
+    aa = ref.tensor_scale(bits)
+    ca, sa, _ = ref.quantize(bits, aa)
+    want, total = ref.gemm(ca, sa, aa, cb, sb.repeat(16, axis=0) if tiles else sb, ab, want_abs=True)
+    print(f"few rows case M={M} K={K} N={N} tiles={tiles}", flush=True)
+    got = B.product_of_rows(wl.make("c3", M, K).cuda(), _dev(cb), _dev(sb), _alpha(ab), B.GEMM_B_TILE_SCALES if tiles else 0)
+    assert got is not None and got.shape == (M, N)
+    err = abs(_bf16_to_f64(got) - want)
+    assert (err <= _tolerance(want, total, K, B.OUT_BF16)).all(), err.max()
+
+
+def test_two_threads_with_different_sizes():
+    """One kernel, two sizes of LDS, two threads on streams of their own."""
+    qw = [L.quantize_weight(wl.make("c2", 5120, cols).cuda()) for cols in (256, 1792)]
+    xs = [wl.make("c1", rows, cols).cuda() for rows, cols in ((1, 256), (16, 1792))]
+    want = [L.fprop(x, w) for x, w in zip(xs, qw)]
+    torch.cuda.synchronize()
+    got = [[], []]
+
+    def calls(i):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            for _ in range(100):
+                got[i].append(L.fprop(xs[i], qw[i]))
+        s.synchronize()
+
+    threads = [threading.Thread(target=calls, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for i in range(2):
+        assert len(got[i]) == 100 and all(torch.equal(y, want[i]) for y in got[i]), i
 
 
 @pytest.mark.parametrize("N", [4096, 4097, 8192])
