@@ -11,6 +11,8 @@ from oracle import ref
 from paper_2512_02010_amd import binding as B
 from paper_2512_02010_amd import workloads as wl
 
+from . import _host_model as hm
+
 pytestmark = pytest.mark.gpu
 
 SR_SEED, RHT_SEED = wl.C5_SR_SEED, wl.C5_RHT_SEED
@@ -289,7 +291,7 @@ def test_block2d_both_packings_past_one_round_of_the_grid():
 @pytest.mark.parametrize("shape", [(16, 16), (16, 80), (272, 16), (32, 48), (64, 64)])
 def test_block2d_smallest_shapes_in_every_packing(shape):
     """One tile, one row of tiles, one column of tiles, and less than one of the kernel's
-    16 x 4-tile work units in either direction."""
+    work units of 4 x 4 tiles in either direction."""
     for layout in (B.ROWWISE, B.COLWISE, B.BOTH):
         check_case_2d(dict(name="c2", rows=shape[0], cols=shape[1], layout=layout, rounding=B.RTN,
                            select=B.SEL_46_MSE, f32=False), 9400, f"2d-small-{shape}-{layout}")
@@ -331,10 +333,21 @@ def check_case_2d(c, seed, tag):
 
 
 def test_seeded_sweep_of_block2d_shapes_and_options():
-    """Thirty drawn combinations of tile-grid shape (ragged against the kernel's 16 x 4-tile work
-    units), packing(s), rounding, rule and input type, each compared element by element."""
+    """Thirty drawn combinations of tile-grid shape (ragged against the kernel's work units, of 4 x 4 tiles at these
+    sizes), packing(s), rounding, rule and input type, each compared element by element."""
     for i, c in enumerate(_sweep_cases_2d(30, 4647)):
         check_case_2d(c, 9500 + i, f"2d-{i}")
+
+
+@pytest.mark.parametrize("rows,cols,unit_rows", [(2064, 2608, 8), (3344, 2640, 16)])
+@pytest.mark.parametrize("f32,rounding,select", [(False, B.RTN, B.SEL_46_MSE), (True, B.RTN, B.SEL_46_MAE),
+                                                 (False, B.SR, B.SEL_46_MSE), (True, B.SR_AFTER_RTN_SELECT, B.SEL_46_MSE)])
+def test_block2d_in_higher_units(rows, cols, unit_rows, f32, rounding, select):
+    """Units of 8 and of 16 tile rows, both ragged: one tile row and one or three tile columns more than whole ones."""
+    assert hm.tile_unit_rows(rows, cols, f32, torch.cuda.get_device_properties(0).multi_processor_count) == unit_rows
+    for layout in (B.BOTH, B.COLWISE):
+        check_case_2d(dict(name="c2", rows=rows, cols=cols, layout=layout, rounding=rounding, select=select, f32=f32), 9600,
+                      f"2d-units-{unit_rows}-{layout}")
 
 
 @pytest.mark.parametrize("select", [B.SEL_46_MSE, B.SEL_46_MAE])
