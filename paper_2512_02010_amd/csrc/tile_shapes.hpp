@@ -37,16 +37,22 @@ inline TileMap tile_map(int64_t rows, int64_t cols) {
   for (int log = 7; log >= 0; --log) {                 // 8 x 16, 8 x 8, 4 x 8, 4 x 4, ... 1 x 2, 1 x 1
     const int log_wide = log >= 6 ? 3 : log / 2, log_high = log - log_wide;
     const int64_t wide = (int64_t)1 << log_wide, high = (int64_t)1 << log_high;
-    if (((nt_c + wide - 1) >> log_wide) * ((nt_r + high - 1) >> log_high) > 64)
-      return TileMap{(uint32_t)(nt_c < wide ? nt_c : wide), (uint32_t)(nt_r < high ? nt_r : high), 0u};   // more than eight turns even out
-    int64_t tiles[8] = {}, most = 0;                   // of each die
-    uint32_t die = 0;
-    for (int64_t down = nt_r; down > 0; down -= high)
-      for (int64_t right = nt_c; right > 0; right -= wide)
-        tiles[die++ & 7u] += (right < wide ? right : wide) * (down < high ? down : high);
+    const int64_t across = (nt_c + wide - 1) >> log_wide, down = (nt_r + high - 1) >> log_high;
+    const TileMap map{(uint32_t)(nt_c < wide ? nt_c : wide), (uint32_t)(nt_r < high ? nt_r : high), 0u};
+    if (log == 7 && across * down > 64) return map;    // more than eight turns of the largest
+    // The tiles of each die: it has the super-tiles of row i and column j with (i across + j) % 8, so what counts is the
+    // tiles along each axis in super-tiles of the same remainder.
+    int64_t tall[8], broad[8], tiles[8] = {}, most = 0;
+    for (int k = 0; k < 8; ++k) {
+      tall[k] = ((down + 7 - k) >> 3 << log_high) - (((down - 1) & 7) == k ? (down << log_high) - nt_r : 0);
+      broad[k] = ((across + 7 - k) >> 3 << log_wide) - (((across - 1) & 7) == k ? (across << log_wide) - nt_c : 0);
+    }
+    const int rows_used = down < 8 ? (int)down : 8, cols_used = across < 8 ? (int)across : 8;
+    for (int i = 0; i < rows_used; ++i)
+      for (int j = 0; j < cols_used; ++j) tiles[(i * (int)(across & 7) + j) & 7] += tall[i] * broad[j];
     for (int64_t t : tiles) most = t > most ? t : most;
     if (most < best_most) {
-      best = TileMap{(uint32_t)(nt_c < wide ? nt_c : wide), (uint32_t)(nt_r < high ? nt_r : high), 0u};
+      best = map;
       best_most = most;
     }
     if (most <= 32 || most * 32 <= nt_r * nt_c * 5) break;      // within a quarter of an eighth
