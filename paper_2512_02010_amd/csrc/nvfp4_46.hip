@@ -759,20 +759,22 @@ NV_DEV void quantize_tile(
     // the lane's own row blocks, taken back from LDS one at a time (keeps the register
     // footprint of the quantizer to a single block)
     const int64_t nb_per_row = cols / 16;
+    const int blocks = cols - c0 < TC ? (int)(cols - c0) / 16 : kRowBlocksPerTileRow;
 #pragma unroll 1
     for (int j = 0; j < kRowBlocksPerLane; ++j) {
       const int unit = t + j * kThreads;
-      const int row = unit / kRowBlocksPerTileRow, rbk = unit % kRowBlocksPerTileRow;
+      const int row = unit / kRowBlocksPerTileRow, own = unit % kRowBlocksPerTileRow;
+      const int rbk = own < blocks ? own : blocks - 1;      // outside the tensor: the last block again, as in phase 2
       const int64_t gr = r0 + row, gc = c0 + rbk * 16;
-      if (gr < rows && gc < cols) {
+      if (gr < rows) {
         float v[16];
         const int64_t k = gr * nb_per_row + (gc >> 4);
         // the lane's block out of the tile, and its random words (WANT_ROW is for codes: words are in LDS)
         auto block = [&](float (&w)[16]) {
-          const uint4 *own = reinterpret_cast<const uint4 *>(tile) + unit * Raw::kPieces;
+          const uint4 *at = reinterpret_cast<const uint4 *>(tile) + (row * kRowBlocksPerTileRow + rbk) * Raw::kPieces;
           Raw mine;
 #pragma unroll
-          for (int q = 0; q < Raw::kPieces; ++q) mine.w[q] = own[q];
+          for (int q = 0; q < Raw::kPieces; ++q) mine.w[q] = at[q];
           unpack16(mine, w);
         };
         constexpr int kStep = 16;
@@ -800,9 +802,11 @@ NV_DEV void quantize_tile(
         };
         block(v);
         BlockResult r = quantize_block<ROUNDING, SELECT>(v, words_on_demand<kStep>(some), sc, tab, take);
-        reinterpret_cast<uint2 *>(codes_row)[k] = make_uint2(r.lo, r.hi);
-        scales_row[k] = (uint8_t)r.scale;
-        if (choice_row) choice_row[k] = (uint8_t)r.four;
+        if (own == rbk) {
+          reinterpret_cast<uint2 *>(codes_row)[k] = make_uint2(r.lo, r.hi);
+          scales_row[k] = (uint8_t)r.scale;
+          if (choice_row) choice_row[k] = (uint8_t)r.four;
+        }
       }
     }
   }
@@ -811,13 +815,19 @@ NV_DEV void quantize_tile(
   // block) unit is read and, for the fake-quant output, rewritten in place by its owner
   // lane only, so no barrier is needed inside this phase.
   static_assert(kColPairs == 64, "a wave's lanes are the column pairs of one row block");
+  const int pairs = cols - c0 < TC ? (int)(cols - c0) / 2 : kColPairs;
 #pragma unroll 1
   for (int j = 0; j < kPairUnitsPerLane; ++j) {
     // (the row block is the wave's: what follows from it stays on the scalar unit)
-    const int cp = t % kColPairs, rb = __builtin_amdgcn_readfirstlane(t / kColPairs) + j * (kThreads / kColPairs);
+    const int own = t % kColPairs, rb = __builtin_amdgcn_readfirstlane(t / kColPairs) + j * (kThreads / kColPairs);
     const int64_t gr = r0 + rb * 16;              // first row of the block
+    if (gr >= rows) continue;
+    // A lane whose pair is outside the tensor (cols is even, so it is in or out together) does the last one inside over again
+    // and leaves it in its own place, which nobody reads: a wave of 8 lanes, a tile's last 16 columns, takes nearly twice
+    // as long as one of 12 or of 64 (BF16, codes with the transform and SR, us: 64 x 16 9.2, 64 x 24 6.1; the lanes all
+    // at work 64 x 16 6.1).
+    const int cp = own < pairs ? own : pairs - 1;
     const int64_t gc = c0 + 2 * cp;               // even column of the pair
-    if (gr >= rows || gc >= cols) continue;       // (cols is even, so the pair is in or out together)
     float va[16], vb[16];
     // the lane's two column blocks (transformed) out of the tile or memory
     auto take = [&](float (&wa)[16], float (&wb)[16]) {
@@ -902,7 +912,7 @@ NV_DEV void quantize_tile(
       rbk = quantize_block<ROUNDING, SELECT>(vb, words_of(1), sc, tab, second);
     }
     if (OUT == kOutCodes) {
-      const int ia = (2 * cp) * kColBlockRows + rb, ib = ia + kColBlockRows;
+      const int ia = (2 * own) * kColBlockRows + rb, ib = ia + kColBlockRows;
       stage_codes[ia] = make_uint2(ra.lo, ra.hi);
       stage_codes[ib] = make_uint2(rbk.lo, rbk.hi);
       stage_scale[ia] = (uint8_t)ra.scale;
@@ -929,7 +939,7 @@ NV_DEV void quantize_tile(
       // the BF16 pair takes the first word of the pair's slot
 #pragma unroll
       for (int i = 0; i < 16; ++i)
-        tile[((rb * 16 + i) * kColPairs + cp) * kXW] = pack_bf16x2(Da[i], Db[i]);
+        tile[((rb * 16 + i) * kColPairs + own) * kXW] = pack_bf16x2(Da[i], Db[i]);
     }
   }
   __syncthreads();

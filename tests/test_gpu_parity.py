@@ -339,6 +339,19 @@ def test_seeded_sweep_of_block2d_shapes_and_options():
         check_case_2d(c, 9500 + i, f"2d-{i}")
 
 
+# tiles of 64 x 128 whose last has 8, 16, 24, 112 and 120 columns, alone and beside whole ones, with whole and ragged rows
+@pytest.mark.parametrize("rows,cols", [(64, 8), (64, 16), (80, 136), (16, 144), (128, 24), (144, 112), (48, 248)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rounding,select", [(B.RTN, B.SEL_46_MSE), (B.SR, B.SEL_46_MSE), (B.SR, B.SEL_46_MAE),
+                                             (B.SR_AFTER_RTN_SELECT, B.SEL_46_MSE)])
+def test_last_columns_of_a_tile(rows, cols, dtype, rounding, select):
+    """Lanes past the last column do its work over again and keep it to themselves."""
+    x = wl.make("c5", rows, cols, dtype=dtype)
+    for layout, rht in ((B.COLWISE, 0), (B.COLWISE, 1), (B.BOTH, 0)):
+        if layout == B.COLWISE or cols % 16 == 0:
+            check_case(x, layout=layout, rounding=rounding, select=select, rht=rht, tag=f"few-columns-{layout}-{rht}")
+
+
 @pytest.mark.parametrize("rows,cols,unit_rows", [(2064, 2608, 8), (3344, 2640, 16)])
 @pytest.mark.parametrize("f32,rounding,select", [(False, B.RTN, B.SEL_46_MSE), (True, B.RTN, B.SEL_46_MAE),
                                                  (False, B.SR, B.SEL_46_MSE), (True, B.SR_AFTER_RTN_SELECT, B.SEL_46_MSE)])
