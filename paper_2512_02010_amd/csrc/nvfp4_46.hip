@@ -1369,13 +1369,17 @@ __global__ void k_dbg_philox(const uint32_t *ctr, uint32_t k0, uint32_t k1, int6
 
 // ---------------------------------------------------------------- launchers
 
-// Compute units of the device that is current for the calling thread, asked for on every
-// call (the library keeps no state, and two devices of one process may differ).
+constexpr int kMaxDevices = 64;
+// Compute units of the device that is current for the calling thread (two devices of one process may differ), which does not
+// change: asked for in a device's first calls (once for each part that the library is built of) and kept; threads that ask at the
+// same time are told the same.
 static int compute_units() {
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-    cus = 256;
+  static std::atomic<int> known[kMaxDevices];
+  int dev = -1, cus = 0;
+  const bool counted = hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices;
+  if (counted && (cus = known[dev].load(std::memory_order_relaxed)) > 0) return cus;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
+  if (counted) known[dev].store(cus, std::memory_order_relaxed);
   return cus;
 }
 
@@ -1697,7 +1701,6 @@ static int check_workspace(const void *workspace, size_t bytes) {
 // and that pointer is what kernels get (threads that look it up at the same time find the same).
 static __device__ __align__(256) uint32_t scratch[2 * kScratchWords];
 static_assert(kScratchWords * sizeof(uint32_t) == NVFP4_46_TENSOR_SCALE_WS_BYTES, "header and kernels agree on the scratch size");
-constexpr int kMaxDevices = 64;
 static std::atomic<uint32_t *> g_scratch_ptr[kMaxDevices];   // per device; nullptr until that device's first call
 
 static uint32_t *scratch_of_device() {

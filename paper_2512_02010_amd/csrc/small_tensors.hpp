@@ -23,15 +23,16 @@ namespace nvfp4_46 {
 // in the cache (us per call among others from Python, BF16: 512 KiB 6.5 / 11.1, 768 KiB 8.9 / 8.7 to 11.4, 896 KiB
 // 9.9 / 8.8 to 12, 1 MiB 11.2 / 11.2; first read from memory 10.7 / 9.5, 15.2 / 8.5, 17.3 / 10.1 and 19.8 / 9.9;
 // programs that replay graphs have a workspace).
-// On the default stream, without a workspace, it replaces one launch on lent words, which costs the host 0.4 us more (the
-// device is asked for, and its compute units).  Such calls come one by one and have others after them that the host is busy
+// On the default stream, without a workspace, it replaces one launch on lent words, which costs the host 0.2 to 0.5 us more.
+// Such calls come one by one and have others after them that the host is busy
 // with while the one workgroup reads, so what counts is the whole pass (us among others from Python, BF16, one workgroup /
-// lent words; fp32 is within 0.3 of it):
+// lent words; fp32 is within 0.5 of it):
 //   KiB     scale, codes, values    scale, fake-quant   scale, both orientations   scale alone
-//   256     15.7 / 16.1             8.9 / 9.5           12.1 / 12.5                4.3 / 4.7
-//   512     15.7 / 16.0             9.3 / 9.6           12.2 / 12.6                5.3 / 4.7
-//   640     15.5 / 15.9             9.9 / 9.4           12.1 / 12.5                6.2 / 4.7
-//   768     15.6 / 16.0             10.8 / 9.4          13.3 / 12.6                7.1 / 4.7
+//   256     15.2 / 15.7             9.1 / 9.3           12.0 / 12.2                4.2 / 4.6
+//   384     15.2 / 15.7             9.3 / 9.3           12.0 / 12.2                4.5 / 4.5
+//   512     15.2 / 15.8             9.7 / 9.1           11.9 / 12.2                5.5 / 4.6
+//   640     15.1 / 15.5             10.0 / 9.3          12.1 / 12.4                6.4 / 4.6
+//   768     15.0 / 15.4             11.3 / 9.3          12.9 / 12.2                7.2 / 4.5
 enum class ScratchWords { kNone, kLent, kWorkspace };
 constexpr bool scale_in_one_workgroup(int64_t bytes, ScratchWords words) {
   return bytes <= (int64_t)(words == ScratchWords::kWorkspace ? 128 : words == ScratchWords::kLent ? 512 : 768) << 10;

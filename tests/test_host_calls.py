@@ -53,6 +53,7 @@ def on(stream):
     assert L.nvfp4_46_scale_quantize(P, params(4096, 4096, layout=2, rht=1), P, P, 4352, None, None, P, P, None, None, stream) == 0
     assert L.nvfp4_46_wgrad_operands(P, P, 16384, 6144, 256, 0, 1, 2, P, P, P, P, P, P, P, 4352, stream) == 0    # one after the other
     return [c[:4] for c in calls()]
+on(None)                                      # (the first calls ask for the compute units)
 result = on(None), on(1 << 12)
 """)
     assert default == other and len(default) >= 6
@@ -94,6 +95,19 @@ for call in (lambda: q(), lambda: q(rounding=1, rht=1), lambda: q(layout=2), lam
 """)
     for kinds in calls:
         assert kinds.count("device_attribute") <= 1 <= kinds.count("launch"), kinds
+
+
+def test_compute_units_are_kept_for_a_device():
+    """They do not change; before they were kept every call asked for them."""
+    kinds = _hip_calls.run("""
+for _ in range(5):
+    assert L.nvfp4_46_tensor_scale(P, params(4096, 4096), P, None) == 0
+    assert L.nvfp4_46_quantize(P, params(4096, 4096), P, P, P, None, None, None, None, None) == 0
+    assert L.nvfp4_46_quantize(P, params(4096, 4096, layout=3, block2d=1), P, P, P, P, P, None, None, None) == 0
+    assert L.nvfp4_46_dequantize(P, P, P, 4096, 4096, 1, P, None) == 0
+result = [c[0] for c in calls()]
+""")
+    assert kinds.count("launch") == 20 and kinds.count("device_attribute") <= 4, kinds
 
 
 def test_rounds_of_the_rowwise_transform():
