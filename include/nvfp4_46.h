@@ -9,9 +9,10 @@
  *
  * General conventions (all entry points)
  *   - Every data pointer is a DEVICE pointer owned by the caller.  The library
- *     allocates no memory and keeps no state between calls (the one exception is a
- *     fixed array of scratch words, for nvfp4_46_tensor_scale_static and, apart from those,
- *     for tensor scales on the default stream; both are zero between calls).
+ *     allocates no memory and keeps no state between calls, except for two fixed arrays of
+ *     scratch words per device, one for nvfp4_46_tensor_scale_static and one for tensor
+ *     scales on the default stream (zero between calls), their addresses, and each
+ *     device's number of compute units.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     Work is enqueued on it and the call returns without synchronising; a call
  *     that fails validation enqueues nothing.

@@ -67,9 +67,10 @@ inline int tile_grid(int64_t rows, int64_t cols, TileMap m) {
   return (int)(8 * ((supers + 7) / 8) * m.sx * m.sy);
 }
 
-// Both packings of 16x16 tiles (k_block2d) are made in units of 4, 8 or 16 tile rows x 4 tile columns.  A unit's steps of 4 x 4 tiles follow each other in its workgroup, a high unit stores longer runs.
-// High units pay where they fill the chip: what counts is how many of them there are for the four workgroups of a compute
-// unit that run at once, a turn.  Tensor scale and codes, us in a replayed graph, 16 / 8 / 4 tile rows:
+// Both packings of 16x16 tiles (k_block2d) are made in units of 4, 8 or 16 tile rows x 4 tile columns.  A unit's steps
+// of 4 x 4 tiles follow each other in its workgroup, a high unit stores longer runs.  High units pay where they fill the
+// chip: what counts is how many of them there are for the four workgroups of a compute unit that run at once, a turn.
+// Tensor scale and codes, us in a replayed graph, 16 / 8 / 4 tile rows:
 //                       fp32                    BF16
 //   512 x 512         12.5 /  9.6 /  8.0     12.1 /  9.3 /  7.8     64 units of 4
 //   2048 x 2048       15.0 / 12.3 / 11.6     13.1 / 10.6 /  9.8     1024 (a turn)

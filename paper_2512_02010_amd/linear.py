@@ -13,13 +13,17 @@ packing for W and for W^T with identical codes and scales.  Stochastic rounding 
 the gradient operands, the random Hadamard transform on both operands of WGRAD (same sign
 vector along the contraction axis, so it cancels in the product).
 
-On the current stream (``stream`` left out) a product is one call into the library's Python module, which runs the
-same kernels with the operands it quantizes in a buffer of its own; on any other stream, and for operands that are not plain
-contiguous tensors, it is those calls one by one.
+On the current stream (``stream`` left out) a product is one call into the library's Python module, with the operands it
+quantizes in a buffer of its own: codes and scales are those of the calls one by one, and so are the products, except that
+``fprop`` of few rows (``few_rows_in_one_launch`` in csrc/gemm_shapes.hpp) finds scale, codes and product in one launch whose waves share K
+another way.  There the fp32 sums are added in another order than ``nvfp4_46_gemm`` adds them, and an output can be the
+neighbouring BF16 value of the one that the same call with ``stream=`` returns.  On any other stream, and for operands that are
+not plain contiguous tensors, a product is those calls one by one.
 
-Every function takes an optional ``workspace`` (``binding.new_workspace()``): with it the five
-tensor scales of a step are one launch each (``nvfp4_46_tensor_scale_ws``) instead of three.
-One workspace serves all calls issued on one stream.
+Every function takes an optional ``workspace`` (``binding.new_workspace()``).  With it, and on the default stream also without,
+a tensor scale is one launch; on another stream without a workspace it is three.  ``wgrad`` on the current stream finds the
+scales of its two operands in one launch and their codes in a second where such scratch words are at hand and the operands
+are not too large for it (``nvfp4_46_wgrad_operands`` in csrc/nvfp4_46.hip).  One workspace serves all calls issued on one stream.
 """
 from __future__ import annotations
 
