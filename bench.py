@@ -44,7 +44,7 @@ VALU_INSTS_PER_BLOCK_46 = 14430273.0 / (4194304.0 / 64.0)
 # the same for the kernels of c4 (both orientations, per 16 elements;
 # profiles/c4_both_and_fake_quant_counters.txt) and c5 (Hadamard + stochastic rounding;
 # profiles/c5_rowwise_rht_sr_counters.txt)
-VALU_INSTS_PER_BLOCK_C4 = 30962205.0 / (4194304.0 / 64.0)
+VALU_INSTS_PER_BLOCK_C4 = 31322653.0 / (4194304.0 / 64.0)
 VALU_INSTS_PER_BLOCK_C5 = 45377092.0 / (4194304.0 / 64.0)
 # HBM bytes per element of the same kernel from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, scaled
 # by a plain copy's readings (same file): (65665.8 * 2.000 + 36891.5 * 1.000) KiB per 67,108,864
